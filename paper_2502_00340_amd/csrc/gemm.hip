@@ -746,6 +746,9 @@ __device__ __forceinline__ void gemm_bf16_block(const GemmArgs& g, unsigned char
             // tiles of 256x192, all of one kind: block b takes tiles b, b + gridDim.x, ...
             const int tiles_n192 = (g.N + 191) / 192, n_items = tiles_m * tiles_n192;
             int w = (int)blockIdx.x;
+            // with a device-side count there are as many blocks as CUs, whatever the number of tiles: a block
+            // past the last tile would compute another block's tile a second time (and with beta = 1 add to it twice)
+            if (w >= n_items) return;
             auto tile = [&](int w, TileRef& t) __attribute__((always_inline)) {
                 int bm, bn;
                 tile_coords(xcd_order(w, n_items), tiles_m, tiles_n192, bm, bn);

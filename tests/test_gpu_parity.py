@@ -759,3 +759,35 @@ def test_layer_lora_nothing_kept():
     assert n == 0
     for k in LORA_NAMES:
         assert not bool(plan.grads[k].float().abs().max() > 0), k
+
+
+def test_layer_lora_same_result_twice():
+    """2572 kept rows of a 4096-wide layer: the second dh1 product (beta = 1) runs on 242 tiles of 256x192 with a
+    device-side count, i.e. fewer tiles than blocks.  Every tile has to be added exactly once: the call gives the
+    same bits every time, and those of a call whose launch has no spare block (the known count as its bound)."""
+    shape = WL.LayerShape("lora_spare_blocks", B=4, S=732, H=4096, Hq=4, Hkv=1, d=128, F=256, dtype="bf16")
+    say("layer lora, fewer tiles than blocks")
+    gen = torch.Generator(device=DEV).manual_seed(61)
+    rn = lambda *s, std=1.0: (torch.randn(s, generator=gen, device=DEV) * std).to(torch.bfloat16)
+    T, H, F, Nq, Nkv, R = shape.T, shape.H, shape.F, shape.Nq, shape.Nkv, 16
+    sv = dict(x=rn(T, H), r=rn(T, H), q=rn(T, Nq), k=rn(T, Nkv), v=rn(T, Nkv), attn_out=rn(T, Nq), gate=rn(T, F), up=rn(T, F),
+              lse=torch.full((shape.B, shape.Hq, shape.S), 6.0, device=DEV))
+    W = {n: rn(i, o, std=0.02) for n, (i, o) in dict(wq=(H, Nq), wk=(H, Nkv), wv=(H, Nkv), wo=(Nq, H), wg=(H, F), wu=(H, F),
+                                                    wd=(F, H)).items()}
+    W.update(g1=rn(H) * 0.02 + 1.0, g2=rn(H) * 0.02 + 1.0)
+    lo = {"scale": 2.0}
+    for p, (i, o) in dict(q=(H, Nq), k=(H, Nkv), v=(H, Nkv), o=(Nq, H)).items():
+        lo["a" + p], lo["b" + p] = rn(i, R, std=0.02), rn(R, o, std=0.02)
+    mask = torch.zeros((shape.B, shape.S), dtype=torch.uint8, device=DEV)
+    mask[:, :643] = 1
+    dy = rn(T, H)
+    plan = Bn.LoraBackward(Bn.make_desc(shape.B, shape.S, H, shape.Hq, shape.Hkv, shape.d, F, "bf16"), R, device=DEV)
+    first = None
+    for it in range(6):
+        n = plan.run(sv, W, lo, dy, mask)
+        assert n == 4 * 643
+        got = {k: v.clone() for k, v in plan.grads.items()}
+        got["dx"] = got["dx"][:n]
+        first = first or got
+        for k in got:
+            assert torch.equal(got[k], first[k]), (it, k)
