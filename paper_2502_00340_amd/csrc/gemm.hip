@@ -159,8 +159,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4_t;
 typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
 typedef __attribute__((address_space(3))) s16x4_t* lds_s16x4_ptr;
 
-static constexpr int GEMM_STAGES = 4;
-static constexpr int GEMM_STAGE_BYTES = 32768;
+static constexpr int GEMM_RING = 128 * 1024;        // the operand stages; their number and size depend on the tile (gemm_tiles)
 static constexpr int GEMM_SMEM = 160 * 1024;    // the whole LDS of a CU: four operand stages; the C tile staging of the epilogue needs 132 KB
 
 // Position l of a block in the logical order of its group of n blocks: XCD x (block id
@@ -224,7 +223,13 @@ template <int MODE, int TM, int TN, bool SPLIT, bool CF32, typename Next>
 __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, const int K0x, const TileRef first,
                                            Next next_tile, unsigned char* smem,
                                            const int kbeg = 0, const int kend = 0, float* part_out = nullptr) {
-    constexpr int BM = 64 * TM, BN = 64 * TN, KB = 32, STAGE = GEMM_STAGE_BYTES;
+    // Ring of operand stages: four of 32 KB, i.e. two pairs of K-steps, or for the 128x128 tile eight of 16 KB = four
+    // pairs.  A pair of the small tile is 32 MFMAs (0.22 us) per wave, and with one pair of lookahead a block waited
+    // out most of a load's latency per pair; three pairs of lookahead cover it.
+    constexpr bool DEEP = TM == 2 && TN == 2;
+    constexpr int BM = 64 * TM, BN = 64 * TN, KB = 32, STAGE = DEEP ? 16384 : 32768;
+    constexpr int NSTG = GEMM_RING / STAGE, NPR = NSTG / 2;     // stages and pairs in the ring
+    constexpr int SWIN = 65536 / STAGE;                 // stages within reach of one LDS base register
     constexpr int A_BYTES = BM * KB * 2;                // B tile follows the A tile inside a stage
     constexpr int NU = TM + TN;                         // 1 KB wave-loads per wave per K-step: TM for A, TN for B
     constexpr int FM = 2 * TM, FN = 2 * TN;             // 16-row fragments of the wave tile along M and N
@@ -341,7 +346,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         if (k0 >= Kseg) {
             k0 = 0;
             ++seg;
-            open_segment(seg);
+            if (!DEEP || seg < g.nseg) open_segment(seg);
+            else { Kseg = 0; pair_inside = false; }     // past the last segment: only the range of k matters any more
         }
     };
 
@@ -375,8 +381,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
 
     // ---- LDS -> fragments.  A fragment is 16 rows x 32 k (one K-step): lane l holds row l%16,
     // k = 8*(l/16) .. +7.  An LDS address is a per-lane base register that never changes plus a
-    // compile-time constant (stage, fragment) in the instruction's 16-bit offset field; stages 2
-    // and 3 lie past that field's reach from the base of stage 0 and get base registers of their own.
+    // compile-time constant (stage, fragment) in the instruction's 16-bit offset field; the upper half of
+    // the ring lies past that field's reach from the base of stage 0 and has base registers of its own.
     typedef __attribute__((address_space(3))) unsigned char* lds_u8_ptr;
     typedef const __attribute__((address_space(3))) u32x4_t* lds_u32x4_cptr;
     constexpr int NBASE = MODE == 0 ? 2 : NU;       // NT: A, B; TN: one per 32-row block (the swizzle mixes the block in)
@@ -390,7 +396,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
                 const int wrow = ab == 0 ? wm * (32 * TM) : wn * (32 * TN);
                 const unsigned v = s0 + (ab == 0 ? 0 : A_BYTES) + (wrow + l16) * 64 + ((g4 ^ nt_sw) << 4);
                 fbase[ab][0] = v;
-                fbase[ab][1] = v + 2 * STAGE;
+                fbase[ab][1] = v + 65536;
             }
         } else {
 #pragma unroll
@@ -404,7 +410,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
                 const int sw = (kl & 3) << 2;                       // the same for k and k + 4
                 const unsigned v = s0 + (isA ? 0 : A_BYTES) + kl * W2 + ((lc ^ sw) << 4) + (lane & 1) * 8;
                 fbase[u][0] = v;
-                fbase[u][1] = v + 2 * STAGE;
+                fbase[u][1] = v + 65536;
             }
         }
     }
@@ -415,7 +421,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         constexpr int s = decltype(S)::value, fr = decltype(F)::value, buf = decltype(BUF)::value;
         constexpr bool isA = fr < FM;
         constexpr int f = isA ? fr : fr - FM;
-        constexpr int win = s >> 1, soff = (s & 1) * STAGE;
+        constexpr int win = s / SWIN, soff = (s % SWIN) * STAGE;
         bf16x8_t v;
         if (MODE == 0) {
             const lds_u8_ptr p = reinterpret_cast<lds_u8_ptr>(fbase[isA ? 0 : 1][win]);
@@ -445,7 +451,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
     auto substep = [&](auto ST, auto T) __attribute__((always_inline)) {
         constexpr int st = decltype(ST)::value, t = decltype(T)::value;
         constexpr int ks = t / TM, a = t % TM;
-        constexpr int st1 = st + 1, st2 = (st + 2) & 3;
+        constexpr int st1 = st + 1, st2 = (st + 2) % NSTG;          // st2: the next pair
+        constexpr int stp = (st + NSTG - 2) % NSTG;                 // the pair before
         constexpr bool last = t == 2 * TM - 1;
         constexpr int cur = st + ks;                                // stage of this K-step
         constexpr int nxt = ks == 0 ? st1 : st2;                    // stage of the next K-step
@@ -457,7 +464,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         // wave-loads of this sub-step: group 0 (last sub-step) or group t + 1 (t < TM - 1)
         constexpr int grp = last ? 0 : (t < NG - 1 ? t + 1 : -1);
         constexpr int e_lo = grp < 0 ? 0 : ((grp * NU) / NG) * 2, e_hi = grp < 0 ? 0 : (((grp + 1) * NU) / NG) * 2;
-        constexpr int d0 = last ? st : st2, d1 = d0 + 1;
+        constexpr int d0 = last ? st : stp, d1 = d0 + 1;
         static_for<NQ>([&](auto Q) __attribute__((always_inline)) {
             constexpr int q = decltype(Q)::value;
             static_for<NR>([&](auto R) __attribute__((always_inline)) {
@@ -494,9 +501,9 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
             dma_one(ic<(e & 1) ? decltype(D1)::value : decltype(D0)::value>{}, ic<(e >> 1)>{}, ic<(e & 1)>{});
         });
     };
-    // One pair of K-steps s, s+1 in stages ST, ST+1 of the ring of four; the next pair lies in the
-    // other two stages, and the loads of the pair after that go back into ST, ST+1 once the barrier
-    // has retired them.  The loop body is two pairs, so every stage is a compile-time constant.
+    // One pair of K-steps s, s+1 in stages ST, ST+1 of the ring; the next NPR - 1 pairs lie in the
+    // other stages, and the loads of the pair after those go back into ST, ST+1 once the barrier
+    // has retired them.  The loop body is NPR pairs, so every stage is a compile-time constant.
     // The loads of a pair are issued in NG groups, the first right after the barrier that frees their
     // stages, which keeps the burst that the load path sees short; the last group still has more
     // than half a pair to land before the next barrier.
@@ -505,7 +512,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
             constexpr int t = decltype(T)::value;
             if constexpr (t == 2 * TM - 1) {
                 prepare_pair();
-                wait_vmcnt<0>();        // K-steps s+2, s+3 have landed (nothing else is in flight)
+                wait_vmcnt<(NPR - 2) * 2 * NU>();       // K-steps s+2, s+3 have landed; later pairs (loads only) may be in flight
                 lds_barrier();          // ... and every wave is done with stages ST and ST+1
             }
             substep(ST, T);
@@ -517,7 +524,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
     const int npairs = SPLIT ? (kend - kbeg + 2 * KB - 1) / (2 * KB)
                              : (K0x + 2 * KB - 1) / (2 * KB) + (g.K[1] + 2 * KB - 1) / (2 * KB) +
                                    (g.K[2] + 2 * KB - 1) / (2 * KB);
-    // prologue of tile ld: K-steps 0, 1 and the first group of the loads of K-steps 2, 3
+    // prologue of tile ld: the first NPR - 1 pairs and the first group of the loads of the pair behind them
     auto start_tile = [&]() __attribute__((always_inline)) {
         seg = 0;
         k0 = 0;
@@ -526,13 +533,16 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
             k0 = kbeg;
             Kseg = kend;
         }
-        issue_pair(ic<0>{}, ic<1>{}, ic<0>{});
-        advance_pair();
-        issue_pair(ic<2>{}, ic<3>{}, ic<1>{});      // the loop's first sub-steps issue the other groups
+        static_for<NPR - 1>([&](auto P) __attribute__((always_inline)) {
+            constexpr int p = decltype(P)::value;
+            issue_pair(ic<2 * p>{}, ic<2 * p + 1>{}, ic<0>{});
+            advance_pair();
+        });
+        issue_pair(ic<NSTG - 2>{}, ic<NSTG - 1>{}, ic<1>{});        // the loop's first sub-steps issue the other groups
     };
     constexpr bool OVERLAP = !SPLIT && !CF32;       // the epilogue leaves the operand stages alone
     if (npairs > 0) start_tile();
-    for (;;) {
+    for (bool first_tile = true;; first_tile = false) {
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -540,19 +550,33 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
 #pragma unroll
                 for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
         if (npairs > 0) {
-            // K-steps 0 and 1 have landed.  Everything is waited for, the previous tile's stores
+            // K-steps 0 and 1 have landed.  Behind a previous tile everything is waited for, its stores
             // included: loads and stores share the counter and retire out of order with respect
             // to each other, so a partial count would say nothing about the loads.
-            wait_vmcnt<0>();
+            if (DEEP && first_tile) wait_vmcnt<(NPR - 2) * 2 * NU + (NU / NG) * 2>();
+            else wait_vmcnt<0>();
             lds_barrier();
             frag_one(ic<0>{}, ic<0>{}, ic<0>{});
             static_for<FN>([&](auto J) __attribute__((always_inline)) { frag_one(ic<0>{}, ic<FM + decltype(J)::value>{}, ic<0>{}); });
             frag_one(ic<0>{}, ic<1>{}, ic<0>{});
             // two pairs per iteration; an odd count runs one pair of zero K-steps (loads past the last
             // segment return zeros)
-            for (int p = 0; p < npairs; p += 2) {
-                pair_body(ic<0>{});
-                pair_body(ic<2>{});
+            if constexpr (DEEP) {       // short contractions are the rule here: leave after the last pair
+                for (int p = npairs;;) {
+                    pair_body(ic<0>{});
+                    if (--p <= 0) break;
+                    pair_body(ic<2>{});
+                    if (--p <= 0) break;
+                    pair_body(ic<4>{});
+                    if (--p <= 0) break;
+                    pair_body(ic<6>{});
+                    if (--p <= 0) break;
+                }
+            } else {
+                for (int p = 0; p < npairs; p += 2) {
+                    pair_body(ic<0>{});
+                    pair_body(ic<2>{});
+                }
             }
             wait_vmcnt<0>();
             // The MFMAs are inline assembly (see substep), so the compiler does not know that their
@@ -659,7 +683,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         constexpr int RBY = 64 * (TN == 3 ? 4 : TN);
         constexpr int CPR = RBY / 16, RPP = 64 / CPR;       // 16-byte chunks per row, rows per pass of the wave
         constexpr int NP = 32 / RPP, NV = CPR / RPP;        // passes per 32 rows; distinct swizzle phases
-        unsigned char* stg = smem + GEMM_STAGES * STAGE + wave * 8192;
+        unsigned char* stg = smem + GEMM_RING + wave * 8192;
         const __amdgpu_buffer_rsrc_t rc =
             __builtin_amdgcn_make_buffer_rsrc(ep.C, 0, (int)((int64_t)Mx * ep.N * 2), 0x00020000);
         const float beta = g.beta;

@@ -124,6 +124,22 @@ def test_linear_bwd_reduced(dtype, n_kept, fin, fout):
     assert np.max(np.abs(Hn.to_np(dw) - rdw)) <= tol_abs * max(1.0, np.max(np.abs(rdw)))
 
 
+@pytest.mark.parametrize("k", [8, 64, 72, 128, 200, 256, 264, 320, 520, 584])
+def test_linear_small_tiles_short_contraction(k):
+    """Outputs of a few 128x128 tiles with contractions of one to ten 64-wide steps, whole and ragged: every position of
+    the ring of four steps as the last one.  Reference in fp64 on the GPU; one rounding to bf16 and fp32 sums of k terms
+    give 2^-9 relative to the value plus about k * 2^-24 * |terms|, far below the bounds used."""
+    gen = torch.Generator(device=DEV).manual_seed(k)
+    rn = lambda *s: torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16)
+    for n, fin, fout in ((k, 264, 136), (200, 136, k)):         # dW contracts over n, dX over out
+        x, dy, w = rn(n, fin), rn(n, fout), rn(fin, fout)
+        dx, dw = Bn.linear_bwd_reduced(x, dy, w)
+        rdx, rdw = dy.double() @ w.double().T, x.double().T @ dy.double()
+        for got, ref in ((dx, rdx), (dw, rdw)):
+            err = (got.double() - ref).abs()
+            assert bool((err <= ref.abs() * 2.0 ** -8 + 1e-4 * math.sqrt(k)).all()), (n, fin, fout, err.max().item())
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_linear_dw_accumulate_and_empty(dtype):
     say("linear accumulate/empty %s" % dtype)
