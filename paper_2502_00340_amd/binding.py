@@ -138,20 +138,25 @@ _dummy = {}
 
 
 def _ptr(t):
-    """Device pointer of a tensor; an empty tensor (no storage) maps to a small
-    dummy allocation so that "zero rows" is not mistaken for a NULL argument."""
+    """Device address of a tensor as a plain int (the declared argument types make it a pointer; a ctypes object of its
+    own would only cost time); an empty tensor (no storage) maps to a small dummy allocation so that "zero rows" is not
+    mistaken for a NULL argument."""
     if t is None:
         return None
     if t.numel() == 0:
         key = str(t.device)
         if key not in _dummy:
             _dummy[key] = torch.zeros(256, dtype=torch.uint8, device=t.device)
-        return C.c_void_p(_dummy[key].data_ptr())
-    return C.c_void_p(t.data_ptr())
+        return _dummy[key].data_ptr()
+    return t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Handle of the current device's current stream, read on every call.  The raw query costs 0.1 us where building a
+    torch.cuda.Stream object for it costs 2.8 us, a fifth of the smallest calls."""
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -186,7 +191,7 @@ def build_keep_index(mask: torch.Tensor, sync: bool = True):
     n_dev = torch.empty(1, dtype=torch.int32, device=dev)
     wsb = lib().cf_index_workspace_bytes(B * S)
     ws = torch.empty(wsb, dtype=torch.uint8, device=dev)
-    n_host = C.c_int32(-1)
+    n_host = C.c_int32(-1) if sync else None
     _check(lib().cf_build_keep_index(_ptr(mask), B, S, _ptr(idx), _ptr(cu), _ptr(n_dev),
                                      C.byref(n_host) if sync else None, _ptr(ws), wsb, _stream()),
            "cf_build_keep_index")
