@@ -3,6 +3,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <initializer_list>
 
 #include "common.h"
 
@@ -190,7 +191,7 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     const bool mg = G.main_grad != 0;
     auto dw_gemm = [&](const void* A, const void* B, void* C, int M, int Ncols) {
         GemmSeg s{A, B, N};
-        return launch_gemm(dt, 1, &s, 1, C, M, Ncols, mg ? 1.f : 0.f, st, 1.f, nullptr, 0, mg, nd);
+        return launch_gemm(dt, 1, &s, 1, C, M, Ncols, mg ? 1.f : 0.f, st, mg, nd);
     };
 
     if (N == 0) {   // nothing kept (known to the host): every gradient is zero, dx has no rows
@@ -209,8 +210,7 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     void* d_act = w.bufF1;
     {   // [N,F] = [N,H] x [F,H]^T
         GemmSeg s{dy, W.wd, H};
-        CF_HIP(launch_gemm(dt, 0, &s, 1, d_act, N, F, 0.f, st, 1.f, nullptr, 0, false, nd,
-                           dy_is_full ? idx : nullptr, dy_is_full ? T : 0));
+        CF_HIP(launch_gemm(dt, 0, &s, 1, d_act, N, F, 0.f, st, false, nd, dy_is_full ? idx : nullptr, dy_is_full ? T : 0));
     }
     void* d_gate = w.bufF1;   // in place over d_act
     void* d_up = w.bufF0;
@@ -223,7 +223,7 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     void* dh2 = w.bufHb;
     {   // dh2 = d_gate*Wg^T + d_up*Wu^T   [N,H], contraction over F twice
         GemmSeg s[2] = {{d_gate, W.wg, F}, {d_up, W.wu, F}};
-        CF_HIP(launch_gemm(dt, 0, s, 2, dh2, N, H, 0.f, st, 1.f, nullptr, 0, false, nd));
+        CF_HIP(launch_gemm(dt, 0, s, 2, dh2, N, H, 0.f, st, false, nd));
     }
     // dr = dy + rmsnorm_bwd(dh2; r, g2);  dg2.  The pass has r and its rstd in registers, so it also
     // writes h2 = rmsnorm(r)*g2, the operand of the two parameter-gradient products below (which is why
@@ -246,7 +246,7 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     // ---- attention block: r = x + attn_out*Wo ------------------------------------
     {
         GemmSeg s2{w.dr, W.wo, H};                        // da = dr * Wo^T      [N,Nq]
-        CF_HIP(launch_gemm(dt, 0, &s2, 1, w.da, N, Nq, 0.f, st, 1.f, nullptr, 0, false, nd));
+        CF_HIP(launch_gemm(dt, 0, &s2, 1, w.da, N, Nq, 0.f, st, false, nd));
     }
     // the attention backward's row-statistics pass reads attn_out and q through idx and leaves their
     // compact copies in w.a_k, w.q_k (no gather kernel)
@@ -258,13 +258,12 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     CF_HIP(dw_gemm(a_rows, w.dr, G.dwo, Nq, H));          // dWo = a^T * dr      [Nq,H]
 
     if (sv.rope_cos) {      // transposed rotation of dq and dk at the original positions of the kept rows
-        CF_HIP(launch_rope_bwd(dt, w.dq, idx, rows, L.Hq, L.d, L.S, sv.rope_cos, sv.rope_sin, st));
-        CF_HIP(launch_rope_bwd(dt, w.dk, idx, rows, L.Hkv, L.d, L.S, sv.rope_cos, sv.rope_sin, st));
+        CF_HIP(launch_rope_bwd(dt, w.dq, L.Hq, w.dk, L.Hkv, idx, rows, L.d, L.S, sv.rope_cos, sv.rope_sin, st));
     }
     void* dh1 = w.bufHb;
     {   // dh1 = dq*Wq^T + dk*Wk^T + dv*Wv^T
         GemmSeg s[3] = {{w.dq, W.wq, Nq}, {w.dk, W.wk, Nkv}, {w.dv, W.wv, Nkv}};
-        CF_HIP(launch_gemm(dt, 0, s, 3, dh1, N, H, 0.f, st, 1.f, nullptr, 0, false, nd));
+        CF_HIP(launch_gemm(dt, 0, s, 3, dh1, N, H, 0.f, st, false, nd));
     }
     // dx = dr + rmsnorm_bwd(dh1; x, g1);  dg1; h1 = rmsnorm(x)*g1 on the way (see h2 above)
     void* h1 = w.bufHa;
@@ -288,67 +287,30 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
 // ---- LoRA-adapted layer: base weights and gains frozen, adapters on q, k, v, o ---------------
 struct LoraWs {
     LayerWs base;
-    void *a_t;                  // [rank, max(H, Nq)]  transposed adapter
-    void *u;                    // [N, rank]           scale * X * a
+    void *uq, *uk, *uv, *uo;    // [N, rank]           scale * X * a
     void *tq, *tk, *tv, *to;    // [N, rank]           scale * dY * b^T
-    void *dg_scratch;           // [H]
-    void *splitk;               // fp32 parts of the split-K adapter GEMMs
+    float* slots;               // fp32 parts of the split adapter products
     size_t total;
 };
-
-// Upper bound of what a split-K launch uses: parts <= CUs / tiles and a part holds at most
-// tiles * 128 * 128 floats, so 64 KB per CU; sized for 512 CUs.
-constexpr size_t kSplitKBytes = (size_t)32 << 20;
 
 LoraWs carve_lora(const cf_layer_desc& L, int rank, int max_kept, void* ws) {
     LoraWs w;
     w.base = carve_layer(L, max_kept, ws);
     const size_t e = dtype_size(L.dtype);
     const size_t N = (size_t)(max_kept > 0 ? max_kept : 1);
-    const size_t Nq = (size_t)L.Hq * L.d;
     Carver c(ws);
     c.off = w.base.total;
-    w.a_t = c.take((size_t)rank * (Nq > (size_t)L.H ? Nq : (size_t)L.H) * e);
-    w.u = c.take(N * rank * e);
-    w.tq = c.take(N * rank * e);
-    w.tk = c.take(N * rank * e);
-    w.tv = c.take(N * rank * e);
-    w.to = c.take(N * rank * e);
-    w.dg_scratch = c.take((size_t)L.H * e);
-    w.splitk = c.take(kSplitKBytes);
+    for (void** p : {&w.uq, &w.uk, &w.uv, &w.uo, &w.tq, &w.tk, &w.tv, &w.to}) *p = c.take(N * rank * e);
+    w.slots = (float*)c.take(gemm_group_slot_bytes());
     w.total = c.off;
     return w;
 }
 
-// One adapted projection with input rows x [N,in] and output gradient dy [N,out]:
-// t = scale*dy*b^T (kept for the caller's dX GEMM), db = (scale*x*a)^T*dy, da = x^T*t.
-cf_status lora_proj(int dt, const void* x, const void* dy, const void* a, const void* b, RowCount rows, int in,
-                    int out, int rank, float scale, void* t, void* da, void* db, const LoraWs& w,
-                    hipStream_t st) {
-    const int N = rows.n;
-    const int32_t* nd = rows.dev;
-    {   // t [N,rank] = scale * dy [N,out] * b [rank,out]^T
-        GemmSeg s{dy, b, out};
-        CF_HIP(launch_gemm(dt, 0, &s, 1, t, N, rank, 0.f, st, scale, w.splitk, kSplitKBytes, false, nd));
-    }
-    CF_HIP(launch_transpose(dt, a, in, rank, w.a_t, st));
-    {   // u [N,rank] = scale * x [N,in] * a_t [rank,in]^T
-        GemmSeg s{x, w.a_t, in};
-        CF_HIP(launch_gemm(dt, 0, &s, 1, w.u, N, rank, 0.f, st, scale, w.splitk, kSplitKBytes, false, nd));
-    }
-    {   // db [rank,out] = u^T * dy
-        GemmSeg s{w.u, dy, N};
-        CF_HIP(launch_gemm(dt, 1, &s, 1, db, rank, out, 0.f, st, 1.f, w.splitk, kSplitKBytes, false, nd));
-    }
-    {   // da [in,rank] = x^T * t
-        GemmSeg s{x, t, N};
-        CF_HIP(launch_gemm(dt, 1, &s, 1, da, in, rank, 0.f, st, 1.f, w.splitk, kSplitKBytes, false, nd));
-    }
-    return CF_OK;
-}
-
+// An adapted projection with input rows x [N,in] and output gradient dy [N,out] needs t = scale*dy*b^T (for the caller's
+// dX product and da = x^T*t) and u = scale*x*a (for db = u^T*dy).  The sixteen products of the four projections go out in
+// four grouped launches, each as soon as its operands exist: t_o; t_q, t_k, t_v and u_o; u_q, u_k, u_v; all da and db.
 cf_status layer_core_lora(const cf_layer_desc& L, const cf_saved& sv, const cf_weights& W,
-                          const cf_lora& A, const void* dy_rows, const int32_t* idx,
+                          const cf_lora& A, const void* dy, bool dy_is_full, const int32_t* idx,
                           const int32_t* cu_kept, RowCount rows, cf_lora_grads& G, const LoraWs& lw,
                           hipStream_t st) {
     const LayerWs& w = lw.base;
@@ -357,6 +319,7 @@ cf_status layer_core_lora(const cf_layer_desc& L, const cf_saved& sv, const cf_w
     const int H = L.H, F = L.F, Nq = L.Hq * L.d, Nkv = L.Hkv * L.d, R = A.rank;
     const int N = rows.n;                   // the live rows, or their upper bound when the count is on the device
     const int32_t* nd = rows.dev;
+    const int64_t T = (int64_t)L.B * L.S;
     if (N == 0) {
         void* outs[8] = {G.daq, G.dbq, G.dak, G.dbk, G.dav, G.dbv, G.dao, G.dbo};
         size_t sz[8] = {(size_t)H * R, (size_t)R * Nq, (size_t)H * R, (size_t)R * Nkv,
@@ -364,62 +327,65 @@ cf_status layer_core_lora(const cf_layer_desc& L, const cf_saved& sv, const cf_w
         for (int i = 0; i < 8; ++i) CF_HIP(launch_fill_zero(outs[i], sz[i] * e, st));
         return CF_OK;
     }
-    const void* a_rows = sv.attn_out;
-    const void* q_rows = sv.q;
-    if (idx) {
-        CF_HIP(launch_gather(sv.attn_out, (int64_t)Nq * e, idx, rows, w.a_k, st));
-        CF_HIP(launch_gather(sv.q, (int64_t)Nq * e, idx, rows, w.q_k, st));
-        a_rows = w.a_k;
-        q_rows = w.q_k;
-    }
+    if (dy_is_full && !idx) return CF_ERR_NULL;
+    auto group = [&](std::initializer_list<GemmGroupProb> ps) {
+        return launch_gemm_group(dt, ps.begin(), (int)ps.size(), st, lw.slots, nd);
+    };
     // ---- frozen SwiGLU FFN: only the input gradient
     void* d_act = w.bufF1;
     {
-        GemmSeg s{dy_rows, W.wd, H};
-        CF_HIP(launch_gemm(dt, 0, &s, 1, d_act, N, F, 0.f, st, 1.f, nullptr, 0, false, nd));
+        GemmSeg s{dy, W.wd, H};
+        CF_HIP(launch_gemm(dt, 0, &s, 1, d_act, N, F, 0.f, st, false, nd, dy_is_full ? idx : nullptr, dy_is_full ? T : 0));
     }
     void* d_gate = w.bufF1;
     void* d_up = w.bufF0;
-    CF_HIP(launch_swiglu_bwd(dt, d_act, sv.gate, sv.up, idx, rows, F, d_gate, d_up, nullptr, st));
+    const void* dy_rows = dy_is_full ? w.dy_k : dy;
+    CF_HIP(launch_swiglu_bwd(dt, d_act, sv.gate, sv.up, idx, rows, F, d_gate, d_up, nullptr, st, dy_is_full ? dy : nullptr,
+                             H, dy_is_full ? w.dy_k : nullptr));
     void* dh2 = w.bufHb;
     {
         GemmSeg s[2] = {{d_gate, W.wg, F}, {d_up, W.wu, F}};
-        CF_HIP(launch_gemm(dt, 0, s, 2, dh2, N, H, 0.f, st, 1.f, nullptr, 0, false, nd));
+        CF_HIP(launch_gemm(dt, 0, s, 2, dh2, N, H, 0.f, st, false, nd));
     }
-    CF_HIP(launch_rmsnorm_bwd(dt, dh2, sv.r, W.g2, idx, dy_rows, rows, H, L.rms_eps, w.dr, w.dg_partial,
-                              lw.dg_scratch, st));
+    CF_HIP(launch_rmsnorm_bwd(dt, dh2, sv.r, W.g2, idx, dy_rows, rows, H, L.rms_eps, w.dr, w.dg_partial, nullptr, st));
     // ---- adapted O projection: input a [N,Nq], output gradient dr [N,H]
-    cf_status ps = lora_proj(dt, a_rows, w.dr, A.ao, A.bo, rows, Nq, H, R, A.scale, lw.to, G.dao, G.dbo, lw, st);
-    if (ps != CF_OK) return ps;
+    CF_HIP(group({{w.dr, A.bo, lw.to, N, R, H, 0, A.scale}}));
     {   // da = dr*Wo^T + t_o*a_o^T
         GemmSeg s[2] = {{w.dr, W.wo, H}, {lw.to, A.ao, R}};
-        CF_HIP(launch_gemm(dt, 0, s, 2, w.da, N, Nq, 0.f, st, 1.f, nullptr, 0, false, nd));
+        CF_HIP(launch_gemm(dt, 0, s, 2, w.da, N, Nq, 0.f, st, false, nd));
     }
+    const void* a_rows = idx ? w.a_k : sv.attn_out;
+    const void* q_rows = idx ? w.q_k : sv.q;
     cf_status as = attn_dispatch(L, q_rows, sv.k, sv.v, a_rows, sv.lse, w.da, idx, cu_kept, rows, w.dq,
-                                 w.dk, w.dv, w.attn_ws, st);
+                                 w.dk, w.dv, w.attn_ws, st, idx ? sv.attn_out : nullptr, idx ? sv.q : nullptr);
     if (as != CF_OK) return as;
     if (sv.rope_cos) {
-        CF_HIP(launch_rope_bwd(dt, w.dq, idx, rows, L.Hq, L.d, L.S, sv.rope_cos, sv.rope_sin, st));
-        CF_HIP(launch_rope_bwd(dt, w.dk, idx, rows, L.Hkv, L.d, L.S, sv.rope_cos, sv.rope_sin, st));
+        CF_HIP(launch_rope_bwd(dt, w.dq, L.Hq, w.dk, L.Hkv, idx, rows, L.d, L.S, sv.rope_cos, sv.rope_sin, st));
     }
     // ---- adapted Q, K, V projections: input h1 [N,H]
-    void* h1 = w.bufHa;
-    CF_HIP(launch_rmsnorm_fwd(dt, sv.x, W.g1, idx, rows, H, L.rms_eps, h1, st));
-    ps = lora_proj(dt, h1, w.dq, A.aq, A.bq, rows, H, Nq, R, A.scale, lw.tq, G.daq, G.dbq, lw, st);
-    if (ps != CF_OK) return ps;
-    ps = lora_proj(dt, h1, w.dk, A.ak, A.bk, rows, H, Nkv, R, A.scale, lw.tk, G.dak, G.dbk, lw, st);
-    if (ps != CF_OK) return ps;
-    ps = lora_proj(dt, h1, w.dv, A.av, A.bv, rows, H, Nkv, R, A.scale, lw.tv, G.dav, G.dbv, lw, st);
-    if (ps != CF_OK) return ps;
+    CF_HIP(group({{w.dq, A.bq, lw.tq, N, R, Nq, 0, A.scale},
+                  {w.dk, A.bk, lw.tk, N, R, Nkv, 0, A.scale},
+                  {w.dv, A.bv, lw.tv, N, R, Nkv, 0, A.scale},
+                  {a_rows, A.ao, lw.uo, N, R, Nq, 2, A.scale}}));
     void* dh1 = w.bufHb;
-    {   // dh1 = dq*Wq^T + dk*Wk^T + dv*Wv^T, then += t_q*a_q^T + t_k*a_k^T + t_v*a_v^T
-        GemmSeg s[3] = {{w.dq, W.wq, Nq}, {w.dk, W.wk, Nkv}, {w.dv, W.wv, Nkv}};
-        CF_HIP(launch_gemm(dt, 0, s, 3, dh1, N, H, 0.f, st, 1.f, nullptr, 0, false, nd));
-        GemmSeg s2[3] = {{lw.tq, A.aq, R}, {lw.tk, A.ak, R}, {lw.tv, A.av, R}};
-        CF_HIP(launch_gemm(dt, 0, s2, 3, dh1, N, H, 1.f, st, 1.f, nullptr, 0, false, nd));
+    {   // dh1 = dq*Wq^T + dk*Wk^T + dv*Wv^T + t_q*a_q^T + t_k*a_k^T + t_v*a_v^T
+        GemmSeg s[6] = {{w.dq, W.wq, Nq}, {w.dk, W.wk, Nkv}, {w.dv, W.wv, Nkv},
+                        {lw.tq, A.aq, R}, {lw.tk, A.ak, R}, {lw.tv, A.av, R}};
+        CF_HIP(launch_gemm(dt, 0, s, 6, dh1, N, H, 0.f, st, false, nd));
     }
-    CF_HIP(launch_rmsnorm_bwd(dt, dh1, sv.x, W.g1, idx, w.dr, rows, H, L.rms_eps, G.dx, w.dg_partial,
-                              lw.dg_scratch, st));
+    void* h1 = w.bufHa;         // a by-product of the norm's backward pass
+    CF_HIP(launch_rmsnorm_bwd(dt, dh1, sv.x, W.g1, idx, w.dr, rows, H, L.rms_eps, G.dx, w.dg_partial, nullptr, st, false, h1));
+    CF_HIP(group({{h1, A.aq, lw.uq, N, R, H, 2, A.scale},
+                  {h1, A.ak, lw.uk, N, R, H, 2, A.scale},
+                  {h1, A.av, lw.uv, N, R, H, 2, A.scale}}));
+    CF_HIP(group({{a_rows, lw.to, G.dao, Nq, R, N, 1, 1.f},
+                  {lw.uo, w.dr, G.dbo, R, H, N, 1, 1.f},
+                  {h1, lw.tq, G.daq, H, R, N, 1, 1.f},
+                  {lw.uq, w.dq, G.dbq, R, Nq, N, 1, 1.f},
+                  {h1, lw.tk, G.dak, H, R, N, 1, 1.f},
+                  {lw.uk, w.dk, G.dbk, R, Nkv, N, 1, 1.f},
+                  {h1, lw.tv, G.dav, H, R, N, 1, 1.f},
+                  {lw.uv, w.dv, G.dbv, R, Nkv, N, 1, 1.f}}));
     return CF_OK;
 }
 
@@ -715,7 +681,7 @@ cf_status cf_layer_bwd_lora(const cf_layer_desc* desc, const cf_saved* saved, co
         LoraWs lw = carve_lora(*desc, lora->rank, T, ws);
         if (ws_bytes < lw.total) return CF_ERR_WORKSPACE;
         if (n_kept_host) *n_kept_host = T;
-        return layer_core_lora(*desc, *saved, *w, *lora, dy_full, nullptr, nullptr, RowCount{T, nullptr}, *grads,
+        return layer_core_lora(*desc, *saved, *w, *lora, dy_full, false, nullptr, nullptr, RowCount{T, nullptr}, *grads,
                                lw, st);
     }
     LoraWs lw = carve_lora(*desc, lora->rank, max_kept, ws);
@@ -726,8 +692,7 @@ cf_status cf_layer_bwd_lora(const cf_layer_desc* desc, const cf_saved* saved, co
     CF_HIP(launch_keep_index(mask, desc->B, desc->S, idx, cu, n_dev, lw.base.index_ws, st));
     // the count stays on the device, as in cf_layer_bwd_filtered: nothing here waits for the host
     const RowCount rows{max_kept, n_dev};
-    CF_HIP(launch_gather(dy_full, (int64_t)desc->H * dtype_size(desc->dtype), idx, rows, lw.base.dy_k, st));
-    s = layer_core_lora(*desc, *saved, *w, *lora, lw.base.dy_k, idx, cu, rows, *grads, lw, st);
+    s = layer_core_lora(*desc, *saved, *w, *lora, dy_full, true, idx, cu, rows, *grads, lw, st);
     if (s != CF_OK) return s;
     if (n_kept_host)
         CF_HIP(hipMemcpyAsync(n_kept_host, n_dev, sizeof(int32_t), hipMemcpyDeviceToHost, st));

@@ -134,20 +134,18 @@ hipError_t launch_swiglu_bwd(int dtype, const void* d_act, const void* gate, con
                              const int32_t* idx, RowCount rows, int F, void* d_gate, void* d_up,
                              void* act, hipStream_t st, const void* copy_src = nullptr, int copy_cols = 0,
                              void* copy_dst = nullptr);
-hipError_t launch_rmsnorm_fwd(int dtype, const void* x, const void* g, const int32_t* idx,
-                              RowCount rows, int H, float eps, void* h, hipStream_t st);
 // dx_out = res + rmsnorm_bwd(dh; x, g); dg_partial is [rmsnorm_bwd_blocks(n_rows), H] fp32 scratch.
 // dg_acc_f32: dg_out is fp32 [H] and the gain gradient is added to it instead of written.
-// h_out (nullable, [n_rows, H]): also receives the normalised rows rmsnorm(x)*g, as launch_rmsnorm_fwd
-// would write them.
+// dg_out null: the gains are frozen, no gradient is summed up for them.
+// h_out (nullable, [n_rows, H]): also receives the normalised rows rmsnorm(x)*g.
 int rmsnorm_bwd_blocks(int n_rows);
 hipError_t launch_rmsnorm_bwd(int dtype, const void* dh, const void* x, const void* g,
                               const int32_t* idx, const void* res, RowCount rows, int H, float eps,
                               void* dx_out, float* dg_partial, void* dg_out, hipStream_t st,
                               bool dg_acc_f32 = false, void* h_out = nullptr);
-// g[j, h*d + i] (in place, [n_rows, heads*d]): transposed rotary rotation at position idx[j] % S
+// gq [n_rows, hq*d] and gk [n_rows, hk*d], in place: transposed rotary rotation at position idx[j] % S
 // (idx null: j % S); cos, sin are [S, d/2] fp32
-hipError_t launch_rope_bwd(int dtype, void* g, const int32_t* idx, RowCount rows, int heads, int d, int S,
+hipError_t launch_rope_bwd(int dtype, void* gq, int hq, void* gk, int hk, const int32_t* idx, RowCount rows, int d, int S,
                            const float* cos, const float* sin, hipStream_t st);
 // D[j,h] = sum_c da[j,h*d+c] * a[row,h*d+c], row = a_idx ? a_idx[j] : j; with a_idx the same launch also
 // writes the compact copies a_out[j,:] = a[row,:] and (q_src non-null) q_out[j,:] = q_src[row,:]
@@ -155,16 +153,13 @@ hipError_t launch_attn_rowdot(int dtype, const void* da, const void* a, RowCount
                               float* D, hipStream_t st, const int32_t* a_idx = nullptr, void* a_out = nullptr,
                               const void* q_src = nullptr, void* q_out = nullptr);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
-// dst [cols, rows] = src [rows, cols]^T  (small matrices: the low-rank adapters)
-hipError_t launch_transpose(int dtype, const void* src, int rows, int cols, void* dst, hipStream_t st);
-
 // gemm.hip
 struct GemmSeg {
     const void* A;
     const void* B;
     int K;
 };
-// C[M,N] = beta*C + alpha * sum_seg op(A_seg)*op(B_seg); all matrices dense row-major.
+// C[M,N] = beta*C + sum_seg op(A_seg)*op(B_seg), up to six segments; all matrices dense row-major.
 //   mode 0 ("NT"): A_seg [M,K], B_seg [N,K]      (C = A * B^T)
 //   mode 1 ("TN"): A_seg [K,M], B_seg [K,N]      (C = A^T * B)
 // c_f32 (bf16 dtype only): C is an fp32 matrix (a main-gradient buffer) and the accumulators are
@@ -173,13 +168,26 @@ struct GemmSeg {
 // (M in mode 0, the K of segment 0 in mode 1) is only an upper bound and the kernel uses
 // min(*n_dev, bound).  a_idx (nullable, mode 0, segment 0): row m of A is row a_idx[m] of a longer
 // matrix (the gather of the upstream gradient folded into the A-tile loads); a_rows = rows of that matrix.
-// splitk_ws (device, splitk_bytes, 16-byte aligned, may be null): scratch that lets a bf16 product
-// with one segment, few output tiles and a long K run as a split-K launch (fp32 parts summed in a
-// fixed order by a second kernel).
 hipError_t launch_gemm(int dtype, int mode, const GemmSeg* segs, int nseg, void* C, int M, int N,
-                       float beta, hipStream_t st, float alpha = 1.0f, void* splitk_ws = nullptr,
-                       size_t splitk_bytes = 0, bool c_f32 = false, const int32_t* n_dev = nullptr,
+                       float beta, hipStream_t st, bool c_f32 = false, const int32_t* n_dev = nullptr,
                        const int32_t* a_idx = nullptr, int64_t a_rows = 0);
+
+// One launch for up to GROUP_MAX independent products C [M,N] = alpha * op(A) * op(B) with few output tiles:
+//   mode 0 ("NT"): A [M,K], B [N,K]    1 ("TN"): A [K,M], B [K,N]    2 ("NN"): A [M,K], B [K,N]
+// No product may read another one's result.  slots (nullable, gemm_group_slot_bytes(), 16-byte aligned): scratch that
+// lets the contractions be split over idle CUs.  n_dev (nullable): the live kept-token count, which bounds M in
+// modes 0 and 2 and K in mode 1.
+static constexpr int GROUP_MAX = 8;
+struct GemmGroupProb {
+    const void *A, *B;
+    void* C;
+    int M, N, K;
+    int mode;
+    float alpha;
+};
+size_t gemm_group_slot_bytes();
+hipError_t launch_gemm_group(int dtype, const GemmGroupProb* probs, int np, hipStream_t st, float* slots = nullptr,
+                             const int32_t* n_dev = nullptr);
 
 // One TN launch for up to three products that share A [K,M]: C_j [M,Ng[j]] = A^T * B_j [K,Ng[j]].
 // bf16 only, every Ng[j] a multiple of 256 (gemm_tn_groups_supported says whether it applies).

@@ -76,10 +76,12 @@
 
 namespace cf {
 
+static constexpr int MAX_SEG = 6;
+
 struct GemmArgs {
-    const void* A[3];
-    const void* B[3];
-    int K[3];
+    const void* A[MAX_SEG];
+    const void* B[MAX_SEG];
+    int K[MAX_SEG];
     int nseg;
     void* C;
     int M, N;
@@ -216,7 +218,7 @@ struct TileRef {
 // tile's first K-steps are in flight while the finished tile leaves through a staging area of its
 // own, and its stores drain under the next tile's MFMAs.  SPLIT: the block contracts only k in
 // [kbeg, kend) of the single segment and stores its fp32 accumulators, unscaled, to `part_out`
-// ([M, N] fp32); a second kernel adds the parts up.
+// ([BM, BN] fp32); a second kernel adds the parts up.
 // Mx, K0x: the live values of g.M and g.K[0] (they differ from the launch arguments when the
 // kept-token count is read on the device).
 template <int MODE, int TM, int TN, bool SPLIT, bool CF32, typename Next>
@@ -230,6 +232,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
     constexpr int BM = 64 * TM, BN = 64 * TN, KB = 32, STAGE = DEEP ? 16384 : 32768;
     constexpr int NSTG = GEMM_RING / STAGE, NPR = NSTG / 2;     // stages and pairs in the ring
     constexpr int SWIN = 65536 / STAGE;                 // stages within reach of one LDS base register
+    // MODE 0 (NT): both operands lie with K contiguous in memory; 1 (TN): both K-major; 2 (NN): A K-contiguous, B K-major
+    constexpr bool AK = MODE != 1, BK = MODE == 0;
     constexpr int A_BYTES = BM * KB * 2;                // B tile follows the A tile inside a stage
     constexpr int NU = TM + TN;                         // 1 KB wave-loads per wave per K-step: TM for A, TN for B
     constexpr int FM = 2 * TM, FN = 2 * TN;             // 16-row fragments of the wave tile along M and N
@@ -263,23 +267,28 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
     bool pair_inside = false;
     const unsigned nt_lc = (unsigned)((lane & 3) ^ nt_swz(lane >> 4));
     auto open_segment = [&](int s) __attribute__((always_inline)) {
-        const bool live = s < g.nseg;
+        const bool live = (unsigned)s < (unsigned)g.nseg;
         const int m0 = ld.m0, n0 = ld.n0;
-        const bf16_t* A = static_cast<const bf16_t*>(s == 1 ? g.A[1] : (s == 2 ? g.A[2] : g.A[0]));
-        const bf16_t* B = static_cast<const bf16_t*>(s == 1 ? g.B[1] : (s == 2 ? g.B[2] : ld.B0));
-        const int Kraw = s == 1 ? g.K[1] : (s == 2 ? g.K[2] : K0x);
+        const int sa = live ? s : 0;
+        const bf16_t* A = static_cast<const bf16_t*>(g.A[sa]);
+        const bf16_t* B = static_cast<const bf16_t*>(sa == 0 ? ld.B0 : g.B[sa]);
+        const int Kraw = sa == 0 ? K0x : g.K[sa];
         Kseg = live ? Kraw : 0;
         const int64_t K = Kraw;
         const bool gatherA = MODE == 0 && s == 0 && g.a_idx != nullptr;
-        if (MODE == 0) {
+        if (AK) {
             // gathered A: the descriptor spans the whole source matrix and a lane's offset starts at its source row
             rsA = gatherA ? make_rsrc(A, g.a_rows * K * 2) : make_rsrc(A + (int64_t)m0 * K, ((int64_t)Mx - m0) * K * 2);
-            rsB = make_rsrc(B + (int64_t)n0 * K, ((int64_t)ld.N - n0) * K * 2);
-            ldA = ldB = (unsigned)K * 2u;
+            ldA = (unsigned)K * 2u;
         } else {
             rsA = make_rsrc(A + m0, (K * Mx - m0) * 2);
-            rsB = make_rsrc(B + n0, (K * ld.N - n0) * 2);
             ldA = (unsigned)Mx * 2u;
+        }
+        if (BK) {
+            rsB = make_rsrc(B + (int64_t)n0 * K, ((int64_t)ld.N - n0) * K * 2);
+            ldB = (unsigned)K * 2u;
+        } else {
+            rsB = make_rsrc(B + n0, (K * ld.N - n0) * 2);
             ldB = (unsigned)ld.N * 2u;
         }
         // The per-lane parts below never change, but they are cheap to rebuild and registers are
@@ -292,7 +301,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         for (int u = 0; u < NU; ++u) {
             const bool isA = u < TM;
             const int i = isA ? u : u - TM;
-            if (MODE == 0) {
+            if (isA ? AK : BK) {
                 const unsigned row = (4 * i + wave) * 16 + (ln >> 2);
                 vbase[u] = row * (isA ? ldA : ldB) + lc_nt * 16u;
                 if (isA && gatherA) {       // rows past M carry an out-of-range offset; the index is read for live rows only
@@ -319,10 +328,10 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
                 int kpos;                       // first k of the lane's chunk within a K-step
-                if (MODE == 0) {
+                const bool isA = u < TM;
+                if (isA ? AK : BK) {
                     kpos = (int)nt_lc * 8;
                 } else {
-                    const bool isA = u < TM;
                     const int i = isA ? u : u - TM;
                     kpos = ((4 * i + wave) * 64 + lane) / ((isA ? BM : BN) / 8);
                 }
@@ -331,13 +340,10 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
             }
         }
         pair_inside = inside;
-        if (MODE == 0) {
-            ka0 = kb0 = (unsigned)k0 * 2u;
-            ka1 = kb1 = (unsigned)(k0 + KB) * 2u;
-        } else {
-            ka0 = (unsigned)k0 * ldA; kb0 = (unsigned)k0 * ldB;
-            ka1 = (unsigned)(k0 + KB) * ldA; kb1 = (unsigned)(k0 + KB) * ldB;
-        }
+        if (AK) ka0 = (unsigned)k0 * 2u;
+        else { ka0 = (unsigned)k0 * ldA; ka1 = (unsigned)(k0 + KB) * ldA; }
+        if (BK) kb0 = (unsigned)k0 * 2u;
+        else { kb0 = (unsigned)k0 * ldB; kb1 = (unsigned)(k0 + KB) * ldB; }
     };
     // A pair of K-steps never straddles a segment boundary: a segment with an odd number of
     // K-steps gets one all-zero K-step appended (its loads fall past Kseg).
@@ -346,7 +352,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         if (k0 >= Kseg) {
             k0 = 0;
             ++seg;
-            if (!DEEP || seg < g.nseg) open_segment(seg);
+            if (!DEEP || (unsigned)seg < (unsigned)g.nseg) open_segment(seg);
             else { Kseg = 0; pair_inside = false; }     // past the last segment: only the range of k matters any more
         }
     };
@@ -363,7 +369,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         constexpr int dst = s * STAGE + (isA ? 0 : A_BYTES) + i * 4096;
         // the instruction offset moves the LDS destination along with the global address, so the
         // M0 base of the second K-step is set back by the same amount
-        if (MODE == 0) dma16i<dst - (sec ? KB * 2 : 0), sec ? KB * 2 : 0>(lds0, isA ? rsA : rsB, sec ? v1[u] : v0[u], ka0);
+        if (isA ? AK : BK)
+            dma16i<dst - (sec ? KB * 2 : 0), sec ? KB * 2 : 0>(lds0, isA ? rsA : rsB, sec ? v1[u] : v0[u], isA ? ka0 : kb0);
         else dma16i<dst, 0>(lds0, isA ? rsA : rsB, sec ? v1[u] : v0[u], isA ? (sec ? ka1 : ka0) : (sec ? kb1 : kb0));
     };
     // the same load wrapped around the MFMA acc += a x b (inside the MFMA stream)
@@ -372,8 +379,9 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         constexpr bool isA = u < TM;
         constexpr int i = isA ? u : u - TM;
         constexpr int dst = s * STAGE + (isA ? 0 : A_BYTES) + i * 4096;
-        if (MODE == 0)
-            mfma16_dma16i<dst - (sec ? KB * 2 : 0), sec ? KB * 2 : 0>(c, a, b, lds0, isA ? rsA : rsB, sec ? v1[u] : v0[u], ka0);
+        if (isA ? AK : BK)
+            mfma16_dma16i<dst - (sec ? KB * 2 : 0), sec ? KB * 2 : 0>(c, a, b, lds0, isA ? rsA : rsB, sec ? v1[u] : v0[u],
+                                                                      isA ? ka0 : kb0);
         else
             mfma16_dma16i<dst, 0>(c, a, b, lds0, isA ? rsA : rsB, sec ? v1[u] : v0[u],
                                   isA ? (sec ? ka1 : ka0) : (sec ? kb1 : kb0));
@@ -385,33 +393,31 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
     // the ring lies past that field's reach from the base of stage 0 and has base registers of its own.
     typedef __attribute__((address_space(3))) unsigned char* lds_u8_ptr;
     typedef const __attribute__((address_space(3))) u32x4_t* lds_u32x4_cptr;
-    constexpr int NBASE = MODE == 0 ? 2 : NU;       // NT: A, B; TN: one per 32-row block (the swizzle mixes the block in)
+    // base registers: one for a K-contiguous operand; one per 32-row block for a K-major one (the swizzle mixes the block in)
+    constexpr int NBA = AK ? 1 : TM, NBASE = NBA + (BK ? 1 : TN);
     unsigned fbase[NBASE][2];
     {
         const unsigned s0 = lds_addr_of(smem);
-        if (MODE == 0) {
-            const int nt_sw = nt_swz(l16 >> 2);
+        const int nt_sw = nt_swz(l16 >> 2);
 #pragma unroll
-            for (int ab = 0; ab < 2; ++ab) {
-                const int wrow = ab == 0 ? wm * (32 * TM) : wn * (32 * TN);
-                const unsigned v = s0 + (ab == 0 ? 0 : A_BYTES) + (wrow + l16) * 64 + ((g4 ^ nt_sw) << 4);
-                fbase[ab][0] = v;
-                fbase[ab][1] = v + 65536;
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < NU; ++u) {
-                const bool isA = u < TM;
-                const int i = isA ? u : u - TM;
+        for (int u = 0; u < NBASE; ++u) {
+            const bool isA = u < NBA;
+            const int i = isA ? u : u - NBA;
+            const unsigned op0 = s0 + (isA ? 0 : A_BYTES);
+            unsigned v;
+            if (isA ? AK : BK) {
+                const int wrow = isA ? wm * (32 * TM) : wn * (32 * TN);
+                v = op0 + (wrow + l16) * 64 + ((g4 ^ nt_sw) << 4);
+            } else {
                 const int W2 = (isA ? BM : BN) * 2;                 // bytes per k-row
                 const int row0 = isA ? wm * (32 * TM) + i * 32 : wn * (32 * TN) + i * 32;
                 const int kl = 8 * g4 + (l16 >> 2);                 // k within the K-step (and kl + 4)
                 const int lc = row0 / 8 + ((lane & 3) >> 1);
                 const int sw = (kl & 3) << 2;                       // the same for k and k + 4
-                const unsigned v = s0 + (isA ? 0 : A_BYTES) + kl * W2 + ((lc ^ sw) << 4) + (lane & 1) * 8;
-                fbase[u][0] = v;
-                fbase[u][1] = v + 65536;
+                v = op0 + kl * W2 + ((lc ^ sw) << 4) + (lane & 1) * 8;
             }
+            fbase[u][0] = v;
+            fbase[u][1] = v + 65536;
         }
     }
     bf16x8_t fa[2][2], fb[2][FN];
@@ -423,12 +429,12 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         constexpr int f = isA ? fr : fr - FM;
         constexpr int win = s / SWIN, soff = (s % SWIN) * STAGE;
         bf16x8_t v;
-        if (MODE == 0) {
-            const lds_u8_ptr p = reinterpret_cast<lds_u8_ptr>(fbase[isA ? 0 : 1][win]);
+        if (isA ? AK : BK) {
+            const lds_u8_ptr p = reinterpret_cast<lds_u8_ptr>(fbase[isA ? 0 : NBA][win]);
             v = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<lds_u32x4_cptr>(p + (soff + f * 1024)));
         } else {
             constexpr int W2 = (isA ? BM : BN) * 2;
-            const lds_u8_ptr p = reinterpret_cast<lds_u8_ptr>(fbase[(isA ? 0 : TM) + f / 2][win]);
+            const lds_u8_ptr p = reinterpret_cast<lds_u8_ptr>(fbase[(isA ? 0 : NBA) + f / 2][win]);
             const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + (soff + (f & 1) * 32)));
             const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + (soff + (f & 1) * 32 + 4 * W2)));
             v = __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
@@ -521,9 +527,9 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
     };
 
     // pairs of K-steps, a segment with an odd number of K-steps padded with a zero K-step
-    const int npairs = SPLIT ? (kend - kbeg + 2 * KB - 1) / (2 * KB)
-                             : (K0x + 2 * KB - 1) / (2 * KB) + (g.K[1] + 2 * KB - 1) / (2 * KB) +
-                                   (g.K[2] + 2 * KB - 1) / (2 * KB);
+    int npairs = SPLIT ? (kend - kbeg + 2 * KB - 1) / (2 * KB) : (K0x + 2 * KB - 1) / (2 * KB);
+    if (!SPLIT)
+        for (int s = 1; s < g.nseg; ++s) npairs += (g.K[s] + 2 * KB - 1) / (2 * KB);
     // prologue of tile ld: the first NPR - 1 pairs and the first group of the loads of the pair behind them
     auto start_tile = [&]() __attribute__((always_inline)) {
         seg = 0;
@@ -593,18 +599,15 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         const int m0 = ep.m0, n0 = ep.n0;
 
     if (SPLIT) {
-        // ---- split-K epilogue: fp32 accumulators straight to the block's part ----------
+        // ---- split-K epilogue: the whole tile's fp32 accumulators, unscaled, straight to the item's own slot (rows and
+        // columns past the matrix are zeros in it)
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int j = 0; j < FN; ++j) {
-                const int m = m0 + wm * (32 * TM) + i * 16 + l16;
-                const int n = n0 + wn * (32 * TN) + j * 16 + 4 * g4;
-                if (m < Mx && n < ep.N) {                   // N is a multiple of 8
-                    float4 o;
-                    o.x = acc[i][j][0]; o.y = acc[i][j][1]; o.z = acc[i][j][2]; o.w = acc[i][j][3];
-                    *reinterpret_cast<float4*>(part_out + (int64_t)m * ep.N + n) = o;
-                }
+                float4 o;
+                o.x = acc[i][j][0]; o.y = acc[i][j][1]; o.z = acc[i][j][2]; o.w = acc[i][j][3];
+                *reinterpret_cast<float4*>(part_out + (wm * (32 * TM) + i * 16 + l16) * BN + wn * (32 * TN) + j * 16 + 4 * g4) = o;
             }
         break;
     }
@@ -875,60 +878,170 @@ __global__ __launch_bounds__(256) void gemm_bf16_f32out_kernel(GemmArgs g) {
     gemm_bf16_block<MODE, true>(g, smem);
 }
 
-// Split-K variant for outputs with too few tiles to fill the chip (a skinny M or N with a long
-// K: the products with a rank-r adapter matrix).  grid = (128x128 tiles, parts); part p contracts
-// k in [p*kchunk, (p+1)*kchunk) into partial[p]; splitk_reduce_kernel sums the parts in a fixed
-// order, so the result does not depend on scheduling.
-template <int MODE>
-__global__ __launch_bounds__(256) void gemm_bf16_splitk_kernel(GemmArgs g, float* partial, int kchunk) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int tiles_m = (g.M + 127) / 128;
-    const int m0 = ((int)blockIdx.x % tiles_m) * 128, n0 = ((int)blockIdx.x / tiles_m) * 128;
-    // a device-side kept-token count bounds M (mode NT) or K (mode TN); the launch was planned for the
-    // host's upper bound, so a block may find its rows or its K range empty: it then stores nothing
-    // (NT; the reduction skips those rows too) or a tile of zeros (TN)
-    int Mx = g.M, Kx = g.K[0];
-    if (g.n_dev != nullptr) {
-        const int n = max(*g.n_dev, 0);
-        if (MODE == 0) Mx = min(Mx, n);
-        else Kx = min(Kx, n);
+// ---------------------------------------------------------------------------
+// Grouped launch: up to GROUP_MAX independent products with 128x128 tiles, their contractions cut into parts when the
+// tiles alone leave CUs idle.  For the products with a rank-r adapter matrix (an output of r columns or r rows with a long
+// contraction: 2 to 32 tiles each) and for layers with few kept tokens: what they cost one by one is launches (5 us
+// for the smallest kernel), blocks that wait for loads on a few CUs (a CU takes in about 60 B/ns whatever the number
+// of active CUs, so a product that lies on 100 of them runs at 100/256 of the rate), and a reduction each.
+// An item is one (tile, part); a part of a split tile leaves its fp32 accumulators in a 64 KB slot of its own and
+// gemm_group_reduce_kernel adds the slots of a tile up in the order of the parts.  Blocks and reduction make the same plan
+// from the live kept-token count, so the result is the same whether the count was known to the host or not.
+// ---------------------------------------------------------------------------
+struct GroupArgs {
+    GemmGroupProb p[GROUP_MAX];
+    int np;
+    int n_cu;               // items that may be split over (and slots)
+    const int32_t* n_dev;   // nullable: the live kept-token count (M in modes 0 and 2, K in mode 1), at most the one in p
+    float* slots;           // nullable: no splitting; n_cu slots and, behind them, the plan (one int)
+    __host__ __device__ int32_t* plan() const { return reinterpret_cast<int32_t*>(slots + (size_t)n_cu * (128 * 128)); }
+};
+
+__host__ __device__ inline void group_sizes(const GemmGroupProb& p, int n_live, int& M, int& K) {
+    M = p.mode != 1 && n_live < p.M ? n_live : p.M;
+    K = p.mode == 1 && n_live < p.K ? n_live : p.K;
+}
+// Part sizes are numbered q = 2, 3, 4, 5, ...: 2, 3, 4, 6, 8, 12, ... steps of 64.
+__host__ __device__ inline int group_step(int q) { return q & 1 ? 3 << ((q >> 1) - 1) : 1 << (q >> 1); }
+// parts of a contraction of K, at least one
+__host__ __device__ inline int group_parts(int K, int q) {
+    const int k64 = (K + 63) >> 6, up = k64 + group_step(q) - 1;
+    if (k64 <= 0) return 1;
+    return q & 1 ? (up / 3) >> ((q >> 1) - 1) : up >> (q >> 1);
+}
+// Part size number of a launch: the smallest (at least 128 k: two steps) with which the items of all products fit one
+// round of the CUs; -1, nothing is split, when even the whole tiles do not, or without slots.
+static constexpr int GROUP_Q = 40;
+__host__ __device__ inline bool group_fits(const GroupArgs& g, int n_live, int q, bool& split) {
+    int items = 0;
+    split = false;
+#pragma unroll
+    for (int j = 0; j < GROUP_MAX; ++j) {
+        int M, K;
+        group_sizes(g.p[j], n_live, M, K);
+        const int parts = group_parts(K, q);
+        const bool used = j < g.np;
+        items += used ? cdiv(M, 128) * cdiv(g.p[j].N, 128) * parts : 0;
+        split |= used && parts > 1;
     }
-    const int kbeg = (int)blockIdx.y * kchunk;
-    const int kend = max(kbeg, min(Kx, kbeg + kchunk));
-    if (MODE == 0 && m0 >= Mx) return;
-    const TileRef t{m0, n0, g.N, g.B[0], g.C};
-    gemm_tiles<MODE, 2, 2, true, false>(g, Mx, Kx, t, [](TileRef&) { return false; }, smem, kbeg, kend,
-                                        partial + (int64_t)blockIdx.y * g.M * g.N);
+    return items <= g.n_cu;
+}
+inline int group_plan_host(const GroupArgs& g, int n_live) {
+    if (g.slots == nullptr) return -1;
+    for (int q = 2; q < GROUP_Q; ++q) {
+        bool split;
+        const bool fits = group_fits(g, n_live, q, split);
+        if (fits || !split) return split ? q : -1;
+    }
+    return -1;
+}
+// The same with a candidate per lane: one after the other they cost every block several microseconds.
+__device__ __forceinline__ int group_plan(const GroupArgs& g, int n_live) {
+    if (g.slots == nullptr) return -1;
+    const int q = 2 + (int)(threadIdx.x & 63);
+    bool split = false;
+    const bool fits = group_fits(g, n_live, q < GROUP_Q ? q : GROUP_Q - 1, split);
+    const uint64_t done = __ballot(q < GROUP_Q && (fits || !split)), cut = __ballot(split);
+    if (done == 0) return -1;
+    const int first = __ffsll((unsigned long long)done) - 1;
+    return (cut >> first) & 1 ? first + 2 : -1;
 }
 
-// C[m, n..n+7] = alpha * sum_p partial[p][m, n..n+7] + beta * C
-// rows_dev (nullable): the live number of rows of C on the device (mode NT with a device-side count);
-// rows past it have no partials and are left alone.
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ partial, bf16_t* __restrict__ C,
-                                                            int64_t mn, int parts, float alpha, float beta,
-                                                            const int32_t* __restrict__ rows_dev, int ncols) {
-    const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
-    if (e >= mn) return;
-    if (rows_dev != nullptr && e >= (int64_t)max(*rows_dev, 0) * ncols) return;
-    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int p = 0; p < parts; ++p) {
-        const float4 a = *reinterpret_cast<const float4*>(partial + p * mn + e);
-        const float4 b = *reinterpret_cast<const float4*>(partial + p * mn + e + 4);
-        s[0] += a.x; s[1] += a.y; s[2] += a.z; s[3] += a.w;
-        s[4] += b.x; s[5] += b.y; s[6] += b.z; s[7] += b.w;
-    }
-    u32x4_t val;
-    if (beta != 0.f) {
-        const u32x4_t old = *reinterpret_cast<const u32x4_t*>(C + e);
+// item -> product, tile and part; false past the last item
+struct GroupItem {
+    int j, M, K, m0, n0, parts, part;
+};
+__device__ __forceinline__ bool group_item(const GroupArgs& g, int n_live, int plan, int w, GroupItem& it) {
+    it.j = -1;
+    int tm_j = 1;
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            val[q] = pack_bf16x2(alpha * s[2 * q] + beta * __uint_as_float(old[q] << 16),
-                                 alpha * s[2 * q + 1] + beta * __uint_as_float(old[q] & 0xFFFF0000u));
+    for (int j = 0; j < GROUP_MAX; ++j) {
+        int M, K;
+        group_sizes(g.p[j], n_live, M, K);
+        const int tm = cdiv(M, 128), parts = plan < 0 ? 1 : group_parts(K, plan);
+        const int n = j < g.np ? tm * cdiv(g.p[j].N, 128) * parts : 0;
+        if (it.j < 0 && w < n) { it.j = j; it.M = M; it.K = K; it.parts = parts; it.part = w; tm_j = tm; }
+        w -= n;
+    }
+    if (it.j < 0) return false;
+    const int t = it.part / it.parts;
+    it.part -= t * it.parts;
+    it.m0 = (t % tm_j) * 128;
+    it.n0 = (t / tm_j) * 128;
+    return true;
+}
+
+template <int MODE>
+__device__ __forceinline__ void group_tile(const GroupArgs& ga, const GroupItem& it, int plan, int w, unsigned char* smem) {
+    const GemmGroupProb& p = ga.p[it.j];
+    GemmArgs g;
+    g.A[0] = uniform_ptr(p.A); g.B[0] = uniform_ptr(p.B); g.K[0] = it.K; g.nseg = 1;
+    g.C = uniform_ptr(p.C); g.M = it.M; g.N = p.N; g.beta = 0.f; g.alpha = p.alpha; g.c_f32 = 0; g.ngroups = 1;
+    g.n_dev = nullptr; g.a_idx = nullptr; g.a_rows = 0;
+    const TileRef t{it.m0, it.n0, p.N, g.B[0], g.C};
+    auto none = [](TileRef&) { return false; };
+    if (it.parts > 1) {
+        const int c = group_step(plan) * 64, kbeg = it.part * c, kend = min(it.K, kbeg + c);
+        gemm_tiles<MODE, 2, 2, true, false>(g, it.M, it.K, t, none, smem, kbeg, kend, ga.slots + (int64_t)w * (128 * 128));
     } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) val[q] = pack_bf16x2(alpha * s[2 * q], alpha * s[2 * q + 1]);
+        gemm_tiles<MODE, 2, 2, false, false>(g, it.M, it.K, t, none, smem);
     }
-    *reinterpret_cast<u32x4_t*>(C + e) = val;
+}
+
+__global__ __launch_bounds__(256) void gemm_group_kernel(GroupArgs g) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int n_live = g.n_dev != nullptr ? __builtin_amdgcn_readfirstlane(max(*g.n_dev, 0)) : INT32_MAX;
+    const int plan = __builtin_amdgcn_readfirstlane(group_plan(g, n_live));
+    // for the reduction: made by every one of its blocks, the plan would cost it more than the sums (12 us for 4096 blocks)
+    if (blockIdx.x == 0 && threadIdx.x == 0 && g.slots != nullptr) *g.plan() = plan;
+    for (int w = blockIdx.x;; w += gridDim.x) {
+        GroupItem it;
+        if (!group_item(g, n_live, plan, w, it)) return;
+        it.j = __builtin_amdgcn_readfirstlane(it.j);
+        it.m0 = __builtin_amdgcn_readfirstlane(it.m0);
+        it.n0 = __builtin_amdgcn_readfirstlane(it.n0);
+        const int mode = g.p[it.j].mode;
+        if (mode == 0) group_tile<0>(g, it, plan, w, smem);
+        else if (mode == 1) group_tile<1>(g, it, plan, w, smem);
+        else group_tile<2>(g, it, plan, w, smem);
+        wait_vmcnt<0>();
+        lds_barrier();          // the stages are free for the block's next item
+    }
+}
+
+// C tile = alpha * (sum of its parts); tiles that were not split have been written already.  A block sums 8 rows of a
+// tile, 4 columns per thread, eight parts in flight.  The grid has 16 blocks for every tile that the plan may hold.
+__global__ __launch_bounds__(256) void gemm_group_reduce_kernel(GroupArgs g) {
+    const int n_live = g.n_dev != nullptr ? max(*g.n_dev, 0) : INT32_MAX;
+    const int plan = *g.plan();
+    if (plan < 0) return;
+    int t = (int)blockIdx.x >> 4, w0 = 0, jj = -1, Mj = 0, parts_j = 1, tm_j = 1, t_j = 0, w_j = 0;
+#pragma unroll
+    for (int j = 0; j < GROUP_MAX; ++j) {
+        int M, K;
+        group_sizes(g.p[j], n_live, M, K);
+        const int tm = cdiv(M, 128), tiles = j < g.np ? tm * cdiv(g.p[j].N, 128) : 0;
+        const int parts = group_parts(K, plan);
+        if (jj < 0 && t < tiles) { jj = j; Mj = M; parts_j = parts; tm_j = tm; t_j = t; w_j = w0; }
+        t -= tiles;
+        w0 += tiles * parts;
+    }
+    if (jj < 0 || parts_j == 1) return;
+    const GemmGroupProb& p = g.p[jj];
+    const int row = ((int)blockIdx.x & 15) * 8 + ((int)threadIdx.x >> 5), col = ((int)threadIdx.x & 31) * 4;
+    const int m = (t_j % tm_j) * 128 + row, n = (t_j / tm_j) * 128 + col;
+    if (m >= Mj || n >= p.N) return;            // N is a multiple of 8
+    const float* src = g.slots + (int64_t)(w_j + t_j * parts_j) * (128 * 128) + row * 128 + col;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
+    for (int k = 0; k < parts_j; ++k) {
+        const float4 v = *reinterpret_cast<const float4*>(src + (int64_t)k * (128 * 128));
+        s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    }
+    uint2 o;
+    o.x = pack_bf16x2(p.alpha * s.x, p.alpha * s.y);
+    o.y = pack_bf16x2(p.alpha * s.z, p.alpha * s.w);
+    *reinterpret_cast<uint2*>(static_cast<bf16_t*>(p.C) + (int64_t)m * p.N + n) = o;
 }
 
 // ---------------------------------------------------------------------------
@@ -942,8 +1055,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
     const int tiles_m = (g.M + 63) / 64;        // of the upper bound: the grid was sized for it
     const int m0 = (blockIdx.x % tiles_m) * 64, n0 = (blockIdx.x / tiles_m) * 64;
     if (g.n_dev != nullptr) {
-        const int n = live_rows(MODE == 0 ? g.M : g.K[0], g.n_dev);
-        if (MODE == 0) g.M = n;
+        const int n = live_rows(MODE != 1 ? g.M : g.K[0], g.n_dev);
+        if (MODE != 1) g.M = n;
         else g.K[0] = n;
         if (m0 >= g.M) return;
     }
@@ -958,12 +1071,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
             for (int i = 0; i < 4; ++i) {
                 const int e = tid + 256 * i;      // 0..1023
                 int kk, r;
-                if (MODE == 0) { kk = e & 15; r = e >> 4; } else { r = e & 63; kk = e >> 6; }
+                if (MODE != 1) { kk = e & 15; r = e >> 4; } else { r = e & 63; kk = e >> 6; }
                 const bool ka = k0 + kk < K;
                 float av = 0.f, bv = 0.f;
                 if (ka && m0 + r < g.M) {
                     const int64_t arow = (MODE == 0 && s == 0 && g.a_idx != nullptr) ? g.a_idx[m0 + r] : m0 + r;
-                    av = MODE == 0 ? A[arow * K + k0 + kk] : A[(int64_t)(k0 + kk) * g.M + m0 + r];
+                    av = MODE != 1 ? A[arow * K + k0 + kk] : A[(int64_t)(k0 + kk) * g.M + m0 + r];
                 }
                 if (ka && n0 + r < g.N)
                     bv = MODE == 0 ? B[(int64_t)(n0 + r) * K + k0 + kk] : B[(int64_t)(k0 + kk) * g.N + n0 + r];
@@ -1000,37 +1113,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
 }
 
 
-// Number of K parts for a split-K launch (0: use the ordinary kernel) and the K range of a part.
-// Splitting pays when the 128x128 tiles cover at most half of the CUs and K is long enough that
-// every part still runs several K-steps.
-static int plan_splitk(const GemmArgs& g, int n_cu, size_t ws_bytes, int& kchunk) {
-    if (g.nseg != 1 || g.ngroups > 1 || g.c_f32) return 0;
-    const int K = g.K[0];
-    const int tiles = ceil_div(g.M, 128) * ceil_div(g.N, 128);
-    if (tiles * 2 > n_cu || K < 1024) return 0;
-    const size_t per_part = (size_t)g.M * g.N * sizeof(float);
-    int parts = std::min(std::min(n_cu / tiles, K / 256), 32);
-    parts = (int)std::min<size_t>((size_t)parts, ws_bytes / per_part);
-    if (parts < 2) return 0;
-    kchunk = ceil_div(ceil_div(K, parts), 64) * 64;
-    return ceil_div(K, kchunk);
-}
-
-template <int MODE>
-static hipError_t launch_bf16_splitk(GemmArgs& g, int parts, int kchunk, float* partial, hipStream_t st) {
-    static std::atomic<uint64_t> lds_ok{0};
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_bf16_splitk_kernel<MODE>), GEMM_SMEM, lds_ok);
-    if (e != hipSuccess) return e;
-    const dim3 grid(ceil_div(g.M, 128) * ceil_div(g.N, 128), parts);
-    gemm_bf16_splitk_kernel<MODE><<<grid, 256, GEMM_SMEM, st>>>(g, partial, kchunk);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int64_t mn = (int64_t)g.M * g.N;
-    splitk_reduce_kernel<<<(unsigned)ceil_div(mn / 8, (int64_t)256), 256, 0, st>>>(
-        partial, static_cast<bf16_t*>(g.C), mn, parts, g.alpha, g.beta, MODE == 0 ? g.n_dev : nullptr, g.N);
-    return hipGetLastError();
-}
-
 template <int MODE>
 static hipError_t launch_bf16(GemmArgs& g, hipStream_t st) {
     static std::atomic<uint64_t> lds_ok{0}, lds_ok_f32{0};
@@ -1047,10 +1129,11 @@ static hipError_t launch_bf16(GemmArgs& g, hipStream_t st) {
 }
 
 hipError_t launch_gemm(int dtype, int mode, const GemmSeg* segs, int nseg, void* C, int M, int N,
-                       float beta, hipStream_t st, float alpha, void* splitk_ws, size_t splitk_bytes,
-                       bool c_f32, const int32_t* n_dev, const int32_t* a_idx, int64_t a_rows) {
+                       float beta, hipStream_t st, bool c_f32, const int32_t* n_dev, const int32_t* a_idx,
+                       int64_t a_rows) {
     if (M <= 0 || N <= 0) return hipSuccess;
     if (a_idx != nullptr && (mode != 0 || a_rows <= 0)) return hipErrorInvalidValue;
+    if (nseg > MAX_SEG) return hipErrorInvalidValue;
     GemmArgs g;
     g.nseg = 0;
     for (int s = 0; s < nseg; ++s) {
@@ -1060,8 +1143,8 @@ hipError_t launch_gemm(int dtype, int mode, const GemmSeg* segs, int nseg, void*
         g.K[g.nseg] = segs[s].K;
         ++g.nseg;
     }
-    for (int s = g.nseg; s < 3; ++s) { g.A[s] = nullptr; g.B[s] = nullptr; g.K[s] = 0; }
-    g.C = C; g.M = M; g.N = N; g.beta = beta; g.alpha = alpha; g.n_full = 0; g.sub = 1; g.tile_n = 256;
+    for (int s = g.nseg; s < MAX_SEG; ++s) { g.A[s] = nullptr; g.B[s] = nullptr; g.K[s] = 0; }
+    g.C = C; g.M = M; g.N = N; g.beta = beta; g.alpha = 1.f; g.n_full = 0; g.sub = 1; g.tile_n = 256;
     g.c_f32 = (c_f32 && dtype == CF_BF16) ? 1 : 0;
     g.ngroups = 1;
     for (int j = 0; j < 3; ++j) { g.Bg[j] = nullptr; g.Cg[j] = nullptr; g.Ng[j] = 0; }
@@ -1087,13 +1170,6 @@ hipError_t launch_gemm(int dtype, int mode, const GemmSeg* segs, int nseg, void*
         if (mode == 0) gemm_f32_kernel<0><<<grid, 256, 0, st>>>(g);
         else gemm_f32_kernel<1><<<grid, 256, 0, st>>>(g);
         return hipGetLastError();
-    }
-    if (splitk_ws != nullptr && a_idx == nullptr) {
-        int kchunk = 0;
-        const int parts = plan_splitk(g, compute_units(), splitk_bytes, kchunk);
-        if (parts >= 2)
-            return mode == 0 ? launch_bf16_splitk<0>(g, parts, kchunk, static_cast<float*>(splitk_ws), st)
-                             : launch_bf16_splitk<1>(g, parts, kchunk, static_cast<float*>(splitk_ws), st);
     }
     return mode == 0 ? launch_bf16<0>(g, st) : launch_bf16<1>(g, st);
 }
@@ -1123,11 +1199,58 @@ hipError_t launch_gemm_tn_groups(const void* A, int K, int M, int ngroups, const
         if (((int64_t)M + 256) * Ng[j] * 2 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     g.ngroups = ngroups;
     g.A[0] = A; g.B[0] = Bg[0]; g.K[0] = K; g.nseg = 1;
-    for (int s = 1; s < 3; ++s) { g.A[s] = nullptr; g.B[s] = nullptr; g.K[s] = 0; }
+    for (int s = 1; s < MAX_SEG; ++s) { g.A[s] = nullptr; g.B[s] = nullptr; g.K[s] = 0; }
     g.C = Cg[0]; g.M = M; g.N = N; g.beta = beta; g.alpha = 1.f; g.n_full = 0; g.sub = 1; g.tile_n = 256;
     g.c_f32 = c_f32 ? 1 : 0;
     g.n_dev = n_dev; g.a_idx = nullptr; g.a_rows = 0;
     return launch_bf16<1>(g, st);
+}
+
+size_t gemm_group_slot_bytes() { return (size_t)compute_units() * 128 * 128 * sizeof(float) + 256; }
+
+hipError_t launch_gemm_group(int dtype, const GemmGroupProb* probs, int np, hipStream_t st, float* slots,
+                             const int32_t* n_dev) {
+    if (np < 1 || np > GROUP_MAX) return hipErrorInvalidValue;
+    if (dtype == CF_F32) {
+        for (int j = 0; j < np; ++j) {
+            const GemmGroupProb& p = probs[j];
+            GemmArgs g{};
+            g.A[0] = p.A; g.B[0] = p.B; g.K[0] = p.K; g.nseg = 1; g.C = p.C; g.M = p.M; g.N = p.N; g.alpha = p.alpha;
+            g.ngroups = 1; g.n_dev = n_dev;
+            const int grid = ceil_div(p.M, 64) * ceil_div(p.N, 64);
+            if (p.mode == 0) gemm_f32_kernel<0><<<grid, 256, 0, st>>>(g);
+            else if (p.mode == 1) gemm_f32_kernel<1><<<grid, 256, 0, st>>>(g);
+            else gemm_f32_kernel<2><<<grid, 256, 0, st>>>(g);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    GroupArgs g{};
+    int64_t tiles = 0;
+    for (int j = 0; j < np; ++j) {
+        const GemmGroupProb& p = probs[j];
+        if (p.M <= 0 || p.N <= 0 || p.K <= 0) return hipErrorInvalidValue;
+        if ((int64_t)p.M * p.K * 2 >= ((int64_t)1 << 31) || (int64_t)p.N * p.K * 2 >= ((int64_t)1 << 31) ||
+            ((int64_t)p.M + 256) * p.N * 2 >= ((int64_t)1 << 31))
+            return hipErrorInvalidValue;
+        g.p[j] = p;
+        tiles += (int64_t)ceil_div(p.M, 128) * ceil_div(p.N, 128);
+    }
+    g.np = np; g.n_cu = compute_units(); g.n_dev = n_dev; g.slots = slots;
+    static std::atomic<uint64_t> lds_ok{0};
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_group_kernel), GEMM_SMEM, lds_ok);
+    if (e != hipSuccess) return e;
+    // a live count below the bound may be split although the bound is not: the launches are sized for either
+    const bool may_split = slots != nullptr && (n_dev != nullptr || group_plan_host(g, INT32_MAX) >= 0);
+    const int grid = (int)(may_split ? g.n_cu : std::min<int64_t>(tiles, g.n_cu));
+    gemm_group_kernel<<<grid, 256, GEMM_SMEM, st>>>(g);
+    e = hipGetLastError();
+    if (e != hipSuccess || !may_split) return e;
+    // a plan with parts has at most n_cu items, so at most n_cu / 2 of its tiles are split; whole ones count too
+    const int rtiles = (int)std::min<int64_t>(tiles, g.n_cu);
+    gemm_group_reduce_kernel<<<16 * rtiles, 256, 0, st>>>(g);
+    return hipGetLastError();
 }
 
 }  // namespace cf

@@ -60,64 +60,10 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(const T* d_act,
     }
 }
 
-static constexpr int RMS_MAX_VEC = 8;   // 16-byte vectors per thread: H <= 256*8*VN
-
-__device__ __forceinline__ void block_sum2(float& a, float& b, float* red /*8 floats*/) {
-    a = wave_sum(a);
-    b = wave_sum(b);
-    const int wave = threadIdx.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) { red[wave] = a; red[4 + wave] = b; }
-    __syncthreads();
-    a = red[0] + red[1] + red[2] + red[3];
-    b = red[4] + red[5] + red[6] + red[7];
-}
-
-// h[j,:] = x[row,:] * rstd * g,  rstd = (mean(x^2) + eps)^-1/2
-template <typename T>
-__global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const T* __restrict__ x,
-                                                          const T* __restrict__ g,
-                                                          const int32_t* __restrict__ idx,
-                                                          int n_max, const int32_t* __restrict__ n_dev, int H, float eps,
-                                                          T* __restrict__ h) {
-    constexpr int VN = Vec<T>::N;
-    __shared__ float red[8];
-    const int n_rows = live_rows(n_max, n_dev);
-    const int vpr = H / VN;
-    for (int j = blockIdx.x; j < n_rows; j += gridDim.x) {
-        const int64_t row = idx ? idx[j] : j;
-        float xv[RMS_MAX_VEC][VN];
-        float ss = 0.f, dummy = 0.f;
-#pragma unroll
-        for (int i = 0; i < RMS_MAX_VEC; ++i) {
-            const int v = threadIdx.x + i * 256;
-            if (v < vpr) {
-                Vec<T>::load(x + row * H + v * VN, xv[i]);
-#pragma unroll
-                for (int e = 0; e < VN; ++e) ss += xv[i][e] * xv[i][e];
-            }
-        }
-        block_sum2(ss, dummy, red);
-        const float rstd = rsqrtf(ss / (float)H + eps);
-#pragma unroll
-        for (int i = 0; i < RMS_MAX_VEC; ++i) {
-            const int v = threadIdx.x + i * 256;
-            if (v < vpr) {
-                float gv[VN], o[VN];
-                Vec<T>::load(g + v * VN, gv);
-#pragma unroll
-                for (int e = 0; e < VN; ++e) o[e] = xv[i][e] * rstd * gv[e];
-                Vec<T>::store(h + (int64_t)j * H + v * VN, o);
-            }
-        }
-    }
-}
-
 // dx_out[j,:] = res[j,:] + rstd*(u - n*mean(u*n)),  n = x*rstd, u = dh*g
 // dg_partial[block,:] = sum over the block's rows of dh*n
-// h_out (nullable): h_out[j,:] = n*g, the normalised row itself (what rmsnorm_fwd_kernel computes, with
-// the same arithmetic): the parameter-gradient GEMMs of the linears behind this norm need it as an
-// operand, and the row and its rstd are in registers here anyway.
+// h_out (nullable): h_out[j,:] = n*g, the normalised row itself: the parameter-gradient GEMMs of the linears behind
+// this norm need it as an operand, and the row and its rstd are in registers here anyway.
 // A block owns one row at a time, NV 16-byte vectors per thread, and works on two rows per
 // iteration so that the loads of the second row overlap the reduction of the first; every
 // load of an iteration (x, dh, res of both rows) is issued before the first reduction.
@@ -300,15 +246,17 @@ __global__ __launch_bounds__(256) void attn_rowdot_kernel(const T* __restrict__ 
 
 // Transposed rotary rotation, in place: for i < d/2 and c = cos[pos,i], s = sin[pos,i]
 //   dx[i] = dy[i]*c + dy[i+d/2]*s,   dx[i+d/2] = dy[i+d/2]*c - dy[i]*s
+// of the hq heads of a row of gq and the hk heads of a row of gk (one launch: the smallest kernel costs 5 us).
 // One thread per vector of VN frequencies of one (row, head); d/2 is a multiple of VN.
 template <typename T>
-__global__ __launch_bounds__(256) void rope_bwd_kernel(T* __restrict__ g, const int32_t* __restrict__ idx,
-                                                       int n_max, const int32_t* __restrict__ n_dev, int heads, int d, int S,
+__global__ __launch_bounds__(256) void rope_bwd_kernel(T* __restrict__ gq, int hq, T* __restrict__ gk, int hk,
+                                                       const int32_t* __restrict__ idx,
+                                                       int n_max, const int32_t* __restrict__ n_dev, int d, int S,
                                                        const float* __restrict__ cs,
                                                        const float* __restrict__ sn) {
     constexpr int VN = Vec<T>::N;
     const int n_rows = live_rows(n_max, n_dev);
-    const int half = d / 2, vph = half / VN;            // vectors per head half
+    const int half = d / 2, vph = half / VN, heads = hq + hk;           // vph: vectors per head half
     const int64_t total = (int64_t)n_rows * heads * vph;
     for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
         const int iv = (int)(t % vph);
@@ -316,15 +264,18 @@ __global__ __launch_bounds__(256) void rope_bwd_kernel(T* __restrict__ g, const 
         const int h = (int)(rh % heads);
         const int64_t j = rh / heads;
         const int pos = (int)((idx ? (int64_t)idx[j] : j) % S);
-        T* p = g + (j * heads + h) * d + iv * VN;
-        float lo[VN], hi[VN], olo[VN], ohi[VN];
+        T* p = (h < hq ? gq + (j * hq + h) * d : gk + (j * hk + (h - hq)) * d) + iv * VN;
+        float lo[VN], hi[VN], olo[VN], ohi[VN], c[VN], s[VN];
         Vec<T>::load(p, lo);
         Vec<T>::load(p + half, hi);
+        const float* pc = cs + (int64_t)pos * half + iv * VN;
+        const float* ps = sn + (int64_t)pos * half + iv * VN;
+#pragma unroll
+        for (int e = 0; e < VN; ++e) { c[e] = pc[e]; s[e] = ps[e]; }
 #pragma unroll
         for (int e = 0; e < VN; ++e) {
-            const float c = cs[(int64_t)pos * half + iv * VN + e], s = sn[(int64_t)pos * half + iv * VN + e];
-            olo[e] = lo[e] * c + hi[e] * s;
-            ohi[e] = hi[e] * c - lo[e] * s;
+            olo[e] = lo[e] * c[e] + hi[e] * s[e];
+            ohi[e] = hi[e] * c[e] - lo[e] * s[e];
         }
         Vec<T>::store(p, olo);
         Vec<T>::store(p + half, ohi);
@@ -357,20 +308,6 @@ hipError_t launch_swiglu_bwd(int dtype, const void* d_act, const void* gate, con
     return hipGetLastError();
 }
 
-hipError_t launch_rmsnorm_fwd(int dtype, const void* x, const void* g, const int32_t* idx,
-                              RowCount rows, int H, float eps, void* h, hipStream_t st) {
-    const int n_rows = rows.n;
-    if (n_rows <= 0) return hipSuccess;
-    const int grid = n_rows < 256 * 16 ? n_rows : 256 * 16;
-    if (dtype == CF_F32)
-        rmsnorm_fwd_kernel<float><<<grid, 256, 0, st>>>((const float*)x, (const float*)g, idx,
-                                                        n_rows, rows.dev, H, eps, (float*)h);
-    else
-        rmsnorm_fwd_kernel<bf16_t><<<grid, 256, 0, st>>>((const bf16_t*)x, (const bf16_t*)g, idx,
-                                                         n_rows, rows.dev, H, eps, (bf16_t*)h);
-    return hipGetLastError();
-}
-
 int rmsnorm_bwd_blocks(int n_rows) {
     return n_rows < 1 ? 1 : rmsnorm_bwd_nblk(n_rows);
 }
@@ -395,33 +332,35 @@ hipError_t launch_rmsnorm_bwd(int dtype, const void* dh, const void* x, const vo
                               void* h_out) {
     const int n_rows = rows.n;
     const int nblk = rmsnorm_bwd_blocks(n_rows);
-    if (n_rows <= 0) return dg_acc_f32 ? hipSuccess : launch_fill_zero(dg_out, (size_t)H * dtype_size(dtype), st);
+    if (n_rows <= 0) return dg_acc_f32 || dg_out == nullptr ? hipSuccess : launch_fill_zero(dg_out, (size_t)H * dtype_size(dtype), st);
     const int vn = dtype == CF_F32 ? 4 : 8;
-    const int nv = ceil_div(H / vn, 256);           // 16-byte vectors per thread (<= RMS_MAX_VEC, checked by the API)
+    const int nv = ceil_div(H / vn, 256);           // 16-byte vectors per thread (at most 8, checked by the API)
     const int fin = ceil_div(H, 32);
     if (dtype == CF_F32) {
         rmsnorm_bwd_dispatch<float>(nv, nblk, st, dh, x, g, idx, res, rows, H, eps, dx_out, dg_partial, h_out);
+        if (dg_out == nullptr) return hipGetLastError();
         if (dg_acc_f32) colsum_finish_kernel<float, true><<<fin, 256, 0, st>>>(dg_partial, n_rows, rows.dev, H, (float*)dg_out);
         else colsum_finish_kernel<float><<<fin, 256, 0, st>>>(dg_partial, n_rows, rows.dev, H, (float*)dg_out);
     } else {
         rmsnorm_bwd_dispatch<bf16_t>(nv, nblk, st, dh, x, g, idx, res, rows, H, eps, dx_out, dg_partial, h_out);
+        if (dg_out == nullptr) return hipGetLastError();
         if (dg_acc_f32) colsum_finish_kernel<float, true><<<fin, 256, 0, st>>>(dg_partial, n_rows, rows.dev, H, (float*)dg_out);
         else colsum_finish_kernel<bf16_t><<<fin, 256, 0, st>>>(dg_partial, n_rows, rows.dev, H, (bf16_t*)dg_out);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_rope_bwd(int dtype, void* g, const int32_t* idx, RowCount rows, int heads, int d, int S,
+hipError_t launch_rope_bwd(int dtype, void* gq, int hq, void* gk, int hk, const int32_t* idx, RowCount rows, int d, int S,
                            const float* cos, const float* sin, hipStream_t st) {
     const int n_rows = rows.n;
     if (n_rows <= 0) return hipSuccess;
     const int vn = dtype == CF_F32 ? 4 : 8;
     if ((d / 2) % vn != 0) return hipErrorInvalidValue;
-    const int64_t total = (int64_t)n_rows * heads * (d / 2 / vn);
+    const int grid = stream_grid((int64_t)n_rows * (hq + hk) * (d / 2 / vn));
     if (dtype == CF_F32)
-        rope_bwd_kernel<float><<<stream_grid(total), 256, 0, st>>>((float*)g, idx, n_rows, rows.dev, heads, d, S, cos, sin);
+        rope_bwd_kernel<float><<<grid, 256, 0, st>>>((float*)gq, hq, (float*)gk, hk, idx, n_rows, rows.dev, d, S, cos, sin);
     else
-        rope_bwd_kernel<bf16_t><<<stream_grid(total), 256, 0, st>>>((bf16_t*)g, idx, n_rows, rows.dev, heads, d, S, cos, sin);
+        rope_bwd_kernel<bf16_t><<<grid, 256, 0, st>>>((bf16_t*)gq, hq, (bf16_t*)gk, hk, idx, n_rows, rows.dev, d, S, cos, sin);
     return hipGetLastError();
 }
 

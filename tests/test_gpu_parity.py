@@ -714,6 +714,8 @@ LORA_SHAPES = {
     # long enough contractions (H, Hq*d and the kept-token count above 1024) for the adapter products
     # to take the split-K path, with ragged K ranges
     "splitk": dict(B=2, S=640, H=1024, Hq=16, Hkv=4, d=64, F=512),
+    # with every token kept 4 x 65 row tiles in one grouped launch: nothing is split and blocks take a second item
+    "rows": dict(B=5, S=1664, H=128, Hq=2, Hkv=1, d=64, F=128),
 }
 
 
@@ -721,7 +723,9 @@ LORA_SHAPES = {
                                                    ("bf16", "independent", 16, "small"),
                                                    ("bf16", "independent", 64, "small"),
                                                    ("bf16", "independent", 64, "splitk"),
-                                                   ("bf16", "independent", 24, "splitk")])
+                                                   ("bf16", "independent", 24, "splitk"),
+                                                   ("bf16", "independent", 136, "splitk"),
+                                                   ("bf16", "independent", 8, "rows")])
 def test_layer_lora(dtype, mode, rank, which):
     """Adapters on q, k, v, o with frozen base weights: adapter gradients and compact dx against
     the oracle, filtered and with every token kept."""
