@@ -46,7 +46,11 @@ static constexpr float LOG2E = 1.4426950408889634f;
 
 struct AttnParams {
     const bf16_t *q_kept, *k_full, *v_full, *do_kept;
-    const float* stat;             // [2][Hq][n_kept]: log2(e)*LSE and D = rowsum(dO*O) of every kept row and head
+    float* stat;                   // [2][Hq][n_kept]: log2(e)*LSE and D = rowsum(dO*O) of every kept row and head
+    // The attention output's kept rows; when set, the dQ kernel forms the row terms from them and writes stat (the dK/dV
+    // kernel behind it loads 64 rows of a head at a time).  Null: attn_stats_kernel has written stat already.
+    const bf16_t* o_kept;
+    const float* lse_full;
     const int32_t *idx, *cu_kept;
     bf16_t *dq_kept, *dk_kept, *dv_kept;
     float *dk_part, *dv_part;      // [G/hp][n_kept][Hkv*d] fp32 partials, one per block of hp query heads (G > hp only)
@@ -160,22 +164,56 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
     const int j0 = seq_begin + qt * 128;
     const int rows_in_tile = min(128, cnt - qt * 128);
 
-    // this lane's query
+    // This lane's query: its fragments and its row terms.  D = rowsum(dO*O) is formed here, from the dO fragments that
+    // the kernel holds anyway, unless a pass before had to read O for its compact copy (a pass of its own over dO and O
+    // costs 16 us where the dQ kernel gets 6 us slower: [4096 rows, 32 heads, d = 128], 206 us).
     const int jq = j0 + wave * 32 + slot;
     const bool qvalid = wave * 32 + slot < rows_in_tile;
     const int pos = qvalid ? (p.idx ? p.idx[jq] : jq) - b * p.S : -1;
-    const float lse2 = qvalid ? p.stat[(int64_t)h * p.n_kept + jq] : 0.f;
-    const float Dq = qvalid ? p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq] : 0.f;
+    float lse2 = 0.f, Dq = 0.f;
     bf16x8_t qf[KS], dof[KS];
+    const int64_t off_q = (int64_t)jq * Nq + h * D + hh * 8;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
         uint4 a = make_uint4(0, 0, 0, 0), c = make_uint4(0, 0, 0, 0);
         if (qvalid) {
-            a = *reinterpret_cast<const uint4*>(p.q_kept + (int64_t)jq * Nq + h * D + ks * 16 + hh * 8);
-            c = *reinterpret_cast<const uint4*>(p.do_kept + (int64_t)jq * Nq + h * D + ks * 16 + hh * 8);
+            a = *reinterpret_cast<const uint4*>(p.q_kept + off_q + ks * 16);
+            c = *reinterpret_cast<const uint4*>(p.do_kept + off_q + ks * 16);
         }
         qf[ks] = __builtin_bit_cast(bf16x8_t, a);
         dof[ks] = __builtin_bit_cast(bf16x8_t, c);
+    }
+    if (p.o_kept != nullptr) {
+        // summed in the order of attn_stats_kernel, so that both give the same bits: 8 columns in sequence, then a tree
+        if (qvalid) {
+            float part[KS];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                part[ks] = 0.f;
+                const uint4 o = *reinterpret_cast<const uint4*>(p.o_kept + off_q + ks * 16);
+                const uint4 c = __builtin_bit_cast(uint4, dof[ks]);
+                const unsigned ow[4] = {o.x, o.y, o.z, o.w}, cw[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    part[ks] += __uint_as_float(cw[e] << 16) * __uint_as_float(ow[e] << 16);
+                    part[ks] += __uint_as_float(cw[e] & 0xFFFF0000u) * __uint_as_float(ow[e] & 0xFFFF0000u);
+                }
+            }
+#pragma unroll
+            for (int o = KS / 2; o > 0; o >>= 1)
+#pragma unroll
+                for (int ks = 0; ks < o; ++ks) part[ks] += part[ks + o];
+            Dq = part[0];
+            lse2 = p.lse_full[((int64_t)b * p.Hq + h) * p.S + pos] * LOG2E;
+        }
+        Dq += __shfl_xor(Dq, 32, 64);           // the other half of the row's columns
+        if (qvalid && hh == 0) {
+            p.stat[(int64_t)h * p.n_kept + jq] = lse2;
+            p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq] = Dq;
+        }
+    } else if (qvalid) {
+        lse2 = p.stat[(int64_t)h * p.n_kept + jq];
+        Dq = p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq];
     }
     const int jlast = j0 + rows_in_tile - 1;
     const int maxpos = (p.idx ? p.idx[jlast] : jlast) - b * p.S;
@@ -713,12 +751,12 @@ __global__ __launch_bounds__(256) void attn_dkv_reduce_kernel(const float* __res
 // stat[0][h][j] = log2(e) * LSE(b, h, position of kept row j); stat[1][h][j] = D = sum_c dO*O of
 // (row j, head h): the row terms of the FlashAttention backward, laid out so that the 64 rows a
 // dK/dV block needs per step are contiguous.  d/8 lanes share one (row, head).
-// o_full / q_full (nullable, need idx): the attention output and the queries are still stored full
-// length; the pass reads their kept rows through idx and writes the compact copies o_out / q_out
+// Only launched where the attention output and the queries are still stored full length (o_full, q_full, with idx):
+// the pass reads their kept rows through idx and writes the compact copies o_out / q_out
 // that the parameter-gradient GEMM of the output projection and the attention kernels' tile loads
-// use (the gathers of the two tensors folded into this read).
+// use (the gathers of the two tensors folded into this read).  In the dQ kernel, whose lanes hold 32-byte pieces of a
+// row, the copies cost 35 us more where this pass takes 37 (4096 rows, 32 heads, d = 128).
 __global__ __launch_bounds__(256) void attn_stats_kernel(const bf16_t* __restrict__ do_kept,
-                                                         const bf16_t* __restrict__ o_rows,
                                                          const float* __restrict__ lse_full,
                                                          const int32_t* __restrict__ idx, int n_max,
                                                          const int32_t* __restrict__ n_dev,
@@ -735,20 +773,15 @@ __global__ __launch_bounds__(256) void attn_stats_kernel(const bf16_t* __restric
         const int part = (int)(gid % lanes);
         float a[8], b[8];
         Vec<bf16_t>::load(do_kept + pair * d + part * 8, a);
-        if (o_full != nullptr) {
-            const int64_t src = ((int64_t)idx[pair / Hq] * Hq + pair % Hq) * d + part * 8;
-            const uint4 ov = *reinterpret_cast<const uint4*>(o_full + src);
-            *reinterpret_cast<uint4*>(o_out + pair * d + part * 8) = ov;
-            if (q_full != nullptr)
-                *reinterpret_cast<uint4*>(q_out + pair * d + part * 8) = *reinterpret_cast<const uint4*>(q_full + src);
-            const unsigned w[4] = {ov.x, ov.y, ov.z, ov.w};
+        const int64_t src = ((int64_t)idx[pair / Hq] * Hq + pair % Hq) * d + part * 8;
+        const uint4 ov = *reinterpret_cast<const uint4*>(o_full + src);
+        *reinterpret_cast<uint4*>(o_out + pair * d + part * 8) = ov;
+        *reinterpret_cast<uint4*>(q_out + pair * d + part * 8) = *reinterpret_cast<const uint4*>(q_full + src);
+        const unsigned w[4] = {ov.x, ov.y, ov.z, ov.w};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                b[2 * i] = __uint_as_float(w[i] << 16);
-                b[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
-            }
-        } else {
-            Vec<bf16_t>::load(o_rows + pair * d + part * 8, b);
+        for (int i = 0; i < 4; ++i) {
+            b[2 * i] = __uint_as_float(w[i] << 16);
+            b[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
         }
 #pragma unroll
         for (int e = 0; e < 8; ++e) s += a[e] * b[e];
@@ -756,7 +789,7 @@ __global__ __launch_bounds__(256) void attn_stats_kernel(const bf16_t* __restric
     for (int o = lanes >> 1; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
     if (gid < total && (gid % lanes) == 0) {
         const int j = (int)(pair / Hq), h = (int)(pair % Hq);
-        const int64_t tok = idx ? idx[j] : j;
+        const int64_t tok = idx[j];
         const int64_t bb = tok / S, pos = tok - bb * S;
         stat[(int64_t)h * n_max + j] = lse_full[(bb * Hq + h) * S + pos] * LOG2E;
         stat[(int64_t)(Hq + h) * n_max + j] = s;
@@ -774,8 +807,8 @@ size_t attn_mfma_partial_bytes(const cf_layer_desc& L, int n_kept) {
 }
 
 template <int D>
-static hipError_t launch_t(const AttnParams& p, const bf16_t* o_rows, const float* lse_full, float* stat,
-                           const bf16_t* o_full, bf16_t* o_out, const bf16_t* q_full, bf16_t* q_out, hipStream_t st) {
+static hipError_t launch_t(const AttnParams& p, const bf16_t* o_full, bf16_t* o_out, const bf16_t* q_full, bf16_t* q_out,
+                           hipStream_t st) {
     constexpr int smem_dq = 2 * 2 * 64 * D * 2;
     constexpr int smem_dkv = 4 * (2 * 64 * D * 2 + 512);
     static std::atomic<uint64_t> lds_ok_dq{0}, lds_ok_dkv{0};
@@ -784,11 +817,10 @@ static hipError_t launch_t(const AttnParams& p, const bf16_t* o_rows, const floa
     e = allow_dynamic_lds(reinterpret_cast<const void*>(&attn_dkv_kernel<D>), smem_dkv, lds_ok_dkv);
     if (e != hipSuccess) return e;
     const int n_kept = p.n_kept;        // grids cover the upper bound of the row count
-    {
+    if (p.o_kept == nullptr) {
         const int64_t total = (int64_t)n_kept * p.Hq * (D / 8);
-        attn_stats_kernel<<<(int)((total + 255) / 256), 256, 0, st>>>(p.do_kept, o_rows, lse_full, p.idx, n_kept,
-                                                                     p.n_dev, p.Hq, D, p.S, stat, o_full, o_out,
-                                                                     q_full, q_out);
+        attn_stats_kernel<<<(int)((total + 255) / 256), 256, 0, st>>>(p.do_kept, p.lse_full, p.idx, n_kept, p.n_dev, p.Hq, D,
+                                                                     p.S, p.stat, o_full, o_out, q_full, q_out);
     }
     const int max_per_seq = n_kept < p.S ? n_kept : p.S;
     const int tiles = ceil_div(max_per_seq, 128);
@@ -803,7 +835,7 @@ static hipError_t launch_t(const AttnParams& p, const bf16_t* o_rows, const floa
     return hipGetLastError();
 }
 
-// o_full / q_full (both nullable, need idx): attention output and queries at full length; their kept
+// o_full / q_full (null or both set, need idx): attention output and queries at full length; their kept
 // rows are then copied to o_kept / q_kept (which must be writable buffers) by the row-statistics pass.
 hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void* q_kept,
                                 const void* k_full, const void* v_full, const void* o_kept,
@@ -814,7 +846,7 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     AttnParams p;
     const int n_kept = rows.n;
     p.q_kept = (const bf16_t*)q_kept; p.k_full = (const bf16_t*)k_full; p.v_full = (const bf16_t*)v_full;
-    p.do_kept = (const bf16_t*)do_kept; p.stat = stat; p.idx = idx;
+    p.do_kept = (const bf16_t*)do_kept; p.o_kept = o_full ? nullptr : (const bf16_t*)o_kept; p.lse_full = lse_full; p.stat = stat; p.idx = idx;
     p.cu_kept = cu_kept; p.dq_kept = (bf16_t*)dq_kept; p.dk_kept = (bf16_t*)dk_kept;
     p.dv_kept = (bf16_t*)dv_kept; p.B = L.B; p.S = L.S; p.Hq = L.Hq; p.Hkv = L.Hkv; p.scale = scale;
     p.n_kept = n_kept;
@@ -822,13 +854,11 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     p.n_dev = rows.dev;
     p.dk_part = partials;
     p.dv_part = partials ? partials + (size_t)n_kept * L.Hq * L.d : nullptr;
-    bf16_t* o_out = o_full ? (bf16_t*)const_cast<void*>(o_kept) : nullptr;
-    bf16_t* q_out = q_full ? (bf16_t*)const_cast<void*>(q_kept) : nullptr;
-    if (L.d == 64)
-        return launch_t<64>(p, (const bf16_t*)o_kept, lse_full, stat, (const bf16_t*)o_full, o_out,
-                            (const bf16_t*)q_full, q_out, st);
-    return launch_t<128>(p, (const bf16_t*)o_kept, lse_full, stat, (const bf16_t*)o_full, o_out,
-                         (const bf16_t*)q_full, q_out, st);
+    bf16_t* o_out = (bf16_t*)const_cast<void*>(o_kept);
+    bf16_t* q_out = (bf16_t*)const_cast<void*>(q_kept);
+    if ((o_full != nullptr) != (q_full != nullptr) || (o_full != nullptr && idx == nullptr)) return hipErrorInvalidValue;
+    return L.d == 64 ? launch_t<64>(p, (const bf16_t*)o_full, o_out, (const bf16_t*)q_full, q_out, st)
+                     : launch_t<128>(p, (const bf16_t*)o_full, o_out, (const bf16_t*)q_full, q_out, st);
 }
 
 }  // namespace cf
