@@ -275,6 +275,13 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
             const void* Bg[3] = {w.dq, w.dk, w.dv};
             void* Cg[3] = {G.dwq, G.dwk, G.dwv};
             CF_HIP(launch_gemm_tn_groups(h1, N, H, 3, Bg, Cg, Ng, st, mg ? 1.f : 0.f, mg, nd));
+        } else if (!mg && dt == CF_BF16 && ceil_div(H, 128) * (ceil_div(Nq, 128) + 2 * ceil_div(Nkv, 128)) <= compute_units()) {
+            // narrow outputs (a tensor-parallel share's heads): 128x128 tiles of all three in one launch that fits one
+            // round of the CUs (H = 4096, 512 + 128 + 128 columns, 841 kept rows: 36 us as three launches, 15 us as one)
+            const GemmGroupProb ps[3] = {{h1, w.dq, G.dwq, H, Nq, N, 1, 1.f},
+                                         {h1, w.dk, G.dwk, H, Nkv, N, 1, 1.f},
+                                         {h1, w.dv, G.dwv, H, Nkv, N, 1, 1.f}};
+            CF_HIP(launch_gemm_group(dt, ps, 3, st, nullptr, nd));
         } else {
             CF_HIP(dw_gemm(h1, w.dq, G.dwq, H, Nq));
             CF_HIP(dw_gemm(h1, w.dk, G.dwk, H, Nkv));
