@@ -506,6 +506,13 @@ cf_status cf_linear_bwd_reduced(const void* x_kept, const void* dy_kept, const v
         (dx_kept && misaligned(dx_kept)) || (dw && misaligned(dw)))
         return CF_ERR_SHAPE;
     hipStream_t st = as_stream(stream);
+    if (dtype == CF_BF16 && dx_kept && dw && n_kept > 0 && dw_beta == 0.f &&
+        ceil_div(in, 128) * (ceil_div(n_kept, 128) + ceil_div(out, 128)) <= compute_units()) {
+        // both products on 128x128 tiles fit one round of the CUs: one launch, and neither waits for the other
+        const GemmGroupProb ps[2] = {{dy_kept, w, dx_kept, n_kept, in, out, 0, 1.f}, {x_kept, dy_kept, dw, in, out, n_kept, 1, 1.f}};
+        CF_HIP(launch_gemm_group(dtype, ps, 2, st));
+        return CF_OK;
+    }
     if (dx_kept && n_kept > 0) {
         GemmSeg seg{dy_kept, w, out};
         CF_HIP(launch_gemm(dtype, 0, &seg, 1, dx_kept, n_kept, in, 0.f, st));
