@@ -54,7 +54,7 @@ struct AttnParams {
     const int32_t *idx, *cu_kept;
     bf16_t *dq_kept, *dk_kept, *dv_kept;
     float *dk_part, *dv_part;      // [G/hp][n_kept][Hkv*d] fp32 partials, one per block of hp query heads (G > hp only)
-    int n_cu;                      // compute units of the device (the dK/dV kernel sizes its blocks' work by it)
+    int n_slots;                   // dK/dV blocks that the device holds at a time (the kernel sizes its blocks' work by it)
     int B, S, Hq, Hkv;
     int n_kept;                    // rows that the compact buffers are laid out for (the stride of stat and of the partials)
     const int32_t* n_dev;          // nullable: the live row count on the device, at most n_kept
@@ -62,14 +62,14 @@ struct AttnParams {
 };
 
 // Query heads of one KV group that a dK/dV block walks through: the largest divisor of the group size G
-// that still leaves about two blocks per CU (a block costs between one and `tiles` steps and blocks are
-// handed out heaviest first, so two per CU already balance); every head more in a block saves that
+// that still leaves about two blocks for every one that the device holds at a time (a block costs between one and `tiles` steps
+// and blocks are handed out heaviest first, so two per slot already balance); every head more in a block saves that
 // block's fixed cost once and one fp32 partial.  A function of the LIVE row count, which only the
 // device may know: the dK/dV blocks and the reduction evaluate it themselves and agree.
-__host__ __device__ inline int attn_heads_per_block(int n_rows, int Hq, int G, int n_cu) {
+__host__ __device__ inline int attn_heads_per_block(int n_rows, int Hq, int G, int n_slots) {
     const int64_t tile_rows = (n_rows + 127) / 128;             // key tiles over all sequences, roughly
     for (int c = G; c > 1; --c)
-        if (G % c == 0 && tile_rows * (Hq / c) >= 2 * (int64_t)n_cu) return c;
+        if (G % c == 0 && tile_rows * (Hq / c) >= 2 * (int64_t)n_slots) return c;
     return 1;
 }
 
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// dK/dV kernel: one (key tile, query head) per block
+// dK/dV kernel (instantiated at d = 128; d = 64 has a kernel of its own below): one key tile and HP query heads per block
 // ---------------------------------------------------------------------------
 // Slot order of an iteration of the kernel's pipeline (2*KS positions, KS "A" slots and KS "C" slots;
 // see the kernel): odd iterations alternate A, C; even iterations put all C slots into the first
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int slot = lane & 31, hh = lane >> 5;
     const int G = p.Hq / p.Hkv;
-    const int HP = attn_heads_per_block(live_rows(p.n_kept, p.n_dev), p.Hq, G, p.n_cu);
+    const int HP = attn_heads_per_block(live_rows(p.n_kept, p.n_dev), p.Hq, G, p.n_slots);
     // The grid is one-dimensional and has a block per (key tile, sequence, query head).  Only nhb * B blocks
     // per key tile are needed; they are numbered first, key tile by key tile (heaviest first), so the blocks
     // without work all come at the end of the launch order instead of between the working ones (a block
@@ -470,7 +470,7 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     // fragments), B(n) = P and dS from them (vector ALU: exp2, mask, products, packing), C(n) = dV and
     // dK (4*NT MFMAs).  A wave runs alone on its SIMD, so nothing overlaps unless the instruction
     // stream interleaves it: ITERATION t issues A(t+1), B(t) and C(t-1) together, one softmax value
-    // (two at d = 64) and the LDS reads of a later slot between two MFMA pairs, so that in the steady
+    // and the LDS reads of a later slot between two MFMA pairs, so that in the steady
     // state the matrix core runs back to back while the exponentials of the half before and the
     // fragment reads of the slots ahead proceed under it.  Fragment reads go through a ring of four
     // register pairs and are issued three slots ahead of their MFMAs, across iteration boundaries
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     // slots read.  Accumulation order of every output element is that of a plain loop over the rows.
     constexpr int NP = 2 * KS;                      // slots per iteration (KS A slots, 2*NT = KS C slots)
     constexpr int VPS = 16 / NP;                    // softmax values per slot
-    constexpr int LOOK = KS >= 8 ? 3 : 2, RING = 4;     // the reads issued for the next iteration must follow the barrier
+    constexpr int LOOK = 3, RING = 4;               // the reads issued for the next iteration must follow the barrier
     static_assert(2 * NT == KS && NP % RING == 0 && (16 % NP) == 0 && NP - LOOK >= 3 * KS / 2, "slot layout");
     typedef __attribute__((address_space(3))) unsigned char* lds_u8_ptr;
     typedef const __attribute__((address_space(3))) u32x4_t* lds_u4_cptr;
@@ -717,14 +717,220 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     }
 }
 
+// ---------------------------------------------------------------------------
+// dK/dV kernel at d = 64: two blocks per CU
+// ---------------------------------------------------------------------------
+// The same work split as attn_dkv_kernel (128 kept keys and HP query heads per block, halves of 32 queries), but at
+// d = 64 accumulators, K/V fragments and scores of a wave take half the registers, so two waves fit a SIMD and
+// overlap each other's matrix, vector and LDS phases; a plain order of the phases is then better than the software pipeline
+// that a lone wave needs: [8192 rows, 32/4 heads, S = 2048] 220 -> 181 us, [1377 rows of 4593, 32/4 heads] 27 -> 23 us
+// against that pipeline at d = 64.  Fragment reads run one MFMA pair ahead.  The accumulation order of every element is that
+// of the pipelined kernel.
+__global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
+    constexpr int D = 64, KS = D / 16, NT = D / 32;
+    constexpr int TILE = 64 * D * 2;
+    constexpr int STAGE = 2 * TILE + 512;       // Q tile, dO tile, lse2[64], D[64]
+    extern __shared__ __align__(16) unsigned char smem[];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int slot = lane & 31, hh = lane >> 5;
+    const int G = p.Hq / p.Hkv;
+    const int HP = attn_heads_per_block(live_rows(p.n_kept, p.n_dev), p.Hq, G, p.n_slots);
+    // block numbering as in attn_dkv_kernel: key tile by key tile, blocks without work last
+    const int nhb = p.Hq / HP, per_tile = nhb * p.B;
+    const int kt = blockIdx.x / per_tile, bx = blockIdx.x % per_tile;
+    if (kt >= (int)gridDim.x / (p.Hq * p.B)) return;
+    const int h0 = (bx % nhb) * HP, b = bx / nhb, g = h0 / G;
+    const int Nq = p.Hq * D, Nkv = p.Hkv * D;
+    int seq_begin, seq_end;
+    seq_range(p, b, seq_begin, seq_end);
+    const int cnt = seq_end - seq_begin;
+    if (kt * 128 >= cnt) return;
+    const int c0 = seq_begin + kt * 128;            // compact row of the tile's first key
+    const int keys_in_tile = min(128, cnt - kt * 128);
+
+    const int jk = c0 + wave * 32 + slot;           // this lane's key
+    const bool kvalid = wave * 32 + slot < keys_in_tile;
+    bf16x8_t kf[KS], vf[KS];
+    {
+        const int64_t tok = kvalid ? (p.idx ? p.idx[jk] : jk) : 0;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            uint4 a = make_uint4(0, 0, 0, 0), c = make_uint4(0, 0, 0, 0);
+            if (kvalid) {
+                a = *reinterpret_cast<const uint4*>(p.k_full + tok * Nkv + g * D + ks * 16 + hh * 8);
+                c = *reinterpret_cast<const uint4*>(p.v_full + tok * Nkv + g * D + ks * 16 + hh * 8);
+            }
+            kf[ks] = __builtin_bit_cast(bf16x8_t, a);
+            vf[ks] = __builtin_bit_cast(bf16x8_t, c);
+        }
+    }
+    const float scale2 = p.scale * LOG2E;
+    const int steps = (seq_end - c0 + 63) / 64;     // query tiles from the first key to the sequence end
+
+    f32x16_t dk[NT], dv[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) { dk[nt][v] = 0.f; dv[nt][v] = 0.f; }
+
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_addr_of(smem));
+    unsigned ra[KS], ta[NT][2];                     // per-lane offsets of the fragment reads inside a tile (see attn_dkv_kernel)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) ra[ks] = (unsigned)tile_off<D>(slot, ks * 2 + hh);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        const int r = 4 * hh + ((lane & 15) >> 2);
+        const int chunk = nt * 4 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+        ta[nt][0] = (unsigned)tile_off<D>(r, chunk) + (lane & 1) * 8;
+        ta[nt][1] = (unsigned)tile_off<D>(r + 8, chunk) + (lane & 1) * 8;
+    }
+    // global -> LDS as in attn_dkv_kernel; rows past the sequence end arrive as zeros
+    constexpr int NCH = D / 8, RPL = 64 / NCH, NLD = 64 / RPL / 4, LPS = 2 * NLD + 2;
+    unsigned voff[NLD];
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+        const int row = (4 * i + wave) * RPL + lane / NCH;
+        const int sw = (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
+        voff[i] = (unsigned)row * (unsigned)(Nq * 2) + (unsigned)(((lane % NCH) ^ sw) << 4);
+    }
+    typedef __attribute__((address_space(3))) unsigned char* lds_u8_ptr;
+    typedef const __attribute__((address_space(3))) u32x4_t* lds_u4_cptr;
+    typedef float f32x4v_t __attribute__((ext_vector_type(4)));
+    typedef const __attribute__((address_space(3))) f32x4v_t* lds_f4_cptr;
+    typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
+
+    bf16x8_t fa[2][2], fc[2][2];
+    auto load_a = [&](unsigned sb, int hf, int ks, int buf) __attribute__((always_inline)) {
+        const lds_u8_ptr q = reinterpret_cast<lds_u8_ptr>(sb + ra[ks]);
+        fa[buf][0] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<lds_u4_cptr>(q + hf * 32 * (D * 2)));
+        fa[buf][1] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<lds_u4_cptr>(q + (TILE + hf * 32 * (D * 2))));
+    };
+    auto load_c = [&](unsigned sb, int hf, int c, int buf) __attribute__((always_inline)) {
+        const lds_u8_ptr lo = reinterpret_cast<lds_u8_ptr>(sb + ta[c % NT][0]);
+        const lds_u8_ptr hi = reinterpret_cast<lds_u8_ptr>(sb + ta[c % NT][1]);
+        const int off = (hf * 32 + 16 * (c / NT)) * (D * 2);
+        const s16x4_t q0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lo + off));
+        const s16x4_t q1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(hi + off));
+        const s16x4_t o0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lo + (TILE + off)));
+        const s16x4_t o1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(hi + (TILE + off)));
+        fc[buf][0] = __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(q0, q1, 0, 1, 2, 3, 4, 5, 6, 7));
+        fc[buf][1] = __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(o0, o1, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    // One step of 64 queries in the stage at sb, whose first query is compact row qrow0
+    auto step = [&](auto MASKED_, const unsigned sb, const int qrow0) __attribute__((always_inline)) {
+        constexpr bool masked = decltype(MASKED_)::value != 0;
+        load_a(sb, 0, 0, 0);
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            f32x16_t st, dpt;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { st[v] = 0.f; dpt[v] = 0.f; }
+            f32x4v_t lq[2], dq[2];                  // log2(e)*LSE and D of four queries at a time, one group ahead
+            const lds_u8_ptr ps = reinterpret_cast<lds_u8_ptr>(sb + 2 * TILE + 16 * hh);
+            auto load_stats = [&](int v4) __attribute__((always_inline)) {
+                lq[v4 & 1] = *reinterpret_cast<lds_f4_cptr>(ps + (hf * 32 + 8 * v4) * 4);
+                dq[v4 & 1] = *reinterpret_cast<lds_f4_cptr>(ps + (64 + hf * 32 + 8 * v4) * 4);
+            };
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                if (ks + 1 < KS) load_a(sb, hf, ks + 1, (ks + 1) & 1);
+                else { load_stats(0); load_c(sb, hf, 0, 0); }
+                CF_SCHED_FENCE();
+                st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks & 1][0], kf[ks], st, 0, 0, 0);
+                dpt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks & 1][1], vf[ks], dpt, 0, 0, 0);
+                CF_SCHED_FENCE();
+            }
+            // P and dS: lane = key, register = query 8*(v/4) + 4*hh + v%4 of the half
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int v4 = v >> 2, e = v & 3;
+                if (e == 0 && v4 < 3) load_stats(v4 + 1);
+                float pr = __builtin_amdgcn_exp2f(st[v] * scale2 - lq[v4 & 1][e]);
+                if (masked) {
+                    const bool ok = kvalid && (qrow0 + hf * 32 + 8 * v4 + 4 * hh + e >= jk);
+                    pr = ok ? pr : 0.f;
+                }
+                st[v] = pr;
+                dpt[v] = pr * (dpt[v] - dq[v4 & 1][e]);
+            }
+            const bf16x8_t ap[2] = {pack8(st, 0), pack8(st, 1)}, ads[2] = {pack8(dpt, 0), pack8(dpt, 1)};
+#pragma unroll
+            for (int c = 0; c < 2 * NT; ++c) {
+                if (c + 1 < 2 * NT) load_c(sb, hf, c + 1, (c + 1) & 1);
+                else if (hf == 0) load_a(sb, 1, 0, 0);
+                CF_SCHED_FENCE();
+                dk[c % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ads[c / NT], fc[c & 1][0], dk[c % NT], 0, 0, 0);
+                dv[c % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ap[c / NT], fc[c & 1][1], dv[c % NT], 0, 0, 0);
+                CF_SCHED_FENCE();
+            }
+        }
+    };
+
+    wait_vmcnt<0>();        // the K and V fragments: the counts below are those of the ring's loads alone
+    const int masked_steps = keys_in_tile < 128 ? steps : min(steps, 2);
+    for (int hi = 0; hi < HP; ++hi) {
+        const int h = h0 + hi;
+        const i32x4_t rsQ = make_rsrc(p.q_kept + (int64_t)c0 * Nq + h * D, ((int64_t)(seq_end - c0) * Nq - h * D) * 2);
+        const i32x4_t rsO = make_rsrc(p.do_kept + (int64_t)c0 * Nq + h * D, ((int64_t)(seq_end - c0) * Nq - h * D) * 2);
+        const i32x4_t rsL = make_rsrc(p.stat + (int64_t)h * p.n_kept + c0, (int64_t)(seq_end - c0) * 4);
+        const i32x4_t rsD = make_rsrc(p.stat + (int64_t)(p.Hq + h) * p.n_kept + c0, (int64_t)(seq_end - c0) * 4);
+        // every wave issues the same loads for every step, also past the end (zero fill), so a step is LPS loads of a wave
+        auto issue_q = [&](int s, int stage) __attribute__((always_inline)) {
+            const unsigned sq = lds0 + stage * STAGE;
+            const unsigned base = (unsigned)(s * 64) * (unsigned)(Nq * 2);
+#pragma unroll
+            for (int i = 0; i < NLD; ++i) dma16(__builtin_amdgcn_readfirstlane(sq + (4 * i + wave) * 1024), rsQ, base + voff[i]);
+#pragma unroll
+            for (int i = 0; i < NLD; ++i) dma16(__builtin_amdgcn_readfirstlane(sq + TILE + (4 * i + wave) * 1024), rsO, base + voff[i]);
+            const unsigned off = (unsigned)(s * 64 + lane) * 4u;
+            dma4(sq + 2 * TILE, rsL, off);
+            dma4(sq + 2 * TILE + 256, rsD, off);
+        };
+        if (hi > 0) lds_barrier();                  // every wave is done with the previous head's stages
+        issue_q(0, 0);
+        issue_q(1, 1);
+        issue_q(2, 2);
+        for (int s = 0; s < steps; ++s) {
+            wait_vmcnt<2 * LPS>();                  // step s has landed; steps s+1 and s+2 may be in flight
+            lds_barrier();                          // ... for every wave, and every wave is done with step s-1
+            issue_q(s + 3, (s + 3) & 3);
+            const unsigned sb = lds0 + (unsigned)(s & 3) * STAGE;
+            if (s < masked_steps) step(ic<1>{}, sb, c0 + s * 64);
+            else step(ic<0>{}, sb, c0 + s * 64);
+        }
+        wait_vmcnt<0>();                            // the zero-fill loads of the steps past the end
+    }
+
+    const bool whole = G == HP;
+    const int64_t part = whole ? 0 : (int64_t)((h0 - g * G) / HP) * p.n_kept * Nkv;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int r = wave * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
+            if (r < keys_in_tile) {
+                const int64_t off = part + (int64_t)(c0 + r) * Nkv + g * D + nt * 32 + slot;
+                if (whole) {
+                    p.dk_kept[off] = f32_to_bf16(dk[nt][v] * p.scale);
+                    p.dv_kept[off] = f32_to_bf16(dv[nt][v]);
+                } else {
+                    p.dk_part[off] = dk[nt][v];
+                    p.dv_part[off] = dv[nt][v];
+                }
+            }
+        }
+    }
+}
+
 // dk = scale * sum_g dk_part[g], dv = sum_g dv_part[g]   (fixed order: deterministic)
 __global__ __launch_bounds__(256) void attn_dkv_reduce_kernel(const float* __restrict__ dk_part,
                                                               const float* __restrict__ dv_part, int Hq, int Hkv,
-                                                              int n_cu, int n_max, const int32_t* __restrict__ n_dev,
+                                                              int n_slots, int n_max, const int32_t* __restrict__ n_dev,
                                                               int Nkv, float scale,
                                                               bf16_t* __restrict__ dk, bf16_t* __restrict__ dv) {
     const int n_live = live_rows(n_max, n_dev);
-    const int hp = attn_heads_per_block(n_live, Hq, Hq / Hkv, n_cu);
+    const int hp = attn_heads_per_block(n_live, Hq, Hq / Hkv, n_slots);
     const int G = Hq / Hkv / hp;                                        // partials per KV group
     if (G == 1) return;                                                 // the dK/dV blocks wrote the results themselves
     const int64_t n_elems = (int64_t)n_max * Nkv;                       // stride between two partials
@@ -814,7 +1020,8 @@ static hipError_t launch_t(const AttnParams& p, const bf16_t* o_full, bf16_t* o_
     static std::atomic<uint64_t> lds_ok_dq{0}, lds_ok_dkv{0};
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&attn_dq_kernel<D>), smem_dq, lds_ok_dq);
     if (e != hipSuccess) return e;
-    e = allow_dynamic_lds(reinterpret_cast<const void*>(&attn_dkv_kernel<D>), smem_dkv, lds_ok_dkv);
+    void (*const dkv)(AttnParams) = D == 64 ? attn_dkv64_kernel : attn_dkv_kernel<128>;
+    e = allow_dynamic_lds(reinterpret_cast<const void*>(dkv), smem_dkv, lds_ok_dkv);
     if (e != hipSuccess) return e;
     const int n_kept = p.n_kept;        // grids cover the upper bound of the row count
     if (p.o_kept == nullptr) {
@@ -825,10 +1032,10 @@ static hipError_t launch_t(const AttnParams& p, const bf16_t* o_full, bf16_t* o_
     const int max_per_seq = n_kept < p.S ? n_kept : p.S;
     const int tiles = ceil_div(max_per_seq, 128);
     attn_dq_kernel<D><<<dim3(p.Hq * p.B, tiles), 256, smem_dq, st>>>(p);
-    attn_dkv_kernel<D><<<dim3(p.Hq * p.B * tiles), 256, smem_dkv, st>>>(p);
+    dkv<<<dim3(p.Hq * p.B * tiles), 256, smem_dkv, st>>>(p);
     if (p.Hq != p.Hkv) {
         const int64_t n_elems = (int64_t)n_kept * p.Hkv * D;
-        attn_dkv_reduce_kernel<<<ceil_div(n_elems / 8, 256), 256, 0, st>>>(p.dk_part, p.dv_part, p.Hq, p.Hkv, p.n_cu,
+        attn_dkv_reduce_kernel<<<ceil_div(n_elems / 8, 256), 256, 0, st>>>(p.dk_part, p.dv_part, p.Hq, p.Hkv, p.n_slots,
                                                                           n_kept, p.n_dev, p.Hkv * D, p.scale,
                                                                           p.dk_kept, p.dv_kept);
     }
@@ -850,7 +1057,7 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     p.cu_kept = cu_kept; p.dq_kept = (bf16_t*)dq_kept; p.dk_kept = (bf16_t*)dk_kept;
     p.dv_kept = (bf16_t*)dv_kept; p.B = L.B; p.S = L.S; p.Hq = L.Hq; p.Hkv = L.Hkv; p.scale = scale;
     p.n_kept = n_kept;
-    p.n_cu = compute_units();
+    p.n_slots = compute_units() * (L.d == 64 ? 2 : 1);
     p.n_dev = rows.dev;
     p.dk_part = partials;
     p.dv_part = partials ? partials + (size_t)n_kept * L.Hq * L.d : nullptr;
