@@ -54,6 +54,8 @@ struct AttnParams {
     const int32_t *idx, *cu_kept;
     bf16_t *dq_kept, *dk_kept, *dv_kept;
     float *dk_part, *dv_part;      // [G/hp][n_kept][Hkv*d] fp32 partials, one per block of hp query heads (G > hp only)
+    float* dq_part;                // [dq_split][n_kept][Hq*d] fp32 partials (dq_split > 1 only)
+    int dq_split;                  // key ranges that the dQ blocks of a query tile share out
     int n_slots;                   // dK/dV blocks that the device holds at a time (the kernel sizes its blocks' work by it)
     int B, S, Hq, Hkv;
     int n_kept;                    // rows that the compact buffers are laid out for (the stride of stat and of the partials)
@@ -71,6 +73,22 @@ __host__ __device__ inline int attn_heads_per_block(int n_rows, int Hq, int G, i
     for (int c = G; c > 1; --c)
         if (G % c == 0 && tile_rows * (Hq / c) >= 2 * (int64_t)n_slots) return c;
     return 1;
+}
+
+// Key ranges per query tile of the dQ kernel.  Where a batch of few heads (a tensor-parallel share) has at most one query
+// tile per CU, each of them is a serial chain of 1.6 us per 64 keys on a CU of its own: several blocks per tile, one per range
+// of keys, shorten it, at the price of fp32 partials and their sum.  Ranges of at least 192 keys, about four blocks per CU:
+// [2662 of 7479 rows, 4/1 heads, d = 128] 184 -> 75 us on 84 tiles, [841 of 2103 rows] 23 -> 12 us on 28.  With more tiles the
+// sum costs what the shorter chain gives (384 tiles of 24 heads, S = 909: 36 -> 37 us and 6 us for the sum), unless the
+// chain is long: up to two tiles per CU are split into ranges of at least 1536 keys.
+// A function of the shape alone (not of the kept count), so every call on a shape sums in the same order.
+static int attn_dq_split(const cf_layer_desc& L) {
+    const int64_t tiles = (int64_t)L.Hq * L.B * ceil_div(L.S, 128), n_cu = compute_units();
+    if (tiles > 2 * n_cu) return 1;
+    int64_t n = 4 * n_cu / tiles;
+    const int64_t longest = L.S / (tiles <= n_cu ? 192 : 1536);
+    if (n > longest) n = longest;
+    return n < 1 ? 1 : (n > 8 ? 8 : (int)n);
 }
 
 // Compact rows [begin, end) of sequence b.  The prefix counts are clamped to the live row count, so a
@@ -207,7 +225,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
             lse2 = p.lse_full[((int64_t)b * p.Hq + h) * p.S + pos] * LOG2E;
         }
         Dq += __shfl_xor(Dq, 32, 64);           // the other half of the row's columns
-        if (qvalid && hh == 0) {
+        if (qvalid && hh == 0 && blockIdx.z == 0) {
             p.stat[(int64_t)h * p.n_kept + jq] = lse2;
             p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq] = Dq;
         }
@@ -217,7 +235,9 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
     }
     const int jlast = j0 + rows_in_tile - 1;
     const int maxpos = (p.idx ? p.idx[jlast] : jlast) - b * p.S;
-    const int nkt = maxpos / 64 + 1;
+    // the block's range of key tiles: all of them, or its share (possibly empty) of a split tile
+    const int nkt_all = maxpos / 64 + 1, per = (nkt_all + p.dq_split - 1) / p.dq_split;
+    const int kt0 = min((int)blockIdx.z * per, nkt_all), nkt = min(kt0 + per, nkt_all);
     // positions of the wave's last and first query: key tiles past the former are skipped, key tiles
     // that end at or before the latter are visible to every query of the wave and need no mask
     int wave_maxpos = -1, wave_minpos = -1;
@@ -316,10 +336,10 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
         }
     };
 
-    issue_kv(0, 0);
+    if (kt0 < nkt) issue_kv(kt0, kt0 & 1);
     wait_vmcnt<0>();
     lds_barrier();
-    for (int kt = 0; kt < nkt; ++kt) {
+    for (int kt = kt0; kt < nkt; ++kt) {
         if (kt + 1 < nkt) issue_kv(kt + 1, (kt + 1) & 1);
         if (kt * 64 <= wave_maxpos) {
             // a query that does not exist (a ragged last wave) has position -1 and is masked in every tile
@@ -332,6 +352,18 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
         lds_barrier();
     }
 
+    if (p.dq_split > 1) {       // fp32, unscaled, to the range's own partial (zeros when the range is empty)
+        float* part = p.dq_part + (int64_t)blockIdx.z * p.n_kept * Nq;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int r = wave * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
+                if (r < rows_in_tile) part[(int64_t)(j0 + r) * Nq + h * D + nt * 32 + slot] = acc[nt][v];
+            }
+        }
+        return;
+    }
     // dq[query][d]: lane = d column, registers = query rows
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -923,35 +955,44 @@ __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
     }
 }
 
-// dk = scale * sum_g dk_part[g], dv = sum_g dv_part[g]   (fixed order: deterministic)
-__global__ __launch_bounds__(256) void attn_dkv_reduce_kernel(const float* __restrict__ dk_part,
-                                                              const float* __restrict__ dv_part, int Hq, int Hkv,
-                                                              int n_slots, int n_max, const int32_t* __restrict__ n_dev,
-                                                              int Nkv, float scale,
-                                                              bf16_t* __restrict__ dk, bf16_t* __restrict__ dv) {
-    const int n_live = live_rows(n_max, n_dev);
-    const int hp = attn_heads_per_block(n_live, Hq, Hq / Hkv, n_slots);
-    const int G = Hq / Hkv / hp;                                        // partials per KV group
+// acc += part[0..7]
+__device__ __forceinline__ void add8(const float* __restrict__ part, float (&acc)[8]) {
+    const float4 a = reinterpret_cast<const float4*>(part)[0], b = reinterpret_cast<const float4*>(part)[1];
+    acc[0] += a.x; acc[1] += a.y; acc[2] += a.z; acc[3] += a.w;
+    acc[4] += b.x; acc[5] += b.y; acc[6] += b.z; acc[7] += b.w;
+}
+
+// dk = scale * sum_g dk_part[g], dv = sum_g dv_part[g], and for a split dQ launch dq = scale * sum_z dq_part[z] (one launch
+// for both: the smallest kernel costs 5 us), in a fixed order: deterministic.  Blocks below kv_blocks take dk and dv, the others dq.
+__global__ __launch_bounds__(256) void attn_reduce_kernel(AttnParams p, int Nkv, int Nq, int kv_blocks) {
+    const int n_live = live_rows(p.n_kept, p.n_dev);
+    if ((int)blockIdx.x >= kv_blocks) {
+        const int64_t i = ((int64_t)(blockIdx.x - kv_blocks) * 256 + threadIdx.x) * 8;
+        if (i >= (int64_t)n_live * Nq) return;
+        float sq[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int z = 0; z < p.dq_split; ++z) add8(p.dq_part + (int64_t)z * p.n_kept * Nq + i, sq);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sq[e] *= p.scale;
+        Vec<bf16_t>::store(p.dq_kept + i, sq);
+        return;
+    }
+    const int hp = attn_heads_per_block(n_live, p.Hq, p.Hq / p.Hkv, p.n_slots);
+    const int G = p.Hq / p.Hkv / hp;                                    // partials per KV group
     if (G == 1) return;                                                 // the dK/dV blocks wrote the results themselves
-    const int64_t n_elems = (int64_t)n_max * Nkv;                       // stride between two partials
+    const int64_t stride = (int64_t)p.n_kept * Nkv;                     // between two partials
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
     if (i >= (int64_t)n_live * Nkv) return;
-    float sk[8], sv[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { sk[e] = 0.f; sv[e] = 0.f; }
+    float sk[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, sv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
     for (int g = 0; g < G; ++g) {
-        const float4* pk = reinterpret_cast<const float4*>(dk_part + (int64_t)g * n_elems + i);
-        const float4* pv = reinterpret_cast<const float4*>(dv_part + (int64_t)g * n_elems + i);
-        const float4 a0 = pk[0], a1 = pk[1], b0 = pv[0], b1 = pv[1];
-        sk[0] += a0.x; sk[1] += a0.y; sk[2] += a0.z; sk[3] += a0.w;
-        sk[4] += a1.x; sk[5] += a1.y; sk[6] += a1.z; sk[7] += a1.w;
-        sv[0] += b0.x; sv[1] += b0.y; sv[2] += b0.z; sv[3] += b0.w;
-        sv[4] += b1.x; sv[5] += b1.y; sv[6] += b1.z; sv[7] += b1.w;
+        add8(p.dk_part + g * stride + i, sk);
+        add8(p.dv_part + g * stride + i, sv);
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) sk[e] *= scale;
-    Vec<bf16_t>::store(dk + i, sk);
-    Vec<bf16_t>::store(dv + i, sv);
+    for (int e = 0; e < 8; ++e) sk[e] *= p.scale;
+    Vec<bf16_t>::store(p.dk_kept + i, sk);
+    Vec<bf16_t>::store(p.dv_kept + i, sv);
 }
 
 // stat[0][h][j] = log2(e) * LSE(b, h, position of kept row j); stat[1][h][j] = D = sum_c dO*O of
@@ -1006,10 +1047,15 @@ bool attn_mfma_supported(const cf_layer_desc& L) {
     return L.dtype == CF_BF16 && (L.d == 64 || L.d == 128);
 }
 
-// bytes of fp32 per-head partials behind the D row statistics (0 for MHA)
+// bytes of fp32 partials behind the row statistics: dK and dV per head block (none for MHA), dQ per key range (split only)
+static size_t attn_dkv_partial_bytes(const cf_layer_desc& L, int n_kept) {
+    return L.Hq == L.Hkv ? 0 : align_up((size_t)2 * (size_t)(n_kept > 0 ? n_kept : 1) * L.Hq * L.d * sizeof(float), 256);
+}
 size_t attn_mfma_partial_bytes(const cf_layer_desc& L, int n_kept) {
-    if (!attn_mfma_supported(L) || L.Hq == L.Hkv) return 0;
-    return align_up((size_t)2 * (size_t)(n_kept > 0 ? n_kept : 1) * L.Hq * L.d * sizeof(float), 256);
+    if (!attn_mfma_supported(L)) return 0;
+    const int split = attn_dq_split(L);
+    const size_t dq = split > 1 ? (size_t)split * (size_t)(n_kept > 0 ? n_kept : 1) * L.Hq * L.d * sizeof(float) : 0;
+    return attn_dkv_partial_bytes(L, n_kept) + align_up(dq, 256);
 }
 
 template <int D>
@@ -1031,14 +1077,11 @@ static hipError_t launch_t(const AttnParams& p, const bf16_t* o_full, bf16_t* o_
     }
     const int max_per_seq = n_kept < p.S ? n_kept : p.S;
     const int tiles = ceil_div(max_per_seq, 128);
-    attn_dq_kernel<D><<<dim3(p.Hq * p.B, tiles), 256, smem_dq, st>>>(p);
+    attn_dq_kernel<D><<<dim3(p.Hq * p.B, tiles, p.dq_split), 256, smem_dq, st>>>(p);
     dkv<<<dim3(p.Hq * p.B * tiles), 256, smem_dkv, st>>>(p);
-    if (p.Hq != p.Hkv) {
-        const int64_t n_elems = (int64_t)n_kept * p.Hkv * D;
-        attn_dkv_reduce_kernel<<<ceil_div(n_elems / 8, 256), 256, 0, st>>>(p.dk_part, p.dv_part, p.Hq, p.Hkv, p.n_slots,
-                                                                          n_kept, p.n_dev, p.Hkv * D, p.scale,
-                                                                          p.dk_kept, p.dv_kept);
-    }
+    const int kv_blocks = p.Hq != p.Hkv ? ceil_div((int64_t)n_kept * p.Hkv * D / 8, 256) : 0;
+    const int q_blocks = p.dq_split > 1 ? ceil_div((int64_t)n_kept * p.Hq * D / 8, 256) : 0;
+    if (kv_blocks + q_blocks > 0) attn_reduce_kernel<<<kv_blocks + q_blocks, 256, 0, st>>>(p, p.Hkv * D, p.Hq * D, kv_blocks);
     return hipGetLastError();
 }
 
@@ -1059,6 +1102,8 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     p.n_kept = n_kept;
     p.n_slots = compute_units() * (L.d == 64 ? 2 : 1);
     p.n_dev = rows.dev;
+    p.dq_split = attn_dq_split(L);
+    p.dq_part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(partials) + attn_dkv_partial_bytes(L, n_kept));
     p.dk_part = partials;
     p.dv_part = partials ? partials + (size_t)n_kept * L.Hq * L.d : nullptr;
     bf16_t* o_out = (bf16_t*)const_cast<void*>(o_kept);

@@ -288,6 +288,18 @@ def test_attn_bwd_filtered_heads_sharing_a_block(B, S, Hq, Hkv, d, kind, rho):
     _attn_case("bf16", B, S, Hq, Hkv, d, mask, seed=S + Hq + d, f8=np.float32)
 
 
+@pytest.mark.parametrize("B,S,Hq,Hkv,d", [(2, 400, 4, 2, 128), (1, 1601, 3, 3, 64), (3, 701, 4, 1, 128), (1, 3100, 16, 16, 64)])
+def test_attn_bwd_filtered_split_keys(B, S, Hq, Hkv, d):
+    """Few query tiles: dQ is summed from several key ranges.  The last sequence keeps only tokens near its start and
+    one at its end, so that most of its tiles leave ranges empty and the last one is ragged; with and without KV groups."""
+    say("attn bf16 split keys B=%d S=%d Hq=%d Hkv=%d d=%d" % (B, S, Hq, Hkv, d))
+    mask = (np.random.default_rng(S).random((B, S)) < 0.6).astype(np.uint8)
+    if B > 1:
+        mask[-1, 70:-1] = 0
+        mask[-1, -1] = 1
+    _attn_case("bf16", B, S, Hq, Hkv, d, mask, seed=S + d)
+
+
 def test_attn_fp32_small_head_dims():
     for d in (8, 32):
         say("attn f32 d=%d" % d)
