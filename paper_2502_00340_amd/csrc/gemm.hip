@@ -270,9 +270,14 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         const bool live = (unsigned)s < (unsigned)g.nseg;
         const int m0 = ld.m0, n0 = ld.n0;
         const int sa = live ? s : 0;
-        const bf16_t* A = static_cast<const bf16_t*>(g.A[sa]);
-        const bf16_t* B = static_cast<const bf16_t*>(sa == 0 ? ld.B0 : g.B[sa]);
-        const int Kraw = sa == 0 ? K0x : g.K[sa];
+        const bf16_t* A = static_cast<const bf16_t*>(g.A[0]);
+        const bf16_t* B = static_cast<const bf16_t*>(ld.B0);
+        int Kraw = K0x;
+        if (sa != 0) {      // a branch: the first segment's operands, which open every tile, do not wait for a load
+            A = static_cast<const bf16_t*>(g.A[sa]);
+            B = static_cast<const bf16_t*>(g.B[sa]);
+            Kraw = g.K[sa];
+        }
         Kseg = live ? Kraw : 0;
         const int64_t K = Kraw;
         const bool gatherA = MODE == 0 && s == 0 && g.a_idx != nullptr;
