@@ -256,9 +256,8 @@ typedef struct {
 
 /* cf_layer_bwd_lora: the filtered layer backward of a LoRA-adapted layer.  Arguments as for
  * cf_layer_bwd_filtered (max_kept, idx_out, cu_kept_out, n_kept_dev_out, n_kept_host included): the kept
- * count stays on the device, every kernel reads it there, and the call never synchronises (the split-K
- * launches of the rank-r products are planned for max_kept; a part of the contraction that lies past the
- * live count contributes zeros).  mask == NULL means "every token kept" (no index, no gather: the dense
+ * count stays on the device, every kernel reads it there (the grouped launches of the rank-r products plan
+ * their tiles and parts from it), and the call never synchronises.  mask == NULL means "every token kept" (no index, no gather: the dense
  * LoRA backward of the same library; *n_kept_host, when given, is set to T at once).
  * ws must hold cf_lora_workspace_bytes(desc, rank, max_kept) bytes (max_kept 0 or above T means T). */
 size_t cf_lora_workspace_bytes(const cf_layer_desc* desc, int32_t rank, int32_t max_kept);
