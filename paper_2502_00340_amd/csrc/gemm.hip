@@ -672,8 +672,11 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
                 }
             }
         }
+        // The staging area overlaps the operand stages: every wave is done with it before anybody's loads go into them
+        // again, those of this call's next tile or, behind the last one, those that the block's next call of this function
+        // starts with (a block's whole tiles are followed by its share of the cut ones).
+        lds_barrier();
         if (!has_next) break;
-        lds_barrier();                  // the staging area overlaps the stages
         if (npairs > 0) start_tile();
         continue;
     }

@@ -556,6 +556,44 @@ def test_layer_main_grad_accumulation(shape):
     assert not bad, bad
 
 
+def _random_layer(shape, seed):
+    """Saved activations, weights, upstream gradient of a bf16 layer, drawn on the GPU (lse: a constant near that of N(0,1) scores)."""
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    rn = lambda *s, std=1.0: (torch.randn(s, generator=gen, device=DEV) * std).to(torch.bfloat16)
+    T, H, F, Nq, Nkv = shape.T, shape.H, shape.F, shape.Nq, shape.Nkv
+    sv = dict(x=rn(T, H), r=rn(T, H), q=rn(T, Nq), k=rn(T, Nkv), v=rn(T, Nkv), attn_out=rn(T, Nq), gate=rn(T, F), up=rn(T, F),
+              lse=torch.full((shape.B, shape.Hq, shape.S), 6.0, device=DEV))
+    W = {n: rn(i, o, std=0.02) for n, (i, o) in dict(wq=(H, Nq), wk=(H, Nkv), wv=(H, Nkv), wo=(Nq, H), wg=(H, F), wu=(H, F),
+                                                    wd=(F, H)).items()}
+    W.update(g1=rn(H) * 0.02 + 1.0, g2=rn(H) * 0.02 + 1.0)
+    return sv, W, rn(T, H)
+
+
+@pytest.mark.parametrize("F", [4352, 5632, 6656])
+@pytest.mark.parametrize("kept", [96, 700])
+def test_layer_main_grad_full_round_and_a_remainder(F, kept):
+    """dWg and dWu of a 2048-wide layer are 16 * F/256 tiles of 256x256 in one launch: one round of 256 CUs and 16, 96 or 160
+    tiles more, which go out in quarters, halves or whole.  The blocks with a part of the remainder start its loads right
+    behind the write-out of a whole tile, into the LDS that the fp32 write-out stages its rows in.  Both outputs are made from
+    the same fp32 accumulators, so the fp32 buffers rounded to bf16 have the bits of the bf16 call; added to itself once
+    more every element doubles exactly."""
+    say("layer main-grad remainder F=%d kept=%d" % (F, kept))
+    shape = WL.LayerShape("main_grad_rounds", B=1, S=1024, H=2048, Hq=4, Hkv=2, d=64, F=F, dtype="bf16")
+    sv, W, dy = _random_layer(shape, F + kept)
+    mask = torch.zeros((1, shape.S), dtype=torch.uint8, device=DEV)
+    mask[:, shape.S - kept:] = 1
+    desc = Bn.make_desc(shape.B, shape.S, shape.H, shape.Hq, shape.Hkv, shape.d, F, "bf16")
+    ref = Bn.LayerBackward(desc, device=DEV)
+    plan = Bn.LayerBackward(desc, device=DEV, main_grad=True)
+    assert ref.filtered(sv, W, dy, mask) == kept
+    for rep in (1, 2):
+        plan.filtered(sv, W, dy, mask)
+        for name in ("dwq", "dwk", "dwv", "dwo", "dwg", "dwu", "dwd"):
+            got = plan.grads[name] / rep
+            bad = (got.to(torch.bfloat16) != ref.grads[name]).nonzero()
+            assert bad.numel() == 0, (name, rep, bad.shape[0], bad[0].tolist())
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_layer_invariants_on_gpu_outputs(dtype):
     """Keep ratio 1 reproduces the dense call bit for bit (same kernels, same
