@@ -177,7 +177,9 @@ cf_status cf_linear_bwd_reduced(const void* x_kept, const void* dy_kept, const v
  *   idx [n_kept], cu_kept [B+1]              from cf_build_keep_index
  *   dq_kept [n_kept,Hq*d], dk_kept, dv_kept [n_kept,Hkv*d]   outputs, overwritten
  * dk/dv are summed over the Hq/Hkv query heads that share a key/value head.
- * Uses only B,S,Hq,Hkv,d,dtype,softmax_scale of desc. */
+ * Uses only B,S,Hq,Hkv,d,dtype,softmax_scale of desc.
+ * cf_attn_workspace_bytes grows with n_kept and is the same for every B and S: a workspace sized for the largest
+ * n_kept serves all batch shapes of a model. */
 size_t cf_attn_workspace_bytes(const cf_layer_desc* desc, int32_t n_kept);
 cf_status cf_attn_bwd_filtered(const cf_layer_desc* desc, const void* q_kept, const void* k_full,
                                const void* v_full, const void* o_kept, const float* lse_full,
@@ -212,7 +214,8 @@ cf_status cf_attn_bwd_filtered(const cf_layer_desc* desc, const void* q_kept, co
  * cf_layer_bwd_compact_dev: the same for a caller that has not read N_k back: n_kept_dev is the
  * device count the filtered call returned and max_kept the bound it was given, so a whole stack of
  * layers runs without a single synchronisation.
- * ws must hold cf_layer_workspace_bytes(desc, max_kept) bytes (compact call: max_kept >= n_kept). */
+ * ws must hold cf_layer_workspace_bytes(desc, max_kept) bytes (compact call: max_kept >= n_kept).  One workspace sized
+ * for the largest B, S and max_kept serves all smaller ones too. */
 size_t cf_layer_workspace_bytes(const cf_layer_desc* desc, int32_t max_kept);
 cf_status cf_layer_bwd_filtered(const cf_layer_desc* desc, const cf_saved* saved,
                                 const cf_weights* w, const void* dy_full, const uint8_t* mask,

@@ -15,6 +15,7 @@ hipError_t launch_attn_bwd_ref(const cf_layer_desc& L, float scale, const void* 
                                void* dv_kept, hipStream_t st);
 bool attn_mfma_supported(const cf_layer_desc& L);
 size_t attn_mfma_partial_bytes(const cf_layer_desc& L, int n_kept);
+size_t attn_mfma_partial_bound(const cf_layer_desc& L, int n_kept);
 hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void* q_kept,
                                 const void* k_full, const void* v_full, const void* o_kept,
                                 const float* lse_full, const void* do_kept, float* stat,
@@ -94,6 +95,13 @@ size_t attn_drow_bytes(const cf_layer_desc& L, int n_kept) {
 // D row statistics followed by the per-head dK/dV partials of the matrix-core path
 size_t attn_ws_total(const cf_layer_desc& L, int n_kept) {
     return attn_drow_bytes(L, n_kept) + attn_mfma_partial_bytes(L, n_kept);
+}
+
+// What a workspace query adds to the layout of its own shape, so that one workspace serves every batch shape (B, S) with as
+// many kept rows or fewer: the dQ partials depend on the shape, and a call on a shorter sequence may need more of them.
+size_t attn_ws_spare(const cf_layer_desc& L, int n_kept) {
+    const size_t most = attn_mfma_partial_bound(L, n_kept), own = attn_mfma_partial_bytes(L, n_kept);
+    return most > own ? most - own : 0;         // a query for more rows than the shape has tokens may exceed the bound
 }
 
 // bump allocator over the caller's workspace
@@ -526,7 +534,7 @@ cf_status cf_linear_bwd_reduced(const void* x_kept, const void* dy_kept, const v
 
 size_t cf_attn_workspace_bytes(const cf_layer_desc* desc, int32_t n_kept) {
     if (check_attn_desc(desc) != CF_OK || n_kept < 0) return 0;
-    return attn_ws_total(*desc, n_kept);
+    return attn_ws_total(*desc, n_kept) + attn_ws_spare(*desc, n_kept);
 }
 
 cf_status cf_attn_bwd_filtered(const cf_layer_desc* desc, const void* q_kept, const void* k_full,
@@ -547,7 +555,7 @@ cf_status cf_attn_bwd_filtered(const cf_layer_desc* desc, const void* q_kept, co
     for (const void* p : req) {
         if (misaligned(p, (p == idx || p == cu_kept || p == lse_full) ? 4 : 16)) return CF_ERR_SHAPE;
     }
-    if (!ws || misaligned(ws, 256) || ws_bytes < cf_attn_workspace_bytes(desc, n_kept))
+    if (!ws || misaligned(ws, 256) || ws_bytes < attn_ws_total(*desc, n_kept))
         return CF_ERR_WORKSPACE;
     return attn_dispatch(*desc, q_kept, k_full, v_full, o_kept, lse_full, do_kept, idx, cu_kept,
                          RowCount{n_kept, nullptr}, dq_kept, dk_kept, dv_kept, ws, as_stream(stream));
@@ -555,7 +563,7 @@ cf_status cf_attn_bwd_filtered(const cf_layer_desc* desc, const void* q_kept, co
 
 size_t cf_layer_workspace_bytes(const cf_layer_desc* desc, int32_t max_kept) {
     if (check_layer_desc(desc) != CF_OK || max_kept < 0) return 0;
-    return carve_layer(*desc, max_kept, nullptr).total;
+    return carve_layer(*desc, max_kept, nullptr).total + attn_ws_spare(*desc, max_kept);
 }
 
 cf_status cf_layer_bwd_filtered(const cf_layer_desc* desc, const cf_saved* saved, const cf_weights* w,
@@ -655,7 +663,7 @@ cf_status cf_layer_bwd_dense(const cf_layer_desc* desc, const cf_saved* saved, c
 
 size_t cf_lora_workspace_bytes(const cf_layer_desc* desc, int32_t rank, int32_t max_kept) {
     if (check_layer_desc(desc) != CF_OK || max_kept < 0 || rank <= 0) return 0;
-    return carve_lora(*desc, rank, max_kept, nullptr).total;
+    return carve_lora(*desc, rank, max_kept, nullptr).total + attn_ws_spare(*desc, max_kept);
 }
 
 cf_status cf_layer_bwd_lora(const cf_layer_desc* desc, const cf_saved* saved, const cf_weights* w,

@@ -1058,6 +1058,17 @@ size_t attn_mfma_partial_bytes(const cf_layer_desc& L, int n_kept) {
     return attn_dkv_partial_bytes(L, n_kept) + align_up(dq, 256);
 }
 
+// The largest attn_mfma_partial_bytes over all batch shapes that can hold n_kept rows.  A launch of `split` ranges has at most
+// 4 * CUs / split query tiles, and those are at least Hq * n_kept / 128: split * n_kept * Hq <= 512 * CUs, and split <= 8.
+size_t attn_mfma_partial_bound(const cf_layer_desc& L, int n_kept) {
+    if (!attn_mfma_supported(L)) return 0;
+    const size_t rows = (size_t)(n_kept > 0 ? n_kept : 1);
+    size_t split_rows = 8 * rows * L.Hq;
+    const size_t most = (size_t)512 * compute_units();
+    if (split_rows > most) split_rows = most;
+    return attn_dkv_partial_bytes(L, n_kept) + align_up(split_rows * L.d * sizeof(float), 256);
+}
+
 template <int D>
 static hipError_t launch_t(const AttnParams& p, const bf16_t* o_full, bf16_t* o_out, const bf16_t* q_full, bf16_t* q_out,
                            hipStream_t st) {

@@ -57,6 +57,27 @@ def test_workspace_sizes(L):
     assert L.cf_attn_workspace_bytes(C.byref(d), 100) >= 100 * 4 * 4
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("Hq,Hkv,d", [(8, 8, 64), (32, 4, 64), (4, 1, 128), (16, 16, 128), (24, 8, 128)])
+def test_one_workspace_serves_all_smaller_batches(L, Hq, Hkv, d, dtype):
+    """A program sizes one workspace for its longest sequences and keeps it for the shorter ones."""
+    dq = lambda B, S: C.byref(_desc(B=B, S=S, Hq=Hq, Hkv=Hkv, d=d, dtype=dtype))
+    shapes = [(1, 16384), (2, 8192), (4, 4096), (16, 1024), (1, 8192), (1, 4096), (3, 1500), (1, 1500), (2, 700), (1, 384), (1, 129),
+              (1, 1)]
+    for n in (1, 129, 700, 1500, 16384):
+        assert len({L.cf_attn_workspace_bytes(dq(B, S), n) for B, S in shapes if B * S >= n}) == 1
+    for B, S in shapes:     # a bound above the number of tokens asks for more rows, not for a wrapped size
+        assert L.cf_attn_workspace_bytes(dq(B, S), B * S) <= L.cf_attn_workspace_bytes(dq(B, S), 1 << 20) < 1 << 40
+    for B, S in shapes:
+        for b, s in shapes:
+            if b > B or s > S:
+                continue
+            n, m = B * S, b * s
+            assert L.cf_attn_workspace_bytes(dq(B, S), n) >= L.cf_attn_workspace_bytes(dq(b, s), m), (B, S, b, s)
+            assert L.cf_layer_workspace_bytes(dq(B, S), n) >= L.cf_layer_workspace_bytes(dq(b, s), m), (B, S, b, s)
+            assert L.cf_lora_workspace_bytes(dq(B, S), 16, n) >= L.cf_lora_workspace_bytes(dq(b, s), 16, m), (B, S, b, s)
+
+
 def test_keep_index_argument_errors(L):
     n = C.c_int32(0)
     f = L.cf_build_keep_index
