@@ -162,7 +162,8 @@ cf_status cf_gather_rows(const void* src, int64_t src_rows, int64_t cols, int32_
  * For Y = X*W with W [in,out]:
  *   dx_kept [n_kept,in]  = dy_kept [n_kept,out] * W^T          (nullable: skipped)
  *   dw      [in,out]     = dw_beta*dw + x_kept^T [in,n_kept] * dy_kept   (nullable: skipped)
- * x_kept is [n_kept,in].  dw_beta is 0 (overwrite) or 1 (accumulate).
+ * x_kept is [n_kept,in].  dw_beta is 0 (overwrite) or 1 (accumulate).  With dw_beta 0, dw may be w's own memory
+ * (W is read for dx_kept first); no other output may overlap an input.
  * n_kept == 0 is valid: dw is zeroed (beta 0) or left alone (beta 1). */
 cf_status cf_linear_bwd_reduced(const void* x_kept, const void* dy_kept, const void* w,
                                 int32_t n_kept, int32_t in, int32_t out, int32_t dtype,

@@ -514,7 +514,10 @@ cf_status cf_linear_bwd_reduced(const void* x_kept, const void* dy_kept, const v
         (dx_kept && misaligned(dx_kept)) || (dw && misaligned(dw)))
         return CF_ERR_SHAPE;
     hipStream_t st = as_stream(stream);
-    if (dtype == CF_BF16 && dx_kept && dw && n_kept > 0 && dw_beta == 0.f &&
+    // dW may go over W: the launches below read W for dX before the second one writes
+    const uintptr_t w0 = (uintptr_t)w, dw0 = (uintptr_t)dw, wb = (uintptr_t)in * out * dtype_size(dtype);
+    const bool over_w = w0 < dw0 + wb && dw0 < w0 + wb;
+    if (dtype == CF_BF16 && dx_kept && dw && n_kept > 0 && dw_beta == 0.f && !over_w &&
         ceil_div(in, 128) * (ceil_div(n_kept, 128) + ceil_div(out, 128)) <= compute_units()) {
         // both products on 128x128 tiles fit one round of the CUs: one launch, and neither waits for the other
         const GemmGroupProb ps[2] = {{dy_kept, w, dx_kept, n_kept, in, out, 0, 1.f}, {x_kept, dy_kept, dw, in, out, n_kept, 1, 1.f}};

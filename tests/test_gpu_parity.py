@@ -154,6 +154,21 @@ def test_linear_small_tiles_short_contraction(k):
             assert bool((err <= ref.abs() * 2.0 ** -8 + 1e-4 * math.sqrt(k)).all()), (n, fin, fout, err.max().item())
 
 
+@pytest.mark.parametrize("n,fin,fout", [(128, 2048, 256), (300, 1032, 520), (2048, 2048, 2048)])
+def test_linear_dw_over_w(n, fin, fout):
+    """dW written over W: dX still comes from the weights that were there, whether the two products would share a launch
+    (the first two sizes) or not."""
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    rn = lambda *s: torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16)
+    x, dy, w = rn(n, fin), rn(n, fout), rn(fin, fout)
+    rdx, rdw = Bn.linear_bwd_reduced(x, dy, w)
+    for _ in range(5):
+        dx, wdw = torch.empty_like(rdx), w.clone()
+        Bn._check(Bn.lib().cf_linear_bwd_reduced(Bn._ptr(x), Bn._ptr(dy), Bn._ptr(wdw), n, fin, fout, Bn.CF_BF16, Bn._ptr(dx),
+                                                 Bn._ptr(wdw), 0.0, Bn._stream()), "cf_linear_bwd_reduced")
+        assert torch.equal(dx, rdx) and torch.equal(wdw, rdw)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_linear_dw_accumulate_and_empty(dtype):
     say("linear accumulate/empty %s" % dtype)
