@@ -254,13 +254,14 @@ hipError_t launch_keep_index_static(const uint8_t* mask, int B, int S, int32_t* 
 // gather: dst[j,:] = src[idx[j],:], rows copied as 16-byte (or 4-byte) words
 // ---------------------------------------------------------------------------
 
-// STREAM: loads and stores past the caches.  Taken when the gathered rows alone exceed the 256 MB memory-side cache, so that
-// whoever reads them next finds them in HBM either way: 1 GiB source, half of its rows: 197 -> 179 us (6.0 TB/s, the rate of
+// Loads and stores go past the caches when the gathered rows alone exceed the 256 MB memory-side cache, so that
+// whoever reads them next finds them in HBM either way: 1 GiB source, half of its rows: 197 -> 172 us (6.2 TB/s, the rate of
 // a plain copy).  Below that the cached form is the better one as soon as the rows are read again (gather and a
 // sum of the result behind it, 134 MB of rows: 88.5 us cached, 91.5 us streamed; 268 MB: 174 and 170 us).
+// The LIVE rows decide, which with a device-side count only the kernel knows.
 static constexpr int64_t GATHER_STREAM_BYTES = (int64_t)256 << 20;
 
-template <typename W, bool STREAM>
+template <typename W>
 __global__ __launch_bounds__(256) void gather_rows_kernel(const W* __restrict__ src,
                                                           const int32_t* __restrict__ idx,
                                                           int n_max, const int32_t* __restrict__ n_dev,
@@ -274,21 +275,12 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const W* __restrict__ 
     if (r >= rows_per_block || j >= n_rows) return;
     const W* s = src + (int64_t)idx[j] * words_per_row;
     W* d = dst + (int64_t)j * words_per_row;
-    for (int c = c0; c < words_per_row; c += lanes_per_row) {
-        if (STREAM) __builtin_nontemporal_store(__builtin_nontemporal_load(s + c), d + c);
-        else d[c] = s[c];
+    if ((int64_t)n_rows * words_per_row * (int64_t)sizeof(W) >= GATHER_STREAM_BYTES) {
+        for (int c = c0; c < words_per_row; c += lanes_per_row)
+            __builtin_nontemporal_store(__builtin_nontemporal_load(s + c), d + c);
+    } else {
+        for (int c = c0; c < words_per_row; c += lanes_per_row) d[c] = s[c];
     }
-}
-
-template <typename W>
-static void gather_launch(bool stream, int grid, hipStream_t st, const void* src, const int32_t* idx, RowCount rows, int words,
-                          int lanes, int rpb, void* dst) {
-    if (stream)
-        gather_rows_kernel<W, true><<<grid, 256, 0, st>>>(static_cast<const W*>(src), idx, rows.n, rows.dev, words, lanes, rpb,
-                                                          static_cast<W*>(dst));
-    else
-        gather_rows_kernel<W, false><<<grid, 256, 0, st>>>(static_cast<const W*>(src), idx, rows.n, rows.dev, words, lanes, rpb,
-                                                           static_cast<W*>(dst));
 }
 
 hipError_t launch_gather(const void* src, int64_t cols_bytes, const int32_t* idx, RowCount rows,
@@ -302,10 +294,14 @@ hipError_t launch_gather(const void* src, int64_t cols_bytes, const int32_t* idx
     while (lanes > 1 && lanes / 2 >= words) lanes /= 2;   // smallest power of two >= words, capped at 256
     const int rpb = 256 / lanes;
     const int grid = ceil_div(n_rows, rpb);
-    const bool stream = (int64_t)n_rows * cols_bytes >= GATHER_STREAM_BYTES;
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    if (vec16) gather_launch<u32x4>(stream, grid, st, src, idx, rows, words, lanes, rpb, dst);
-    else gather_launch<unsigned>(stream, grid, st, src, idx, rows, words, lanes, rpb, dst);
+    if (vec16)
+        gather_rows_kernel<u32x4><<<grid, 256, 0, st>>>(static_cast<const u32x4*>(src), idx, n_rows, rows.dev,
+                                                        words, lanes, rpb, static_cast<u32x4*>(dst));
+    else
+        gather_rows_kernel<unsigned><<<grid, 256, 0, st>>>(static_cast<const unsigned*>(src), idx,
+                                                           n_rows, rows.dev, words, lanes, rpb,
+                                                           static_cast<unsigned*>(dst));
     return hipGetLastError();
 }
 

@@ -87,16 +87,19 @@ def test_gather_rows_bit_exact(rows, cols, dtype, frac):
 
 @pytest.mark.parametrize("rows,cols", [(33000, 4096), (33000, 4098)])
 def test_gather_rows_beyond_the_cache(rows, cols):
-    """More than 256 MB of gathered rows go past the caches, as 16-byte words and (rows of 4098 elements) as 4-byte words;
-    a device-side count below the bound leaves the rows past it alone."""
+    """More than 256 MB of gathered rows go past the caches, as 16-byte words and (rows of 4098 elements) as 4-byte words.
+    The live rows decide: with a device-side count just above, below and far below that amount under the same bound the rows
+    are the same, and those past the count are left alone."""
     src = torch.randint(-2 ** 15, 2 ** 15, (rows, cols), dtype=torch.int16, device=DEV).view(torch.bfloat16)
     idx = torch.randperm(rows, device=DEV).to(torch.int32)
     ref = src.view(torch.int16)[idx.long()]
     assert torch.equal(Bn.gather_rows(src, idx, rows).view(torch.int16), ref)
-    out = torch.zeros_like(src)
-    Bn.gather_rows(src, idx, rows, out=out, n_kept_dev=torch.tensor([rows - 777], dtype=torch.int32, device=DEV))
-    assert torch.equal(out.view(torch.int16)[:rows - 777], ref[:rows - 777])
-    assert not bool(out.view(torch.int16)[rows - 777:].any())
+    edge = -(-(256 << 20) // (2 * cols))        # the first count whose rows are 256 MB
+    for n in (rows - 100, edge, edge - 1, rows - 777, 1000, 0):
+        out = torch.zeros_like(src)
+        Bn.gather_rows(src, idx, rows, out=out, n_kept_dev=torch.tensor([n], dtype=torch.int32, device=DEV))
+        assert torch.equal(out.view(torch.int16)[:n], ref[:n])
+        assert not bool(out.view(torch.int16)[n:].any())
 
 
 # ---------------------------------------------------------------------------
