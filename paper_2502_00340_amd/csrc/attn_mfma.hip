@@ -33,6 +33,8 @@
 // so accumulator registers 8j..8j+7 of a lane, used as one A/B fragment, carry
 // rows {16j + 4hh + e, 16j + 8 + 4hh + e}; the transpose reads fetch exactly
 // those rows for the other operand.
+#include <algorithm>
+
 #include "common.h"
 #include "mfma_util.h"
 
@@ -54,14 +56,26 @@ struct AttnParams {
     const int32_t *idx, *cu_kept;
     bf16_t *dq_kept, *dk_kept, *dv_kept;
     float *dk_part, *dv_part;      // [G/hp][n_kept][Hkv*d] fp32 partials, one per block of hp query heads (G > hp only)
-    float* dq_part;                // [dq_split][n_kept][Hq*d] fp32 partials (dq_split > 1 only)
-    int dq_split;                  // key ranges that the dQ blocks of a query tile share out
+    float* dq_part;                // [ranges][n_kept][Hq*d] fp32 partials (more than one range only)
+    // Key ranges that the dQ blocks of a query tile share out (see attn_dq_plan): seven limits of 9 bits, the k-th one the most
+    // 128-row tiles with which k + 2 ranges or more are taken.  One word next to the sizes: with the rule itself
+    // evaluated here instead a call took 1.1 us more (of 16 at S = 384).
+    uint64_t dq_limits;
     int n_slots;                   // dK/dV blocks that the device holds at a time (the kernel sizes its blocks' work by it)
     int B, S, Hq, Hkv;
     int n_kept;                    // rows that the compact buffers are laid out for (the stride of stat and of the partials)
     const int32_t* n_dev;          // nullable: the live row count on the device, at most n_kept
     float scale;
 };
+
+static constexpr int DQ_MAX_RANGES = 8, DQ_LIMIT_BITS = 9;
+__host__ __device__ inline int dq_ranges(uint64_t limits, int n_rows) {
+    const int tiles = (n_rows + 127) / 128;
+    int r = 1;
+#pragma unroll
+    for (int k = 0; k < DQ_MAX_RANGES - 1; ++k) r += tiles <= (int)((limits >> (DQ_LIMIT_BITS * k)) & ((1 << DQ_LIMIT_BITS) - 1)) ? 1 : 0;
+    return r;
+}
 
 // Query heads of one KV group that a dK/dV block walks through: the largest divisor of the group size G
 // that still leaves about two blocks for every one that the device holds at a time (a block costs between one and `tiles` steps
@@ -75,20 +89,60 @@ __host__ __device__ inline int attn_heads_per_block(int n_rows, int Hq, int G, i
     return 1;
 }
 
-// Key ranges per query tile of the dQ kernel.  Where a batch of few heads (a tensor-parallel share) has at most one query
-// tile per CU, each of them is a serial chain of 1.6 us per 64 keys on a CU of its own: several blocks per tile, one per range
-// of keys, shorten it, at the price of fp32 partials and their sum.  Ranges of at least 192 keys, about four blocks per CU:
-// [2662 of 7479 rows, 4/1 heads, d = 128] 184 -> 75 us on 84 tiles, [841 of 2103 rows] 23 -> 12 us on 28.  With more tiles the
-// sum costs what the shorter chain gives (384 tiles of 24 heads, S = 909: 36 -> 37 us and 6 us for the sum), unless the
-// chain is long: up to two tiles per CU are split into ranges of at least 1536 keys.
-// A function of the shape alone (not of the kept count), so every call on a shape sums in the same order.
+// Key ranges per query tile of the dQ kernel.  Where a batch of few heads (a tensor-parallel share) has few query tiles, each
+// of them is a serial chain on a CU of its own: several blocks per tile, one per range of keys, shorten it, at the price of
+// fp32 partials and their sum: [2662 of 7479 rows, 4/1 heads, d = 128] 184 -> 75 us on 84 tiles, [841 of 2103 rows]
+// 23 -> 12 us on 28.
+// The most ranges that a batch shape may take, which grid and workspace are sized for: at least 192 keys in a range, about
+// four blocks per CU; with more than one tile per CU at least 1536 keys; none above two.
 static int attn_dq_split(const cf_layer_desc& L) {
     const int64_t tiles = (int64_t)L.Hq * L.B * ceil_div(L.S, 128), n_cu = compute_units();
     if (tiles > 2 * n_cu) return 1;
     int64_t n = 4 * n_cu / tiles;
     const int64_t longest = L.S / (tiles <= n_cu ? 192 : 1536);
     if (n > longest) n = longest;
-    return n < 1 ? 1 : (n > 8 ? 8 : (int)n);
+    return n < 1 ? 1 : (n > DQ_MAX_RANGES ? DQ_MAX_RANGES : (int)n);
+}
+
+// The ranges that a call takes of them.  What the partials cost goes with the live rows: 8 bytes per element and range,
+// written and read at about 3.5 TB/s, against the chain of S keys, 9.4 ns * d per 64 of them.  Without KV groups the split
+// also costs a launch that would not be there otherwise, about 1 us; with them that launch is there and gains 1 us by a dQ kernel
+// that ends sooner.  A gain below 1/64 of the chain is none.  (Decided from the batch shape alone, calls that keep
+// most of their tokens were split as far as sparse ones: 32/32 heads, d = 128, S = 1024, all kept, four ranges 88 us, none 69;
+// 307 of 1024 kept, 45 and 48.  Over 1152 calls of 4 to 64 heads, S = 260 to 16384, 0.1 to 1 kept, by this rule none is more
+// than 2 % slower than unsplit and the mean is 1.22 times as fast; by the shape 153 were slower, the worst by 24 %, the
+// mean 1.20.)
+// In units of 1/16 ns per column: k > 1 ranges gain A(k) - k * part, A(k) = chain - chain/k - launch, part = what
+// one range's partials cost; k = 1 counts as a gain of chain / 64.  The k of the largest gain, the smaller one of
+// equals, is k or more exactly if some j >= k gains more than every i < k, which is a limit on part and so on the rows.  These
+// limits, in tiles of 128 rows (of which a batch that may be split has 512 at most), go to the kernels.
+// Returns the ranges that the grid needs: those taken where the host knows the rows, the most there may be where it does not.
+static int attn_dq_plan(const cf_layer_desc& L, const RowCount& rows, uint64_t& limits) {
+    limits = 0;
+    const int cap = attn_dq_split(L);
+    if (cap == 1) return 1;                         // from here on S <= 64 K
+    const int chain = L.S * 75 / 32, launch = (L.Hq == L.Hkv ? 16000 : -16000) / L.d;
+    int A[DQ_MAX_RANGES + 1] = {0, chain / 64};
+    for (int k = 2; k <= cap; ++k) A[k] = chain - chain / k - launch;
+    auto put = [&](int k, uint64_t v) { limits |= std::min<uint64_t>(v, (1 << DQ_LIMIT_BITS) - 1) << (DQ_LIMIT_BITS * (k - 2)); };
+    for (int k = 2; k <= cap; ++k) {
+        int most = -1;                              // largest part that takes k or more
+        for (int j = k; j <= cap; ++j) {
+            int beats = INT32_MAX;
+            for (int i = 1; i < k; ++i) {
+                const int lead = A[j] - A[i] - 1;
+                beats = std::min(beats, lead < 0 ? -1 : lead / (i == 1 ? j : j - i));
+            }
+            most = std::max(most, beats);
+        }
+        // part = tiles * 128 rows * Hq * 32 / 875, rounded down
+        put(k, most < 0 ? 0 : ((uint64_t)(most + 1) * 875 - 1) / ((uint64_t)L.Hq * 4096));
+    }
+    if (rows.dev != nullptr) return cap;
+    const int taken = dq_ranges(limits, rows.n);
+    limits = 0;
+    for (int k = 2; k <= taken; ++k) put(k, ~0ull);
+    return taken;
 }
 
 // Compact rows [begin, end) of sequence b.  The prefix counts are clamped to the live row count, so a
@@ -178,6 +232,8 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
     // row count, and the blocks past this sequence's tiles come last in the launch order
     const int seq_tiles = (cnt + 127) / 128;
     if ((int)blockIdx.y >= seq_tiles) return;
+    // (a tile's first block does not wait for the number of ranges until its rows are on their way)
+    if (blockIdx.z != 0 && (int)blockIdx.z >= dq_ranges(p.dq_limits, live_rows(p.n_kept, p.n_dev))) return;
     const int qt = seq_tiles - 1 - blockIdx.y;
     const int j0 = seq_begin + qt * 128;
     const int rows_in_tile = min(128, cnt - qt * 128);
@@ -236,7 +292,8 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
     const int jlast = j0 + rows_in_tile - 1;
     const int maxpos = (p.idx ? p.idx[jlast] : jlast) - b * p.S;
     // the block's range of key tiles: all of them, or its share (possibly empty) of a split tile
-    const int nkt_all = maxpos / 64 + 1, per = (nkt_all + p.dq_split - 1) / p.dq_split;
+    const int ranges = dq_ranges(p.dq_limits, live_rows(p.n_kept, p.n_dev));
+    const int nkt_all = maxpos / 64 + 1, per = (nkt_all + ranges - 1) / ranges;
     const int kt0 = min((int)blockIdx.z * per, nkt_all), nkt = min(kt0 + per, nkt_all);
     // positions of the wave's last and first query: key tiles past the former are skipped, key tiles
     // that end at or before the latter are visible to every query of the wave and need no mask
@@ -352,7 +409,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
         lds_barrier();
     }
 
-    if (p.dq_split > 1) {       // fp32, unscaled, to the range's own partial (zeros when the range is empty)
+    if (ranges > 1) {           // fp32, unscaled, to the range's own partial (zeros when the range is empty)
         float* part = p.dq_part + (int64_t)blockIdx.z * p.n_kept * Nq;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -967,11 +1024,12 @@ __device__ __forceinline__ void add8(const float* __restrict__ part, float (&acc
 __global__ __launch_bounds__(256) void attn_reduce_kernel(AttnParams p, int Nkv, int Nq, int kv_blocks) {
     const int n_live = live_rows(p.n_kept, p.n_dev);
     if ((int)blockIdx.x >= kv_blocks) {
+        const int ranges = dq_ranges(p.dq_limits, n_live);
         const int64_t i = ((int64_t)(blockIdx.x - kv_blocks) * 256 + threadIdx.x) * 8;
-        if (i >= (int64_t)n_live * Nq) return;
+        if (ranges == 1 || i >= (int64_t)n_live * Nq) return;           // whole tiles: the dQ blocks wrote the results themselves
         float sq[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
-        for (int z = 0; z < p.dq_split; ++z) add8(p.dq_part + (int64_t)z * p.n_kept * Nq + i, sq);
+        for (int z = 0; z < ranges; ++z) add8(p.dq_part + (int64_t)z * p.n_kept * Nq + i, sq);
 #pragma unroll
         for (int e = 0; e < 8; ++e) sq[e] *= p.scale;
         Vec<bf16_t>::store(p.dq_kept + i, sq);
@@ -1063,14 +1121,14 @@ size_t attn_mfma_partial_bytes(const cf_layer_desc& L, int n_kept) {
 size_t attn_mfma_partial_bound(const cf_layer_desc& L, int n_kept) {
     if (!attn_mfma_supported(L)) return 0;
     const size_t rows = (size_t)(n_kept > 0 ? n_kept : 1);
-    size_t split_rows = 8 * rows * L.Hq;
+    size_t split_rows = DQ_MAX_RANGES * rows * L.Hq;
     const size_t most = (size_t)512 * compute_units();
     if (split_rows > most) split_rows = most;
     return attn_dkv_partial_bytes(L, n_kept) + align_up(split_rows * L.d * sizeof(float), 256);
 }
 
 template <int D>
-static hipError_t launch_t(const AttnParams& p, const bf16_t* o_full, bf16_t* o_out, const bf16_t* q_full, bf16_t* q_out,
+static hipError_t launch_t(const AttnParams& p, int dq_cap, const bf16_t* o_full, bf16_t* o_out, const bf16_t* q_full, bf16_t* q_out,
                            hipStream_t st) {
     constexpr int smem_dq = 2 * 2 * 64 * D * 2;
     constexpr int smem_dkv = 4 * (2 * 64 * D * 2 + 512);
@@ -1088,10 +1146,10 @@ static hipError_t launch_t(const AttnParams& p, const bf16_t* o_full, bf16_t* o_
     }
     const int max_per_seq = n_kept < p.S ? n_kept : p.S;
     const int tiles = ceil_div(max_per_seq, 128);
-    attn_dq_kernel<D><<<dim3(p.Hq * p.B, tiles, p.dq_split), 256, smem_dq, st>>>(p);
+    attn_dq_kernel<D><<<dim3(p.Hq * p.B, tiles, dq_cap), 256, smem_dq, st>>>(p);
     dkv<<<dim3(p.Hq * p.B * tiles), 256, smem_dkv, st>>>(p);
     const int kv_blocks = p.Hq != p.Hkv ? ceil_div((int64_t)n_kept * p.Hkv * D / 8, 256) : 0;
-    const int q_blocks = p.dq_split > 1 ? ceil_div((int64_t)n_kept * p.Hq * D / 8, 256) : 0;
+    const int q_blocks = dq_cap > 1 ? ceil_div((int64_t)n_kept * p.Hq * D / 8, 256) : 0;
     if (kv_blocks + q_blocks > 0) attn_reduce_kernel<<<kv_blocks + q_blocks, 256, 0, st>>>(p, p.Hkv * D, p.Hq * D, kv_blocks);
     return hipGetLastError();
 }
@@ -1113,15 +1171,15 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     p.n_kept = n_kept;
     p.n_slots = compute_units() * (L.d == 64 ? 2 : 1);
     p.n_dev = rows.dev;
-    p.dq_split = attn_dq_split(L);
+    const int dq_cap = attn_dq_plan(L, rows, p.dq_limits);
     p.dq_part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(partials) + attn_dkv_partial_bytes(L, n_kept));
     p.dk_part = partials;
     p.dv_part = partials ? partials + (size_t)n_kept * L.Hq * L.d : nullptr;
     bf16_t* o_out = (bf16_t*)const_cast<void*>(o_kept);
     bf16_t* q_out = (bf16_t*)const_cast<void*>(q_kept);
     if ((o_full != nullptr) != (q_full != nullptr) || (o_full != nullptr && idx == nullptr)) return hipErrorInvalidValue;
-    return L.d == 64 ? launch_t<64>(p, (const bf16_t*)o_full, o_out, (const bf16_t*)q_full, q_out, st)
-                     : launch_t<128>(p, (const bf16_t*)o_full, o_out, (const bf16_t*)q_full, q_out, st);
+    return L.d == 64 ? launch_t<64>(p, dq_cap, (const bf16_t*)o_full, o_out, (const bf16_t*)q_full, q_out, st)
+                     : launch_t<128>(p, dq_cap, (const bf16_t*)o_full, o_out, (const bf16_t*)q_full, q_out, st);
 }
 
 }  // namespace cf

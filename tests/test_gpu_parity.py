@@ -507,6 +507,37 @@ def test_layer_device_side_count_with_a_tight_bound_and_a_stack_without_any_host
     say("  " + " ".join("%s=%.1e" % kv for kv in errs.items()))
 
 
+@pytest.mark.parametrize("Hq,Hkv,d,kept", [
+    (16, 16, 64, 1024), (16, 16, 64, 300), (16, 16, 64, 1),     # of up to five key ranges per query tile: none, some, all
+    (32, 8, 128, 1024), (32, 8, 128, 400), (4, 1, 128, 1024),
+])
+def test_layer_key_ranges_follow_the_live_rows(Hq, Hkv, d, kept):
+    """How far the dQ kernel splits the keys is decided from the live rows, by the host where it knows them and by every
+    block where the device has the count: the same bits for a host count, a device count under the bound T and one under a
+    tight bound.  dQ, seen through dWq and dx, is that of the same rows without any split (the fp32 library call) up to
+    the rounding of bf16."""
+    say("layer key ranges Hq=%d Hkv=%d d=%d kept=%d" % (Hq, Hkv, d, kept))
+    shape = WL.LayerShape("ranges", B=1, S=1024, H=256, Hq=Hq, Hkv=Hkv, d=d, F=256, dtype="bf16")
+    sv, W, dy = _random_layer(shape, kept + Hq)
+    mask = torch.zeros((1, shape.S), dtype=torch.uint8, device=DEV)
+    mask[0, torch.randperm(shape.S, device=DEV)[:kept]] = 1
+    desc = lambda dt: Bn.make_desc(1, shape.S, shape.H, Hq, Hkv, d, shape.F, dt)
+    idx, cu, n_dev, n = Bn.build_keep_index(mask)
+    dyk = Bn.gather_rows(dy, idx, n)
+    host, full, tight = (Bn.LayerBackward(desc("bf16"), device=DEV, max_kept=m) for m in (kept, None, kept))
+    host.compact(sv, W, dyk, idx, cu, n)
+    full.compact_dev(sv, W, dyk, idx, cu, n_dev)
+    tight.compact_dev(sv, W, dyk, idx, cu, n_dev)
+    f32 = Bn.LayerBackward(desc("f32"), device=DEV, max_kept=kept)
+    up = lambda ts: {k: v.float().contiguous() for k, v in ts.items()}
+    f32.compact(up(sv), up(W), dyk.float(), idx, cu, n)
+    for name in Bn.GRAD_NAMES:
+        cut = (lambda t: t[:n]) if name == "dx" else (lambda t: t)
+        assert torch.equal(cut(host.grads[name]), cut(full.grads[name])), name
+        assert torch.equal(cut(host.grads[name]), cut(tight.grads[name])), name
+        assert Hn.rel_fro(Hn.to_np(cut(host.grads[name])), Hn.to_np(cut(f32.grads[name]))) <= Hn.TOL["bf16"], name
+
+
 def test_layer_mask_that_keeps_more_than_max_kept_stays_inside_its_buffers():
     """A caller's bound that the mask exceeds: the call processes the first max_kept kept tokens, writes
     nothing outside buffers sized for max_kept, and reports the true count, which exposes the mistake."""
