@@ -434,7 +434,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// dK/dV kernel (instantiated at d = 128; d = 64 has a kernel of its own below): one key tile and HP query heads per block
+// dK/dV kernel, one block per CU: one key tile and HP query heads per block (d = 64 has a second kernel below)
 // ---------------------------------------------------------------------------
 // Slot order of an iteration of the kernel's pipeline (2*KS positions, KS "A" slots and KS "C" slots;
 // see the kernel): odd iterations alternate A, C; even iterations put all C slots into the first
@@ -559,7 +559,7 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     // fragments), B(n) = P and dS from them (vector ALU: exp2, mask, products, packing), C(n) = dV and
     // dK (4*NT MFMAs).  A wave runs alone on its SIMD, so nothing overlaps unless the instruction
     // stream interleaves it: ITERATION t issues A(t+1), B(t) and C(t-1) together, one softmax value
-    // and the LDS reads of a later slot between two MFMA pairs, so that in the steady
+    // (two at d = 64) and the LDS reads of a later slot between two MFMA pairs, so that in the steady
     // state the matrix core runs back to back while the exponentials of the half before and the
     // fragment reads of the slots ahead proceed under it.  Fragment reads go through a ring of four
     // register pairs and are issued three slots ahead of their MFMAs, across iteration boundaries
@@ -574,7 +574,7 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     // slots read.  Accumulation order of every output element is that of a plain loop over the rows.
     constexpr int NP = 2 * KS;                      // slots per iteration (KS A slots, 2*NT = KS C slots)
     constexpr int VPS = 16 / NP;                    // softmax values per slot
-    constexpr int LOOK = 3, RING = 4;               // the reads issued for the next iteration must follow the barrier
+    constexpr int LOOK = KS >= 8 ? 3 : 2, RING = 4;     // the reads issued for the next iteration must follow the barrier
     static_assert(2 * NT == KS && NP % RING == 0 && (16 % NP) == 0 && NP - LOOK >= 3 * KS / 2, "slot layout");
     typedef __attribute__((address_space(3))) unsigned char* lds_u8_ptr;
     typedef const __attribute__((address_space(3))) u32x4_t* lds_u4_cptr;
@@ -812,9 +812,9 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
 // The same work split as attn_dkv_kernel (128 kept keys and HP query heads per block, halves of 32 queries), but at
 // d = 64 accumulators, K/V fragments and scores of a wave take half the registers, so two waves fit a SIMD and
 // overlap each other's matrix, vector and LDS phases; a plain order of the phases is then better than the software pipeline
-// that a lone wave needs: [8192 rows, 32/4 heads, S = 2048] 220 -> 181 us, [1377 rows of 4593, 32/4 heads] 27 -> 23 us
-// against that pipeline at d = 64.  Fragment reads run one MFMA pair ahead.  The accumulation order of every element is that
-// of the pipelined kernel.
+// that a lone wave needs, as long as there are two blocks for every CU and more to follow: whole attention call at d = 64, this
+// kernel and the pipelined one, [8192 rows, 32/32 heads, S = 2048] 274 and 322 us, [4096, 64/64, S = 1024] 177 and 212.  Fragment reads
+// run one MFMA pair ahead.  The accumulation order of every element is that of the pipelined kernel.
 __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
     constexpr int D = 64, KS = D / 16, NT = D / 32;
     constexpr int TILE = 64 * D * 2;
@@ -1128,24 +1128,31 @@ size_t attn_mfma_partial_bound(const cf_layer_desc& L, int n_kept) {
 }
 
 template <int D>
-static hipError_t launch_t(const AttnParams& p, int dq_cap, const bf16_t* o_full, bf16_t* o_out, const bf16_t* q_full, bf16_t* q_out,
+static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16_t* o_out, const bf16_t* q_full, bf16_t* q_out,
                            hipStream_t st) {
     constexpr int smem_dq = 2 * 2 * 64 * D * 2;
     constexpr int smem_dkv = 4 * (2 * 64 * D * 2 + 512);
-    static std::atomic<uint64_t> lds_ok_dq{0}, lds_ok_dkv{0};
+    const int n_kept = p.n_kept;        // grids cover the upper bound of the row count
+    const int max_per_seq = n_kept < p.S ? n_kept : p.S;
+    const int tiles = ceil_div(max_per_seq, 128), n_cu = compute_units();
+    // dK/dV kernel at d = 64.  Without a third block per CU to follow, the launch lasts as long as its longest chains, and a
+    // block that shares its CU from the start walks through its own more slowly than the pipelined kernel does alone: whole call,
+    // two per CU and pipelined, [8192 rows, 8/8 heads, S = 8192: 512 blocks] 317 and 298 us, [3072, 16/16: 384] 117 and 108,
+    // [2048, 4/4: 64] 62.6 and 58.7; just above the line [4593 rows, 16/16, S = 1531: 576] 90 and 101 us.  Chains of less than
+    // 12 tiles are too short for that to make up for two full rounds ([4096, 16/16, S = 1024: 512] 55 and 58 us).
+    const bool paired = D == 64 && (int64_t)p.Hq * p.B * tiles * 4 > (int64_t)n_cu * (tiles < 12 ? 7 : 8);
+    p.n_slots = n_cu * (paired ? 2 : 1);
+    static std::atomic<uint64_t> lds_ok_dq{0}, lds_ok_dkv{0}, lds_ok_paired{0};
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&attn_dq_kernel<D>), smem_dq, lds_ok_dq);
     if (e != hipSuccess) return e;
-    void (*const dkv)(AttnParams) = D == 64 ? attn_dkv64_kernel : attn_dkv_kernel<128>;
-    e = allow_dynamic_lds(reinterpret_cast<const void*>(dkv), smem_dkv, lds_ok_dkv);
+    void (*const dkv)(AttnParams) = paired ? attn_dkv64_kernel : attn_dkv_kernel<D>;
+    e = allow_dynamic_lds(reinterpret_cast<const void*>(dkv), smem_dkv, paired ? lds_ok_paired : lds_ok_dkv);
     if (e != hipSuccess) return e;
-    const int n_kept = p.n_kept;        // grids cover the upper bound of the row count
     if (p.o_kept == nullptr) {
         const int64_t total = (int64_t)n_kept * p.Hq * (D / 8);
         attn_stats_kernel<<<(int)((total + 255) / 256), 256, 0, st>>>(p.do_kept, p.lse_full, p.idx, n_kept, p.n_dev, p.Hq, D,
                                                                      p.S, p.stat, o_full, o_out, q_full, q_out);
     }
-    const int max_per_seq = n_kept < p.S ? n_kept : p.S;
-    const int tiles = ceil_div(max_per_seq, 128);
     attn_dq_kernel<D><<<dim3(p.Hq * p.B, tiles, dq_cap), 256, smem_dq, st>>>(p);
     dkv<<<dim3(p.Hq * p.B * tiles), 256, smem_dkv, st>>>(p);
     const int kv_blocks = p.Hq != p.Hkv ? ceil_div((int64_t)n_kept * p.Hkv * D / 8, 256) : 0;
@@ -1169,7 +1176,6 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     p.cu_kept = cu_kept; p.dq_kept = (bf16_t*)dq_kept; p.dk_kept = (bf16_t*)dk_kept;
     p.dv_kept = (bf16_t*)dv_kept; p.B = L.B; p.S = L.S; p.Hq = L.Hq; p.Hkv = L.Hkv; p.scale = scale;
     p.n_kept = n_kept;
-    p.n_slots = compute_units() * (L.d == 64 ? 2 : 1);
     p.n_dev = rows.dev;
     const int dq_cap = attn_dq_plan(L, rows, p.dq_limits);
     p.dq_part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(partials) + attn_dkv_partial_bytes(L, n_kept));

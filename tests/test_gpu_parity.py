@@ -507,17 +507,19 @@ def test_layer_device_side_count_with_a_tight_bound_and_a_stack_without_any_host
     say("  " + " ".join("%s=%.1e" % kv for kv in errs.items()))
 
 
-@pytest.mark.parametrize("Hq,Hkv,d,kept", [
-    (16, 16, 64, 1024), (16, 16, 64, 300), (16, 16, 64, 1),     # of up to five key ranges per query tile: none, some, all
-    (32, 8, 128, 1024), (32, 8, 128, 400), (4, 1, 128, 1024),
+@pytest.mark.parametrize("S,Hq,Hkv,d,kept", [
+    (1024, 16, 16, 64, 1024), (1024, 16, 16, 64, 300), (1024, 16, 16, 64, 1),   # of up to five key ranges: none, some, all
+    (1024, 32, 8, 128, 1024), (1024, 32, 8, 128, 400), (1024, 4, 1, 128, 1024),
+    # dK/dV blocks by the bound T: 576, two of them per CU; by the true count fewer, one per CU
+    (2304, 32, 4, 64, 400), (2304, 32, 32, 64, 1500),
 ])
-def test_layer_key_ranges_follow_the_live_rows(Hq, Hkv, d, kept):
+def test_layer_key_ranges_follow_the_live_rows(S, Hq, Hkv, d, kept):
     """How far the dQ kernel splits the keys is decided from the live rows, by the host where it knows them and by every
-    block where the device has the count: the same bits for a host count, a device count under the bound T and one under a
-    tight bound.  dQ, seen through dWq and dx, is that of the same rows without any split (the fp32 library call) up to
+    block where the device has the count; which dK/dV kernel runs at d = 64 goes by the bound.  The same bits for a host count,
+    a device count under the bound T and one under a tight bound.  dQ, seen through dWq and dx, is that of the same rows without any split (the fp32 library call) up to
     the rounding of bf16."""
-    say("layer key ranges Hq=%d Hkv=%d d=%d kept=%d" % (Hq, Hkv, d, kept))
-    shape = WL.LayerShape("ranges", B=1, S=1024, H=256, Hq=Hq, Hkv=Hkv, d=d, F=256, dtype="bf16")
+    say("layer key ranges S=%d Hq=%d Hkv=%d d=%d kept=%d" % (S, Hq, Hkv, d, kept))
+    shape = WL.LayerShape("ranges", B=1, S=S, H=256, Hq=Hq, Hkv=Hkv, d=d, F=256, dtype="bf16")
     sv, W, dy = _random_layer(shape, kept + Hq)
     mask = torch.zeros((1, shape.S), dtype=torch.uint8, device=DEV)
     mask[0, torch.randperm(shape.S, device=DEV)[:kept]] = 1
