@@ -40,6 +40,13 @@ def test_status_strings(L):
     assert b"gfx950" in L.cf_version()
 
 
+def test_stream_handle_without_the_raw_query(monkeypatch):
+    """A torch without the private query: the handle comes from the public stream object."""
+    monkeypatch.setattr(Bn, "_raw_stream", None)
+    monkeypatch.setattr(Bn.torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 0x1234}))
+    assert Bn._stream() == 0x1234
+
+
 def _desc(**kw):
     base = dict(B=2, S=128, H=256, Hq=4, Hkv=4, d=64, F=688, dtype="f32")
     base.update(kw)
