@@ -4,7 +4,7 @@
 //   mode NT: C[M,N] = sum_seg A[M,K] * B[N,K]^T   (both operands contiguous along K)
 //   mode TN: C[M,N] = sum_seg A[K,M]^T * B[K,N]   (both operands contiguous along M / N;
 //                                                  K is the kept-token dimension)
-// Up to three (A, B, K) segments accumulate into one output tile, which sums
+// Up to six (A, B, K) segments accumulate into one output tile, which sums
 // the gradients of a tensor consumed by several linears without rounding in
 // between (e.g. d_gate*Wg^T + d_up*Wu^T).
 //
@@ -32,7 +32,8 @@
 //     the loads of the next tile's first K-steps are already in flight while the
 //     finished tile leaves, and its stores drain under the next tile's MFMAs (the
 //     write-out of a tile used to be 13 % of its time).
-//   * Operand tiles move in K-steps of 32 through a ring of four 32 KB LDS stages,
+//   * Operand tiles move in K-steps of 32 through a ring of four 32 KB LDS stages (the 128x128
+//     tile: eight of 16 KB, four pairs instead of two, three of them ahead),
 //     filled by buffer_load ... lds (16 bytes per lane, no register hop).  K-steps are
 //     handled in pairs (64 k: one whole 128-byte line of every NT operand row, fetched
 //     by two adjacent instructions); a pair is loaded two pairs ahead, into the two
@@ -162,7 +163,7 @@ typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
 typedef __attribute__((address_space(3))) s16x4_t* lds_s16x4_ptr;
 
 static constexpr int GEMM_RING = 128 * 1024;        // the operand stages; their number and size depend on the tile (gemm_tiles)
-static constexpr int GEMM_SMEM = 160 * 1024;    // the whole LDS of a CU: four operand stages; the C tile staging of the epilogue needs 132 KB
+static constexpr int GEMM_SMEM = 160 * 1024;    // the whole LDS of a CU: the ring and the bf16 write-out's staging above it, or the fp32 write-out's (130 KB, over the ring)
 
 // Position l of a block in the logical order of its group of n blocks: XCD x (block id
 // mod 8) takes the x-th contiguous share of the order.
@@ -561,18 +562,20 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
 #pragma unroll
                 for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
         if (npairs > 0) {
-            // K-steps 0 and 1 have landed.  Behind a previous tile everything is waited for, its stores
-            // included: loads and stores share the counter and retire out of order with respect
-            // to each other, so a partial count would say nothing about the loads.
+            // K-steps 0 and 1 have landed.  The counter covers loads and stores, which retire out of order with respect
+            // to each other, but a bound on what is outstanding is one on the outstanding loads, and those retire in order:
+            // a partial count is safe with a previous call's stores in flight too.  Between two tiles of a call
+            // everything is waited for: the tile's stores, issued behind these loads, are in flight then and a partial
+            // count would be met little earlier.
             if (DEEP && first_tile) wait_vmcnt<(NPR - 2) * 2 * NU + (NU / NG) * 2>();
             else wait_vmcnt<0>();
             lds_barrier();
             frag_one(ic<0>{}, ic<0>{}, ic<0>{});
             static_for<FN>([&](auto J) __attribute__((always_inline)) { frag_one(ic<0>{}, ic<FM + decltype(J)::value>{}, ic<0>{}); });
             frag_one(ic<0>{}, ic<1>{}, ic<0>{});
-            // two pairs per iteration; an odd count runs one pair of zero K-steps (loads past the last
-            // segment return zeros)
-            if constexpr (DEEP) {       // short contractions are the rule here: leave after the last pair
+            // NPR pairs per iteration.  The small tile, where short contractions are the rule, leaves after the last
+            // pair; the others run an odd count's extra pair on zeros (loads past the last segment return them)
+            if constexpr (DEEP) {
                 for (int p = npairs;;) {
                     pair_body(ic<0>{});
                     if (--p <= 0) break;
@@ -782,7 +785,7 @@ __device__ __forceinline__ void gemm_bf16_block(const GemmArgs& g, unsigned char
             const int tiles_n192 = (g.N + 191) / 192, n_items = tiles_m * tiles_n192;
             int w = (int)blockIdx.x;
             // with a device-side count there are as many blocks as CUs, whatever the number of tiles: a block
-            // past the last tile would compute another block's tile a second time (and with beta = 1 add to it twice)
+            // past the last tile would compute another block's tile a second time (and add to it twice if beta were 1)
             if (w >= n_items) return;
             auto tile = [&](int w, TileRef& t) __attribute__((always_inline)) {
                 int bm, bn;
@@ -891,7 +894,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_f32out_kernel(GemmArgs g) {
 // tiles alone leave CUs idle.  For the products with a rank-r adapter matrix (an output of r columns or r rows with a long
 // contraction: 2 to 32 tiles each) and for layers with few kept tokens: what they cost one by one is launches (5 us
 // for the smallest kernel), blocks that wait for loads on a few CUs (a CU takes in about 60 B/ns whatever the number
-// of active CUs, so a product that lies on 100 of them runs at 100/256 of the rate), and a reduction each.
+// of active CUs), and a reduction each.  A launch has a fixed cost, though (scale * dY*b^T of 4096 rows, rank 64, K = 3072, six
+// steps of 64 k in every block: 16 us and 6 us for the sum), so a single product of medium size gains nothing here.
 // An item is one (tile, part); a part of a split tile leaves its fp32 accumulators in a 64 KB slot of its own and
 // gemm_group_reduce_kernel adds the slots of a tile up in the order of the parts.  Blocks and reduction make the same plan
 // from the live kept-token count, so the result is the same whether the count was known to the host or not.

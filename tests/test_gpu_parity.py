@@ -141,7 +141,7 @@ def test_linear_bwd_reduced(dtype, n_kept, fin, fout):
     assert np.max(np.abs(Hn.to_np(dw) - rdw)) <= tol_abs * max(1.0, np.max(np.abs(rdw)))
 
 
-@pytest.mark.parametrize("k", [8, 64, 72, 128, 200, 256, 264, 320, 520, 584])
+@pytest.mark.parametrize("k", [8, 64, 72, 128, 136, 192, 200, 256, 264, 320, 440, 520, 584])
 def test_linear_small_tiles_short_contraction(k):
     """Outputs of a few 128x128 tiles with contractions of one to ten 64-wide steps, whole and ragged: every position of
     the ring of four steps as the last one.  Reference in fp64 on the GPU; one rounding to bf16 and fp32 sums of k terms
@@ -290,13 +290,17 @@ def test_attn_bwd_filtered_long_context(S, Hq, Hkv, d, kind):
 @pytest.mark.parametrize("B,S,Hq,Hkv,d,kind,rho", [
     # enough key tiles that a dK/dV block takes several query heads of its KV group in a row
     # (the launcher wants about two blocks per CU of a 256-CU chip):
-    (4, 2048, 16, 4, 64, "topk", 1.0),      # 64 key tiles x 16 heads: two heads per block, two partials per group
-    (8, 2048, 8, 4, 128, "spans", 1.0),     # 128 x 8: the whole group of two in one block, no partials
-    (8, 2048, 8, 4, 64, "topk", 1.0),       # the same rows at d = 64: one head per block, two partials
-    (12, 2048, 16, 2, 64, "ragged", 0.8),   # about 154 x 16, ragged sequences of a group of eight
+    (8, 2048, 8, 4, 128, "spans", 1.0),     # 128 key tiles x 8 heads: the whole group of two in one block, no partials
+    (12, 2048, 16, 2, 128, "ragged", 0.8),  # half of every sequence, 96 x 16: two heads of a group of eight, four partials
+    (12, 2047, 16, 2, 128, "topk", 0.8),    # 154 x 16, ragged tiles: four heads of a group of eight, two partials
     # at d = 64 a CU holds two blocks and the launcher wants twice as many
+    (4, 2048, 16, 4, 64, "topk", 1.0),      # 64 x 16: one head per block, four partials
+    (8, 2048, 8, 4, 64, "topk", 1.0),       # 128 x 8: one head per block, two partials
+    (12, 2048, 16, 2, 64, "ragged", 0.8),   # 96 x 16: one head per block, eight partials
+    (12, 2047, 16, 2, 64, "topk", 0.8),     # 154 x 16, ragged tiles: two heads of a group of eight, four partials
     (16, 1024, 16, 8, 64, "topk", 1.0),     # 128 x 16: the whole group of two in one block, no partials
     (16, 1024, 16, 2, 64, "topk", 1.0),     # two heads of a group of eight per block, four partials
+    (3, 1531, 32, 4, 64, "topk", 0.3),      # 11 x 32, ragged tiles, one head per block
 ])
 def test_attn_bwd_filtered_heads_sharing_a_block(B, S, Hq, Hkv, d, kind, rho):
     say("attn bf16 heads per block B=%d S=%d Hq=%d Hkv=%d d=%d %s rho=%.1f" % (B, S, Hq, Hkv, d, kind, rho))
@@ -829,8 +833,7 @@ def _run_lora(p, lora_np, rank, mask_on=True):
 
 LORA_SHAPES = {
     "small": dict(B=2, S=224, H=256, Hq=4, Hkv=2, d=64, F=384),
-    # long enough contractions (H, Hq*d and the kept-token count above 1024) for the adapter products
-    # to take the split-K path, with ragged K ranges
+    # few tiles and contractions of 1024 and more: the grouped launches cut them into several parts, the last one ragged
     "splitk": dict(B=2, S=640, H=1024, Hq=16, Hkv=4, d=64, F=512),
     # with every token kept 4 x 65 row tiles in one grouped launch: nothing is split and blocks take a second item
     "rows": dict(B=5, S=1664, H=128, Hq=2, Hkv=1, d=64, F=128),
@@ -900,32 +903,38 @@ def test_layer_lora_nothing_kept():
 
 
 def test_layer_lora_same_result_twice():
-    """2572 kept rows of a 4096-wide layer: the second dh1 product (beta = 1) runs on 242 tiles of 256x192 with a
-    device-side count, i.e. fewer tiles than blocks.  Every tile has to be added exactly once: the call gives the
-    same bits every time, and those of a call whose launch has no spare block (the known count as its bound)."""
+    """2572 kept rows of a 4096-wide layer: the dh2 and dh1 products run on 242 tiles of 256x192.  With a device-side count
+    there are as many blocks as CUs, more than tiles, and the spare ones leave.  The adapter call gives the same bits
+    every time and under the true count as its bound; the call without adapters gives those of a host count, whose launches
+    have a block per tile and none to spare."""
     shape = WL.LayerShape("lora_spare_blocks", B=4, S=732, H=4096, Hq=4, Hkv=1, d=128, F=256, dtype="bf16")
     say("layer lora, fewer tiles than blocks")
-    gen = torch.Generator(device=DEV).manual_seed(61)
-    rn = lambda *s, std=1.0: (torch.randn(s, generator=gen, device=DEV) * std).to(torch.bfloat16)
-    T, H, F, Nq, Nkv, R = shape.T, shape.H, shape.F, shape.Nq, shape.Nkv, 16
-    sv = dict(x=rn(T, H), r=rn(T, H), q=rn(T, Nq), k=rn(T, Nkv), v=rn(T, Nkv), attn_out=rn(T, Nq), gate=rn(T, F), up=rn(T, F),
-              lse=torch.full((shape.B, shape.Hq, shape.S), 6.0, device=DEV))
-    W = {n: rn(i, o, std=0.02) for n, (i, o) in dict(wq=(H, Nq), wk=(H, Nkv), wv=(H, Nkv), wo=(Nq, H), wg=(H, F), wu=(H, F),
-                                                    wd=(F, H)).items()}
-    W.update(g1=rn(H) * 0.02 + 1.0, g2=rn(H) * 0.02 + 1.0)
+    sv, W, dy = _random_layer(shape, 61)
+    gen = torch.Generator(device=DEV).manual_seed(62)
+    rn = lambda *s: (torch.randn(s, generator=gen, device=DEV) * 0.02).to(torch.bfloat16)
+    H, Nq, Nkv, R = shape.H, shape.Nq, shape.Nkv, 16
     lo = {"scale": 2.0}
     for p, (i, o) in dict(q=(H, Nq), k=(H, Nkv), v=(H, Nkv), o=(Nq, H)).items():
-        lo["a" + p], lo["b" + p] = rn(i, R, std=0.02), rn(R, o, std=0.02)
+        lo["a" + p], lo["b" + p] = rn(i, R), rn(R, o)
     mask = torch.zeros((shape.B, shape.S), dtype=torch.uint8, device=DEV)
     mask[:, :643] = 1
-    dy = rn(T, H)
-    plan = Bn.LoraBackward(Bn.make_desc(shape.B, shape.S, H, shape.Hq, shape.Hkv, shape.d, F, "bf16"), R, device=DEV)
+    n = 4 * 643
+    desc = Bn.make_desc(shape.B, shape.S, H, shape.Hq, shape.Hkv, shape.d, shape.F, "bf16")
+    plan, tight = Bn.LoraBackward(desc, R, device=DEV), Bn.LoraBackward(desc, R, device=DEV)
+    tight.max_kept = n
     first = None
-    for it in range(6):
-        n = plan.run(sv, W, lo, dy, mask)
-        assert n == 4 * 643
-        got = {k: v.clone() for k, v in plan.grads.items()}
+    for it, pl in enumerate([plan] * 5 + [tight]):
+        assert pl.run(sv, W, lo, dy, mask) == n
+        got = {k: v.clone() for k, v in pl.grads.items()}
         got["dx"] = got["dx"][:n]
         first = first or got
         for k in got:
             assert torch.equal(got[k], first[k]), (it, k)
+    idx, cu, n_dev, _ = Bn.build_keep_index(mask)
+    dyk = Bn.gather_rows(dy, idx, n)
+    dev, host = Bn.LayerBackward(desc, device=DEV), Bn.LayerBackward(desc, device=DEV)
+    dev.compact_dev(sv, W, dyk, idx, cu, n_dev)
+    host.compact(sv, W, dyk, idx, cu, n)
+    for k in Bn.GRAD_NAMES:
+        cut = n if k == "dx" else None
+        assert torch.equal(dev.grads[k][:cut], host.grads[k][:cut]), k
