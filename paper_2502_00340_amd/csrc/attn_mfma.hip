@@ -221,6 +221,8 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
     constexpr int NLD = D / 32;                 // wave-loads per wave per tile
     extern __shared__ __align__(16) unsigned char smem[];   // [2 stages][K tile, V tile]
 
+    uint64_t dq_limits = p.dq_limits;
+    asm("" : "+s"(dq_limits));                  // fetched with the first arguments, not in a round trip of its own further down
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int slot = lane & 31, hh = lane >> 5;
     const int h = blockIdx.x % p.Hq, b = blockIdx.x / p.Hq, g = h / (p.Hq / p.Hkv);
@@ -231,9 +233,8 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
     // heaviest (latest) query tiles of the sequence first; the grid is sized for an upper bound of the
     // row count, and the blocks past this sequence's tiles come last in the launch order
     const int seq_tiles = (cnt + 127) / 128;
-    if ((int)blockIdx.y >= seq_tiles) return;
-    // (a tile's first block does not wait for the number of ranges until its rows are on their way)
-    if (blockIdx.z != 0 && (int)blockIdx.z >= dq_ranges(p.dq_limits, live_rows(p.n_kept, p.n_dev))) return;
+    const int ranges = dq_ranges(dq_limits, live_rows(p.n_kept, p.n_dev));
+    if ((int)blockIdx.y >= seq_tiles || (int)blockIdx.z >= ranges) return;
     const int qt = seq_tiles - 1 - blockIdx.y;
     const int j0 = seq_begin + qt * 128;
     const int rows_in_tile = min(128, cnt - qt * 128);
@@ -292,7 +293,6 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
     const int jlast = j0 + rows_in_tile - 1;
     const int maxpos = (p.idx ? p.idx[jlast] : jlast) - b * p.S;
     // the block's range of key tiles: all of them, or its share (possibly empty) of a split tile
-    const int ranges = dq_ranges(p.dq_limits, live_rows(p.n_kept, p.n_dev));
     const int nkt_all = maxpos / 64 + 1, per = (nkt_all + ranges - 1) / ranges;
     const int kt0 = min((int)blockIdx.z * per, nkt_all), nkt = min(kt0 + per, nkt_all);
     // positions of the wave's last and first query: key tiles past the former are skipped, key tiles
@@ -1140,7 +1140,9 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
     // two per CU and pipelined, [8192 rows, 8/8 heads, S = 8192: 512 blocks] 317 and 298 us, [3072, 16/16: 384] 117 and 108,
     // [2048, 4/4: 64] 62.6 and 58.7; just above the line [4593 rows, 16/16, S = 1531: 576] 90 and 101 us.  Chains of less than
     // 12 tiles are too short for that to make up for two full rounds ([4096, 16/16, S = 1024: 512] 55 and 58 us).
-    const bool paired = D == 64 && (int64_t)p.Hq * p.B * tiles * 4 > (int64_t)n_cu * (tiles < 12 ? 7 : 8);
+    // On a single tile the two take the same time, and the plain one less for a few rows
+    // (13 rows, 16/16: 6.2 and 6.5 us).
+    const bool paired = D == 64 && (tiles == 1 || (int64_t)p.Hq * p.B * tiles * 4 > (int64_t)n_cu * (tiles < 12 ? 7 : 8));
     p.n_slots = n_cu * (paired ? 2 : 1);
     static std::atomic<uint64_t> lds_ok_dq{0}, lds_ok_dkv{0}, lds_ok_paired{0};
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&attn_dq_kernel<D>), smem_dq, lds_ok_dq);
