@@ -205,6 +205,8 @@ cf_status cf_attn_bwd_filtered(const cf_layer_desc* desc, const void* q_kept, co
  *   the mask keeps more than max_kept tokens the call processes the first max_kept kept tokens only
  *   and the result is not the layer's gradient: compare the N_k read back with max_kept.
  * cf_layer_bwd_dense: the same kernels with every token kept and no index; dx is [T,H].
+ *   When a dense call writes dx, the only saved tensor that is still read is x: dx may lie over another one that has room
+ *   for it (also in cf_layer_bwd_lora without a mask).
  * cf_layer_bwd_compact: a layer BELOW the one whose call built the keep index
  * (Sec. 3.2: once the first gradient is reduced, every later gradient is; Sec. 3.1:
  * the sparsity is handed on to all front layers).  dy_kept [n_kept,H] is the compact

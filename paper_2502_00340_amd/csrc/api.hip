@@ -29,6 +29,10 @@ using namespace cf;
 namespace {
 
 inline bool misaligned(const void* p, size_t a = 16) { return ((uintptr_t)p % a) != 0; }
+// do the byte ranges share an address
+inline bool overlap(const void* a, size_t an, const void* b, size_t bn) {
+    return (uintptr_t)a < (uintptr_t)b + bn && (uintptr_t)b < (uintptr_t)a + an;
+}
 inline hipStream_t as_stream(cf_stream s) { return reinterpret_cast<hipStream_t>(s); }
 
 #define CF_HIP(expr)                                   \
@@ -382,6 +386,11 @@ cf_status layer_core_lora(const cf_layer_desc& L, const cf_saved& sv, const cf_w
                   {w.dk, A.bk, lw.tk, N, R, Nkv, 0, A.scale},
                   {w.dv, A.bv, lw.tv, N, R, Nkv, 0, A.scale},
                   {a_rows, A.ao, lw.uo, N, R, Nq, 2, A.scale}}));
+    // Every saved tensor but x is dead when dx is written, so a dense call's dx may lie over attn_out: da_o then goes out
+    // ahead of it (as a part of the launch above it would keep that one from being split: 2-4 % of calls with 8192 rows and more)
+    const GemmGroupProb dao{a_rows, lw.to, G.dao, Nq, R, N, 1, 1.f};
+    const bool dx_over_a = overlap(G.dx, (size_t)N * H * e, a_rows, (size_t)N * Nq * e);
+    if (dx_over_a) CF_HIP(group({dao}));
     void* dh1 = w.bufHb;
     {   // dh1 = dq*Wq^T + dk*Wk^T + dv*Wv^T + t_q*a_q^T + t_k*a_k^T + t_v*a_v^T
         GemmSeg s[6] = {{w.dq, W.wq, Nq}, {w.dk, W.wk, Nkv}, {w.dv, W.wv, Nkv},
@@ -393,14 +402,15 @@ cf_status layer_core_lora(const cf_layer_desc& L, const cf_saved& sv, const cf_w
     CF_HIP(group({{h1, A.aq, lw.uq, N, R, H, 2, A.scale},
                   {h1, A.ak, lw.uk, N, R, H, 2, A.scale},
                   {h1, A.av, lw.uv, N, R, H, 2, A.scale}}));
-    CF_HIP(group({{a_rows, lw.to, G.dao, Nq, R, N, 1, 1.f},
-                  {lw.uo, w.dr, G.dbo, R, H, N, 1, 1.f},
-                  {h1, lw.tq, G.daq, H, R, N, 1, 1.f},
-                  {lw.uq, w.dq, G.dbq, R, Nq, N, 1, 1.f},
-                  {h1, lw.tk, G.dak, H, R, N, 1, 1.f},
-                  {lw.uk, w.dk, G.dbk, R, Nkv, N, 1, 1.f},
-                  {h1, lw.tv, G.dav, H, R, N, 1, 1.f},
-                  {lw.uv, w.dv, G.dbv, R, Nkv, N, 1, 1.f}}));
+    const GemmGroupProb last[8] = {dao,
+                                   {lw.uo, w.dr, G.dbo, R, H, N, 1, 1.f},
+                                   {h1, lw.tq, G.daq, H, R, N, 1, 1.f},
+                                   {lw.uq, w.dq, G.dbq, R, Nq, N, 1, 1.f},
+                                   {h1, lw.tk, G.dak, H, R, N, 1, 1.f},
+                                   {lw.uk, w.dk, G.dbk, R, Nkv, N, 1, 1.f},
+                                   {h1, lw.tv, G.dav, H, R, N, 1, 1.f},
+                                   {lw.uv, w.dv, G.dbv, R, Nkv, N, 1, 1.f}};
+    CF_HIP(launch_gemm_group(dt, last + dx_over_a, 8 - dx_over_a, st, lw.slots, nd));
     return CF_OK;
 }
 
@@ -515,8 +525,8 @@ cf_status cf_linear_bwd_reduced(const void* x_kept, const void* dy_kept, const v
         return CF_ERR_SHAPE;
     hipStream_t st = as_stream(stream);
     // dW may go over W: the launches below read W for dX before the second one writes
-    const uintptr_t w0 = (uintptr_t)w, dw0 = (uintptr_t)dw, wb = (uintptr_t)in * out * dtype_size(dtype);
-    const bool over_w = w0 < dw0 + wb && dw0 < w0 + wb;
+    const size_t w_bytes = (size_t)in * out * dtype_size(dtype);
+    const bool over_w = overlap(w, w_bytes, dw, w_bytes);
     if (dtype == CF_BF16 && dx_kept && dw && n_kept > 0 && dw_beta == 0.f && !over_w &&
         ceil_div(in, 128) * (ceil_div(n_kept, 128) + ceil_div(out, 128)) <= compute_units()) {
         // both products on 128x128 tiles fit one round of the CUs: one launch, and neither waits for the other

@@ -938,3 +938,28 @@ def test_layer_lora_same_result_twice():
     for k in Bn.GRAD_NAMES:
         cut = n if k == "dx" else None
         assert torch.equal(dev.grads[k][:cut], host.grads[k][:cut]), k
+
+
+def test_layer_dense_dx_over_attn_out():
+    """The attention output is dead when a dense call writes dx: a caller may let dx lie over it, with and without adapters."""
+    say("dx over attn_out")
+    shape = WL.LayerShape("dx_over_attn_out", B=2, S=512, H=512, Hq=8, Hkv=2, d=64, F=256, dtype="bf16")
+    sv, W, dy = _random_layer(shape, 71)
+    gen = torch.Generator(device=DEV).manual_seed(72)
+    rn = lambda *s: (torch.randn(s, generator=gen, device=DEV) * 0.02).to(torch.bfloat16)
+    H, Nq, Nkv, R = shape.H, shape.Nq, shape.Nkv, 16
+    lo = {"scale": 2.0}
+    for p, (i, o) in dict(q=(H, Nq), k=(H, Nkv), v=(H, Nkv), o=(Nq, H)).items():
+        lo["a" + p], lo["b" + p] = rn(i, R), rn(R, o)
+    desc = Bn.make_desc(shape.B, shape.S, H, shape.Hq, shape.Hkv, shape.d, shape.F, "bf16")
+    for make, call in ((lambda: Bn.LoraBackward(desc, R, device=DEV), lambda pl, s: pl.run(s, W, lo, dy, None)),
+                       (lambda: Bn.LayerBackward(desc, device=DEV), lambda pl, s: pl.dense(s, W, dy))):
+        ref, over = make(), make()
+        call(ref, sv)
+        for _ in range(5):
+            s2 = dict(sv, attn_out=sv["attn_out"].clone())
+            over._g.dx = s2["attn_out"].data_ptr()
+            call(over, s2)
+            torch.cuda.synchronize()
+            for k in ref.grads:
+                assert torch.equal(s2["attn_out"] if k == "dx" else over.grads[k], ref.grads[k]), k
