@@ -35,8 +35,8 @@
 //   * Operand tiles move in K-steps of 32 through a ring of four 32 KB LDS stages (the 128x128
 //     tile: eight of 16 KB, four pairs instead of two, three of them ahead),
 //     filled by buffer_load ... lds (16 bytes per lane, no register hop).  K-steps are
-//     handled in pairs (64 k: one whole 128-byte line of every NT operand row, fetched
-//     by two adjacent instructions); a pair is loaded two pairs ahead, into the two
+//     handled in pairs (64 k: one whole 128-byte line of every NT operand row, eight such
+//     lines per load); a pair is loaded two pairs ahead, into the two
 //     stages that the barrier of the pair being computed has just retired; completion
 //     is tracked with vmcnt.  Ragged edges come from the buffer descriptor's range
 //     check, which returns zeros, so there are no branches around loads.
@@ -54,8 +54,8 @@
 //   * The loads of a pair go out in groups spread over the sub-steps (four groups in
 //     NT, three in TN; two cost 4 %): a CU sustains only so many bytes in flight, and a
 //     burst of 64 KB stalls the stream.
-//   * NT stage: [rows][32 k], 64-byte rows, the 16-byte chunk index of a row XOR-ed with a
-//     function of row/4 chosen so that the 16 lanes that the LDS serves in one pass of a
+//   * NT pair: [rows][64 k], 128-byte rows, the 16-byte chunk index of a row XOR-ed with a
+//     function of the row chosen so that the 16 lanes that the LDS serves in one pass of a
 //     ds_read_b128 hit distinct banks (see nt_swz); a lane of the loading wave picks the
 //     global chunk that belongs in its (fixed) LDS slot.
 //   * TN stage: [32 k][rows] exactly as in memory, with the 64-byte group index of a
@@ -191,13 +191,12 @@ __device__ __forceinline__ P* uniform_ptr(P* p) {
     return reinterpret_cast<P*>(((uint64_t)hi << 32) | lo);
 }
 
-// Swizzle of an NT stage: the 16-byte chunk index of row r is XOR-ed with nt_swz(r / 4) = {0, 2, 3, 1}
-// [(r / 4) % 4].  The LDS serves a ds_read_b128 in four passes of 16 lanes, and the passes are not
-// runs of consecutive lanes: {0-3, 12-15, 20-27}, {4-11, 16-19, 28-31} and the same plus 32
-// (measured).  A fragment read has lane l at row l % 16, chunk l / 16, so a pass mixes chunk c of rows
-// 0-3 and 12-15 with chunk c + 1 of rows 4-11 (or the other way round); with this table the 16
-// lanes of every pass fall into 16 different 16-byte bank groups (with r / 4 itself they do not).
-__device__ __forceinline__ int nt_swz(int q) { return (0x78 >> (2 * (q & 3))) & 3; }
+// Swizzle of a K-contiguous operand's rows in LDS (128 bytes, 64 k): the 16-byte chunk index of row r is XOR-ed with
+// (r / 2) % 8.  The LDS serves a ds_read_b128 in four passes of 16 lanes, and the passes are not runs of consecutive lanes:
+// {0-3, 12-15, 20-27}, {4-11, 16-19, 28-31} and the same plus 32 (measured).  A fragment read has lane l at row l % 16,
+// chunk l / 16 of a K-step, so a pass mixes chunk c of rows 0-3 and 12-15 with chunk c + 1 of rows 4-11 (or the other way
+// round); with this function its 16 lanes fall into 16 different 16-byte bank groups.
+__device__ __forceinline__ int nt_swz(int row) { return (row >> 1) & 7; }
 
 // Of D loads spread over the N MFMAs of a sub-step (D <= N), the one that goes with MFMA q, or -1.
 constexpr int load_in_gap(int q, int D, int N) {
@@ -232,17 +231,17 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
     constexpr bool DEEP = TM == 2 && TN == 2;
     constexpr int BM = 64 * TM, BN = 64 * TN, KB = 32, STAGE = DEEP ? 16384 : 32768;
     constexpr int NSTG = GEMM_RING / STAGE, NPR = NSTG / 2;     // stages and pairs in the ring
-    constexpr int SWIN = 65536 / STAGE;                 // stages within reach of one LDS base register
+    constexpr int PAIR = 2 * STAGE, PWIN = 65536 / PAIR;    // bytes of a pair, pairs within reach of one LDS base register
     // MODE 0 (NT): both operands lie with K contiguous in memory; 1 (TN): both K-major; 2 (NN): A K-contiguous, B K-major
     constexpr bool AK = MODE != 1, BK = MODE == 0;
-    constexpr int A_BYTES = BM * KB * 2;                // B tile follows the A tile inside a stage
+    constexpr int A_BYTES = BM * KB * 2, B_BYTES = BN * KB * 2;     // of one K-step; a pair holds A's two K-steps, then B's
     constexpr int NU = TM + TN;                         // 1 KB wave-loads per wave per K-step: TM for A, TN for B
     constexpr int FM = 2 * TM, FN = 2 * TN;             // 16-row fragments of the wave tile along M and N
     constexpr int NQ = 2 * FN;                          // MFMAs per sub-step: one 32-row block of A x all of B
     // groups that the wave-loads of a pair are issued in (measured: 2 groups cost 4 %; NT is best
     // with 4 to 6, TN with 3)
     constexpr int NG = TM == 2 ? 2 : (MODE == 0 ? 4 : 3);
-    static_assert(A_BYTES + BN * KB * 2 <= STAGE, "tile shape");
+    static_assert(A_BYTES + B_BYTES <= STAGE, "tile shape");
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -258,15 +257,11 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
     int seg = 0, k0 = 0, Kseg = 0;
     i32x4_t rsA, rsB;
     unsigned ldA = 0, ldB = 0;
-    // Per-lane byte offset of wave-load u at k = 0 of the current segment (out of range for rows /
-    // columns beyond the matrix edge); the K position of a K-step is added as the load's scalar
-    // offset, so the steady-state loop spends no vector instruction on addresses.  v0 / v1 are the
-    // offsets used for the first / second K-step of the pair at (seg, k0): equal to vbase while the
-    // pair lies inside the segment, out of range for the lanes whose k falls past its end.
+    // Per-lane byte offsets of the pair's wave-loads at k = 0 of the current segment (out of range for rows / columns beyond the
+    // matrix edge); the K position of a pair is added as the load's scalar offset, so the steady-state loop spends no vector
+    // instruction on addresses.
     constexpr unsigned OOB_FAST = 0x80000000u;          // stays out of range when the scalar offset is added
-    unsigned vbase[NU], v0[NU], v1[NU];
-    bool pair_inside = false;
-    const unsigned nt_lc = (unsigned)((lane & 3) ^ nt_swz(lane >> 4));
+    unsigned vo[NU][2];
     auto open_segment = [&](int s) __attribute__((always_inline)) {
         const bool live = (unsigned)s < (unsigned)g.nseg;
         const int m0 = ld.m0, n0 = ld.n0;
@@ -302,17 +297,20 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         // them across the main loop (and spilling them) by hiding where the lane number comes from.
         int ln = lane;
         asm volatile("" : "+v"(ln));
-        const unsigned lc_nt = (unsigned)((ln & 3) ^ nt_swz(ln >> 4));
+        const unsigned lc_nt = (unsigned)((ln & 7) ^ nt_swz(wave * 8 + (ln >> 3)));
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             const bool isA = u < TM;
             const int i = isA ? u : u - TM;
             if (isA ? AK : BK) {
-                const unsigned row = (4 * i + wave) * 16 + (ln >> 2);
-                vbase[u] = row * (isA ? ldA : ldB) + lc_nt * 16u;
-                if (isA && gatherA) {       // rows past M carry an out-of-range offset; the index is read for live rows only
-                    const int m = m0 + (int)row;
-                    vbase[u] = m < Mx ? (unsigned)g.a_idx[m] * ldA + lc_nt * 16u : OOB_FAST;
+#pragma unroll
+                for (int sec = 0; sec < 2; ++sec) {
+                    const unsigned row = (4 * (2 * i + sec) + wave) * 8 + (ln >> 3);
+                    vo[u][sec] = row * (isA ? ldA : ldB) + lc_nt * 16u;
+                    if (isA && gatherA) {   // rows past M carry an out-of-range offset; the index is read for live rows only
+                        const int m = m0 + (int)row;
+                        vo[u][sec] = m < Mx ? (unsigned)g.a_idx[m] * ldA + lc_nt * 16u : OOB_FAST;
+                    }
                 }
             } else {
                 const int cpr = (isA ? BM : BN) / 8;
@@ -320,77 +318,66 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
                 const int kr = qq / cpr;
                 const int c = (qq % cpr) ^ ((kr & 3) << 2);
                 const bool ok = (isA ? m0 : n0) + c * 8 < (isA ? Mx : ld.N);
-                vbase[u] = ok ? (unsigned)kr * (isA ? ldA : ldB) + c * 16u : OOB_FAST;
+                vo[u][0] = vo[u][1] = ok ? (unsigned)kr * (isA ? ldA : ldB) + c * 16u : OOB_FAST;
             }
         }
-        pair_inside = false;
     };
-    // offsets and scalar K offsets of the pair at (seg, k0); cheap when this pair and the previous one
-    // lie inside the segment
+    // scalar K offsets of the pair at (seg, k0); in the last pair of a segment (and past the last segment, where Kseg = 0) the lanes
+    // whose k falls past its end go out of range
     unsigned ka0 = 0, kb0 = 0, ka1 = 0, kb1 = 0;
     auto prepare_pair = [&]() __attribute__((always_inline)) {
-        const bool inside = k0 + 2 * KB <= Kseg;
-        if (!(inside && pair_inside)) {
+        if (k0 + 2 * KB > Kseg) {
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
-                int kpos;                       // first k of the lane's chunk within a K-step
                 const bool isA = u < TM;
-                if (isA ? AK : BK) {
-                    kpos = (int)nt_lc * 8;
-                } else {
-                    const int i = isA ? u : u - TM;
-                    kpos = ((4 * i + wave) * 64 + lane) / ((isA ? BM : BN) / 8);
+                const int i = isA ? u : u - TM;
+#pragma unroll
+                for (int sec = 0; sec < 2; ++sec) {         // first k of the lane's chunk within the pair
+                    const int kpos = (isA ? AK : BK) ? (int)((lane & 7) ^ nt_swz(wave * 8 + (lane >> 3))) * 8
+                                                     : sec * KB + ((4 * i + wave) * 64 + lane) / ((isA ? BM : BN) / 8);
+                    if (k0 + kpos >= Kseg) vo[u][sec] = OOB_FAST;
                 }
-                v0[u] = (k0 + kpos < Kseg) ? vbase[u] : OOB_FAST;
-                v1[u] = (k0 + KB + kpos < Kseg) ? vbase[u] : OOB_FAST;
             }
         }
-        pair_inside = inside;
         if (AK) ka0 = (unsigned)k0 * 2u;
         else { ka0 = (unsigned)k0 * ldA; ka1 = (unsigned)(k0 + KB) * ldA; }
         if (BK) kb0 = (unsigned)k0 * 2u;
         else { kb0 = (unsigned)k0 * ldB; kb1 = (unsigned)(k0 + KB) * ldB; }
     };
-    // A pair of K-steps never straddles a segment boundary: a segment with an odd number of
-    // K-steps gets one all-zero K-step appended (its loads fall past Kseg).
+    // A pair of K-steps never straddles a segment boundary: the part of a segment's last pair past Kseg is zeros.
     auto advance_pair = [&]() __attribute__((always_inline)) {
         k0 += 2 * KB;
         if (k0 >= Kseg) {
             k0 = 0;
             ++seg;
             if (!DEEP || (unsigned)seg < (unsigned)g.nseg) open_segment(seg);
-            else { Kseg = 0; pair_inside = false; }     // past the last segment: only the range of k matters any more
+            else Kseg = 0;      // past the last segment: only the range of k matters any more
         }
     };
 
     const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_addr_of(smem) + wave * 1024);
-    // wave-load U of K-step SEC (0 / 1) of the pair at (seg, k0) into stage S: U < TM -> A tile, else B
-    // tile; tile bytes [(4*i + wave) KB, +1 KB).  NT: 16 rows x 4 chunks, the chunk a lane fetches undoes
-    // the XOR swizzle of its LDS slot; the second K-step of a pair is the other half of the same
-    // 128-byte lines (instruction offset 64).  TN: 1024 / (2*rows) k-rows of the tile.
-    auto dma_one = [&](auto S, auto U, auto SEC) __attribute__((always_inline)) {
-        constexpr int s = decltype(S)::value, u = decltype(U)::value, sec = decltype(SEC)::value;
-        constexpr bool isA = u < TM;
-        constexpr int i = isA ? u : u - TM;
-        constexpr int dst = s * STAGE + (isA ? 0 : A_BYTES) + i * 4096;
-        // the instruction offset moves the LDS destination along with the global address, so the
-        // M0 base of the second K-step is set back by the same amount
-        if (isA ? AK : BK)
-            dma16i<dst - (sec ? KB * 2 : 0), sec ? KB * 2 : 0>(lds0, isA ? rsA : rsB, sec ? v1[u] : v0[u], isA ? ka0 : kb0);
-        else dma16i<dst, 0>(lds0, isA ? rsA : rsB, sec ? v1[u] : v0[u], isA ? (sec ? ka1 : ka0) : (sec ? kb1 : kb0));
+    // Wave-load (U, SEC) of the pair at (seg, k0) into pair P of the ring: U < TM -> A tile, else B tile.  K-contiguous: 8 rows of
+    // 64 k, whole 128-byte lines, and the chunk a lane fetches undoes the XOR swizzle of its LDS slot.  (Loads of 16 rows x 32 k,
+    // with the other half of the lines in the next instruction, cost a third more of the time that a CU needs to take in its
+    // operands: 0.46 us per pair of a 128x128 tile without MFMAs against 0.35; [4096, 4096], K = 14336, 328 us and 319,
+    // [300, 4096], K = 14336, 90 and 82, [841, 1792], K = 4096, 30.8 and 29.0.)  K-major: 1024 / (2*rows) k-rows of K-step SEC.
+    auto load_dst = [](int p, int u, int sec) constexpr {
+        const bool isA = u < TM;
+        const int i = isA ? u : u - TM, op0 = p * PAIR + (isA ? 0 : 2 * A_BYTES);
+        return op0 + ((isA ? AK : BK) ? (2 * i + sec) * 4096 : sec * (isA ? A_BYTES : B_BYTES) + i * 4096);
+    };
+    auto dma_one = [&](auto P, auto U, auto SEC) __attribute__((always_inline)) {
+        constexpr int p = decltype(P)::value, u = decltype(U)::value, sec = decltype(SEC)::value;
+        constexpr bool isA = u < TM, kc = isA ? AK : BK;
+        dma16i<load_dst(p, u, sec), 0>(lds0, isA ? rsA : rsB, vo[u][sec],
+                                       isA ? (!kc && sec ? ka1 : ka0) : (!kc && sec ? kb1 : kb0));
     };
     // the same load wrapped around the MFMA acc += a x b (inside the MFMA stream)
-    auto mma_dma_one = [&](f32x4_t& c, const bf16x8_t a, const bf16x8_t b, auto S, auto U, auto SEC) __attribute__((always_inline)) {
-        constexpr int s = decltype(S)::value, u = decltype(U)::value, sec = decltype(SEC)::value;
-        constexpr bool isA = u < TM;
-        constexpr int i = isA ? u : u - TM;
-        constexpr int dst = s * STAGE + (isA ? 0 : A_BYTES) + i * 4096;
-        if (isA ? AK : BK)
-            mfma16_dma16i<dst - (sec ? KB * 2 : 0), sec ? KB * 2 : 0>(c, a, b, lds0, isA ? rsA : rsB, sec ? v1[u] : v0[u],
-                                                                      isA ? ka0 : kb0);
-        else
-            mfma16_dma16i<dst, 0>(c, a, b, lds0, isA ? rsA : rsB, sec ? v1[u] : v0[u],
-                                  isA ? (sec ? ka1 : ka0) : (sec ? kb1 : kb0));
+    auto mma_dma_one = [&](f32x4_t& c, const bf16x8_t a, const bf16x8_t b, auto P, auto U, auto SEC) __attribute__((always_inline)) {
+        constexpr int p = decltype(P)::value, u = decltype(U)::value, sec = decltype(SEC)::value;
+        constexpr bool isA = u < TM, kc = isA ? AK : BK;
+        mfma16_dma16i<load_dst(p, u, sec), 0>(c, a, b, lds0, isA ? rsA : rsB, vo[u][sec],
+                                              isA ? (!kc && sec ? ka1 : ka0) : (!kc && sec ? kb1 : kb0));
     };
 
     // ---- LDS -> fragments.  A fragment is 16 rows x 32 k (one K-step): lane l holds row l%16,
@@ -399,21 +386,21 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
     // the ring lies past that field's reach from the base of stage 0 and has base registers of its own.
     typedef __attribute__((address_space(3))) unsigned char* lds_u8_ptr;
     typedef const __attribute__((address_space(3))) u32x4_t* lds_u32x4_cptr;
-    // base registers: one for a K-contiguous operand; one per 32-row block for a K-major one (the swizzle mixes the block in)
-    constexpr int NBA = AK ? 1 : TM, NBASE = NBA + (BK ? 1 : TN);
+    // base registers: one per K-step for a K-contiguous operand (the swizzle mixes the K-step's chunk bit in), one per 32-row block
+    // for a K-major one (it mixes the block in)
+    constexpr int NBA = AK ? 2 : TM, NBASE = NBA + (BK ? 2 : TN);
     unsigned fbase[NBASE][2];
     {
         const unsigned s0 = lds_addr_of(smem);
-        const int nt_sw = nt_swz(l16 >> 2);
 #pragma unroll
         for (int u = 0; u < NBASE; ++u) {
             const bool isA = u < NBA;
             const int i = isA ? u : u - NBA;
-            const unsigned op0 = s0 + (isA ? 0 : A_BYTES);
+            const unsigned op0 = s0 + (isA ? 0 : 2 * A_BYTES);
             unsigned v;
             if (isA ? AK : BK) {
                 const int wrow = isA ? wm * (32 * TM) : wn * (32 * TN);
-                v = op0 + (wrow + l16) * 64 + ((g4 ^ nt_sw) << 4);
+                v = op0 + (wrow + l16) * 128 + (((4 * i + g4) ^ nt_swz(l16)) << 4);
             } else {
                 const int W2 = (isA ? BM : BN) * 2;                 // bytes per k-row
                 const int row0 = isA ? wm * (32 * TM) + i * 32 : wn * (32 * TN) + i * 32;
@@ -427,28 +414,28 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         }
     }
     bf16x8_t fa[2][2], fb[2][FN];
-    // fragment F (16 rows; F < FM: of the wave's A rows, else of its B rows) of the K-step in stage S
+    // fragment F (16 rows; F < FM: of the wave's A rows, else of its B rows) of K-step KS of pair P of the ring
     // into fa[BUF][F % 2] or fb[BUF][F - FM]
-    auto frag_one = [&](auto S, auto F, auto BUF) __attribute__((always_inline)) {
-        constexpr int s = decltype(S)::value, fr = decltype(F)::value, buf = decltype(BUF)::value;
+    auto frag_one = [&](auto P, auto KS, auto F, auto BUF) __attribute__((always_inline)) {
+        constexpr int p = decltype(P)::value, ks = decltype(KS)::value, fr = decltype(F)::value, buf = decltype(BUF)::value;
         constexpr bool isA = fr < FM;
         constexpr int f = isA ? fr : fr - FM;
-        constexpr int win = s / SWIN, soff = (s % SWIN) * STAGE;
+        constexpr int win = p / PWIN, poff = (p % PWIN) * PAIR;
         bf16x8_t v;
-        if (isA ? AK : BK) {
-            const lds_u8_ptr p = reinterpret_cast<lds_u8_ptr>(fbase[isA ? 0 : NBA][win]);
-            v = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<lds_u32x4_cptr>(p + (soff + f * 1024)));
+        if constexpr (isA ? AK : BK) {
+            const lds_u8_ptr q = reinterpret_cast<lds_u8_ptr>(fbase[(isA ? 0 : NBA) + ks][win]);
+            v = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<lds_u32x4_cptr>(q + (poff + f * 2048)));
         } else {
-            constexpr int W2 = (isA ? BM : BN) * 2;
-            const lds_u8_ptr p = reinterpret_cast<lds_u8_ptr>(fbase[(isA ? 0 : NBA) + f / 2][win]);
-            const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + (soff + (f & 1) * 32)));
-            const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + (soff + (f & 1) * 32 + 4 * W2)));
+            constexpr int W2 = (isA ? BM : BN) * 2, off = poff + ks * (isA ? A_BYTES : B_BYTES) + (f & 1) * 32;
+            const lds_u8_ptr q = reinterpret_cast<lds_u8_ptr>(fbase[(isA ? 0 : NBA) + f / 2][win]);
+            const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(q + off));
+            const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(q + (off + 4 * W2)));
             v = __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
         }
         if constexpr (isA) fa[buf][f & 1] = v;
         else fb[buf][f] = v;
     };
-    // Sub-step T of a pair (T = KS*TM + A): the MFMAs of K-step KS (stage ST + KS) for the 32-row
+    // Sub-step T of pair P of the ring (T = KS*TM + A): the MFMAs of K-step KS for the 32-row
     // block A of the wave's rows against all its columns.  D = Bfrag x Afrag: lane l holds row l%16 of
     // the fragment and 4 adjacent output columns.  Spread between the MFMAs:
     //   * the two A fragments of the next sub-step (the next block of the same K-step, or block 0 of
@@ -457,18 +444,14 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
     //     per sub-step; K-step 0 of the next pair is published by the barrier ahead of the pair's last
     //     sub-step, which therefore reads all of them;
     //   * a share of the wave-loads: the pair at (seg, k0) is loaded in NG groups, group 0 in the last
-    //     sub-step of a pair (into the two stages its barrier has just retired), groups 1.. in the first
-    //     sub-steps of the next pair, the two halves of each 128-byte line of an NT operand row in
-    //     adjacent instructions.
-    auto substep = [&](auto ST, auto T) __attribute__((always_inline)) {
-        constexpr int st = decltype(ST)::value, t = decltype(T)::value;
+    //     sub-step of a pair (into the pair of stages its barrier has just retired), groups 1.. in the first
+    //     sub-steps of the next pair.
+    auto substep = [&](auto P, auto T) __attribute__((always_inline)) {
+        constexpr int p = decltype(P)::value, t = decltype(T)::value;
         constexpr int ks = t / TM, a = t % TM;
-        constexpr int st1 = st + 1, st2 = (st + 2) % NSTG;          // st2: the next pair
-        constexpr int stp = (st + NSTG - 2) % NSTG;                 // the pair before
+        constexpr int nxt = ks == 0 ? p : (p + 1) % NPR;            // pair of the next K-step
         constexpr bool last = t == 2 * TM - 1;
-        constexpr int cur = st + ks;                                // stage of this K-step
-        constexpr int nxt = ks == 0 ? st1 : st2;                    // stage of the next K-step
-        constexpr int a_stage = a + 1 < TM ? cur : nxt, a_blk = a + 1 < TM ? a + 1 : 0;
+        constexpr int a_pair = a + 1 < TM ? p : nxt, a_ks = a + 1 < TM ? ks : ks ^ 1, a_blk = a + 1 < TM ? a + 1 : 0;
         // reads of this sub-step, in the order their first users come: A fragment 0, B fragments, A fragment 1
         constexpr int NB = ks == 0 ? 0 : (last ? FN : 0);           // all B fragments at once
         constexpr int b_lo = ks == 0 ? (a * FN) / TM : 0, b_hi = ks == 0 ? ((a + 1) * FN) / TM : NB;
@@ -476,15 +459,15 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         // wave-loads of this sub-step: group 0 (last sub-step) or group t + 1 (t < TM - 1)
         constexpr int grp = last ? 0 : (t < NG - 1 ? t + 1 : -1);
         constexpr int e_lo = grp < 0 ? 0 : ((grp * NU) / NG) * 2, e_hi = grp < 0 ? 0 : (((grp + 1) * NU) / NG) * 2;
-        constexpr int d0 = last ? st : stp, d1 = d0 + 1;
+        constexpr int dp = last ? p : (p + NPR - 1) % NPR;          // where they go: this pair, or the one before
         static_for<NQ>([&](auto Q) __attribute__((always_inline)) {
             constexpr int q = decltype(Q)::value;
             static_for<NR>([&](auto R) __attribute__((always_inline)) {
                 constexpr int r = decltype(R)::value;
                 if constexpr ((r * NQ) / NR == q) {
-                    if constexpr (r == 0) frag_one(ic<a_stage>{}, ic<2 * a_blk>{}, ic<((a + 1) & 1)>{});
-                    else if constexpr (r == NR - 1) frag_one(ic<a_stage>{}, ic<2 * a_blk + 1>{}, ic<((a + 1) & 1)>{});
-                    else frag_one(ic<nxt>{}, ic<FM + b_lo + r - 1>{}, ic<(ks ^ 1)>{});
+                    if constexpr (r == 0) frag_one(ic<a_pair>{}, ic<a_ks>{}, ic<2 * a_blk>{}, ic<((a + 1) & 1)>{});
+                    else if constexpr (r == NR - 1) frag_one(ic<a_pair>{}, ic<a_ks>{}, ic<2 * a_blk + 1>{}, ic<((a + 1) & 1)>{});
+                    else frag_one(ic<nxt>{}, ic<(ks ^ 1)>{}, ic<FM + b_lo + r - 1>{}, ic<(ks ^ 1)>{});
                 }
             });
             CF_SCHED_FENCE();
@@ -497,7 +480,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
                 constexpr int dsel = load_in_gap(q, e_hi - e_lo, NQ);       // the wave-load that goes with this MFMA
                 if constexpr (dsel >= 0) {
                     constexpr int e = dsel + e_lo;
-                    mma_dma_one(acc[i][j], fb[ks][j], fa[a & 1][h], ic<(e & 1) ? d1 : d0>{}, ic<(e >> 1)>{}, ic<(e & 1)>{});
+                    mma_dma_one(acc[i][j], fb[ks][j], fa[a & 1][h], ic<dp>{}, ic<(e >> 1)>{}, ic<(e & 1)>{});
                 } else {
                     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(fb[ks][j]), "v"(fa[a & 1][h]));
                 }
@@ -506,33 +489,33 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         });
     };
     // loads of the pair at (seg, k0) outside the MFMA stream (prologue): all of them, or group 0 only
-    auto issue_pair = [&](auto D0, auto D1, auto FIRST_GROUP) __attribute__((always_inline)) {
+    auto issue_pair = [&](auto P, auto FIRST_GROUP) __attribute__((always_inline)) {
         prepare_pair();
         static_for<(decltype(FIRST_GROUP)::value ? (NU / NG) * 2 : 2 * NU)>([&](auto E) __attribute__((always_inline)) {
             constexpr int e = decltype(E)::value;
-            dma_one(ic<(e & 1) ? decltype(D1)::value : decltype(D0)::value>{}, ic<(e >> 1)>{}, ic<(e & 1)>{});
+            dma_one(P, ic<(e >> 1)>{}, ic<(e & 1)>{});
         });
     };
-    // One pair of K-steps s, s+1 in stages ST, ST+1 of the ring; the next NPR - 1 pairs lie in the
-    // other stages, and the loads of the pair after those go back into ST, ST+1 once the barrier
-    // has retired them.  The loop body is NPR pairs, so every stage is a compile-time constant.
+    // One pair of K-steps in pair P of the ring; the next NPR - 1 pairs lie in the
+    // others, and the loads of the pair after those go back into P once the barrier
+    // has retired it.  The loop body is NPR pairs, so every LDS place is a compile-time constant.
     // The loads of a pair are issued in NG groups, the first right after the barrier that frees their
-    // stages, which keeps the burst that the load path sees short; the last group still has more
+    // place, which keeps the burst that the load path sees short; the last group still has more
     // than half a pair to land before the next barrier.
-    auto pair_body = [&](auto ST) __attribute__((always_inline)) {
+    auto pair_body = [&](auto P) __attribute__((always_inline)) {
         static_for<2 * TM>([&](auto T) __attribute__((always_inline)) {
             constexpr int t = decltype(T)::value;
             if constexpr (t == 2 * TM - 1) {
                 prepare_pair();
-                wait_vmcnt<(NPR - 2) * 2 * NU>();       // K-steps s+2, s+3 have landed; later pairs (loads only) may be in flight
-                lds_barrier();          // ... and every wave is done with stages ST and ST+1
+                wait_vmcnt<(NPR - 2) * 2 * NU>();       // the next pair has landed; later pairs (loads only) may be in flight
+                lds_barrier();          // ... and every wave is done with pair P
             }
-            substep(ST, T);
+            substep(P, T);
             if constexpr (t == NG - 2) advance_pair();      // the last group of the pair has been issued
         });
     };
 
-    // pairs of K-steps, a segment with an odd number of K-steps padded with a zero K-step
+    // pairs of K-steps; the last one of a segment may be a part of one
     int npairs = SPLIT ? (kend - kbeg + 2 * KB - 1) / (2 * KB) : (K0x + 2 * KB - 1) / (2 * KB);
     if (!SPLIT)
         for (int s = 1; s < g.nseg; ++s) npairs += (g.K[s] + 2 * KB - 1) / (2 * KB);
@@ -547,10 +530,10 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         }
         static_for<NPR - 1>([&](auto P) __attribute__((always_inline)) {
             constexpr int p = decltype(P)::value;
-            issue_pair(ic<2 * p>{}, ic<2 * p + 1>{}, ic<0>{});
+            issue_pair(ic<p>{}, ic<0>{});
             advance_pair();
         });
-        issue_pair(ic<NSTG - 2>{}, ic<NSTG - 1>{}, ic<1>{});        // the loop's first sub-steps issue the other groups
+        issue_pair(ic<NPR - 1>{}, ic<1>{});        // the loop's first sub-steps issue the other groups
     };
     constexpr bool OVERLAP = !SPLIT && !CF32;       // the epilogue leaves the operand stages alone
     if (npairs > 0) start_tile();
@@ -570,26 +553,26 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
             if (DEEP && first_tile) wait_vmcnt<(NPR - 2) * 2 * NU + (NU / NG) * 2>();
             else wait_vmcnt<0>();
             lds_barrier();
-            frag_one(ic<0>{}, ic<0>{}, ic<0>{});
-            static_for<FN>([&](auto J) __attribute__((always_inline)) { frag_one(ic<0>{}, ic<FM + decltype(J)::value>{}, ic<0>{}); });
-            frag_one(ic<0>{}, ic<1>{}, ic<0>{});
+            frag_one(ic<0>{}, ic<0>{}, ic<0>{}, ic<0>{});
+            static_for<FN>([&](auto J) __attribute__((always_inline)) { frag_one(ic<0>{}, ic<0>{}, ic<FM + decltype(J)::value>{}, ic<0>{}); });
+            frag_one(ic<0>{}, ic<0>{}, ic<1>{}, ic<0>{});
             // NPR pairs per iteration.  The small tile, where short contractions are the rule, leaves after the last
             // pair; the others run an odd count's extra pair on zeros (loads past the last segment return them)
             if constexpr (DEEP) {
                 for (int p = npairs;;) {
                     pair_body(ic<0>{});
                     if (--p <= 0) break;
+                    pair_body(ic<1>{});
+                    if (--p <= 0) break;
                     pair_body(ic<2>{});
                     if (--p <= 0) break;
-                    pair_body(ic<4>{});
-                    if (--p <= 0) break;
-                    pair_body(ic<6>{});
+                    pair_body(ic<3>{});
                     if (--p <= 0) break;
                 }
             } else {
                 for (int p = 0; p < npairs; p += 2) {
                     pair_body(ic<0>{});
-                    pair_body(ic<2>{});
+                    pair_body(ic<1>{});
                 }
             }
             wait_vmcnt<0>();

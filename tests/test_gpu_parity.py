@@ -157,6 +157,21 @@ def test_linear_small_tiles_short_contraction(k):
             assert bool((err <= ref.abs() * 2.0 ** -8 + 1e-4 * math.sqrt(k)).all()), (n, fin, fout, err.max().item())
 
 
+@pytest.mark.parametrize("k", [8, 56, 72, 104, 128, 136, 200])
+@pytest.mark.parametrize("n,fin", [(2048, 8192), (2500, 3600), (1024, 8192)])
+def test_linear_large_tiles_ragged_contraction(n, fin, k):
+    """dX outputs on 256x256, 256x192 and 256x128 tiles whose contraction ends inside a 64-wide step, in its first or its
+    second half.  Bounds as above."""
+    gen = torch.Generator(device=DEV).manual_seed(k + n)
+    rn = lambda *s: torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16)
+    dy, w, dx = rn(n, k), rn(fin, k), torch.empty(n, fin, dtype=torch.bfloat16, device=DEV)
+    Bn._check(Bn.lib().cf_linear_bwd_reduced(None, Bn._ptr(dy), Bn._ptr(w), n, fin, k, Bn.CF_BF16, Bn._ptr(dx), None, 0.0,
+                                             Bn._stream()), "cf_linear_bwd_reduced")
+    ref = dy.double() @ w.double().T
+    err = (dx.double() - ref).abs()
+    assert bool((err <= ref.abs() * 2.0 ** -8 + 1e-4 * math.sqrt(k)).all()), err.max().item()
+
+
 @pytest.mark.parametrize("n,fin,fout", [(128, 2048, 256), (300, 1032, 520), (2048, 2048, 2048)])
 def test_linear_dw_over_w(n, fin, fout):
     """dW written over W: dX still comes from the weights that were there, whether the two products would share a launch
