@@ -162,8 +162,8 @@ struct GemmSeg {
 // C[M,N] = beta*C + sum_seg op(A_seg)*op(B_seg), up to six segments; all matrices dense row-major.
 //   mode 0 ("NT"): A_seg [M,K], B_seg [N,K]      (C = A * B^T)
 //   mode 1 ("TN"): A_seg [K,M], B_seg [K,N]      (C = A^T * B)
-// c_f32 (bf16 dtype only): C is an fp32 matrix (a main-gradient buffer) and the accumulators are
-// added to beta*C without rounding to bf16.
+// c_f32 (bf16 dtype, mode 1, beta = 1 only): C is an fp32 matrix (a main-gradient buffer) and the accumulators are
+// added to it without rounding to bf16.
 // n_dev (nullable): the kept-token count on the device; then the kept-token dimension of the product
 // (M in mode 0, the K of segment 0 in mode 1) is only an upper bound and the kernel uses
 // min(*n_dev, bound).  a_idx (nullable, mode 0, segment 0): row m of A is row a_idx[m] of a longer

@@ -88,10 +88,10 @@ struct GemmArgs {
     int M, N;
     float beta;
     float alpha;    // the product is scaled by alpha before beta*C is added
-    int c_f32;      // bf16 kernels: C is fp32 (a main-gradient buffer), written without rounding
+    int c_f32;      // bf16 kernels, mode TN: C is fp32 (a main-gradient buffer) that the product is added to, without rounding
     int n_full;     // leading blocks that own a whole 256x256 tile
     int sub;        // the remaining tiles are cut into `sub` (1, 2 or 4) sub-tiles, one block each
-    int tile_n;     // 256, or 192 (NT, bf16 output only): every tile is 256x192 and n_full, sub are unused
+    int tile_n;     // 256, or 192 (NT only): every tile is 256x192 and n_full, sub are unused
     // Column groups (ngroups > 1, one K segment): output columns [off_j, off_j + Ng[j]) belong to a
     // matrix of their own, C = Cg[j] [M, Ng[j]] with B operand Bg[j]; every Ng[j] is a multiple of
     // 256, so a tile lies in one group.  N is the sum of the Ng.  One launch then covers several
@@ -140,13 +140,13 @@ __host__ __device__ inline double plan_tiles(int tiles, int n_cu, int& n_full, i
 // Tile plan of a bf16 launch with n_cu blocks: sets n_full, sub, tile_n; returns the number of work
 // items.  The host plans a launch whose sizes it knows; with a device-side count every block runs
 // the same code on the count it read, so both give the same tiles for the same sizes.
-__host__ __device__ inline int plan_launch(int M, int N, int mode, bool c_f32, int ngroups, int n_cu,
+__host__ __device__ inline int plan_launch(int M, int N, int mode, int ngroups, int n_cu,
                                            int& n_full, int& sub, int& tile_n) {
     const int tiles = cdiv(M, 256) * cdiv(N, 256);
     const double rounds = plan_tiles(tiles, n_cu, n_full, sub);
     int items = n_full + (tiles - n_full) * sub;
     tile_n = 256;
-    if (mode == 0 && !c_f32 && ngroups == 1) {
+    if (mode == 0 && ngroups == 1) {
         // 256x192 tiles instead, when they fill the CUs better (an output of 16 x 12 tiles of
         // 256x256 leaves a quarter of the CUs idle; as 16 x 16 tiles of 256x192 it is one full round)
         const int tiles192 = cdiv(M, 256) * cdiv(N, 192);
@@ -163,7 +163,7 @@ typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
 typedef __attribute__((address_space(3))) s16x4_t* lds_s16x4_ptr;
 
 static constexpr int GEMM_RING = 128 * 1024;        // the operand stages; their number and size depend on the tile (gemm_tiles)
-static constexpr int GEMM_SMEM = 160 * 1024;    // the whole LDS of a CU: the ring and the bf16 write-out's staging above it, or the fp32 write-out's (130 KB, over the ring)
+static constexpr int GEMM_SMEM = 160 * 1024;    // the whole LDS of a CU: the ring and the bf16 write-out's staging above it
 
 // Position l of a block in the logical order of its group of n blocks: XCD x (block id
 // mod 8) takes the x-th contiguous share of the order.
@@ -214,7 +214,7 @@ struct TileRef {
 };
 
 // The block's output tiles of (64*TM) x (64*TN), one after the other: `first`, then whatever
-// next_tile(TileRef&) hands out until it returns false.  With bf16 output the loads of the next
+// next_tile(TileRef&) hands out until it returns false.  The loads of the next
 // tile's first K-steps are in flight while the finished tile leaves through a staging area of its
 // own, and its stores drain under the next tile's MFMAs.  SPLIT: the block contracts only k in
 // [kbeg, kend) of the single segment and stores its fp32 accumulators, unscaled, to `part_out`
@@ -535,7 +535,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
         });
         issue_pair(ic<NPR - 1>{}, ic<1>{});        // the loop's first sub-steps issue the other groups
     };
-    constexpr bool OVERLAP = !SPLIT && !CF32;       // the epilogue leaves the operand stages alone
+    constexpr bool OVERLAP = !SPLIT;        // the epilogue leaves the operand stages alone
     if (npairs > 0) start_tile();
     for (bool first_tile = true;; first_tile = false) {
 #pragma unroll
@@ -604,66 +604,41 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
     }
     const float alpha = g.alpha;
     if constexpr (CF32) {
-        // ---- fp32 epilogue: the two halves of the tile rows (one per wave row) go through LDS in
-        // turn, then out as full rows of 16-byte stores, added to beta*C in fp32
-        constexpr int HP = BN * 4 + 16;                     // pitch of a staged row of floats
-        static_assert((BM / 2) * HP <= GEMM_SMEM, "fp32 staging");
-        float* C = static_cast<float*>(ep.C);
-        const float beta = g.beta;
-        constexpr int CPR = BN / 4, RPP = 256 / CPR;        // 16-byte chunks per row, rows per pass
-        const int c = tid % CPR, r0 = tid / CPR;
-        const int n = n0 + c * 4;
-#pragma unroll 1
-        for (int h = 0; h < 2; ++h) {
-            lds_barrier();
-            if (wm == h) {
+        // ---- fp32 epilogue: C += the tile, straight from the accumulators: a lane's 4 adjacent columns are 16 bytes of a row, and
+        // the four lanes of a row cover half a line, whose other half is the next column fragment.  The old values of the
+        // next 16 rows are on their way while these are added.  No LDS, so the next tile's operands are loaded meanwhile, as in
+        // the bf16 epilogue.  (Through LDS in two halves of the tile, to whole rows, with nothing else in flight:
+        // [5632, 2048] += , K = 8192, 238 us, now 223.)
+        // Descriptor over this wave's rows: an offset stays below 2^31 for every N that the launcher accepts.
+        const int mw = m0 + wm * (32 * TM), rows = min(Mx - mw, 32 * TM);
+        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
+            static_cast<float*>(ep.C) + (int64_t)mw * ep.N, 0, rows > 0 ? (int)((unsigned)rows * (unsigned)ep.N * 4u) : 0, 0x00020000);
+        int ln = lane;                                      // as in open_segment: rebuilt per tile, not carried
+        asm volatile("" : "+v"(ln));
+        const unsigned row_bytes = (unsigned)ep.N * 4u;
+        const int n = n0 + wn * (32 * TN) + 4 * (ln >> 4);
+        const unsigned voff = (unsigned)(ln & 15) * row_bytes + (unsigned)n * 4u;
+        u32x4_t old[2][FN];
+        auto fetch = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
-                for (int i = 0; i < FM; ++i)
+            for (int j = 0; j < FN; ++j)                    // N is a multiple of 8
+                old[i & 1][j] = __builtin_amdgcn_raw_buffer_load_b128(
+                    rc, n + j * 16 < ep.N ? voff + (unsigned)(i * 16) * row_bytes + j * 64u : OOB_FAST, 0, 0);
+        };
+        fetch(0);
 #pragma unroll
-                    for (int j = 0; j < FN; ++j) {
-                        const int r = i * 16 + l16;
-                        const int cc = wn * (32 * TN) + j * 16 + 4 * g4;
-                        float4 o;
-                        o.x = acc[i][j][0] * alpha; o.y = acc[i][j][1] * alpha;
-                        o.z = acc[i][j][2] * alpha; o.w = acc[i][j][3] * alpha;
-                        *reinterpret_cast<float4*>(smem + r * HP + cc * 4) = o;
-                    }
-            }
-            lds_barrier();
-            if (n < ep.N) {                                  // N is a multiple of 8
-                // eight rows per round: all loads of the old values are in flight before the first add
-                constexpr int RB = 8;
-                static_assert((BM / 2) % (RPP * RB) == 0, "row batches");
-#pragma unroll 1
-                for (int rb = r0; rb < BM / 2; rb += RPP * RB) {
-                    float4 old[RB], val[RB];
+        for (int i = 0; i < FM; ++i) {
+            if (i + 1 < FM) fetch(i + 1);
 #pragma unroll
-                    for (int q = 0; q < RB; ++q) {
-                        const int m = m0 + h * (BM / 2) + rb + q * RPP;
-                        old[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-                        if (beta != 0.f && m < Mx) old[q] = *reinterpret_cast<const float4*>(C + (int64_t)m * ep.N + n);
-                    }
+            for (int j = 0; j < FN; ++j) {
+                u32x4_t o;
 #pragma unroll
-                    for (int q = 0; q < RB; ++q)
-                        val[q] = *reinterpret_cast<const float4*>(smem + (rb + q * RPP) * HP + c * 16);
-#pragma unroll
-                    for (int q = 0; q < RB; ++q) {
-                        const int m = m0 + h * (BM / 2) + rb + q * RPP;
-                        if (m < Mx) {
-                            val[q].x += beta * old[q].x; val[q].y += beta * old[q].y;
-                            val[q].z += beta * old[q].z; val[q].w += beta * old[q].w;
-                            *reinterpret_cast<float4*>(C + (int64_t)m * ep.N + n) = val[q];
-                        }
-                    }
-                }
+                for (int e = 0; e < 4; ++e) o[e] = __float_as_uint(acc[i][j][e] * alpha + __uint_as_float(old[i & 1][j][e]));
+                __builtin_amdgcn_raw_buffer_store_b128(
+                    o, rc, n + j * 16 < ep.N ? voff + (unsigned)(i * 16) * row_bytes + j * 64u : OOB_FAST, 0, 0);
             }
         }
-        // The staging area overlaps the operand stages: every wave is done with it before anybody's loads go into them
-        // again, those of this call's next tile or, behind the last one, those that the block's next call of this function
-        // starts with (a block's whole tiles are followed by its share of the cut ones).
-        lds_barrier();
         if (!has_next) break;
-        if (npairs > 0) start_tile();
         continue;
     }
     // ---- epilogue: 32 rows of the wave tile at a time: acc -> bf16 -> the wave's own 8 KB above the
@@ -752,7 +727,7 @@ __device__ __forceinline__ void gemm_bf16_block(const GemmArgs& g, unsigned char
         n = __builtin_amdgcn_readfirstlane(n < 0 ? 0 : n);
         if (MODE == 0) {
             Mx = n < Mx ? n : Mx;
-            plan_launch(Mx, g.N, 0, g.c_f32 != 0, g.ngroups, (int)gridDim.x, n_full, sub, tile_n);
+            plan_launch(Mx, g.N, 0, g.ngroups, (int)gridDim.x, n_full, sub, tile_n);
             n_full = __builtin_amdgcn_readfirstlane(n_full);
             sub = __builtin_amdgcn_readfirstlane(sub);
             tile_n = __builtin_amdgcn_readfirstlane(tile_n);
@@ -762,7 +737,7 @@ __device__ __forceinline__ void gemm_bf16_block(const GemmArgs& g, unsigned char
     }
     const int tiles_m = (Mx + 255) / 256, tiles_n = (g.N + 255) / 256;
     const int stride = (int)gridDim.x;
-    if constexpr (MODE == 0 && !CF32) {
+    if constexpr (MODE == 0) {
         if (tile_n == 192) {
             // tiles of 256x192, all of one kind: block b takes tiles b, b + gridDim.x, ...
             const int tiles_n192 = (g.N + 191) / 192, n_items = tiles_m * tiles_n192;
@@ -865,11 +840,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
     gemm_bf16_block<MODE, false>(g, smem);
 }
 
-// The same with fp32 output (main-gradient buffers): C is float, added to beta*C without rounding.
-template <int MODE>
+// Parameter gradients added to fp32 main-gradient buffers.
 __global__ __launch_bounds__(256) void gemm_bf16_f32out_kernel(GemmArgs g) {
     extern __shared__ __align__(16) unsigned char smem[];
-    gemm_bf16_block<MODE, true>(g, smem);
+    gemm_bf16_block<1, true>(g, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -1111,15 +1085,15 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
 template <int MODE>
 static hipError_t launch_bf16(GemmArgs& g, hipStream_t st) {
     static std::atomic<uint64_t> lds_ok{0}, lds_ok_f32{0};
-    hipError_t e = g.c_f32 ? allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_bf16_f32out_kernel<MODE>), GEMM_SMEM, lds_ok_f32)
-                           : allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_bf16_kernel<MODE>), GEMM_SMEM, lds_ok);
+    const bool f32 = MODE == 1 && g.c_f32;
+    void (*const kernel)(GemmArgs) = f32 ? gemm_bf16_f32out_kernel : gemm_bf16_kernel<MODE>;
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), GEMM_SMEM, f32 ? lds_ok_f32 : lds_ok);
     if (e != hipSuccess) return e;
-    const int items = plan_launch(g.M, g.N, MODE, g.c_f32 != 0, g.ngroups, compute_units(), g.n_full, g.sub, g.tile_n);
+    const int items = plan_launch(g.M, g.N, MODE, g.ngroups, compute_units(), g.n_full, g.sub, g.tile_n);
     // a block walks through its items; with a device-side count the blocks plan for themselves (for
     // as many blocks as CUs) and those without an item leave at once
     const int grid = g.n_dev != nullptr ? compute_units() : std::min(items, compute_units());
-    if (g.c_f32) gemm_bf16_f32out_kernel<MODE><<<grid, 256, GEMM_SMEM, st>>>(g);
-    else gemm_bf16_kernel<MODE><<<grid, 256, GEMM_SMEM, st>>>(g);
+    kernel<<<grid, 256, GEMM_SMEM, st>>>(g);
     return hipGetLastError();
 }
 
@@ -1129,6 +1103,7 @@ hipError_t launch_gemm(int dtype, int mode, const GemmSeg* segs, int nseg, void*
     if (M <= 0 || N <= 0) return hipSuccess;
     if (a_idx != nullptr && (mode != 0 || a_rows <= 0)) return hipErrorInvalidValue;
     if (nseg > MAX_SEG) return hipErrorInvalidValue;
+    if (c_f32 && dtype == CF_BF16 && (mode != 1 || beta != 1.f)) return hipErrorInvalidValue;
     GemmArgs g;
     g.nseg = 0;
     for (int s = 0; s < nseg; ++s) {
@@ -1180,6 +1155,7 @@ hipError_t launch_gemm_tn_groups(const void* A, int K, int M, int ngroups, const
                                  void* const* Cg, const int* Ng, hipStream_t st, float beta, bool c_f32,
                                  const int32_t* n_dev) {
     if (M <= 0) return hipSuccess;
+    if (c_f32 && beta != 1.f) return hipErrorInvalidValue;
     GemmArgs g;
     int N = 0;
     for (int j = 0; j < 3; ++j) {
