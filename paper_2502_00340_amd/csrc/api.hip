@@ -201,11 +201,6 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     const int64_t T = (int64_t)L.B * L.S;
     // main-gradient mode: the nine parameter gradients are fp32 buffers that this call adds to
     const bool mg = G.main_grad != 0;
-    auto dw_gemm = [&](const void* A, const void* B, void* C, int M, int Ncols) {
-        GemmSeg s{A, B, N};
-        return launch_gemm(dt, 1, &s, 1, C, M, Ncols, mg ? 1.f : 0.f, st, mg, nd);
-    };
-
     if (N == 0) {   // nothing kept (known to the host): every gradient is zero, dx has no rows
         if (mg) return CF_OK;
         void* outs[9] = {G.dwq, G.dwk, G.dwv, G.dwo, G.dwg, G.dwu, G.dwd, G.dg1, G.dg2};
@@ -215,6 +210,34 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
         return CF_OK;
     }
     if (dy_is_full && !idx) return CF_ERR_NULL;
+    const void* dy_rows = dy_is_full ? w.dy_k : dy;
+    const void* a_rows = idx ? w.a_k : sv.attn_out;
+    const void* q_rows = idx ? w.q_k : sv.q;
+    // The seven dW products wait for nothing but their operands, which stay where they are until the end: one launch then
+    // has one remainder of tiles, not four.  Two operands may be the caller's (the upstream gradient of a compact or
+    // dense call, the attention output of a dense one): where an output lies over them, which the order of the passes has always
+    // allowed for dx, each product goes out as soon as its operands exist.
+    bool late = true;
+    {
+        const size_t ps = mg ? 4 : e, n = (size_t)N;
+        const struct { const void* p; size_t bytes; } outs[] = {
+            {G.dx, n * H * e}, {G.dg1, H * ps}, {G.dg2, H * ps}, {G.dwq, (size_t)H * Nq * ps}, {G.dwk, (size_t)H * Nkv * ps},
+            {G.dwv, (size_t)H * Nkv * ps}, {G.dwo, (size_t)Nq * H * ps}, {G.dwg, (size_t)H * F * ps}, {G.dwu, (size_t)H * F * ps},
+            {G.dwd, (size_t)F * H * ps}};
+        for (const auto& o : outs)
+            late = late && !overlap(o.p, o.bytes, dy_rows, n * H * e) && !overlap(o.p, o.bytes, a_rows, n * Nq * e);
+    }
+    GemmTnProb dws[TN_MAX];
+    int n_dw = 0;
+    auto dw_launch = [&]() {
+        const int np = n_dw;
+        n_dw = 0;
+        return np ? launch_gemm_tn(dt, dws, np, N, mg ? 1.f : 0.f, st, mg, nd) : hipSuccess;
+    };
+    auto dw = [&](const void* A, const void* B, void* C, int M, int Ncols) {
+        dws[n_dw++] = GemmTnProb{A, B, C, M, Ncols};
+        return late ? hipSuccess : dw_launch();
+    };
 
     // ---- SwiGLU FFN: y = r + act*Wd --------------------------------------------
     // d_act = dy * Wd^T first; one pass over it then yields d_gate, d_up and act (the SwiGLU
@@ -222,20 +245,19 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     void* d_act = w.bufF1;
     {   // [N,F] = [N,H] x [F,H]^T
         GemmSeg s{dy, W.wd, H};
-        CF_HIP(launch_gemm(dt, 0, &s, 1, d_act, N, F, 0.f, st, false, nd, dy_is_full ? idx : nullptr, dy_is_full ? T : 0));
+        CF_HIP(launch_gemm_nt(dt, &s, 1, d_act, N, F, st, nd, dy_is_full ? idx : nullptr, dy_is_full ? T : 0));
     }
     void* d_gate = w.bufF1;   // in place over d_act
     void* d_up = w.bufF0;
     void* act = w.bufF2;
-    const void* dy_rows = dy_is_full ? w.dy_k : dy;
     CF_HIP(launch_swiglu_bwd(dt, d_act, sv.gate, sv.up, idx, rows, F, d_gate, d_up, act, st,
                              dy_is_full ? dy : nullptr, H, dy_is_full ? w.dy_k : nullptr));
-    CF_HIP(dw_gemm(act, dy_rows, G.dwd, F, H));     // dWd = act^T * dy           [F,H]
+    CF_HIP(dw(act, dy_rows, G.dwd, F, H));     // dWd = act^T * dy           [F,H]
 
     void* dh2 = w.bufHb;
     {   // dh2 = d_gate*Wg^T + d_up*Wu^T   [N,H], contraction over F twice
         GemmSeg s[2] = {{d_gate, W.wg, F}, {d_up, W.wu, F}};
-        CF_HIP(launch_gemm(dt, 0, s, 2, dh2, N, H, 0.f, st, false, nd));
+        CF_HIP(launch_gemm_nt(dt, s, 2, dh2, N, H, st, nd));
     }
     // dr = dy + rmsnorm_bwd(dh2; r, g2);  dg2.  The pass has r and its rstd in registers, so it also
     // writes h2 = rmsnorm(r)*g2, the operand of the two parameter-gradient products below (which is why
@@ -243,31 +265,20 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     void* h2 = w.bufHa;
     CF_HIP(launch_rmsnorm_bwd(dt, dh2, sv.r, W.g2, idx, dy_rows, rows, H, L.rms_eps, w.dr, w.dg_partial,
                               G.dg2, st, mg, h2));
-    {   // dWg, dWu = h2^T * d_gate, d_up: one launch (7 rounds of tiles instead of 2 x 3.5 at the 8B shape)
-        const int Ng[2] = {F, F};
-        if (gemm_tn_groups_supported(dt, N, 2, Ng)) {
-            const void* Bg[2] = {d_gate, d_up};
-            void* Cg[2] = {G.dwg, G.dwu};
-            CF_HIP(launch_gemm_tn_groups(h2, N, H, 2, Bg, Cg, Ng, st, mg ? 1.f : 0.f, mg, nd));
-        } else {
-            CF_HIP(dw_gemm(h2, d_gate, G.dwg, H, F));
-            CF_HIP(dw_gemm(h2, d_up, G.dwu, H, F));
-        }
-    }
+    CF_HIP(dw(h2, d_gate, G.dwg, H, F));
+    CF_HIP(dw(h2, d_up, G.dwu, H, F));
 
     // ---- attention block: r = x + attn_out*Wo ------------------------------------
     {
         GemmSeg s2{w.dr, W.wo, H};                        // da = dr * Wo^T      [N,Nq]
-        CF_HIP(launch_gemm(dt, 0, &s2, 1, w.da, N, Nq, 0.f, st, false, nd));
+        CF_HIP(launch_gemm_nt(dt, &s2, 1, w.da, N, Nq, st, nd));
     }
     // the attention backward's row-statistics pass reads attn_out and q through idx and leaves their
     // compact copies in w.a_k, w.q_k (no gather kernel)
-    const void* a_rows = idx ? w.a_k : sv.attn_out;
-    const void* q_rows = idx ? w.q_k : sv.q;
     cf_status as = attn_dispatch(L, q_rows, sv.k, sv.v, a_rows, sv.lse, w.da, idx, cu_kept, rows, w.dq,
                                  w.dk, w.dv, w.attn_ws, st, idx ? sv.attn_out : nullptr, idx ? sv.q : nullptr);
     if (as != CF_OK) return as;
-    CF_HIP(dw_gemm(a_rows, w.dr, G.dwo, Nq, H));          // dWo = a^T * dr      [Nq,H]
+    CF_HIP(dw(a_rows, w.dr, G.dwo, Nq, H));          // dWo = a^T * dr      [Nq,H]
 
     if (sv.rope_cos) {      // transposed rotation of dq and dk at the original positions of the kept rows
         CF_HIP(launch_rope_bwd(dt, w.dq, L.Hq, w.dk, L.Hkv, idx, rows, L.d, L.S, sv.rope_cos, sv.rope_sin, st));
@@ -275,31 +286,16 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     void* dh1 = w.bufHb;
     {   // dh1 = dq*Wq^T + dk*Wk^T + dv*Wv^T
         GemmSeg s[3] = {{w.dq, W.wq, Nq}, {w.dk, W.wk, Nkv}, {w.dv, W.wv, Nkv}};
-        CF_HIP(launch_gemm(dt, 0, s, 3, dh1, N, H, 0.f, st, false, nd));
+        CF_HIP(launch_gemm_nt(dt, s, 3, dh1, N, H, st, nd));
     }
-    // dx = dr + rmsnorm_bwd(dh1; x, g1);  dg1; h1 = rmsnorm(x)*g1 on the way (see h2 above)
-    void* h1 = w.bufHa;
+    // dx = dr + rmsnorm_bwd(dh1; x, g1);  dg1; h1 = rmsnorm(x)*g1 on the way (see h2 above), over dh1: h2 is still an operand
+    void* h1 = dh1;
     CF_HIP(launch_rmsnorm_bwd(dt, dh1, sv.x, W.g1, idx, w.dr, rows, H, L.rms_eps, G.dx, w.dg_partial,
                               G.dg1, st, mg, h1));
-    {   // dWq, dWk, dWv = h1^T * dq, dk, dv: one launch when the column groups fall on tile boundaries
-        const int Ng[3] = {Nq, Nkv, Nkv};
-        if (gemm_tn_groups_supported(dt, N, 3, Ng)) {
-            const void* Bg[3] = {w.dq, w.dk, w.dv};
-            void* Cg[3] = {G.dwq, G.dwk, G.dwv};
-            CF_HIP(launch_gemm_tn_groups(h1, N, H, 3, Bg, Cg, Ng, st, mg ? 1.f : 0.f, mg, nd));
-        } else if (!mg && dt == CF_BF16 && ceil_div(H, 128) * (ceil_div(Nq, 128) + 2 * ceil_div(Nkv, 128)) <= compute_units()) {
-            // narrow outputs (a tensor-parallel share's heads): 128x128 tiles of all three in one launch that fits one
-            // round of the CUs (H = 4096, 512 + 128 + 128 columns, 841 kept rows: 36 us as three launches, 15 us as one)
-            const GemmGroupProb ps[3] = {{h1, w.dq, G.dwq, H, Nq, N, 1, 1.f},
-                                         {h1, w.dk, G.dwk, H, Nkv, N, 1, 1.f},
-                                         {h1, w.dv, G.dwv, H, Nkv, N, 1, 1.f}};
-            CF_HIP(launch_gemm_group(dt, ps, 3, st, nullptr, nd));
-        } else {
-            CF_HIP(dw_gemm(h1, w.dq, G.dwq, H, Nq));
-            CF_HIP(dw_gemm(h1, w.dk, G.dwk, H, Nkv));
-            CF_HIP(dw_gemm(h1, w.dv, G.dwv, H, Nkv));
-        }
-    }
+    CF_HIP(dw(h1, w.dq, G.dwq, H, Nq));
+    CF_HIP(dw(h1, w.dk, G.dwk, H, Nkv));
+    CF_HIP(dw(h1, w.dv, G.dwv, H, Nkv));
+    CF_HIP(dw_launch());
     return CF_OK;
 }
 
@@ -354,7 +350,7 @@ cf_status layer_core_lora(const cf_layer_desc& L, const cf_saved& sv, const cf_w
     void* d_act = w.bufF1;
     {
         GemmSeg s{dy, W.wd, H};
-        CF_HIP(launch_gemm(dt, 0, &s, 1, d_act, N, F, 0.f, st, false, nd, dy_is_full ? idx : nullptr, dy_is_full ? T : 0));
+        CF_HIP(launch_gemm_nt(dt, &s, 1, d_act, N, F, st, nd, dy_is_full ? idx : nullptr, dy_is_full ? T : 0));
     }
     void* d_gate = w.bufF1;
     void* d_up = w.bufF0;
@@ -364,14 +360,14 @@ cf_status layer_core_lora(const cf_layer_desc& L, const cf_saved& sv, const cf_w
     void* dh2 = w.bufHb;
     {
         GemmSeg s[2] = {{d_gate, W.wg, F}, {d_up, W.wu, F}};
-        CF_HIP(launch_gemm(dt, 0, s, 2, dh2, N, H, 0.f, st, false, nd));
+        CF_HIP(launch_gemm_nt(dt, s, 2, dh2, N, H, st, nd));
     }
     CF_HIP(launch_rmsnorm_bwd(dt, dh2, sv.r, W.g2, idx, dy_rows, rows, H, L.rms_eps, w.dr, w.dg_partial, nullptr, st));
     // ---- adapted O projection: input a [N,Nq], output gradient dr [N,H]
     CF_HIP(group({{w.dr, A.bo, lw.to, N, R, H, 0, A.scale}}));
     {   // da = dr*Wo^T + t_o*a_o^T
         GemmSeg s[2] = {{w.dr, W.wo, H}, {lw.to, A.ao, R}};
-        CF_HIP(launch_gemm(dt, 0, s, 2, w.da, N, Nq, 0.f, st, false, nd));
+        CF_HIP(launch_gemm_nt(dt, s, 2, w.da, N, Nq, st, nd));
     }
     const void* a_rows = idx ? w.a_k : sv.attn_out;
     const void* q_rows = idx ? w.q_k : sv.q;
@@ -395,7 +391,7 @@ cf_status layer_core_lora(const cf_layer_desc& L, const cf_saved& sv, const cf_w
     {   // dh1 = dq*Wq^T + dk*Wk^T + dv*Wv^T + t_q*a_q^T + t_k*a_k^T + t_v*a_v^T
         GemmSeg s[6] = {{w.dq, W.wq, Nq}, {w.dk, W.wk, Nkv}, {w.dv, W.wv, Nkv},
                         {lw.tq, A.aq, R}, {lw.tk, A.ak, R}, {lw.tv, A.av, R}};
-        CF_HIP(launch_gemm(dt, 0, s, 6, dh1, N, H, 0.f, st, false, nd));
+        CF_HIP(launch_gemm_nt(dt, s, 6, dh1, N, H, st, nd));
     }
     void* h1 = w.bufHa;         // a by-product of the norm's backward pass
     CF_HIP(launch_rmsnorm_bwd(dt, dh1, sv.x, W.g1, idx, w.dr, rows, H, L.rms_eps, G.dx, w.dg_partial, nullptr, st, false, h1));
@@ -536,11 +532,11 @@ cf_status cf_linear_bwd_reduced(const void* x_kept, const void* dy_kept, const v
     }
     if (dx_kept && n_kept > 0) {
         GemmSeg seg{dy_kept, w, out};
-        CF_HIP(launch_gemm(dtype, 0, &seg, 1, dx_kept, n_kept, in, 0.f, st));
+        CF_HIP(launch_gemm_nt(dtype, &seg, 1, dx_kept, n_kept, in, st));
     }
     if (dw) {
-        GemmSeg seg{x_kept, dy_kept, n_kept};
-        CF_HIP(launch_gemm(dtype, 1, &seg, 1, dw, in, out, dw_beta, st));
+        const GemmTnProb p{x_kept, dy_kept, dw, in, out};
+        CF_HIP(launch_gemm_tn(dtype, &p, 1, n_kept, dw_beta, st));
     }
     return CF_OK;
 }

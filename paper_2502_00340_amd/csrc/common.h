@@ -159,18 +159,24 @@ struct GemmSeg {
     const void* B;
     int K;
 };
-// C[M,N] = beta*C + sum_seg op(A_seg)*op(B_seg), up to six segments; all matrices dense row-major.
-//   mode 0 ("NT"): A_seg [M,K], B_seg [N,K]      (C = A * B^T)
-//   mode 1 ("TN"): A_seg [K,M], B_seg [K,N]      (C = A^T * B)
-// c_f32 (bf16 dtype, mode 1, beta = 1 only): C is an fp32 matrix (a main-gradient buffer) and the accumulators are
-// added to it without rounding to bf16.
-// n_dev (nullable): the kept-token count on the device; then the kept-token dimension of the product
-// (M in mode 0, the K of segment 0 in mode 1) is only an upper bound and the kernel uses
-// min(*n_dev, bound).  a_idx (nullable, mode 0, segment 0): row m of A is row a_idx[m] of a longer
+// C [M,N] = sum_seg A_seg [M,K] * B_seg [N,K]^T, up to six segments; all matrices dense row-major.
+// n_dev (nullable): the kept-token count on the device; then M is only an upper bound and the kernel uses
+// min(*n_dev, M) rows.  a_idx (nullable, segment 0): row m of A is row a_idx[m] of a longer
 // matrix (the gather of the upstream gradient folded into the A-tile loads); a_rows = rows of that matrix.
-hipError_t launch_gemm(int dtype, int mode, const GemmSeg* segs, int nseg, void* C, int M, int N,
-                       float beta, hipStream_t st, bool c_f32 = false, const int32_t* n_dev = nullptr,
-                       const int32_t* a_idx = nullptr, int64_t a_rows = 0);
+hipError_t launch_gemm_nt(int dtype, const GemmSeg* segs, int nseg, void* C, int M, int N, hipStream_t st,
+                          const int32_t* n_dev = nullptr, const int32_t* a_idx = nullptr, int64_t a_rows = 0);
+
+// One launch for up to TN_MAX products over the same K rows: C_j [M,N] = beta*C_j + A_j [K,M]^T * B_j [K,N].  c_f32 (bf16
+// dtype, beta = 1): the C_j are fp32 (main-gradient buffers) and the accumulators are added to them without rounding to
+// bf16.  No product may read another one's result.  n_dev (nullable): the kept-token count, which bounds K.
+static constexpr int TN_MAX = 7;
+struct GemmTnProb {
+    const void *A, *B;
+    void* C;
+    int M, N;
+};
+hipError_t launch_gemm_tn(int dtype, const GemmTnProb* probs, int np, int K, float beta, hipStream_t st, bool c_f32 = false,
+                          const int32_t* n_dev = nullptr);
 
 // One launch for up to GROUP_MAX independent products C [M,N] = alpha * op(A) * op(B) with few output tiles:
 //   mode 0 ("NT"): A [M,K], B [N,K]    1 ("TN"): A [K,M], B [K,N]    2 ("NN"): A [M,K], B [K,N]
@@ -188,13 +194,6 @@ struct GemmGroupProb {
 size_t gemm_group_slot_bytes();
 hipError_t launch_gemm_group(int dtype, const GemmGroupProb* probs, int np, hipStream_t st, float* slots = nullptr,
                              const int32_t* n_dev = nullptr);
-
-// One TN launch for up to three products that share A [K,M]: C_j [M,Ng[j]] = A^T * B_j [K,Ng[j]].
-// bf16 only, every Ng[j] a multiple of 256 (gemm_tn_groups_supported says whether it applies).
-bool gemm_tn_groups_supported(int dtype, int K, int ngroups, const int* Ng);
-hipError_t launch_gemm_tn_groups(const void* A, int K, int M, int ngroups, const void* const* Bg,
-                                 void* const* Cg, const int* Ng, hipStream_t st, float beta = 0.f,
-                                 bool c_f32 = false, const int32_t* n_dev = nullptr);
 
 // CUs of the current device (cached per device ordinal; 256 if the query fails)
 inline int compute_units() {

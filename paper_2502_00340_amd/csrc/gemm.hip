@@ -88,18 +88,9 @@ struct GemmArgs {
     int M, N;
     float beta;
     float alpha;    // the product is scaled by alpha before beta*C is added
-    int c_f32;      // bf16 kernels, mode TN: C is fp32 (a main-gradient buffer) that the product is added to, without rounding
     int n_full;     // leading blocks that own a whole 256x256 tile
     int sub;        // the remaining tiles are cut into `sub` (1, 2 or 4) sub-tiles, one block each
     int tile_n;     // 256, or 192 (NT only): every tile is 256x192 and n_full, sub are unused
-    // Column groups (ngroups > 1, one K segment): output columns [off_j, off_j + Ng[j]) belong to a
-    // matrix of their own, C = Cg[j] [M, Ng[j]] with B operand Bg[j]; every Ng[j] is a multiple of
-    // 256, so a tile lies in one group.  N is the sum of the Ng.  One launch then covers several
-    // products that share their A operand (the dW of the q, k and v projections).
-    int ngroups;
-    const void* Bg[3];
-    void* Cg[3];
-    int Ng[3];
     // Kept-token count on the device (nullable).  When set, the kept-token dimension handed in by the
     // host (M in mode NT, K[0] in mode TN) is only an upper bound: every block reads the count, takes
     // min(count, bound) for that dimension and, in mode NT, plans the tiles itself (plan_launch).
@@ -108,6 +99,16 @@ struct GemmArgs {
     // gather of the upstream gradient's kept rows, folded into the A-tile loads).
     const int32_t* a_idx;
     int64_t a_rows;
+};
+
+// Mode TN: up to TN_MAX products C_j [M_j,N_j] = A_j^T * B_j over the same K rows (A, B, C, M and N above are unused).  Their
+// tiles form one list, product by product; all the parameter gradients of a layer are one launch, whose tiles fill whole
+// rounds of the CUs but for one remainder, where a launch per product has a remainder each: [8192 rows, H = 2048,
+// F = 5632, 32/4 heads of 64] 176 + 352 + 64 + 80 tiles are 2.6 rounds instead of 1 + 2 + 1 + 1, into fp32 buffers 822 us in
+// four launches and 750 in one; [841 rows, H = 4096, F = 1792, 4/1 heads of 128] 81 us in four, 60 in one.
+struct TnArgs : GemmArgs {
+    GemmTnProb p[TN_MAX];
+    int end[TN_MAX];    // tiles of products 0..j
 };
 
 // How the tiles of the last, partial round are cut.  The cost of a round of sub-tiles
@@ -137,23 +138,20 @@ __host__ __device__ inline double plan_tiles(int tiles, int n_cu, int& n_full, i
     return n_full / n_cu + best;
 }
 
-// Tile plan of a bf16 launch with n_cu blocks: sets n_full, sub, tile_n; returns the number of work
+// Tile plan of an NT launch with n_cu blocks: sets n_full, sub, tile_n; returns the number of work
 // items.  The host plans a launch whose sizes it knows; with a device-side count every block runs
 // the same code on the count it read, so both give the same tiles for the same sizes.
-__host__ __device__ inline int plan_launch(int M, int N, int mode, int ngroups, int n_cu,
-                                           int& n_full, int& sub, int& tile_n) {
+__host__ __device__ inline int plan_launch(int M, int N, int n_cu, int& n_full, int& sub, int& tile_n) {
     const int tiles = cdiv(M, 256) * cdiv(N, 256);
     const double rounds = plan_tiles(tiles, n_cu, n_full, sub);
     int items = n_full + (tiles - n_full) * sub;
     tile_n = 256;
-    if (mode == 0 && ngroups == 1) {
-        // 256x192 tiles instead, when they fill the CUs better (an output of 16 x 12 tiles of
-        // 256x256 leaves a quarter of the CUs idle; as 16 x 16 tiles of 256x192 it is one full round)
-        const int tiles192 = cdiv(M, 256) * cdiv(N, 192);
-        if (cdiv(tiles192, n_cu) * kCost192 < rounds - 1e-9) {
-            tile_n = 192;
-            items = tiles192;
-        }
+    // 256x192 tiles instead, when they fill the CUs better (an output of 16 x 12 tiles of
+    // 256x256 leaves a quarter of the CUs idle; as 16 x 16 tiles of 256x192 it is one full round)
+    const int tiles192 = cdiv(M, 256) * cdiv(N, 192);
+    if (cdiv(tiles192, n_cu) * kCost192 < rounds - 1e-9) {
+        tile_n = 192;
+        items = tiles192;
     }
     return items;
 }
@@ -205,11 +203,10 @@ constexpr int load_in_gap(int q, int D, int N) {
     return -1;
 }
 
-// One output tile: its origin, and the B operand (of segment 0), output matrix and column count
-// it belongs to (those of its column group in a grouped launch).
+// One output tile: its origin, and the operands (of segment 0), output matrix and its sizes that it belongs to.
 struct TileRef {
-    int m0, n0, N;
-    const void* B0;
+    int m0, n0, M, N;
+    const void *A0, *B0;
     void* C;
 };
 
@@ -219,10 +216,9 @@ struct TileRef {
 // own, and its stores drain under the next tile's MFMAs.  SPLIT: the block contracts only k in
 // [kbeg, kend) of the single segment and stores its fp32 accumulators, unscaled, to `part_out`
 // ([BM, BN] fp32); a second kernel adds the parts up.
-// Mx, K0x: the live values of g.M and g.K[0] (they differ from the launch arguments when the
-// kept-token count is read on the device).
+// K0x: the live value of g.K[0] (it differs from the launch argument when the kept-token count is read on the device).
 template <int MODE, int TM, int TN, bool SPLIT, bool CF32, typename Next>
-__device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, const int K0x, const TileRef first,
+__device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int K0x, const TileRef first,
                                            Next next_tile, unsigned char* smem,
                                            const int kbeg = 0, const int kend = 0, float* part_out = nullptr) {
     // Ring of operand stages: four of 32 KB, i.e. two pairs of K-steps, or for the 128x128 tile eight of 16 KB = four
@@ -264,9 +260,9 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
     unsigned vo[NU][2];
     auto open_segment = [&](int s) __attribute__((always_inline)) {
         const bool live = (unsigned)s < (unsigned)g.nseg;
-        const int m0 = ld.m0, n0 = ld.n0;
+        const int m0 = ld.m0, n0 = ld.n0, Mx = ld.M;
         const int sa = live ? s : 0;
-        const bf16_t* A = static_cast<const bf16_t*>(g.A[0]);
+        const bf16_t* A = static_cast<const bf16_t*>(ld.A0);
         const bf16_t* B = static_cast<const bf16_t*>(ld.B0);
         int Kraw = K0x;
         if (sa != 0) {      // a branch: the first segment's operands, which open every tile, do not wait for a load
@@ -587,7 +583,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
             lds_barrier();              // every wave has read its last fragments: the stages are free
             if (has_next && npairs > 0) start_tile();
         }
-        const int m0 = ep.m0, n0 = ep.n0;
+        const int m0 = ep.m0, n0 = ep.n0, Mx = ep.M;
 
     if (SPLIT) {
         // ---- split-K epilogue: the whole tile's fp32 accumulators, unscaled, straight to the item's own slot (rows and
@@ -690,7 +686,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
 #pragma unroll
             for (int q = 0; q < NP; ++q)
                 val[q] = *reinterpret_cast<const u32x4_t*>(rd[q % NV] + q * RPP * RBY);
-            if (beta != 0.f) {
+            if (MODE == 1 && beta != 0.f) {
 #pragma unroll
                 for (int q = 0; q < NP; ++q) {
                     const u32x4_t old = __builtin_amdgcn_raw_buffer_load_b128(
@@ -717,88 +713,35 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int Mx, cons
 // tiles.  Block b takes items b, b + gridDim.x, ...: with as many blocks as CUs every block runs
 // its share of the whole tiles back to back and then at most a few sub-tiles, and the items of
 // one block stay on one XCD (item id mod 8 = block id mod 8).
-template <int MODE, bool CF32>
-__device__ __forceinline__ void gemm_bf16_block(const GemmArgs& g, unsigned char* smem) {
-    int Mx = g.M, K0x = g.K[0], n_full = g.n_full, sub = g.sub, tile_n = g.tile_n;
-    if (g.n_dev != nullptr) {
-        // the kept-token count is a device value: clamp the kept-token dimension to it and (NT: the
-        // output shape depends on it) plan the tiles here, as the host does for sizes it knows
-        int n = *g.n_dev;
-        n = __builtin_amdgcn_readfirstlane(n < 0 ? 0 : n);
-        if (MODE == 0) {
-            Mx = n < Mx ? n : Mx;
-            plan_launch(Mx, g.N, 0, g.ngroups, (int)gridDim.x, n_full, sub, tile_n);
-            n_full = __builtin_amdgcn_readfirstlane(n_full);
-            sub = __builtin_amdgcn_readfirstlane(sub);
-            tile_n = __builtin_amdgcn_readfirstlane(tile_n);
-        } else {
-            K0x = n < K0x ? n : K0x;
-        }
-    }
-    const int tiles_m = (Mx + 255) / 256, tiles_n = (g.N + 255) / 256;
+// locate(l, t, bm, bn): logical tile l of the launch -> the product it belongs to (t without its origin) and its tile coordinates.
+template <int MODE, bool CF32, typename Locate>
+__device__ __forceinline__ void gemm_items(const GemmArgs& g, const int K0x, const int tiles, const int n_full, const int sub,
+                                           Locate locate, unsigned char* smem) {
     const int stride = (int)gridDim.x;
-    if constexpr (MODE == 0) {
-        if (tile_n == 192) {
-            // tiles of 256x192, all of one kind: block b takes tiles b, b + gridDim.x, ...
-            const int tiles_n192 = (g.N + 191) / 192, n_items = tiles_m * tiles_n192;
-            int w = (int)blockIdx.x;
-            // with a device-side count there are as many blocks as CUs, whatever the number of tiles: a block
-            // past the last tile would compute another block's tile a second time (and add to it twice if beta were 1)
-            if (w >= n_items) return;
-            auto tile = [&](int w, TileRef& t) __attribute__((always_inline)) {
-                int bm, bn;
-                tile_coords(xcd_order(w, n_items), tiles_m, tiles_n192, bm, bn);
-                t.m0 = __builtin_amdgcn_readfirstlane(bm * 256);
-                t.n0 = __builtin_amdgcn_readfirstlane(bn * 192);
-                t.N = __builtin_amdgcn_readfirstlane(g.N);
-                t.B0 = uniform_ptr(g.B[0]);
-                t.C = uniform_ptr(g.C);
-            };
-            TileRef t;
-            tile(w, t);
-            gemm_tiles<MODE, 4, 3, false, false>(g, Mx, K0x, t, [&](TileRef& nx) __attribute__((always_inline)) {
-                w += stride;
-                if (w >= n_items) return false;
-                tile(w, nx);
-                return true;
-            }, smem);
-            return;
-        }
-    }
-    const int n_items = n_full + (tiles_m * tiles_n - n_full) * sub;
+    const int n_items = n_full + (tiles - n_full) * sub;
     // item -> tile; false when a sub-tile lies outside the matrix
     auto decode = [&](int w, TileRef& t) __attribute__((always_inline)) {
         int bm, bn, m0, n0;
         if (w < n_full) {
-            tile_coords(xcd_order(w, n_full), tiles_m, tiles_n, bm, bn);
+            locate(xcd_order(w, n_full), t, bm, bn);
             m0 = bm * 256;
             n0 = bn * 256;
         } else {
             const int cut = sub;
             const int j = xcd_order(w - n_full, n_items - n_full);
             const int part = j % cut;
-            tile_coords(n_full + j / cut, tiles_m, tiles_n, bm, bn);
+            locate(n_full + j / cut, t, bm, bn);
             m0 = bm * 256 + (cut == 4 ? (part >> 1) * 128 : 0);
             n0 = bn * 256 + (cut == 4 ? (part & 1) * 128 : (cut == 2 ? part * 128 : 0));
-            if (m0 >= Mx || n0 >= g.N) return false;
-        }
-        t.B0 = g.B[0];
-        t.C = g.C;
-        t.N = g.N;
-        if (g.ngroups > 1) {
-            // the tile's column group: rebase the B operand, the output and the column range on it
-            const int j = n0 < g.Ng[0] ? 0 : (n0 < g.Ng[0] + g.Ng[1] ? 1 : 2);
-            const int off = j == 0 ? 0 : (j == 1 ? g.Ng[0] : g.Ng[0] + g.Ng[1]);
-            t.B0 = j == 0 ? g.Bg[0] : (j == 1 ? g.Bg[1] : g.Bg[2]);
-            t.C = j == 0 ? g.Cg[0] : (j == 1 ? g.Cg[1] : g.Cg[2]);
-            t.N = j == 0 ? g.Ng[0] : (j == 1 ? g.Ng[1] : g.Ng[2]);
-            n0 -= off;
+            if (m0 >= t.M || n0 >= t.N) return false;
         }
         // every field is the same in all lanes: say so, which keeps the address arithmetic of the
         // tile's prologue on the scalar unit
         t.m0 = __builtin_amdgcn_readfirstlane(m0);
         t.n0 = __builtin_amdgcn_readfirstlane(n0);
+        t.M = __builtin_amdgcn_readfirstlane(t.M);
         t.N = __builtin_amdgcn_readfirstlane(t.N);
+        t.A0 = uniform_ptr(t.A0);
         t.B0 = uniform_ptr(t.B0);
         t.C = uniform_ptr(t.C);
         return true;
@@ -813,7 +756,7 @@ __device__ __forceinline__ void gemm_bf16_block(const GemmArgs& g, unsigned char
     };
     if (w < n_full) {         // whole tiles
         decode(w, t);
-        gemm_tiles<MODE, 4, 4, false, CF32>(g, Mx, K0x, t, [&](TileRef& nx) __attribute__((always_inline)) {
+        gemm_tiles<MODE, 4, 4, false, CF32>(g, K0x, t, [&](TileRef& nx) __attribute__((always_inline)) {
             if (!advance(n_full)) return false;
             nx = t;
             return true;
@@ -829,21 +772,80 @@ __device__ __forceinline__ void gemm_bf16_block(const GemmArgs& g, unsigned char
         nx = t;
         return true;
     };
-    if (sub == 1) gemm_tiles<MODE, 4, 4, false, CF32>(g, Mx, K0x, t, next_sub, smem);
-    else if (sub == 2) gemm_tiles<MODE, 4, 2, false, CF32>(g, Mx, K0x, t, next_sub, smem);
-    else gemm_tiles<MODE, 2, 2, false, CF32>(g, Mx, K0x, t, next_sub, smem);
+    if (sub == 1) gemm_tiles<MODE, 4, 4, false, CF32>(g, K0x, t, next_sub, smem);
+    else if (sub == 2) gemm_tiles<MODE, 4, 2, false, CF32>(g, K0x, t, next_sub, smem);
+    else gemm_tiles<MODE, 2, 2, false, CF32>(g, K0x, t, next_sub, smem);
 }
 
-template <int MODE>
-__global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
+__global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs g) {
     extern __shared__ __align__(16) unsigned char smem[];
-    gemm_bf16_block<MODE, false>(g, smem);
+    int Mx = g.M, n_full = g.n_full, sub = g.sub, tile_n = g.tile_n;
+    if (g.n_dev != nullptr) {
+        // the kept-token count is a device value: clamp the rows to it and plan the tiles here, as the host does for sizes it
+        // knows (the output shape depends on it)
+        int n = *g.n_dev;
+        n = __builtin_amdgcn_readfirstlane(n < 0 ? 0 : n);
+        Mx = n < Mx ? n : Mx;
+        plan_launch(Mx, g.N, (int)gridDim.x, n_full, sub, tile_n);
+        n_full = __builtin_amdgcn_readfirstlane(n_full);
+        sub = __builtin_amdgcn_readfirstlane(sub);
+        tile_n = __builtin_amdgcn_readfirstlane(tile_n);
+    }
+    const int tiles_m = (Mx + 255) / 256, tiles_n = (g.N + 255) / 256;
+    const TileRef whole{0, 0, Mx, g.N, g.A[0], g.B[0], g.C};
+    if (tile_n == 192) {
+        // tiles of 256x192, all of one kind: block b takes tiles b, b + gridDim.x, ...
+        const int tiles_n192 = (g.N + 191) / 192, n_items = tiles_m * tiles_n192;
+        int w = (int)blockIdx.x;
+        // with a device-side count there are as many blocks as CUs, whatever the number of tiles: a block
+        // past the last tile would compute another block's tile a second time
+        if (w >= n_items) return;
+        auto tile = [&](int w, TileRef& t) __attribute__((always_inline)) {
+            int bm, bn;
+            tile_coords(xcd_order(w, n_items), tiles_m, tiles_n192, bm, bn);
+            t = whole;
+            t.m0 = __builtin_amdgcn_readfirstlane(bm * 256);
+            t.n0 = __builtin_amdgcn_readfirstlane(bn * 192);
+        };
+        TileRef t;
+        tile(w, t);
+        gemm_tiles<0, 4, 3, false, false>(g, g.K[0], t, [&](TileRef& nx) __attribute__((always_inline)) {
+            w += (int)gridDim.x;
+            if (w >= n_items) return false;
+            tile(w, nx);
+            return true;
+        }, smem);
+        return;
+    }
+    gemm_items<0, false>(g, g.K[0], tiles_m * tiles_n, n_full, sub, [&](int l, TileRef& t, int& bm, int& bn) __attribute__((always_inline)) {
+        t = whole;
+        tile_coords(l, tiles_m, tiles_n, bm, bn);
+    }, smem);
 }
 
-// Parameter gradients added to fp32 main-gradient buffers.
-__global__ __launch_bounds__(256) void gemm_bf16_f32out_kernel(GemmArgs g) {
+// CF32: C is fp32 (main-gradient buffers) and the products are added to it without rounding.
+template <bool CF32>
+__global__ __launch_bounds__(256) void gemm_tn_kernel(TnArgs g) {
     extern __shared__ __align__(16) unsigned char smem[];
-    gemm_bf16_block<1, true>(g, smem);
+    int K0x = g.K[0];
+    if (g.n_dev != nullptr) {           // the contraction is over the kept tokens: only its length depends on the count
+        int n = *g.n_dev;
+        n = __builtin_amdgcn_readfirstlane(n < 0 ? 0 : n);
+        K0x = n < K0x ? n : K0x;
+    }
+    gemm_items<1, CF32>(g, K0x, g.end[TN_MAX - 1], g.n_full, g.sub, [&](int l, TileRef& t, int& bm, int& bn) __attribute__((always_inline)) {
+        int j = 0, first = 0;
+#pragma unroll
+        for (int q = 0; q + 1 < TN_MAX; ++q) {
+            const int e = g.end[q];
+            j = l >= e ? q + 1 : j;
+            first = l >= e ? e : first;
+        }
+        j = __builtin_amdgcn_readfirstlane(j);
+        const GemmTnProb& p = g.p[j];
+        t.M = p.M; t.N = p.N; t.A0 = p.A; t.B0 = p.B; t.C = p.C;
+        tile_coords(l - first, (t.M + 255) / 256, (t.N + 255) / 256, bm, bn);
+    }, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -945,15 +947,15 @@ __device__ __forceinline__ void group_tile(const GroupArgs& ga, const GroupItem&
     const GemmGroupProb& p = ga.p[it.j];
     GemmArgs g;
     g.A[0] = uniform_ptr(p.A); g.B[0] = uniform_ptr(p.B); g.K[0] = it.K; g.nseg = 1;
-    g.C = uniform_ptr(p.C); g.M = it.M; g.N = p.N; g.beta = 0.f; g.alpha = p.alpha; g.c_f32 = 0; g.ngroups = 1;
+    g.C = uniform_ptr(p.C); g.M = it.M; g.N = p.N; g.beta = 0.f; g.alpha = p.alpha;
     g.n_dev = nullptr; g.a_idx = nullptr; g.a_rows = 0;
-    const TileRef t{it.m0, it.n0, p.N, g.B[0], g.C};
+    const TileRef t{it.m0, it.n0, it.M, p.N, g.A[0], g.B[0], g.C};
     auto none = [](TileRef&) { return false; };
     if (it.parts > 1) {
         const int c = group_step(plan) * 64, kbeg = it.part * c, kend = min(it.K, kbeg + c);
-        gemm_tiles<MODE, 2, 2, true, false>(g, it.M, it.K, t, none, smem, kbeg, kend, ga.slots + (int64_t)w * (128 * 128));
+        gemm_tiles<MODE, 2, 2, true, false>(g, it.K, t, none, smem, kbeg, kend, ga.slots + (int64_t)w * (128 * 128));
     } else {
-        gemm_tiles<MODE, 2, 2, false, false>(g, it.M, it.K, t, none, smem);
+        gemm_tiles<MODE, 2, 2, false, false>(g, it.K, t, none, smem);
     }
 }
 
@@ -1082,99 +1084,83 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
 }
 
 
-template <int MODE>
-static hipError_t launch_bf16(GemmArgs& g, hipStream_t st) {
-    static std::atomic<uint64_t> lds_ok{0}, lds_ok_f32{0};
-    const bool f32 = MODE == 1 && g.c_f32;
-    void (*const kernel)(GemmArgs) = f32 ? gemm_bf16_f32out_kernel : gemm_bf16_kernel<MODE>;
-    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), GEMM_SMEM, f32 ? lds_ok_f32 : lds_ok);
+// per-lane load and store offsets are 32-bit with the upper half reserved for "out of range"
+static bool offsets_fit(int64_t M, int64_t N, int64_t K) {
+    const int64_t lim = (int64_t)1 << 31;
+    return M * K * 2 < lim && N * K * 2 < lim && (M + 256) * N * 2 < lim;
+}
+
+hipError_t launch_gemm_nt(int dtype, const GemmSeg* segs, int nseg, void* C, int M, int N, hipStream_t st, const int32_t* n_dev,
+                          const int32_t* a_idx, int64_t a_rows) {
+    if (M <= 0 || N <= 0) return hipSuccess;
+    if (a_idx != nullptr && a_rows <= 0) return hipErrorInvalidValue;
+    if (nseg > MAX_SEG) return hipErrorInvalidValue;
+    GemmArgs g{};
+    for (int s = 0; s < nseg; ++s) {
+        if (segs[s].K <= 0) return hipErrorInvalidValue;
+        g.A[s] = segs[s].A;
+        g.B[s] = segs[s].B;
+        g.K[s] = segs[s].K;
+        if (dtype == CF_BF16 && !offsets_fit(M, N, segs[s].K)) return hipErrorInvalidValue;
+    }
+    g.nseg = nseg;
+    g.C = C; g.M = M; g.N = N; g.alpha = 1.f; g.sub = 1; g.tile_n = 256;
+    g.n_dev = n_dev; g.a_idx = a_idx; g.a_rows = a_rows;
+    if (dtype == CF_F32) {
+        gemm_f32_kernel<0><<<ceil_div(M, 64) * ceil_div(N, 64), 256, 0, st>>>(g);
+        return hipGetLastError();
+    }
+    if (a_idx != nullptr && a_rows * g.K[0] * 2 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    static std::atomic<uint64_t> lds_ok{0};
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_nt_kernel), GEMM_SMEM, lds_ok);
     if (e != hipSuccess) return e;
-    const int items = plan_launch(g.M, g.N, MODE, g.ngroups, compute_units(), g.n_full, g.sub, g.tile_n);
+    const int items = plan_launch(M, N, compute_units(), g.n_full, g.sub, g.tile_n);
     // a block walks through its items; with a device-side count the blocks plan for themselves (for
     // as many blocks as CUs) and those without an item leave at once
-    const int grid = g.n_dev != nullptr ? compute_units() : std::min(items, compute_units());
-    kernel<<<grid, 256, GEMM_SMEM, st>>>(g);
+    const int grid = n_dev != nullptr ? compute_units() : std::min(items, compute_units());
+    gemm_nt_kernel<<<grid, 256, GEMM_SMEM, st>>>(g);
     return hipGetLastError();
 }
 
-hipError_t launch_gemm(int dtype, int mode, const GemmSeg* segs, int nseg, void* C, int M, int N,
-                       float beta, hipStream_t st, bool c_f32, const int32_t* n_dev, const int32_t* a_idx,
-                       int64_t a_rows) {
-    if (M <= 0 || N <= 0) return hipSuccess;
-    if (a_idx != nullptr && (mode != 0 || a_rows <= 0)) return hipErrorInvalidValue;
-    if (nseg > MAX_SEG) return hipErrorInvalidValue;
-    if (c_f32 && dtype == CF_BF16 && (mode != 1 || beta != 1.f)) return hipErrorInvalidValue;
-    GemmArgs g;
-    g.nseg = 0;
-    for (int s = 0; s < nseg; ++s) {
-        if (segs[s].K <= 0) continue;
-        g.A[g.nseg] = segs[s].A;
-        g.B[g.nseg] = segs[s].B;
-        g.K[g.nseg] = segs[s].K;
-        ++g.nseg;
-    }
-    for (int s = g.nseg; s < MAX_SEG; ++s) { g.A[s] = nullptr; g.B[s] = nullptr; g.K[s] = 0; }
-    g.C = C; g.M = M; g.N = N; g.beta = beta; g.alpha = 1.f; g.n_full = 0; g.sub = 1; g.tile_n = 256;
-    g.c_f32 = (c_f32 && dtype == CF_BF16) ? 1 : 0;
-    g.ngroups = 1;
-    for (int j = 0; j < 3; ++j) { g.Bg[j] = nullptr; g.Cg[j] = nullptr; g.Ng[j] = 0; }
-    g.n_dev = n_dev; g.a_idx = a_idx; g.a_rows = a_rows;
-    // with a device-side count the kept-token dimension must be that of segment 0 (mode TN) and no
-    // segment may have been dropped
-    if (n_dev != nullptr && (g.nseg != nseg || (mode == 1 && nseg != 1))) return hipErrorInvalidValue;
-    if (g.nseg == 0) {
-        // empty contraction: C = beta*C; only beta in {0,1} is supported by the API
-        if (beta == 0.f) return launch_fill_zero(C, (size_t)M * N * (c_f32 ? 4 : dtype_size(dtype)), st);
+hipError_t launch_gemm_tn(int dtype, const GemmTnProb* probs, int np, int K, float beta, hipStream_t st, bool c_f32,
+                          const int32_t* n_dev) {
+    if (np < 1 || np > TN_MAX) return hipErrorInvalidValue;
+    if (c_f32 && dtype == CF_BF16 && beta != 1.f) return hipErrorInvalidValue;
+    if (K <= 0) {           // empty contraction: C = beta*C; only beta in {0,1} is supported by the API
+        for (int j = 0; j < np && beta == 0.f; ++j) {
+            const hipError_t e = launch_fill_zero(probs[j].C, (size_t)probs[j].M * probs[j].N * dtype_size(dtype), st);
+            if (e != hipSuccess) return e;
+        }
         return hipSuccess;
     }
-    if (dtype == CF_BF16) {
-        // per-lane load and store offsets are 32-bit with the upper half reserved for "out of range"
-        for (int s = 0; s < g.nseg; ++s)
-            if ((int64_t)M * g.K[s] * 2 >= ((int64_t)1 << 31) || (int64_t)N * g.K[s] * 2 >= ((int64_t)1 << 31))
-                return hipErrorInvalidValue;
-        if (a_idx != nullptr && a_rows * g.K[0] * 2 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-        if (((int64_t)M + 256) * N * 2 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    }
+    TnArgs g{};
+    g.K[0] = K; g.nseg = 1; g.beta = beta; g.alpha = 1.f; g.n_dev = n_dev;
     if (dtype == CF_F32) {
-        const int grid = ceil_div(M, 64) * ceil_div(N, 64);
-        if (mode == 0) gemm_f32_kernel<0><<<grid, 256, 0, st>>>(g);
-        else gemm_f32_kernel<1><<<grid, 256, 0, st>>>(g);
-        return hipGetLastError();
+        for (int j = 0; j < np; ++j) {
+            g.A[0] = probs[j].A; g.B[0] = probs[j].B; g.C = probs[j].C; g.M = probs[j].M; g.N = probs[j].N;
+            gemm_f32_kernel<1><<<ceil_div(g.M, 64) * ceil_div(g.N, 64), 256, 0, st>>>(g);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
     }
-    return mode == 0 ? launch_bf16<0>(g, st) : launch_bf16<1>(g, st);
-}
-
-bool gemm_tn_groups_supported(int dtype, int K, int ngroups, const int* Ng) {
-    if (dtype != CF_BF16 || K <= 0 || ngroups < 2 || ngroups > 3) return false;
-    for (int j = 0; j < ngroups; ++j)
-        if (Ng[j] <= 0 || Ng[j] % 256 != 0) return false;
-    return true;
-}
-
-hipError_t launch_gemm_tn_groups(const void* A, int K, int M, int ngroups, const void* const* Bg,
-                                 void* const* Cg, const int* Ng, hipStream_t st, float beta, bool c_f32,
-                                 const int32_t* n_dev) {
-    if (M <= 0) return hipSuccess;
-    if (c_f32 && beta != 1.f) return hipErrorInvalidValue;
-    GemmArgs g;
-    int N = 0;
-    for (int j = 0; j < 3; ++j) {
-        g.Bg[j] = j < ngroups ? Bg[j] : nullptr;
-        g.Cg[j] = j < ngroups ? Cg[j] : nullptr;
-        g.Ng[j] = j < ngroups ? Ng[j] : 0;
-        N += g.Ng[j];
-        if ((int64_t)g.Ng[j] * K * 2 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    int tiles = 0;
+    for (int j = 0; j < TN_MAX; ++j) {
+        if (j < np) {
+            const GemmTnProb& p = probs[j];
+            if (p.M <= 0 || p.N <= 0 || !offsets_fit(p.M, p.N, K)) return hipErrorInvalidValue;
+            g.p[j] = p;
+            tiles += ceil_div(p.M, 256) * ceil_div(p.N, 256);
+        }
+        g.end[j] = tiles;       // behind the last product: no tile there
     }
-    if ((int64_t)M * K * 2 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    for (int j = 0; j < ngroups; ++j)
-        if (((int64_t)M + 256) * Ng[j] * 2 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    g.ngroups = ngroups;
-    g.A[0] = A; g.B[0] = Bg[0]; g.K[0] = K; g.nseg = 1;
-    for (int s = 1; s < MAX_SEG; ++s) { g.A[s] = nullptr; g.B[s] = nullptr; g.K[s] = 0; }
-    g.C = Cg[0]; g.M = M; g.N = N; g.beta = beta; g.alpha = 1.f; g.n_full = 0; g.sub = 1; g.tile_n = 256;
-    g.c_f32 = c_f32 ? 1 : 0;
-    g.n_dev = n_dev; g.a_idx = nullptr; g.a_rows = 0;
-    return launch_bf16<1>(g, st);
+    static std::atomic<uint64_t> lds_ok{0}, lds_ok_f32{0};
+    void (*const kernel)(TnArgs) = c_f32 ? gemm_tn_kernel<true> : gemm_tn_kernel<false>;
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), GEMM_SMEM, c_f32 ? lds_ok_f32 : lds_ok);
+    if (e != hipSuccess) return e;
+    plan_tiles(tiles, compute_units(), g.n_full, g.sub);
+    kernel<<<std::min(g.n_full + (tiles - g.n_full) * g.sub, compute_units()), 256, GEMM_SMEM, st>>>(g);
+    return hipGetLastError();
 }
 
 size_t gemm_group_slot_bytes() { return (size_t)compute_units() * 128 * 128 * sizeof(float) + 256; }
@@ -1187,7 +1173,7 @@ hipError_t launch_gemm_group(int dtype, const GemmGroupProb* probs, int np, hipS
             const GemmGroupProb& p = probs[j];
             GemmArgs g{};
             g.A[0] = p.A; g.B[0] = p.B; g.K[0] = p.K; g.nseg = 1; g.C = p.C; g.M = p.M; g.N = p.N; g.alpha = p.alpha;
-            g.ngroups = 1; g.n_dev = n_dev;
+            g.n_dev = n_dev;
             const int grid = ceil_div(p.M, 64) * ceil_div(p.N, 64);
             if (p.mode == 0) gemm_f32_kernel<0><<<grid, 256, 0, st>>>(g);
             else if (p.mode == 1) gemm_f32_kernel<1><<<grid, 256, 0, st>>>(g);
@@ -1202,9 +1188,7 @@ hipError_t launch_gemm_group(int dtype, const GemmGroupProb* probs, int np, hipS
     for (int j = 0; j < np; ++j) {
         const GemmGroupProb& p = probs[j];
         if (p.M <= 0 || p.N <= 0 || p.K <= 0) return hipErrorInvalidValue;
-        if ((int64_t)p.M * p.K * 2 >= ((int64_t)1 << 31) || (int64_t)p.N * p.K * 2 >= ((int64_t)1 << 31) ||
-            ((int64_t)p.M + 256) * p.N * 2 >= ((int64_t)1 << 31))
-            return hipErrorInvalidValue;
+        if (!offsets_fit(p.M, p.N, p.K)) return hipErrorInvalidValue;
         g.p[j] = p;
         tiles += (int64_t)ceil_div(p.M, 128) * ceil_div(p.N, 128);
     }

@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(const T* d_act,
 
 // dx_out[j,:] = res[j,:] + rstd*(u - n*mean(u*n)),  n = x*rstd, u = dh*g
 // dg_partial[block,:] = sum over the block's rows of dh*n
-// h_out (nullable): h_out[j,:] = n*g, the normalised row itself: the parameter-gradient GEMMs of the linears behind
+// h_out (nullable, may be dh: every element is read before it is written, by the same thread): h_out[j,:] = n*g, the normalised row itself: the parameter-gradient GEMMs of the linears behind
 // this norm need it as an operand, and the row and its rstd are in registers here anyway.
 // A block owns one row at a time, NV 16-byte vectors per thread, and works on two rows per
 // iteration so that the loads of the second row overlap the reduction of the first; every
@@ -76,14 +76,14 @@ __host__ __device__ inline int rmsnorm_bwd_nblk(int n_rows) {
 }
 
 template <typename T, int NV>
-__global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* __restrict__ dh,
+__global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* dh,
                                                           const T* __restrict__ x,
                                                           const T* __restrict__ g,
                                                           const int32_t* __restrict__ idx,
                                                           const T* __restrict__ res, int n_max,
                                                           const int32_t* __restrict__ n_dev,
                                                           int H, float eps, T* __restrict__ dx_out,
-                                                          float* __restrict__ dg_partial, T* __restrict__ h_out) {
+                                                          float* __restrict__ dg_partial, T* h_out) {
     constexpr int VN = Vec<T>::N;
     __shared__ float red[16];
     const int n_rows = live_rows(n_max, n_dev);

@@ -664,6 +664,27 @@ def test_layer_main_grad_full_round_and_a_remainder(F, kept):
             assert bad.numel() == 0, (name, rep, bad.shape[0], bad[0].tolist())
 
 
+@pytest.mark.parametrize("main_grad", [False, True])
+@pytest.mark.parametrize("H,Hq,Hkv,d,F", [(512, 8, 2, 64, 256), (840, 12, 4, 64, 2312), (2048, 32, 4, 64, 4864), (2048, 32, 4, 64, 5632)])
+def test_layer_parameter_gradients_in_one_launch_or_one_by_one(H, Hq, Hkv, d, F, main_grad):
+    """The seven dW products share a launch unless an output lies over an operand that the caller owns (dx over dy in a dense
+    call, here): then each goes out by itself, as soon as its operands exist.  The list's remainder of tiles is cut
+    into quarters (first size), stays whole at the end of ragged matrices (second), is cut into halves (600 tiles) and stays whole
+    behind two full rounds (672); the single launches are cut otherwise.  Every element is summed in the order of its rows on
+    either route, so both give the same bits."""
+    shape = WL.LayerShape("one_launch", B=1, S=328, H=H, Hq=Hq, Hkv=Hkv, d=d, F=F, dtype="bf16")
+    sv, W, dy = _random_layer(shape, F)
+    desc = Bn.make_desc(shape.B, shape.S, H, Hq, Hkv, d, F, "bf16")
+    ref, over = (Bn.LayerBackward(desc, device=DEV, main_grad=main_grad) for _ in range(2))
+    ref.dense(sv, W, dy)
+    dy2 = dy.clone()
+    over._g.dx = dy2.data_ptr()
+    over.dense(sv, W, dy2)
+    torch.cuda.synchronize()
+    for k in ref.grads:
+        assert torch.equal(dy2 if k == "dx" else over.grads[k], ref.grads[k]), k
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_layer_invariants_on_gpu_outputs(dtype):
     """Keep ratio 1 reproduces the dense call bit for bit (same kernels, same
