@@ -21,7 +21,7 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
                                 const float* lse_full, const void* do_kept, float* stat,
                                 const int32_t* idx, const int32_t* cu_kept, RowCount rows, void* dq_kept,
                                 void* dk_kept, void* dv_kept, float* partials, hipStream_t st,
-                                const void* o_full = nullptr, const void* q_full = nullptr);
+                                const void* o_full, const void* q_full, const float* rope_cos, const float* rope_sin);
 }  // namespace cf
 
 using namespace cf;
@@ -161,11 +161,13 @@ LayerWs carve_layer(const cf_layer_desc& L, int max_kept, void* ws) {
 
 // o_full / q_full (nullable): the attention output and the queries at full length; the row-statistics
 // pass then copies their kept rows (through idx) into the writable buffers o_kept / q_kept.
+// rope_cos / rope_sin (nullable): dq and dk are rotated back to before the rotary embedding.
 cf_status attn_dispatch(const cf_layer_desc& L, const void* q_kept, const void* k_full,
                         const void* v_full, const void* o_kept, const float* lse_full,
                         const void* do_kept, const int32_t* idx, const int32_t* cu_kept, RowCount rows,
                         void* dq_kept, void* dk_kept, void* dv_kept, void* attn_ws, hipStream_t st,
-                        const void* o_full = nullptr, const void* q_full = nullptr) {
+                        const void* o_full = nullptr, const void* q_full = nullptr, const float* rope_cos = nullptr,
+                        const float* rope_sin = nullptr) {
     const int n_kept = rows.n;
     if (n_kept <= 0) return CF_OK;
     const float scale = eff_scale(L);
@@ -173,13 +175,14 @@ cf_status attn_dispatch(const cf_layer_desc& L, const void* q_kept, const void* 
     float* partials = reinterpret_cast<float*>(static_cast<unsigned char*>(attn_ws) + attn_drow_bytes(L, n_kept));
     if (attn_mfma_supported(L)) {
         CF_HIP(launch_attn_bwd_mfma(L, scale, q_kept, k_full, v_full, o_kept, lse_full, do_kept, Drow, idx,
-                                    cu_kept, rows, dq_kept, dk_kept, dv_kept, partials, st, o_full, q_full));
+                                    cu_kept, rows, dq_kept, dk_kept, dv_kept, partials, st, o_full, q_full, rope_cos, rope_sin));
     } else {
         CF_HIP(launch_attn_rowdot(L.dtype, do_kept, o_full ? o_full : o_kept, rows, L.Hq, L.d, Drow, st,
                                   o_full ? idx : nullptr, const_cast<void*>(o_kept), q_full,
                                   const_cast<void*>(q_kept)));
         CF_HIP(launch_attn_bwd_ref(L, scale, q_kept, k_full, v_full, lse_full, do_kept, Drow, idx,
                                    cu_kept, rows, dq_kept, dk_kept, dv_kept, st));
+        if (rope_cos) CF_HIP(launch_rope_bwd_f32(dq_kept, L.Hq, dk_kept, L.Hkv, idx, rows, L.d, L.S, rope_cos, rope_sin, st));
     }
     return CF_OK;
 }
@@ -276,13 +279,11 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     // the attention backward's row-statistics pass reads attn_out and q through idx and leaves their
     // compact copies in w.a_k, w.q_k (no gather kernel)
     cf_status as = attn_dispatch(L, q_rows, sv.k, sv.v, a_rows, sv.lse, w.da, idx, cu_kept, rows, w.dq,
-                                 w.dk, w.dv, w.attn_ws, st, idx ? sv.attn_out : nullptr, idx ? sv.q : nullptr);
+                                 w.dk, w.dv, w.attn_ws, st, idx ? sv.attn_out : nullptr, idx ? sv.q : nullptr, sv.rope_cos,
+                                 sv.rope_sin);
     if (as != CF_OK) return as;
     CF_HIP(dw(a_rows, w.dr, G.dwo, Nq, H));          // dWo = a^T * dr      [Nq,H]
 
-    if (sv.rope_cos) {      // transposed rotation of dq and dk at the original positions of the kept rows
-        CF_HIP(launch_rope_bwd(dt, w.dq, L.Hq, w.dk, L.Hkv, idx, rows, L.d, L.S, sv.rope_cos, sv.rope_sin, st));
-    }
     void* dh1 = w.bufHb;
     {   // dh1 = dq*Wq^T + dk*Wk^T + dv*Wv^T
         GemmSeg s[3] = {{w.dq, W.wq, Nq}, {w.dk, W.wk, Nkv}, {w.dv, W.wv, Nkv}};
@@ -372,11 +373,9 @@ cf_status layer_core_lora(const cf_layer_desc& L, const cf_saved& sv, const cf_w
     const void* a_rows = idx ? w.a_k : sv.attn_out;
     const void* q_rows = idx ? w.q_k : sv.q;
     cf_status as = attn_dispatch(L, q_rows, sv.k, sv.v, a_rows, sv.lse, w.da, idx, cu_kept, rows, w.dq,
-                                 w.dk, w.dv, w.attn_ws, st, idx ? sv.attn_out : nullptr, idx ? sv.q : nullptr);
+                                 w.dk, w.dv, w.attn_ws, st, idx ? sv.attn_out : nullptr, idx ? sv.q : nullptr, sv.rope_cos,
+                                 sv.rope_sin);
     if (as != CF_OK) return as;
-    if (sv.rope_cos) {
-        CF_HIP(launch_rope_bwd(dt, w.dq, L.Hq, w.dk, L.Hkv, idx, rows, L.d, L.S, sv.rope_cos, sv.rope_sin, st));
-    }
     // ---- adapted Q, K, V projections: input h1 [N,H]
     CF_HIP(group({{w.dq, A.bq, lw.tq, N, R, Nq, 0, A.scale},
                   {w.dk, A.bk, lw.tk, N, R, Nkv, 0, A.scale},

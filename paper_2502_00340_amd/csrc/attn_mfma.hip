@@ -63,6 +63,11 @@ struct AttnParams {
     uint64_t dq_limits;
     int n_slots;                   // dK/dV blocks that the device holds at a time (the kernel sizes its blocks' work by it)
     int B, S, Hq, Hkv;
+    // Nullable, both or none: rotary tables [S][d/2].  dQ and dK leave rotated back to before the rotary embedding, at the original
+    // positions of their rows: the pair (c, c + d/2) of a row lies in two registers of one lane where the results are written, and in
+    // a thread of the reduction where partials are (a pass of its own over dQ and dK, which also rounds them once
+    // more: 16 us at [8192 rows, 32/4 heads of 64] and [4096, 24/8 of 128]).
+    const float *rope_cos, *rope_sin;
     int n_kept;                    // rows that the compact buffers are laid out for (the stride of stat and of the partials)
     const int32_t* n_dev;          // nullable: the live row count on the device, at most n_kept
     float scale;
@@ -207,6 +212,36 @@ __device__ __forceinline__ bf16x8_t frag_tokens(const unsigned char* tile, int r
     return __builtin_bit_cast(bf16x8_t, both);
 }
 
+// Writes a wave's [32 rows][D] accumulators (lane = column within 32, register v = row 8*(v/4) + 4*hh + v%4) as bf16, times
+// scale and rotated back to before the rotary embedding, to rows of `out` (its first row and the head's first column; `stride`
+// elements apart); the wave's rows from `rows` on do not exist.  lane_pos = position of row lane % 32.
+template <int D>
+__device__ __forceinline__ void store_rows_rotated(bf16_t* out, int64_t stride, int rows, const f32x16_t (&acc)[D / 32], float scale,
+                                                   int lane, int lane_pos, const float* __restrict__ rope_cos,
+                                                   const float* __restrict__ rope_sin) {
+    constexpr int NT = D / 32;
+    const int slot = lane & 31, hh = lane >> 5;
+    int at[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) at[v] = max(__shfl(lane_pos, 8 * (v >> 2) + 4 * hh + (v & 3), 64), 0) * (D / 2) + slot;
+#pragma unroll
+    for (int nt = 0; nt < NT / 2; ++nt) {
+        float c[16], s[16];             // loaded for every row, existing or not: nothing here waits for a branch
+#pragma unroll
+        for (int v = 0; v < 16; ++v) { c[v] = rope_cos[at[v] + nt * 32]; s[v] = rope_sin[at[v] + nt * 32]; }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int r = 8 * (v >> 2) + 4 * hh + (v & 3);
+            const float a = acc[nt][v] * scale, b = acc[nt + NT / 2][v] * scale;
+            if (r < rows) {
+                bf16_t* row = out + r * stride + nt * 32 + slot;
+                row[0] = f32_to_bf16(a * c[v] + b * s[v]);
+                row[D / 2] = f32_to_bf16(b * c[v] - a * s[v]);
+            }
+        }
+    }
+}
+
 // global -> LDS: a [64][D] tile goes in as 1 KB wave-loads (16 bytes per lane): wave w, load i fills
 // LDS bytes [(4*i + w) KB, +1 KB) of the tile, i.e. 1024/(2D) rows, and a lane fetches the global chunk
 // that belongs in its (swizzled) LDS slot.  Rows outside the source's descriptor range arrive as zeros.
@@ -214,7 +249,9 @@ __device__ __forceinline__ bf16x8_t frag_tokens(const unsigned char* tile, int r
 // ---------------------------------------------------------------------------
 // dQ kernel
 // ---------------------------------------------------------------------------
-template <int D>
+// ROPE here and below: rope_cos and rope_sin are set.  (A template: as a branch behind the loop it cost calls without tables 6 % of
+// the dQ kernel's time, through the registers it takes.)
+template <int D, bool ROPE>
 __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
     constexpr int KS = D / 16, NT = D / 32;
     constexpr int TILE = 64 * D * 2;            // one 64-token tile in bytes
@@ -421,6 +458,11 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
         }
         return;
     }
+    if constexpr (ROPE) {
+        store_rows_rotated<D>(p.dq_kept + (int64_t)(j0 + wave * 32) * Nq + h * D, Nq, rows_in_tile - wave * 32, acc, p.scale, lane, pos,
+                              p.rope_cos, p.rope_sin);
+        return;
+    }
     // dq[query][d]: lane = d column, registers = query rows
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -448,7 +490,7 @@ __host__ __device__ constexpr int dkv_slot_index(int KS, bool even, int p) {
     return n;
 }
 
-template <int D>
+template <int D, bool ROPE>
 __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     constexpr int KS = D / 16, NT = D / 32;
     constexpr int TILE = 64 * D * 2;
@@ -777,6 +819,11 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     }
 
     if (G == HP) {
+        if constexpr (ROPE) {
+            const int pos = kvalid ? (p.idx ? p.idx[jk] : jk) - b * p.S : 0;
+            store_rows_rotated<D>(p.dk_kept + (int64_t)(c0 + wave * 32) * Nkv + g * D, Nkv, keys_in_tile - wave * 32, dk, p.scale, lane,
+                                  pos, p.rope_cos, p.rope_sin);
+        }
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
@@ -784,7 +831,7 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
                 const int r = wave * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
                 if (r < keys_in_tile) {
                     const int64_t off = (int64_t)(c0 + r) * Nkv + g * D + nt * 32 + slot;
-                    p.dk_kept[off] = f32_to_bf16(dk[nt][v] * p.scale);
+                    if constexpr (!ROPE) p.dk_kept[off] = f32_to_bf16(dk[nt][v] * p.scale);
                     p.dv_kept[off] = f32_to_bf16(dv[nt][v]);
                 }
             }
@@ -815,6 +862,7 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
 // that a lone wave needs, as long as there are two blocks for every CU and more to follow: whole attention call at d = 64, this
 // kernel and the pipelined one, [8192 rows, 32/32 heads, S = 2048] 274 and 322 us, [4096, 64/64, S = 1024] 177 and 212.  Fragment reads
 // run one MFMA pair ahead.  The accumulation order of every element is that of the pipelined kernel.
+template <bool ROPE>
 __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
     constexpr int D = 64, KS = D / 16, NT = D / 32;
     constexpr int TILE = 64 * D * 2;
@@ -993,6 +1041,13 @@ __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
 
     const bool whole = G == HP;
     const int64_t part = whole ? 0 : (int64_t)((h0 - g * G) / HP) * p.n_kept * Nkv;
+    if constexpr (ROPE) {
+        if (whole) {
+            const int pos = kvalid ? (p.idx ? p.idx[jk] : jk) - b * p.S : 0;
+            store_rows_rotated<D>(p.dk_kept + (int64_t)(c0 + wave * 32) * Nkv + g * D, Nkv, keys_in_tile - wave * 32, dk, p.scale, lane,
+                                  pos, p.rope_cos, p.rope_sin);
+        }
+    }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
@@ -1001,7 +1056,7 @@ __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
             if (r < keys_in_tile) {
                 const int64_t off = part + (int64_t)(c0 + r) * Nkv + g * D + nt * 32 + slot;
                 if (whole) {
-                    p.dk_kept[off] = f32_to_bf16(dk[nt][v] * p.scale);
+                    if constexpr (!ROPE) p.dk_kept[off] = f32_to_bf16(dk[nt][v] * p.scale);
                     p.dv_kept[off] = f32_to_bf16(dv[nt][v]);
                 } else {
                     p.dk_part[off] = dk[nt][v];
@@ -1012,45 +1067,69 @@ __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
     }
 }
 
-// acc += part[0..7]
-__device__ __forceinline__ void add8(const float* __restrict__ part, float (&acc)[8]) {
-    const float4 a = reinterpret_cast<const float4*>(part)[0], b = reinterpret_cast<const float4*>(part)[1];
+// acc += part[0..3], part[half..half+3]
+__device__ __forceinline__ void add4x2(const float* __restrict__ part, int half, float (&acc)[8]) {
+    const float4 a = *reinterpret_cast<const float4*>(part), b = *reinterpret_cast<const float4*>(part + half);
     acc[0] += a.x; acc[1] += a.y; acc[2] += a.z; acc[3] += a.w;
     acc[4] += b.x; acc[5] += b.y; acc[6] += b.z; acc[7] += b.w;
 }
 
 // dk = scale * sum_g dk_part[g], dv = sum_g dv_part[g], and for a split dQ launch dq = scale * sum_z dq_part[z] (one launch
 // for both: the smallest kernel costs 5 us), in a fixed order: deterministic.  Blocks below kv_blocks take dk and dv, the others dq.
-__global__ __launch_bounds__(256) void attn_reduce_kernel(AttnParams p, int Nkv, int Nq, int kv_blocks) {
+// A thread sums columns c..c+3 and d/2+c..d/2+c+3 of a head: the pairs of the rotary embedding.
+template <int D, bool ROPE>
+__global__ __launch_bounds__(256) void attn_reduce_kernel(AttnParams p, int kv_blocks) {
+    constexpr int half = D / 2;
     const int n_live = live_rows(p.n_kept, p.n_dev);
-    if ((int)blockIdx.x >= kv_blocks) {
-        const int ranges = dq_ranges(p.dq_limits, n_live);
-        const int64_t i = ((int64_t)(blockIdx.x - kv_blocks) * 256 + threadIdx.x) * 8;
-        if (ranges == 1 || i >= (int64_t)n_live * Nq) return;           // whole tiles: the dQ blocks wrote the results themselves
-        float sq[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const bool is_q = (int)blockIdx.x >= kv_blocks;
+    const int heads = is_q ? p.Hq : p.Hkv;
+    const int64_t stride = (int64_t)p.n_kept * heads * D;               // between two partials
+    int parts;
+    if (is_q) {
+        parts = dq_ranges(p.dq_limits, n_live);
+    } else {
+        const int G = p.Hq / p.Hkv;
+        parts = G / attn_heads_per_block(n_live, p.Hq, G, p.n_slots);
+    }
+    if (parts == 1) return;                                             // the dQ or dK/dV blocks wrote the results themselves
+    const unsigned u = (blockIdx.x - (is_q ? kv_blocks : 0)) * 256u + threadIdx.x;
+    const unsigned rh = u / (D / 8);                                    // row * heads + head
+    if ((int64_t)rh >= (int64_t)n_live * heads) return;
+    const int c = (int)(u % (D / 8)) * 4;
+    const int64_t i = (int64_t)rh * D + c;
+    float y[8], dv[8];                                                  // columns c + e, half + c + e
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] = dv[e] = 0.f;
+    if (is_q) {
 #pragma unroll 4
-        for (int z = 0; z < ranges; ++z) add8(p.dq_part + (int64_t)z * p.n_kept * Nq + i, sq);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) sq[e] *= p.scale;
-        Vec<bf16_t>::store(p.dq_kept + i, sq);
-        return;
-    }
-    const int hp = attn_heads_per_block(n_live, p.Hq, p.Hq / p.Hkv, p.n_slots);
-    const int G = p.Hq / p.Hkv / hp;                                    // partials per KV group
-    if (G == 1) return;                                                 // the dK/dV blocks wrote the results themselves
-    const int64_t stride = (int64_t)p.n_kept * Nkv;                     // between two partials
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
-    if (i >= (int64_t)n_live * Nkv) return;
-    float sk[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, sv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int z = 0; z < parts; ++z) add4x2(p.dq_part + z * stride + i, half, y);
+    } else {
 #pragma unroll 2
-    for (int g = 0; g < G; ++g) {
-        add8(p.dk_part + g * stride + i, sk);
-        add8(p.dv_part + g * stride + i, sv);
+        for (int z = 0; z < parts; ++z) {
+            add4x2(p.dk_part + z * stride + i, half, y);
+            add4x2(p.dv_part + z * stride + i, half, dv);
+        }
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) sk[e] *= p.scale;
-    Vec<bf16_t>::store(p.dk_kept + i, sk);
-    Vec<bf16_t>::store(p.dv_kept + i, sv);
+    for (int e = 0; e < 8; ++e) y[e] *= p.scale;
+    if constexpr (ROPE) {
+        const int row = (int)(rh / (unsigned)heads);
+        const int64_t at = (int64_t)((p.idx ? p.idx[row] : row) % p.S) * half + c;
+        const float4 co = *reinterpret_cast<const float4*>(p.rope_cos + at), si = *reinterpret_cast<const float4*>(p.rope_sin + at);
+        const float cs[4] = {co.x, co.y, co.z, co.w}, sn[4] = {si.x, si.y, si.z, si.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float a = y[e], b = y[4 + e];
+            y[e] = a * cs[e] + b * sn[e];
+            y[4 + e] = b * cs[e] - a * sn[e];
+        }
+    }
+    bf16_t* out = is_q ? p.dq_kept : p.dk_kept;
+    *reinterpret_cast<uint2*>(out + i) = make_uint2(pack2(y[0], y[1]), pack2(y[2], y[3]));
+    *reinterpret_cast<uint2*>(out + i + half) = make_uint2(pack2(y[4], y[5]), pack2(y[6], y[7]));
+    if (is_q) return;
+    *reinterpret_cast<uint2*>(p.dv_kept + i) = make_uint2(pack2(dv[0], dv[1]), pack2(dv[2], dv[3]));
+    *reinterpret_cast<uint2*>(p.dv_kept + i + half) = make_uint2(pack2(dv[4], dv[5]), pack2(dv[6], dv[7]));
 }
 
 // stat[0][h][j] = log2(e) * LSE(b, h, position of kept row j); stat[1][h][j] = D = sum_c dO*O of
@@ -1127,7 +1206,7 @@ size_t attn_mfma_partial_bound(const cf_layer_desc& L, int n_kept) {
     return attn_dkv_partial_bytes(L, n_kept) + align_up(split_rows * L.d * sizeof(float), 256);
 }
 
-template <int D>
+template <int D, bool ROPE>
 static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16_t* o_out, const bf16_t* q_full, bf16_t* q_out,
                            hipStream_t st) {
     constexpr int smem_dq = 2 * 2 * 64 * D * 2;
@@ -1145,9 +1224,9 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
     const bool paired = D == 64 && (tiles == 1 || (int64_t)p.Hq * p.B * tiles * 4 > (int64_t)n_cu * (tiles < 12 ? 7 : 8));
     p.n_slots = n_cu * (paired ? 2 : 1);
     static std::atomic<uint64_t> lds_ok_dq{0}, lds_ok_dkv{0}, lds_ok_paired{0};
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&attn_dq_kernel<D>), smem_dq, lds_ok_dq);
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&attn_dq_kernel<D, ROPE>), smem_dq, lds_ok_dq);
     if (e != hipSuccess) return e;
-    void (*const dkv)(AttnParams) = paired ? attn_dkv64_kernel : attn_dkv_kernel<D>;
+    void (*const dkv)(AttnParams) = paired ? attn_dkv64_kernel<ROPE> : attn_dkv_kernel<D, ROPE>;
     e = allow_dynamic_lds(reinterpret_cast<const void*>(dkv), smem_dkv, paired ? lds_ok_paired : lds_ok_dkv);
     if (e != hipSuccess) return e;
     if (p.o_kept == nullptr) {
@@ -1155,28 +1234,30 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
         attn_stats_kernel<<<(int)((total + 255) / 256), 256, 0, st>>>(p.do_kept, p.lse_full, p.idx, n_kept, p.n_dev, p.Hq, D,
                                                                      p.S, p.stat, o_full, o_out, q_full, q_out);
     }
-    attn_dq_kernel<D><<<dim3(p.Hq * p.B, tiles, dq_cap), 256, smem_dq, st>>>(p);
+    attn_dq_kernel<D, ROPE><<<dim3(p.Hq * p.B, tiles, dq_cap), 256, smem_dq, st>>>(p);
     dkv<<<dim3(p.Hq * p.B * tiles), 256, smem_dkv, st>>>(p);
     const int kv_blocks = p.Hq != p.Hkv ? ceil_div((int64_t)n_kept * p.Hkv * D / 8, 256) : 0;
     const int q_blocks = dq_cap > 1 ? ceil_div((int64_t)n_kept * p.Hq * D / 8, 256) : 0;
-    if (kv_blocks + q_blocks > 0) attn_reduce_kernel<<<kv_blocks + q_blocks, 256, 0, st>>>(p, p.Hkv * D, p.Hq * D, kv_blocks);
+    if (kv_blocks + q_blocks > 0) attn_reduce_kernel<D, ROPE><<<kv_blocks + q_blocks, 256, 0, st>>>(p, kv_blocks);
     return hipGetLastError();
 }
 
 // o_full / q_full (null or both set, need idx): attention output and queries at full length; their kept
 // rows are then copied to o_kept / q_kept (which must be writable buffers) by the row-statistics pass.
+// rope_cos / rope_sin: null or the rotary tables, see AttnParams.
 hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void* q_kept,
                                 const void* k_full, const void* v_full, const void* o_kept,
                                 const float* lse_full, const void* do_kept, float* stat,
                                 const int32_t* idx, const int32_t* cu_kept, RowCount rows, void* dq_kept,
                                 void* dk_kept, void* dv_kept, float* partials, hipStream_t st,
-                                const void* o_full, const void* q_full) {
+                                const void* o_full, const void* q_full, const float* rope_cos, const float* rope_sin) {
     AttnParams p;
     const int n_kept = rows.n;
     p.q_kept = (const bf16_t*)q_kept; p.k_full = (const bf16_t*)k_full; p.v_full = (const bf16_t*)v_full;
     p.do_kept = (const bf16_t*)do_kept; p.o_kept = o_full ? nullptr : (const bf16_t*)o_kept; p.lse_full = lse_full; p.stat = stat; p.idx = idx;
     p.cu_kept = cu_kept; p.dq_kept = (bf16_t*)dq_kept; p.dk_kept = (bf16_t*)dk_kept;
     p.dv_kept = (bf16_t*)dv_kept; p.B = L.B; p.S = L.S; p.Hq = L.Hq; p.Hkv = L.Hkv; p.scale = scale;
+    p.rope_cos = rope_cos; p.rope_sin = rope_sin;
     p.n_kept = n_kept;
     p.n_dev = rows.dev;
     const int dq_cap = attn_dq_plan(L, rows, p.dq_limits);
@@ -1186,8 +1267,9 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     bf16_t* o_out = (bf16_t*)const_cast<void*>(o_kept);
     bf16_t* q_out = (bf16_t*)const_cast<void*>(q_kept);
     if ((o_full != nullptr) != (q_full != nullptr) || (o_full != nullptr && idx == nullptr)) return hipErrorInvalidValue;
-    return L.d == 64 ? launch_t<64>(p, dq_cap, (const bf16_t*)o_full, o_out, (const bf16_t*)q_full, q_out, st)
-                     : launch_t<128>(p, dq_cap, (const bf16_t*)o_full, o_out, (const bf16_t*)q_full, q_out, st);
+    const auto launch = L.d == 64 ? (rope_cos ? launch_t<64, true> : launch_t<64, false>)
+                                  : (rope_cos ? launch_t<128, true> : launch_t<128, false>);
+    return launch(p, dq_cap, (const bf16_t*)o_full, o_out, (const bf16_t*)q_full, q_out, st);
 }
 
 }  // namespace cf

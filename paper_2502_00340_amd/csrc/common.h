@@ -143,10 +143,10 @@ hipError_t launch_rmsnorm_bwd(int dtype, const void* dh, const void* x, const vo
                               const int32_t* idx, const void* res, RowCount rows, int H, float eps,
                               void* dx_out, float* dg_partial, void* dg_out, hipStream_t st,
                               bool dg_acc_f32 = false, void* h_out = nullptr);
-// gq [n_rows, hq*d] and gk [n_rows, hk*d], in place: transposed rotary rotation at position idx[j] % S
+// fp32 gq [n_rows, hq*d] and gk [n_rows, hk*d], in place: transposed rotary rotation at position idx[j] % S
 // (idx null: j % S); cos, sin are [S, d/2] fp32
-hipError_t launch_rope_bwd(int dtype, void* gq, int hq, void* gk, int hk, const int32_t* idx, RowCount rows, int d, int S,
-                           const float* cos, const float* sin, hipStream_t st);
+hipError_t launch_rope_bwd_f32(void* gq, int hq, void* gk, int hk, const int32_t* idx, RowCount rows, int d, int S,
+                               const float* cos, const float* sin, hipStream_t st);
 // D[j,h] = sum_c da[j,h*d+c] * a[row,h*d+c], row = a_idx ? a_idx[j] : j; with a_idx the same launch also
 // writes the compact copies a_out[j,:] = a[row,:] and (q_src non-null) q_out[j,:] = q_src[row,:]
 hipError_t launch_attn_rowdot(int dtype, const void* da, const void* a, RowCount rows, int Hq, int d,

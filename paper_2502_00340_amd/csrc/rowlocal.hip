@@ -248,12 +248,13 @@ __global__ __launch_bounds__(256) void attn_rowdot_kernel(const T* __restrict__ 
 //   dx[i] = dy[i]*c + dy[i+d/2]*s,   dx[i+d/2] = dy[i+d/2]*c - dy[i]*s
 // of the hq heads of a row of gq and the hk heads of a row of gk (one launch: the smallest kernel costs 5 us).
 // One thread per vector of VN frequencies of one (row, head); d/2 is a multiple of VN.
-template <typename T>
-__global__ __launch_bounds__(256) void rope_bwd_kernel(T* __restrict__ gq, int hq, T* __restrict__ gk, int hk,
-                                                       const int32_t* __restrict__ idx,
-                                                       int n_max, const int32_t* __restrict__ n_dev, int d, int S,
-                                                       const float* __restrict__ cs,
-                                                       const float* __restrict__ sn) {
+// fp32 check mode only: the matrix-core attention kernels rotate where they write dq and dk.
+__global__ __launch_bounds__(256) void rope_bwd_f32_kernel(float* __restrict__ gq, int hq, float* __restrict__ gk, int hk,
+                                                           const int32_t* __restrict__ idx,
+                                                           int n_max, const int32_t* __restrict__ n_dev, int d, int S,
+                                                           const float* __restrict__ cs,
+                                                           const float* __restrict__ sn) {
+    typedef float T;
     constexpr int VN = Vec<T>::N;
     const int n_rows = live_rows(n_max, n_dev);
     const int half = d / 2, vph = half / VN, heads = hq + hk;           // vph: vectors per head half
@@ -350,17 +351,13 @@ hipError_t launch_rmsnorm_bwd(int dtype, const void* dh, const void* x, const vo
     return hipGetLastError();
 }
 
-hipError_t launch_rope_bwd(int dtype, void* gq, int hq, void* gk, int hk, const int32_t* idx, RowCount rows, int d, int S,
-                           const float* cos, const float* sin, hipStream_t st) {
-    const int n_rows = rows.n;
+hipError_t launch_rope_bwd_f32(void* gq, int hq, void* gk, int hk, const int32_t* idx, RowCount rows, int d, int S,
+                               const float* cos, const float* sin, hipStream_t st) {
+    const int n_rows = rows.n, vn = Vec<float>::N;
     if (n_rows <= 0) return hipSuccess;
-    const int vn = dtype == CF_F32 ? 4 : 8;
     if ((d / 2) % vn != 0) return hipErrorInvalidValue;
     const int grid = stream_grid((int64_t)n_rows * (hq + hk) * (d / 2 / vn));
-    if (dtype == CF_F32)
-        rope_bwd_kernel<float><<<grid, 256, 0, st>>>((float*)gq, hq, (float*)gk, hk, idx, n_rows, rows.dev, d, S, cos, sin);
-    else
-        rope_bwd_kernel<bf16_t><<<grid, 256, 0, st>>>((bf16_t*)gq, hq, (bf16_t*)gk, hk, idx, n_rows, rows.dev, d, S, cos, sin);
+    rope_bwd_f32_kernel<<<grid, 256, 0, st>>>((float*)gq, hq, (float*)gk, hk, idx, n_rows, rows.dev, d, S, cos, sin);
     return hipGetLastError();
 }
 

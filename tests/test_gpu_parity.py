@@ -821,6 +821,23 @@ def test_layer_with_rotary_embedding(dtype, mode):
     assert Hn.rel_fro(Hn.to_np(got0["dwq"]), ref["dwq"]) > 10 * Hn.TOL[dtype]
 
 
+@pytest.mark.parametrize("Hq,Hkv,d,S,rho", [
+    (4, 4, 64, 100, 0.5),       # one key tile, dQ and dK written by their own kernels
+    (3, 3, 128, 301, 0.7),      # the same at d = 128, several tiles, ragged
+    (4, 1, 128, 170, 0.6),      # dK from partials
+    (2, 2, 64, 401, 0.6),       # dQ from key ranges, dK whole
+    (4, 2, 128, 401, 0.4),      # both from partials
+])
+def test_layer_rotary_embedding_wherever_dq_and_dk_are_written(Hq, Hkv, d, S, rho):
+    shape = WL.LayerShape("rope_routes", B=2, S=S, H=256, Hq=Hq, Hkv=Hkv, d=d, F=128, dtype="bf16")
+    say("layer rotary %d/%d d=%d S=%d" % (Hq, Hkv, d, S))
+    p = Hn.Problem(shape, S + d, "independent", rho=rho, rope=True)
+    got, ridx, n = _run_layer(p)
+    Hn.check_layer(p, got, p.oracle(), ridx, Hn.TOL["bf16"])
+    gotd, _, _ = _run_layer(p, dense=True)
+    Hn.check_layer(p, gotd, p.oracle(dense=True), None, Hn.TOL["bf16"])
+
+
 def test_no_write_outside_the_outputs_and_the_workspace():
     """Every output tensor and the workspace sit inside a larger allocation filled with a
     sentinel; after filtered, compact and dense calls on a ragged shape (no dimension a tile
