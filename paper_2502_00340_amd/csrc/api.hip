@@ -125,7 +125,7 @@ struct LayerWs {
     int32_t *idx, *cu_kept, *n_kept_dev;
     void *dy_k, *bufF0, *bufF1, *bufF2, *bufHa, *bufHb, *dr, *a_k, *da, *q_k, *dq, *dk, *dv;
     void* attn_ws;
-    float* dg_partial;
+    float *dg_partial1, *dg_partial2;       // of the two norms
     size_t total;
 };
 
@@ -154,7 +154,8 @@ LayerWs carve_layer(const cf_layer_desc& L, int max_kept, void* ws) {
     w.dk = c.take(N * Nkv * e);
     w.dv = c.take(N * Nkv * e);
     w.attn_ws = c.take(attn_ws_total(L, (int)N));
-    w.dg_partial = (float*)c.take((size_t)rmsnorm_bwd_blocks((int)N) * L.H * 4);
+    w.dg_partial1 = (float*)c.take((size_t)rmsnorm_bwd_blocks((int)N) * L.H * 4);
+    w.dg_partial2 = (float*)c.take((size_t)rmsnorm_bwd_blocks((int)N) * L.H * 4);
     w.total = c.off;
     return w;
 }
@@ -266,8 +267,7 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     // writes h2 = rmsnorm(r)*g2, the operand of the two parameter-gradient products below (which is why
     // they come after it: no norm-recompute pass of its own).
     void* h2 = w.bufHa;
-    CF_HIP(launch_rmsnorm_bwd(dt, dh2, sv.r, W.g2, idx, dy_rows, rows, H, L.rms_eps, w.dr, w.dg_partial,
-                              G.dg2, st, mg, h2));
+    CF_HIP(launch_rmsnorm_bwd(dt, dh2, sv.r, W.g2, idx, dy_rows, rows, H, L.rms_eps, w.dr, w.dg_partial2, st, h2));
     CF_HIP(dw(h2, d_gate, G.dwg, H, F));
     CF_HIP(dw(h2, d_up, G.dwu, H, F));
 
@@ -291,8 +291,8 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     }
     // dx = dr + rmsnorm_bwd(dh1; x, g1);  dg1; h1 = rmsnorm(x)*g1 on the way (see h2 above), over dh1: h2 is still an operand
     void* h1 = dh1;
-    CF_HIP(launch_rmsnorm_bwd(dt, dh1, sv.x, W.g1, idx, w.dr, rows, H, L.rms_eps, G.dx, w.dg_partial,
-                              G.dg1, st, mg, h1));
+    CF_HIP(launch_rmsnorm_bwd(dt, dh1, sv.x, W.g1, idx, w.dr, rows, H, L.rms_eps, G.dx, w.dg_partial1, st, h1));
+    CF_HIP(launch_gain_grads(dt, w.dg_partial1, w.dg_partial2, rows, H, G.dg1, G.dg2, mg, st));
     CF_HIP(dw(h1, w.dq, G.dwq, H, Nq));
     CF_HIP(dw(h1, w.dk, G.dwk, H, Nkv));
     CF_HIP(dw(h1, w.dv, G.dwv, H, Nkv));
@@ -363,7 +363,7 @@ cf_status layer_core_lora(const cf_layer_desc& L, const cf_saved& sv, const cf_w
         GemmSeg s[2] = {{d_gate, W.wg, F}, {d_up, W.wu, F}};
         CF_HIP(launch_gemm_nt(dt, s, 2, dh2, N, H, st, nd));
     }
-    CF_HIP(launch_rmsnorm_bwd(dt, dh2, sv.r, W.g2, idx, dy_rows, rows, H, L.rms_eps, w.dr, w.dg_partial, nullptr, st));
+    CF_HIP(launch_rmsnorm_bwd(dt, dh2, sv.r, W.g2, idx, dy_rows, rows, H, L.rms_eps, w.dr, nullptr, st));
     // ---- adapted O projection: input a [N,Nq], output gradient dr [N,H]
     CF_HIP(group({{w.dr, A.bo, lw.to, N, R, H, 0, A.scale}}));
     {   // da = dr*Wo^T + t_o*a_o^T
@@ -393,7 +393,7 @@ cf_status layer_core_lora(const cf_layer_desc& L, const cf_saved& sv, const cf_w
         CF_HIP(launch_gemm_nt(dt, s, 6, dh1, N, H, st, nd));
     }
     void* h1 = w.bufHa;         // a by-product of the norm's backward pass
-    CF_HIP(launch_rmsnorm_bwd(dt, dh1, sv.x, W.g1, idx, w.dr, rows, H, L.rms_eps, G.dx, w.dg_partial, nullptr, st, false, h1));
+    CF_HIP(launch_rmsnorm_bwd(dt, dh1, sv.x, W.g1, idx, w.dr, rows, H, L.rms_eps, G.dx, nullptr, st, h1));
     CF_HIP(group({{h1, A.aq, lw.uq, N, R, H, 2, A.scale},
                   {h1, A.ak, lw.uk, N, R, H, 2, A.scale},
                   {h1, A.av, lw.uv, N, R, H, 2, A.scale}}));

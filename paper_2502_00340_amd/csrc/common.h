@@ -134,15 +134,16 @@ hipError_t launch_swiglu_bwd(int dtype, const void* d_act, const void* gate, con
                              const int32_t* idx, RowCount rows, int F, void* d_gate, void* d_up,
                              void* act, hipStream_t st, const void* copy_src = nullptr, int copy_cols = 0,
                              void* copy_dst = nullptr);
-// dx_out = res + rmsnorm_bwd(dh; x, g); dg_partial is [rmsnorm_bwd_blocks(n_rows), H] fp32 scratch.
-// dg_acc_f32: dg_out is fp32 [H] and the gain gradient is added to it instead of written.
-// dg_out null: the gains are frozen, no gradient is summed up for them.
-// h_out (nullable, [n_rows, H]): also receives the normalised rows rmsnorm(x)*g.
+// dx_out = res + rmsnorm_bwd(dh; x, g); dg_partial (nullable: the gains are frozen) receives the gain gradient's
+// [rmsnorm_bwd_blocks(n_rows), H] fp32 partials for launch_gain_grads.
+// h_out (nullable, [n_rows, H], may be dh): also receives the normalised rows rmsnorm(x)*g.
 int rmsnorm_bwd_blocks(int n_rows);
 hipError_t launch_rmsnorm_bwd(int dtype, const void* dh, const void* x, const void* g,
                               const int32_t* idx, const void* res, RowCount rows, int H, float eps,
-                              void* dx_out, float* dg_partial, void* dg_out, hipStream_t st,
-                              bool dg_acc_f32 = false, void* h_out = nullptr);
+                              void* dx_out, float* dg_partial, hipStream_t st, void* h_out = nullptr);
+// The gain gradients of both norms from their partials.  acc_f32: dg1 and dg2 are fp32 [H] and added to instead of written.
+hipError_t launch_gain_grads(int dtype, const float* partial1, const float* partial2, RowCount rows, int H, void* dg1, void* dg2,
+                             bool acc_f32, hipStream_t st);
 // fp32 gq [n_rows, hq*d] and gk [n_rows, hk*d], in place: transposed rotary rotation at position idx[j] % S
 // (idx null: j % S); cos, sin are [S, d/2] fp32
 hipError_t launch_rope_bwd_f32(void* gq, int hq, void* gk, int hk, const int32_t* idx, RowCount rows, int d, int S,

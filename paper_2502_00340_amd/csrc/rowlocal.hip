@@ -165,6 +165,7 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* dh,
             }
         }
     }
+    if (dg_partial == nullptr) return;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
         const int v = threadIdx.x + i * 256;
@@ -178,12 +179,14 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* dh,
 // out[c] = sum_b partial[b,c]: a block owns 32 columns (8 lanes x 4 columns), 32 row groups
 // stride through the partials with 16-byte loads, many in flight; H is a multiple of 4.
 // The order of the additions is fixed, so the result is reproducible.  ACC: out is fp32 and the
-// sum is added to it (main-gradient accumulation).
+// sum is added to it (main-gradient accumulation).  blockIdx.y: which of the two norms' partials (one launch for both: 5 us).
 template <typename T, bool ACC = false>
-__global__ __launch_bounds__(256) void colsum_finish_kernel(const float* __restrict__ partial,
+__global__ __launch_bounds__(256) void colsum_finish_kernel(const float* __restrict__ partial1, const float* __restrict__ partial2,
                                                             int n_max, const int32_t* __restrict__ n_dev, int H,
-                                                            T* __restrict__ out) {
+                                                            T* __restrict__ out1, T* __restrict__ out2) {
     __shared__ float red[32][33];
+    const float* partial = blockIdx.y == 0 ? partial1 : partial2;
+    T* out = blockIdx.y == 0 ? out1 : out2;
     const int nblk = rmsnorm_bwd_nblk(live_rows(n_max, n_dev));     // the partials that the backward kernel wrote
     const int cq = threadIdx.x & 7, rg = threadIdx.x >> 3;
     const int c = blockIdx.x * 32 + cq * 4;
@@ -329,25 +332,23 @@ static void rmsnorm_bwd_dispatch(int nv, int nblk, hipStream_t st, const void* d
 
 hipError_t launch_rmsnorm_bwd(int dtype, const void* dh, const void* x, const void* g,
                               const int32_t* idx, const void* res, RowCount rows, int H, float eps,
-                              void* dx_out, float* dg_partial, void* dg_out, hipStream_t st, bool dg_acc_f32,
-                              void* h_out) {
+                              void* dx_out, float* dg_partial, hipStream_t st, void* h_out) {
     const int n_rows = rows.n;
+    if (n_rows <= 0) return hipSuccess;
     const int nblk = rmsnorm_bwd_blocks(n_rows);
-    if (n_rows <= 0) return dg_acc_f32 || dg_out == nullptr ? hipSuccess : launch_fill_zero(dg_out, (size_t)H * dtype_size(dtype), st);
     const int vn = dtype == CF_F32 ? 4 : 8;
     const int nv = ceil_div(H / vn, 256);           // 16-byte vectors per thread (at most 8, checked by the API)
-    const int fin = ceil_div(H, 32);
-    if (dtype == CF_F32) {
-        rmsnorm_bwd_dispatch<float>(nv, nblk, st, dh, x, g, idx, res, rows, H, eps, dx_out, dg_partial, h_out);
-        if (dg_out == nullptr) return hipGetLastError();
-        if (dg_acc_f32) colsum_finish_kernel<float, true><<<fin, 256, 0, st>>>(dg_partial, n_rows, rows.dev, H, (float*)dg_out);
-        else colsum_finish_kernel<float><<<fin, 256, 0, st>>>(dg_partial, n_rows, rows.dev, H, (float*)dg_out);
-    } else {
-        rmsnorm_bwd_dispatch<bf16_t>(nv, nblk, st, dh, x, g, idx, res, rows, H, eps, dx_out, dg_partial, h_out);
-        if (dg_out == nullptr) return hipGetLastError();
-        if (dg_acc_f32) colsum_finish_kernel<float, true><<<fin, 256, 0, st>>>(dg_partial, n_rows, rows.dev, H, (float*)dg_out);
-        else colsum_finish_kernel<bf16_t><<<fin, 256, 0, st>>>(dg_partial, n_rows, rows.dev, H, (bf16_t*)dg_out);
-    }
+    if (dtype == CF_F32) rmsnorm_bwd_dispatch<float>(nv, nblk, st, dh, x, g, idx, res, rows, H, eps, dx_out, dg_partial, h_out);
+    else rmsnorm_bwd_dispatch<bf16_t>(nv, nblk, st, dh, x, g, idx, res, rows, H, eps, dx_out, dg_partial, h_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_gain_grads(int dtype, const float* partial1, const float* partial2, RowCount rows, int H, void* dg1, void* dg2,
+                             bool acc_f32, hipStream_t st) {
+    const dim3 grid(ceil_div(H, 32), 2);
+    if (acc_f32) colsum_finish_kernel<float, true><<<grid, 256, 0, st>>>(partial1, partial2, rows.n, rows.dev, H, (float*)dg1, (float*)dg2);
+    else if (dtype == CF_F32) colsum_finish_kernel<float><<<grid, 256, 0, st>>>(partial1, partial2, rows.n, rows.dev, H, (float*)dg1, (float*)dg2);
+    else colsum_finish_kernel<bf16_t><<<grid, 256, 0, st>>>(partial1, partial2, rows.n, rows.dev, H, (bf16_t*)dg1, (bf16_t*)dg2);
     return hipGetLastError();
 }
 
