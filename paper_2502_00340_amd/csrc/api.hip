@@ -21,7 +21,8 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
                                 const float* lse_full, const void* do_kept, float* stat,
                                 const int32_t* idx, const int32_t* cu_kept, RowCount rows, void* dq_kept,
                                 void* dk_kept, void* dv_kept, float* partials, hipStream_t st,
-                                const void* o_full, const void* q_full, const float* rope_cos, const float* rope_sin);
+                                const void* o_full, const void* q_full, const float* rope_cos, const float* rope_sin,
+                                const NtParts& do_parts);
 }  // namespace cf
 
 using namespace cf;
@@ -126,10 +127,16 @@ struct LayerWs {
     void *dy_k, *bufF0, *bufF1, *bufF2, *bufHa, *bufHb, *dr, *a_k, *da, *q_k, *dq, *dk, *dv;
     void* attn_ws;
     float *dg_partial1, *dg_partial2;       // of the two norms
+    float* slots;                           // fp32 parts of a product (NtParts), from its launch to its reader's; null in fp32
     size_t total;
 };
 
-LayerWs carve_layer(const cf_layer_desc& L, int max_kept, void* ws) {
+// the slots come last in a workspace (behind an adapter call's own buffers)
+float* take_slots(Carver& c, const cf_layer_desc& L) {
+    return L.dtype == CF_BF16 ? (float*)c.take(gemm_group_slot_bytes()) : nullptr;
+}
+
+LayerWs carve_layer(const cf_layer_desc& L, int max_kept, void* ws, bool with_slots = true) {
     const size_t e = dtype_size(L.dtype);
     const size_t N = (size_t)(max_kept > 0 ? max_kept : 1);
     const size_t T = (size_t)L.B * L.S;
@@ -156,19 +163,21 @@ LayerWs carve_layer(const cf_layer_desc& L, int max_kept, void* ws) {
     w.attn_ws = c.take(attn_ws_total(L, (int)N));
     w.dg_partial1 = (float*)c.take((size_t)rmsnorm_bwd_blocks((int)N) * L.H * 4);
     w.dg_partial2 = (float*)c.take((size_t)rmsnorm_bwd_blocks((int)N) * L.H * 4);
+    w.slots = with_slots ? take_slots(c, L) : nullptr;
     w.total = c.off;
     return w;
 }
 
 // o_full / q_full (nullable): the attention output and the queries at full length; the row-statistics
 // pass then copies their kept rows (through idx) into the writable buffers o_kept / q_kept.
-// rope_cos / rope_sin (nullable): dq and dk are rotated back to before the rotary embedding.
+// rope_cos / rope_sin (nullable): dq and dk are rotated back to before the rotary embedding.  do_parts: with o_full, do_kept may
+// still lie there; it is a writable buffer then.
 cf_status attn_dispatch(const cf_layer_desc& L, const void* q_kept, const void* k_full,
                         const void* v_full, const void* o_kept, const float* lse_full,
                         const void* do_kept, const int32_t* idx, const int32_t* cu_kept, RowCount rows,
                         void* dq_kept, void* dk_kept, void* dv_kept, void* attn_ws, hipStream_t st,
                         const void* o_full = nullptr, const void* q_full = nullptr, const float* rope_cos = nullptr,
-                        const float* rope_sin = nullptr) {
+                        const float* rope_sin = nullptr, const NtParts& do_parts = NtParts{}) {
     const int n_kept = rows.n;
     if (n_kept <= 0) return CF_OK;
     const float scale = eff_scale(L);
@@ -176,7 +185,8 @@ cf_status attn_dispatch(const cf_layer_desc& L, const void* q_kept, const void* 
     float* partials = reinterpret_cast<float*>(static_cast<unsigned char*>(attn_ws) + attn_drow_bytes(L, n_kept));
     if (attn_mfma_supported(L)) {
         CF_HIP(launch_attn_bwd_mfma(L, scale, q_kept, k_full, v_full, o_kept, lse_full, do_kept, Drow, idx,
-                                    cu_kept, rows, dq_kept, dk_kept, dv_kept, partials, st, o_full, q_full, rope_cos, rope_sin));
+                                    cu_kept, rows, dq_kept, dk_kept, dv_kept, partials, st, o_full, q_full, rope_cos, rope_sin,
+                                    do_parts));
     } else {
         CF_HIP(launch_attn_rowdot(L.dtype, do_kept, o_full ? o_full : o_kept, rows, L.Hq, L.d, Drow, st,
                                   o_full ? idx : nullptr, const_cast<void*>(o_kept), q_full,
@@ -246,52 +256,58 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     // ---- SwiGLU FFN: y = r + act*Wd --------------------------------------------
     // d_act = dy * Wd^T first; one pass over it then yields d_gate, d_up and act (the SwiGLU
     // product, rebuilt for dWd), so gate and up are read once
+    NtParts parts;      // where the product behind the next pass may lie instead of in its buffer
     void* d_act = w.bufF1;
     {   // [N,F] = [N,H] x [F,H]^T
         GemmSeg s{dy, W.wd, H};
-        CF_HIP(launch_gemm_nt(dt, &s, 1, d_act, N, F, st, nd, dy_is_full ? idx : nullptr, dy_is_full ? T : 0));
+        parts = gemm_nt_parts(dt, &s, 1, F, w.slots);
+        CF_HIP(launch_gemm_nt(dt, &s, 1, d_act, N, F, st, nd, dy_is_full ? idx : nullptr, dy_is_full ? T : 0, &parts));
     }
     void* d_gate = w.bufF1;   // in place over d_act
     void* d_up = w.bufF0;
     void* act = w.bufF2;
-    CF_HIP(launch_swiglu_bwd(dt, d_act, sv.gate, sv.up, idx, rows, F, d_gate, d_up, act, st,
+    CF_HIP(launch_swiglu_bwd(dt, d_act, sv.gate, sv.up, idx, rows, F, d_gate, d_up, act, st, parts,
                              dy_is_full ? dy : nullptr, H, dy_is_full ? w.dy_k : nullptr));
     CF_HIP(dw(act, dy_rows, G.dwd, F, H));     // dWd = act^T * dy           [F,H]
 
     void* dh2 = w.bufHb;
     {   // dh2 = d_gate*Wg^T + d_up*Wu^T   [N,H], contraction over F twice
         GemmSeg s[2] = {{d_gate, W.wg, F}, {d_up, W.wu, F}};
-        CF_HIP(launch_gemm_nt(dt, s, 2, dh2, N, H, st, nd));
+        parts = gemm_nt_parts(dt, s, 2, H, w.slots);
+        CF_HIP(launch_gemm_nt(dt, s, 2, dh2, N, H, st, nd, nullptr, 0, &parts));
     }
     // dr = dy + rmsnorm_bwd(dh2; r, g2);  dg2.  The pass has r and its rstd in registers, so it also
     // writes h2 = rmsnorm(r)*g2, the operand of the two parameter-gradient products below (which is why
     // they come after it: no norm-recompute pass of its own).
     void* h2 = w.bufHa;
-    CF_HIP(launch_rmsnorm_bwd(dt, dh2, sv.r, W.g2, idx, dy_rows, rows, H, L.rms_eps, w.dr, w.dg_partial2, st, h2));
+    CF_HIP(launch_rmsnorm_bwd(dt, dh2, sv.r, W.g2, idx, dy_rows, rows, H, L.rms_eps, w.dr, w.dg_partial2, st, parts, h2));
     CF_HIP(dw(h2, d_gate, G.dwg, H, F));
     CF_HIP(dw(h2, d_up, G.dwu, H, F));
 
     // ---- attention block: r = x + attn_out*Wo ------------------------------------
     {
         GemmSeg s2{w.dr, W.wo, H};                        // da = dr * Wo^T      [N,Nq]
-        CF_HIP(launch_gemm_nt(dt, &s2, 1, w.da, N, Nq, st, nd));
+        parts = gemm_nt_parts(dt, &s2, 1, Nq, w.slots);
+        CF_HIP(launch_gemm_nt(dt, &s2, 1, w.da, N, Nq, st, nd, nullptr, 0, &parts));
+        if (!idx) CF_HIP(launch_gemm_nt_sum(parts, N, w.da, st));       // with an index the row-statistics pass does it
     }
     // the attention backward's row-statistics pass reads attn_out and q through idx and leaves their
     // compact copies in w.a_k, w.q_k (no gather kernel)
     cf_status as = attn_dispatch(L, q_rows, sv.k, sv.v, a_rows, sv.lse, w.da, idx, cu_kept, rows, w.dq,
                                  w.dk, w.dv, w.attn_ws, st, idx ? sv.attn_out : nullptr, idx ? sv.q : nullptr, sv.rope_cos,
-                                 sv.rope_sin);
+                                 sv.rope_sin, parts);
     if (as != CF_OK) return as;
     CF_HIP(dw(a_rows, w.dr, G.dwo, Nq, H));          // dWo = a^T * dr      [Nq,H]
 
     void* dh1 = w.bufHb;
     {   // dh1 = dq*Wq^T + dk*Wk^T + dv*Wv^T
         GemmSeg s[3] = {{w.dq, W.wq, Nq}, {w.dk, W.wk, Nkv}, {w.dv, W.wv, Nkv}};
-        CF_HIP(launch_gemm_nt(dt, s, 3, dh1, N, H, st, nd));
+        parts = gemm_nt_parts(dt, s, 3, H, w.slots);
+        CF_HIP(launch_gemm_nt(dt, s, 3, dh1, N, H, st, nd, nullptr, 0, &parts));
     }
     // dx = dr + rmsnorm_bwd(dh1; x, g1);  dg1; h1 = rmsnorm(x)*g1 on the way (see h2 above), over dh1: h2 is still an operand
     void* h1 = dh1;
-    CF_HIP(launch_rmsnorm_bwd(dt, dh1, sv.x, W.g1, idx, w.dr, rows, H, L.rms_eps, G.dx, w.dg_partial1, st, h1));
+    CF_HIP(launch_rmsnorm_bwd(dt, dh1, sv.x, W.g1, idx, w.dr, rows, H, L.rms_eps, G.dx, w.dg_partial1, st, parts, h1));
     CF_HIP(launch_gain_grads(dt, w.dg_partial1, w.dg_partial2, rows, H, G.dg1, G.dg2, mg, st));
     CF_HIP(dw(h1, w.dq, G.dwq, H, Nq));
     CF_HIP(dw(h1, w.dk, G.dwk, H, Nkv));
@@ -305,19 +321,18 @@ struct LoraWs {
     LayerWs base;
     void *uq, *uk, *uv, *uo;    // [N, rank]           scale * X * a
     void *tq, *tk, *tv, *to;    // [N, rank]           scale * dY * b^T
-    float* slots;               // fp32 parts of the split adapter products
     size_t total;
 };
 
 LoraWs carve_lora(const cf_layer_desc& L, int rank, int max_kept, void* ws) {
     LoraWs w;
-    w.base = carve_layer(L, max_kept, ws);
+    w.base = carve_layer(L, max_kept, ws, false);
     const size_t e = dtype_size(L.dtype);
     const size_t N = (size_t)(max_kept > 0 ? max_kept : 1);
     Carver c(ws);
     c.off = w.base.total;
     for (void** p : {&w.uq, &w.uk, &w.uv, &w.uo, &w.tq, &w.tk, &w.tv, &w.to}) *p = c.take(N * rank * e);
-    w.slots = (float*)c.take(gemm_group_slot_bytes());
+    w.base.slots = take_slots(c, L);
     w.total = c.off;
     return w;
 }
@@ -345,36 +360,41 @@ cf_status layer_core_lora(const cf_layer_desc& L, const cf_saved& sv, const cf_w
     }
     if (dy_is_full && !idx) return CF_ERR_NULL;
     auto group = [&](std::initializer_list<GemmGroupProb> ps) {
-        return launch_gemm_group(dt, ps.begin(), (int)ps.size(), st, lw.slots, nd);
+        return launch_gemm_group(dt, ps.begin(), (int)ps.size(), st, w.slots, nd);
     };
     // ---- frozen SwiGLU FFN: only the input gradient
+    NtParts parts;      // where the product behind the next pass may lie instead of in its buffer
     void* d_act = w.bufF1;
     {
         GemmSeg s{dy, W.wd, H};
-        CF_HIP(launch_gemm_nt(dt, &s, 1, d_act, N, F, st, nd, dy_is_full ? idx : nullptr, dy_is_full ? T : 0));
+        parts = gemm_nt_parts(dt, &s, 1, F, w.slots);
+        CF_HIP(launch_gemm_nt(dt, &s, 1, d_act, N, F, st, nd, dy_is_full ? idx : nullptr, dy_is_full ? T : 0, &parts));
     }
     void* d_gate = w.bufF1;
     void* d_up = w.bufF0;
     const void* dy_rows = dy_is_full ? w.dy_k : dy;
-    CF_HIP(launch_swiglu_bwd(dt, d_act, sv.gate, sv.up, idx, rows, F, d_gate, d_up, nullptr, st, dy_is_full ? dy : nullptr,
+    CF_HIP(launch_swiglu_bwd(dt, d_act, sv.gate, sv.up, idx, rows, F, d_gate, d_up, nullptr, st, parts, dy_is_full ? dy : nullptr,
                              H, dy_is_full ? w.dy_k : nullptr));
     void* dh2 = w.bufHb;
     {
         GemmSeg s[2] = {{d_gate, W.wg, F}, {d_up, W.wu, F}};
-        CF_HIP(launch_gemm_nt(dt, s, 2, dh2, N, H, st, nd));
+        parts = gemm_nt_parts(dt, s, 2, H, w.slots);
+        CF_HIP(launch_gemm_nt(dt, s, 2, dh2, N, H, st, nd, nullptr, 0, &parts));
     }
-    CF_HIP(launch_rmsnorm_bwd(dt, dh2, sv.r, W.g2, idx, dy_rows, rows, H, L.rms_eps, w.dr, nullptr, st));
+    CF_HIP(launch_rmsnorm_bwd(dt, dh2, sv.r, W.g2, idx, dy_rows, rows, H, L.rms_eps, w.dr, nullptr, st, parts));
     // ---- adapted O projection: input a [N,Nq], output gradient dr [N,H]
     CF_HIP(group({{w.dr, A.bo, lw.to, N, R, H, 0, A.scale}}));
     {   // da = dr*Wo^T + t_o*a_o^T
         GemmSeg s[2] = {{w.dr, W.wo, H}, {lw.to, A.ao, R}};
-        CF_HIP(launch_gemm_nt(dt, s, 2, w.da, N, Nq, st, nd));
+        parts = gemm_nt_parts(dt, s, 2, Nq, w.slots);
+        CF_HIP(launch_gemm_nt(dt, s, 2, w.da, N, Nq, st, nd, nullptr, 0, &parts));
+        if (!idx) CF_HIP(launch_gemm_nt_sum(parts, N, w.da, st));
     }
     const void* a_rows = idx ? w.a_k : sv.attn_out;
     const void* q_rows = idx ? w.q_k : sv.q;
     cf_status as = attn_dispatch(L, q_rows, sv.k, sv.v, a_rows, sv.lse, w.da, idx, cu_kept, rows, w.dq,
                                  w.dk, w.dv, w.attn_ws, st, idx ? sv.attn_out : nullptr, idx ? sv.q : nullptr, sv.rope_cos,
-                                 sv.rope_sin);
+                                 sv.rope_sin, parts);
     if (as != CF_OK) return as;
     // ---- adapted Q, K, V projections: input h1 [N,H]
     CF_HIP(group({{w.dq, A.bq, lw.tq, N, R, Nq, 0, A.scale},
@@ -390,10 +410,11 @@ cf_status layer_core_lora(const cf_layer_desc& L, const cf_saved& sv, const cf_w
     {   // dh1 = dq*Wq^T + dk*Wk^T + dv*Wv^T + t_q*a_q^T + t_k*a_k^T + t_v*a_v^T
         GemmSeg s[6] = {{w.dq, W.wq, Nq}, {w.dk, W.wk, Nkv}, {w.dv, W.wv, Nkv},
                         {lw.tq, A.aq, R}, {lw.tk, A.ak, R}, {lw.tv, A.av, R}};
-        CF_HIP(launch_gemm_nt(dt, s, 6, dh1, N, H, st, nd));
+        parts = gemm_nt_parts(dt, s, 6, H, w.slots);
+        CF_HIP(launch_gemm_nt(dt, s, 6, dh1, N, H, st, nd, nullptr, 0, &parts));
     }
     void* h1 = w.bufHa;         // a by-product of the norm's backward pass
-    CF_HIP(launch_rmsnorm_bwd(dt, dh1, sv.x, W.g1, idx, w.dr, rows, H, L.rms_eps, G.dx, nullptr, st, h1));
+    CF_HIP(launch_rmsnorm_bwd(dt, dh1, sv.x, W.g1, idx, w.dr, rows, H, L.rms_eps, G.dx, nullptr, st, parts, h1));
     CF_HIP(group({{h1, A.aq, lw.uq, N, R, H, 2, A.scale},
                   {h1, A.ak, lw.uk, N, R, H, 2, A.scale},
                   {h1, A.av, lw.uv, N, R, H, 2, A.scale}}));
@@ -405,7 +426,7 @@ cf_status layer_core_lora(const cf_layer_desc& L, const cf_saved& sv, const cf_w
                                    {lw.uk, w.dk, G.dbk, R, Nkv, N, 1, 1.f},
                                    {h1, lw.tv, G.dav, H, R, N, 1, 1.f},
                                    {lw.uv, w.dv, G.dbv, R, Nkv, N, 1, 1.f}};
-    CF_HIP(launch_gemm_group(dt, last + dx_over_a, 8 - dx_over_a, st, lw.slots, nd));
+    CF_HIP(launch_gemm_group(dt, last + dx_over_a, 8 - dx_over_a, st, w.slots, nd));
     return CF_OK;
 }
 

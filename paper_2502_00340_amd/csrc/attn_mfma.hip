@@ -1140,27 +1140,37 @@ __global__ __launch_bounds__(256) void attn_reduce_kernel(AttnParams p, int kv_b
 // that the parameter-gradient GEMM of the output projection and the attention kernels' tile loads
 // use (the gathers of the two tensors folded into this read).  In the dQ kernel, whose lanes hold 32-byte pieces of a
 // row, the copies cost 35 us more where this pass takes 37 (4096 rows, 32 heads, d = 128).
-__global__ __launch_bounds__(256) void attn_stats_kernel(const bf16_t* __restrict__ do_kept,
+// parts: dO may lie there; the pass then leaves it in do_kept, rounded.
+template <int D>
+__global__ __launch_bounds__(256, 8) void attn_stats_kernel(bf16_t* do_kept,
                                                          const float* __restrict__ lse_full,
                                                          const int32_t* __restrict__ idx, int n_max,
                                                          const int32_t* __restrict__ n_dev,
-                                                         int Hq, int d, int S, float* __restrict__ stat,
+                                                         int Hq, int S, float* __restrict__ stat,
                                                          const bf16_t* __restrict__ o_full, bf16_t* __restrict__ o_out,
-                                                         const bf16_t* __restrict__ q_full, bf16_t* __restrict__ q_out) {
+                                                         const bf16_t* __restrict__ q_full, bf16_t* __restrict__ q_out,
+                                                         NtParts parts) {
     const int n_kept = live_rows(n_max, n_dev);
-    const int lanes = d / 8;
-    const int64_t total = (int64_t)n_kept * Hq * lanes;
-    const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    constexpr int lanes = D / 8;
+    const unsigned pair = (blockIdx.x * 256u + threadIdx.x) / lanes;    // (row, head); a matrix has less than 2^31 vectors
+    const bool live = pair < (unsigned)n_kept * (unsigned)Hq;
     float s = 0.f;
-    const int64_t pair = gid / lanes;
-    if (gid < total) {
-        const int part = (int)(gid % lanes);
+    const unsigned j = pair / (unsigned)Hq, h = pair % (unsigned)Hq;
+    int per;
+    const int np = parts.count(n_kept, per);
+    if (live) {
+        const int part = (int)(threadIdx.x % lanes) * 8;
+        const int64_t at = (int64_t)pair * D + part;
         float a[8], b[8];
-        Vec<bf16_t>::load(do_kept + pair * d + part * 8, a);
-        const int64_t src = ((int64_t)idx[pair / Hq] * Hq + pair % Hq) * d + part * 8;
+        if (__builtin_expect(np > 1, 0)) {
+            parts.load(n_kept, np, (int)j, (int)h * D + part, a);
+            Vec<bf16_t>::store(do_kept + at, a);
+        }
+        Vec<bf16_t>::load(do_kept + at, a);
+        const int64_t src = ((int64_t)idx[j] * Hq + h) * D + part;
         const uint4 ov = *reinterpret_cast<const uint4*>(o_full + src);
-        *reinterpret_cast<uint4*>(o_out + pair * d + part * 8) = ov;
-        *reinterpret_cast<uint4*>(q_out + pair * d + part * 8) = *reinterpret_cast<const uint4*>(q_full + src);
+        *reinterpret_cast<uint4*>(o_out + at) = ov;
+        *reinterpret_cast<uint4*>(q_out + at) = *reinterpret_cast<const uint4*>(q_full + src);
         const unsigned w[4] = {ov.x, ov.y, ov.z, ov.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -1170,12 +1180,11 @@ __global__ __launch_bounds__(256) void attn_stats_kernel(const bf16_t* __restric
 #pragma unroll
         for (int e = 0; e < 8; ++e) s += a[e] * b[e];
     }
+#pragma unroll
     for (int o = lanes >> 1; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (gid < total && (gid % lanes) == 0) {
-        const int j = (int)(pair / Hq), h = (int)(pair % Hq);
-        const int64_t tok = idx[j];
-        const int64_t bb = tok / S, pos = tok - bb * S;
-        stat[(int64_t)h * n_max + j] = lse_full[(bb * Hq + h) * S + pos] * LOG2E;
+    if (live && threadIdx.x % lanes == 0) {
+        const unsigned tok = (unsigned)idx[j], bb = tok / (unsigned)S, pos = tok - bb * (unsigned)S;
+        stat[(int64_t)h * n_max + j] = lse_full[((int64_t)bb * Hq + h) * S + pos] * LOG2E;
         stat[(int64_t)(Hq + h) * n_max + j] = s;
     }
 }
@@ -1208,7 +1217,7 @@ size_t attn_mfma_partial_bound(const cf_layer_desc& L, int n_kept) {
 
 template <int D, bool ROPE>
 static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16_t* o_out, const bf16_t* q_full, bf16_t* q_out,
-                           hipStream_t st) {
+                           const NtParts& do_parts, hipStream_t st) {
     constexpr int smem_dq = 2 * 2 * 64 * D * 2;
     constexpr int smem_dkv = 4 * (2 * 64 * D * 2 + 512);
     const int n_kept = p.n_kept;        // grids cover the upper bound of the row count
@@ -1231,8 +1240,9 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
     if (e != hipSuccess) return e;
     if (p.o_kept == nullptr) {
         const int64_t total = (int64_t)n_kept * p.Hq * (D / 8);
-        attn_stats_kernel<<<(int)((total + 255) / 256), 256, 0, st>>>(p.do_kept, p.lse_full, p.idx, n_kept, p.n_dev, p.Hq, D,
-                                                                     p.S, p.stat, o_full, o_out, q_full, q_out);
+        attn_stats_kernel<D><<<(int)((total + 255) / 256), 256, 0, st>>>(const_cast<bf16_t*>(p.do_kept), p.lse_full, p.idx, n_kept,
+                                                                     p.n_dev, p.Hq, p.S, p.stat, o_full, o_out, q_full, q_out,
+                                                                     do_parts);
     }
     attn_dq_kernel<D, ROPE><<<dim3(p.Hq * p.B, tiles, dq_cap), 256, smem_dq, st>>>(p);
     dkv<<<dim3(p.Hq * p.B * tiles), 256, smem_dkv, st>>>(p);
@@ -1244,13 +1254,14 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
 
 // o_full / q_full (null or both set, need idx): attention output and queries at full length; their kept
 // rows are then copied to o_kept / q_kept (which must be writable buffers) by the row-statistics pass.
-// rope_cos / rope_sin: null or the rotary tables, see AttnParams.
+// rope_cos / rope_sin: null or the rotary tables, see AttnParams.  do_parts: with o_full, dO may lie there, and do_kept is written.
 hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void* q_kept,
                                 const void* k_full, const void* v_full, const void* o_kept,
                                 const float* lse_full, const void* do_kept, float* stat,
                                 const int32_t* idx, const int32_t* cu_kept, RowCount rows, void* dq_kept,
                                 void* dk_kept, void* dv_kept, float* partials, hipStream_t st,
-                                const void* o_full, const void* q_full, const float* rope_cos, const float* rope_sin) {
+                                const void* o_full, const void* q_full, const float* rope_cos, const float* rope_sin,
+                                const NtParts& do_parts) {
     AttnParams p;
     const int n_kept = rows.n;
     p.q_kept = (const bf16_t*)q_kept; p.k_full = (const bf16_t*)k_full; p.v_full = (const bf16_t*)v_full;
@@ -1269,7 +1280,7 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     if ((o_full != nullptr) != (q_full != nullptr) || (o_full != nullptr && idx == nullptr)) return hipErrorInvalidValue;
     const auto launch = L.d == 64 ? (rope_cos ? launch_t<64, true> : launch_t<64, false>)
                                   : (rope_cos ? launch_t<128, true> : launch_t<128, false>);
-    return launch(p, dq_cap, (const bf16_t*)o_full, o_out, (const bf16_t*)q_full, q_out, st);
+    return launch(p, dq_cap, (const bf16_t*)o_full, o_out, (const bf16_t*)q_full, q_out, do_parts, st);
 }
 
 }  // namespace cf

@@ -126,34 +126,6 @@ hipError_t launch_keep_index_static(const uint8_t* mask, int B, int S, int32_t* 
 hipError_t launch_gather(const void* src, int64_t cols_bytes, const int32_t* idx, RowCount rows,
                          void* dst, hipStream_t st);
 
-// rowlocal.hip
-// act (nullable) also receives silu(gate)*up; d_gate may alias d_act.  copy_src (nullable, needs idx):
-// a full-length [.., copy_cols] tensor whose kept rows the same launch copies to copy_dst
-// [n_rows, copy_cols] (the compact upstream gradient that the parameter-gradient GEMM contracts over).
-hipError_t launch_swiglu_bwd(int dtype, const void* d_act, const void* gate, const void* up,
-                             const int32_t* idx, RowCount rows, int F, void* d_gate, void* d_up,
-                             void* act, hipStream_t st, const void* copy_src = nullptr, int copy_cols = 0,
-                             void* copy_dst = nullptr);
-// dx_out = res + rmsnorm_bwd(dh; x, g); dg_partial (nullable: the gains are frozen) receives the gain gradient's
-// [rmsnorm_bwd_blocks(n_rows), H] fp32 partials for launch_gain_grads.
-// h_out (nullable, [n_rows, H], may be dh): also receives the normalised rows rmsnorm(x)*g.
-int rmsnorm_bwd_blocks(int n_rows);
-hipError_t launch_rmsnorm_bwd(int dtype, const void* dh, const void* x, const void* g,
-                              const int32_t* idx, const void* res, RowCount rows, int H, float eps,
-                              void* dx_out, float* dg_partial, hipStream_t st, void* h_out = nullptr);
-// The gain gradients of both norms from their partials.  acc_f32: dg1 and dg2 are fp32 [H] and added to instead of written.
-hipError_t launch_gain_grads(int dtype, const float* partial1, const float* partial2, RowCount rows, int H, void* dg1, void* dg2,
-                             bool acc_f32, hipStream_t st);
-// fp32 gq [n_rows, hq*d] and gk [n_rows, hk*d], in place: transposed rotary rotation at position idx[j] % S
-// (idx null: j % S); cos, sin are [S, d/2] fp32
-hipError_t launch_rope_bwd_f32(void* gq, int hq, void* gk, int hk, const int32_t* idx, RowCount rows, int d, int S,
-                               const float* cos, const float* sin, hipStream_t st);
-// D[j,h] = sum_c da[j,h*d+c] * a[row,h*d+c], row = a_idx ? a_idx[j] : j; with a_idx the same launch also
-// writes the compact copies a_out[j,:] = a[row,:] and (q_src non-null) q_out[j,:] = q_src[row,:]
-hipError_t launch_attn_rowdot(int dtype, const void* da, const void* a, RowCount rows, int Hq, int d,
-                              float* D, hipStream_t st, const int32_t* a_idx = nullptr, void* a_out = nullptr,
-                              const void* q_src = nullptr, void* q_out = nullptr);
-hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 // gemm.hip
 struct GemmSeg {
     const void* A;
@@ -164,8 +136,56 @@ struct GemmSeg {
 // n_dev (nullable): the kept-token count on the device; then M is only an upper bound and the kernel uses
 // min(*n_dev, M) rows.  a_idx (nullable, segment 0): row m of A is row a_idx[m] of a longer
 // matrix (the gather of the upstream gradient folded into the A-tile loads); a_rows = rows of that matrix.
+// parts (nullable): where the product may be left in parts instead of in C.
+struct NtParts;
 hipError_t launch_gemm_nt(int dtype, const GemmSeg* segs, int nseg, void* C, int M, int N, hipStream_t st,
-                          const int32_t* n_dev = nullptr, const int32_t* a_idx = nullptr, int64_t a_rows = 0);
+                          const int32_t* n_dev = nullptr, const int32_t* a_idx = nullptr, int64_t a_rows = 0,
+                          const NtParts* parts = nullptr);
+
+// An NT product with few output tiles and a long contraction may leave its result in parts: fp32 [128,128] slots, tile by tile
+// (column of tiles by column), a tile's parts one after the other, for the kernel that reads the product to add up (or
+// launch_gemm_nt_sum).  A CU takes in the operands of a 128x128 tile at 0.35 us per 64 k whatever the others do, so that few
+// tiles are a long chain on few CUs.  A function of the live rows: launch and readers agree on it, and the result does not
+// depend on who knows the count.
+struct NtParts {
+    float* slots;       // null: never in parts
+    int N, pairs;       // columns; 64-wide steps of all segments
+    int n_cu;           // slots
+    int max_rows;       // more rows than this are one part: a kernel that is not concerned finds out with a compare
+    // Parts of a contraction for M rows, `per` steps each.  The items fit one round of the CUs, a part has eight steps or more (three
+    // microseconds; the ring's prologue is another two) and a reader sixteen parts at most; less than 16 steps saved do
+    // not pay for the fp32 slots.  [100, 4096], K = 28672: 268 -> 74 us (its reader 8 -> 15), [841, 512], K = 4096: 27.5 -> 12.0 (4.9 -> 6.2),
+    // [841, 1792], K = 4096, 98 tiles in two parts: 31.6 -> 22.7 (6.4 -> 7.6).
+    __host__ __device__ int count(int M, int& per) const {
+        per = pairs;
+        if (M <= 0 || M > max_rows) return 1;
+        const int tiles = ((M + 127) / 128) * ((N + 127) / 128);
+        int parts = n_cu / tiles;
+        if (parts > pairs / 8) parts = pairs / 8;
+        if (parts > 16) parts = 16;
+        if (parts < 2) return 1;
+        per = (pairs + parts - 1) / parts;
+        if (pairs - per < 16) { per = pairs; return 1; }
+        return (pairs + per - 1) / per;
+    }
+    // columns c .. c+VN-1 of row j of M
+    template <int VN>
+    __device__ __forceinline__ void load(int M, int parts, int j, int c, float (&o)[VN]) const {
+        const float* p = slots + (int64_t)((c >> 7) * ((M + 127) >> 7) + (j >> 7)) * parts * (128 * 128) + (j & 127) * 128 + (c & 127);
+#pragma unroll
+        for (int e = 0; e < VN; ++e) o[e] = 0.f;
+#pragma unroll 4
+        for (int k = 0; k < parts; ++k, p += 128 * 128) {
+#pragma unroll
+            for (int q = 0; q < VN / 4; ++q) {
+                const float4 a = reinterpret_cast<const float4*>(p)[q];
+                o[4 * q] += a.x; o[4 * q + 1] += a.y; o[4 * q + 2] += a.z; o[4 * q + 3] += a.w;
+            }
+        }
+    }
+};
+NtParts gemm_nt_parts(int dtype, const GemmSeg* segs, int nseg, int N, float* slots);
+hipError_t launch_gemm_nt_sum(const NtParts& parts, int M, void* C, hipStream_t st);    // M: the live rows, known to the host
 
 // One launch for up to TN_MAX products over the same K rows: C_j [M,N] = beta*C_j + A_j [K,M]^T * B_j [K,N].  c_f32 (bf16
 // dtype, beta = 1): the C_j are fp32 (main-gradient buffers) and the accumulators are added to them without rounding to
@@ -196,6 +216,36 @@ size_t gemm_group_slot_bytes();
 hipError_t launch_gemm_group(int dtype, const GemmGroupProb* probs, int np, hipStream_t st, float* slots = nullptr,
                              const int32_t* n_dev = nullptr);
 
+// rowlocal.hip
+// act (nullable) also receives silu(gate)*up; d_gate may alias d_act.  parts: d_act may lie there; it is then summed
+// up into d_act first.  copy_src (nullable, needs idx):
+// a full-length [.., copy_cols] tensor whose kept rows the same launch copies to copy_dst
+// [n_rows, copy_cols] (the compact upstream gradient that the parameter-gradient GEMM contracts over).
+hipError_t launch_swiglu_bwd(int dtype, void* d_act, const void* gate, const void* up,
+                             const int32_t* idx, RowCount rows, int F, void* d_gate, void* d_up,
+                             void* act, hipStream_t st, const NtParts& parts, const void* copy_src = nullptr, int copy_cols = 0,
+                             void* copy_dst = nullptr);
+// dx_out = res + rmsnorm_bwd(dh; x, g); dg_partial (nullable: the gains are frozen) receives the gain gradient's
+// [rmsnorm_bwd_blocks(n_rows), H] fp32 partials for launch_gain_grads.
+// h_out (nullable, [n_rows, H], may be dh): also receives the normalised rows rmsnorm(x)*g.  parts: dh may lie
+// there; it is then summed up into dh first.
+int rmsnorm_bwd_blocks(int n_rows);
+hipError_t launch_rmsnorm_bwd(int dtype, void* dh, const void* x, const void* g,
+                              const int32_t* idx, const void* res, RowCount rows, int H, float eps,
+                              void* dx_out, float* dg_partial, hipStream_t st, const NtParts& parts, void* h_out = nullptr);
+// The gain gradients of both norms from their partials.  acc_f32: dg1 and dg2 are fp32 [H] and added to instead of written.
+hipError_t launch_gain_grads(int dtype, const float* partial1, const float* partial2, RowCount rows, int H, void* dg1, void* dg2,
+                             bool acc_f32, hipStream_t st);
+// fp32 gq [n_rows, hq*d] and gk [n_rows, hk*d], in place: transposed rotary rotation at position idx[j] % S
+// (idx null: j % S); cos, sin are [S, d/2] fp32
+hipError_t launch_rope_bwd_f32(void* gq, int hq, void* gk, int hk, const int32_t* idx, RowCount rows, int d, int S,
+                               const float* cos, const float* sin, hipStream_t st);
+// D[j,h] = sum_c da[j,h*d+c] * a[row,h*d+c], row = a_idx ? a_idx[j] : j; with a_idx the same launch also
+// writes the compact copies a_out[j,:] = a[row,:] and (q_src non-null) q_out[j,:] = q_src[row,:]
+hipError_t launch_attn_rowdot(int dtype, const void* da, const void* a, RowCount rows, int Hq, int d,
+                              float* D, hipStream_t st, const int32_t* a_idx = nullptr, void* a_out = nullptr,
+                              const void* q_src = nullptr, void* q_out = nullptr);
+hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 // CUs of the current device (cached per device ordinal; 256 if the query fails)
 inline int compute_units() {
     static std::atomic<int> cache[64];

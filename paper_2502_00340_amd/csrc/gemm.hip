@@ -99,6 +99,7 @@ struct GemmArgs {
     // gather of the upstream gradient's kept rows, folded into the A-tile loads).
     const int32_t* a_idx;
     int64_t a_rows;
+    NtParts parts;  // mode NT: the contraction cut into parts where the output has few tiles
 };
 
 // Mode TN: up to TN_MAX products C_j [M_j,N_j] = A_j^T * B_j over the same K rows (A, B, C, M and N above are unused).  Their
@@ -213,14 +214,14 @@ struct TileRef {
 // The block's output tiles of (64*TM) x (64*TN), one after the other: `first`, then whatever
 // next_tile(TileRef&) hands out until it returns false.  The loads of the next
 // tile's first K-steps are in flight while the finished tile leaves through a staging area of its
-// own, and its stores drain under the next tile's MFMAs.  SPLIT: the block contracts only k in
-// [kbeg, kend) of the single segment and stores its fp32 accumulators, unscaled, to `part_out`
-// ([BM, BN] fp32); a second kernel adds the parts up.
+// own, and its stores drain under the next tile's MFMAs.  SPLIT: the block contracts only the pairs of K-steps
+// [pbeg, pend) of the segments' sequence and stores its fp32 accumulators, unscaled, to `part_out`
+// ([BM, BN] fp32, the rows below M); whoever needs the product adds the parts up.
 // K0x: the live value of g.K[0] (it differs from the launch argument when the kept-token count is read on the device).
 template <int MODE, int TM, int TN, bool SPLIT, bool CF32, typename Next>
 __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int K0x, const TileRef first,
                                            Next next_tile, unsigned char* smem,
-                                           const int kbeg = 0, const int kend = 0, float* part_out = nullptr) {
+                                           const int pbeg = 0, const int pend = 0, float* part_out = nullptr) {
     // Ring of operand stages: four of 32 KB, i.e. two pairs of K-steps, or for the 128x128 tile eight of 16 KB = four
     // pairs.  A pair of the small tile is 32 MFMAs (0.22 us) per wave, and with one pair of lookahead a block waited
     // out most of a load's latency per pair; three pairs of lookahead cover it.
@@ -341,7 +342,12 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int K0x, con
         else { kb0 = (unsigned)k0 * ldB; kb1 = (unsigned)(k0 + KB) * ldB; }
     };
     // A pair of K-steps never straddles a segment boundary: the part of a segment's last pair past Kseg is zeros.
+    int left = SPLIT ? pend - pbeg : 0;         // pairs of the part whose loads are not all out yet
     auto advance_pair = [&]() __attribute__((always_inline)) {
+        if (SPLIT && --left <= 0) {             // nothing of the part is left: the loads behind it are out of range
+            Kseg = 0;
+            return;
+        }
         k0 += 2 * KB;
         if (k0 >= Kseg) {
             k0 = 0;
@@ -512,18 +518,22 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int K0x, con
     };
 
     // pairs of K-steps; the last one of a segment may be a part of one
-    int npairs = SPLIT ? (kend - kbeg + 2 * KB - 1) / (2 * KB) : (K0x + 2 * KB - 1) / (2 * KB);
+    int npairs = SPLIT ? pend - pbeg : (K0x + 2 * KB - 1) / (2 * KB);
     if (!SPLIT)
         for (int s = 1; s < g.nseg; ++s) npairs += (g.K[s] + 2 * KB - 1) / (2 * KB);
     // prologue of tile ld: the first NPR - 1 pairs and the first group of the loads of the pair behind them
     auto start_tile = [&]() __attribute__((always_inline)) {
         seg = 0;
         k0 = 0;
-        open_segment(0);
-        if (SPLIT) {                    // the block's K range stands for the segment
-            k0 = kbeg;
-            Kseg = kend;
+        if (SPLIT) {                    // the part's first pair
+            int p = pbeg;
+            for (int n = (K0x + 2 * KB - 1) / (2 * KB); seg + 1 < g.nseg && p >= n; n = (g.K[seg] + 2 * KB - 1) / (2 * KB)) {
+                p -= n;
+                ++seg;
+            }
+            k0 = p * 2 * KB;
         }
+        open_segment(seg);
         static_for<NPR - 1>([&](auto P) __attribute__((always_inline)) {
             constexpr int p = decltype(P)::value;
             issue_pair(ic<p>{}, ic<0>{});
@@ -586,16 +596,20 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int K0x, con
         const int m0 = ep.m0, n0 = ep.n0, Mx = ep.M;
 
     if (SPLIT) {
-        // ---- split-K epilogue: the whole tile's fp32 accumulators, unscaled, straight to the item's own slot (rows and
-        // columns past the matrix are zeros in it)
+        // ---- split-K epilogue: the tile's fp32 accumulators, unscaled, straight to the item's own slot (columns past the
+        // matrix are zeros in it, rows past it are not written)
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+        for (int i = 0; i < FM; ++i) {
+            const int r = wm * (32 * TM) + i * 16 + l16;
+            if (m0 + r < Mx) {
 #pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                float4 o;
-                o.x = acc[i][j][0]; o.y = acc[i][j][1]; o.z = acc[i][j][2]; o.w = acc[i][j][3];
-                *reinterpret_cast<float4*>(part_out + (wm * (32 * TM) + i * 16 + l16) * BN + wn * (32 * TN) + j * 16 + 4 * g4) = o;
+                for (int j = 0; j < FN; ++j) {
+                    float4 o;
+                    o.x = acc[i][j][0]; o.y = acc[i][j][1]; o.z = acc[i][j][2]; o.w = acc[i][j][3];
+                    *reinterpret_cast<float4*>(part_out + r * BN + wn * (32 * TN) + j * 16 + 4 * g4) = o;
+                }
             }
+        }
         break;
     }
     const float alpha = g.alpha;
@@ -791,8 +805,25 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs g) {
         sub = __builtin_amdgcn_readfirstlane(sub);
         tile_n = __builtin_amdgcn_readfirstlane(tile_n);
     }
-    const int tiles_m = (Mx + 255) / 256, tiles_n = (g.N + 255) / 256;
     const TileRef whole{0, 0, Mx, g.N, g.A[0], g.B[0], g.C};
+    int per = 0;
+    const int parts = g.parts.count(Mx, per);
+    if (__builtin_expect(parts > 1, 0)) {
+        // An item is a part of a 128x128 tile.  The items of one part come together, column of tiles by column: an XCD's share
+        // of them reads the same rows of A and B.
+        const int tm = (Mx + 127) / 128, tiles = tm * ((g.N + 127) / 128), items = tiles * parts;
+        if ((int)blockIdx.x >= items) return;
+        const int w = xcd_order((int)blockIdx.x, items);
+        const int part = __builtin_amdgcn_readfirstlane(w / tiles), tile = __builtin_amdgcn_readfirstlane(w % tiles);
+        TileRef t = whole;
+        t.m0 = __builtin_amdgcn_readfirstlane((tile % tm) * 128);
+        t.n0 = __builtin_amdgcn_readfirstlane((tile / tm) * 128);
+        per = __builtin_amdgcn_readfirstlane(per);
+        gemm_tiles<0, 2, 2, true, false>(g, g.K[0], t, [](TileRef&) { return false; }, smem, part * per,
+                                         min(g.parts.pairs, part * per + per), g.parts.slots + ((int64_t)tile * parts + part) * (128 * 128));
+        return;
+    }
+    const int tiles_m = (Mx + 255) / 256, tiles_n = (g.N + 255) / 256;
     if (tile_n == 192) {
         // tiles of 256x192, all of one kind: block b takes tiles b, b + gridDim.x, ...
         const int tiles_n192 = (g.N + 191) / 192, n_items = tiles_m * tiles_n192;
@@ -952,8 +983,8 @@ __device__ __forceinline__ void group_tile(const GroupArgs& ga, const GroupItem&
     const TileRef t{it.m0, it.n0, it.M, p.N, g.A[0], g.B[0], g.C};
     auto none = [](TileRef&) { return false; };
     if (it.parts > 1) {
-        const int c = group_step(plan) * 64, kbeg = it.part * c, kend = min(it.K, kbeg + c);
-        gemm_tiles<MODE, 2, 2, true, false>(g, it.K, t, none, smem, kbeg, kend, ga.slots + (int64_t)w * (128 * 128));
+        const int c = group_step(plan), pbeg = it.part * c, pend = min((it.K + 63) >> 6, pbeg + c);
+        gemm_tiles<MODE, 2, 2, true, false>(g, it.K, t, none, smem, pbeg, pend, ga.slots + (int64_t)w * (128 * 128));
     } else {
         gemm_tiles<MODE, 2, 2, false, false>(g, it.K, t, none, smem);
     }
@@ -1090,8 +1121,44 @@ static bool offsets_fit(int64_t M, int64_t N, int64_t K) {
     return M * K * 2 < lim && N * K * 2 < lim && (M + 256) * N * 2 < lim;
 }
 
+// C = the sum of the parts of a product that was cut into some
+__global__ __launch_bounds__(256) void gemm_nt_sum_kernel(NtParts pt, int M, bf16_t* __restrict__ C) {
+    int per;
+    const int parts = pt.count(M, per), vpr = pt.N / 8;
+    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (v >= (int64_t)M * vpr) return;
+    const int j = (int)(v / vpr), c = (int)(v % vpr) * 8;
+    float o[8];
+    pt.load(M, parts, j, c, o);
+    Vec<bf16_t>::store(C + (int64_t)j * pt.N + c, o);
+}
+
+hipError_t launch_gemm_nt_sum(const NtParts& parts, int M, void* C, hipStream_t st) {
+    int per;
+    if (M <= 0 || parts.count(M, per) == 1) return hipSuccess;
+    gemm_nt_sum_kernel<<<ceil_div((int64_t)M * parts.N, 256 * 8), 256, 0, st>>>(parts, M, (bf16_t*)C);
+    return hipGetLastError();
+}
+
+NtParts gemm_nt_parts(int dtype, const GemmSeg* segs, int nseg, int N, float* slots) {
+    NtParts p{slots, N, 0, compute_units(), 0};
+    if (dtype != CF_BF16 || slots == nullptr) return p;
+    for (int s = 0; s < nseg; ++s) p.pairs += ceil_div(segs[s].K, 64);
+    // the more tiles, the fewer parts: the last number of tile rows with more than one
+    const int tn = ceil_div(N, 128);
+    int per;
+    for (int tm = 1; 2 * tm * tn <= p.n_cu; ++tm) {
+        p.max_rows = tm * 128;
+        if (p.count(tm * 128, per) == 1) {
+            p.max_rows = (tm - 1) * 128;
+            break;
+        }
+    }
+    return p;
+}
+
 hipError_t launch_gemm_nt(int dtype, const GemmSeg* segs, int nseg, void* C, int M, int N, hipStream_t st, const int32_t* n_dev,
-                          const int32_t* a_idx, int64_t a_rows) {
+                          const int32_t* a_idx, int64_t a_rows, const NtParts* parts) {
     if (M <= 0 || N <= 0) return hipSuccess;
     if (a_idx != nullptr && a_rows <= 0) return hipErrorInvalidValue;
     if (nseg > MAX_SEG) return hipErrorInvalidValue;
@@ -1114,7 +1181,10 @@ hipError_t launch_gemm_nt(int dtype, const GemmSeg* segs, int nseg, void* C, int
     static std::atomic<uint64_t> lds_ok{0};
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_nt_kernel), GEMM_SMEM, lds_ok);
     if (e != hipSuccess) return e;
-    const int items = plan_launch(M, N, compute_units(), g.n_full, g.sub, g.tile_n);
+    if (parts != nullptr) g.parts = *parts;
+    int per, items = plan_launch(M, N, compute_units(), g.n_full, g.sub, g.tile_n);
+    const int np = g.parts.count(M, per);
+    if (np > 1) items = ceil_div(M, 128) * ceil_div(N, 128) * np;
     // a block walks through its items; with a device-side count the blocks plan for themselves (for
     // as many blocks as CUs) and those without an item leave at once
     const int grid = n_dev != nullptr ? compute_units() : std::min(items, compute_units());

@@ -3,6 +3,8 @@
 // optional kept-row index for tensors that are still stored full length, so
 // the gather of those tensors is folded into the read.  Arithmetic is fp32;
 // storage is fp32 or bf16.  All of them are HBM-bound streaming kernels.
+#include <type_traits>
+
 #include "common.h"
 
 namespace cf {
@@ -17,29 +19,45 @@ __device__ __forceinline__ float sigmoidf_(float z) { return 1.0f / (1.0f + __ex
 // upstream gradient, which the down projection's parameter-gradient GEMM contracts over; folding the
 // copy in here saves the launch of a gather kernel.
 template <typename T>
-__global__ __launch_bounds__(256) void swiglu_bwd_kernel(const T* d_act,
+__global__ __launch_bounds__(256) void swiglu_bwd_kernel(T* d_act,
                                                          const T* __restrict__ gate,
                                                          const T* __restrict__ up,
                                                          const int32_t* __restrict__ idx,
                                                          int n_max, const int32_t* __restrict__ n_dev, int F, T* d_gate,
                                                          T* __restrict__ d_up, T* __restrict__ act,
                                                          const T* __restrict__ copy_src, int copy_cols,
-                                                         T* __restrict__ copy_dst) {
+                                                         T* __restrict__ copy_dst, NtParts parts) {
     constexpr int VN = Vec<T>::N;
+    // vectors are counted in 32 bits where every matrix is below 2 GiB (the bf16 layers); a 64-bit division per vector
+    // is a tenth of the pass
+    typedef typename std::conditional<VN == 8, unsigned, uint64_t>::type Count;
     const int n_rows = live_rows(n_max, n_dev);
     if (copy_src != nullptr) {
-        const int cvpr = copy_cols / VN;
-        const int64_t ctotal = (int64_t)n_rows * cvpr;
-        for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < ctotal; v += (int64_t)gridDim.x * 256) {
+        const Count cvpr = copy_cols / VN;
+        const Count ctotal = (Count)n_rows * cvpr;
+        for (Count v = (Count)blockIdx.x * 256 + threadIdx.x; v < ctotal; v += gridDim.x * 256) {
             const int j = (int)(v / cvpr);
             const int c = (int)(v % cvpr) * VN;
             *reinterpret_cast<uint4*>(copy_dst + (int64_t)j * copy_cols + c) =
                 *reinterpret_cast<const uint4*>(copy_src + (int64_t)idx[j] * copy_cols + c);
         }
     }
-    const int vpr = F / VN;
-    const int64_t total = (int64_t)n_rows * vpr;
-    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < total; v += (int64_t)gridDim.x * 256) {
+    const Count vpr = F / VN;
+    const Count total = (Count)n_rows * vpr;
+    // In parts: every thread first sums up what it is going to read.  (A second loop with the sum in the load's place, let
+    // alone a branch there, costs the calls without parts a microsecond or two a pass.)
+    if constexpr (VN == 8) {
+        int per;
+        const int np = parts.count(n_rows, per);
+        if (__builtin_expect(np > 1, 0))
+            for (Count v = (Count)blockIdx.x * 256 + threadIdx.x; v < total; v += gridDim.x * 256) {
+                const int j = (int)(v / vpr), c = (int)(v % vpr) * VN;
+                float da[VN];
+                parts.load(n_rows, np, j, c, da);
+                Vec<T>::store(d_act + (int64_t)j * F + c, da);
+            }
+    }
+    for (Count v = (Count)blockIdx.x * 256 + threadIdx.x; v < total; v += gridDim.x * 256) {
         const int j = (int)(v / vpr);
         const int c = (int)(v % vpr) * VN;
         const int64_t row = idx ? idx[j] : j;
@@ -76,14 +94,14 @@ __host__ __device__ inline int rmsnorm_bwd_nblk(int n_rows) {
 }
 
 template <typename T, int NV>
-__global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* dh,
+__global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(T* dh,
                                                           const T* __restrict__ x,
                                                           const T* __restrict__ g,
                                                           const int32_t* __restrict__ idx,
                                                           const T* __restrict__ res, int n_max,
                                                           const int32_t* __restrict__ n_dev,
                                                           int H, float eps, T* __restrict__ dx_out,
-                                                          float* __restrict__ dg_partial, T* h_out) {
+                                                          float* __restrict__ dg_partial, T* h_out, NtParts parts) {
     constexpr int VN = Vec<T>::N;
     __shared__ float red[16];
     const int n_rows = live_rows(n_max, n_dev);
@@ -99,6 +117,18 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* dh,
         if (v < vpr) Vec<T>::load(g + v * VN, gv[i]);
     }
     const int wave = threadIdx.x >> 6;
+    if constexpr (VN == 8) {        // in parts: as in the SwiGLU pass
+        int per;
+        const int np = parts.count(n_rows, per);
+        if (__builtin_expect(np > 1, 0))
+            for (int j0 = blockIdx.x * 2; j0 < n_rows; j0 += nblk * 2)
+                for (int j = j0; j < min(j0 + 2, n_rows); ++j)
+                    for (int v = threadIdx.x; v < vpr; v += 256) {
+                        float o[VN];
+                        parts.load(n_rows, np, j, v * VN, o);
+                        Vec<T>::store(dh + (int64_t)j * H + v * VN, o);
+                    }
+    }
     for (int j0 = blockIdx.x * 2; j0 < n_rows; j0 += nblk * 2) {
         float xv[2][NV][VN], dv[2][NV][VN], rv[2][NV][VN];
         float ss[2] = {0.f, 0.f}, sd[2] = {0.f, 0.f};
@@ -295,20 +325,20 @@ static int stream_grid(int64_t vec_total) {
     return (int)g;
 }
 
-hipError_t launch_swiglu_bwd(int dtype, const void* d_act, const void* gate, const void* up,
+hipError_t launch_swiglu_bwd(int dtype, void* d_act, const void* gate, const void* up,
                              const int32_t* idx, RowCount rows, int F, void* d_gate, void* d_up,
-                             void* act, hipStream_t st, const void* copy_src, int copy_cols, void* copy_dst) {
+                             void* act, hipStream_t st, const NtParts& parts, const void* copy_src, int copy_cols, void* copy_dst) {
     const int n_rows = rows.n;
     if (n_rows <= 0) return hipSuccess;
     if (copy_src != nullptr && idx == nullptr) return hipErrorInvalidValue;
     if (dtype == CF_F32)
         swiglu_bwd_kernel<float><<<stream_grid((int64_t)n_rows * F / 4), 256, 0, st>>>(
-            (const float*)d_act, (const float*)gate, (const float*)up, idx, n_rows, rows.dev, F,
-            (float*)d_gate, (float*)d_up, (float*)act, (const float*)copy_src, copy_cols, (float*)copy_dst);
+            (float*)d_act, (const float*)gate, (const float*)up, idx, n_rows, rows.dev, F,
+            (float*)d_gate, (float*)d_up, (float*)act, (const float*)copy_src, copy_cols, (float*)copy_dst, parts);
     else
         swiglu_bwd_kernel<bf16_t><<<stream_grid((int64_t)n_rows * F / 8), 256, 0, st>>>(
-            (const bf16_t*)d_act, (const bf16_t*)gate, (const bf16_t*)up, idx, n_rows, rows.dev, F,
-            (bf16_t*)d_gate, (bf16_t*)d_up, (bf16_t*)act, (const bf16_t*)copy_src, copy_cols, (bf16_t*)copy_dst);
+            (bf16_t*)d_act, (const bf16_t*)gate, (const bf16_t*)up, idx, n_rows, rows.dev, F,
+            (bf16_t*)d_gate, (bf16_t*)d_up, (bf16_t*)act, (const bf16_t*)copy_src, copy_cols, (bf16_t*)copy_dst, parts);
     return hipGetLastError();
 }
 
@@ -317,12 +347,12 @@ int rmsnorm_bwd_blocks(int n_rows) {
 }
 
 template <typename T>
-static void rmsnorm_bwd_dispatch(int nv, int nblk, hipStream_t st, const void* dh, const void* x, const void* g,
+static void rmsnorm_bwd_dispatch(int nv, int nblk, hipStream_t st, void* dh, const void* x, const void* g,
                                  const int32_t* idx, const void* res, RowCount rows, int H, float eps,
-                                 void* dx_out, float* dg_partial, void* h_out) {
+                                 void* dx_out, float* dg_partial, void* h_out, const NtParts& parts) {
 #define CF_RMS_BWD(NV)                                                                               \
-    rmsnorm_bwd_kernel<T, NV><<<nblk, 256, 0, st>>>((const T*)dh, (const T*)x, (const T*)g, idx,      \
-                                                    (const T*)res, rows.n, rows.dev, H, eps, (T*)dx_out, dg_partial, (T*)h_out)
+    rmsnorm_bwd_kernel<T, NV><<<nblk, 256, 0, st>>>((T*)dh, (const T*)x, (const T*)g, idx,      \
+                                                    (const T*)res, rows.n, rows.dev, H, eps, (T*)dx_out, dg_partial, (T*)h_out, parts)
     if (nv <= 1) CF_RMS_BWD(1);
     else if (nv <= 2) CF_RMS_BWD(2);
     else if (nv <= 4) CF_RMS_BWD(4);
@@ -330,16 +360,16 @@ static void rmsnorm_bwd_dispatch(int nv, int nblk, hipStream_t st, const void* d
 #undef CF_RMS_BWD
 }
 
-hipError_t launch_rmsnorm_bwd(int dtype, const void* dh, const void* x, const void* g,
+hipError_t launch_rmsnorm_bwd(int dtype, void* dh, const void* x, const void* g,
                               const int32_t* idx, const void* res, RowCount rows, int H, float eps,
-                              void* dx_out, float* dg_partial, hipStream_t st, void* h_out) {
+                              void* dx_out, float* dg_partial, hipStream_t st, const NtParts& parts, void* h_out) {
     const int n_rows = rows.n;
     if (n_rows <= 0) return hipSuccess;
     const int nblk = rmsnorm_bwd_blocks(n_rows);
     const int vn = dtype == CF_F32 ? 4 : 8;
     const int nv = ceil_div(H / vn, 256);           // 16-byte vectors per thread (at most 8, checked by the API)
-    if (dtype == CF_F32) rmsnorm_bwd_dispatch<float>(nv, nblk, st, dh, x, g, idx, res, rows, H, eps, dx_out, dg_partial, h_out);
-    else rmsnorm_bwd_dispatch<bf16_t>(nv, nblk, st, dh, x, g, idx, res, rows, H, eps, dx_out, dg_partial, h_out);
+    if (dtype == CF_F32) rmsnorm_bwd_dispatch<float>(nv, nblk, st, dh, x, g, idx, res, rows, H, eps, dx_out, dg_partial, h_out, parts);
+    else rmsnorm_bwd_dispatch<bf16_t>(nv, nblk, st, dh, x, g, idx, res, rows, H, eps, dx_out, dg_partial, h_out, parts);
     return hipGetLastError();
 }
 

@@ -1016,3 +1016,38 @@ def test_layer_dense_dx_over_attn_out():
             torch.cuda.synchronize()
             for k in ref.grads:
                 assert torch.equal(s2["attn_out"] if k == "dx" else over.grads[k], ref.grads[k]), k
+
+
+PARTS_SHAPE = dict(B=2, H=2048, Hq=16, Hkv=4, d=64, F=4104)
+
+
+@pytest.mark.parametrize("S,rho", [(45, 0.7), (129, 0.6), (250, 0.9)])
+def test_layer_products_in_parts(S, rho):
+    """A few rows against long contractions: d_act, dh2, da and dh1 are left in up to sixteen fp32 parts that the next pass adds up.
+    62 (one tile row), 154 and 450 rows; a contraction that ends inside a step (F = 4104), a part that spans two segments.  The
+    parts follow the live count: the default bound, the tight one and a host count give the same bits."""
+    shape = WL.LayerShape("parts", S=S, dtype="bf16", **PARTS_SHAPE)
+    say("layer in parts S=%d" % S)
+    p = Hn.Problem(shape, S, "independent", rho=rho, rope=True, oracle_dtype=np.float32)
+    sv, W, dy, mask = p.device_tensors(DEV)
+    ridx = np.flatnonzero(p.mask.reshape(-1))
+    n = len(ridx)
+    full = Bn.LayerBackward(p.desc(), device=DEV)
+    assert full.filtered(sv, W, dy, mask) == n
+    errs = Hn.check_layer(p, dict(full.grads, dx=full.grads["dx"][:n]), p.oracle(), ridx, Hn.TOL["bf16"])
+    say("  " + " ".join("%s=%.1e" % kv for kv in errs.items()))
+    tight, host = Bn.LayerBackward(p.desc(), device=DEV, max_kept=n), Bn.LayerBackward(p.desc(), device=DEV)
+    tight.filtered(sv, W, dy, mask)
+    host.compact(sv, W, Bn.gather_rows(dy, full.idx, n), full.idx, full.cu_kept, n)
+    torch.cuda.synchronize()
+    for other in (tight, host):
+        for k in full.grads:
+            assert torch.equal(full.grads[k][:n] if k == "dx" else full.grads[k], other.grads[k][:n] if k == "dx" else other.grads[k]), k
+    gotd, _, _ = _run_layer(p, dense=True)
+    Hn.check_layer(p, gotd, p.oracle(dense=True), None, Hn.TOL["bf16"])
+
+
+def test_layer_lora_products_in_parts():
+    """The same products of an adapter call (five and six segments with the rank-16 ones), filtered and dense."""
+    LORA_SHAPES["parts"] = dict(S=129, **PARTS_SHAPE)
+    test_layer_lora("bf16", "independent", 16, "parts")
