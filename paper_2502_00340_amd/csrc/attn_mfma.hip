@@ -61,6 +61,7 @@ struct AttnParams {
     // 128-row tiles with which k + 2 ranges or more are taken.  One word next to the sizes: with the rule itself
     // evaluated here instead a call took 1.1 us more (of 16 at S = 384).
     uint64_t dq_limits;
+    int dq_fine_rows;              // up to this many live rows the dQ blocks take tiles of 64 queries (see attn_dq_kernel)
     int n_slots;                   // dK/dV blocks that the device holds at a time (the kernel sizes its blocks' work by it)
     int B, S, Hq, Hkv;
     // Nullable, both or none: rotary tables [S][d/2].  dQ and dK leave rotated back to before the rotary embedding, at the original
@@ -94,29 +95,38 @@ __host__ __device__ inline int attn_heads_per_block(int n_rows, int Hq, int G, i
     return 1;
 }
 
+// Live rows up to which the dQ blocks take tiles of 64 queries, with the keys of a tile shared out inside the block: up to one
+// 128-query tile per CU (d = 128) or one and a half (d = 64).  A lone block's step is a chain of LDS reads, MFMAs, exponentials and
+// a barrier, 1.3 us at d = 64 where its MFMAs take 0.35: half the step and twice the blocks, which fill the CUs more evenly,
+// for twice the K/V loads.  Whole attention call on coarse and fine tiles, over 1088 calls of 4 to 64 heads: 128-255 tiles 1.14 times as
+// fast (d = 64) and 1.11 (d = 128), 256-383 tiles 1.12 and 1.06 (0.87 to 1.28), 384-511 tiles 1.03 and 0.95, more tiles
+// 0.83-0.99.  [1377 rows, 32/4 heads, d = 64, S = 1531]: dQ 36 -> 30 us (a third stage of the K/V ring: 32).
+static int attn_dq_fine_rows(const cf_layer_desc& L) {
+    const int n_cu = compute_units();
+    return (L.d == 64 ? n_cu * 3 / 2 : n_cu) / L.Hq * 128;
+}
+
 // Key ranges per query tile of the dQ kernel.  Where a batch of few heads (a tensor-parallel share) has few query tiles, each
 // of them is a serial chain on a CU of its own: several blocks per tile, one per range of keys, shorten it, at the price of
-// fp32 partials and their sum: [2662 of 7479 rows, 4/1 heads, d = 128] 184 -> 75 us on 84 tiles, [841 of 2103 rows]
-// 23 -> 12 us on 28.
-// The most ranges that a batch shape may take, which grid and workspace are sized for: at least 192 keys in a range, about
+// fp32 partials and their sum: [2662 of 7479 rows, 4/1 heads, d = 128] 184 -> 75 us on 84 tiles.
+// The most ranges that a batch shape may take, which grid and workspace are sized for: at least 128 keys in a range, about
 // four blocks per CU; with more than one tile per CU at least 1536 keys; none above two.
 static int attn_dq_split(const cf_layer_desc& L) {
     const int64_t tiles = (int64_t)L.Hq * L.B * ceil_div(L.S, 128), n_cu = compute_units();
     if (tiles > 2 * n_cu) return 1;
     int64_t n = 4 * n_cu / tiles;
-    const int64_t longest = L.S / (tiles <= n_cu ? 192 : 1536);
+    const int64_t longest = L.S / (tiles <= n_cu ? 128 : 1536);
     if (n > longest) n = longest;
     return n < 1 ? 1 : (n > DQ_MAX_RANGES ? DQ_MAX_RANGES : (int)n);
 }
 
 // The ranges that a call takes of them.  What the partials cost goes with the live rows: 8 bytes per element and range,
-// written and read at about 3.5 TB/s, against the chain of S keys, 9.4 ns * d per 64 of them.  Without KV groups the split
+// written and read at about 3.5 TB/s, against the chain of S keys, 6.6 ns * d per 64 of them on fine tiles.  Without KV groups the split
 // also costs a launch that would not be there otherwise, about 1 us; with them that launch is there and gains 1 us by a dQ kernel
 // that ends sooner.  A gain below 1/64 of the chain is none.  (Decided from the batch shape alone, calls that keep
-// most of their tokens were split as far as sparse ones: 32/32 heads, d = 128, S = 1024, all kept, four ranges 88 us, none 69;
-// 307 of 1024 kept, 45 and 48.  Over 1152 calls of 4 to 64 heads, S = 260 to 16384, 0.1 to 1 kept, by this rule none is more
-// than 2 % slower than unsplit and the mean is 1.22 times as fast; by the shape 153 were slower, the worst by 24 %, the
-// mean 1.20.)
+// most of their tokens were split as far as sparse ones: 32/32 heads, d = 128, S = 1024, all kept, four ranges 88 us, none 69.
+// Over the 1088 calls above, fine tiles with these ranges against coarse ones with the ranges fitted to them: 1.09 times as fast, two
+// below 0.97: [408 rows in four sequences, 64/8, d = 128] 64 and 72 us.)
 // In units of 1/16 ns per column: k > 1 ranges gain A(k) - k * part, A(k) = chain - chain/k - launch, part = what
 // one range's partials cost; k = 1 counts as a gain of chain / 64.  The k of the largest gain, the smaller one of
 // equals, is k or more exactly if some j >= k gains more than every i < k, which is a limit on part and so on the rows.  These
@@ -126,7 +136,7 @@ static int attn_dq_plan(const cf_layer_desc& L, const RowCount& rows, uint64_t& 
     limits = 0;
     const int cap = attn_dq_split(L);
     if (cap == 1) return 1;                         // from here on S <= 64 K
-    const int chain = L.S * 75 / 32, launch = (L.Hq == L.Hkv ? 16000 : -16000) / L.d;
+    const int chain = L.S * 105 / 64, launch = (L.Hq == L.Hkv ? 16000 : -16000) / L.d;
     int A[DQ_MAX_RANGES + 1] = {0, chain / 64};
     for (int k = 2; k <= cap; ++k) A[k] = chain - chain / k - launch;
     auto put = [&](int k, uint64_t v) { limits |= std::min<uint64_t>(v, (1 << DQ_LIMIT_BITS) - 1) << (DQ_LIMIT_BITS * (k - 2)); };
@@ -251,16 +261,15 @@ __device__ __forceinline__ void store_rows_rotated(bf16_t* out, int64_t stride, 
 // ---------------------------------------------------------------------------
 // ROPE here and below: rope_cos and rope_sin are set.  (A template: as a branch behind the loop it cost calls without tables 6 % of
 // the dQ kernel's time, through the registers it takes.)
-template <int D, bool ROPE>
-__global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
-    constexpr int KS = D / 16, NT = D / 32;
+// FINE: tiles of 64 queries; the two waves of a group of 32 take the first and the second 32 keys of every key tile, and their sums
+// meet in LDS at the end (see attn_dq_fine_rows).
+template <int D, bool ROPE, bool FINE>
+__device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_t dq_limits, const int n_live, unsigned char* smem) {
+    constexpr int KS = D / 16, NT = D / 32, QT = FINE ? 64 : 128;
     constexpr int TILE = 64 * D * 2;            // one 64-token tile in bytes
     constexpr int NLD = D / 32;                 // wave-loads per wave per tile
-    extern __shared__ __align__(16) unsigned char smem[];   // [2 stages][K tile, V tile]
-
-    uint64_t dq_limits = p.dq_limits;
-    asm("" : "+s"(dq_limits));                  // fetched with the first arguments, not in a round trip of its own further down
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int wave = FINE ? wv & 1 : wv, kw = FINE ? __builtin_amdgcn_readfirstlane(wv >> 1) : 0;   // group of 32 queries; half of the key tiles
     const int slot = lane & 31, hh = lane >> 5;
     const int h = blockIdx.x % p.Hq, b = blockIdx.x / p.Hq, g = h / (p.Hq / p.Hkv);
     const int Nq = p.Hq * D, Nkv = p.Hkv * D;
@@ -269,12 +278,12 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
     const int cnt = seq_end - seq_begin;
     // heaviest (latest) query tiles of the sequence first; the grid is sized for an upper bound of the
     // row count, and the blocks past this sequence's tiles come last in the launch order
-    const int seq_tiles = (cnt + 127) / 128;
-    const int ranges = dq_ranges(dq_limits, live_rows(p.n_kept, p.n_dev));
+    const int seq_tiles = (cnt + QT - 1) / QT;
+    const int ranges = dq_ranges(dq_limits, n_live);
     if ((int)blockIdx.y >= seq_tiles || (int)blockIdx.z >= ranges) return;
     const int qt = seq_tiles - 1 - blockIdx.y;
-    const int j0 = seq_begin + qt * 128;
-    const int rows_in_tile = min(128, cnt - qt * 128);
+    const int j0 = seq_begin + qt * QT;
+    const int rows_in_tile = min(QT, cnt - qt * QT);
 
     // This lane's query: its fragments and its row terms.  D = rowsum(dO*O) is formed here, from the dO fragments that
     // the kernel holds anyway, unless a pass before had to read O for its compact copy (a pass of its own over dO and O
@@ -319,7 +328,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
             lse2 = p.lse_full[((int64_t)b * p.Hq + h) * p.S + pos] * LOG2E;
         }
         Dq += __shfl_xor(Dq, 32, 64);           // the other half of the row's columns
-        if (qvalid && hh == 0 && blockIdx.z == 0) {
+        if (qvalid && hh == 0 && blockIdx.z == 0 && kw == 0) {
             p.stat[(int64_t)h * p.n_kept + jq] = lse2;
             p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq] = Dq;
         }
@@ -362,12 +371,12 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
     constexpr int NCH = D / 8, RPL = 64 / NCH;
     unsigned voff0;
     {
-        const int row = wave * RPL + lane / NCH;
+        const int row = wv * RPL + lane / NCH;
         const int pc = lane % NCH;
         const int sw = (D == 128) ? (((row & 3) << 2) | ((row >> 2) & 3)) : ((((row >> 1) & 1) << 2) | ((row >> 2) & 3));
         voff0 = (unsigned)row * (unsigned)(Nkv * 2) + (unsigned)((pc ^ sw) << 4);
     }
-    const unsigned wave_lds = __builtin_amdgcn_readfirstlane(lds0 + (unsigned)wave * 1024u);   // scalar: the wave's 1 KB slot
+    const unsigned wave_lds = __builtin_amdgcn_readfirstlane(lds0 + (unsigned)wv * 1024u);   // scalar: the wave's 1 KB slot
     auto issue_kv = [&](int kt, int stage) __attribute__((always_inline)) {
         const unsigned sk = wave_lds + stage * 2 * TILE;
         const unsigned step = (unsigned)(4 * RPL) * (unsigned)(Nkv * 2);
@@ -382,7 +391,8 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
     // One 32-key half of the tile at a time keeps the score registers at 2 x 16.  The LDS fragments of an
     // MFMA are read while the previous MFMAs run (one step ahead).  (Fragment addresses are rebuilt per
     // read: with two waves per SIMD the register file has no room to keep them at d = 128.)
-    auto tile = [&](auto MASKED_, const int kt, const unsigned char* sk) __attribute__((always_inline)) {
+    // key0: the first of the wave's keys in the tile, whose K rows begin at sk.
+    auto tile = [&](auto MASKED_, const int key0, const unsigned char* sk) __attribute__((always_inline)) {
         constexpr bool masked = decltype(MASKED_)::value != 0;
         const unsigned char* sv = sk + TILE;
         bf16x8_t fa[2][2], fc[2];
@@ -395,7 +405,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
         };
         load_a(0, 0, 0);
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
+        for (int mt = 0; mt < (FINE ? 1 : 2); ++mt) {
             f32x16_t st, dpt;
 #pragma unroll
             for (int v = 0; v < 16; ++v) { st[v] = 0.f; dpt[v] = 0.f; }
@@ -413,7 +423,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
             for (int v = 0; v < 16; ++v) {
                 float pr = __builtin_amdgcn_exp2f(st[v] * scale2 - lse2);
                 if (masked) {
-                    const int key = kt * 64 + mt * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
+                    const int key = key0 + mt * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
                     pr = key <= pos ? pr : 0.f;
                 }
                 st[v] = pr * (dpt[v] - Dq);
@@ -422,7 +432,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
 #pragma unroll
             for (int c = 0; c < 2 * NT; ++c) {
                 if (c + 1 < 2 * NT) load_c(mt, c + 1, (c + 1) & 1);
-                else if (mt == 0) load_a(1, 0, 0);
+                else if (!FINE && mt == 0) load_a(mt + 1, 0, 0);
                 CF_SCHED_FENCE();
                 acc[c % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c < NT ? a0 : a1, fc[c & 1], acc[c % NT], 0, 0, 0);
                 CF_SCHED_FENCE();
@@ -430,22 +440,44 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
         }
     };
 
+    auto step = [&](const int kt, const int stage) __attribute__((always_inline)) {
+        const int key0 = kt * 64 + kw * 32;
+        if (key0 <= wave_maxpos) {
+            const unsigned char* sk = smem + stage * 2 * TILE + kw * (32 * D * 2);
+            // a query that does not exist (a ragged last wave) has position -1 and is masked in every tile
+            if (key0 + (FINE ? 31 : 63) <= wave_minpos && wave * 32 + 32 <= rows_in_tile) tile(ic<0>{}, key0, sk);
+            else tile(ic<1>{}, key0, sk);
+        }
+    };
     if (kt0 < nkt) issue_kv(kt0, kt0 & 1);
     wait_vmcnt<0>();
     lds_barrier();
     for (int kt = kt0; kt < nkt; ++kt) {
         if (kt + 1 < nkt) issue_kv(kt + 1, (kt + 1) & 1);
-        if (kt * 64 <= wave_maxpos) {
-            // a query that does not exist (a ragged last wave) has position -1 and is masked in every tile
-            const bool clear = kt * 64 + 63 <= wave_minpos && wave * 32 + 32 <= rows_in_tile;
-            const unsigned char* sk = smem + (kt & 1) * 2 * TILE;
-            if (clear) tile(ic<0>{}, kt, sk);
-            else tile(ic<1>{}, kt, sk);
-        }
+        step(kt, kt & 1);
         wait_vmcnt<0>();
         lds_barrier();
     }
 
+    if constexpr (FINE) {       // the second half of the keys joins the first one's wave; the last barrier has freed the tiles' LDS
+        float4* buf = reinterpret_cast<float4*>(smem) + wave * (NT * 4 * 64) + lane;
+        if (kw == 1) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    buf[(nt * 4 + q) * 64] = make_float4(acc[nt][4 * q], acc[nt][4 * q + 1], acc[nt][4 * q + 2], acc[nt][4 * q + 3]);
+        }
+        lds_barrier();
+        if (kw == 1) return;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 o = buf[(nt * 4 + q) * 64];
+                acc[nt][4 * q] += o.x; acc[nt][4 * q + 1] += o.y; acc[nt][4 * q + 2] += o.z; acc[nt][4 * q + 3] += o.w;
+            }
+    }
     if (ranges > 1) {           // fp32, unscaled, to the range's own partial (zeros when the range is empty)
         float* part = p.dq_part + (int64_t)blockIdx.z * p.n_kept * Nq;
 #pragma unroll
@@ -473,6 +505,16 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
                 p.dq_kept[(int64_t)(j0 + r) * Nq + h * D + nt * 32 + slot] = f32_to_bf16(acc[nt][v] * p.scale);
         }
     }
+}
+
+template <int D, bool ROPE>
+__global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
+    extern __shared__ __align__(16) unsigned char smem[];   // [2 stages][K tile, V tile]
+    uint64_t dq_limits = p.dq_limits;
+    asm("" : "+s"(dq_limits));                  // fetched with the first arguments, not in a round trip of its own further down
+    const int n_live = live_rows(p.n_kept, p.n_dev);
+    if (n_live <= p.dq_fine_rows) attn_dq_block<D, ROPE, true>(p, dq_limits, n_live, smem);
+    else attn_dq_block<D, ROPE, false>(p, dq_limits, n_live, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -1244,7 +1286,8 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
                                                                      p.n_dev, p.Hq, p.S, p.stat, o_full, o_out, q_full, q_out,
                                                                      do_parts);
     }
-    attn_dq_kernel<D, ROPE><<<dim3(p.Hq * p.B, tiles, dq_cap), 256, smem_dq, st>>>(p);
+    const int dq_tiles = std::max(tiles, ceil_div(std::min(max_per_seq, p.dq_fine_rows), 64));
+    attn_dq_kernel<D, ROPE><<<dim3(p.Hq * p.B, dq_tiles, dq_cap), 256, smem_dq, st>>>(p);
     dkv<<<dim3(p.Hq * p.B * tiles), 256, smem_dkv, st>>>(p);
     const int kv_blocks = p.Hq != p.Hkv ? ceil_div((int64_t)n_kept * p.Hkv * D / 8, 256) : 0;
     const int q_blocks = dq_cap > 1 ? ceil_div((int64_t)n_kept * p.Hq * D / 8, 256) : 0;
@@ -1272,6 +1315,7 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     p.n_kept = n_kept;
     p.n_dev = rows.dev;
     const int dq_cap = attn_dq_plan(L, rows, p.dq_limits);
+    p.dq_fine_rows = attn_dq_fine_rows(L);
     p.dq_part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(partials) + attn_dkv_partial_bytes(L, n_kept));
     p.dk_part = partials;
     p.dv_part = partials ? partials + (size_t)n_kept * L.Hq * L.d : nullptr;

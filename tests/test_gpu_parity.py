@@ -337,6 +337,19 @@ def test_attn_bwd_filtered_split_keys(B, S, Hq, Hkv, d):
     _attn_case("bf16", B, S, Hq, Hkv, d, mask, seed=S + d)
 
 
+@pytest.mark.parametrize("B,S,Hq,Hkv,d,n", [
+    (1, 600, 64, 8, 128, 512), (1, 600, 64, 8, 128, 513),       # 256 CUs: 4 tiles of 64 heads are the last fine ones at d = 128
+    (1, 800, 64, 64, 64, 768), (1, 800, 64, 64, 64, 769),       # 6 at d = 64
+    (3, 130, 4, 1, 128, 99), (2, 97, 4, 4, 64, 66),             # a second tile of a few rows, a wave without rows
+])
+def test_attn_bwd_filtered_fine_query_tiles(B, S, Hq, Hkv, d, n):
+    """Tiles of 64 queries whose keys two waves share out, up to the row count where tiles of 128 take over, and one row more."""
+    say("attn bf16 fine tiles B=%d S=%d Hq=%d Hkv=%d d=%d rows=%d" % (B, S, Hq, Hkv, d, n))
+    mask = np.zeros(B * S, np.uint8)
+    mask[np.random.default_rng(n).permutation(B * S)[:n]] = 1
+    _attn_case("bf16", B, S, Hq, Hkv, d, mask.reshape(B, S), seed=n)
+
+
 def test_attn_fp32_small_head_dims():
     for d in (8, 32):
         say("attn f32 d=%d" % d)
