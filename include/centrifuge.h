@@ -141,8 +141,8 @@ cf_status cf_build_keep_index(const uint8_t* mask, int32_t B, int32_t S,
 /* The keep-index build for callers that cannot allocate device memory or carry a workspace
  * (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).  Same
  * arguments and results as cf_build_keep_index without the workspace and without the host copy:
- * the per-span counts (one per 8192 tokens) live in a device array built into the library (8 KiB per GPU, held until
- * the process ends), nothing is allocated, freed or copied to the host and the stream is not
+ * what the first of two launches leaves for the second (a count per 8192 tokens and a bit per token) lives in a device array
+ * built into the library (2.1 MB per GPU, held until the process ends), nothing is allocated, freed or copied to the host and the stream is not
  * synchronised.  At most 2^24 tokens (B*S); more returns CF_ERR_UNSUPPORTED before any launch.
  * All calls on one GPU share that array: calls that overlap on one GPU (two streams, two host
  * threads) race and must be serialised by the caller. */

@@ -7,7 +7,10 @@ namespace cf {
 static constexpr int IDX_THREADS = 256;
 static constexpr int IDX_PER_THREAD = 16;
 static constexpr int IDX_CHUNK = IDX_THREADS * IDX_PER_THREAD;   // tokens per block
-static constexpr int IDX_SELF_COUNT_MAX_BLOCKS = 8;
+// Chunks up to which one launch does it, every block counting the mask bytes before its chunk itself; the last one reads all of them,
+// in loads that are in flight together, which a byte-wise mask (not on a 16-byte boundary) has no such loads for.
+// One launch and two: 64 K tokens 6.4 and 8.0 us, 128 K 7.7 and 8.1 (and a launch's host time), 256 K 10.2 and 8.1.
+static constexpr int IDX_SELF_COUNT_MAX_BLOCKS = 32, IDX_SELF_COUNT_MAX_UNALIGNED = 8;
 
 // number of non-zero bytes among 16 mask bytes starting at t0 (bytes >= T read as 0)
 __device__ __forceinline__ void load_flags(const uint8_t* mask, int64_t t0, int64_t T, bool aligned,
@@ -39,6 +42,14 @@ __device__ __forceinline__ int count_flags(const unsigned (&w)[4]) {
            __popc(nonzero_bytes(w[2])) + __popc(nonzero_bytes(w[3]));
 }
 
+// one bit per byte: bit e of the result is byte e
+__device__ __forceinline__ unsigned flag_bits(const unsigned (&w)[4]) {
+    unsigned m = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) m |= ((nonzero_bytes(w[i]) * 0x01020408u) >> 24 & 0xFu) << (4 * i);
+    return m;
+}
+
 __device__ __forceinline__ int block_sum_256(int v, int* red) {
     // red: 4 ints of LDS
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -49,8 +60,8 @@ __device__ __forceinline__ int block_sum_256(int v, int* red) {
     return red[0] + red[1] + red[2] + red[3];
 }
 
-// Masks of a handful of chunks (up to IDX_SELF_COUNT_MAX_BLOCKS, i.e. every layer-sized batch): one
-// launch, no scratch; every block counts the mask bytes before its chunk itself.
+// Masks of a few chunks (every layer-sized batch): one launch, no scratch; every block counts the mask bytes before its
+// chunk itself.
 __global__ __launch_bounds__(IDX_THREADS) void mask_scatter_kernel(
     const uint8_t* __restrict__ mask, int64_t T, int S, int B, int aligned,
     int32_t* __restrict__ idx, int32_t* __restrict__ cu_kept, int32_t* __restrict__ n_kept_dev) {
@@ -63,9 +74,19 @@ __global__ __launch_bounds__(IDX_THREADS) void mask_scatter_kernel(
     {
         int before = 0;
         unsigned w[4];
-        for (int c = 0; c < (int)blockIdx.x; ++c) {
-            load_flags(mask, (int64_t)c * IDX_CHUNK + (int64_t)tid * IDX_PER_THREAD, T, aligned != 0, w);
-            before += count_flags(w);
+        if (aligned) {              // the chunks before this one are whole
+            const uint4* m = reinterpret_cast<const uint4*>(mask) + tid;
+#pragma unroll 16
+            for (int c = 0; c < (int)blockIdx.x; ++c) {
+                const uint4 v = m[c * IDX_THREADS];
+                w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+                before += count_flags(w);
+            }
+        } else {
+            for (int c = 0; c < (int)blockIdx.x; ++c) {
+                load_flags(mask, (int64_t)c * IDX_CHUNK + (int64_t)tid * IDX_PER_THREAD, T, false, w);
+                before += count_flags(w);
+            }
         }
         base = block_sum_256(before, red);
     }
@@ -89,8 +110,8 @@ __global__ __launch_bounds__(IDX_THREADS) void mask_scatter_kernel(
     int pos = base + wave_base + incl - cnt;
 
     if (t0 < T) {
-        int s = (int)(t0 % S);
-        int b = (int)(t0 / S);
+        int b = (int)((unsigned)t0 / (unsigned)S);         // T <= 2^30
+        int s = (int)t0 - b * S;
 #pragma unroll
         for (int e = 0; e < IDX_PER_THREAD; ++e) {
             int64_t t = t0 + e;
@@ -111,9 +132,10 @@ __global__ __launch_bounds__(IDX_THREADS) void mask_scatter_kernel(
 // Masks of more than a handful of chunks: two launches over SPANS of IDX_SPAN_CHUNKS chunks (8192
 // tokens), one block per span.  The first counts the kept tokens of every span; the second has every block add up the counts of the spans before its own
 // (two thousand numbers for 16 M tokens, read by all threads at once: no scan kernel, no waiting on
-// other blocks) and then compact its span chunk by chunk: flags -> wave / block scan -> the chunk's
-// kept positions gathered in LDS -> full 256-byte lines out.  The second pass over the mask finds it
-// in the memory-side cache.
+// other blocks) and then compact its span: flags -> one wave / block scan for its two chunks -> the
+// kept positions gathered in LDS -> full 256-byte lines out.  The first launch leaves the flags as bits, so the second one reads
+// an eighth of the mask.  (Chunk by chunk, with five barriers, the mask's bytes read twice and 32-bit places without the bank
+// offset: 16 M tokens, half kept, 18.4 us, now 16.7; 4 M 10.0 and 8.5.)
 // (A single-pass chained scan with decoupled look-back was measured as well: one status word per chunk
 // has to cross from one XCD's L2 to another's through memory, about a microsecond per hop, and the chain
 // of hops made it slower than the two launches: 70 us against 45 us for 16 M tokens.)
@@ -122,7 +144,8 @@ static constexpr int IDX_SPAN_CHUNKS = 2;
 static constexpr int64_t IDX_SPAN = (int64_t)IDX_SPAN_CHUNKS * IDX_CHUNK;
 
 __global__ __launch_bounds__(IDX_THREADS) void mask_span_count_kernel(const uint8_t* __restrict__ mask, int64_t T,
-                                                                      int aligned, int32_t* __restrict__ span_count) {
+                                                                      int aligned, int32_t* __restrict__ span_count,
+                                                                      uint16_t* __restrict__ bits) {
     __shared__ int red[4];
     const int64_t s0 = (int64_t)blockIdx.x * IDX_SPAN + (int64_t)threadIdx.x * IDX_PER_THREAD;
     unsigned w[IDX_SPAN_CHUNKS][4];
@@ -130,80 +153,95 @@ __global__ __launch_bounds__(IDX_THREADS) void mask_span_count_kernel(const uint
     for (int c = 0; c < IDX_SPAN_CHUNKS; ++c) load_flags(mask, s0 + (int64_t)c * IDX_CHUNK, T, aligned != 0, w[c]);
     int n = 0;
 #pragma unroll
-    for (int c = 0; c < IDX_SPAN_CHUNKS; ++c) n += count_flags(w[c]);
+    for (int c = 0; c < IDX_SPAN_CHUNKS; ++c) {
+        const unsigned m = flag_bits(w[c]);
+        bits[(int64_t)blockIdx.x * (IDX_SPAN / 16) + c * IDX_THREADS + threadIdx.x] = (uint16_t)m;
+        n += __popc(m);
+    }
     const int total = block_sum_256(n, red);
     if (threadIdx.x == 0) span_count[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(IDX_THREADS) void mask_span_scatter_kernel(
-    const uint8_t* __restrict__ mask, int64_t T, int S, int B, int aligned,
+// Where position p of a span's kept tokens is staged: one bank further every 128 positions, so that lanes whose tokens are
+// kept alike (16 positions apart at a keep ratio of a half) write to different banks.
+__device__ __forceinline__ int staged_at(int p) { return p + ((p >> 7) << 1); }
+
+__global__ __launch_bounds__(IDX_THREADS, 8) void mask_span_scatter_kernel(
+    const uint16_t* __restrict__ bits, int64_t T, int S, int B,
     const int32_t* __restrict__ span_count, int32_t* __restrict__ idx, int32_t* __restrict__ cu_kept,
     int32_t* __restrict__ n_kept_dev) {
-    __shared__ int red[4];
-    __shared__ int wave_tot[4];
-    __shared__ int32_t staged[IDX_CHUNK];
+    static_assert(IDX_SPAN_CHUNKS == 2 && IDX_SPAN <= 65536, "packed counts, 16-bit places");
+    __shared__ int before_tot[4], wave_tot[4];
+    __shared__ uint16_t staged[IDX_SPAN + IDX_SPAN / 64];       // kept tokens of the span, counted from its first token
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    // the span's mask bytes are requested first: they are on their way while the counts are added up
-    unsigned wall[IDX_SPAN_CHUNKS][4];
+    const unsigned span0 = blockIdx.x * (unsigned)IDX_SPAN;
+    // the span's flags are requested first: they are on their way while the counts are added up
+    unsigned w[2];
 #pragma unroll
-    for (int c = 0; c < IDX_SPAN_CHUNKS; ++c)
-        load_flags(mask, (int64_t)blockIdx.x * IDX_SPAN + (int64_t)c * IDX_CHUNK + (int64_t)tid * IDX_PER_THREAD, T,
-                   aligned != 0, wall[c]);
+    for (int c = 0; c < 2; ++c) w[c] = bits[(int64_t)blockIdx.x * (IDX_SPAN / 16) + c * IDX_THREADS + tid];
+    // kept tokens in all spans before this one, four counts per load (the counts' buffer is a multiple of 256 bytes)
     int before = 0;
-    for (int i = tid; i < (int)blockIdx.x; i += IDX_THREADS) before += span_count[i];
-    int base = block_sum_256(before, red);          // kept tokens in all spans before this one
-
-#pragma unroll
-    for (int c = 0; c < IDX_SPAN_CHUNKS; ++c) {
-        const int64_t t0 = (int64_t)blockIdx.x * IDX_SPAN + (int64_t)c * IDX_CHUNK + (int64_t)tid * IDX_PER_THREAD;
-        if ((int64_t)blockIdx.x * IDX_SPAN + (int64_t)c * IDX_CHUNK >= T) break;         // uniform: past the mask's end
-        const unsigned (&w)[4] = wall[c];
-        const int cnt = count_flags(w);
-        int incl = cnt;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int n = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += n;
-        }
-        __syncthreads();                            // the previous chunk's staged positions and totals have been read
-        if (lane == 63) wave_tot[wave] = incl;
-        __syncthreads();
-        int wave_base = 0;
-        for (int i = 0; i < wave; ++i) wave_base += wave_tot[i];
-        const int total = wave_tot[0] + wave_tot[1] + wave_tot[2] + wave_tot[3];
-        int pos = wave_base + incl - cnt;           // kept tokens of this chunk before this thread's 16
-        if (t0 < T) {
-            // T <= 2^30: token numbers fit 32 bits.  Sequence starts inside these 16 tokens (none, as a rule:
-            // only then is the division's result used) get their prefix count; bytes past T were read as zero.
-            const unsigned u0 = (unsigned)t0;
-            unsigned b = (u0 + (unsigned)S - 1u) / (unsigned)S;          // first sequence that starts at or after u0
-            unsigned next_start = b * (unsigned)S;
-#pragma unroll
-            for (int e = 0; e < IDX_PER_THREAD; ++e) {
-                const unsigned t = u0 + e;
-                if (t == next_start && t < (unsigned)T) {
-                    cu_kept[b] = base + pos;
-                    ++b;
-                    next_start += (unsigned)S;
-                }
-                if ((w[e >> 2] >> (8 * (e & 3))) & 0xFFu) staged[pos++] = (int32_t)t;
-            }
-            if (t0 + IDX_PER_THREAD >= T) {         // this thread owns token T-1
-                cu_kept[B] = base + pos;
-                if (n_kept_dev != nullptr) *n_kept_dev = base + pos;
-            }
-        }
-        __syncthreads();
-        for (int i = tid; i < total; i += IDX_THREADS) idx[base + i] = staged[i];
-        base += total;
+#pragma unroll 2
+    for (int i = tid * 4; i < (int)blockIdx.x; i += IDX_THREADS * 4) {
+        const int4 v = *reinterpret_cast<const int4*>(span_count + i);
+        const int n = (int)blockIdx.x - i;
+        before += v.x + (n > 1 ? v.y : 0) + (n > 2 ? v.z : 0) + (n > 3 ? v.w : 0);
     }
+    // one scan for both chunks (a wave has at most 1024 of a chunk's tokens) and one barrier for all totals
+    const int cnt = __popc(w[0]) | (__popc(w[1]) << 16);
+    int incl = cnt;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int n = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += n;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+    if (lane == 63) { wave_tot[wave] = incl; before_tot[wave] = before; }
+    __syncthreads();
+    const int base = before_tot[0] + before_tot[1] + before_tot[2] + before_tot[3];
+    int tot[2] = {0, 0}, pos[2] = {(incl - cnt) & 0xFFFF, (int)((unsigned)(incl - cnt) >> 16)};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int a = wave_tot[i] & 0xFFFF, b = (int)((unsigned)wave_tot[i] >> 16);
+        tot[0] += a;
+        tot[1] += b;
+        pos[0] += i < wave ? a : 0;
+        pos[1] += i < wave ? b : 0;
+    }
+    pos[1] += tot[0];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const unsigned u0 = span0 + c * IDX_CHUNK + tid * IDX_PER_THREAD;       // T <= 2^30: token numbers fit 32 bits
+        if (u0 >= (unsigned)T) break;
+        int p = pos[c];
+        // Sequence starts inside these 16 tokens (none, as a rule) get their prefix count; bytes past T were read as zero.
+        unsigned b = (u0 + (unsigned)S - 1u) / (unsigned)S;                     // first sequence that starts at or after u0
+        for (unsigned t = b * (unsigned)S; t < u0 + IDX_PER_THREAD && t < (unsigned)T; t += (unsigned)S, ++b) {
+            cu_kept[b] = base + p + __popc(w[c] & ((1u << (t - u0)) - 1u));
+        }
+        const unsigned local = c * IDX_CHUNK + tid * IDX_PER_THREAD;
+#pragma unroll
+        for (int e = 0; e < IDX_PER_THREAD; ++e)
+            if ((w[c] >> e) & 1u) staged[staged_at(p++)] = (uint16_t)(local + e);
+        if (u0 + IDX_PER_THREAD >= (unsigned)T) {       // this thread owns token T-1
+            cu_kept[B] = base + p;
+            if (n_kept_dev != nullptr) *n_kept_dev = base + p;
+        }
+    }
+    __syncthreads();
+    const int total = tot[0] + tot[1];
+#pragma unroll 4
+    for (int i = tid; i < total; i += IDX_THREADS) idx[base + i] = (int32_t)(span0 + staged[staged_at(i)]);
 }
 
+// one count per span, then a bit per token of the spans
+static size_t span_count_bytes(int64_t nspan) { return align_up((size_t)nspan * sizeof(int32_t), 256); }
 size_t index_ws_bytes(int64_t n_tokens) {
     int64_t nspan = (n_tokens + IDX_SPAN - 1) / IDX_SPAN;
     if (nspan < 1) nspan = 1;
-    return align_up((size_t)nspan * sizeof(int32_t), 256);      // one count per span
+    return span_count_bytes(nspan) + (size_t)nspan * (IDX_SPAN / 8);
 }
 
 hipError_t launch_keep_index(const uint8_t* mask, int B, int S, int32_t* idx, int32_t* cu_kept,
@@ -211,27 +249,27 @@ hipError_t launch_keep_index(const uint8_t* mask, int B, int S, int32_t* idx, in
     const int64_t T = (int64_t)B * S;
     const int nblk = ceil_div(T, IDX_CHUNK);
     const int aligned = ((uintptr_t)mask % 16 == 0) ? 1 : 0;
-    if (nblk <= IDX_SELF_COUNT_MAX_BLOCKS) {
+    if (nblk <= (aligned ? IDX_SELF_COUNT_MAX_BLOCKS : IDX_SELF_COUNT_MAX_UNALIGNED)) {
         mask_scatter_kernel<<<nblk, IDX_THREADS, 0, st>>>(mask, T, S, B, aligned, idx, cu_kept, n_kept_dev);
     } else {
         const int nspan = ceil_div(T, IDX_SPAN);
         int32_t* span_count = static_cast<int32_t*>(ws);
-        mask_span_count_kernel<<<nspan, IDX_THREADS, 0, st>>>(mask, T, aligned, span_count);
-        mask_span_scatter_kernel<<<nspan, IDX_THREADS, 0, st>>>(mask, T, S, B, aligned, span_count, idx, cu_kept,
-                                                                n_kept_dev);
+        uint16_t* bits = reinterpret_cast<uint16_t*>(static_cast<unsigned char*>(ws) + span_count_bytes(nspan));
+        mask_span_count_kernel<<<nspan, IDX_THREADS, 0, st>>>(mask, T, aligned, span_count, bits);
+        mask_span_scatter_kernel<<<nspan, IDX_THREADS, 0, st>>>(bits, T, S, B, span_count, idx, cu_kept, n_kept_dev);
     }
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
 // The same index build for callers that cannot allocate or hand in a workspace: the per-block
-// counts live in a file-scope device array.  Every GPU holds its own copy of the array at its own
+// counts and the flag bits live in a file-scope device array.  Every GPU holds its own copy of the array at its own
 // address; host code never uses the array's name as a pointer but looks its address up once per
 // device (with that device current) and passes that pointer to the kernels.  The kernels write
-// every entry they later read (span b's count, b < number of spans), so nothing has to be cleared
+// every entry they later read (span b's count and bits, b < number of spans), so nothing has to be cleared
 // between calls; calls that overlap on one GPU share the array and race.
 // ---------------------------------------------------------------------------
-static __device__ __align__(256) int32_t scratch[IDX_STATIC_MAX_TOKENS / IDX_SPAN];
+static __device__ __align__(256) int32_t scratch[IDX_STATIC_MAX_TOKENS / IDX_SPAN * (1 + IDX_SPAN / 32)];
 
 hipError_t launch_keep_index_static(const uint8_t* mask, int B, int S, int32_t* idx, int32_t* cu_kept,
                                     int32_t* n_kept_dev, hipStream_t st) {

@@ -61,6 +61,22 @@ def test_keep_index_unaligned_mask_pointer():
     assert n == rn and np.array_equal(cu.cpu().numpy(), rcu) and np.array_equal(idx[:n].cpu().numpy(), ridx)
 
 
+@pytest.mark.parametrize("off", [0, 3])
+@pytest.mark.parametrize("B,S", [(1, 32768), (1, 32769), (2, 65536), (1, 131073), (131089, 1), (4097, 33), (7, 8192 * 9 + 1)])
+def test_keep_index_on_both_sides_of_the_second_launch(B, S, off):
+    """One launch up to 32 chunks of 4096 tokens (8 where the mask does not lie on a 16-byte boundary), two beyond; sequences that
+    start inside a thread's 16 tokens, at every one of them, and at a chunk's and a span's first."""
+    say("keep_index B=%d S=%d off=%d" % (B, S, off))
+    for p in (0.02, 0.5, 1.0):
+        mask = (np.random.default_rng(B + S).random(B * S) < p).astype(np.uint8) * 128
+        t = torch.zeros(off + B * S, dtype=torch.uint8, device=DEV)
+        t[off:] = torch.from_numpy(mask).to(DEV)
+        idx, cu, n_dev, n = Bn.build_keep_index(t[off:].view(B, S))
+        rcu = np.concatenate([[0], np.cumsum((mask.reshape(B, S) != 0).sum(axis=1))])
+        assert n == rcu[-1] and int(n_dev.item()) == n
+        assert np.array_equal(cu.cpu().numpy(), rcu) and np.array_equal(idx[:n].cpu().numpy(), np.flatnonzero(mask))
+
+
 # ---------------------------------------------------------------------------
 # A2 gather
 # ---------------------------------------------------------------------------
