@@ -144,8 +144,8 @@ cf_status cf_build_keep_index(const uint8_t* mask, int32_t B, int32_t S,
  * what the first of two launches leaves for the second (a count per 8192 tokens and a bit per token) lives in a device array
  * built into the library (2.1 MB per GPU, held until the process ends), nothing is allocated, freed or copied to the host and the stream is not
  * synchronised.  At most 2^24 tokens (B*S); more returns CF_ERR_UNSUPPORTED before any launch.
- * All calls on one GPU share that array: calls that overlap on one GPU (two streams, two host
- * threads) race and must be serialised by the caller. */
+ * All calls on one GPU of more than 32768 tokens share that array: such calls that overlap on one GPU (two streams, two host
+ * threads) race and must be serialised by the caller.  Shorter masks are indexed in one launch that does not touch it. */
 cf_status cf_build_keep_index_static(const uint8_t* mask, int32_t B, int32_t S,
                                      int32_t* idx, int32_t* cu_kept, int32_t* n_kept_dev,
                                      cf_stream stream);

@@ -244,12 +244,17 @@ size_t index_ws_bytes(int64_t n_tokens) {
     return span_count_bytes(nspan) + (size_t)nspan * (IDX_SPAN / 8);
 }
 
+// one launch, which touches no workspace
+static bool one_launch(const uint8_t* mask, int64_t T) {
+    return ceil_div(T, IDX_CHUNK) <= ((uintptr_t)mask % 16 == 0 ? IDX_SELF_COUNT_MAX_BLOCKS : IDX_SELF_COUNT_MAX_UNALIGNED);
+}
+
 hipError_t launch_keep_index(const uint8_t* mask, int B, int S, int32_t* idx, int32_t* cu_kept,
                              int32_t* n_kept_dev, void* ws, hipStream_t st) {
     const int64_t T = (int64_t)B * S;
     const int nblk = ceil_div(T, IDX_CHUNK);
     const int aligned = ((uintptr_t)mask % 16 == 0) ? 1 : 0;
-    if (nblk <= (aligned ? IDX_SELF_COUNT_MAX_BLOCKS : IDX_SELF_COUNT_MAX_UNALIGNED)) {
+    if (one_launch(mask, T)) {
         mask_scatter_kernel<<<nblk, IDX_THREADS, 0, st>>>(mask, T, S, B, aligned, idx, cu_kept, n_kept_dev);
     } else {
         const int nspan = ceil_div(T, IDX_SPAN);
@@ -273,6 +278,7 @@ static __device__ __align__(256) int32_t scratch[IDX_STATIC_MAX_TOKENS / IDX_SPA
 
 hipError_t launch_keep_index_static(const uint8_t* mask, int B, int S, int32_t* idx, int32_t* cu_kept,
                                     int32_t* n_kept_dev, hipStream_t st) {
+    if (one_launch(mask, (int64_t)B * S)) return launch_keep_index(mask, B, S, idx, cu_kept, n_kept_dev, nullptr, st);
     static std::atomic<void*> scratch_ptr[64];
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
