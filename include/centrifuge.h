@@ -168,6 +168,13 @@ cf_status cf_gather_rows(const void* src, int64_t src_rows, int64_t cols, int32_
 cf_status cf_linear_bwd_reduced(const void* x_kept, const void* dy_kept, const void* w,
                                 int32_t n_kept, int32_t in, int32_t out, int32_t dtype,
                                 void* dx_kept, void* dw, float dw_beta, cf_stream stream);
+/* The same with scratch (ws: 256-byte aligned, overlapping no other argument, or NULL) that lets a product of few output
+ * tiles and a long contraction be cut into parts, which idle compute units work on, and summed up.  The size is 0 where
+ * nothing would be cut (and for invalid sizes); a ws that is smaller is CF_ERR_WORKSPACE. */
+size_t cf_linear_workspace_bytes(int32_t n_kept, int32_t in, int32_t out, int32_t dtype);
+cf_status cf_linear_bwd_reduced_ws(const void* x_kept, const void* dy_kept, const void* w,
+                                   int32_t n_kept, int32_t in, int32_t out, int32_t dtype,
+                                   void* dx_kept, void* dw, float dw_beta, void* ws, size_t ws_bytes, cf_stream stream);
 
 /* ---- A5: filtered attention backward (Sec. 3.1, Eq. 3 and Eq. 4) -----------
  * Kept queries attend to ALL keys/values at positions <= their own (causal on

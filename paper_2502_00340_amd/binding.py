@@ -7,6 +7,7 @@ CPU fallback: if the library has not been built, `lib()` raises.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import math
 import os
 
@@ -22,7 +23,7 @@ _STATUS = {0: "CF_OK", 1: "CF_ERR_NULL", 2: "CF_ERR_SHAPE", 3: "CF_ERR_DTYPE", 4
 EXPORTS = (
     "cf_status_str", "cf_version", "cf_index_workspace_bytes", "cf_build_keep_index",
     "cf_build_keep_index_static", "cf_gather_rows",
-    "cf_linear_bwd_reduced", "cf_attn_workspace_bytes", "cf_attn_bwd_filtered",
+    "cf_linear_bwd_reduced", "cf_linear_workspace_bytes", "cf_linear_bwd_reduced_ws", "cf_attn_workspace_bytes", "cf_attn_bwd_filtered",
     "cf_layer_workspace_bytes", "cf_layer_bwd_filtered", "cf_layer_bwd_compact", "cf_layer_bwd_compact_dev",
     "cf_layer_bwd_dense",
     "cf_lora_workspace_bytes", "cf_layer_bwd_lora", "cf_probe_mfma_bf16", "cf_probe_mfma_lds_bf16",
@@ -95,6 +96,10 @@ def lib() -> C.CDLL:
     L.cf_gather_rows.argtypes = [vp, i64, i64, i32, vp, vp, i32, vp, vp]
     L.cf_linear_bwd_reduced.restype = C.c_int
     L.cf_linear_bwd_reduced.argtypes = [vp, vp, vp, i32, i32, i32, i32, vp, vp, f32, vp]
+    L.cf_linear_workspace_bytes.restype = sz
+    L.cf_linear_workspace_bytes.argtypes = [i32, i32, i32, i32]
+    L.cf_linear_bwd_reduced_ws.restype = C.c_int
+    L.cf_linear_bwd_reduced_ws.argtypes = [vp, vp, vp, i32, i32, i32, i32, vp, vp, f32, vp, sz, vp]
     L.cf_attn_workspace_bytes.restype = sz
     L.cf_attn_workspace_bytes.argtypes = [C.POINTER(LayerDesc), i32]
     L.cf_attn_bwd_filtered.restype = C.c_int
@@ -149,6 +154,10 @@ def _ptr(t):
             _dummy[key] = torch.zeros(256, dtype=torch.uint8, device=t.device)
         return _dummy[key].data_ptr()
     return t.data_ptr()
+
+
+def _addr(t):
+    return None if t is None else t.data_ptr()
 
 
 # torch's raw query of a device's current stream, absent from torch's public interface
@@ -233,6 +242,12 @@ def gather_rows(src: torch.Tensor, idx: torch.Tensor, n_rows: int, out: torch.Te
     return out
 
 
+@functools.lru_cache(maxsize=1024)
+def _linear_ws_bytes(n_kept, in_f, out_f, code):
+    """A function of the sizes alone (and of the GPU's kind)."""
+    return lib().cf_linear_workspace_bytes(n_kept, in_f, out_f, code)
+
+
 def linear_bwd_reduced(x_kept, dy_kept, w, need_dx=True, need_dw=True, dw_accumulate_into=None):
     """Returns (dx_kept or None, dw or None)."""
     n_kept, out_f = dy_kept.shape
@@ -246,9 +261,12 @@ def linear_bwd_reduced(x_kept, dy_kept, w, need_dx=True, need_dw=True, dw_accumu
             dw, beta = dw_accumulate_into, 1.0
         else:
             dw = torch.empty((in_f, out_f), dtype=dy_kept.dtype, device=dev)
-    _check(lib().cf_linear_bwd_reduced(_ptr(x_kept), _ptr(dy_kept), _ptr(w), n_kept, in_f, out_f,
-                                       _dtype_code(dy_kept), _ptr(dx), _ptr(dw), beta, _stream()),
-           "cf_linear_bwd_reduced")
+    code = _dtype_code(dy_kept)
+    wsb = _linear_ws_bytes(n_kept, in_f, out_f, code) if need_dx else 0
+    ws = torch.empty(wsb, dtype=torch.uint8, device=dev) if wsb else None
+    at = _addr if n_kept else _ptr          # with rows no tensor is empty
+    _check((_lib or lib()).cf_linear_bwd_reduced_ws(at(x_kept), at(dy_kept), at(w), n_kept, in_f, out_f, code, at(dx), at(dw),
+                                                    beta, _addr(ws), wsb, _stream()), "cf_linear_bwd_reduced")
     return dx, dw
 
 

@@ -454,6 +454,31 @@ cf_status check_rope(const cf_layer_desc* L, const cf_saved* sv) {
     return (L->d % 2 == 0 && (L->d / 2) % vn == 0) ? CF_OK : CF_ERR_SHAPE;
 }
 
+// Both products of a linear on 128x128 tiles fit one round of the CUs.
+bool linear_in_one_round(int n, int in, int out) {
+    return (int64_t)ceil_div(in, 128) * (ceil_div(n, 128) + ceil_div(out, 128)) <= compute_units();
+}
+// dX in parts pays: the chain of 64-wide steps (0.35 us each, or what reading W takes where that is longer) gets shorter by 28
+// steps or more, against a launch that sums the parts up and their fp32 slots.  Both products, without and with parts: [38 rows, 256 x
+// 4096] 26 and 15 us, [48, 512 x 8192] 56 and 19, [34, 4096 x 8192] 74 and 42, [452, 2048 x 4096] 43 and 35, [445, 4096 x 4096] 52 and
+// 49; over 110 drawn shapes 1.6 times as fast.
+bool linear_in_parts(int n, int in, int out) {
+    const int64_t tiles = (int64_t)ceil_div(in, 128) * ceil_div(n, 128), w_steps = (int64_t)in * out / 875000;
+    const int pairs = ceil_div(out, 64);
+    int per = pairs;
+    const bool one_round = linear_in_one_round(n, in, out);
+    if (one_round) {            // as many parts as the other product's tiles leave CUs for
+        const int64_t k = (compute_units() - (int64_t)ceil_div(in, 128) * ceil_div(out, 128)) / tiles;
+        if (k > 1) per = ceil_div(pairs, k);
+    } else {
+        const GemmSeg seg{nullptr, nullptr, out};
+        float slot;
+        gemm_nt_parts(CF_BF16, &seg, 1, in, &slot).count(n, per);
+    }
+    // the grouped launch's reduction takes longer: 32 steps 17 and 22 us, 48 steps 22 and 21, 64 steps in two parts 30 and 33, in more 26 and 21
+    return pairs - std::max<int64_t>(per, w_steps) >= (one_round ? 40 : 28);
+}
+
 }  // namespace
 
 extern "C" {
@@ -520,9 +545,20 @@ cf_status cf_gather_rows(const void* src, int64_t src_rows, int64_t cols, int32_
     return CF_OK;
 }
 
+size_t cf_linear_workspace_bytes(int32_t n_kept, int32_t in, int32_t out, int32_t dtype) {
+    if (n_kept <= 0 || in <= 0 || out <= 0 || dtype != CF_BF16) return 0;
+    return linear_in_parts(n_kept, in, out) ? gemm_group_slot_bytes() : 0;
+}
+
 cf_status cf_linear_bwd_reduced(const void* x_kept, const void* dy_kept, const void* w, int32_t n_kept,
                                 int32_t in, int32_t out, int32_t dtype, void* dx_kept, void* dw,
                                 float dw_beta, cf_stream stream) {
+    return cf_linear_bwd_reduced_ws(x_kept, dy_kept, w, n_kept, in, out, dtype, dx_kept, dw, dw_beta, nullptr, 0, stream);
+}
+
+cf_status cf_linear_bwd_reduced_ws(const void* x_kept, const void* dy_kept, const void* w, int32_t n_kept,
+                                   int32_t in, int32_t out, int32_t dtype, void* dx_kept, void* dw,
+                                   float dw_beta, void* ws, size_t ws_bytes, cf_stream stream) {
     cf_status s = check_dtype(dtype);
     if (s != CF_OK) return s;
     if (!dy_kept) return CF_ERR_NULL;
@@ -543,16 +579,23 @@ cf_status cf_linear_bwd_reduced(const void* x_kept, const void* dy_kept, const v
     // dW may go over W: the launches below read W for dX before the second one writes
     const size_t w_bytes = (size_t)in * out * dtype_size(dtype);
     const bool over_w = overlap(w, w_bytes, dw, w_bytes);
-    if (dtype == CF_BF16 && dx_kept && dw && n_kept > 0 && dw_beta == 0.f && !over_w &&
-        ceil_div(in, 128) * (ceil_div(n_kept, 128) + ceil_div(out, 128)) <= compute_units()) {
+    float* slots = nullptr;
+    if (ws) {
+        const size_t need = cf_linear_workspace_bytes(n_kept, in, out, dtype);
+        if (misaligned(ws, 256) || ws_bytes < need) return CF_ERR_WORKSPACE;
+        if (need) slots = static_cast<float*>(ws);
+    }
+    if (dtype == CF_BF16 && dx_kept && dw && n_kept > 0 && dw_beta == 0.f && !over_w && linear_in_one_round(n_kept, in, out)) {
         // both products on 128x128 tiles fit one round of the CUs: one launch, and neither waits for the other
         const GemmGroupProb ps[2] = {{dy_kept, w, dx_kept, n_kept, in, out, 0, 1.f}, {x_kept, dy_kept, dw, in, out, n_kept, 1, 1.f}};
-        CF_HIP(launch_gemm_group(dtype, ps, 2, st));
+        CF_HIP(launch_gemm_group(dtype, ps, 2, st, slots));
         return CF_OK;
     }
     if (dx_kept && n_kept > 0) {
         GemmSeg seg{dy_kept, w, out};
-        CF_HIP(launch_gemm_nt(dtype, &seg, 1, dx_kept, n_kept, in, st));
+        const NtParts parts = gemm_nt_parts(dtype, &seg, 1, in, slots);
+        CF_HIP(launch_gemm_nt(dtype, &seg, 1, dx_kept, n_kept, in, st, nullptr, nullptr, 0, &parts));
+        CF_HIP(launch_gemm_nt_sum(parts, n_kept, dx_kept, st));
     }
     if (dw) {
         const GemmTnProb p{x_kept, dy_kept, dw, in, out};

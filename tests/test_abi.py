@@ -129,6 +129,18 @@ def test_linear_argument_errors(L):
     assert f(FAKE, FAKE, FAKE, 1 << 20, 14336, 4096, 0, FAKE, FAKE, 0.0, None) == 5    # bf16 matrix of 2 GiB or more
 
 
+def test_linear_scratch(L):
+    """Scratch is asked for where dX has few tiles and a long contraction, in bf16 only; too little of it is refused."""
+    need = L.cf_linear_workspace_bytes
+    assert need(100, 4096, 4096, 0) > 0
+    assert need(100, 4096, 4096, 1) == need(4096, 4096, 4096, 0) == need(100, 4096, 512, 0) == 0
+    assert need(0, 4096, 4096, 0) == need(100, -1, 4096, 0) == 0
+    f = L.cf_linear_bwd_reduced_ws
+    assert f(FAKE, FAKE, FAKE, 100, 4096, 4096, 0, FAKE, FAKE, 0.0, FAKE, need(100, 4096, 4096, 0) - 1, None) == 4
+    assert f(FAKE, FAKE, FAKE, 100, 4096, 4096, 0, FAKE, FAKE, 0.0, C.c_void_p(0x10010), 1 << 30, None) == 4    # misaligned
+    assert f(FAKE, None, FAKE, 100, 4096, 4096, 0, FAKE, FAKE, 0.0, FAKE, 1 << 30, None) == 1
+
+
 def test_attention_argument_errors(L):
     f = L.cf_attn_bwd_filtered
     d = _desc()

@@ -188,6 +188,30 @@ def test_linear_large_tiles_ragged_contraction(n, fin, k):
     assert bool((err <= ref.abs() * 2.0 ** -8 + 1e-4 * math.sqrt(k)).all()), err.max().item()
 
 
+@pytest.mark.parametrize("n,fin,fout", [(38, 256, 4096), (97, 512, 4096), (129, 512, 8200), (31, 1024, 4104), (257, 840, 8192), (445, 4096, 4096),
+                                        (16, 8, 4104), (1, 2048, 3072)])
+def test_linear_in_parts(n, fin, fout):
+    """dX of few tiles and a long contraction with scratch: its parts summed up in a launch of their own or, where both products share a
+    launch (the first two sizes and the seventh), by the grouped launch's; without scratch, and with dW over W.  Bounds as above."""
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    rn = lambda *s: torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16)
+    x, dy, w = rn(n, fin), rn(n, fout), rn(fin, fout)
+    need = Bn.lib().cf_linear_workspace_bytes(n, fin, fout, Bn.CF_BF16)
+    assert need > 0
+    rdx, rdw = dy.double() @ w.double().T, x.double().T @ dy.double()
+    ws = torch.empty(need, dtype=torch.uint8, device=DEV)
+    for scratch, over in ((ws, False), (None, False), (ws, True)):
+        w2 = w.clone()
+        dx, dw = torch.empty(n, fin, dtype=torch.bfloat16, device=DEV), w2 if over else torch.empty_like(w)
+        Bn._check(Bn.lib().cf_linear_bwd_reduced_ws(Bn._ptr(x), Bn._ptr(dy), Bn._ptr(w2), n, fin, fout, Bn.CF_BF16, Bn._ptr(dx),
+                                                    Bn._ptr(dw), 0.0, Bn._ptr(scratch), need, Bn._stream()), "cf_linear_bwd_reduced_ws")
+        for got, ref, k in ((dx, rdx, fout), (dw, rdw, n)):
+            err = (got.double() - ref).abs()
+            assert bool((err <= ref.abs() * 2.0 ** -8 + 1e-4 * math.sqrt(k)).all()), (scratch is None, over, err.max().item())
+    got = Bn.linear_bwd_reduced(x, dy, w)
+    assert bool(((got[0].double() - rdx).abs() <= rdx.abs() * 2.0 ** -8 + 1e-4 * math.sqrt(fout)).all())
+
+
 @pytest.mark.parametrize("n,fin,fout", [(128, 2048, 256), (300, 1032, 520), (2048, 2048, 2048)])
 def test_linear_dw_over_w(n, fin, fout):
     """dW written over W: dX still comes from the weights that were there, whether the two products would share a launch
