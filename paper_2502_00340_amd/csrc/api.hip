@@ -475,8 +475,9 @@ bool linear_in_parts(int n, int in, int out) {
         float slot;
         gemm_nt_parts(CF_BF16, &seg, 1, in, &slot).count(n, per);
     }
-    // the grouped launch's reduction takes longer: 32 steps 17 and 22 us, 48 steps 22 and 21, 64 steps in two parts 30 and 33, in more 26 and 21
-    return pairs - std::max<int64_t>(per, w_steps) >= (one_round ? 40 : 28);
+    // the grouped launch's reduction takes longer: 32 steps 17 and 22 us, 48 steps 22 and 21, 64 steps in two parts 30 and 33, in more 26
+    // and 21
+    return pairs - std::max<int64_t>(per, w_steps) >= (one_round ? GROUP_GAIN : 28);
 }
 
 }  // namespace

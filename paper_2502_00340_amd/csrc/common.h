@@ -205,6 +205,7 @@ hipError_t launch_gemm_tn(int dtype, const GemmTnProb* probs, int np, int K, flo
 // lets the contractions be split over idle CUs.  n_dev (nullable): the live kept-token count, which bounds M in
 // modes 0 and 2 and K in mode 1.
 static constexpr int GROUP_MAX = 8;
+static constexpr int GROUP_GAIN = 47, GROUP_GAIN_ONE = 36;      // steps of 64 that parts have to save (see gemm.hip)
 struct GemmGroupProb {
     const void *A, *B;
     void* C;

@@ -895,6 +895,7 @@ struct GroupArgs {
     int np;
     int n_cu;               // items that may be split over (and slots)
     const int32_t* n_dev;   // nullable: the live kept-token count (M in modes 0 and 2, K in mode 1), at most the one in p
+    int gain;               // steps of 64 that parts have to take off the longest contraction
     float* slots;           // nullable: no splitting; n_cu slots and, behind them, the plan (one int)
     __host__ __device__ int32_t* plan() const { return reinterpret_cast<int32_t*>(slots + (size_t)n_cu * (128 * 128)); }
 };
@@ -914,6 +915,21 @@ __host__ __device__ inline int group_parts(int K, int q) {
 // Part size number of a launch: the smallest (at least 128 k: two steps) with which the items of all products fit one
 // round of the CUs; -1, nothing is split, when even the whole tiles do not, or without slots.
 static constexpr int GROUP_Q = 40;
+// ... or when the longest contraction gets shorter by fewer than g.gain steps: a step is 0.35 to 0.5 us, against the launch that sums
+// the parts up and their slots (GROUP_GAIN; GROUP_GAIN_ONE for a single product, whose sum is smaller).  Four products
+// [4096, 64] of 48 and 16 steps, 128 tiles: 24 + 13 us in two parts, 33 whole; three of 48 steps, 96 tiles: 23 + 10 and 28; one, 32
+// tiles: 16 + 6 in eight parts, 28 whole.  (Every launch that fits was cut before.)
+__host__ __device__ inline int group_steps(const GroupArgs& g, int n_live) {        // of the longest contraction
+    int most = 0;
+#pragma unroll
+    for (int j = 0; j < GROUP_MAX; ++j) {
+        int M, K;
+        group_sizes(g.p[j], n_live, M, K);
+        const int k64 = (K + 63) >> 6;
+        most = j < g.np && k64 > most ? k64 : most;
+    }
+    return most;
+}
 __host__ __device__ inline bool group_fits(const GroupArgs& g, int n_live, int q, bool& split) {
     int items = 0;
     split = false;
@@ -933,7 +949,7 @@ inline int group_plan_host(const GroupArgs& g, int n_live) {
     for (int q = 2; q < GROUP_Q; ++q) {
         bool split;
         const bool fits = group_fits(g, n_live, q, split);
-        if (fits || !split) return split ? q : -1;
+        if (fits || !split) return split && group_steps(g, n_live) - group_step(q) >= g.gain ? q : -1;
     }
     return -1;
 }
@@ -946,7 +962,7 @@ __device__ __forceinline__ int group_plan(const GroupArgs& g, int n_live) {
     const uint64_t done = __ballot(q < GROUP_Q && (fits || !split)), cut = __ballot(split);
     if (done == 0) return -1;
     const int first = __ffsll((unsigned long long)done) - 1;
-    return (cut >> first) & 1 ? first + 2 : -1;
+    return ((cut >> first) & 1) && group_steps(g, n_live) - group_step(first + 2) >= g.gain ? first + 2 : -1;
 }
 
 // item -> product, tile and part; false past the last item
@@ -1255,14 +1271,19 @@ hipError_t launch_gemm_group(int dtype, const GemmGroupProb* probs, int np, hipS
     }
     GroupArgs g{};
     int64_t tiles = 0;
+    bool all_tn = true;
     for (int j = 0; j < np; ++j) {
         const GemmGroupProb& p = probs[j];
         if (p.M <= 0 || p.N <= 0 || p.K <= 0) return hipErrorInvalidValue;
         if (!offsets_fit(p.M, p.N, p.K)) return hipErrorInvalidValue;
         g.p[j] = p;
         tiles += (int64_t)ceil_div(p.M, 128) * ceil_div(p.N, 128);
+        all_tn = all_tn && p.mode == 1;
     }
-    g.np = np; g.n_cu = compute_units(); g.n_dev = n_dev; g.slots = slots;
+    g.np = np; g.n_cu = compute_units(); g.n_dev = n_dev; g.slots = slots; g.gain = np == 1 ? GROUP_GAIN_ONE : GROUP_GAIN;
+    // no live count can lead to parts: their sum is not launched (products over the kept tokens have the same tiles whatever the count, and
+    // are cut alike)
+    if (group_steps(g, INT32_MAX) - group_step(2) < g.gain || (all_tn && 2 * tiles > g.n_cu)) g.slots = slots = nullptr;
     static std::atomic<uint64_t> lds_ok{0};
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_group_kernel), GEMM_SMEM, lds_ok);
     if (e != hipSuccess) return e;
