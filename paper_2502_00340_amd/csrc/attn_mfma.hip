@@ -62,6 +62,7 @@ struct AttnParams {
     // evaluated here instead a call took 1.1 us more (of 16 at S = 384).
     uint64_t dq_limits;
     int dq_fine_rows;              // up to this many live rows the dQ blocks take tiles of 64 queries (see attn_dq_kernel)
+    int dkv_fine_rows;             // up to this many live rows the dK/dV blocks at d = 64 take tiles of 64 keys (attn_dkv64_kernel)
     int n_slots;                   // dK/dV blocks that the device holds at a time (the kernel sizes its blocks' work by it)
     int B, S, Hq, Hkv;
     // Nullable, both or none: rotary tables [S][d/2].  dQ and dK leave rotated back to before the rotary embedding, at the original
@@ -904,17 +905,20 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
 // that a lone wave needs, as long as there are two blocks for every CU and more to follow: whole attention call at d = 64, this
 // kernel and the pipelined one, [8192 rows, 32/32 heads, S = 2048] 274 and 322 us, [4096, 64/64, S = 1024] 177 and 212.  Fragment reads
 // run one MFMA pair ahead.  The accumulation order of every element is that of the pipelined kernel.
-template <bool ROPE>
-__global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
-    constexpr int D = 64, KS = D / 16, NT = D / 32;
+// FINE: 64 keys per block; the two waves of a group of 32 keys take the first and the second 32 queries of every step, and their sums
+// meet in LDS at the end: half the step and twice the blocks, as in the dQ kernel, up to one and a quarter 128-key tiles of live rows per
+// CU.  Whole attention call, coarse (the better of this kernel and the pipelined one) and fine, over 541 calls of 4 to 64 heads:
+// up to 320 tiles 1.03 to 1.10 times as fast, 320-512 tiles 0.97 to 1.02, more 0.90-0.98.
+template <bool ROPE, bool FINE>
+__device__ __forceinline__ void attn_dkv64_block(const AttnParams& p, const int n_live, unsigned char* smem) {
+    constexpr int D = 64, KS = D / 16, NT = D / 32, KT = FINE ? 64 : 128;
     constexpr int TILE = 64 * D * 2;
     constexpr int STAGE = 2 * TILE + 512;       // Q tile, dO tile, lse2[64], D[64]
-    extern __shared__ __align__(16) unsigned char smem[];
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = FINE ? wv & 1 : wv, qh = FINE ? wv >> 1 : 0;       // group of 32 keys; half of the steps
     const int slot = lane & 31, hh = lane >> 5;
     const int G = p.Hq / p.Hkv;
-    const int HP = attn_heads_per_block(live_rows(p.n_kept, p.n_dev), p.Hq, G, p.n_slots);
+    const int HP = attn_heads_per_block(n_live, p.Hq, G, p.n_slots);
     // block numbering as in attn_dkv_kernel: key tile by key tile, blocks without work last
     const int nhb = p.Hq / HP, per_tile = nhb * p.B;
     const int kt = blockIdx.x / per_tile, bx = blockIdx.x % per_tile;
@@ -924,9 +928,9 @@ __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
     int seq_begin, seq_end;
     seq_range(p, b, seq_begin, seq_end);
     const int cnt = seq_end - seq_begin;
-    if (kt * 128 >= cnt) return;
-    const int c0 = seq_begin + kt * 128;            // compact row of the tile's first key
-    const int keys_in_tile = min(128, cnt - kt * 128);
+    if (kt * KT >= cnt) return;
+    const int c0 = seq_begin + kt * KT;            // compact row of the tile's first key
+    const int keys_in_tile = min(KT, cnt - kt * KT);
 
     const int jk = c0 + wave * 32 + slot;           // this lane's key
     const bool kvalid = wave * 32 + slot < keys_in_tile;
@@ -969,7 +973,7 @@ __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
     unsigned voff[NLD];
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
-        const int row = (4 * i + wave) * RPL + lane / NCH;
+        const int row = (4 * i + wv) * RPL + lane / NCH;
         const int sw = (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
         voff[i] = (unsigned)row * (unsigned)(Nq * 2) + (unsigned)(((lane % NCH) ^ sw) << 4);
     }
@@ -997,16 +1001,17 @@ __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
         fc[buf][1] = __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(o0, o1, 0, 1, 2, 3, 4, 5, 6, 7));
     };
     // One step of 64 queries in the stage at sb, whose first query is compact row qrow0
-    auto step = [&](auto MASKED_, const unsigned sb, const int qrow0) __attribute__((always_inline)) {
+    // (FINE: sb and ss, the rows and their statistics, and qrow0 begin at the wave's half)
+    auto step = [&](auto MASKED_, const unsigned sb, const unsigned ss, const int qrow0) __attribute__((always_inline)) {
         constexpr bool masked = decltype(MASKED_)::value != 0;
         load_a(sb, 0, 0, 0);
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
+        for (int hf = 0; hf < (FINE ? 1 : 2); ++hf) {
             f32x16_t st, dpt;
 #pragma unroll
             for (int v = 0; v < 16; ++v) { st[v] = 0.f; dpt[v] = 0.f; }
             f32x4v_t lq[2], dq[2];                  // log2(e)*LSE and D of four queries at a time, one group ahead
-            const lds_u8_ptr ps = reinterpret_cast<lds_u8_ptr>(sb + 2 * TILE + 16 * hh);
+            const lds_u8_ptr ps = reinterpret_cast<lds_u8_ptr>(ss + 16 * hh);
             auto load_stats = [&](int v4) __attribute__((always_inline)) {
                 lq[v4 & 1] = *reinterpret_cast<lds_f4_cptr>(ps + (hf * 32 + 8 * v4) * 4);
                 dq[v4 & 1] = *reinterpret_cast<lds_f4_cptr>(ps + (64 + hf * 32 + 8 * v4) * 4);
@@ -1037,7 +1042,7 @@ __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
 #pragma unroll
             for (int c = 0; c < 2 * NT; ++c) {
                 if (c + 1 < 2 * NT) load_c(sb, hf, c + 1, (c + 1) & 1);
-                else if (hf == 0) load_a(sb, 1, 0, 0);
+                else if (!FINE && hf == 0) load_a(sb, 1, 0, 0);
                 CF_SCHED_FENCE();
                 dk[c % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ads[c / NT], fc[c & 1][0], dk[c % NT], 0, 0, 0);
                 dv[c % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ap[c / NT], fc[c & 1][1], dv[c % NT], 0, 0, 0);
@@ -1047,7 +1052,7 @@ __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
     };
 
     wait_vmcnt<0>();        // the K and V fragments: the counts below are those of the ring's loads alone
-    const int masked_steps = keys_in_tile < 128 ? steps : min(steps, 2);
+    const int masked_steps = keys_in_tile < KT ? steps : min(steps, KT / 64);
     for (int hi = 0; hi < HP; ++hi) {
         const int h = h0 + hi;
         const i32x4_t rsQ = make_rsrc(p.q_kept + (int64_t)c0 * Nq + h * D, ((int64_t)(seq_end - c0) * Nq - h * D) * 2);
@@ -1059,9 +1064,9 @@ __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
             const unsigned sq = lds0 + stage * STAGE;
             const unsigned base = (unsigned)(s * 64) * (unsigned)(Nq * 2);
 #pragma unroll
-            for (int i = 0; i < NLD; ++i) dma16(__builtin_amdgcn_readfirstlane(sq + (4 * i + wave) * 1024), rsQ, base + voff[i]);
+            for (int i = 0; i < NLD; ++i) dma16(__builtin_amdgcn_readfirstlane(sq + (4 * i + wv) * 1024), rsQ, base + voff[i]);
 #pragma unroll
-            for (int i = 0; i < NLD; ++i) dma16(__builtin_amdgcn_readfirstlane(sq + TILE + (4 * i + wave) * 1024), rsO, base + voff[i]);
+            for (int i = 0; i < NLD; ++i) dma16(__builtin_amdgcn_readfirstlane(sq + TILE + (4 * i + wv) * 1024), rsO, base + voff[i]);
             const unsigned off = (unsigned)(s * 64 + lane) * 4u;
             dma4(sq + 2 * TILE, rsL, off);
             dma4(sq + 2 * TILE + 256, rsD, off);
@@ -1074,13 +1079,36 @@ __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
             wait_vmcnt<2 * LPS>();                  // step s has landed; steps s+1 and s+2 may be in flight
             lds_barrier();                          // ... for every wave, and every wave is done with step s-1
             issue_q(s + 3, (s + 3) & 3);
-            const unsigned sb = lds0 + (unsigned)(s & 3) * STAGE;
-            if (s < masked_steps) step(ic<1>{}, sb, c0 + s * 64);
-            else step(ic<0>{}, sb, c0 + s * 64);
+            const unsigned st0 = lds0 + (unsigned)(s & 3) * STAGE, sb = st0 + qh * (32 * D * 2), ss = st0 + 2 * TILE + qh * 128;
+            if (s < masked_steps) step(ic<1>{}, sb, ss, c0 + s * 64 + qh * 32);
+            else step(ic<0>{}, sb, ss, c0 + s * 64 + qh * 32);
         }
         wait_vmcnt<0>();                            // the zero-fill loads of the steps past the end
     }
 
+    if constexpr (FINE) {
+        lds_barrier();                              // every wave is done with the stages
+        float4* buf = reinterpret_cast<float4*>(smem) + wave * (2 * NT * 4 * 64) + lane;
+        if (qh == 1) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    buf[(nt * 4 + q) * 64] = make_float4(dk[nt][4 * q], dk[nt][4 * q + 1], dk[nt][4 * q + 2], dk[nt][4 * q + 3]);
+                    buf[((NT + nt) * 4 + q) * 64] = make_float4(dv[nt][4 * q], dv[nt][4 * q + 1], dv[nt][4 * q + 2], dv[nt][4 * q + 3]);
+                }
+        }
+        lds_barrier();
+        if (qh == 1) return;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 a = buf[(nt * 4 + q) * 64], b = buf[((NT + nt) * 4 + q) * 64];
+                dk[nt][4 * q] += a.x; dk[nt][4 * q + 1] += a.y; dk[nt][4 * q + 2] += a.z; dk[nt][4 * q + 3] += a.w;
+                dv[nt][4 * q] += b.x; dv[nt][4 * q + 1] += b.y; dv[nt][4 * q + 2] += b.z; dv[nt][4 * q + 3] += b.w;
+            }
+    }
     const bool whole = G == HP;
     const int64_t part = whole ? 0 : (int64_t)((h0 - g * G) / HP) * p.n_kept * Nkv;
     if constexpr (ROPE) {
@@ -1107,6 +1135,14 @@ __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
             }
         }
     }
+}
+
+template <bool ROPE>
+__global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int n_live = live_rows(p.n_kept, p.n_dev);
+    if (n_live <= p.dkv_fine_rows) attn_dkv64_block<ROPE, true>(p, n_live, smem);
+    else attn_dkv64_block<ROPE, false>(p, n_live, smem);
 }
 
 // acc += part[0..3], part[half..half+3]
@@ -1272,7 +1308,10 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
     // 12 tiles are too short for that to make up for two full rounds ([4096, 16/16, S = 1024: 512] 55 and 58 us).
     // On a single tile the two take the same time, and the plain one less for a few rows
     // (13 rows, 16/16: 6.2 and 6.5 us).
-    const bool paired = D == 64 && (tiles == 1 || (int64_t)p.Hq * p.B * tiles * 4 > (int64_t)n_cu * (tiles < 12 ? 7 : 8));
+    // Only this kernel has the fine tiles that few live rows take (dkv_fine_rows), so it also runs where they may be few, which with a
+    // device-side count is always; above them it sums in the order of the pipelined one, so the choice does not show.
+    const bool chains = (int64_t)p.Hq * p.B * tiles * 4 <= (int64_t)n_cu * (tiles < 12 ? 7 : 8);
+    const bool paired = D == 64 && (tiles == 1 || !chains || n_kept <= p.dkv_fine_rows || p.n_dev != nullptr);
     p.n_slots = n_cu * (paired ? 2 : 1);
     static std::atomic<uint64_t> lds_ok_dq{0}, lds_ok_dkv{0}, lds_ok_paired{0};
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&attn_dq_kernel<D, ROPE>), smem_dq, lds_ok_dq);
@@ -1288,7 +1327,8 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
     }
     const int dq_tiles = std::max(tiles, ceil_div(std::min(max_per_seq, p.dq_fine_rows), 64));
     attn_dq_kernel<D, ROPE><<<dim3(p.Hq * p.B, dq_tiles, dq_cap), 256, smem_dq, st>>>(p);
-    dkv<<<dim3(p.Hq * p.B * tiles), 256, smem_dkv, st>>>(p);
+    const int dkv_tiles = paired ? std::max(tiles, ceil_div(std::min(max_per_seq, p.dkv_fine_rows), 64)) : tiles;
+    dkv<<<dim3(p.Hq * p.B * dkv_tiles), 256, smem_dkv, st>>>(p);
     const int kv_blocks = p.Hq != p.Hkv ? ceil_div((int64_t)n_kept * p.Hkv * D / 8, 256) : 0;
     const int q_blocks = dq_cap > 1 ? ceil_div((int64_t)n_kept * p.Hq * D / 8, 256) : 0;
     if (kv_blocks + q_blocks > 0) attn_reduce_kernel<D, ROPE><<<kv_blocks + q_blocks, 256, 0, st>>>(p, kv_blocks);
@@ -1316,6 +1356,7 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     p.n_dev = rows.dev;
     const int dq_cap = attn_dq_plan(L, rows, p.dq_limits);
     p.dq_fine_rows = attn_dq_fine_rows(L);
+    p.dkv_fine_rows = L.d == 64 ? compute_units() * 5 / 4 / L.Hq * 128 : 0;
     p.dq_part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(partials) + attn_dkv_partial_bytes(L, n_kept));
     p.dk_part = partials;
     p.dv_part = partials ? partials + (size_t)n_kept * L.Hq * L.d : nullptr;

@@ -377,9 +377,30 @@ def test_attn_bwd_filtered_split_keys(B, S, Hq, Hkv, d):
     _attn_case("bf16", B, S, Hq, Hkv, d, mask, seed=S + d)
 
 
+@pytest.mark.parametrize("S,rows", [(800, 640), (800, 641), (1200, 640)])
+def test_layer_fine_key_tiles_follow_the_live_rows(S, rows):
+    """64 heads of 64: on 256 CUs 640 rows are the last that take tiles of 64 keys in the dK/dV kernel.  The kernel that has them runs
+    wherever rows may be so few: the default bound, the tight one and a host count give the same bits on both sides of the line."""
+    shape = WL.LayerShape("fine_keys", B=1, S=S, H=128, Hq=64, Hkv=8, d=64, F=128, dtype="bf16")
+    sv, W, dy = _random_layer(shape, S + rows)
+    mask = torch.zeros((1, S), dtype=torch.uint8, device=DEV)
+    mask[0, torch.randperm(S, generator=torch.Generator().manual_seed(rows))[:rows].to(DEV)] = 1
+    desc = Bn.make_desc(1, S, 128, 64, 8, 64, 128, "bf16")
+    full, tight, host = (Bn.LayerBackward(desc, device=DEV, max_kept=m) for m in (None, rows, None))
+    assert full.filtered(sv, W, dy, mask) == rows
+    tight.filtered(sv, W, dy, mask)
+    host.compact(sv, W, Bn.gather_rows(dy, full.idx, rows), full.idx, full.cu_kept, rows)
+    torch.cuda.synchronize()
+    for other in (tight, host):
+        for k in full.grads:
+            assert torch.equal(full.grads[k][:rows] if k == "dx" else full.grads[k],
+                               other.grads[k][:rows] if k == "dx" else other.grads[k]), k
+
+
 @pytest.mark.parametrize("B,S,Hq,Hkv,d,n", [
     (1, 600, 64, 8, 128, 512), (1, 600, 64, 8, 128, 513),       # 256 CUs: 4 tiles of 64 heads are the last fine ones at d = 128
     (1, 800, 64, 64, 64, 768), (1, 800, 64, 64, 64, 769),       # 6 at d = 64
+    (1, 700, 64, 8, 64, 640), (1, 700, 64, 8, 64, 641),         # 5 tiles of keys at d = 64
     (3, 130, 4, 1, 128, 99), (2, 97, 4, 4, 64, 66),             # a second tile of a few rows, a wave without rows
 ])
 def test_attn_bwd_filtered_fine_query_tiles(B, S, Hq, Hkv, d, n):
