@@ -233,7 +233,7 @@ def roofline_leg(shape: WL.LayerShape, n_k: int, reps: int = 20):
             "frac": round(ach / PEAK_BF16_TFLOPS, 4), "traffic": traffic, "traffic_source": traffic_source,
             "ceiling_measured": ceil["TFLOPs"], "frac_of_ceiling": round(ach / ceil["TFLOPs"], 4),
             "ceiling": ceil,
-            "kernel": "cf::gemm_bf16_kernel<1> (TN): dW[F,H] = X_kept^T dY_kept",
+            "kernel": "cf::gemm_tn_kernel<false> (TN): dW[F,H] = X_kept^T dY_kept",
             "flops_per_launch": flops, "avg_launch_ms": round(avg, 4), "launches": reps}
 
 
