@@ -264,7 +264,7 @@ def linear_bwd_reduced(x_kept, dy_kept, w, need_dx=True, need_dw=True, dw_accumu
     code = _dtype_code(dy_kept)
     wsb = _linear_ws_bytes(n_kept, in_f, out_f, code) if need_dx else 0
     ws = torch.empty(wsb, dtype=torch.uint8, device=dev) if wsb else None
-    at = _addr if n_kept else _ptr          # with rows no tensor is empty
+    at = _addr if n_kept and in_f and out_f else _ptr          # with all sizes no tensor is empty
     _check((_lib or lib()).cf_linear_bwd_reduced_ws(at(x_kept), at(dy_kept), at(w), n_kept, in_f, out_f, code, at(dx), at(dw),
                                                     beta, _addr(ws), wsb, _stream()), "cf_linear_bwd_reduced")
     return dx, dw

@@ -212,6 +212,15 @@ def test_linear_in_parts(n, fin, fout):
     assert bool(((got[0].double() - rdx).abs() <= rdx.abs() * 2.0 ** -8 + 1e-4 * math.sqrt(fout)).all())
 
 
+@pytest.mark.parametrize("fin,fout", [(0, 64), (64, 0)])
+def test_linear_without_features_is_a_shape_error(fin, fout):
+    """Refused before any launch, for its shape, not for the empty tensors' missing addresses."""
+    t = lambda *s: torch.zeros(s, dtype=torch.bfloat16, device=DEV)
+    with pytest.raises(Bn.CfError) as e:
+        Bn.linear_bwd_reduced(t(16, fin), t(16, fout), t(fin, fout))
+    assert e.value.code == 2
+
+
 @pytest.mark.parametrize("n,fin,fout", [(128, 2048, 256), (300, 1032, 520), (2048, 2048, 2048)])
 def test_linear_dw_over_w(n, fin, fout):
     """dW written over W: dX still comes from the weights that were there, whether the two products would share a launch
