@@ -224,34 +224,32 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
         return CF_OK;
     }
     if (dy_is_full && !idx) return CF_ERR_NULL;
-    const void* dy_rows = dy_is_full ? w.dy_k : dy;
     const void* a_rows = idx ? w.a_k : sv.attn_out;
     const void* q_rows = idx ? w.q_k : sv.q;
     // The seven dW products wait for nothing but their operands, which stay where they are until the end: one launch then
     // has one remainder of tiles, not four.  Two operands may be the caller's (the upstream gradient of a compact or
-    // dense call, the attention output of a dense one): where an output lies over them, which the order of the passes has always
-    // allowed for dx, each product goes out as soon as its operands exist.
-    bool late = true;
+    // dense call, the attention output of a dense one), and an output may lie over them, which the order of the passes has always
+    // allowed for dx.  Of the first the SwiGLU pass then leaves a copy in the workspace, as it does of the kept rows of a full-length
+    // one; with the second dWo goes out at once.  A count on the device leaves open where the caller's rows end: up to the bound
+    // they may lie under whatever was allocated behind them, so this must not cost much: [2662 of 5834 rows, H = 4096,
+    // F = 1792, 4/1 heads] 485 us, with the copy 496, in a launch per product 569; H = 2048, F = 5632, 32/4 heads: 717, 721 and 791.
+    bool own_dy = dy_is_full, late_dwo = true;
     {
         const size_t ps = mg ? 4 : e, n = (size_t)N;
         const struct { const void* p; size_t bytes; } outs[] = {
             {G.dx, n * H * e}, {G.dg1, H * ps}, {G.dg2, H * ps}, {G.dwq, (size_t)H * Nq * ps}, {G.dwk, (size_t)H * Nkv * ps},
             {G.dwv, (size_t)H * Nkv * ps}, {G.dwo, (size_t)Nq * H * ps}, {G.dwg, (size_t)H * F * ps}, {G.dwu, (size_t)H * F * ps},
             {G.dwd, (size_t)F * H * ps}};
-        for (const auto& o : outs)
-            late = late && !overlap(o.p, o.bytes, dy_rows, n * H * e) && !overlap(o.p, o.bytes, a_rows, n * Nq * e);
+        for (const auto& o : outs) {
+            own_dy = own_dy || overlap(o.p, o.bytes, dy, n * H * e);
+            late_dwo = late_dwo && (idx || !overlap(o.p, o.bytes, a_rows, n * Nq * e));
+        }
     }
+    const void* dy_rows = own_dy ? w.dy_k : dy;
     GemmTnProb dws[TN_MAX];
     int n_dw = 0;
-    auto dw_launch = [&]() {
-        const int np = n_dw;
-        n_dw = 0;
-        return np ? launch_gemm_tn(dt, dws, np, N, mg ? 1.f : 0.f, st, mg, nd) : hipSuccess;
-    };
-    auto dw = [&](const void* A, const void* B, void* C, int M, int Ncols) {
-        dws[n_dw++] = GemmTnProb{A, B, C, M, Ncols};
-        return late ? hipSuccess : dw_launch();
-    };
+    auto dw_launch = [&](const GemmTnProb* ps, int np) { return launch_gemm_tn(dt, ps, np, N, mg ? 1.f : 0.f, st, mg, nd); };
+    auto dw = [&](const void* A, const void* B, void* C, int M, int Ncols) { dws[n_dw++] = GemmTnProb{A, B, C, M, Ncols}; };
 
     // ---- SwiGLU FFN: y = r + act*Wd --------------------------------------------
     // d_act = dy * Wd^T first; one pass over it then yields d_gate, d_up and act (the SwiGLU
@@ -267,8 +265,8 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     void* d_up = w.bufF0;
     void* act = w.bufF2;
     CF_HIP(launch_swiglu_bwd(dt, d_act, sv.gate, sv.up, idx, rows, F, d_gate, d_up, act, st, parts,
-                             dy_is_full ? dy : nullptr, H, dy_is_full ? w.dy_k : nullptr));
-    CF_HIP(dw(act, dy_rows, G.dwd, F, H));     // dWd = act^T * dy           [F,H]
+                             own_dy ? dy : nullptr, H, w.dy_k, dy_is_full ? idx : nullptr));
+    dw(act, dy_rows, G.dwd, F, H);             // dWd = act^T * dy           [F,H]
 
     void* dh2 = w.bufHb;
     {   // dh2 = d_gate*Wg^T + d_up*Wu^T   [N,H], contraction over F twice
@@ -281,8 +279,8 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     // they come after it: no norm-recompute pass of its own).
     void* h2 = w.bufHa;
     CF_HIP(launch_rmsnorm_bwd(dt, dh2, sv.r, W.g2, idx, dy_rows, rows, H, L.rms_eps, w.dr, w.dg_partial2, st, parts, h2));
-    CF_HIP(dw(h2, d_gate, G.dwg, H, F));
-    CF_HIP(dw(h2, d_up, G.dwu, H, F));
+    dw(h2, d_gate, G.dwg, H, F);
+    dw(h2, d_up, G.dwu, H, F);
 
     // ---- attention block: r = x + attn_out*Wo ------------------------------------
     {
@@ -297,7 +295,8 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
                                  w.dk, w.dv, w.attn_ws, st, idx ? sv.attn_out : nullptr, idx ? sv.q : nullptr, sv.rope_cos,
                                  sv.rope_sin, parts);
     if (as != CF_OK) return as;
-    CF_HIP(dw(a_rows, w.dr, G.dwo, Nq, H));          // dWo = a^T * dr      [Nq,H]
+    dw(a_rows, w.dr, G.dwo, Nq, H);                  // dWo = a^T * dr      [Nq,H]
+    if (!late_dwo) CF_HIP(dw_launch(&dws[--n_dw], 1));
 
     void* dh1 = w.bufHb;
     {   // dh1 = dq*Wq^T + dk*Wk^T + dv*Wv^T
@@ -309,10 +308,10 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     void* h1 = dh1;
     CF_HIP(launch_rmsnorm_bwd(dt, dh1, sv.x, W.g1, idx, w.dr, rows, H, L.rms_eps, G.dx, w.dg_partial1, st, parts, h1));
     CF_HIP(launch_gain_grads(dt, w.dg_partial1, w.dg_partial2, rows, H, G.dg1, G.dg2, mg, st));
-    CF_HIP(dw(h1, w.dq, G.dwq, H, Nq));
-    CF_HIP(dw(h1, w.dk, G.dwk, H, Nkv));
-    CF_HIP(dw(h1, w.dv, G.dwv, H, Nkv));
-    CF_HIP(dw_launch());
+    dw(h1, w.dq, G.dwq, H, Nq);
+    dw(h1, w.dk, G.dwk, H, Nkv);
+    dw(h1, w.dv, G.dwv, H, Nkv);
+    CF_HIP(dw_launch(dws, n_dw));
     return CF_OK;
 }
 
@@ -374,7 +373,7 @@ cf_status layer_core_lora(const cf_layer_desc& L, const cf_saved& sv, const cf_w
     void* d_up = w.bufF0;
     const void* dy_rows = dy_is_full ? w.dy_k : dy;
     CF_HIP(launch_swiglu_bwd(dt, d_act, sv.gate, sv.up, idx, rows, F, d_gate, d_up, nullptr, st, parts, dy_is_full ? dy : nullptr,
-                             H, dy_is_full ? w.dy_k : nullptr));
+                             H, w.dy_k, idx));
     void* dh2 = w.bufHb;
     {
         GemmSeg s[2] = {{d_gate, W.wg, F}, {d_up, W.wu, F}};

@@ -219,13 +219,13 @@ hipError_t launch_gemm_group(int dtype, const GemmGroupProb* probs, int np, hipS
 
 // rowlocal.hip
 // act (nullable) also receives silu(gate)*up; d_gate may alias d_act.  parts: d_act may lie there; it is then summed
-// up into d_act first.  copy_src (nullable, needs idx):
-// a full-length [.., copy_cols] tensor whose kept rows the same launch copies to copy_dst
+// up into d_act first.  copy_src (nullable):
+// a [.., copy_cols] tensor whose rows copy_idx (null: the first n_rows) the same launch copies to copy_dst
 // [n_rows, copy_cols] (the compact upstream gradient that the parameter-gradient GEMM contracts over).
 hipError_t launch_swiglu_bwd(int dtype, void* d_act, const void* gate, const void* up,
                              const int32_t* idx, RowCount rows, int F, void* d_gate, void* d_up,
                              void* act, hipStream_t st, const NtParts& parts, const void* copy_src = nullptr, int copy_cols = 0,
-                             void* copy_dst = nullptr);
+                             void* copy_dst = nullptr, const int32_t* copy_idx = nullptr);
 // dx_out = res + rmsnorm_bwd(dh; x, g); dg_partial (nullable: the gains are frozen) receives the gain gradient's
 // [rmsnorm_bwd_blocks(n_rows), H] fp32 partials for launch_gain_grads.
 // h_out (nullable, [n_rows, H], may be dh): also receives the normalised rows rmsnorm(x)*g.  parts: dh may lie

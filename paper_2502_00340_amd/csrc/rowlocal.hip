@@ -15,7 +15,7 @@ __device__ __forceinline__ float sigmoidf_(float z) { return 1.0f / (1.0f + __ex
 // act (nullable) = gate * s * up, the SwiGLU product rebuilt in the same pass.
 // d_gate may alias d_act (every element is read before it is written, by the same thread).
 // copy_src (nullable): after its share of the SwiGLU elements every thread also copies its share of
-// copy_dst[j, :] = copy_src[idx[j], :] (copy_cols columns, a multiple of VN): the kept rows of the
+// copy_dst[j, :] = copy_src[copy_idx[j], :] (copy_idx null: row j; copy_cols columns, a multiple of VN): the kept rows of the
 // upstream gradient, which the down projection's parameter-gradient GEMM contracts over; folding the
 // copy in here saves the launch of a gather kernel.
 template <typename T>
@@ -26,7 +26,8 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(T* d_act,
                                                          int n_max, const int32_t* __restrict__ n_dev, int F, T* d_gate,
                                                          T* __restrict__ d_up, T* __restrict__ act,
                                                          const T* __restrict__ copy_src, int copy_cols,
-                                                         T* __restrict__ copy_dst, NtParts parts) {
+                                                         T* __restrict__ copy_dst, const int32_t* __restrict__ copy_idx,
+                                                         NtParts parts) {
     constexpr int VN = Vec<T>::N;
     // vectors are counted in 32 bits where every matrix is below 2 GiB (the bf16 layers); a 64-bit division per vector
     // is a tenth of the pass
@@ -39,7 +40,7 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(T* d_act,
             const int j = (int)(v / cvpr);
             const int c = (int)(v % cvpr) * VN;
             *reinterpret_cast<uint4*>(copy_dst + (int64_t)j * copy_cols + c) =
-                *reinterpret_cast<const uint4*>(copy_src + (int64_t)idx[j] * copy_cols + c);
+                *reinterpret_cast<const uint4*>(copy_src + (int64_t)(copy_idx ? copy_idx[j] : j) * copy_cols + c);
         }
     }
     const Count vpr = F / VN;
@@ -327,18 +328,19 @@ static int stream_grid(int64_t vec_total) {
 
 hipError_t launch_swiglu_bwd(int dtype, void* d_act, const void* gate, const void* up,
                              const int32_t* idx, RowCount rows, int F, void* d_gate, void* d_up,
-                             void* act, hipStream_t st, const NtParts& parts, const void* copy_src, int copy_cols, void* copy_dst) {
+                             void* act, hipStream_t st, const NtParts& parts, const void* copy_src, int copy_cols, void* copy_dst,
+                             const int32_t* copy_idx) {
     const int n_rows = rows.n;
     if (n_rows <= 0) return hipSuccess;
-    if (copy_src != nullptr && idx == nullptr) return hipErrorInvalidValue;
     if (dtype == CF_F32)
         swiglu_bwd_kernel<float><<<stream_grid((int64_t)n_rows * F / 4), 256, 0, st>>>(
             (float*)d_act, (const float*)gate, (const float*)up, idx, n_rows, rows.dev, F,
-            (float*)d_gate, (float*)d_up, (float*)act, (const float*)copy_src, copy_cols, (float*)copy_dst, parts);
+            (float*)d_gate, (float*)d_up, (float*)act, (const float*)copy_src, copy_cols, (float*)copy_dst, copy_idx, parts);
     else
         swiglu_bwd_kernel<bf16_t><<<stream_grid((int64_t)n_rows * F / 8), 256, 0, st>>>(
             (bf16_t*)d_act, (const bf16_t*)gate, (const bf16_t*)up, idx, n_rows, rows.dev, F,
-            (bf16_t*)d_gate, (bf16_t*)d_up, (bf16_t*)act, (const bf16_t*)copy_src, copy_cols, (bf16_t*)copy_dst, parts);
+            (bf16_t*)d_gate, (bf16_t*)d_up, (bf16_t*)act, (const bf16_t*)copy_src, copy_cols, (bf16_t*)copy_dst, copy_idx,
+            parts);
     return hipGetLastError();
 }
 

@@ -750,11 +750,10 @@ def test_layer_main_grad_full_round_and_a_remainder(F, kept):
 @pytest.mark.parametrize("main_grad", [False, True])
 @pytest.mark.parametrize("H,Hq,Hkv,d,F", [(512, 8, 2, 64, 256), (840, 12, 4, 64, 2312), (2048, 32, 4, 64, 4864), (2048, 32, 4, 64, 5632)])
 def test_layer_parameter_gradients_in_one_launch_or_one_by_one(H, Hq, Hkv, d, F, main_grad):
-    """The seven dW products share a launch unless an output lies over an operand that the caller owns (dx over dy in a dense
-    call, here): then each goes out by itself, as soon as its operands exist.  The list's remainder of tiles is cut
+    """The seven dW products share a launch, also where an output lies over an operand that the caller owns (dx over dy in a dense
+    call, here: they read a copy of it).  The list's remainder of tiles is cut
     into quarters (first size), stays whole at the end of ragged matrices (second), is cut into halves (600 tiles) and stays whole
-    behind two full rounds (672); the single launches are cut otherwise.  Every element is summed in the order of its rows on
-    either route, so both give the same bits."""
+    behind two full rounds (672).  Both calls give the same bits."""
     shape = WL.LayerShape("one_launch", B=1, S=328, H=H, Hq=Hq, Hkv=Hkv, d=d, F=F, dtype="bf16")
     sv, W, dy = _random_layer(shape, F)
     desc = Bn.make_desc(shape.B, shape.S, H, Hq, Hkv, d, F, "bf16")

@@ -1,0 +1,98 @@
+"""Which launches a call makes, read from a captured graph that is never replayed, where that is what a rule decides:
+the results are the same either way."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2502_00340_amd import binding as Bn
+from paper_2502_00340_amd import workloads as WL
+from tests.test_gpu_parity import _random_layer, say
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+class _Dim3(C.Structure):
+    _fields_ = [("x", C.c_uint32), ("y", C.c_uint32), ("z", C.c_uint32)]
+
+
+class _KernelNode(C.Structure):     # hipKernelNodeParams
+    _fields_ = [("block", _Dim3), ("extra", C.c_void_p), ("func", C.c_void_p), ("grid", _Dim3), ("params", C.c_void_p),
+                ("shared", C.c_uint32)]
+
+
+def _hip():
+    """The HIP runtime that this process has loaded."""
+    with open("/proc/self/maps") as f:
+        return C.CDLL(next(line.split()[-1] for line in f if "libamdhip64.so" in line))
+
+
+def launches(call):
+    """Grid of every kernel that `call` launches on the current stream, in order."""
+    call()                                  # first use sets kernel attributes
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    hip, raw, n = _hip(), C.c_void_p(graph.raw_cuda_graph()), C.c_size_t(0)
+    assert hip.hipGraphGetNodes(raw, None, C.byref(n)) == 0
+    nodes = (C.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, C.byref(n)) == 0
+    grids = []
+    for node in nodes[:n.value]:
+        kind, p = C.c_int(-1), _KernelNode()
+        assert hip.hipGraphNodeGetType(C.c_void_p(node), C.byref(kind)) == 0
+        if kind.value == 0:                 # hipGraphNodeTypeKernel
+            assert hip.hipGraphKernelNodeGetParams(C.c_void_p(node), C.byref(p)) == 0
+            grids.append((p.grid.x, p.grid.y, p.grid.z))
+    return grids
+
+
+def _compact_case(S, kept, main_grad=False):
+    shape = WL.LayerShape("routes", B=1, S=S, H=512, Hq=8, Hkv=2, d=64, F=256, dtype="bf16")
+    sv, W, dy = _random_layer(shape, S)
+    mask = torch.zeros((1, S), dtype=torch.uint8, device=DEV)
+    mask[0, torch.randperm(S, generator=torch.Generator().manual_seed(kept))[:kept].to(DEV)] = 1
+    idx, cu, n_dev, n = Bn.build_keep_index(mask)
+    plan = lambda: Bn.LayerBackward(Bn.make_desc(1, S, 512, 8, 2, 64, 256, "bf16"), device=DEV, main_grad=main_grad)
+    return sv, W, Bn.gather_rows(dy, idx, n), idx, cu, n_dev, plan
+
+
+@pytest.mark.parametrize("main_grad", [False, True])
+def test_layer_output_behind_the_upstream_gradient(main_grad):
+    """A count on the device leaves open where the caller's upstream gradient ends: a parameter gradient that lies right behind its
+    rows, within the bound, and dx over them, give the bits and the number of launches of outputs elsewhere."""
+    sv, W, dyk, idx, cu, n_dev, plan = _compact_case(400, 100, main_grad)
+    roomy = torch.empty(400, 512, dtype=torch.bfloat16, device=DEV)         # rows up to the bound: nothing else lies there
+    roomy[:100] = dyk
+    dyk = roomy[:100]
+    ref = plan()
+    ref_launches = launches(lambda: ref.compact_dev(sv, W, dyk, idx, cu, n_dev))
+    for g in ref.grads.values():
+        g.zero_()
+    ref.compact_dev(sv, W, dyk, idx, cu, n_dev)
+    for where in ("dwd behind dy", "dx over dy", "dx one row into dy"):
+        say("layer, " + where)
+        p = plan()
+        buf = torch.zeros(400 * 512 * 4 + p.grads["dwd"].numel() * 4, dtype=torch.uint8, device=DEV)
+        dy2 = buf[:dyk.numel() * 2].view(torch.bfloat16).view(dyk.shape)
+        if where == "dwd behind dy":
+            g = p.grads["dwd"]
+            at = dyk.numel() * 2
+            p.grads["dwd"] = buf[at:at + g.numel() * g.element_size()].view(g.dtype).view(g.shape)
+            p._g.dwd = p.grads["dwd"].data_ptr()
+        else:
+            at = 0 if where == "dx over dy" else 512 * 2
+            p.grads["dx"] = buf[at:at + 400 * 512 * 2].view(torch.bfloat16).view(400, 512)
+            p._g.dx = p.grads["dx"].data_ptr()
+        call = lambda: p.compact_dev(sv, W, dy2, idx, cu, n_dev)
+        assert len(launches(call)) == len(ref_launches)
+        for g in p.grads.values():
+            g.zero_()
+        dy2.copy_(dyk)
+        call()
+        torch.cuda.synchronize()
+        for k in ref.grads:
+            a, b = (t[:100] if k == "dx" else t for t in (p.grads[k], ref.grads[k]))
+            assert torch.equal(a, b), (where, k)
