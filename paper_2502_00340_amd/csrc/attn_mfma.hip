@@ -59,8 +59,9 @@ struct AttnParams {
     float* dq_part;                // [ranges][n_kept][Hq*d] fp32 partials (more than one range only)
     // Key ranges that the dQ blocks of a query tile share out (see attn_dq_plan): seven limits of 9 bits, the k-th one the most
     // 128-row tiles with which k + 2 ranges or more are taken.  One word next to the sizes: with the rule itself
-    // evaluated here instead a call took 1.1 us more (of 16 at S = 384).
-    uint64_t dq_limits;
+    // evaluated here instead a call took 1.1 us more (of 16 at S = 384).  One word for each of the dQ kernel's tiles: a chain on coarse
+    // tiles takes longer.
+    uint64_t dq_limits_fine, dq_limits_coarse;
     int dq_fine_rows;              // up to this many live rows the dQ blocks take tiles of 64 queries (see attn_dq_kernel)
     int dkv_fine_rows;             // up to this many live rows the dK/dV blocks at d = 64 take tiles of 64 keys (attn_dkv64_kernel)
     int n_slots;                   // dK/dV blocks that the device holds at a time (the kernel sizes its blocks' work by it)
@@ -110,19 +111,21 @@ static int attn_dq_fine_rows(const cf_layer_desc& L) {
 // Key ranges per query tile of the dQ kernel.  Where a batch of few heads (a tensor-parallel share) has few query tiles, each
 // of them is a serial chain on a CU of its own: several blocks per tile, one per range of keys, shorten it, at the price of
 // fp32 partials and their sum: [2662 of 7479 rows, 4/1 heads, d = 128] 184 -> 75 us on 84 tiles.
-// The most ranges that a batch shape may take, which grid and workspace are sized for: at least 128 keys in a range, about
-// four blocks per CU; with more than one tile per CU at least 1536 keys; none above two.
-static int attn_dq_split(const cf_layer_desc& L) {
+// The most ranges that a batch shape may take, which grid and workspace are sized for: at least 128 keys in a range (192 on
+// coarse tiles), about four blocks per CU; with more than one tile per CU at least 1536 keys; none above two.
+static int attn_dq_split(const cf_layer_desc& L, bool fine = true) {
     const int64_t tiles = (int64_t)L.Hq * L.B * ceil_div(L.S, 128), n_cu = compute_units();
     if (tiles > 2 * n_cu) return 1;
     int64_t n = 4 * n_cu / tiles;
-    const int64_t longest = L.S / (tiles <= n_cu ? 128 : 1536);
+    const int64_t longest = L.S / (tiles <= n_cu ? (fine ? 128 : 192) : 1536);
     if (n > longest) n = longest;
     return n < 1 ? 1 : (n > DQ_MAX_RANGES ? DQ_MAX_RANGES : (int)n);
 }
 
 // The ranges that a call takes of them.  What the partials cost goes with the live rows: 8 bytes per element and range,
-// written and read at about 3.5 TB/s, against the chain of S keys, 6.6 ns * d per 64 of them on fine tiles.  Without KV groups the split
+// written and read at about 3.5 TB/s, against the chain of S keys, 6.6 ns * d per 64 of them on fine tiles, 9.4 on coarse ones.  (With the
+// fine tiles' 6.6 for both, coarse calls were split too little: [4200 rows, 12/4 heads, d = 64] 171 us whole and 154 in two ranges,
+// [3481 of 4096, 16/16] 148 and 139.)  Without KV groups the split
 // also costs a launch that would not be there otherwise, about 1 us; with them that launch is there and gains 1 us by a dQ kernel
 // that ends sooner.  A gain below 1/64 of the chain is none.  (Decided from the batch shape alone, calls that keep
 // most of their tokens were split as far as sparse ones: 32/32 heads, d = 128, S = 1024, all kept, four ranges 88 us, none 69.
@@ -133,11 +136,11 @@ static int attn_dq_split(const cf_layer_desc& L) {
 // equals, is k or more exactly if some j >= k gains more than every i < k, which is a limit on part and so on the rows.  These
 // limits, in tiles of 128 rows (of which a batch that may be split has 512 at most), go to the kernels.
 // Returns the ranges that the grid needs: those taken where the host knows the rows, the most there may be where it does not.
-static int attn_dq_plan(const cf_layer_desc& L, const RowCount& rows, uint64_t& limits) {
+static int attn_dq_plan(const cf_layer_desc& L, const RowCount& rows, bool fine, uint64_t& limits) {
     limits = 0;
-    const int cap = attn_dq_split(L);
+    const int cap = attn_dq_split(L, fine);
     if (cap == 1) return 1;                         // from here on S <= 64 K
-    const int chain = L.S * 105 / 64, launch = (L.Hq == L.Hkv ? 16000 : -16000) / L.d;
+    const int chain = fine ? L.S * 105 / 64 : L.S * 75 / 32, launch = (L.Hq == L.Hkv ? 16000 : -16000) / L.d;
     int A[DQ_MAX_RANGES + 1] = {0, chain / 64};
     for (int k = 2; k <= cap; ++k) A[k] = chain - chain / k - launch;
     auto put = [&](int k, uint64_t v) { limits |= std::min<uint64_t>(v, (1 << DQ_LIMIT_BITS) - 1) << (DQ_LIMIT_BITS * (k - 2)); };
@@ -511,11 +514,11 @@ __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_
 template <int D, bool ROPE>
 __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
     extern __shared__ __align__(16) unsigned char smem[];   // [2 stages][K tile, V tile]
-    uint64_t dq_limits = p.dq_limits;
-    asm("" : "+s"(dq_limits));                  // fetched with the first arguments, not in a round trip of its own further down
+    uint64_t fine = p.dq_limits_fine, coarse = p.dq_limits_coarse;
+    asm("" : "+s"(fine), "+s"(coarse));         // fetched with the first arguments, not in a round trip of its own further down
     const int n_live = live_rows(p.n_kept, p.n_dev);
-    if (n_live <= p.dq_fine_rows) attn_dq_block<D, ROPE, true>(p, dq_limits, n_live, smem);
-    else attn_dq_block<D, ROPE, false>(p, dq_limits, n_live, smem);
+    if (n_live <= p.dq_fine_rows) attn_dq_block<D, ROPE, true>(p, fine, n_live, smem);
+    else attn_dq_block<D, ROPE, false>(p, coarse, n_live, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -1164,7 +1167,7 @@ __global__ __launch_bounds__(256) void attn_reduce_kernel(AttnParams p, int kv_b
     const int64_t stride = (int64_t)p.n_kept * heads * D;               // between two partials
     int parts;
     if (is_q) {
-        parts = dq_ranges(p.dq_limits, n_live);
+        parts = dq_ranges(n_live <= p.dq_fine_rows ? p.dq_limits_fine : p.dq_limits_coarse, n_live);
     } else {
         const int G = p.Hq / p.Hkv;
         parts = G / attn_heads_per_block(n_live, p.Hq, G, p.n_slots);
@@ -1354,8 +1357,9 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     p.rope_cos = rope_cos; p.rope_sin = rope_sin;
     p.n_kept = n_kept;
     p.n_dev = rows.dev;
-    const int dq_cap = attn_dq_plan(L, rows, p.dq_limits);
     p.dq_fine_rows = attn_dq_fine_rows(L);
+    const int cap_fine = attn_dq_plan(L, rows, true, p.dq_limits_fine), cap_coarse = attn_dq_plan(L, rows, false, p.dq_limits_coarse);
+    const int dq_cap = rows.dev ? std::max(cap_fine, cap_coarse) : (n_kept <= p.dq_fine_rows ? cap_fine : cap_coarse);
     p.dkv_fine_rows = L.d == 64 ? compute_units() * 5 / 4 / L.Hq * 128 : 0;
     p.dq_part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(partials) + attn_dkv_partial_bytes(L, n_kept));
     p.dk_part = partials;

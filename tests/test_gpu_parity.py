@@ -614,6 +614,8 @@ def test_layer_device_side_count_with_a_tight_bound_and_a_stack_without_any_host
     (1024, 32, 8, 128, 1024), (1024, 32, 8, 128, 400), (1024, 4, 1, 128, 1024),
     # dK/dV blocks by the bound T: 576, two of them per CU; by the true count fewer, one per CU
     (2304, 32, 4, 64, 400), (2304, 32, 32, 64, 1500),
+    # more rows than take fine query tiles, in two key ranges
+    (4200, 12, 4, 64, 4200), (4500, 8, 8, 128, 4300),
 ])
 def test_layer_key_ranges_follow_the_live_rows(S, Hq, Hkv, d, kept):
     """How far the dQ kernel splits the keys is decided from the live rows, by the host where it knows them and by every

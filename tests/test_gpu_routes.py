@@ -96,3 +96,21 @@ def test_layer_output_behind_the_upstream_gradient(main_grad):
         for k in ref.grads:
             a, b = (t[:100] if k == "dx" else t for t in (p.grads[k], ref.grads[k]))
             assert torch.equal(a, b), (where, k)
+
+
+def _attn_call(B, S, Hq, Hkv, d, n):
+    """cf_attn_bwd_filtered of n rows, the first n / B of every sequence."""
+    bf = lambda *s: torch.randn(s, device=DEV).to(torch.bfloat16)
+    idx = (torch.arange(B, device=DEV)[:, None] * S + torch.arange(n // B, device=DEV)).reshape(-1).int()
+    cu = torch.arange(B + 1, device=DEV, dtype=torch.int32) * (n // B)
+    q, o, do, k, v = bf(n, Hq * d), bf(n, Hq * d), bf(n, Hq * d), bf(B * S, Hkv * d), bf(B * S, Hkv * d)
+    lse = torch.full((B, Hq, S), 8.0, device=DEV)
+    desc = Bn.make_desc(B, S, 8, Hq, Hkv, d, 8, "bf16")
+    return lambda: Bn.attn_bwd_filtered(desc, q, k, v, o, lse, do, idx, cu, n)
+
+
+@pytest.mark.parametrize("S,Hq,Hkv,d,n", [(4200, 12, 4, 64, 4200), (4096, 16, 16, 64, 3481), (4500, 8, 8, 128, 4300)])
+def test_attn_key_ranges_of_coarse_tiles(S, Hq, Hkv, d, n):
+    """A chain on tiles of 128 queries takes longer than one on 64: on 256 CUs these calls take two ranges."""
+    say("attn routes S=%d Hq=%d d=%d" % (S, Hq, d))
+    assert launches(_attn_call(1, S, Hq, Hkv, d, n))[0][2] == 2
