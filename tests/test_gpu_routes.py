@@ -114,3 +114,13 @@ def test_attn_key_ranges_of_coarse_tiles(S, Hq, Hkv, d, n):
     """A chain on tiles of 128 queries takes longer than one on 64: on 256 CUs these calls take two ranges."""
     say("attn routes S=%d Hq=%d d=%d" % (S, Hq, d))
     assert launches(_attn_call(1, S, Hq, Hkv, d, n))[0][2] == 2
+
+
+@pytest.mark.parametrize("B,S,Hq,Hkv,d,n", [(8, 933, 32, 4, 64, 3352), (8, 516, 64, 8, 64, 1856), (3, 700, 24, 8, 128, 1800)])
+def test_attn_grid_has_no_fine_tiles_that_cannot_be_taken(B, S, Hq, Hkv, d, n):
+    """The host knows the rows: with more of them than take fine tiles, dQ and dK/dV have a block for every tile of 128 that a
+    sequence may fill, and no more."""
+    say("attn routes B=%d S=%d Hq=%d d=%d rows=%d" % (B, S, Hq, d, n))
+    grids = launches(_attn_call(B, S, Hq, Hkv, d, n))
+    tiles = -(-S // 128)
+    assert grids[0][:2] == (Hq * B, tiles) and grids[1] == (Hq * B * tiles, 1, 1)
