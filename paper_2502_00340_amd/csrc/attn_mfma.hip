@@ -62,7 +62,7 @@ struct AttnParams {
     // evaluated here instead a call took 1.1 us more (of 16 at S = 384).  One word for each of the dQ kernel's tiles: a chain on coarse
     // tiles takes longer.
     uint64_t dq_limits_fine, dq_limits_coarse;
-    int dq_fine_rows;              // up to this many live rows the dQ blocks take tiles of 64 queries (see attn_dq_kernel)
+    int dq_fine_above, dq_fine_rows;    // of more live rows than the first and at most the second the dQ blocks take tiles of 64 queries (see attn_dq_kernel)
     int dkv_fine_rows;             // up to this many live rows the dK/dV blocks at d = 64 take tiles of 64 keys (attn_dkv64_kernel)
     int n_slots;                   // dK/dV blocks that the device holds at a time (the kernel sizes its blocks' work by it)
     int B, S, Hq, Hkv;
@@ -103,10 +103,26 @@ __host__ __device__ inline int attn_heads_per_block(int n_rows, int Hq, int G, i
 // for twice the K/V loads.  Whole attention call on coarse and fine tiles, over 1088 calls of 4 to 64 heads: 128-255 tiles 1.14 times as
 // fast (d = 64) and 1.11 (d = 128), 256-383 tiles 1.12 and 1.06 (0.87 to 1.28), 384-511 tiles 1.03 and 0.95, more tiles
 // 0.83-0.99.  [1377 rows, 32/4 heads, d = 64, S = 1531]: dQ 36 -> 30 us (a third stage of the K/V ring: 32).
-static int attn_dq_fine_rows(const cf_layer_desc& L) {
+// At d = 128, where a CU holds two blocks, short chains of keys need more room (637 calls of one to eight sequences: fine tiles where the rows
+// alone say so 0.85 to 1.25 times as fast as coarse ones, with these lines 1.058 in the mean, the worst 0.955, at 4 heads in key ranges):
+//   * up to twelve key tiles every sequence but the first counts as 48 rows more: it ends in a part of a tile, and blocks that do not
+//     fit beside the others do not pay ([1200 rows in eight sequences, S = 300, 24/8 heads] 60.8 and 55.2 us, [450 in three, S = 300, 64/8]
+//     58.6 and 55.7; [1200 in four, S = 600, 24/8] 50.7 and 55.4; longer chains even out: [4095 in three, S = 5460, 8/8] 186 and 237);
+//   * up to four key tiles two blocks on a CU gain nothing over one: half the rows, a further sequence as 32 ([768 in four, S = 192,
+//     32/32] 31.1 and 28.8; [400 in four, S = 200, 32/32] 24.4 and 26.5);
+//   * up to two key tiles with no second tile of queries per sequence are a single short step each ([64 rows, S = 64, 24/8] 21.7 and 20.6,
+//     S = 128 22.6 and 22.1; [90 rows, S = 90] 24.5 and 25.4).
+static void attn_dq_fine_rows(const cf_layer_desc& L, int& above, int& rows) {
     const int n_cu = compute_units();
-    return (L.d == 64 ? n_cu * 3 / 2 : n_cu) / L.Hq * 128;
+    above = 0;
+    rows = (L.d == 64 ? n_cu * 3 / 2 : n_cu) / L.Hq * 128;
+    if (L.d == 64) return;
+    const int64_t more = L.B - 1;
+    if (L.S <= 256) rows = (int)std::max<int64_t>(rows / 2 - 32 * more, 0);
+    else if (L.S <= 768) rows = (int)std::max<int64_t>(std::min<int64_t>(rows, n_cu * 128 / L.Hq - 48 * more), 0);
+    if (L.S <= 128) above = (int)std::min<int64_t>((int64_t)64 * L.B, INT32_MAX);
 }
+__host__ __device__ inline bool attn_dq_fine(const AttnParams& p, int n_live) { return n_live > p.dq_fine_above && n_live <= p.dq_fine_rows; }
 
 // Key ranges per query tile of the dQ kernel.  Where a batch of few heads (a tensor-parallel share) has few query tiles, each
 // of them is a serial chain on a CU of its own: several blocks per tile, one per range of keys, shorten it, at the price of
@@ -517,7 +533,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
     uint64_t fine = p.dq_limits_fine, coarse = p.dq_limits_coarse;
     asm("" : "+s"(fine), "+s"(coarse));         // fetched with the first arguments, not in a round trip of its own further down
     const int n_live = live_rows(p.n_kept, p.n_dev);
-    if (n_live <= p.dq_fine_rows) attn_dq_block<D, ROPE, true>(p, fine, n_live, smem);
+    if (attn_dq_fine(p, n_live)) attn_dq_block<D, ROPE, true>(p, fine, n_live, smem);
     else attn_dq_block<D, ROPE, false>(p, coarse, n_live, smem);
 }
 
@@ -1167,7 +1183,7 @@ __global__ __launch_bounds__(256) void attn_reduce_kernel(AttnParams p, int kv_b
     const int64_t stride = (int64_t)p.n_kept * heads * D;               // between two partials
     int parts;
     if (is_q) {
-        parts = dq_ranges(n_live <= p.dq_fine_rows ? p.dq_limits_fine : p.dq_limits_coarse, n_live);
+        parts = dq_ranges(attn_dq_fine(p, n_live) ? p.dq_limits_fine : p.dq_limits_coarse, n_live);
     } else {
         const int G = p.Hq / p.Hkv;
         parts = G / attn_heads_per_block(n_live, p.Hq, G, p.n_slots);
@@ -1330,12 +1346,12 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
     }
     // Fine tiles in the grid only where they may be taken: what a block without work costs adds up ([3352 rows in eight sequences, S =
     // 933, 32/4 heads, d = 64]: 97 us with a row of blocks for every fine tile, 92 without).
-    auto fine_tiles = [&](int fine_rows) {
-        return p.n_dev == nullptr && n_kept > fine_rows ? 0 : ceil_div(std::min(max_per_seq, fine_rows), 64);
+    auto fine_tiles = [&](bool taken, int fine_rows) {
+        return p.n_dev == nullptr && !taken ? 0 : ceil_div(std::min(max_per_seq, fine_rows), 64);
     };
-    const int dq_tiles = std::max(tiles, fine_tiles(p.dq_fine_rows));
+    const int dq_tiles = std::max(tiles, fine_tiles(attn_dq_fine(p, n_kept), p.dq_fine_rows));
     attn_dq_kernel<D, ROPE><<<dim3(p.Hq * p.B, dq_tiles, dq_cap), 256, smem_dq, st>>>(p);
-    const int dkv_tiles = paired ? std::max(tiles, fine_tiles(p.dkv_fine_rows)) : tiles;
+    const int dkv_tiles = paired ? std::max(tiles, fine_tiles(n_kept <= p.dkv_fine_rows, p.dkv_fine_rows)) : tiles;
     dkv<<<dim3(p.Hq * p.B * dkv_tiles), 256, smem_dkv, st>>>(p);
     const int kv_blocks = p.Hq != p.Hkv ? ceil_div((int64_t)n_kept * p.Hkv * D / 8, 256) : 0;
     const int q_blocks = dq_cap > 1 ? ceil_div((int64_t)n_kept * p.Hq * D / 8, 256) : 0;
@@ -1362,9 +1378,9 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     p.rope_cos = rope_cos; p.rope_sin = rope_sin;
     p.n_kept = n_kept;
     p.n_dev = rows.dev;
-    p.dq_fine_rows = attn_dq_fine_rows(L);
+    attn_dq_fine_rows(L, p.dq_fine_above, p.dq_fine_rows);
     const int cap_fine = attn_dq_plan(L, rows, true, p.dq_limits_fine), cap_coarse = attn_dq_plan(L, rows, false, p.dq_limits_coarse);
-    const int dq_cap = rows.dev ? std::max(cap_fine, cap_coarse) : (n_kept <= p.dq_fine_rows ? cap_fine : cap_coarse);
+    const int dq_cap = rows.dev ? std::max(cap_fine, cap_coarse) : (attn_dq_fine(p, n_kept) ? cap_fine : cap_coarse);
     p.dkv_fine_rows = L.d == 64 ? compute_units() * 5 / 4 / L.Hq * 128 : 0;
     p.dq_part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(partials) + attn_dkv_partial_bytes(L, n_kept));
     p.dk_part = partials;

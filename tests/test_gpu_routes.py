@@ -124,3 +124,16 @@ def test_attn_grid_has_no_fine_tiles_that_cannot_be_taken(B, S, Hq, Hkv, d, n):
     grids = launches(_attn_call(B, S, Hq, Hkv, d, n))
     tiles = -(-S // 128)
     assert grids[0][:2] == (Hq * B, tiles) and grids[1] == (Hq * B * tiles, 1, 1)
+
+
+@pytest.mark.parametrize("B,S,Hq,Hkv,d,n,fine", [
+    (1, 600, 64, 8, 128, 512, True), (8, 300, 24, 8, 128, 1200, False), (4, 600, 24, 8, 128, 1200, True), (8, 768, 24, 8, 128, 1024, True),
+    (8, 768, 24, 8, 128, 1032, False), (8, 776, 24, 8, 128, 1280, True), (4, 192, 32, 32, 128, 768, False), (4, 256, 32, 32, 128, 416, True),
+    (4, 256, 32, 32, 128, 420, False), (4, 257, 32, 32, 128, 880, True), (4, 257, 32, 32, 128, 884, False),
+    (2, 128, 24, 8, 128, 128, False), (2, 128, 24, 8, 128, 130, True), (2, 129, 24, 8, 128, 128, True), (8, 300, 32, 4, 64, 1536, True),
+])
+def test_attn_rows_that_take_fine_query_tiles(B, S, Hq, Hkv, d, n, fine):
+    """Lines for 256 CUs.  A grid for fine tiles has a row of blocks for every 64 rows that a sequence may hold, one for coarse tiles for
+    every 128."""
+    say("attn routes B=%d S=%d Hq=%d d=%d rows=%d" % (B, S, Hq, d, n))
+    assert launches(_attn_call(B, S, Hq, Hkv, d, n))[0][1] == -(-min(S, n) // (64 if fine else 128))
