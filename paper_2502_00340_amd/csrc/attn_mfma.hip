@@ -63,7 +63,7 @@ struct AttnParams {
     // tiles takes longer.
     uint64_t dq_limits_fine, dq_limits_coarse;
     int dq_fine_above, dq_fine_rows;    // of more live rows than the first and at most the second the dQ blocks take tiles of 64 queries (see attn_dq_kernel)
-    int dkv_fine_rows;             // up to this many live rows the dK/dV blocks at d = 64 take tiles of 64 keys (attn_dkv64_kernel)
+    int dkv_fine_above, dkv_fine_rows;  // the same for the dK/dV blocks at d = 64 and tiles of 64 keys (attn_dkv64_kernel)
     int n_slots;                   // dK/dV blocks that the device holds at a time (the kernel sizes its blocks' work by it)
     int B, S, Hq, Hkv;
     // Nullable, both or none: rotary tables [S][d/2].  dQ and dK leave rotated back to before the rotary embedding, at the original
@@ -103,26 +103,40 @@ __host__ __device__ inline int attn_heads_per_block(int n_rows, int Hq, int G, i
 // for twice the K/V loads.  Whole attention call on coarse and fine tiles, over 1088 calls of 4 to 64 heads: 128-255 tiles 1.14 times as
 // fast (d = 64) and 1.11 (d = 128), 256-383 tiles 1.12 and 1.06 (0.87 to 1.28), 384-511 tiles 1.03 and 0.95, more tiles
 // 0.83-0.99.  [1377 rows, 32/4 heads, d = 64, S = 1531]: dQ 36 -> 30 us (a third stage of the K/V ring: 32).
-// At d = 128, where a CU holds two blocks, short chains of keys need more room (637 calls of one to eight sequences: fine tiles where the rows
-// alone say so 0.85 to 1.25 times as fast as coarse ones, with these lines 1.058 in the mean, the worst 0.955, at 4 heads in key ranges):
+// Short chains of keys need more room (637 calls at d = 128, of one to eight sequences: fine tiles where the rows
+// alone say so 0.85 to 1.25 times as fast as coarse ones, with these lines 1.058 in the mean, the worst 0.955, at 4 heads in key ranges;
+// 498 calls at d = 64: 0.85 to 1.2, 1.065, 0.972):
 //   * up to twelve key tiles every sequence but the first counts as 48 rows more: it ends in a part of a tile, and blocks that do not
-//     fit beside the others do not pay ([1200 rows in eight sequences, S = 300, 24/8 heads] 60.8 and 55.2 us, [450 in three, S = 300, 64/8]
-//     58.6 and 55.7; [1200 in four, S = 600, 24/8] 50.7 and 55.4; longer chains even out: [4095 in three, S = 5460, 8/8] 186 and 237);
-//   * up to four key tiles two blocks on a CU gain nothing over one: half the rows, a further sequence as 32 ([768 in four, S = 192,
-//     32/32] 31.1 and 28.8; [400 in four, S = 200, 32/32] 24.4 and 26.5);
-//   * up to two key tiles with no second tile of queries per sequence are a single short step each ([64 rows, S = 64, 24/8] 21.7 and 20.6,
-//     S = 128 22.6 and 22.1; [90 rows, S = 90] 24.5 and 25.4).
+//     fit beside the others do not pay ([1200 rows in eight sequences, S = 300, 24/8 heads of 128] 60.8 and 55.2 us, [450 in three,
+//     S = 300, 64/8] 58.6 and 55.7, d = 64 [768 in eight, S = 320, 64/8] 1.13 times as long; [1200 in four, S = 600, 24/8 of 128] 50.7 and 55.4; longer
+//     chains even out: [4095 in three, S = 5460, 8/8] 186 and 237);
+//   * up to four key tiles further blocks on a CU gain nothing: half the rows, a further sequence as 32 ([768 in four, S = 192,
+//     32/32 of 128] 31.1 and 28.8; [400 in four, S = 200, 32/32] 24.4 and 26.5);
+//   * up to two key tiles with no second tile of queries per sequence are a single short step each ([64 rows, S = 64, 24/8 of 128] 21.7 and
+//     20.6, S = 128 22.6 and 22.1, d = 64 [64 rows, S = 64, 8/8] 12.8 and 12.4; [90 rows, S = 90, 24/8 of 128] 24.5 and 25.4).
 static void attn_dq_fine_rows(const cf_layer_desc& L, int& above, int& rows) {
-    const int n_cu = compute_units();
-    above = 0;
-    rows = (L.d == 64 ? n_cu * 3 / 2 : n_cu) / L.Hq * 128;
-    if (L.d == 64) return;
+    const int n_cu = compute_units(), tiles = L.d == 64 ? n_cu * 3 / 2 : n_cu;
     const int64_t more = L.B - 1;
+    rows = tiles / L.Hq * 128;
     if (L.S <= 256) rows = (int)std::max<int64_t>(rows / 2 - 32 * more, 0);
-    else if (L.S <= 768) rows = (int)std::max<int64_t>(std::min<int64_t>(rows, n_cu * 128 / L.Hq - 48 * more), 0);
-    if (L.S <= 128) above = (int)std::min<int64_t>((int64_t)64 * L.B, INT32_MAX);
+    else if (L.S <= 768) rows = (int)std::max<int64_t>(std::min<int64_t>(rows, tiles * 128 / L.Hq - 48 * more), 0);
+    above = L.S <= 128 ? (int)std::min<int64_t>((int64_t)64 * L.B, INT32_MAX) : 0;
 }
 __host__ __device__ inline bool attn_dq_fine(const AttnParams& p, int n_live) { return n_live > p.dq_fine_above && n_live <= p.dq_fine_rows; }
+
+// Live rows between which the dK/dV blocks at d = 64 take tiles of 64 keys: up to one and a quarter 128-key tiles per
+// CU.  Whole attention call, coarse (the better of the two kernels) and fine, over 541 calls of 4 to 64 heads:
+// up to 320 tiles 1.03 to 1.10 times as fast, 320-512 tiles 0.97 to 1.02, more 0.90-0.98.  Up to S = 1408 a sequence counts as 80 rows
+// more: it ends in a part of a tile, of which there are twice as many, and short sequences make short blocks, whose fixed cost counts
+// ([447 rows in three sequences, S = 298, 64/8 heads] 35.8 us fine and 32.8 coarse, [1086 in six, S = 362, 32/4] 1.14 times as long; [5120 in two,
+// S = 5120, 8/8] 99 and 114).  Sequences of no second tile take coarse ones ([64 rows, S = 64, 8/8] 13.3 and 12.8).  Over 298 calls
+// of one to eight sequences fine tiles are 1.028 times as fast by the rows alone, 69 calls slower, 0.86 at worst; with this 1.045, 0.978.
+static void attn_dkv_fine_rows(const cf_layer_desc& L, int& above, int& rows) {
+    rows = L.d == 64 ? compute_units() * 5 / 4 / L.Hq * 128 : 0;
+    if (L.S <= 1408) rows = (int)std::max<int64_t>(rows - (int64_t)80 * L.B, 0);
+    above = (int)std::min<int64_t>((int64_t)64 * L.B, INT32_MAX);
+}
+__host__ __device__ inline bool attn_dkv_fine(const AttnParams& p, int n_live) { return n_live > p.dkv_fine_above && n_live <= p.dkv_fine_rows; }
 
 // Key ranges per query tile of the dQ kernel.  Where a batch of few heads (a tensor-parallel share) has few query tiles, each
 // of them is a serial chain on a CU of its own: several blocks per tile, one per range of keys, shorten it, at the price of
@@ -925,9 +939,7 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
 // kernel and the pipelined one, [8192 rows, 32/32 heads, S = 2048] 274 and 322 us, [4096, 64/64, S = 1024] 177 and 212.  Fragment reads
 // run one MFMA pair ahead.  The accumulation order of every element is that of the pipelined kernel.
 // FINE: 64 keys per block; the two waves of a group of 32 keys take the first and the second 32 queries of every step, and their sums
-// meet in LDS at the end: half the step and twice the blocks, as in the dQ kernel, up to one and a quarter 128-key tiles of live rows per
-// CU.  Whole attention call, coarse (the better of this kernel and the pipelined one) and fine, over 541 calls of 4 to 64 heads:
-// up to 320 tiles 1.03 to 1.10 times as fast, 320-512 tiles 0.97 to 1.02, more 0.90-0.98.
+// meet in LDS at the end: half the step and twice the blocks, as in the dQ kernel (attn_dkv_fine_rows says where).
 template <bool ROPE, bool FINE>
 __device__ __forceinline__ void attn_dkv64_block(const AttnParams& p, const int n_live, unsigned char* smem) {
     constexpr int D = 64, KS = D / 16, NT = D / 32, KT = FINE ? 64 : 128;
@@ -1160,7 +1172,7 @@ template <bool ROPE>
 __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int n_live = live_rows(p.n_kept, p.n_dev);
-    if (n_live <= p.dkv_fine_rows) attn_dkv64_block<ROPE, true>(p, n_live, smem);
+    if (attn_dkv_fine(p, n_live)) attn_dkv64_block<ROPE, true>(p, n_live, smem);
     else attn_dkv64_block<ROPE, false>(p, n_live, smem);
 }
 
@@ -1330,7 +1342,7 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
     // Only this kernel has the fine tiles that few live rows take (dkv_fine_rows), so it also runs where they may be few, which with a
     // device-side count is always; above them it sums in the order of the pipelined one, so the choice does not show.
     const bool chains = (int64_t)p.Hq * p.B * tiles * 4 <= (int64_t)n_cu * (tiles < 12 ? 7 : 8);
-    const bool paired = D == 64 && (tiles == 1 || !chains || n_kept <= p.dkv_fine_rows || p.n_dev != nullptr);
+    const bool paired = D == 64 && (tiles == 1 || !chains || attn_dkv_fine(p, n_kept) || p.n_dev != nullptr);
     p.n_slots = n_cu * (paired ? 2 : 1);
     static std::atomic<uint64_t> lds_ok_dq{0}, lds_ok_dkv{0}, lds_ok_paired{0};
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&attn_dq_kernel<D, ROPE>), smem_dq, lds_ok_dq);
@@ -1351,7 +1363,7 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
     };
     const int dq_tiles = std::max(tiles, fine_tiles(attn_dq_fine(p, n_kept), p.dq_fine_rows));
     attn_dq_kernel<D, ROPE><<<dim3(p.Hq * p.B, dq_tiles, dq_cap), 256, smem_dq, st>>>(p);
-    const int dkv_tiles = paired ? std::max(tiles, fine_tiles(n_kept <= p.dkv_fine_rows, p.dkv_fine_rows)) : tiles;
+    const int dkv_tiles = paired ? std::max(tiles, fine_tiles(attn_dkv_fine(p, n_kept), p.dkv_fine_rows)) : tiles;
     dkv<<<dim3(p.Hq * p.B * dkv_tiles), 256, smem_dkv, st>>>(p);
     const int kv_blocks = p.Hq != p.Hkv ? ceil_div((int64_t)n_kept * p.Hkv * D / 8, 256) : 0;
     const int q_blocks = dq_cap > 1 ? ceil_div((int64_t)n_kept * p.Hq * D / 8, 256) : 0;
@@ -1381,7 +1393,7 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     attn_dq_fine_rows(L, p.dq_fine_above, p.dq_fine_rows);
     const int cap_fine = attn_dq_plan(L, rows, true, p.dq_limits_fine), cap_coarse = attn_dq_plan(L, rows, false, p.dq_limits_coarse);
     const int dq_cap = rows.dev ? std::max(cap_fine, cap_coarse) : (attn_dq_fine(p, n_kept) ? cap_fine : cap_coarse);
-    p.dkv_fine_rows = L.d == 64 ? compute_units() * 5 / 4 / L.Hq * 128 : 0;
+    attn_dkv_fine_rows(L, p.dkv_fine_above, p.dkv_fine_rows);
     p.dq_part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(partials) + attn_dkv_partial_bytes(L, n_kept));
     p.dk_part = partials;
     p.dv_part = partials ? partials + (size_t)n_kept * L.Hq * L.d : nullptr;

@@ -130,10 +130,23 @@ def test_attn_grid_has_no_fine_tiles_that_cannot_be_taken(B, S, Hq, Hkv, d, n):
     (1, 600, 64, 8, 128, 512, True), (8, 300, 24, 8, 128, 1200, False), (4, 600, 24, 8, 128, 1200, True), (8, 768, 24, 8, 128, 1024, True),
     (8, 768, 24, 8, 128, 1032, False), (8, 776, 24, 8, 128, 1280, True), (4, 192, 32, 32, 128, 768, False), (4, 256, 32, 32, 128, 416, True),
     (4, 256, 32, 32, 128, 420, False), (4, 257, 32, 32, 128, 880, True), (4, 257, 32, 32, 128, 884, False),
-    (2, 128, 24, 8, 128, 128, False), (2, 128, 24, 8, 128, 130, True), (2, 129, 24, 8, 128, 128, True), (8, 300, 32, 4, 64, 1536, True),
+    (2, 128, 24, 8, 128, 128, False), (2, 128, 24, 8, 128, 130, True), (2, 129, 24, 8, 128, 128, True), (1, 300, 64, 8, 64, 300, True),
+    (8, 300, 32, 4, 64, 1200, True), (8, 300, 32, 4, 64, 1208, False), (8, 800, 32, 4, 64, 1536, True), (4, 256, 64, 8, 64, 288, True),
+    (4, 256, 64, 8, 64, 292, False), (1, 64, 8, 8, 64, 64, False), (1, 70, 8, 8, 64, 65, True),
 ])
 def test_attn_rows_that_take_fine_query_tiles(B, S, Hq, Hkv, d, n, fine):
     """Lines for 256 CUs.  A grid for fine tiles has a row of blocks for every 64 rows that a sequence may hold, one for coarse tiles for
     every 128."""
     say("attn routes B=%d S=%d Hq=%d d=%d rows=%d" % (B, S, Hq, d, n))
     assert launches(_attn_call(B, S, Hq, Hkv, d, n))[0][1] == -(-min(S, n) // (64 if fine else 128))
+
+
+@pytest.mark.parametrize("B,S,Hq,Hkv,n,fine", [
+    (1, 1000, 64, 8, 560, True), (1, 1000, 64, 8, 561, False), (1, 1409, 64, 8, 640, True), (1, 1409, 64, 8, 641, False),
+    (3, 400, 64, 8, 399, True), (3, 400, 64, 8, 402, False), (8, 320, 32, 4, 640, True), (8, 320, 32, 4, 648, False),
+    (2, 300, 8, 8, 128, False), (2, 300, 8, 8, 130, True),
+])
+def test_attn_rows_that_take_fine_key_tiles(B, S, Hq, Hkv, n, fine):
+    """Lines for 256 CUs at d = 64; the grid as for the queries."""
+    say("attn routes B=%d S=%d Hq=%d d=64 rows=%d" % (B, S, Hq, n))
+    assert launches(_attn_call(B, S, Hq, Hkv, 64, n))[1][0] == Hq * B * -(-min(S, n) // (64 if fine else 128))
