@@ -64,6 +64,7 @@ struct AttnParams {
     uint64_t dq_limits_fine, dq_limits_coarse;
     int dq_fine_above, dq_fine_rows;    // of more live rows than the first and at most the second the dQ blocks take tiles of 64 queries (see attn_dq_kernel)
     int dkv_fine_above, dkv_fine_rows;  // the same for the dK/dV blocks at d = 64 and tiles of 64 keys (attn_dkv64_kernel)
+    int dkv_both;                  // both dK/dV kernels of d = 64 are launched: fine tiles are attn_dkv64_kernel's, others attn_dkv_kernel's
     int n_slots;                   // dK/dV blocks that the device holds at a time (the kernel sizes its blocks' work by it)
     int B, S, Hq, Hkv;
     // Nullable, both or none: rotary tables [S][d/2].  dQ and dK leave rotated back to before the rotary embedding, at the original
@@ -577,7 +578,9 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int slot = lane & 31, hh = lane >> 5;
     const int G = p.Hq / p.Hkv;
-    const int HP = attn_heads_per_block(live_rows(p.n_kept, p.n_dev), p.Hq, G, p.n_slots);
+    const int n_live = live_rows(p.n_kept, p.n_dev);
+    if (D == 64 && p.dkv_both && attn_dkv_fine(p, n_live)) return;      // attn_dkv64_kernel takes these rows
+    const int HP = attn_heads_per_block(n_live, p.Hq, G, p.n_slots);
     // The grid is one-dimensional and has a block per (key tile, sequence, query head).  Only nhb * B blocks
     // per key tile are needed; they are numbered first, key tile by key tile (heaviest first), so the blocks
     // without work all come at the end of the launch order instead of between the working ones (a block
@@ -1173,7 +1176,7 @@ __global__ __launch_bounds__(256, 2) void attn_dkv64_kernel(AttnParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int n_live = live_rows(p.n_kept, p.n_dev);
     if (attn_dkv_fine(p, n_live)) attn_dkv64_block<ROPE, true>(p, n_live, smem);
-    else attn_dkv64_block<ROPE, false>(p, n_live, smem);
+    else if (!p.dkv_both) attn_dkv64_block<ROPE, false>(p, n_live, smem);
 }
 
 // acc += part[0..3], part[half..half+3]
@@ -1339,16 +1342,25 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
     // 12 tiles are too short for that to make up for two full rounds ([4096, 16/16, S = 1024: 512] 55 and 58 us).
     // On a single tile the two take the same time, and the plain one less for a few rows
     // (13 rows, 16/16: 6.2 and 6.5 us).
-    // Only this kernel has the fine tiles that few live rows take (dkv_fine_rows), so it also runs where they may be few, which with a
-    // device-side count is always; above them it sums in the order of the pipelined one, so the choice does not show.
+    // Only the plain kernel has the fine tiles that few live rows take (attn_dkv_fine_rows).  Both sum in the same order on coarse tiles and walk
+    // through one head per block where chains decide, so the choice does not show.  With a device-side count either may be
+    // needed: chains of 20 tiles and more launch both, and one of them leaves at once.  Layer calls, plain alone, both, pipelined alone: [7296 of
+    // 7680 rows, 8/8 heads] 452, 428, 428 us, [4500 of 4736, 12/4] 332, 322, 320, on fine tiles [3840 of 7680] 258, 260, 273, [1600 of 3200,
+    // 16/16] 164, 166, 171.  With fewer tiles the pipelined kernel gains no more than a launch costs ([1946 of 2048, 32/4] 213.4 and 212.6).
     const bool chains = (int64_t)p.Hq * p.B * tiles * 4 <= (int64_t)n_cu * (tiles < 12 ? 7 : 8);
-    const bool paired = D == 64 && (tiles == 1 || !chains || attn_dkv_fine(p, n_kept) || p.n_dev != nullptr);
-    p.n_slots = n_cu * (paired ? 2 : 1);
+    bool paired = D == 64;
+    p.dkv_both = 0;
+    if (D == 64 && chains && tiles > 1) {
+        paired = p.n_dev == nullptr ? attn_dkv_fine(p, n_kept) : std::min(n_kept, p.dkv_fine_rows) > p.dkv_fine_above;
+        p.dkv_both = paired && n_kept > p.dkv_fine_rows && tiles >= 20;
+    }
+    p.n_slots = n_cu * (paired && !p.dkv_both ? 2 : 1);
     static std::atomic<uint64_t> lds_ok_dq{0}, lds_ok_dkv{0}, lds_ok_paired{0};
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&attn_dq_kernel<D, ROPE>), smem_dq, lds_ok_dq);
     if (e != hipSuccess) return e;
-    void (*const dkv)(AttnParams) = paired ? attn_dkv64_kernel<ROPE> : attn_dkv_kernel<D, ROPE>;
-    e = allow_dynamic_lds(reinterpret_cast<const void*>(dkv), smem_dkv, paired ? lds_ok_paired : lds_ok_dkv);
+    if (paired) e = allow_dynamic_lds(reinterpret_cast<const void*>(&attn_dkv64_kernel<ROPE>), smem_dkv, lds_ok_paired);
+    if (e == hipSuccess && (!paired || p.dkv_both))
+        e = allow_dynamic_lds(reinterpret_cast<const void*>(&attn_dkv_kernel<D, ROPE>), smem_dkv, lds_ok_dkv);
     if (e != hipSuccess) return e;
     if (p.o_kept == nullptr) {
         const int64_t total = (int64_t)n_kept * p.Hq * (D / 8);
@@ -1363,8 +1375,11 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
     };
     const int dq_tiles = std::max(tiles, fine_tiles(attn_dq_fine(p, n_kept), p.dq_fine_rows));
     attn_dq_kernel<D, ROPE><<<dim3(p.Hq * p.B, dq_tiles, dq_cap), 256, smem_dq, st>>>(p);
-    const int dkv_tiles = paired ? std::max(tiles, fine_tiles(attn_dkv_fine(p, n_kept), p.dkv_fine_rows)) : tiles;
-    dkv<<<dim3(p.Hq * p.B * dkv_tiles), 256, smem_dkv, st>>>(p);
+    if (paired) {
+        const int dkv_tiles = std::max(p.dkv_both ? 1 : tiles, fine_tiles(attn_dkv_fine(p, n_kept), p.dkv_fine_rows));
+        attn_dkv64_kernel<ROPE><<<dim3(p.Hq * p.B * dkv_tiles), 256, smem_dkv, st>>>(p);
+    }
+    if (!paired || p.dkv_both) attn_dkv_kernel<D, ROPE><<<dim3(p.Hq * p.B * tiles), 256, smem_dkv, st>>>(p);
     const int kv_blocks = p.Hq != p.Hkv ? ceil_div((int64_t)n_kept * p.Hkv * D / 8, 256) : 0;
     const int q_blocks = dq_cap > 1 ? ceil_div((int64_t)n_kept * p.Hq * D / 8, 256) : 0;
     if (kv_blocks + q_blocks > 0) attn_reduce_kernel<D, ROPE><<<kv_blocks + q_blocks, 256, 0, st>>>(p, kv_blocks);

@@ -618,6 +618,8 @@ def test_layer_device_side_count_with_a_tight_bound_and_a_stack_without_any_host
     (2304, 32, 4, 64, 400), (2304, 32, 32, 64, 1500),
     # more rows than take fine query tiles, in two key ranges
     (4200, 12, 4, 64, 4200), (4500, 8, 8, 128, 4300),
+    # two dK/dV launches with a count on the device, at the line between them and well to either side
+    (2688, 16, 16, 64, 2560), (2688, 16, 16, 64, 2561), (2688, 16, 4, 64, 500), (2688, 16, 4, 64, 40),
 ])
 def test_layer_key_ranges_follow_the_live_rows(S, Hq, Hkv, d, kept):
     """How far the dQ kernel splits the keys is decided from the live rows, by the host where it knows them and by every

@@ -150,3 +150,16 @@ def test_attn_rows_that_take_fine_key_tiles(B, S, Hq, Hkv, n, fine):
     """Lines for 256 CUs at d = 64; the grid as for the queries."""
     say("attn routes B=%d S=%d Hq=%d d=64 rows=%d" % (B, S, Hq, n))
     assert launches(_attn_call(B, S, Hq, Hkv, 64, n))[1][0] == Hq * B * -(-min(S, n) // (64 if fine else 128))
+
+
+@pytest.mark.parametrize("S,Hq,max_kept,kernels", [(4224, 12, None, 2), (2560, 16, None, 1), (2688, 16, None, 2), (2688, 16, 2560, 1),
+                                                   (2048, 32, None, 1), (8448, 8, None, 1)])
+def test_layer_dkv_launches_with_a_count_on_the_device(S, Hq, max_kept, kernels):
+    """Grouped heads of 64 on 256 CUs: one launch, the plain kernel, where the pipelined one gains no more than a launch (2048 rows),
+    where the rows up to the bound take fine tiles (2560) and where chains do not decide (528 tiles); both in between."""
+    say("layer routes S=%d Hq=%d max_kept=%s" % (S, Hq, max_kept))
+    shape = WL.LayerShape("dkv_routes", B=1, S=S, H=64, Hq=Hq, Hkv=4, d=64, F=64, dtype="bf16")
+    sv, W, dy = _random_layer(shape, S)
+    idx, cu, n_dev, n = Bn.build_keep_index(torch.ones((1, S), dtype=torch.uint8, device=DEV))
+    plan = Bn.LayerBackward(Bn.make_desc(1, S, 64, Hq, 4, 64, 64, "bf16"), device=DEV, max_kept=max_kept)
+    assert len(launches(lambda: plan.compact_dev(sv, W, dy, idx, cu, n_dev))) == 12 + kernels
