@@ -127,14 +127,14 @@ __host__ __device__ inline bool attn_dq_fine(const AttnParams& p, int n_live) { 
 
 // Live rows between which the dK/dV blocks at d = 64 take tiles of 64 keys: up to one and a quarter 128-key tiles per
 // CU.  Whole attention call, coarse (the better of the two kernels) and fine, over 541 calls of 4 to 64 heads:
-// up to 320 tiles 1.03 to 1.10 times as fast, 320-512 tiles 0.97 to 1.02, more 0.90-0.98.  Up to S = 1408 a sequence counts as 80 rows
-// more: it ends in a part of a tile, of which there are twice as many, and short sequences make short blocks, whose fixed cost counts
+// up to 320 tiles 1.03 to 1.10 times as fast, 320-512 tiles 0.97 to 1.02, more 0.90-0.98.  Up to S = 768 a sequence counts as 80 rows more,
+// up to 1408 every one but the first: it ends in a part of a tile, of which there are twice as many, and short sequences make short blocks, whose fixed cost counts
 // ([447 rows in three sequences, S = 298, 64/8 heads] 35.8 us fine and 32.8 coarse, [1086 in six, S = 362, 32/4] 1.14 times as long; [5120 in two,
-// S = 5120, 8/8] 99 and 114).  Sequences of no second tile take coarse ones ([64 rows, S = 64, 8/8] 13.3 and 12.8).  Over 298 calls
+// S = 5120, 8/8] 99 and 114; layer call, [1216 of 1280, 32/4] 149 and 156).  Sequences of no second tile take coarse ones ([64 rows, S = 64, 8/8] 13.3 and 12.8).  Over 298 calls
 // of one to eight sequences fine tiles are 1.028 times as fast by the rows alone, 69 calls slower, 0.86 at worst; with this 1.045, 0.978.
 static void attn_dkv_fine_rows(const cf_layer_desc& L, int& above, int& rows) {
     rows = L.d == 64 ? compute_units() * 5 / 4 / L.Hq * 128 : 0;
-    if (L.S <= 1408) rows = (int)std::max<int64_t>(rows - (int64_t)80 * L.B, 0);
+    if (L.S <= 1408) rows = (int)std::max<int64_t>(rows - (int64_t)80 * (L.S <= 768 ? L.B : L.B - 1), 0);
     above = (int)std::min<int64_t>((int64_t)64 * L.B, INT32_MAX);
 }
 __host__ __device__ inline bool attn_dkv_fine(const AttnParams& p, int n_live) { return n_live > p.dkv_fine_above && n_live <= p.dkv_fine_rows; }
