@@ -918,7 +918,10 @@ static constexpr int GROUP_Q = 40;
 // ... or when the longest contraction gets shorter by fewer than g.gain steps: a step is 0.35 to 0.5 us, against the launch that sums
 // the parts up and their slots (GROUP_GAIN; GROUP_GAIN_ONE for a single product, whose sum is smaller).  Four products
 // [4096, 64] of 48 and 16 steps, 128 tiles: 24 + 13 us in two parts, 33 whole; three of 48 steps, 96 tiles: 23 + 10 and 28; one, 32
-// tiles: 16 + 6 in eight parts, 28 whole.  (Every launch that fits was cut before.)
+// tiles: 16 + 6 in eight parts, 28 whole.  Contractions of up to 32 steps are faster whole whatever the rows (layer calls: H = 840, 215 rows 149
+// and 172 us, H = 2048, 150 rows 167 and 172).  Those of 48 steps would be faster in four parts and more, which a batch of up to 1900 rows
+// allows (H = 3072: 100 rows 202 and 210, 900 443 and 452, 1900 809 and 817), but with the count on the device their sums would have
+// to be launched for longer batches too, where nothing is cut ([4096, 3072] 1216 and 1210, [4096 of 8192 in one sequence] 1436 and 1428).
 __host__ __device__ inline int group_steps(const GroupArgs& g, int n_live) {        // of the longest contraction
     int most = 0;
 #pragma unroll
