@@ -243,8 +243,8 @@ def gather_rows(src: torch.Tensor, idx: torch.Tensor, n_rows: int, out: torch.Te
 
 
 @functools.lru_cache(maxsize=1024)
-def _linear_ws_bytes(n_kept, in_f, out_f, code):
-    """A function of the sizes alone (and of the GPU's kind)."""
+def _linear_ws_bytes(n_kept, in_f, out_f, code, device):
+    """A function of the sizes and of the current device, whose compute units the library asks for."""
     return lib().cf_linear_workspace_bytes(n_kept, in_f, out_f, code)
 
 
@@ -262,7 +262,7 @@ def linear_bwd_reduced(x_kept, dy_kept, w, need_dx=True, need_dw=True, dw_accumu
         else:
             dw = torch.empty((in_f, out_f), dtype=dy_kept.dtype, device=dev)
     code = _dtype_code(dy_kept)
-    wsb = _linear_ws_bytes(n_kept, in_f, out_f, code) if need_dx else 0
+    wsb = _linear_ws_bytes(n_kept, in_f, out_f, code, torch.cuda.current_device()) if need_dx else 0
     ws = torch.empty(wsb, dtype=torch.uint8, device=dev) if wsb else None
     at = _addr if n_kept and in_f and out_f else _ptr          # with all sizes no tensor is empty
     _check((_lib or lib()).cf_linear_bwd_reduced_ws(at(x_kept), at(dy_kept), at(w), n_kept, in_f, out_f, code, at(dx), at(dw),

@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_2502_00340_amd import binding as Bn
 
@@ -234,3 +235,30 @@ def test_product_path_does_not_import_the_oracle():
             if fn.endswith((".py", ".hip", ".h", ".cpp")):
                 text = open(os.path.join(dirpath, fn)).read()
                 assert "oracle" not in text.replace("the CPU oracle's tests", ""), fn
+
+
+def test_linear_scratch_of_unlike_devices(monkeypatch):
+    """The library sizes the scratch for the current device's compute units; one device's answer is not another one's."""
+    asked = []
+
+    class Lib:
+        def cf_linear_workspace_bytes(self, n, i, o, code):
+            asked.append(current[0])
+            return (256, 128)[current[0]] * 65536 + 256
+
+        def cf_linear_bwd_reduced_ws(self, x, dy, w, n, i, o, code, dx, dw, beta, ws, ws_bytes, stream):
+            assert ws_bytes == (256, 128)[current[0]] * 65536 + 256
+            return 0
+
+    current = [0]
+    monkeypatch.setattr(Bn, "_lib", Lib())
+    monkeypatch.setattr(Bn, "_stream", lambda: None)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: current[0])
+    t = lambda *s: torch.zeros(s, dtype=torch.bfloat16)
+    Bn._linear_ws_bytes.cache_clear()
+    try:
+        for current[0] in (0, 1, 0, 1):
+            Bn.linear_bwd_reduced(t(24, 40), t(24, 56), t(40, 56))
+    finally:
+        Bn._linear_ws_bytes.cache_clear()
+    assert asked == [0, 1]
