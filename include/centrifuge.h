@@ -138,13 +138,16 @@ cf_status cf_build_keep_index(const uint8_t* mask, int32_t B, int32_t S,
                               int32_t* idx, int32_t* cu_kept, int32_t* n_kept_dev,
                               int32_t* n_kept_host, void* ws, size_t ws_bytes, cf_stream stream);
 
+/* Masks of up to this many tokens are indexed in one launch that touches neither a workspace nor the library's own array. */
+#define CF_INDEX_NO_SCRATCH_TOKENS 32768
+
 /* The keep-index build for callers that cannot allocate device memory or carry a workspace
  * (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).  Same
  * arguments and results as cf_build_keep_index without the workspace and without the host copy:
  * what the first of two launches leaves for the second (a count per 8192 tokens and a bit per token) lives in a device array
  * built into the library (2.1 MB per GPU, held until the process ends), nothing is allocated, freed or copied to the host and the stream is not
  * synchronised.  At most 2^24 tokens (B*S); more returns CF_ERR_UNSUPPORTED before any launch.
- * All calls on one GPU of more than 32768 tokens share that array: such calls that overlap on one GPU (two streams, two host
+ * All calls on one GPU of more than CF_INDEX_NO_SCRATCH_TOKENS tokens share that array: such calls that overlap on one GPU (two streams, two host
  * threads) race and must be serialised by the caller.  Shorter masks are indexed in one launch that does not touch it. */
 cf_status cf_build_keep_index_static(const uint8_t* mask, int32_t B, int32_t S,
                                      int32_t* idx, int32_t* cu_kept, int32_t* n_kept_dev,

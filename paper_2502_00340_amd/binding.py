@@ -193,7 +193,7 @@ def torch_dtype(desc: LayerDesc):
 # entry points (same names as the C ABI, without the prefix)
 # --------------------------------------------------------------------------
 
-_INDEX_NO_SCRATCH = 32768       # tokens that the library indexes in one launch wherever the mask lies
+_INDEX_NO_SCRATCH = 32768       # CF_INDEX_NO_SCRATCH_TOKENS of the header
 
 
 def build_keep_index(mask: torch.Tensor, sync: bool = True):

@@ -11,6 +11,9 @@ static constexpr int IDX_CHUNK = IDX_THREADS * IDX_PER_THREAD;   // tokens per b
 // in loads that are in flight together, which a byte-wise mask (not on a 16-byte boundary) has no such loads for.
 // One launch and two: 64 K tokens 6.4 and 8.0 us, 128 K 7.7 and 8.1 (and a launch's host time), 256 K 10.2 and 8.1.
 static constexpr int IDX_SELF_COUNT_MAX_BLOCKS = 32, IDX_SELF_COUNT_MAX_UNALIGNED = 8;
+static_assert(IDX_SELF_COUNT_MAX_UNALIGNED <= IDX_SELF_COUNT_MAX_BLOCKS &&
+                  IDX_SELF_COUNT_MAX_UNALIGNED * IDX_CHUNK >= CF_INDEX_NO_SCRATCH_TOKENS,
+              "the header promises one launch without scratch, wherever the mask lies");
 
 // number of non-zero bytes among 16 mask bytes starting at t0 (bytes >= T read as 0)
 __device__ __forceinline__ void load_flags(const uint8_t* mask, int64_t t0, int64_t T, bool aligned,

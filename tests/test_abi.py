@@ -34,6 +34,12 @@ def test_header_symbols_are_exported(L):
         assert getattr(L, n) is not None, n
 
 
+def test_index_without_scratch_goes_by_the_headers_bound():
+    """Where the binding calls the entry point without a workspace, the library must not fall back on its shared array."""
+    text = open(os.path.join(ROOT, "include", "centrifuge.h")).read()
+    assert Bn._INDEX_NO_SCRATCH == int(re.search(r"#define CF_INDEX_NO_SCRATCH_TOKENS (\d+)", text).group(1))
+
+
 def test_status_strings(L):
     assert L.cf_status_str(0) == b"ok"
     for code in range(1, 7):

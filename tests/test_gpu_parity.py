@@ -77,6 +77,20 @@ def test_keep_index_on_both_sides_of_the_second_launch(B, S, off):
         assert np.array_equal(cu.cpu().numpy(), rcu) and np.array_equal(idx[:n].cpu().numpy(), np.flatnonzero(mask))
 
 
+@pytest.mark.parametrize("off", [0, 3])
+@pytest.mark.parametrize("B,S", [(1, 1), (8, 4096), (1, 32769)])
+def test_keep_index_without_a_host_count(B, S, off):
+    """sync=False: up to 32768 tokens without a workspace, one more token with one."""
+    say("keep_index, no sync B=%d S=%d off=%d" % (B, S, off))
+    mask = (np.random.default_rng(S + off).random(B * S) < 0.6).astype(np.uint8)
+    t = torch.zeros(off + B * S, dtype=torch.uint8, device=DEV)
+    t[off:] = torch.from_numpy(mask).to(DEV)
+    idx, cu, n_dev, n = Bn.build_keep_index(t[off:].view(B, S), sync=False)
+    rcu = np.concatenate([[0], np.cumsum(mask.reshape(B, S).sum(axis=1, dtype=np.int64))])
+    assert n is None and int(n_dev.item()) == rcu[-1] and np.array_equal(cu.cpu().numpy(), rcu)
+    assert np.array_equal(idx[:rcu[-1]].cpu().numpy(), np.flatnonzero(mask))
+
+
 # ---------------------------------------------------------------------------
 # A2 gather
 # ---------------------------------------------------------------------------
