@@ -929,8 +929,11 @@ def test_layer_with_rotary_embedding(dtype, mode):
     (4, 1, 128, 170, 0.6),      # dK from partials
     (2, 2, 64, 401, 0.6),       # dQ from key ranges, dK whole
     (4, 2, 128, 401, 0.4),      # both from partials
+    # more rows than take fine tiles: dQ from coarse ones; dK at d = 64 whole from the plain kernel and, dense, the pipelined one
+    (32, 32, 64, 800, 0.98), (32, 4, 64, 800, 0.98), (32, 32, 128, 600, 0.9), (32, 8, 128, 600, 0.9),
 ])
 def test_layer_rotary_embedding_wherever_dq_and_dk_are_written(Hq, Hkv, d, S, rho):
+    """Lines for 256 CUs."""
     shape = WL.LayerShape("rope_routes", B=2, S=S, H=256, Hq=Hq, Hkv=Hkv, d=d, F=128, dtype="bf16")
     say("layer rotary %d/%d d=%d S=%d" % (Hq, Hkv, d, S))
     p = Hn.Problem(shape, S + d, "independent", rho=rho, rope=True)
@@ -988,8 +991,10 @@ def _run_lora(p, lora_np, rank, mask_on=True):
 
 LORA_SHAPES = {
     "small": dict(B=2, S=224, H=256, Hq=4, Hkv=2, d=64, F=384),
-    # few tiles and contractions of 1024 and more: the grouped launches cut them into several parts, the last one ragged
-    "splitk": dict(B=2, S=640, H=1024, Hq=16, Hkv=4, d=64, F=512),
+    # few tiles and contractions of 64 and 65 steps: the grouped launches cut them into several parts, the last one ragged (H = 4104)
+    "splitk": dict(B=1, S=320, H=4104, Hq=64, Hkv=16, d=64, F=512),
+    # d_act, dh2, da and dh1 in parts (five and six segments with the rank-16 products), the grouped launches whole
+    "parts": dict(B=2, S=129, H=2048, Hq=16, Hkv=4, d=64, F=4104),
     # with every token kept 4 x 65 row tiles in one grouped launch: nothing is split and blocks take a second item
     "rows": dict(B=5, S=1664, H=128, Hq=2, Hkv=1, d=64, F=128),
 }
@@ -1151,5 +1156,4 @@ def test_layer_products_in_parts(S, rho):
 
 def test_layer_lora_products_in_parts():
     """The same products of an adapter call (five and six segments with the rank-16 ones), filtered and dense."""
-    LORA_SHAPES["parts"] = dict(S=129, **PARTS_SHAPE)
     test_layer_lora("bf16", "independent", 16, "parts")

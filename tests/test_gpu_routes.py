@@ -7,7 +7,7 @@ import torch
 
 from paper_2502_00340_amd import binding as Bn
 from paper_2502_00340_amd import workloads as WL
-from tests.test_gpu_parity import _random_layer, say
+from tests.test_gpu_parity import LORA_SHAPES, _random_layer, say
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -164,3 +164,19 @@ def test_layer_dkv_launches_with_a_count_on_the_device(S, Hq, max_kept, kernels)
     idx, cu, n_dev, n = Bn.build_keep_index(torch.ones((1, S), dtype=torch.uint8, device=DEV))
     plan = Bn.LayerBackward(Bn.make_desc(1, S, 64, Hq, 4, 64, 64, "bf16"), device=DEV, max_kept=max_kept)
     assert len(launches(lambda: plan.compact_dev(sv, W, dy, idx, cu, n_dev))) == 12 + kernels
+
+
+def test_lora_grouped_products_in_parts():
+    """A dense adapter call of 320 rows, contractions of 64 and 65 steps: t_o, the four products t_q, t_k, t_v and u_o, and the three
+    of the other orientation u_q, u_k, u_v are each summed up by a launch of 16 blocks for every tile (3, 12 and 9)."""
+    say("lora routes")
+    shape = WL.LayerShape("lora_routes", dtype="bf16", **LORA_SHAPES["splitk"])
+    sv, W, dy = _random_layer(shape, 3)
+    bf = lambda *s: torch.randn(s, device=DEV).mul_(0.02).to(torch.bfloat16)
+    lo = {"scale": 2.0}
+    for p, (i, o) in dict(q=(shape.H, shape.Nq), k=(shape.H, shape.Nkv), v=(shape.H, shape.Nkv), o=(shape.Nq, shape.H)).items():
+        lo["a" + p], lo["b" + p] = bf(i, 64), bf(64, o)
+    plan = Bn.LoraBackward(Bn.make_desc(1, shape.S, shape.H, shape.Hq, shape.Hkv, shape.d, shape.F, "bf16"), 64, device=DEV)
+    grids = [g[0] for g in launches(lambda: plan.run_async(sv, W, lo, dy, None))]
+    cut = [b for a, b in zip(grids, grids[1:]) if a == 256 and b in (16 * 3, 16 * 12, 16 * 9)]     # behind a launch of a block per CU
+    assert cut == [16 * 3, 16 * 12, 16 * 9], grids

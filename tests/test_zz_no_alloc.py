@@ -13,9 +13,11 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def _both(mask_np, idx, cu, n_dev):
+def _both(mask_np, idx, cu, n_dev, off=0):
+    """off: bytes between the mask and an aligned address"""
     B, S = mask_np.shape
-    mask = torch.from_numpy(mask_np).to(DEV)
+    mask = torch.zeros(off + B * S, dtype=torch.uint8, device=DEV)[off:].view(B, S)
+    mask.copy_(torch.from_numpy(mask_np))
     ridx, rcu, rn_dev, rn = Bn.build_keep_index(mask)          # the existing entry point (workspace argument)
     idx.fill_(-7)
     cu.fill_(-7)
@@ -38,16 +40,18 @@ def test_static_scratch_index_build_matches_the_workspace_one_on_two_calls_in_a_
     print("[case] no-alloc keep index, two calls", flush=True)
     rng = np.random.default_rng(11)
     # caller-owned buffers, sized once for the larger call
-    idx = torch.empty(3 * 40961, dtype=torch.int32, device=DEV)
+    idx = torch.empty(3 * 200001, dtype=torch.int32, device=DEV)
     cu = torch.empty(8, dtype=torch.int32, device=DEV)
     n_dev = torch.empty(1, dtype=torch.int32, device=DEV)
-    big = (rng.random((3, 40961)) < 0.5).astype(np.uint8)       # 31 blocks: the per-block counts go through the scratch
-    small = (rng.random((2, 20000)) < 0.3).astype(np.uint8)     # 10 blocks: a shorter prefix of the same scratch
+    big = (rng.random((3, 200001)) < 0.5).astype(np.uint8)      # 74 spans: counts and flag bits go through the scratch
+    small = (rng.random((2, 70001)) < 0.3).astype(np.uint8)     # 18 spans: fewer counts, and the bits elsewhere in the same scratch
     n1 = _both(big, idx, cu, n_dev)
     n2 = _both(small, idx, cu, n_dev)
     assert n1 > n2 > 0
-    tiny = (rng.random((2, 300)) < 0.5).astype(np.uint8)        # one block: no scratch at all
-    _both(tiny, idx, cu, n_dev)
+    odd = (rng.random((3, 20001)) < 0.5).astype(np.uint8)       # 8 spans, not on a 16-byte boundary: two launches from 32769 tokens on
+    _both(odd, idx, cu, n_dev, off=5)
+    for B, S in ((3, 40961), (2, 20000), (2, 300)):             # 31, 10 and one chunk: one launch, no scratch
+        _both((rng.random((B, S)) < 0.5).astype(np.uint8), idx, cu, n_dev)
 
 
 def test_static_scratch_index_build_at_its_maximum_size():
