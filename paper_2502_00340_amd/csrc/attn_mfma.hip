@@ -63,7 +63,7 @@ struct AttnParams {
     // tiles takes longer.
     uint64_t dq_limits_fine, dq_limits_coarse;
     int dq_fine_above, dq_fine_rows;    // of more live rows than the first and at most the second the dQ blocks take tiles of 64 queries (see attn_dq_kernel)
-    int dkv_fine_above, dkv_fine_rows;  // the same for the dK/dV blocks at d = 64 and tiles of 64 keys (attn_dkv64_kernel)
+    int dkv_fine_rows;             // up to this many live rows the dK/dV blocks at d = 64 take tiles of 64 keys (attn_dkv64_kernel)
     int dkv_both;                  // both dK/dV kernels of d = 64 are launched: fine tiles are attn_dkv64_kernel's, others attn_dkv_kernel's
     int n_slots;                   // dK/dV blocks that the device holds at a time (the kernel sizes its blocks' work by it)
     int B, S, Hq, Hkv;
@@ -113,31 +113,31 @@ __host__ __device__ inline int attn_heads_per_block(int n_rows, int Hq, int G, i
 //     chains even out: [4095 in three, S = 5460, 8/8] 186 and 237);
 //   * up to four key tiles further blocks on a CU gain nothing: half the rows, a further sequence as 32 ([768 in four, S = 192,
 //     32/32 of 128] 31.1 and 28.8; [400 in four, S = 200, 32/32] 24.4 and 26.5);
-//   * up to two key tiles with no second tile of queries per sequence are a single short step each ([64 rows, S = 64, 24/8 of 128] 21.7 and
-//     20.6, S = 128 22.6 and 22.1, d = 64 [64 rows, S = 64, 8/8] 12.8 and 12.4; [90 rows, S = 90, 24/8 of 128] 24.5 and 25.4).
+//   * up to two key tiles (one at d = 64) with no second tile of queries per sequence are a single short step each ([64 rows, S = 64,
+//     24/8 of 128] 21.7 and 20.6, S = 128 22.6 and 22.1, d = 64 [64 rows, S = 64, 8/8] 12.8 and 12.4; [90 rows, S = 90, 24/8 of 128] 24.5 and 25.4).
 static void attn_dq_fine_rows(const cf_layer_desc& L, int& above, int& rows) {
     const int n_cu = compute_units(), tiles = L.d == 64 ? n_cu * 3 / 2 : n_cu;
     const int64_t more = L.B - 1;
     rows = tiles / L.Hq * 128;
     if (L.S <= 256) rows = (int)std::max<int64_t>(rows / 2 - 32 * more, 0);
     else if (L.S <= 768) rows = (int)std::max<int64_t>(std::min<int64_t>(rows, tiles * 128 / L.Hq - 48 * more), 0);
-    above = L.S <= 128 ? (int)std::min<int64_t>((int64_t)64 * L.B, INT32_MAX) : 0;
+    above = L.S <= (L.d == 64 ? 64 : 128) ? (int)std::min<int64_t>((int64_t)64 * L.B, INT32_MAX) : 0;
 }
 __host__ __device__ inline bool attn_dq_fine(const AttnParams& p, int n_live) { return n_live > p.dq_fine_above && n_live <= p.dq_fine_rows; }
 
-// Live rows between which the dK/dV blocks at d = 64 take tiles of 64 keys: up to one and a quarter 128-key tiles per
+// Live rows up to which the dK/dV blocks at d = 64 take tiles of 64 keys: up to one and a quarter 128-key tiles per
 // CU.  Whole attention call, coarse (the better of the two kernels) and fine, over 541 calls of 4 to 64 heads:
-// up to 320 tiles 1.03 to 1.10 times as fast, 320-512 tiles 0.97 to 1.02, more 0.90-0.98.  Up to S = 768 a sequence counts as 80 rows more,
-// up to 1408 every one but the first: it ends in a part of a tile, of which there are twice as many, and short sequences make short blocks, whose fixed cost counts
-// ([447 rows in three sequences, S = 298, 64/8 heads] 35.8 us fine and 32.8 coarse, [1086 in six, S = 362, 32/4] 1.14 times as long; [5120 in two,
-// S = 5120, 8/8] 99 and 114; layer call, [1216 of 1280, 32/4] 149 and 156).  Sequences of no second tile take coarse ones ([64 rows, S = 64, 8/8] 13.3 and 12.8).  Over 298 calls
-// of one to eight sequences fine tiles are 1.028 times as fast by the rows alone, 69 calls slower, 0.86 at worst; with this 1.045, 0.978.
-static void attn_dkv_fine_rows(const cf_layer_desc& L, int& above, int& rows) {
-    rows = L.d == 64 ? compute_units() * 5 / 4 / L.Hq * 128 : 0;
-    if (L.S <= 1408) rows = (int)std::max<int64_t>(rows - (int64_t)80 * (L.S <= 768 ? L.B : L.B - 1), 0);
-    above = (int)std::min<int64_t>((int64_t)64 * L.B, INT32_MAX);
+// up to 320 tiles 1.03 to 1.10 times as fast, 320-512 tiles 0.97 to 1.02, more 0.90-0.98.  Up to S = 768 a sequence counts as 80 rows
+// more, up to 1408 every one but the first: it ends in a part of a tile, of which there are twice as many, and short sequences make short
+// blocks, whose fixed cost counts ([447 rows in three sequences, S = 298, 64/8 heads] 35.8 us fine and 32.8 coarse, [1086 in six, S = 362,
+// 32/4] 1.14 times as long; [5120 in two, S = 5120, 8/8] 99 and 114; layer call, [1216 of 1280, 32/4] 149 and 156).  Over 298 calls of one to
+// eight sequences fine tiles are 1.028 times as fast by the rows alone, 69 calls slower, 0.86 at worst; with this 1.045, 0.978.  (Of the
+// rows of a single tile up to 32 gain 2 to 3 % by fine ones, 33 to 64 lose up to 1.)
+static int attn_dkv_fine_rows(const cf_layer_desc& L) {
+    const int rows = L.d == 64 ? compute_units() * 5 / 4 / L.Hq * 128 : 0;
+    return L.S > 1408 ? rows : (int)std::max<int64_t>(rows - (int64_t)80 * (L.S <= 768 ? L.B : L.B - 1), 0);
 }
-__host__ __device__ inline bool attn_dkv_fine(const AttnParams& p, int n_live) { return n_live > p.dkv_fine_above && n_live <= p.dkv_fine_rows; }
+__host__ __device__ inline bool attn_dkv_fine(const AttnParams& p, int n_live) { return n_live <= p.dkv_fine_rows; }
 
 // Key ranges per query tile of the dQ kernel.  Where a batch of few heads (a tensor-parallel share) has few query tiles, each
 // of them is a serial chain on a CU of its own: several blocks per tile, one per range of keys, shorten it, at the price of
@@ -1351,7 +1351,7 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
     bool paired = D == 64;
     p.dkv_both = 0;
     if (D == 64 && chains && tiles > 1) {
-        paired = p.n_dev == nullptr ? attn_dkv_fine(p, n_kept) : std::min(n_kept, p.dkv_fine_rows) > p.dkv_fine_above;
+        paired = p.n_dev == nullptr ? attn_dkv_fine(p, n_kept) : p.dkv_fine_rows > 0;
         p.dkv_both = paired && n_kept > p.dkv_fine_rows && tiles >= 20;
     }
     p.n_slots = n_cu * (paired && !p.dkv_both ? 2 : 1);
@@ -1408,7 +1408,7 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     attn_dq_fine_rows(L, p.dq_fine_above, p.dq_fine_rows);
     const int cap_fine = attn_dq_plan(L, rows, true, p.dq_limits_fine), cap_coarse = attn_dq_plan(L, rows, false, p.dq_limits_coarse);
     const int dq_cap = rows.dev ? std::max(cap_fine, cap_coarse) : (attn_dq_fine(p, n_kept) ? cap_fine : cap_coarse);
-    attn_dkv_fine_rows(L, p.dkv_fine_above, p.dkv_fine_rows);
+    p.dkv_fine_rows = attn_dkv_fine_rows(L);
     p.dq_part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(partials) + attn_dkv_partial_bytes(L, n_kept));
     p.dk_part = partials;
     p.dv_part = partials ? partials + (size_t)n_kept * L.Hq * L.d : nullptr;

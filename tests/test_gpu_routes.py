@@ -145,7 +145,7 @@ def test_attn_rows_that_take_fine_query_tiles(B, S, Hq, Hkv, d, n, fine):
     (1, 768, 64, 8, 560, True), (1, 768, 64, 8, 561, False), (1, 769, 64, 8, 640, True), (1, 769, 64, 8, 641, False),
     (2, 1408, 64, 8, 560, True), (2, 1408, 64, 8, 562, False), (2, 1409, 64, 8, 640, True), (2, 1409, 64, 8, 642, False),
     (3, 400, 64, 8, 399, True), (3, 400, 64, 8, 402, False), (8, 320, 32, 4, 640, True), (8, 320, 32, 4, 648, False),
-    (2, 300, 8, 8, 128, False), (2, 300, 8, 8, 130, True),
+    (1, 300, 8, 8, 130, True), (8, 320, 64, 8, 80, False),
 ])
 def test_attn_rows_that_take_fine_key_tiles(B, S, Hq, Hkv, n, fine):
     """Lines for 256 CUs at d = 64; the grid as for the queries."""
