@@ -228,7 +228,8 @@ cf_status cf_attn_bwd_filtered(const cf_layer_desc* desc, const void* q_kept, co
  * device count the filtered call returned and max_kept the bound it was given, so a whole stack of
  * layers runs without a single synchronisation.
  * ws must hold cf_layer_workspace_bytes(desc, max_kept) bytes (compact call: max_kept >= n_kept).  One workspace sized
- * for the largest B, S and max_kept serves all smaller ones too. */
+ * for the largest B, S and max_kept serves all smaller ones too; in bf16 16.8 MB of it (64 KB per compute unit) are for products in
+ * parts, which a call of few kept tokens may come to whatever the shape. */
 size_t cf_layer_workspace_bytes(const cf_layer_desc* desc, int32_t max_kept);
 cf_status cf_layer_bwd_filtered(const cf_layer_desc* desc, const cf_saved* saved,
                                 const cf_weights* w, const void* dy_full, const uint8_t* mask,

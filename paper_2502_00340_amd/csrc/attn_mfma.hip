@@ -1344,9 +1344,9 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
     // (13 rows, 16/16: 6.2 and 6.5 us).
     // Only the plain kernel has the fine tiles that few live rows take (attn_dkv_fine_rows).  Both sum in the same order on coarse tiles and walk
     // through one head per block where chains decide, so the choice does not show.  With a device-side count either may be
-    // needed: chains of 20 tiles and more launch both, and one of them leaves at once.  Layer calls, plain alone, both, pipelined alone: [7296 of
-    // 7680 rows, 8/8 heads] 452, 428, 428 us, [4500 of 4736, 12/4] 332, 322, 320, on fine tiles [3840 of 7680] 258, 260, 273, [1600 of 3200,
-    // 16/16] 164, 166, 171.  With fewer tiles the pipelined kernel gains no more than a launch costs ([1946 of 2048, 32/4] 213.4 and 212.6).
+    // needed: chains of 20 tiles and more launch both, and one of them leaves at once.  Layer calls, the plain kernel alone and both: [7296 of 7680
+    // rows, 8/8 heads] 447 and 431 us, [4500 of 4736, 12/4] 335 and 312, on fine tiles [3840 of 7680] 259 and 260, [1600 of 3200, 16/16] 166 and
+    // 169.  With fewer tiles the pipelined kernel gains no more than a launch costs ([1946 of 2048, 32/4] plain 213.4, pipelined 212.6).
     const bool chains = (int64_t)p.Hq * p.B * tiles * 4 <= (int64_t)n_cu * (tiles < 12 ? 7 : 8);
     bool paired = D == 64;
     p.dkv_both = 0;
