@@ -62,7 +62,9 @@ struct AttnParams {
     // evaluated here instead a call took 1.1 us more (of 16 at S = 384).  One word for each of the dQ kernel's tiles: a chain on coarse
     // tiles takes longer.
     uint64_t dq_limits_fine, dq_limits_coarse;
-    int dq_fine_above, dq_fine_rows;    // of more live rows than the first and at most the second the dQ blocks take tiles of 64 queries (see attn_dq_kernel)
+    // Up to the first many live rows the dQ blocks take tiles of 64 queries (see attn_dq_kernel), but for those of more than the second
+    // and at most the third.
+    int dq_fine_rows, dq_coarse_above, dq_coarse_rows;
     int dkv_fine_rows;             // up to this many live rows the dK/dV blocks at d = 64 take tiles of 64 keys (attn_dkv64_kernel)
     int dkv_both;                  // both dK/dV kernels of d = 64 are launched: fine tiles are attn_dkv64_kernel's, others attn_dkv_kernel's
     int n_slots;                   // dK/dV blocks that the device holds at a time (the kernel sizes its blocks' work by it)
@@ -104,26 +106,41 @@ __host__ __device__ inline int attn_heads_per_block(int n_rows, int Hq, int G, i
 // for twice the K/V loads.  Whole attention call on coarse and fine tiles, over 1088 calls of 4 to 64 heads: 128-255 tiles 1.14 times as
 // fast (d = 64) and 1.11 (d = 128), 256-383 tiles 1.12 and 1.06 (0.87 to 1.28), 384-511 tiles 1.03 and 0.95, more tiles
 // 0.83-0.99.  [1377 rows, 32/4 heads, d = 64, S = 1531]: dQ 36 -> 30 us (a third stage of the K/V ring: 32).
-// Short chains of keys need more room (637 calls at d = 128, of one to eight sequences: fine tiles where the rows
-// alone say so 0.85 to 1.25 times as fast as coarse ones, with these lines 1.058 in the mean, the worst 0.955, at 4 heads in key ranges;
-// 498 calls at d = 64: 0.85 to 1.2, 1.065, 0.972):
+// Several sequences need more room (993 calls at d = 128, of one to forty sequences: fine tiles where the rows alone say
+// so 0.72 to 1.39 times as fast as coarse ones, with these lines 1.061 in the mean, the worst 0.955, at 4 heads in key ranges;
+// 351 calls at d = 64: 0.77 to 1.32, 1.066, 0.962):
 //   * up to twelve key tiles every sequence but the first counts as 48 rows more: it ends in a part of a tile, and blocks that do not
 //     fit beside the others do not pay ([1200 rows in eight sequences, S = 300, 24/8 heads of 128] 60.8 and 55.2 us, [450 in three,
 //     S = 300, 64/8] 58.6 and 55.7, d = 64 [768 in eight, S = 320, 64/8] 1.13 times as long; [1200 in four, S = 600, 24/8 of 128] 50.7 and 55.4; longer
 //     chains even out: [4095 in three, S = 5460, 8/8] 186 and 237);
 //   * up to four key tiles further blocks on a CU gain nothing: half the rows, a further sequence as 32 ([768 in four, S = 192,
-//     32/32 of 128] 31.1 and 28.8; [400 in four, S = 200, 32/32] 24.4 and 26.5);
+//     32/32 of 128] 31.1 and 28.8; [400 in four, S = 200, 32/32] 24.4 and 26.5), and all of up to 128 rows a sequence where their blocks
+//     take a quarter of the slots at most ([512 in four, S = 256, 32/32] 26.5 and 28.9; eight, 32/8: 1.04 times as long);
 //   * up to two key tiles (one at d = 64) with no second tile of queries per sequence are a single short step each ([64 rows, S = 64,
 //     24/8 of 128] 21.7 and 20.6, S = 128 22.6 and 22.1, d = 64 [64 rows, S = 64, 8/8] 12.8 and 12.4; [90 rows, S = 90, 24/8 of 128] 24.5 and 25.4).
-static void attn_dq_fine_rows(const cf_layer_desc& L, int& above, int& rows) {
+// Where no sequence has a second 128-query tile, in the mean, the coarse blocks of B * Hq tiles all run from the start on two or
+// three slots per CU, and fine ones pay while they leave some free (439 calls of up to 40 such sequences, S from 300 to 2000):
+//   * 65 to 128 rows each make two blocks of every one: up to 7/8 of the slots at d = 128 (448 blocks 0.93 to 1.00 of the coarse time, 480
+//     0.97 to 1.06, 512 0.97 to 1.16, 768 1.22 to 1.35), all at d = 64 (768 0.93 to 1.00, 800 1.00 to 1.16, 1024 1.15 to 1.27);
+//   * 33 to 64 rows each as many blocks of half the work: up to 13/16 of them (d = 128: 400 and 416 blocks 0.95 to 1.03, 448 0.98 to 1.04,
+//     512 1.00 to 1.07; d = 64: 512 0.89 to 0.98, 640 1.00 to 1.06, 768 0.99 to 1.06) and again where coarse ones need a second
+//     round (0.85 to 0.98); up to 32 rows half of a block's waves have nothing to do (0.95 to 1.03 with 448 to 512 blocks).
+static void attn_dq_fine_rows(const cf_layer_desc& L, AttnParams& p) {
     const int n_cu = compute_units(), tiles = L.d == 64 ? n_cu * 3 / 2 : n_cu;
-    const int64_t more = L.B - 1;
-    rows = tiles / L.Hq * 128;
-    if (L.S <= 256) rows = (int)std::max<int64_t>(rows / 2 - 32 * more, 0);
+    const int64_t more = L.B - 1, blocks = (int64_t)L.B * L.Hq, slots = n_cu * (L.d == 64 ? 3 : 2);
+    int rows = tiles / L.Hq * 128;
+    if (L.S <= 256) rows = (int)std::max<int64_t>(rows / 2 - 32 * more, 4 * blocks <= slots ? std::min<int64_t>(rows, (int64_t)128 * L.B) : 0);
     else if (L.S <= 768) rows = (int)std::max<int64_t>(std::min<int64_t>(rows, tiles * 128 / L.Hq - 48 * more), 0);
-    above = L.S <= (L.d == 64 ? 64 : 128) ? (int)std::min<int64_t>((int64_t)64 * L.B, INT32_MAX) : 0;
+    const bool two = 2 * blocks > (L.d == 64 ? slots : slots * 7 / 8);
+    int each = blocks > slots * 13 / 16 && blocks <= slots ? 32 : 64;
+    if (L.S <= (L.d == 64 ? 64 : 128)) each = 0;
+    p.dq_fine_rows = rows;
+    p.dq_coarse_above = (int)std::min<int64_t>((int64_t)each * L.B, INT32_MAX);
+    p.dq_coarse_rows = (int)std::min<int64_t>((int64_t)(two ? 128 : 64) * L.B, INT32_MAX);
 }
-__host__ __device__ inline bool attn_dq_fine(const AttnParams& p, int n_live) { return n_live > p.dq_fine_above && n_live <= p.dq_fine_rows; }
+__host__ __device__ inline bool attn_dq_fine(const AttnParams& p, int n_live) {
+    return n_live <= p.dq_fine_rows && (n_live <= p.dq_coarse_above || n_live > p.dq_coarse_rows);
+}
 
 // Live rows up to which the dK/dV blocks at d = 64 take tiles of 64 keys: up to one and a quarter 128-key tiles per
 // CU.  Whole attention call, coarse (the better of the two kernels) and fine, over 541 calls of 4 to 64 heads:
@@ -160,8 +177,7 @@ static int attn_dq_split(const cf_layer_desc& L, bool fine = true) {
 // also costs a launch that would not be there otherwise, about 1 us; with them that launch is there and gains 1 us by a dQ kernel
 // that ends sooner.  A gain below 1/64 of the chain is none.  (Decided from the batch shape alone, calls that keep
 // most of their tokens were split as far as sparse ones: 32/32 heads, d = 128, S = 1024, all kept, four ranges 88 us, none 69.
-// Over the 1088 calls above, fine tiles with these ranges against coarse ones with the ranges fitted to them: 1.09 times as fast, two
-// below 0.97: [408 rows in four sequences, 64/8, d = 128] 64 and 72 us.)
+// Over the 1088 calls above, fine tiles with these ranges against coarse ones with the ranges fitted to them: 1.09 times as fast.)
 // In units of 1/16 ns per column: k > 1 ranges gain A(k) - k * part, A(k) = chain - chain/k - launch, part = what
 // one range's partials cost; k = 1 counts as a gain of chain / 64.  The k of the largest gain, the smaller one of
 // equals, is k or more exactly if some j >= k gains more than every i < k, which is a limit on part and so on the rows.  These
@@ -1405,7 +1421,7 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     p.rope_cos = rope_cos; p.rope_sin = rope_sin;
     p.n_kept = n_kept;
     p.n_dev = rows.dev;
-    attn_dq_fine_rows(L, p.dq_fine_above, p.dq_fine_rows);
+    attn_dq_fine_rows(L, p);
     const int cap_fine = attn_dq_plan(L, rows, true, p.dq_limits_fine), cap_coarse = attn_dq_plan(L, rows, false, p.dq_limits_coarse);
     const int dq_cap = rows.dev ? std::max(cap_fine, cap_coarse) : (attn_dq_fine(p, n_kept) ? cap_fine : cap_coarse);
     p.dkv_fine_rows = attn_dkv_fine_rows(L);

@@ -128,11 +128,18 @@ def test_attn_grid_has_no_fine_tiles_that_cannot_be_taken(B, S, Hq, Hkv, d, n):
 
 @pytest.mark.parametrize("B,S,Hq,Hkv,d,n,fine", [
     (1, 600, 64, 8, 128, 512, True), (8, 300, 24, 8, 128, 1200, False), (4, 600, 24, 8, 128, 1200, True), (8, 768, 24, 8, 128, 1024, True),
-    (8, 768, 24, 8, 128, 1032, False), (8, 776, 24, 8, 128, 1280, True), (4, 192, 32, 32, 128, 768, False), (4, 256, 32, 32, 128, 416, True),
-    (4, 256, 32, 32, 128, 420, False), (4, 257, 32, 32, 128, 880, True), (4, 257, 32, 32, 128, 884, False),
+    (8, 768, 24, 8, 128, 1032, False), (8, 776, 24, 8, 128, 1280, True), (4, 192, 32, 32, 128, 768, False), (4, 256, 32, 32, 128, 512, True),
+    (4, 256, 32, 32, 128, 516, False), (8, 256, 32, 8, 128, 288, True), (8, 256, 32, 8, 128, 296, False), (4, 257, 32, 32, 128, 880, True), (4, 257, 32, 32, 128, 884, False),
     (2, 128, 24, 8, 128, 128, False), (2, 128, 24, 8, 128, 130, True), (2, 129, 24, 8, 128, 128, True), (1, 300, 64, 8, 64, 300, True),
     (8, 300, 32, 4, 64, 1200, True), (8, 300, 32, 4, 64, 1208, False), (8, 800, 32, 4, 64, 1536, True), (4, 256, 64, 8, 64, 288, True),
     (4, 256, 64, 8, 64, 292, False), (1, 64, 8, 8, 64, 64, False), (1, 70, 8, 8, 64, 65, True),
+    # at most 128 rows in a sequence: two fine blocks for every coarse one, up to 448 (d = 128) or 768
+    (7, 800, 32, 8, 128, 700, True), (30, 800, 8, 8, 128, 1950, False), (30, 800, 8, 8, 128, 3840, False), (30, 800, 8, 8, 128, 3870, True),
+    (12, 800, 32, 8, 128, 768, True), (12, 800, 32, 8, 128, 780, False), (12, 800, 32, 4, 64, 1536, True), (13, 800, 32, 4, 64, 832, True),
+    (13, 800, 32, 4, 64, 845, False),
+    # 33 to 64: as many, which either leave slots free (416 and 624) or save a second round (from 513 and 769)
+    (13, 800, 32, 8, 128, 520, True), (14, 800, 32, 8, 128, 448, True), (14, 800, 32, 8, 128, 462, False), (14, 800, 32, 8, 128, 896, False), (17, 800, 32, 8, 128, 680, True),
+    (24, 800, 32, 4, 64, 840, False), (25, 800, 32, 4, 64, 875, True),
 ])
 def test_attn_rows_that_take_fine_query_tiles(B, S, Hq, Hkv, d, n, fine):
     """Lines for 256 CUs.  A grid for fine tiles has a row of blocks for every 64 rows that a sequence may hold, one for coarse tiles for
@@ -151,6 +158,26 @@ def test_attn_rows_that_take_fine_key_tiles(B, S, Hq, Hkv, n, fine):
     """Lines for 256 CUs at d = 64; the grid as for the queries."""
     say("attn routes B=%d S=%d Hq=%d d=64 rows=%d" % (B, S, Hq, n))
     assert launches(_attn_call(B, S, Hq, Hkv, 64, n))[1][0] == Hq * B * -(-min(S, n) // (64 if fine else 128))
+
+
+@pytest.mark.parametrize("B,S,Hq,Hkv,d,each", [(14, 776, 32, 8, 128, 32), (14, 776, 32, 8, 128, 33), (8, 776, 32, 8, 128, 64), (8, 776, 32, 8, 128, 65),
+                                               (13, 776, 32, 4, 64, 64), (13, 776, 32, 4, 64, 65)])
+def test_layer_of_sequences_with_few_rows_each(B, S, Hq, Hkv, d, each):
+    """Tiles follow the live rows: the default bound, the tight one and a host count give the same bits on both sides of a line."""
+    say("layer routes B=%d S=%d Hq=%d d=%d each=%d" % (B, S, Hq, d, each))
+    shape = WL.LayerShape("few_each", B=B, S=S, H=64, Hq=Hq, Hkv=Hkv, d=d, F=64, dtype="bf16")
+    sv, W, dy = _random_layer(shape, S + each)
+    gen = torch.Generator().manual_seed(each)
+    mask = torch.zeros(B, S, dtype=torch.uint8).scatter_(1, torch.rand(B, S, generator=gen).topk(each, 1).indices, 1).to(DEV)
+    desc, rows = Bn.make_desc(B, S, 64, Hq, Hkv, d, 64, "bf16"), B * each
+    full, tight, host = (Bn.LayerBackward(desc, device=DEV, max_kept=m) for m in (None, rows, None))
+    assert full.filtered(sv, W, dy, mask) == rows
+    tight.filtered(sv, W, dy, mask)
+    host.compact(sv, W, Bn.gather_rows(dy, full.idx, rows), full.idx, full.cu_kept, rows)
+    torch.cuda.synchronize()
+    for other in (tight, host):
+        for k, v in full.grads.items():
+            assert torch.equal(v[:rows] if k == "dx" else v, other.grads[k][:rows] if k == "dx" else other.grads[k]), k
 
 
 @pytest.mark.parametrize("S,Hq,max_kept,kernels", [(4224, 12, None, 2), (2560, 16, None, 1), (2688, 16, None, 2), (2688, 16, 2560, 1),
