@@ -65,7 +65,9 @@ struct AttnParams {
     // Up to the first many live rows the dQ blocks take tiles of 64 queries (see attn_dq_kernel), but for those of more than the second
     // and at most the third.
     int dq_fine_rows, dq_coarse_above, dq_coarse_rows;
-    int dkv_fine_rows;             // up to this many live rows the dK/dV blocks at d = 64 take tiles of 64 keys (attn_dkv64_kernel)
+    // Up to the first many live rows the dK/dV blocks at d = 64 take tiles of 64 keys (attn_dkv64_kernel), but for those of more than the
+    // second and at most the third.
+    int dkv_fine_rows, dkv_coarse_above, dkv_coarse_rows;
     int dkv_both;                  // both dK/dV kernels of d = 64 are launched: fine tiles are attn_dkv64_kernel's, others attn_dkv_kernel's
     int n_slots;                   // dK/dV blocks that the device holds at a time (the kernel sizes its blocks' work by it)
     int B, S, Hq, Hkv;
@@ -144,17 +146,23 @@ __host__ __device__ inline bool attn_dq_fine(const AttnParams& p, int n_live) {
 
 // Live rows up to which the dK/dV blocks at d = 64 take tiles of 64 keys: up to one and a quarter 128-key tiles per
 // CU.  Whole attention call, coarse (the better of the two kernels) and fine, over 541 calls of 4 to 64 heads:
-// up to 320 tiles 1.03 to 1.10 times as fast, 320-512 tiles 0.97 to 1.02, more 0.90-0.98.  Up to S = 768 a sequence counts as 80 rows
-// more, up to 1408 every one but the first: it ends in a part of a tile, of which there are twice as many, and short sequences make short
-// blocks, whose fixed cost counts ([447 rows in three sequences, S = 298, 64/8 heads] 35.8 us fine and 32.8 coarse, [1086 in six, S = 362,
-// 32/4] 1.14 times as long; [5120 in two, S = 5120, 8/8] 99 and 114; layer call, [1216 of 1280, 32/4] 149 and 156).  Over 298 calls of one to
-// eight sequences fine tiles are 1.028 times as fast by the rows alone, 69 calls slower, 0.86 at worst; with this 1.045, 0.978.  (Of the
-// rows of a single tile up to 32 gain 2 to 3 % by fine ones, 33 to 64 lose up to 1.)
-static int attn_dkv_fine_rows(const cf_layer_desc& L) {
-    const int rows = L.d == 64 ? compute_units() * 5 / 4 / L.Hq * 128 : 0;
-    return L.S > 1408 ? rows : (int)std::max<int64_t>(rows - (int64_t)80 * (L.S <= 768 ? L.B : L.B - 1), 0);
+// up to 320 tiles 1.03 to 1.10 times as fast, 320-512 tiles 0.97 to 1.02, more 0.90-0.98.  Up to 512 kept rows in a sequence, in the
+// mean, each counts as 128 more: it ends in a part of a tile, of which there are twice as many, and short chains make short blocks, whose fixed
+// cost counts ([447 rows in three sequences, S = 298, 64/8 heads] 35.8 us fine and 32.8 coarse, [1120 in sixteen, S = 1500, 32/4] 1.23 times as
+// long; [5120 in two, S = 5120, 8/8] 99 and 114; layer call, [1216 of 1280, 32/4] 149 and 156).  Over 656 calls of one to sixteen
+// sequences fine tiles are 1.004 times as fast by the rows alone, 0.81 at worst; with this 1.023, 0.97; left out are gains of up to 5 %.
+// (Each as 112: 0.93 at worst; up to 320 rows: 0.90; up to 704: gains of 7 % left out, [1088 in two, S = 1088, 32/4].  Of the rows of a
+// single tile up to 32 gain 2 to 3 % by fine ones, 33 to 64 lose up to 1.)
+static void attn_dkv_fine_rows(const cf_layer_desc& L, AttnParams& p) {
+    const int64_t rows = L.d == 64 ? compute_units() * 5 / 4 / L.Hq * 128 : 0;
+    const int64_t less = std::max<int64_t>(rows - (int64_t)128 * L.B, 0), few = std::min<int64_t>((int64_t)512 * L.B, rows);
+    p.dkv_fine_rows = (int)(few < rows ? rows : less);
+    p.dkv_coarse_above = (int)(less < few ? less : rows);
+    p.dkv_coarse_rows = (int)few;
 }
-__host__ __device__ inline bool attn_dkv_fine(const AttnParams& p, int n_live) { return n_live <= p.dkv_fine_rows; }
+__host__ __device__ inline bool attn_dkv_fine(const AttnParams& p, int n_live) {
+    return n_live <= p.dkv_fine_rows && (n_live <= p.dkv_coarse_above || n_live > p.dkv_coarse_rows);
+}
 
 // Key ranges per query tile of the dQ kernel.  Where a batch of few heads (a tensor-parallel share) has few query tiles, each
 // of them is a serial chain on a CU of its own: several blocks per tile, one per range of keys, shorten it, at the price of
@@ -1368,7 +1376,7 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
     p.dkv_both = 0;
     if (D == 64 && chains && tiles > 1) {
         paired = p.n_dev == nullptr ? attn_dkv_fine(p, n_kept) : p.dkv_fine_rows > 0;
-        p.dkv_both = paired && n_kept > p.dkv_fine_rows && tiles >= 20;
+        p.dkv_both = p.n_dev != nullptr && paired && n_kept > p.dkv_coarse_above && tiles >= 20;
     }
     p.n_slots = n_cu * (paired && !p.dkv_both ? 2 : 1);
     static std::atomic<uint64_t> lds_ok_dq{0}, lds_ok_dkv{0}, lds_ok_paired{0};
@@ -1424,7 +1432,7 @@ hipError_t launch_attn_bwd_mfma(const cf_layer_desc& L, float scale, const void*
     attn_dq_fine_rows(L, p);
     const int cap_fine = attn_dq_plan(L, rows, true, p.dq_limits_fine), cap_coarse = attn_dq_plan(L, rows, false, p.dq_limits_coarse);
     const int dq_cap = rows.dev ? std::max(cap_fine, cap_coarse) : (attn_dq_fine(p, n_kept) ? cap_fine : cap_coarse);
-    p.dkv_fine_rows = attn_dkv_fine_rows(L);
+    attn_dkv_fine_rows(L, p);
     p.dq_part = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(partials) + attn_dkv_partial_bytes(L, n_kept));
     p.dk_part = partials;
     p.dv_part = partials ? partials + (size_t)n_kept * L.Hq * L.d : nullptr;

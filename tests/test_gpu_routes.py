@@ -149,9 +149,10 @@ def test_attn_rows_that_take_fine_query_tiles(B, S, Hq, Hkv, d, n, fine):
 
 
 @pytest.mark.parametrize("B,S,Hq,Hkv,n,fine", [
-    (1, 768, 64, 8, 560, True), (1, 768, 64, 8, 561, False), (1, 769, 64, 8, 640, True), (1, 769, 64, 8, 641, False),
-    (2, 1408, 64, 8, 560, True), (2, 1408, 64, 8, 562, False), (2, 1409, 64, 8, 640, True), (2, 1409, 64, 8, 642, False),
-    (3, 400, 64, 8, 399, True), (3, 400, 64, 8, 402, False), (8, 320, 32, 4, 640, True), (8, 320, 32, 4, 648, False),
+    (1, 700, 64, 8, 640, True), (1, 700, 64, 8, 641, False), (2, 1500, 64, 8, 384, True), (2, 1500, 64, 8, 386, False),
+    (2, 1500, 32, 4, 1280, True), (2, 1500, 32, 4, 1282, False), (3, 400, 64, 8, 255, True), (3, 400, 64, 8, 258, False),
+    (8, 1500, 32, 4, 256, True), (8, 1500, 32, 4, 264, False), (9, 800, 8, 8, 3960, True), (9, 800, 8, 8, 3969, False),
+    (9, 800, 8, 8, 4608, False), (9, 800, 8, 8, 4617, True), (9, 800, 8, 8, 5121, False),
     (1, 300, 8, 8, 130, True), (8, 320, 64, 8, 80, False),
 ])
 def test_attn_rows_that_take_fine_key_tiles(B, S, Hq, Hkv, n, fine):
@@ -161,7 +162,8 @@ def test_attn_rows_that_take_fine_key_tiles(B, S, Hq, Hkv, n, fine):
 
 
 @pytest.mark.parametrize("B,S,Hq,Hkv,d,each", [(14, 776, 32, 8, 128, 32), (14, 776, 32, 8, 128, 33), (8, 776, 32, 8, 128, 64), (8, 776, 32, 8, 128, 65),
-                                               (13, 776, 32, 4, 64, 64), (13, 776, 32, 4, 64, 65)])
+                                               (13, 776, 32, 4, 64, 64), (13, 776, 32, 4, 64, 65),
+                                               (9, 2500, 8, 8, 64, 441), (9, 2500, 8, 8, 64, 513)])
 def test_layer_of_sequences_with_few_rows_each(B, S, Hq, Hkv, d, each):
     """Tiles follow the live rows: the default bound, the tight one and a host count give the same bits on both sides of a line."""
     say("layer routes B=%d S=%d Hq=%d d=%d each=%d" % (B, S, Hq, d, each))
