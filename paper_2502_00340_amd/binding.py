@@ -164,12 +164,13 @@ def _addr(t):
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
-def _stream():
-    """Handle of the current device's current stream, read on every call.  The raw query costs 0.1 us where building a
-    torch.cuda.Stream object for it costs 2.8 us, a fifth of the smallest calls; a torch without it builds the object."""
+def _stream(device: int | None = None):
+    """Handle of the current device's current stream, read on every call; device: its number, where the caller has just asked
+    for it.  The raw query costs 0.1 us where building a torch.cuda.Stream object for it costs 2.8 us, a fifth of the
+    smallest calls; a torch without it builds the object."""
     if _raw_stream is None:
         return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(torch.cuda.current_device())
+    return _raw_stream(torch.cuda.current_device() if device is None else device)
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -262,11 +263,12 @@ def linear_bwd_reduced(x_kept, dy_kept, w, need_dx=True, need_dw=True, dw_accumu
         else:
             dw = torch.empty((in_f, out_f), dtype=dy_kept.dtype, device=dev)
     code = _dtype_code(dy_kept)
-    wsb = _linear_ws_bytes(n_kept, in_f, out_f, code, torch.cuda.current_device()) if need_dx else 0
+    device = torch.cuda.current_device()
+    wsb = _linear_ws_bytes(n_kept, in_f, out_f, code, device) if need_dx else 0
     ws = torch.empty(wsb, dtype=torch.uint8, device=dev) if wsb else None
     at = _addr if n_kept and in_f and out_f else _ptr          # with all sizes no tensor is empty
     _check((_lib or lib()).cf_linear_bwd_reduced_ws(at(x_kept), at(dy_kept), at(w), n_kept, in_f, out_f, code, at(dx), at(dw),
-                                                    beta, _addr(ws), wsb, _stream()), "cf_linear_bwd_reduced")
+                                                    beta, _addr(ws), wsb, _stream(device)), "cf_linear_bwd_reduced")
     return dx, dw
 
 

@@ -258,7 +258,7 @@ def test_linear_scratch_of_unlike_devices(monkeypatch):
 
     current = [0]
     monkeypatch.setattr(Bn, "_lib", Lib())
-    monkeypatch.setattr(Bn, "_stream", lambda: None)
+    monkeypatch.setattr(Bn, "_stream", lambda device=None: None)
     monkeypatch.setattr(torch.cuda, "current_device", lambda: current[0])
     t = lambda *s: torch.zeros(s, dtype=torch.bfloat16)
     Bn._linear_ws_bytes.cache_clear()
