@@ -21,7 +21,7 @@
 //
 // Operand orientation is chosen so that no score tile ever goes through LDS:
 // the dQ kernel forms S^T = K*Q^T (accumulator lane = query, registers = keys),
-// which is already the A-operand layout of dQ += dS*K; the dK/dV kernel forms
+// which is already the B-operand layout of dQ^T += K^T*dS^T; the dK/dV kernel forms
 // S = Q*K^T (lane = key, registers = queries), the A-operand layout of
 // dV += P^T*dO and dK += dS^T*Q.  The second operand of those products has the
 // token dimension as K; it is fetched from the same [token][d] LDS tile with
@@ -33,6 +33,14 @@
 // so accumulator registers 8j..8j+7 of a lane, used as one A/B fragment, carry
 // rows {16j + 4hh + e, 16j + 8 + 4hh + e}; the transpose reads fetch exactly
 // those rows for the other operand.
+//
+// 16x16x32 (the dQ kernel; slot = l%16, qd = l/16): A row = slot, B col = slot, k = 8*qd + e;
+// D: col = slot, row = 4*qd + v.  Two accumulators of 16 rows each, as one operand, carry rows {4qd + e, 16 + 4qd + e}.
+// Large attention calls run at the chip's power limit (on all-zero inputs the same instructions take 0.76 to 0.83 of the time), and
+// this MFMA moves half the accumulator bytes per flop of the 32x32x16 one.  With it, and with dP accumulated from -D on
+// instead of a subtraction per score (four registers hold -D here, sixteen there: those spilled), the whole attention call takes, [2 x 2048 of 4096
+// rows, 32/8 heads, d = 128] 371 -> 354 us, [8192 of 16384, 24/8] 1814 -> 1722, d = 64 [3 x 459 of 1531, 32/4] 53.6 -> 50.9, [4 x 2048, 32/4]
+// 286 -> 277.
 #include <algorithm>
 
 #include "common.h"
@@ -242,6 +250,19 @@ __device__ __forceinline__ int tile_off(int row, int chunk) {
     return row * (D * 2) + ((chunk ^ g) << 4);
 }
 
+// The swizzle for reads by 16x16x32 MFMAs (attn_dq_kernel).  A pass of a ds_read_b128 mixes a chunk of rows 0-3 and 12-15 with its neighbour of
+// rows 4-11 (or the other way round, see gemm.hip), and the transpose read of a half wave takes two neighbouring chunks of
+// eight rows: with the four blocks of four rows numbered 0, 2, 3, 1 in the chunk's low bits both hit every bank once.
+template <int D>
+__device__ __forceinline__ int swz16(int row) {
+    const int q = (row >> 2) & 3, low = (((q ^ (q >> 1)) & 1) << 1) | (q >> 1);
+    return (D == 128 ? (row & 3) << 2 : ((row >> 1) & 1) << 2) | low;
+}
+
+__device__ __forceinline__ f32x4_t mfma16(bf16x8_t a, bf16x8_t b, f32x4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
 __device__ __forceinline__ unsigned pack2(float lo, float hi) {
     bf16x2_t v;
     v[0] = (__bf16)lo;
@@ -256,29 +277,6 @@ __device__ __forceinline__ bf16x8_t pack8(const f32x16_t& a, int j) {
     u.z = pack2(a[8 * j + 4], a[8 * j + 5]);
     u.w = pack2(a[8 * j + 6], a[8 * j + 7]);
     return __builtin_bit_cast(bf16x8_t, u);
-}
-
-// A/B fragment with the tile row as the MFMA row/col and d as K
-template <int D>
-__device__ __forceinline__ bf16x8_t frag_rows(const unsigned char* tile, int row, int ks, int hh) {
-    return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(tile + tile_off<D>(row, ks * 2 + hh)));
-}
-
-// B fragment with d as the MFMA column and the tile row (token) as K:
-// rows row0 + 4hh + {0..3} and row0 + 8 + 4hh + {0..3}, columns nt*32 + slot
-template <int D>
-__device__ __forceinline__ bf16x8_t frag_tokens(const unsigned char* tile, int row0, int nt, int lane) {
-    const int hh = lane >> 5;
-    const int r = row0 + 4 * hh + ((lane & 15) >> 2);
-    const int chunk = nt * 4 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-    const int sub = (lane & 1) * 8;
-    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (lds_s16x4_ptr)(tile + tile_off<D>(r, chunk) + sub));
-    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (lds_s16x4_ptr)(tile + tile_off<D>(r + 8, chunk) + sub));
-    typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
-    s16x8_t both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8_t, both);
 }
 
 // Writes a wave's [32 rows][D] accumulators (lane = column within 32, register v = row 8*(v/4) + 4*hh + v%4) as bf16, times
@@ -324,12 +322,12 @@ __device__ __forceinline__ void store_rows_rotated(bf16_t* out, int64_t stride, 
 // meet in LDS at the end (see attn_dq_fine_rows).
 template <int D, bool ROPE, bool FINE>
 __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_t dq_limits, const int n_live, unsigned char* smem) {
-    constexpr int KS = D / 16, NT = D / 32, QT = FINE ? 64 : 128;
+    constexpr int KS = D / 32, NT = D / 16, QT = FINE ? 64 : 128;
     constexpr int TILE = 64 * D * 2;            // one 64-token tile in bytes
     constexpr int NLD = D / 32;                 // wave-loads per wave per tile
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int wave = FINE ? wv & 1 : wv, kw = FINE ? __builtin_amdgcn_readfirstlane(wv >> 1) : 0;   // group of 32 queries; half of the key tiles
-    const int slot = lane & 31, hh = lane >> 5;
+    const int slot = lane & 15, qd = lane >> 4;
     const int h = blockIdx.x % p.Hq, b = blockIdx.x / p.Hq, g = h / (p.Hq / p.Hkv);
     const int Nq = p.Hq * D, Nkv = p.Hkv * D;
     int seq_begin, seq_end;
@@ -344,56 +342,62 @@ __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_
     const int j0 = seq_begin + qt * QT;
     const int rows_in_tile = min(QT, cnt - qt * QT);
 
-    // This lane's query: its fragments and its row terms.  D = rowsum(dO*O) is formed here, from the dO fragments that
+    // This lane's two queries, 16 rows apart: their fragments and row terms.  D = rowsum(dO*O) is formed here, from the dO fragments that
     // the kernel holds anyway, unless a pass before had to read O for its compact copy (a pass of its own over dO and O
     // costs 16 us where the dQ kernel gets 6 us slower: [4096 rows, 32 heads, d = 128], 206 us).
-    const int jq = j0 + wave * 32 + slot;
-    const bool qvalid = wave * 32 + slot < rows_in_tile;
-    const int pos = qvalid ? (p.idx ? p.idx[jq] : jq) - b * p.S : -1;
-    float lse2 = 0.f, Dq = 0.f;
-    bf16x8_t qf[KS], dof[KS];
-    const int64_t off_q = (int64_t)jq * Nq + h * D + hh * 8;
+    int pos[2];
+    float lse2[2], Dq[2];
+    bf16x8_t qf[2][KS], dof[2][KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        uint4 a = make_uint4(0, 0, 0, 0), c = make_uint4(0, 0, 0, 0);
-        if (qvalid) {
-            a = *reinterpret_cast<const uint4*>(p.q_kept + off_q + ks * 16);
-            c = *reinterpret_cast<const uint4*>(p.do_kept + off_q + ks * 16);
-        }
-        qf[ks] = __builtin_bit_cast(bf16x8_t, a);
-        dof[ks] = __builtin_bit_cast(bf16x8_t, c);
-    }
-    if (p.o_kept != nullptr) {
-        // summed in the order of attn_stats_kernel, so that both give the same bits: 8 columns in sequence, then a tree
-        if (qvalid) {
-            float part[KS];
+    for (int t = 0; t < 2; ++t) {
+        const int r = wave * 32 + t * 16 + slot, jq = j0 + r;
+        const bool qvalid = r < rows_in_tile;
+        pos[t] = qvalid ? (p.idx ? p.idx[jq] : jq) - b * p.S : -1;
+        lse2[t] = Dq[t] = 0.f;
+        const int64_t off_q = (int64_t)jq * Nq + h * D + qd * 8;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                part[ks] = 0.f;
-                const uint4 o = *reinterpret_cast<const uint4*>(p.o_kept + off_q + ks * 16);
-                const uint4 c = __builtin_bit_cast(uint4, dof[ks]);
-                const unsigned ow[4] = {o.x, o.y, o.z, o.w}, cw[4] = {c.x, c.y, c.z, c.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    part[ks] += __uint_as_float(cw[e] << 16) * __uint_as_float(ow[e] << 16);
-                    part[ks] += __uint_as_float(cw[e] & 0xFFFF0000u) * __uint_as_float(ow[e] & 0xFFFF0000u);
-                }
+        for (int ks = 0; ks < KS; ++ks) {
+            uint4 a = make_uint4(0, 0, 0, 0), c = make_uint4(0, 0, 0, 0);
+            if (qvalid) {
+                a = *reinterpret_cast<const uint4*>(p.q_kept + off_q + ks * 32);
+                c = *reinterpret_cast<const uint4*>(p.do_kept + off_q + ks * 32);
             }
-#pragma unroll
-            for (int o = KS / 2; o > 0; o >>= 1)
-#pragma unroll
-                for (int ks = 0; ks < o; ++ks) part[ks] += part[ks + o];
-            Dq = part[0];
-            lse2 = p.lse_full[((int64_t)b * p.Hq + h) * p.S + pos] * LOG2E;
+            qf[t][ks] = __builtin_bit_cast(bf16x8_t, a);
+            dof[t][ks] = __builtin_bit_cast(bf16x8_t, c);
         }
-        Dq += __shfl_xor(Dq, 32, 64);           // the other half of the row's columns
-        if (qvalid && hh == 0 && blockIdx.z == 0 && kw == 0) {
-            p.stat[(int64_t)h * p.n_kept + jq] = lse2;
-            p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq] = Dq;
+        if (p.o_kept != nullptr) {
+            // summed in the order of attn_stats_kernel, so that both give the same bits: 8 columns in sequence, then a tree
+            if (qvalid) {
+                float part[KS];
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    part[ks] = 0.f;
+                    const uint4 o = *reinterpret_cast<const uint4*>(p.o_kept + off_q + ks * 32);
+                    const uint4 c = __builtin_bit_cast(uint4, dof[t][ks]);
+                    const unsigned ow[4] = {o.x, o.y, o.z, o.w}, cw[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        part[ks] += __uint_as_float(cw[e] << 16) * __uint_as_float(ow[e] << 16);
+                        part[ks] += __uint_as_float(cw[e] & 0xFFFF0000u) * __uint_as_float(ow[e] & 0xFFFF0000u);
+                    }
+                }
+#pragma unroll
+                for (int o = KS / 2; o > 0; o >>= 1)
+#pragma unroll
+                    for (int ks = 0; ks < o; ++ks) part[ks] += part[ks + o];
+                Dq[t] = part[0];
+                lse2[t] = p.lse_full[((int64_t)b * p.Hq + h) * p.S + pos[t]] * LOG2E;
+            }
+            Dq[t] += __shfl_xor(Dq[t], 32, 64);     // the other quarters of the row's columns
+            Dq[t] += __shfl_xor(Dq[t], 16, 64);
+            if (qvalid && qd == 0 && blockIdx.z == 0 && kw == 0) {
+                p.stat[(int64_t)h * p.n_kept + jq] = lse2[t];
+                p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq] = Dq[t];
+            }
+        } else if (qvalid) {
+            lse2[t] = p.stat[(int64_t)h * p.n_kept + jq];
+            Dq[t] = p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq];
         }
-    } else if (qvalid) {
-        lse2 = p.stat[(int64_t)h * p.n_kept + jq];
-        Dq = p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq];
     }
     const int jlast = j0 + rows_in_tile - 1;
     const int maxpos = (p.idx ? p.idx[jlast] : jlast) - b * p.S;
@@ -412,12 +416,18 @@ __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_
         }
     }
     const float scale2 = p.scale * LOG2E;
+    // dP accumulates from -D on, which takes a subtraction per score out of the loop
+    f32x4_t negD[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) negD[t] = f32x4_t{-Dq[t], -Dq[t], -Dq[t], -Dq[t]};
 
-    f32x16_t acc[NT];
+    f32x4_t acc[2][NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[nt][v] = 0.f;
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[t][nt][v] = 0.f;
 
     // K and V of this sequence and KV head: rows are Nkv*2 bytes apart.  A tile is loaded whole: rows past
     // the last query's position are later keys of the same sequence (masked out below) or lie outside
@@ -431,9 +441,7 @@ __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_
     unsigned voff0;
     {
         const int row = wv * RPL + lane / NCH;
-        const int pc = lane % NCH;
-        const int sw = (D == 128) ? (((row & 3) << 2) | ((row >> 2) & 3)) : ((((row >> 1) & 1) << 2) | ((row >> 2) & 3));
-        voff0 = (unsigned)row * (unsigned)(Nkv * 2) + (unsigned)((pc ^ sw) << 4);
+        voff0 = (unsigned)row * (unsigned)(Nkv * 2) + (unsigned)(((lane % NCH) ^ swz16<D>(row)) << 4);
     }
     const unsigned wave_lds = __builtin_amdgcn_readfirstlane(lds0 + (unsigned)wv * 1024u);   // scalar: the wave's 1 KB slot
     auto issue_kv = [&](int kt, int stage) __attribute__((always_inline)) {
@@ -445,55 +453,83 @@ __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_
 #pragma unroll
         for (int i = 0; i < NLD; ++i) dma16(sk + TILE + 4 * i * 1024, rsV, voff0 + (base + i * step));
     };
+    // Per-lane offsets of the fragment reads inside a tile: row fragments (key slot of 16, chunk qd of the first 32 columns; columns ks
+    // differ in two bits of the chunk) and token fragments (four keys from 4*qd on, 16 columns; block nt likewise).
+    typedef __attribute__((address_space(3))) unsigned char* lds_u8_ptr;
+    typedef const __attribute__((address_space(3))) u32x4_t* lds_u4_cptr;
+    typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
+    const unsigned ra0 = (unsigned)(slot * (D * 2) + ((qd ^ swz16<D>(slot)) << 4));
+    unsigned ta0;
+    {
+        const int r = 4 * qd + (slot >> 2);
+        ta0 = (unsigned)(r * (D * 2) + ((((lane & 3) >> 1) ^ swz16<D>(r)) << 4) + (lane & 1) * 8);
+    }
     // One 64-key tile in the LDS stage at sk.  MASKED: some key of the tile lies after some query of the
     // wave; the other tiles (most of them) spend no instruction on the mask.
-    // One 32-key half of the tile at a time keeps the score registers at 2 x 16.  The LDS fragments of an
-    // MFMA are read while the previous MFMAs run (one step ahead).  (Fragment addresses are rebuilt per
+    // One 32-key half of the tile at a time keeps the score registers at 2 x 16.  The LDS fragments of a group of
+    // MFMAs are read while the previous ones run (one step ahead).  (Fragment addresses are rebuilt per
     // read: with two waves per SIMD the register file has no room to keep them at d = 128.)
     // key0: the first of the wave's keys in the tile, whose K rows begin at sk.
-    auto tile = [&](auto MASKED_, const int key0, const unsigned char* sk) __attribute__((always_inline)) {
+    auto tile = [&](auto MASKED_, const int key0, const unsigned sk) __attribute__((always_inline)) {
         constexpr bool masked = decltype(MASKED_)::value != 0;
-        const unsigned char* sv = sk + TILE;
         bf16x8_t fa[2][2], fc[2];
-        auto load_a = [&](int mt, int ks, int buf) __attribute__((always_inline)) {
-            fa[buf][0] = frag_rows<D>(sk, mt * 32 + slot, ks, hh);
-            fa[buf][1] = frag_rows<D>(sv, mt * 32 + slot, ks, hh);
+        auto load_a = [&](int mt, int s, int buf) __attribute__((always_inline)) {      // s: 16 keys s / KS, 32 columns s % KS
+            const lds_u8_ptr q = reinterpret_cast<lds_u8_ptr>(sk + (ra0 ^ (unsigned)((s % KS) << 6)));
+            const int off = (mt * 32 + 16 * (s / KS)) * (D * 2);
+            fa[buf][0] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<lds_u4_cptr>(q + off));
+            fa[buf][1] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<lds_u4_cptr>(q + (TILE + off)));
         };
-        auto load_c = [&](int mt, int c, int buf) __attribute__((always_inline)) {
-            fc[buf] = frag_tokens<D>(sk, mt * 32 + 16 * (c / NT), c % NT, lane);
+        auto load_c = [&](int mt, int nt, int buf) __attribute__((always_inline)) {
+            const lds_u8_ptr q = reinterpret_cast<lds_u8_ptr>(sk + (ta0 ^ (unsigned)(nt << 5)));
+            const int off = mt * 32 * (D * 2);
+            const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(q + off));
+            const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(q + (off + 16 * (D * 2))));
+            fc[buf] = __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
         };
         load_a(0, 0, 0);
 #pragma unroll
         for (int mt = 0; mt < (FINE ? 1 : 2); ++mt) {
-            f32x16_t st, dpt;
+            f32x4_t st[2][2], dpt[2][2];            // [16 keys][16 queries]
 #pragma unroll
-            for (int v = 0; v < 16; ++v) { st[v] = 0.f; dpt[v] = 0.f; }
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                if (ks + 1 < KS) load_a(mt, ks + 1, (ks + 1) & 1);
+            for (int s = 0; s < 2 * KS; ++s) {
+                const int k16 = s / KS, ks = s % KS, buf = s & 1;
+                if (s + 1 < 2 * KS) load_a(mt, s + 1, (s + 1) & 1);
                 else load_c(mt, 0, 0);
                 CF_SCHED_FENCE();
-                st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks & 1][0], qf[ks], st, 0, 0, 0);
-                dpt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks & 1][1], dof[ks], dpt, 0, 0, 0);
+                const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    st[k16][t] = mfma16(fa[buf][0], qf[t][ks], ks == 0 ? z : st[k16][t]);
+                    dpt[k16][t] = mfma16(fa[buf][1], dof[t][ks], ks == 0 ? negD[t] : dpt[k16][t]);
+                }
                 CF_SCHED_FENCE();
             }
             // dS^T = P^T o (dP^T - D): lane = query, register = key
+            bf16x8_t a[2];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                float pr = __builtin_amdgcn_exp2f(st[v] * scale2 - lse2);
-                if (masked) {
-                    const int key = key0 + mt * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
-                    pr = key <= pos ? pr : 0.f;
-                }
-                st[v] = pr * (dpt[v] - Dq);
+            for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                for (int k16 = 0; k16 < 2; ++k16)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        float pr = __builtin_amdgcn_exp2f(st[k16][t][v] * scale2 - lse2[t]);
+                        if (masked) {
+                            const int key = key0 + mt * 32 + k16 * 16 + 4 * qd + v;
+                            pr = key <= pos[t] ? pr : 0.f;
+                        }
+                        st[k16][t][v] = pr * dpt[k16][t][v];
+                    }
+                a[t] = __builtin_bit_cast(bf16x8_t, make_uint4(pack2(st[0][t][0], st[0][t][1]), pack2(st[0][t][2], st[0][t][3]),
+                                                               pack2(st[1][t][0], st[1][t][1]), pack2(st[1][t][2], st[1][t][3])));
             }
-            const bf16x8_t a0 = pack8(st, 0), a1 = pack8(st, 1);
+            // dQ^T += K^T * dS^T: lane = query, register = column
 #pragma unroll
-            for (int c = 0; c < 2 * NT; ++c) {
-                if (c + 1 < 2 * NT) load_c(mt, c + 1, (c + 1) & 1);
+            for (int c = 0; c < NT; ++c) {
+                if (c + 1 < NT) load_c(mt, c + 1, (c + 1) & 1);
                 else if (!FINE && mt == 0) load_a(mt + 1, 0, 0);
                 CF_SCHED_FENCE();
-                acc[c % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c < NT ? a0 : a1, fc[c & 1], acc[c % NT], 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < 2; ++t) acc[t][c] = mfma16(fc[c & 1], a[t], acc[t][c]);
                 CF_SCHED_FENCE();
             }
         }
@@ -502,7 +538,7 @@ __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_
     auto step = [&](const int kt, const int stage) __attribute__((always_inline)) {
         const int key0 = kt * 64 + kw * 32;
         if (key0 <= wave_maxpos) {
-            const unsigned char* sk = smem + stage * 2 * TILE + kw * (32 * D * 2);
+            const unsigned sk = lds0 + stage * 2 * TILE + kw * (32 * D * 2);
             // a query that does not exist (a ragged last wave) has position -1 and is masked in every tile
             if (key0 + (FINE ? 31 : 63) <= wave_minpos && wave * 32 + 32 <= rows_in_tile) tile(ic<0>{}, key0, sk);
             else tile(ic<1>{}, key0, sk);
@@ -519,49 +555,48 @@ __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_
     }
 
     if constexpr (FINE) {       // the second half of the keys joins the first one's wave; the last barrier has freed the tiles' LDS
-        float4* buf = reinterpret_cast<float4*>(smem) + wave * (NT * 4 * 64) + lane;
+        f32x4_t* buf = reinterpret_cast<f32x4_t*>(smem) + wave * (2 * NT * 64) + lane;
         if (kw == 1) {
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
+            for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    buf[(nt * 4 + q) * 64] = make_float4(acc[nt][4 * q], acc[nt][4 * q + 1], acc[nt][4 * q + 2], acc[nt][4 * q + 3]);
+                for (int nt = 0; nt < NT; ++nt) buf[(t * NT + nt) * 64] = acc[t][nt];
         }
         lds_barrier();
         if (kw == 1) return;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 o = buf[(nt * 4 + q) * 64];
-                acc[nt][4 * q] += o.x; acc[nt][4 * q + 1] += o.y; acc[nt][4 * q + 2] += o.z; acc[nt][4 * q + 3] += o.w;
-            }
+            for (int nt = 0; nt < NT; ++nt) acc[t][nt] += buf[(t * NT + nt) * 64];
     }
-    if (ranges > 1) {           // fp32, unscaled, to the range's own partial (zeros when the range is empty)
-        float* part = p.dq_part + (int64_t)blockIdx.z * p.n_kept * Nq;
+    // dq[query][d]: lane = query, a block's four registers = columns nt*16 + 4*qd on
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
+    for (int t = 0; t < 2; ++t) {
+        const int r = wave * 32 + t * 16 + slot;
+        if (r >= rows_in_tile) continue;
+        const int64_t at = (int64_t)(j0 + r) * Nq + h * D + 4 * qd;
+        if (ranges > 1) {       // fp32, unscaled, to the range's own partial (zeros when the range is empty)
+            float* part = p.dq_part + (int64_t)blockIdx.z * p.n_kept * Nq + at;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = wave * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
-                if (r < rows_in_tile) part[(int64_t)(j0 + r) * Nq + h * D + nt * 32 + slot] = acc[nt][v];
-            }
+            for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<f32x4_t*>(part + nt * 16) = acc[t][nt];
+            continue;
         }
-        return;
-    }
-    if constexpr (ROPE) {
-        store_rows_rotated<D>(p.dq_kept + (int64_t)(j0 + wave * 32) * Nq + h * D, Nq, rows_in_tile - wave * 32, acc, p.scale, lane, pos,
-                              p.rope_cos, p.rope_sin);
-        return;
-    }
-    // dq[query][d]: lane = d column, registers = query rows
+        auto store = [&](int nt, const f32x4_t& y) __attribute__((always_inline)) {
+            *reinterpret_cast<uint2*>(p.dq_kept + at + nt * 16) = make_uint2(pack2(y[0], y[1]), pack2(y[2], y[3]));
+        };
+        if constexpr (ROPE) {
+            const int64_t tab = (int64_t)pos[t] * (D / 2) + 4 * qd;
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
+            for (int nt = 0; nt < NT / 2; ++nt) {
+                const f32x4_t c = *reinterpret_cast<const f32x4_t*>(p.rope_cos + tab + nt * 16);
+                const f32x4_t s = *reinterpret_cast<const f32x4_t*>(p.rope_sin + tab + nt * 16);
+                const f32x4_t u = acc[t][nt] * p.scale, w = acc[t][nt + NT / 2] * p.scale;
+                store(nt, u * c + w * s);
+                store(nt + NT / 2, w * c - u * s);
+            }
+        } else {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int r = wave * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
-            if (r < rows_in_tile)
-                p.dq_kept[(int64_t)(j0 + r) * Nq + h * D + nt * 32 + slot] = f32_to_bf16(acc[nt][v] * p.scale);
+            for (int nt = 0; nt < NT; ++nt) store(nt, acc[t][nt] * p.scale);
         }
     }
 }
