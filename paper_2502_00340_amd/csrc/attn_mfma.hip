@@ -22,25 +22,23 @@
 // Operand orientation is chosen so that no score tile ever goes through LDS:
 // the dQ kernel forms S^T = K*Q^T (accumulator lane = query, registers = keys),
 // which is already the B-operand layout of dQ^T += K^T*dS^T; the dK/dV kernel forms
-// S = Q*K^T (lane = key, registers = queries), the A-operand layout of
-// dV += P^T*dO and dK += dS^T*Q.  The second operand of those products has the
+// S = Q*K^T (lane = key, registers = queries), the B-operand layout of
+// dV^T += dO^T*P and dK^T += Q^T*dS.  The first operand of those products has the
 // token dimension as K; it is fetched from the same [token][d] LDS tile with
-// the LDS transpose read (ds_read_b64_tr_b16).
+// the LDS transpose read (ds_read_b64_tr_b16).  A lane ends up with four
+// neighbouring columns of one row of dQ, dK or dV.
 //
-// 32x32x16 bf16 MFMA operand layout (lane l, slot = l%32, hh = l/32):
-//   A: row = slot,  k = 8*hh + e (e = 0..7)      B: col = slot, k = 8*hh + e
-//   D: col = slot,  row = 8*(v/4) + 4*hh + v%4   (v = 0..15)
-// so accumulator registers 8j..8j+7 of a lane, used as one A/B fragment, carry
-// rows {16j + 4hh + e, 16j + 8 + 4hh + e}; the transpose reads fetch exactly
-// those rows for the other operand.
-//
-// 16x16x32 (the dQ kernel; slot = l%16, qd = l/16): A row = slot, B col = slot, k = 8*qd + e;
-// D: col = slot, row = 4*qd + v.  Two accumulators of 16 rows each, as one operand, carry rows {4qd + e, 16 + 4qd + e}.
+// 16x16x32 bf16 MFMA operand layout (lane l, slot = l%16, qd = l/16):
+//   A: row = slot,  k = 8*qd + e (e = 0..7)      B: col = slot, k = 8*qd + e
+//   D: col = slot,  row = 4*qd + v   (v = 0..3)
+// so two accumulators of 16 rows each, packed into one operand, carry rows
+// {4qd + e, 16 + 4qd + e}; the transpose reads fetch exactly those rows for the other operand.
 // Large attention calls run at the chip's power limit (on all-zero inputs the same instructions take 0.76 to 0.83 of the time), and
-// this MFMA moves half the accumulator bytes per flop of the 32x32x16 one.  With it, and with dP accumulated from -D on
-// instead of a subtraction per score (four registers hold -D here, sixteen there: those spilled), the whole attention call takes, [2 x 2048 of 4096
-// rows, 32/8 heads, d = 128] 371 -> 354 us, [8192 of 16384, 24/8] 1814 -> 1722, d = 64 [3 x 459 of 1531, 32/4] 53.6 -> 50.9, [4 x 2048, 32/4]
-// 286 -> 277.
+// this MFMA moves half the accumulator bytes per flop that the 32x32x16 one does.  It also leaves four registers with the same row
+// terms instead of sixteen, so that dP can accumulate from -D on instead of a subtraction per score (with 32x32x16 the sixteen
+// registers of -D spilled).  Whole attention call with the larger and with this MFMA, [2 x 2048 of 4096 rows, 32/8 heads, d = 128]
+// 369 and 338 us, [8192 of 16384, 24/8] 1805 and 1629, [2 x 4096, 24/8] 691 and 620; d = 64 [4 x 2048, 32/4] 284 and 258,
+// [4915 of 8192, 8/8] 157 and 141, [3 x 459 of 1531, 32/4] 53.7 and 50.2.
 #include <algorithm>
 
 #include "common.h"
@@ -56,7 +54,7 @@ static constexpr float LOG2E = 1.4426950408889634f;
 
 struct AttnParams {
     const bf16_t *q_kept, *k_full, *v_full, *do_kept;
-    float* stat;                   // [2][Hq][n_kept]: log2(e)*LSE and D = rowsum(dO*O) of every kept row and head
+    float* stat;                   // [2][Hq][n_kept]: log2(e)*LSE and -D = -rowsum(dO*O) of every kept row and head
     // The attention output's kept rows; when set, the dQ kernel forms the row terms from them and writes stat (the dK/dV
     // kernel behind it loads 64 rows of a head at a time).  Null: attn_stats_kernel has written stat already.
     const bf16_t* o_kept;
@@ -240,23 +238,43 @@ __device__ __forceinline__ void seq_range(const AttnParams& p, int b, int& begin
     end = min(p.cu_kept[b + 1], n);
 }
 
-// 16-byte chunk swizzle of a [rows][D] bf16 tile: makes both the row-fragment
-// reads (16 consecutive rows, same chunk) and the transpose reads (4 rows x 4
-// consecutive chunks per half wave) bank-conflict free.
+// 16-byte chunk swizzle of a [rows][D] bf16 tile: chunk c of a row lies at c XOR this.  A pass of a ds_read_b128 mixes a chunk of
+// rows 0-3 and 12-15 with its neighbour of rows 4-11 (or the other way round, see gemm.hip), and the transpose read of a half
+// wave takes two neighbouring chunks of eight rows: with the four blocks of four rows numbered 0, 2, 3, 1 in the chunk's low
+// bits both hit every bank once.
 template <int D>
-__device__ __forceinline__ int tile_off(int row, int chunk) {
-    const int g = (D == 128) ? (((row & 3) << 2) | ((row >> 2) & 3))
-                             : ((((row >> 1) & 1) << 2) | ((row >> 2) & 3));
-    return row * (D * 2) + ((chunk ^ g) << 4);
-}
-
-// The swizzle for reads by 16x16x32 MFMAs (attn_dq_kernel).  A pass of a ds_read_b128 mixes a chunk of rows 0-3 and 12-15 with its neighbour of
-// rows 4-11 (or the other way round, see gemm.hip), and the transpose read of a half wave takes two neighbouring chunks of
-// eight rows: with the four blocks of four rows numbered 0, 2, 3, 1 in the chunk's low bits both hit every bank once.
-template <int D>
-__device__ __forceinline__ int swz16(int row) {
+__device__ __forceinline__ int tile_swz(int row) {
     const int q = (row >> 2) & 3, low = (((q ^ (q >> 1)) & 1) << 1) | (q >> 1);
     return (D == 128 ? (row & 3) << 2 : ((row >> 1) & 1) << 2) | low;
+}
+
+// Per-lane byte offsets of the fragment reads inside a tile.  Row fragments (row lane % 16 as the MFMA's row or column, columns
+// ks*32 + 8*(lane/16) on as K) ...
+template <int D>
+__device__ __forceinline__ unsigned frag_rows_at(int lane, int ks) {
+    const int slot = lane & 15;
+    return (unsigned)(slot * (D * 2) + (((ks * 4 + (lane >> 4)) ^ tile_swz<D>(slot)) << 4));
+}
+// ... and token fragments (column nt*16 + lane % 16 as the MFMA's row, rows 4*(lane/16) + {0..3} as half of K: the
+// transpose read's address for this lane).
+template <int D>
+__device__ __forceinline__ unsigned frag_tokens_at(int lane, int nt) {
+    const int r = 4 * (lane >> 4) + ((lane & 15) >> 2);
+    return (unsigned)(r * (D * 2) + (((nt * 2 + ((lane & 3) >> 1)) ^ tile_swz<D>(r)) << 4) + (lane & 1) * 8);
+}
+
+typedef __attribute__((address_space(3))) unsigned char* lds_u8_ptr;
+typedef const __attribute__((address_space(3))) u32x4_t* lds_u4_cptr;
+typedef const __attribute__((address_space(3))) f32x4_t* lds_f4_cptr;
+
+__device__ __forceinline__ bf16x8_t read_rows(lds_u8_ptr q) { return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<lds_u4_cptr>(q)); }
+// rows 4*(lane/16) + {0..3} and those 16 further on
+template <int D>
+__device__ __forceinline__ bf16x8_t read_tokens(lds_u8_ptr q) {
+    typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)q);
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(q + 16 * (D * 2)));
+    return __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 __device__ __forceinline__ f32x4_t mfma16(bf16x8_t a, bf16x8_t b, f32x4_t c) {
@@ -270,42 +288,32 @@ __device__ __forceinline__ unsigned pack2(float lo, float hi) {
     return __builtin_bit_cast(unsigned, v);
 }
 
-__device__ __forceinline__ bf16x8_t pack8(const f32x16_t& a, int j) {
-    uint4 u;
-    u.x = pack2(a[8 * j + 0], a[8 * j + 1]);
-    u.y = pack2(a[8 * j + 2], a[8 * j + 3]);
-    u.z = pack2(a[8 * j + 4], a[8 * j + 5]);
-    u.w = pack2(a[8 * j + 6], a[8 * j + 7]);
-    return __builtin_bit_cast(bf16x8_t, u);
+// two accumulators of 16 rows as one operand
+__device__ __forceinline__ bf16x8_t pack8(const f32x4_t& a, const f32x4_t& b) {
+    return __builtin_bit_cast(bf16x8_t, make_uint4(pack2(a[0], a[1]), pack2(a[2], a[3]), pack2(b[0], b[1]), pack2(b[2], b[3])));
 }
 
-// Writes a wave's [32 rows][D] accumulators (lane = column within 32, register v = row 8*(v/4) + 4*hh + v%4) as bf16, times
-// scale and rotated back to before the rotary embedding, to rows of `out` (its first row and the head's first column; `stride`
-// elements apart); the wave's rows from `rows` on do not exist.  lane_pos = position of row lane % 32.
-template <int D>
-__device__ __forceinline__ void store_rows_rotated(bf16_t* out, int64_t stride, int rows, const f32x16_t (&acc)[D / 32], float scale,
-                                                   int lane, int lane_pos, const float* __restrict__ rope_cos,
-                                                   const float* __restrict__ rope_sin) {
-    constexpr int NT = D / 32;
-    const int slot = lane & 31, hh = lane >> 5;
-    int at[16];
+// One row of a head, times scale, as bf16: acc[nt] holds columns nt*16 + {0..3} from `out` on.  ROPE: rotated back to before the rotary
+// embedding; rope_cos and rope_sin point to those columns of the row's position.
+template <int D, bool ROPE>
+__device__ __forceinline__ void store_row(bf16_t* out, const f32x4_t (&acc)[D / 16], float scale, const float* __restrict__ rope_cos,
+                                          const float* __restrict__ rope_sin) {
+    constexpr int NT = D / 16;
+    auto store = [&](int nt, const f32x4_t& y) __attribute__((always_inline)) {
+        *reinterpret_cast<uint2*>(out + nt * 16) = make_uint2(pack2(y[0], y[1]), pack2(y[2], y[3]));
+    };
+    if constexpr (ROPE) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) at[v] = max(__shfl(lane_pos, 8 * (v >> 2) + 4 * hh + (v & 3), 64), 0) * (D / 2) + slot;
-#pragma unroll
-    for (int nt = 0; nt < NT / 2; ++nt) {
-        float c[16], s[16];             // loaded for every row, existing or not: nothing here waits for a branch
-#pragma unroll
-        for (int v = 0; v < 16; ++v) { c[v] = rope_cos[at[v] + nt * 32]; s[v] = rope_sin[at[v] + nt * 32]; }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int r = 8 * (v >> 2) + 4 * hh + (v & 3);
-            const float a = acc[nt][v] * scale, b = acc[nt + NT / 2][v] * scale;
-            if (r < rows) {
-                bf16_t* row = out + r * stride + nt * 32 + slot;
-                row[0] = f32_to_bf16(a * c[v] + b * s[v]);
-                row[D / 2] = f32_to_bf16(b * c[v] - a * s[v]);
-            }
+        for (int nt = 0; nt < NT / 2; ++nt) {
+            const f32x4_t c = *reinterpret_cast<const f32x4_t*>(rope_cos + nt * 16);
+            const f32x4_t s = *reinterpret_cast<const f32x4_t*>(rope_sin + nt * 16);
+            const f32x4_t a = acc[nt] * scale, b = acc[nt + NT / 2] * scale;
+            store(nt, a * c + b * s);
+            store(nt + NT / 2, b * c - a * s);
         }
+    } else {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) store(nt, acc[nt] * scale);
     }
 }
 
@@ -392,11 +400,11 @@ __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_
             Dq[t] += __shfl_xor(Dq[t], 16, 64);
             if (qvalid && qd == 0 && blockIdx.z == 0 && kw == 0) {
                 p.stat[(int64_t)h * p.n_kept + jq] = lse2[t];
-                p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq] = Dq[t];
+                p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq] = -Dq[t];
             }
         } else if (qvalid) {
             lse2[t] = p.stat[(int64_t)h * p.n_kept + jq];
-            Dq[t] = p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq];
+            Dq[t] = -p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq];
         }
     }
     const int jlast = j0 + rows_in_tile - 1;
@@ -441,7 +449,7 @@ __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_
     unsigned voff0;
     {
         const int row = wv * RPL + lane / NCH;
-        voff0 = (unsigned)row * (unsigned)(Nkv * 2) + (unsigned)(((lane % NCH) ^ swz16<D>(row)) << 4);
+        voff0 = (unsigned)row * (unsigned)(Nkv * 2) + (unsigned)(((lane % NCH) ^ tile_swz<D>(row)) << 4);
     }
     const unsigned wave_lds = __builtin_amdgcn_readfirstlane(lds0 + (unsigned)wv * 1024u);   // scalar: the wave's 1 KB slot
     auto issue_kv = [&](int kt, int stage) __attribute__((always_inline)) {
@@ -453,56 +461,45 @@ __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_
 #pragma unroll
         for (int i = 0; i < NLD; ++i) dma16(sk + TILE + 4 * i * 1024, rsV, voff0 + (base + i * step));
     };
-    // Per-lane offsets of the fragment reads inside a tile: row fragments (key slot of 16, chunk qd of the first 32 columns; columns ks
-    // differ in two bits of the chunk) and token fragments (four keys from 4*qd on, 16 columns; block nt likewise).
-    typedef __attribute__((address_space(3))) unsigned char* lds_u8_ptr;
-    typedef const __attribute__((address_space(3))) u32x4_t* lds_u4_cptr;
-    typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
-    const unsigned ra0 = (unsigned)(slot * (D * 2) + ((qd ^ swz16<D>(slot)) << 4));
-    unsigned ta0;
-    {
-        const int r = 4 * qd + (slot >> 2);
-        ta0 = (unsigned)(r * (D * 2) + ((((lane & 3) >> 1) ^ swz16<D>(r)) << 4) + (lane & 1) * 8);
-    }
+    // The other columns' fragments lie at these offsets with two (rows) or three (tokens) bits of the chunk changed.
+    const unsigned ra0 = frag_rows_at<D>(lane, 0), ta0 = frag_tokens_at<D>(lane, 0);
     // One 64-key tile in the LDS stage at sk.  MASKED: some key of the tile lies after some query of the
     // wave; the other tiles (most of them) spend no instruction on the mask.
     // One 32-key half of the tile at a time keeps the score registers at 2 x 16.  The LDS fragments of a group of
-    // MFMAs are read while the previous ones run (one step ahead).  (Fragment addresses are rebuilt per
-    // read: with two waves per SIMD the register file has no room to keep them at d = 128.)
+    // MFMAs are read between the previous ones (one group ahead).
     // key0: the first of the wave's keys in the tile, whose K rows begin at sk.
     auto tile = [&](auto MASKED_, const int key0, const unsigned sk) __attribute__((always_inline)) {
         constexpr bool masked = decltype(MASKED_)::value != 0;
         bf16x8_t fa[2][2], fc[2];
-        auto load_a = [&](int mt, int s, int buf) __attribute__((always_inline)) {      // s: 16 keys s / KS, 32 columns s % KS
+        auto load_a = [&](int mt, int s, int buf, int part) __attribute__((always_inline)) {      // s: 16 keys s / KS, 32 columns s % KS
             const lds_u8_ptr q = reinterpret_cast<lds_u8_ptr>(sk + (ra0 ^ (unsigned)((s % KS) << 6)));
             const int off = (mt * 32 + 16 * (s / KS)) * (D * 2);
-            fa[buf][0] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<lds_u4_cptr>(q + off));
-            fa[buf][1] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<lds_u4_cptr>(q + (TILE + off)));
+            fa[buf][part] = read_rows(q + ((part == 0 ? TILE : 0) + off));
         };
         auto load_c = [&](int mt, int nt, int buf) __attribute__((always_inline)) {
-            const lds_u8_ptr q = reinterpret_cast<lds_u8_ptr>(sk + (ta0 ^ (unsigned)(nt << 5)));
-            const int off = mt * 32 * (D * 2);
-            const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(q + off));
-            const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(q + (off + 16 * (D * 2))));
-            fc[buf] = __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            fc[buf] = read_tokens<D>(reinterpret_cast<lds_u8_ptr>(sk + (ta0 ^ (unsigned)(nt << 5))) + mt * 32 * (D * 2));
         };
-        load_a(0, 0, 0);
+        load_a(0, 0, 0, 0);
+        load_a(0, 0, 0, 1);
 #pragma unroll
         for (int mt = 0; mt < (FINE ? 1 : 2); ++mt) {
             f32x4_t st[2][2], dpt[2][2];            // [16 keys][16 queries]
 #pragma unroll
             for (int s = 0; s < 2 * KS; ++s) {
                 const int k16 = s / KS, ks = s % KS, buf = s & 1;
-                if (s + 1 < 2 * KS) load_a(mt, s + 1, (s + 1) & 1);
-                else load_c(mt, 0, 0);
-                CF_SCHED_FENCE();
                 const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    st[k16][t] = mfma16(fa[buf][0], qf[t][ks], ks == 0 ? z : st[k16][t]);
-                    dpt[k16][t] = mfma16(fa[buf][1], dof[t][ks], ks == 0 ? negD[t] : dpt[k16][t]);
+                for (int m = 0; m < 4; ++m) {
+                    const int t = m & 1;
+                    if (m < 2) {
+                        if (s + 1 < 2 * KS) load_a(mt, s + 1, (s + 1) & 1, m);
+                        else if (m == 0) load_c(mt, 0, 0);
+                    }
+                    CF_SCHED_FENCE();
+                    if (m < 2) dpt[k16][t] = mfma16(fa[buf][0], dof[t][ks], ks == 0 ? negD[t] : dpt[k16][t]);
+                    else st[k16][t] = mfma16(fa[buf][1], qf[t][ks], ks == 0 ? z : st[k16][t]);
+                    CF_SCHED_FENCE();
                 }
-                CF_SCHED_FENCE();
             }
             // dS^T = P^T o (dP^T - D): lane = query, register = key
             bf16x8_t a[2];
@@ -519,14 +516,13 @@ __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_
                         }
                         st[k16][t][v] = pr * dpt[k16][t][v];
                     }
-                a[t] = __builtin_bit_cast(bf16x8_t, make_uint4(pack2(st[0][t][0], st[0][t][1]), pack2(st[0][t][2], st[0][t][3]),
-                                                               pack2(st[1][t][0], st[1][t][1]), pack2(st[1][t][2], st[1][t][3])));
+                a[t] = pack8(st[0][t], st[1][t]);
             }
             // dQ^T += K^T * dS^T: lane = query, register = column
 #pragma unroll
             for (int c = 0; c < NT; ++c) {
                 if (c + 1 < NT) load_c(mt, c + 1, (c + 1) & 1);
-                else if (!FINE && mt == 0) load_a(mt + 1, 0, 0);
+                else if (!FINE && mt == 0) { load_a(mt + 1, 0, 0, 0); load_a(mt + 1, 0, 0, 1); }
                 CF_SCHED_FENCE();
 #pragma unroll
                 for (int t = 0; t < 2; ++t) acc[t][c] = mfma16(fc[c & 1], a[t], acc[t][c]);
@@ -581,23 +577,8 @@ __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_
             for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<f32x4_t*>(part + nt * 16) = acc[t][nt];
             continue;
         }
-        auto store = [&](int nt, const f32x4_t& y) __attribute__((always_inline)) {
-            *reinterpret_cast<uint2*>(p.dq_kept + at + nt * 16) = make_uint2(pack2(y[0], y[1]), pack2(y[2], y[3]));
-        };
-        if constexpr (ROPE) {
-            const int64_t tab = (int64_t)pos[t] * (D / 2) + 4 * qd;
-#pragma unroll
-            for (int nt = 0; nt < NT / 2; ++nt) {
-                const f32x4_t c = *reinterpret_cast<const f32x4_t*>(p.rope_cos + tab + nt * 16);
-                const f32x4_t s = *reinterpret_cast<const f32x4_t*>(p.rope_sin + tab + nt * 16);
-                const f32x4_t u = acc[t][nt] * p.scale, w = acc[t][nt + NT / 2] * p.scale;
-                store(nt, u * c + w * s);
-                store(nt + NT / 2, w * c - u * s);
-            }
-        } else {
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) store(nt, acc[t][nt] * p.scale);
-        }
+        const int64_t tab = ROPE ? (int64_t)pos[t] * (D / 2) + 4 * qd : 0;
+        store_row<D, ROPE>(p.dq_kept + at, acc[t], p.scale, p.rope_cos + tab, p.rope_sin + tab);
     }
 }
 
@@ -626,16 +607,33 @@ __host__ __device__ constexpr int dkv_slot_index(int KS, bool even, int p) {
     return n;
 }
 
+// Rows jk of dK and dV: the results, or fp32, unscaled, to the block's own partials; `at`: offset of this lane's first column.
+template <int D, bool ROPE>
+__device__ __forceinline__ void store_dkv(const AttnParams& p, bool whole, int64_t at, int b, int jk, int qd, const f32x4_t (&dk)[D / 16],
+                                          const f32x4_t (&dv)[D / 16]) {
+    if (whole) {
+        const int64_t tab = ROPE ? (int64_t)((p.idx ? p.idx[jk] : jk) - b * p.S) * (D / 2) + 4 * qd : 0;
+        store_row<D, ROPE>(p.dk_kept + at, dk, p.scale, p.rope_cos + tab, p.rope_sin + tab);
+        store_row<D, false>(p.dv_kept + at, dv, 1.f, nullptr, nullptr);
+    } else {
+#pragma unroll
+        for (int nt = 0; nt < D / 16; ++nt) {
+            *reinterpret_cast<f32x4_t*>(p.dk_part + at + nt * 16) = dk[nt];
+            *reinterpret_cast<f32x4_t*>(p.dv_part + at + nt * 16) = dv[nt];
+        }
+    }
+}
+
 template <int D, bool ROPE>
 __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
-    constexpr int KS = D / 16, NT = D / 32;
+    constexpr int KS = D / 32, NT = D / 16;
     constexpr int TILE = 64 * D * 2;
     constexpr int STAGE = 2 * TILE + 512;       // Q tile, dO tile, lse2[64], D[64]
     extern __shared__ __align__(16) unsigned char smem[];
 
     // the wave number is the same in all lanes: saying so keeps everything derived from it in scalar registers
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int slot = lane & 31, hh = lane >> 5;
+    const int slot = lane & 15, qd = lane >> 4;
     const int G = p.Hq / p.Hkv;
     const int n_live = live_rows(p.n_kept, p.n_dev);
     if (D == 64 && p.dkv_both && attn_dkv_fine(p, n_live)) return;      // attn_dkv64_kernel takes these rows
@@ -657,31 +655,34 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     const int c0 = seq_begin + kt * 128;            // compact row of the tile's first key
     const int keys_in_tile = min(128, cnt - kt * 128);
 
-    // this lane's key
-    const int jk = c0 + wave * 32 + slot;
-    const bool kvalid = wave * 32 + slot < keys_in_tile;
-    bf16x8_t kf[KS], vf[KS];
-    {
-        const int64_t tok = kvalid ? (p.idx ? p.idx[jk] : jk) : 0;
+    // this lane's two keys, 16 apart
+    int jk[2];
+    bool kvalid[2];
+    bf16x8_t kf[2][KS], vf[2][KS];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        jk[u] = c0 + wave * 32 + u * 16 + slot;
+        kvalid[u] = wave * 32 + u * 16 + slot < keys_in_tile;
+        const int64_t tok = kvalid[u] ? (p.idx ? p.idx[jk[u]] : jk[u]) : 0;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             uint4 a = make_uint4(0, 0, 0, 0), c = make_uint4(0, 0, 0, 0);
-            if (kvalid) {
-                a = *reinterpret_cast<const uint4*>(p.k_full + tok * Nkv + g * D + ks * 16 + hh * 8);
-                c = *reinterpret_cast<const uint4*>(p.v_full + tok * Nkv + g * D + ks * 16 + hh * 8);
+            if (kvalid[u]) {
+                a = *reinterpret_cast<const uint4*>(p.k_full + tok * Nkv + g * D + ks * 32 + qd * 8);
+                c = *reinterpret_cast<const uint4*>(p.v_full + tok * Nkv + g * D + ks * 32 + qd * 8);
             }
-            kf[ks] = __builtin_bit_cast(bf16x8_t, a);
-            vf[ks] = __builtin_bit_cast(bf16x8_t, c);
+            kf[u][ks] = __builtin_bit_cast(bf16x8_t, a);
+            vf[u][ks] = __builtin_bit_cast(bf16x8_t, c);
         }
     }
     const float scale2 = p.scale * LOG2E;
     const int steps = (seq_end - c0 + 63) / 64;     // query tiles from the first key to the sequence end
 
-    f32x16_t dk[NT], dv[NT];
+    f32x4_t dk[2][NT], dv[2][NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) { dk[nt][v] = 0.f; dv[nt][v] = 0.f; }
+        for (int nt = 0; nt < NT; ++nt) dk[u][nt] = dv[u][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     // Q and dO rows of this sequence from its first key on, the current head's columns (set per head below)
     i32x4_t rsQ, rsO, rsL, rsD;
@@ -692,20 +693,13 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
         rsD = make_rsrc(p.stat + (int64_t)(p.Hq + h) * p.n_kept + c0, (int64_t)(seq_end - c0) * 4);
     };
     const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_addr_of(smem));
-    // Per-lane byte offsets of the fragment reads inside a 64-row tile, fixed for the whole kernel:
-    // row fragments (this lane's row of a 32-row half, d chunk ks) and token fragments (d block nt,
-    // low / high four rows of a 16-row block).  The XOR swizzle is folded in here, so a read in the
+    // Per-lane byte offsets of the fragment reads inside a 64-row tile, fixed for the whole kernel: a read in the
     // loop is "stage base + this + compile-time offset".
-    unsigned ra[KS], ta[NT][2];
+    unsigned ra[KS], ta[NT];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) ra[ks] = (unsigned)tile_off<D>(slot, ks * 2 + hh);
+    for (int ks = 0; ks < KS; ++ks) ra[ks] = frag_rows_at<D>(lane, ks);
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const int r = 4 * hh + ((lane & 15) >> 2);
-        const int chunk = nt * 4 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-        ta[nt][0] = (unsigned)tile_off<D>(r, chunk) + (lane & 1) * 8;
-        ta[nt][1] = (unsigned)tile_off<D>(r + 8, chunk) + (lane & 1) * 8;
-    }
+    for (int nt = 0; nt < NT; ++nt) ta[nt] = frag_tokens_at<D>(lane, nt);
     // ---- global -> LDS.  Per-lane offsets of a tile's loads inside a 64-row step (row * stride +
     // swizzled chunk) never change; the step's row offset is added per step.  Rows past the sequence
     // end lie outside the descriptors' ranges and arrive as zeros (their statistics too), which is
@@ -715,9 +709,7 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
         const int row = (4 * i + wave) * RPL + lane / NCH;
-        const int pc = lane % NCH;
-        const int sw = (D == 128) ? (((row & 3) << 2) | ((row >> 2) & 3)) : ((((row >> 1) & 1) << 2) | ((row >> 2) & 3));
-        voff[i] = (unsigned)row * (unsigned)(Nq * 2) + (unsigned)((pc ^ sw) << 4);
+        voff[i] = (unsigned)row * (unsigned)(Nq * 2) + (unsigned)(((lane % NCH) ^ tile_swz<D>(row)) << 4);
     }
     auto issue_q = [&](int step, int stage) __attribute__((always_inline)) {
         const unsigned sq = lds0 + stage * STAGE;
@@ -735,86 +727,77 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     constexpr int LPS = 2 * NLD + 2;                // loads per wave and step
 
     // ---- the pipeline.  The query rows go by in HALVES of 32 (two per 64-row step / LDS stage).  A
-    // half n needs three kinds of work: A(n) = S and dP (2*KS MFMAs against the wave's K and V
+    // half n needs three kinds of work: A(n) = S and dP (8*KS MFMAs against the wave's K and V
     // fragments), B(n) = P and dS from them (vector ALU: exp2, mask, products, packing), C(n) = dV and
     // dK (4*NT MFMAs).  A wave runs alone on its SIMD, so nothing overlaps unless the instruction
     // stream interleaves it: ITERATION t issues A(t+1), B(t) and C(t-1) together, one softmax value
-    // (two at d = 64) and the LDS reads of a later slot between two MFMA pairs, so that in the steady
+    // (two at d = 64) and the LDS reads of a later slot between two groups of four MFMAs, so that in the steady
     // state the matrix core runs back to back while the exponentials of the half before and the
     // fragment reads of the slots ahead proceed under it.  Fragment reads go through a ring of four
     // register pairs and are issued three slots ahead of their MFMAs, across iteration boundaries
     // too (the LDS answers a read in a few hundred cycles when four waves keep it busy; a single slot
-    // of lookahead left every MFMA pair waiting for it).
-    // A slot = one MFMA pair: A slot ks = {S += Qfrag * K[ks], dP += dOfrag * V[ks]}; C slot c =
-    // {dK[nt] += dS[j] * Qtokens, dV[nt] += P[j] * dOtokens}, j = c / NT, nt = c % NT.
+    // of lookahead left every group waiting for it).
+    // A slot = four MFMAs: A slot s = {S[q][u] += Qfrag * K[u][ks], dP[q][u] += dOfrag * V[u][ks]} for both groups u of 16 keys,
+    // q = s / KS the group of 16 queries and ks = s % KS the 32 columns; C slot nt = {dK[u][nt] += Qtokens * dS[u],
+    // dV[u][nt] += dOtokens * P[u]}.  dP accumulates from -D on.
     // Iterations come in pairs (even t = 2s, odd t = 2s+1) so that stage halves are compile-time.  In
     // the even iteration all C slots come first (with a third of the A slots between them): after
     // them no wave reads stage s-1 any more, so ONE barrier there both frees that stage for the loads
     // of step s+3 and publishes step s+1 (awaited just before it), whose rows the odd iteration's A
     // slots read.  Accumulation order of every output element is that of a plain loop over the rows.
-    constexpr int NP = 2 * KS;                      // slots per iteration (KS A slots, 2*NT = KS C slots)
+    constexpr int NP = 2 * NT;                      // slots per iteration (NT A slots, NT C slots)
     constexpr int VPS = 16 / NP;                    // softmax values per slot
-    constexpr int LOOK = KS >= 8 ? 3 : 2, RING = 4;     // the reads issued for the next iteration must follow the barrier
-    static_assert(2 * NT == KS && NP % RING == 0 && (16 % NP) == 0 && NP - LOOK >= 3 * KS / 2, "slot layout");
-    typedef __attribute__((address_space(3))) unsigned char* lds_u8_ptr;
-    typedef const __attribute__((address_space(3))) u32x4_t* lds_u4_cptr;
-    typedef float f32x4v_t __attribute__((ext_vector_type(4)));
-    typedef const __attribute__((address_space(3))) f32x4v_t* lds_f4_cptr;
-    typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
+    constexpr int LOOK = NT >= 8 ? 3 : 2, RING = 4;     // the reads issued for the next iteration must follow the barrier
+    static_assert(2 * KS == NT && NP % RING == 0 && (16 % NP) == 0 && NP - LOOK >= 3 * NT / 2, "slot layout");
 
-    f32x16_t st[2], dpt[2];                         // S / dP of the half being accumulated and of the one in B, by parity
-    bf16x8_t ap[2][2], ads[2][2];                   // packed P and dS, [half parity][16-query block]
+    f32x4_t st[2][2][2], dpt[2][2][2];              // S / dP of the half being accumulated and of the one in B, by parity: [q][u]
+    unsigned ap[2][2][4], ads[2][2][4];             // packed P and dS, [half parity][u]
     bf16x8_t op[RING][2];                           // fragment pairs on their way to the MFMAs
-    f32x4v_t lqr[2], dqr[2];                        // log2(e)*LSE and D of four queries at a time, two groups in flight
+    f32x4_t lq[2], nd[2];                           // log2(e)*LSE of the queries of group q of the half in B, -D of the half in A
+    const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int h2 = 0; h2 < 2; ++h2)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) { st[h2][v] = 0.f; dpt[h2][v] = 0.f; }
+    for (int i = 0; i < 8; ++i) st[i >> 2][(i >> 1) & 1][i & 1] = dpt[i >> 2][(i >> 1) & 1][i & 1] = z;
 
     // is position p of an (even / odd) iteration an A slot, and which A or C slot is it
-    constexpr auto is_a = [](bool even, int p) constexpr { return dkv_is_a(KS, even, p); };
-    constexpr auto slot_index = [](bool even, int p) constexpr { return dkv_slot_index(KS, even, p); };
+    constexpr auto is_a = [](bool even, int p) constexpr { return dkv_is_a(NT, even, p); };
+    constexpr auto slot_index = [](bool even, int p) constexpr { return dkv_slot_index(NT, even, p); };
     // reads of an A slot (row fragments of Q and dO, half hf of the stage at sb) or of a C slot (token
     // fragments) into ring entry r
-    auto read_a = [&](unsigned sb, int hf, int ks, int r) __attribute__((always_inline)) {
-        const lds_u8_ptr q = reinterpret_cast<lds_u8_ptr>(sb + ra[ks]);
-        op[r][0] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<lds_u4_cptr>(q + hf * 32 * (D * 2)));
-        op[r][1] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<lds_u4_cptr>(q + (TILE + hf * 32 * (D * 2))));
+    // (part 0: of dO and -D, part 1: of Q)
+    auto read_a = [&](unsigned sb, int hf, int s, int r, int part) __attribute__((always_inline)) {
+        const int row = hf * 32 + (s / KS) * 16;
+        op[r][part] = read_rows(reinterpret_cast<lds_u8_ptr>(sb + ra[s % KS]) + ((part == 0 ? TILE : 0) + row * (D * 2)));
+        if (part == 0 && s % KS == 0)
+            nd[s / KS] = *reinterpret_cast<lds_f4_cptr>(reinterpret_cast<lds_u8_ptr>(sb + 2 * TILE + 16 * qd) + (64 + row) * 4);
     };
-    auto read_c = [&](unsigned sb, int hf, int c, int r) __attribute__((always_inline)) {
-        const int j = c / NT, nt = c % NT;
-        const lds_u8_ptr lo = reinterpret_cast<lds_u8_ptr>(sb + ta[nt][0]);
-        const lds_u8_ptr hi = reinterpret_cast<lds_u8_ptr>(sb + ta[nt][1]);
-        const int off = (hf * 32 + 16 * j) * (D * 2);
-        const s16x4_t q0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lo + off));
-        const s16x4_t q1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(hi + off));
-        const s16x4_t o0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lo + (TILE + off)));
-        const s16x4_t o1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(hi + (TILE + off)));
-        op[r][0] = __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(q0, q1, 0, 1, 2, 3, 4, 5, 6, 7));
-        op[r][1] = __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(o0, o1, 0, 1, 2, 3, 4, 5, 6, 7));
+    auto read_c = [&](unsigned sb, int hf, int nt, int r, int part) __attribute__((always_inline)) {
+        op[r][part] = read_tokens<D>(reinterpret_cast<lds_u8_ptr>(sb + ta[nt]) + ((part == 0 ? TILE : 0) + hf * 32 * (D * 2)));
     };
-    // statistics of queries [4*g4, 4*g4 + 4) (+ 4*hh per lane half) of half hf of the stage at sb
-    auto read_stats = [&](unsigned sb, int hf, int g4, int buf) __attribute__((always_inline)) {
-        const lds_u8_ptr ps = reinterpret_cast<lds_u8_ptr>(sb + 2 * TILE + 16 * hh);
-        lqr[buf] = *reinterpret_cast<lds_f4_cptr>(ps + (hf * 32 + 8 * g4) * 4);
-        dqr[buf] = *reinterpret_cast<lds_f4_cptr>(ps + (64 + hf * 32 + 8 * g4) * 4);
+    // log2(e)*LSE of this lane's queries (4*qd on) of group q of half hf of the stage at sb
+    auto read_lse = [&](unsigned sb, int hf, int q) __attribute__((always_inline)) {
+        lq[q] = *reinterpret_cast<lds_f4_cptr>(reinterpret_cast<lds_u8_ptr>(sb + 2 * TILE + 16 * qd) + (hf * 32 + q * 16) * 4);
     };
-    // P and dS of value v (query 8*(v/4) + 4*hh + v%4 of half t): lane = key, register = query
-    auto soft = [&](int par, int v, int qrow0, auto MASKED) __attribute__((always_inline)) {
+    // P and dS of value v (key group v / 8, query 16*(v/4 % 2) + 4*qd + v%4 of half t): lane = key, register = query
+    auto soft_p = [&](int par, int v, int qrow0, auto MASKED) __attribute__((always_inline)) {
         constexpr bool masked = decltype(MASKED)::value != 0;
-        const int v4 = v >> 2, e = v & 3;
-        const float lv = lqr[v4 & 1][e], dd = dqr[v4 & 1][e];
-        float pr = __builtin_amdgcn_exp2f(st[par][v] * scale2 - lv);
+        const int u = v >> 3, q = (v >> 2) & 1, e = v & 3;
+        float pr = __builtin_amdgcn_exp2f(st[par][q][u][e] * scale2 - lq[q][e]);
         if (masked) {
-            const bool ok = kvalid && (qrow0 + 8 * v4 + 4 * hh + e >= jk);
+            const bool ok = kvalid[u] & (qrow0 + 16 * q + 4 * qd + e >= jk[u]);
             pr = ok ? pr : 0.f;
         }
-        st[par][v] = pr;
-        dpt[par][v] = pr * (dpt[par][v] - dd);
-        if ((v & 7) == 7) {                          // a 16-query block (8 registers) is complete
-            ap[par][v >> 3] = pack8(st[par], v >> 3);
-            ads[par][v >> 3] = pack8(dpt[par], v >> 3);
+        st[par][q][u][e] = pr;
+    };
+    auto soft_ds = [&](int par, int v) __attribute__((always_inline)) {
+        const int u = v >> 3, q = (v >> 2) & 1, e = v & 3;
+        dpt[par][q][u][e] *= st[par][q][u][e];
+        if (e & 1) {
+            ap[par][u][2 * q + (e >> 1)] = pack2(st[par][q][u][e - 1], st[par][q][u][e]);
+            ads[par][u][2 * q + (e >> 1)] = pack2(dpt[par][q][u][e - 1], dpt[par][q][u][e]);
         }
+    };
+    auto operand = [](const unsigned (&w)[4]) __attribute__((always_inline)) {
+        return __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
     };
     // One iteration (see above).  KIND 0: steady state; 1: the very first iteration (no half before it:
     // the C slots' MFMAs are left out, their reads are harmless); 2: the drain after the last half
@@ -835,65 +818,68 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
         const int qrow0 = c0 + (2 * s + (EVEN ? 0 : 1)) * 32;       // compact row of the first query of half t
         static_for<NP>([&](auto P) __attribute__((always_inline)) {
             constexpr int pp = decltype(P)::value;
-            if constexpr (EVEN && pp == 3 * KS / 2 && KIND != 2) {
+            if constexpr (EVEN && pp == 3 * NT / 2 && KIND != 2) {
                 // every C slot of this iteration has its fragments: nobody reads stage s-1 any more
                 wait_vmcnt<LPS>();          // step s+1 has landed; step s+2 may be in flight
                 lds_barrier();
                 issue_q(s + 3, (s + 3) & 3);
             }
-            // fragment reads of the slot LOOK positions ahead
-            {
-                constexpr int q = pp + LOOK;
-                if constexpr (q < NP) {
-                    if constexpr (is_a(EVEN, q)) read_a(sbA, hfA, slot_index(EVEN, q), q % RING);
-                    else read_c(sbC, hfC, slot_index(EVEN, q), q % RING);
+            // Ahead of each of the slot's four MFMAs go a quarter of what else there is to do: the fragment reads of the slot LOOK
+            // positions ahead (0, 1) and softmax values of half t, with the next group's row terms fetched ahead (2, 3).  An MFMA
+            // takes 16 cycles, four issue slots: in front of the four together, the matrix core waited for all of it ([2 x 2048 of 4096 rows, 32/8 heads, d =
+            // 128] call 356 us, so 342; [4800 of 8000, 4/1] 228 and 209; [8192 of 16384, 24/8] 1716 and 1637).
+            static_for<4>([&](auto M_) __attribute__((always_inline)) {
+                constexpr int m = decltype(M_)::value;
+                if constexpr (m < 2) {
+                    constexpr int q = pp + LOOK;
+                    if constexpr (q < NP) {
+                        if constexpr (is_a(EVEN, q)) read_a(sbA, hfA, slot_index(EVEN, q), q % RING, m);
+                        else read_c(sbC, hfC, slot_index(EVEN, q), q % RING, m);
+                    } else if constexpr (KIND != 2) {
+                        constexpr int qn = q - NP;
+                        if constexpr (is_a(!EVEN, qn)) read_a(sbA_n, hfA_n, slot_index(!EVEN, qn), q % RING, m);
+                        else read_c(sbC_n, hfC_n, slot_index(!EVEN, qn), q % RING, m);
+                    }
                 } else if constexpr (KIND != 2) {
-                    constexpr int qn = q - NP;
-                    if constexpr (is_a(!EVEN, qn)) read_a(sbA_n, hfA_n, slot_index(!EVEN, qn), q % RING);
-                    else read_c(sbC_n, hfC_n, slot_index(!EVEN, qn), q % RING);
-                }
-            }
-            if constexpr (KIND != 2) {
-                // The A-slot MFMAs are inline assembly (see below), so the compiler does not know that the S and dP
-                // values which the previous iteration's last A slot produced may still be on their way when this
-                // iteration's first softmax value reads them: eight wait states here, on top of the reads above,
-                // cover the eleven that an 8-pass MFMA needs ahead of a vector ALU read of its destination.
-                if constexpr (pp == 0) asm volatile("s_nop 7");
-                // softmax values of half t, with the statistics of the next four queries fetched one group ahead
-#pragma unroll
-                for (int e = 0; e < VPS; ++e) {
-                    const int v = pp * VPS + e;
-                    if ((v & 3) == 0) {
-                        if (v < 12) read_stats(sbB, hfB, (v >> 2) + 1, ((v >> 2) + 1) & 1);
-                        else read_stats(sbB_n, hfB_n, 0, 0);
+                    constexpr int v = pp * VPS + (VPS == 2 ? m - 2 : 0);
+                    if constexpr (VPS == 2 || m == 2) {
+                        if constexpr (v == 0) read_lse(sbB, hfB, 1);
+                        if constexpr (v == 12) read_lse(sbB_n, hfB_n, 0);
+                        soft_p(parB, v, qrow0, MASKED);
                     }
-                    soft(parB, v, qrow0, MASKED);
+                    if constexpr (VPS == 2 || m == 3) soft_ds(parB, v);
                 }
-            }
-            CF_SCHED_FENCE();
-            if constexpr (is_a(EVEN, pp)) {
-                if constexpr (KIND != 2) {
-                    constexpr int ks = slot_index(EVEN, pp);
-                    // Inline assembly keeps S and dP in the VGPR file, where the softmax arithmetic reads them:
-                    // with the builtin the register allocator accumulates them in AGPRs and copies all 32
-                    // registers of a half out again, one v_accvgpr_read each.  The price is that the compiler
-                    // no longer sees these MFMAs' latency (see the wait states at the head of an iteration).
-                    if constexpr (ks == 0) {
-                        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(st[parA]) : "v"(op[pp % RING][0]), "v"(kf[ks]));
-                        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(dpt[parA]) : "v"(op[pp % RING][1]), "v"(vf[ks]));
-                    } else {
-                        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(st[parA]) : "v"(op[pp % RING][0]), "v"(kf[ks]));
-                        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(dpt[parA]) : "v"(op[pp % RING][1]), "v"(vf[ks]));
+                CF_SCHED_FENCE();
+                constexpr int u = m & 1;
+                if constexpr (is_a(EVEN, pp)) {
+                    if constexpr (KIND != 2) {
+                        constexpr int s = slot_index(EVEN, pp), q = s / KS, ks = s % KS;
+                        // Inline assembly keeps S and dP in the VGPR file, where the softmax arithmetic reads them:
+                        // with the builtin the register allocator accumulates them in AGPRs and copies all 32
+                        // registers of a half out again, one v_accvgpr_read each.  The price is that the compiler
+                        // no longer sees these MFMAs' latency.  A softmax value is read eight MFMAs or more after the last one that writes
+                        // it: query group 0 is complete in the middle of an iteration, group 1's first value is read in slot 4 / VPS.
+                        if constexpr (m < 2) {
+                            if constexpr (ks == 0)
+                                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" : "=&v"(dpt[parA][q][u]) : "v"(op[pp % RING][0]), "v"(vf[u][ks]), "v"(nd[q]));
+                            else
+                                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(dpt[parA][q][u]) : "v"(op[pp % RING][0]), "v"(vf[u][ks]));
+                        } else {
+                            if constexpr (ks == 0)
+                                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(st[parA][q][u]) : "v"(op[pp % RING][1]), "v"(kf[u][ks]));
+                            else
+                                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(st[parA][q][u]) : "v"(op[pp % RING][1]), "v"(kf[u][ks]));
+                        }
+                        // -D keeps its registers to the end of the slot: the vector ALU must not write to them while an MFMA reads them
+                        if constexpr (ks == 0 && m == 3) asm volatile("" : : "v"(nd[q]));
                     }
+                } else if constexpr (KIND != 1) {
+                    constexpr int nt = slot_index(EVEN, pp);
+                    if constexpr (m < 2) dv[u][nt] = mfma16(op[pp % RING][0], operand(ap[parC][u]), dv[u][nt]);
+                    else dk[u][nt] = mfma16(op[pp % RING][1], operand(ads[parC][u]), dk[u][nt]);
                 }
-            } else {
-                if constexpr (KIND != 1) {
-                    constexpr int c = slot_index(EVEN, pp), j = c / NT, nt = c % NT;
-                    dk[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ads[parC][j], op[pp % RING][0], dk[nt], 0, 0, 0);
-                    dv[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ap[parC][j], op[pp % RING][1], dv[nt], 0, 0, 0);
-                }
-            }
-            CF_SCHED_FENCE();
+                CF_SCHED_FENCE();
+            });
         });
     };
 
@@ -916,24 +902,26 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     // issued as well: every pair would then wait out a whole global-memory latency.
     wait_vmcnt<0>();
     lds_barrier();
-    // head: A(0), then the statistics group and the fragment reads that the first iteration starts with
+    // head: A(0), then the row terms and the fragment reads that the first iteration starts with
     {
-        f32x16_t z;
+        static_for<NT>([&](auto S_) __attribute__((always_inline)) {
+            constexpr int s = decltype(S_)::value, q = s / KS, ks = s % KS;
+            read_a(lds0, 0, s, s % RING, 0);
+            read_a(lds0, 0, s, s % RING, 1);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) z[v] = 0.f;
-        st[0] = z;
-        dpt[0] = z;
-        static_for<KS>([&](auto K_) __attribute__((always_inline)) {
-            constexpr int ks = decltype(K_)::value;
-            read_a(lds0, 0, ks, ks % RING);
-            st[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[ks % RING][0], kf[ks], st[0], 0, 0, 0);
-            dpt[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[ks % RING][1], vf[ks], dpt[0], 0, 0, 0);
+            for (int u = 0; u < 2; ++u) {
+                dpt[0][q][u] = mfma16(op[s % RING][0], vf[u][ks], ks == 0 ? nd[q] : dpt[0][q][u]);
+                st[0][q][u] = mfma16(op[s % RING][1], kf[u][ks], ks == 0 ? z : st[0][q][u]);
+            }
         });
-        read_stats(lds0, 0, 0, 0);
+        read_lse(lds0, 0, 0);
         static_for<LOOK>([&](auto Q_) __attribute__((always_inline)) {
             constexpr int q = decltype(Q_)::value;
-            if constexpr (is_a(true, q)) read_a(lds0, 1, slot_index(true, q), q % RING);
-            else read_c(lds0 + 3 * STAGE, 1, slot_index(true, q), q % RING);      // a half that does not exist: never used
+            static_for<2>([&](auto M_) __attribute__((always_inline)) {
+                constexpr int m = decltype(M_)::value;
+                if constexpr (is_a(true, q)) read_a(lds0, 1, slot_index(true, q), q % RING, m);
+                else read_c(lds0 + 3 * STAGE, 1, slot_index(true, q), q % RING, m);     // a half that does not exist: never used
+            });
         });
         CF_SCHED_FENCE();
     }
@@ -956,39 +944,11 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     wait_vmcnt<0>();                                // the zero-fill loads of the steps past the end
     }
 
-    if (G == HP) {
-        if constexpr (ROPE) {
-            const int pos = kvalid ? (p.idx ? p.idx[jk] : jk) - b * p.S : 0;
-            store_rows_rotated<D>(p.dk_kept + (int64_t)(c0 + wave * 32) * Nkv + g * D, Nkv, keys_in_tile - wave * 32, dk, p.scale, lane,
-                                  pos, p.rope_cos, p.rope_sin);
-        }
+    const bool whole = G == HP;
+    const int64_t part = whole ? 0 : (int64_t)((h0 - g * G) / HP) * p.n_kept * Nkv;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = wave * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
-                if (r < keys_in_tile) {
-                    const int64_t off = (int64_t)(c0 + r) * Nkv + g * D + nt * 32 + slot;
-                    if constexpr (!ROPE) p.dk_kept[off] = f32_to_bf16(dk[nt][v] * p.scale);
-                    p.dv_kept[off] = f32_to_bf16(dv[nt][v]);
-                }
-            }
-        }
-    } else {
-        const int64_t part = (int64_t)((h0 - g * G) / HP) * p.n_kept * Nkv;
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = wave * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
-                if (r < keys_in_tile) {
-                    const int64_t off = part + (int64_t)(c0 + r) * Nkv + g * D + nt * 32 + slot;
-                    p.dk_part[off] = dk[nt][v];
-                    p.dv_part[off] = dv[nt][v];
-                }
-            }
-        }
-    }
+    for (int u = 0; u < 2; ++u)
+        if (kvalid[u]) store_dkv<D, ROPE>(p, whole, part + (int64_t)jk[u] * Nkv + g * D + 4 * qd, b, jk[u], qd, dk[u], dv[u]);
 }
 
 // ---------------------------------------------------------------------------
@@ -999,17 +959,17 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
 // overlap each other's matrix, vector and LDS phases; a plain order of the phases is then better than the software pipeline
 // that a lone wave needs, as long as there are two blocks for every CU and more to follow: whole attention call at d = 64, this
 // kernel and the pipelined one, [8192 rows, 32/32 heads, S = 2048] 274 and 322 us, [4096, 64/64, S = 1024] 177 and 212.  Fragment reads
-// run one MFMA pair ahead.  The accumulation order of every element is that of the pipelined kernel.
+// run one group of four MFMAs ahead.  The accumulation order of every element is that of the pipelined kernel.
 // FINE: 64 keys per block; the two waves of a group of 32 keys take the first and the second 32 queries of every step, and their sums
 // meet in LDS at the end: half the step and twice the blocks, as in the dQ kernel (attn_dkv_fine_rows says where).
 template <bool ROPE, bool FINE>
 __device__ __forceinline__ void attn_dkv64_block(const AttnParams& p, const int n_live, unsigned char* smem) {
-    constexpr int D = 64, KS = D / 16, NT = D / 32, KT = FINE ? 64 : 128;
+    constexpr int D = 64, KS = D / 32, NT = D / 16, KT = FINE ? 64 : 128;
     constexpr int TILE = 64 * D * 2;
     constexpr int STAGE = 2 * TILE + 512;       // Q tile, dO tile, lse2[64], D[64]
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave = FINE ? wv & 1 : wv, qh = FINE ? wv >> 1 : 0;       // group of 32 keys; half of the steps
-    const int slot = lane & 31, hh = lane >> 5;
+    const int slot = lane & 15, qd = lane >> 4;
     const int G = p.Hq / p.Hkv;
     const int HP = attn_heads_per_block(n_live, p.Hq, G, p.n_slots);
     // block numbering as in attn_dkv_kernel: key tile by key tile, blocks without work last
@@ -1025,121 +985,123 @@ __device__ __forceinline__ void attn_dkv64_block(const AttnParams& p, const int 
     const int c0 = seq_begin + kt * KT;            // compact row of the tile's first key
     const int keys_in_tile = min(KT, cnt - kt * KT);
 
-    const int jk = c0 + wave * 32 + slot;           // this lane's key
-    const bool kvalid = wave * 32 + slot < keys_in_tile;
-    bf16x8_t kf[KS], vf[KS];
-    {
-        const int64_t tok = kvalid ? (p.idx ? p.idx[jk] : jk) : 0;
+    int jk[2];                                      // this lane's two keys, 16 apart
+    bool kvalid[2];
+    bf16x8_t kf[2][KS], vf[2][KS];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        jk[u] = c0 + wave * 32 + u * 16 + slot;
+        kvalid[u] = wave * 32 + u * 16 + slot < keys_in_tile;
+        const int64_t tok = kvalid[u] ? (p.idx ? p.idx[jk[u]] : jk[u]) : 0;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             uint4 a = make_uint4(0, 0, 0, 0), c = make_uint4(0, 0, 0, 0);
-            if (kvalid) {
-                a = *reinterpret_cast<const uint4*>(p.k_full + tok * Nkv + g * D + ks * 16 + hh * 8);
-                c = *reinterpret_cast<const uint4*>(p.v_full + tok * Nkv + g * D + ks * 16 + hh * 8);
+            if (kvalid[u]) {
+                a = *reinterpret_cast<const uint4*>(p.k_full + tok * Nkv + g * D + ks * 32 + qd * 8);
+                c = *reinterpret_cast<const uint4*>(p.v_full + tok * Nkv + g * D + ks * 32 + qd * 8);
             }
-            kf[ks] = __builtin_bit_cast(bf16x8_t, a);
-            vf[ks] = __builtin_bit_cast(bf16x8_t, c);
+            kf[u][ks] = __builtin_bit_cast(bf16x8_t, a);
+            vf[u][ks] = __builtin_bit_cast(bf16x8_t, c);
         }
     }
     const float scale2 = p.scale * LOG2E;
     const int steps = (seq_end - c0 + 63) / 64;     // query tiles from the first key to the sequence end
 
-    f32x16_t dk[NT], dv[NT];
+    f32x4_t dk[2][NT], dv[2][NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) { dk[nt][v] = 0.f; dv[nt][v] = 0.f; }
+        for (int nt = 0; nt < NT; ++nt) dk[u][nt] = dv[u][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_addr_of(smem));
-    unsigned ra[KS], ta[NT][2];                     // per-lane offsets of the fragment reads inside a tile (see attn_dkv_kernel)
+    unsigned ra[KS], ta[NT];                        // per-lane offsets of the fragment reads inside a tile (see attn_dkv_kernel)
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) ra[ks] = (unsigned)tile_off<D>(slot, ks * 2 + hh);
+    for (int ks = 0; ks < KS; ++ks) ra[ks] = frag_rows_at<D>(lane, ks);
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const int r = 4 * hh + ((lane & 15) >> 2);
-        const int chunk = nt * 4 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-        ta[nt][0] = (unsigned)tile_off<D>(r, chunk) + (lane & 1) * 8;
-        ta[nt][1] = (unsigned)tile_off<D>(r + 8, chunk) + (lane & 1) * 8;
-    }
+    for (int nt = 0; nt < NT; ++nt) ta[nt] = frag_tokens_at<D>(lane, nt);
     // global -> LDS as in attn_dkv_kernel; rows past the sequence end arrive as zeros
     constexpr int NCH = D / 8, RPL = 64 / NCH, NLD = 64 / RPL / 4, LPS = 2 * NLD + 2;
     unsigned voff[NLD];
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
         const int row = (4 * i + wv) * RPL + lane / NCH;
-        const int sw = (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
-        voff[i] = (unsigned)row * (unsigned)(Nq * 2) + (unsigned)(((lane % NCH) ^ sw) << 4);
+        voff[i] = (unsigned)row * (unsigned)(Nq * 2) + (unsigned)(((lane % NCH) ^ tile_swz<D>(row)) << 4);
     }
-    typedef __attribute__((address_space(3))) unsigned char* lds_u8_ptr;
-    typedef const __attribute__((address_space(3))) u32x4_t* lds_u4_cptr;
-    typedef float f32x4v_t __attribute__((ext_vector_type(4)));
-    typedef const __attribute__((address_space(3))) f32x4v_t* lds_f4_cptr;
-    typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
 
     bf16x8_t fa[2][2], fc[2][2];
-    auto load_a = [&](unsigned sb, int hf, int ks, int buf) __attribute__((always_inline)) {
-        const lds_u8_ptr q = reinterpret_cast<lds_u8_ptr>(sb + ra[ks]);
-        fa[buf][0] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<lds_u4_cptr>(q + hf * 32 * (D * 2)));
-        fa[buf][1] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<lds_u4_cptr>(q + (TILE + hf * 32 * (D * 2))));
+    // s: 16 queries s / KS, 32 columns s % KS; part 0: of dO, part 1: of Q
+    auto load_a = [&](unsigned sb, int hf, int s, int part) __attribute__((always_inline)) {
+        fa[s & 1][part] = read_rows(reinterpret_cast<lds_u8_ptr>(sb + ra[s % KS]) + ((part == 0 ? TILE : 0) + (hf * 32 + 16 * (s / KS)) * (D * 2)));
     };
-    auto load_c = [&](unsigned sb, int hf, int c, int buf) __attribute__((always_inline)) {
-        const lds_u8_ptr lo = reinterpret_cast<lds_u8_ptr>(sb + ta[c % NT][0]);
-        const lds_u8_ptr hi = reinterpret_cast<lds_u8_ptr>(sb + ta[c % NT][1]);
-        const int off = (hf * 32 + 16 * (c / NT)) * (D * 2);
-        const s16x4_t q0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lo + off));
-        const s16x4_t q1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(hi + off));
-        const s16x4_t o0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lo + (TILE + off)));
-        const s16x4_t o1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(hi + (TILE + off)));
-        fc[buf][0] = __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(q0, q1, 0, 1, 2, 3, 4, 5, 6, 7));
-        fc[buf][1] = __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(o0, o1, 0, 1, 2, 3, 4, 5, 6, 7));
+    auto load_c = [&](unsigned sb, int hf, int nt, int part) __attribute__((always_inline)) {
+        fc[nt & 1][part] = read_tokens<D>(reinterpret_cast<lds_u8_ptr>(sb + ta[nt]) + ((part == 0 ? TILE : 0) + hf * 32 * (D * 2)));
     };
     // One step of 64 queries in the stage at sb, whose first query is compact row qrow0
     // (FINE: sb and ss, the rows and their statistics, and qrow0 begin at the wave's half)
     auto step = [&](auto MASKED_, const unsigned sb, const unsigned ss, const int qrow0) __attribute__((always_inline)) {
         constexpr bool masked = decltype(MASKED_)::value != 0;
         load_a(sb, 0, 0, 0);
+        load_a(sb, 0, 0, 1);
 #pragma unroll
         for (int hf = 0; hf < (FINE ? 1 : 2); ++hf) {
-            f32x16_t st, dpt;
+            f32x4_t st[2][2], dpt[2][2];            // [16 queries][16 keys]
+            f32x4_t lq[2], nd[2];                   // log2(e)*LSE and -D of this lane's queries
+            const lds_u8_ptr ps = reinterpret_cast<lds_u8_ptr>(ss + 16 * qd);
 #pragma unroll
-            for (int v = 0; v < 16; ++v) { st[v] = 0.f; dpt[v] = 0.f; }
-            f32x4v_t lq[2], dq[2];                  // log2(e)*LSE and D of four queries at a time, one group ahead
-            const lds_u8_ptr ps = reinterpret_cast<lds_u8_ptr>(ss + 16 * hh);
-            auto load_stats = [&](int v4) __attribute__((always_inline)) {
-                lq[v4 & 1] = *reinterpret_cast<lds_f4_cptr>(ps + (hf * 32 + 8 * v4) * 4);
-                dq[v4 & 1] = *reinterpret_cast<lds_f4_cptr>(ps + (64 + hf * 32 + 8 * v4) * 4);
-            };
+            for (int q = 0; q < 2; ++q) nd[q] = *reinterpret_cast<lds_f4_cptr>(ps + (64 + hf * 32 + 16 * q) * 4);
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                if (ks + 1 < KS) load_a(sb, hf, ks + 1, (ks + 1) & 1);
-                else { load_stats(0); load_c(sb, hf, 0, 0); }
-                CF_SCHED_FENCE();
-                st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks & 1][0], kf[ks], st, 0, 0, 0);
-                dpt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks & 1][1], vf[ks], dpt, 0, 0, 0);
-                CF_SCHED_FENCE();
-            }
-            // P and dS: lane = key, register = query 8*(v/4) + 4*hh + v%4 of the half
+            for (int s = 0; s < 2 * KS; ++s) {
+                const int q = s / KS, ks = s % KS, buf = s & 1;
+                const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
+                if (s + 1 == 2 * KS)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int v4 = v >> 2, e = v & 3;
-                if (e == 0 && v4 < 3) load_stats(v4 + 1);
-                float pr = __builtin_amdgcn_exp2f(st[v] * scale2 - lq[v4 & 1][e]);
-                if (masked) {
-                    const bool ok = kvalid && (qrow0 + hf * 32 + 8 * v4 + 4 * hh + e >= jk);
-                    pr = ok ? pr : 0.f;
+                    for (int i = 0; i < 2; ++i) lq[i] = *reinterpret_cast<lds_f4_cptr>(ps + (hf * 32 + 16 * i) * 4);
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {       // a fragment read ahead of each of the first two MFMAs
+                    const int u = m & 1;
+                    if (m < 2) {
+                        if (s + 1 < 2 * KS) load_a(sb, hf, s + 1, m);
+                        else load_c(sb, hf, 0, m);
+                    }
+                    CF_SCHED_FENCE();
+                    if (m < 2) dpt[q][u] = mfma16(fa[buf][0], vf[u][ks], ks == 0 ? nd[q] : dpt[q][u]);
+                    else st[q][u] = mfma16(fa[buf][1], kf[u][ks], ks == 0 ? z : st[q][u]);
+                    CF_SCHED_FENCE();
                 }
-                st[v] = pr;
-                dpt[v] = pr * (dpt[v] - dq[v4 & 1][e]);
             }
-            const bf16x8_t ap[2] = {pack8(st, 0), pack8(st, 1)}, ads[2] = {pack8(dpt, 0), pack8(dpt, 1)};
+            // P and dS: lane = key, register = query
+            bf16x8_t ap[2], ads[2];
 #pragma unroll
-            for (int c = 0; c < 2 * NT; ++c) {
-                if (c + 1 < 2 * NT) load_c(sb, hf, c + 1, (c + 1) & 1);
-                else if (!FINE && hf == 0) load_a(sb, 1, 0, 0);
-                CF_SCHED_FENCE();
-                dk[c % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ads[c / NT], fc[c & 1][0], dk[c % NT], 0, 0, 0);
-                dv[c % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ap[c / NT], fc[c & 1][1], dv[c % NT], 0, 0, 0);
-                CF_SCHED_FENCE();
+            for (int u = 0; u < 2; ++u) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        float pr = __builtin_amdgcn_exp2f(st[q][u][e] * scale2 - lq[q][e]);
+                        if (masked) {
+                            const bool ok = kvalid[u] && (qrow0 + hf * 32 + 16 * q + 4 * qd + e >= jk[u]);
+                            pr = ok ? pr : 0.f;
+                        }
+                        st[q][u][e] = pr;
+                        dpt[q][u][e] *= pr;
+                    }
+                ap[u] = pack8(st[0][u], st[1][u]);
+                ads[u] = pack8(dpt[0][u], dpt[1][u]);
+            }
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const int u = m & 1;
+                    if (m < 2) {
+                        if (nt + 1 < NT) load_c(sb, hf, nt + 1, m);
+                        else if (!FINE && hf == 0) load_a(sb, 1, 0, m);
+                    }
+                    CF_SCHED_FENCE();
+                    if (m < 2) dv[u][nt] = mfma16(fc[nt & 1][0], ap[u], dv[u][nt]);
+                    else dk[u][nt] = mfma16(fc[nt & 1][1], ads[u], dk[u][nt]);
+                    CF_SCHED_FENCE();
+                }
             }
         }
     };
@@ -1181,53 +1143,31 @@ __device__ __forceinline__ void attn_dkv64_block(const AttnParams& p, const int 
 
     if constexpr (FINE) {
         lds_barrier();                              // every wave is done with the stages
-        float4* buf = reinterpret_cast<float4*>(smem) + wave * (2 * NT * 4 * 64) + lane;
+        f32x4_t* buf = reinterpret_cast<f32x4_t*>(smem) + wave * (4 * NT * 64) + lane;
         if (qh == 1) {
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
+            for (int u = 0; u < 2; ++u)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    buf[(nt * 4 + q) * 64] = make_float4(dk[nt][4 * q], dk[nt][4 * q + 1], dk[nt][4 * q + 2], dk[nt][4 * q + 3]);
-                    buf[((NT + nt) * 4 + q) * 64] = make_float4(dv[nt][4 * q], dv[nt][4 * q + 1], dv[nt][4 * q + 2], dv[nt][4 * q + 3]);
+                for (int nt = 0; nt < NT; ++nt) {
+                    buf[(u * NT + nt) * 64] = dk[u][nt];
+                    buf[((2 + u) * NT + nt) * 64] = dv[u][nt];
                 }
         }
         lds_barrier();
         if (qh == 1) return;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 a = buf[(nt * 4 + q) * 64], b = buf[((NT + nt) * 4 + q) * 64];
-                dk[nt][4 * q] += a.x; dk[nt][4 * q + 1] += a.y; dk[nt][4 * q + 2] += a.z; dk[nt][4 * q + 3] += a.w;
-                dv[nt][4 * q] += b.x; dv[nt][4 * q + 1] += b.y; dv[nt][4 * q + 2] += b.z; dv[nt][4 * q + 3] += b.w;
+            for (int nt = 0; nt < NT; ++nt) {
+                dk[u][nt] += buf[(u * NT + nt) * 64];
+                dv[u][nt] += buf[((2 + u) * NT + nt) * 64];
             }
     }
     const bool whole = G == HP;
     const int64_t part = whole ? 0 : (int64_t)((h0 - g * G) / HP) * p.n_kept * Nkv;
-    if constexpr (ROPE) {
-        if (whole) {
-            const int pos = kvalid ? (p.idx ? p.idx[jk] : jk) - b * p.S : 0;
-            store_rows_rotated<D>(p.dk_kept + (int64_t)(c0 + wave * 32) * Nkv + g * D, Nkv, keys_in_tile - wave * 32, dk, p.scale, lane,
-                                  pos, p.rope_cos, p.rope_sin);
-        }
-    }
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int r = wave * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
-            if (r < keys_in_tile) {
-                const int64_t off = part + (int64_t)(c0 + r) * Nkv + g * D + nt * 32 + slot;
-                if (whole) {
-                    if constexpr (!ROPE) p.dk_kept[off] = f32_to_bf16(dk[nt][v] * p.scale);
-                    p.dv_kept[off] = f32_to_bf16(dv[nt][v]);
-                } else {
-                    p.dk_part[off] = dk[nt][v];
-                    p.dv_part[off] = dv[nt][v];
-                }
-            }
-        }
-    }
+    for (int u = 0; u < 2; ++u)
+        if (kvalid[u]) store_dkv<D, ROPE>(p, whole, part + (int64_t)jk[u] * Nkv + g * D + 4 * qd, b, jk[u], qd, dk[u], dv[u]);
 }
 
 template <bool ROPE>
@@ -1303,7 +1243,7 @@ __global__ __launch_bounds__(256) void attn_reduce_kernel(AttnParams p, int kv_b
     *reinterpret_cast<uint2*>(p.dv_kept + i + half) = make_uint2(pack2(dv[4], dv[5]), pack2(dv[6], dv[7]));
 }
 
-// stat[0][h][j] = log2(e) * LSE(b, h, position of kept row j); stat[1][h][j] = D = sum_c dO*O of
+// stat[0][h][j] = log2(e) * LSE(b, h, position of kept row j); stat[1][h][j] = -D = -sum_c dO*O of
 // (row j, head h): the row terms of the FlashAttention backward, laid out so that the 64 rows a
 // dK/dV block needs per step are contiguous.  d/8 lanes share one (row, head).
 // Only launched where the attention output and the queries are still stored full length (o_full, q_full, with idx):
@@ -1356,7 +1296,7 @@ __global__ __launch_bounds__(256, 8) void attn_stats_kernel(bf16_t* do_kept,
     if (live && threadIdx.x % lanes == 0) {
         const unsigned tok = (unsigned)idx[j], bb = tok / (unsigned)S, pos = tok - bb * (unsigned)S;
         stat[(int64_t)h * n_max + j] = lse_full[((int64_t)bb * Hq + h) * S + pos] * LOG2E;
-        stat[(int64_t)(Hq + h) * n_max + j] = s;
+        stat[(int64_t)(Hq + h) * n_max + j] = -s;
     }
 }
 

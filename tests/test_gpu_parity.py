@@ -434,6 +434,18 @@ def test_attn_bwd_filtered_fine_query_tiles(B, S, Hq, Hkv, d, n):
     _attn_case("bf16", B, S, Hq, Hkv, d, mask.reshape(B, S), seed=n)
 
 
+@pytest.mark.parametrize("Hq,Hkv,d", [(4, 1, 128), (2, 2, 128), (8, 1, 64), (2, 2, 64)])
+def test_attn_bwd_filtered_rows_around_groups_of_16(Hq, Hkv, d):
+    """A lane holds two rows 16 apart, a wave 32: kept rows per sequence around these, a tile of 64 and one of 128, and none."""
+    counts = (0, 1, 15, 16, 17, 31, 32, 33, 47, 49, 64, 65, 129)
+    say("attn bf16 rows around groups of 16 Hq=%d Hkv=%d d=%d" % (Hq, Hkv, d))
+    rng = np.random.default_rng(d + Hq)
+    mask = np.zeros((len(counts), 140), np.uint8)
+    for b, c in enumerate(counts):
+        mask[b, rng.permutation(140)[:c]] = 1
+    _attn_case("bf16", len(counts), 140, Hq, Hkv, d, mask, seed=Hq + d)
+
+
 def test_attn_fp32_small_head_dims():
     for d in (8, 32):
         say("attn f32 d=%d" % d)
