@@ -471,33 +471,33 @@ __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_
     auto tile = [&](auto MASKED_, const int key0, const unsigned sk) __attribute__((always_inline)) {
         constexpr bool masked = decltype(MASKED_)::value != 0;
         bf16x8_t fa[2][2], fc[2];
-        auto load_a = [&](int mt, int s, int buf, int part) __attribute__((always_inline)) {      // s: 16 keys s / KS, 32 columns s % KS
-            const lds_u8_ptr q = reinterpret_cast<lds_u8_ptr>(sk + (ra0 ^ (unsigned)((s % KS) << 6)));
-            const int off = (mt * 32 + 16 * (s / KS)) * (D * 2);
-            fa[buf][part] = read_rows(q + ((part == 0 ? TILE : 0) + off));
+        // slot s: of V (even) or K (odd), 32 columns s / 2; part: group of 16 keys
+        auto load_a = [&](int mt, int s, int part) __attribute__((always_inline)) {
+            const lds_u8_ptr q = reinterpret_cast<lds_u8_ptr>(sk + (ra0 ^ (unsigned)((s / 2) << 6)));
+            fa[s & 1][part] = read_rows(q + ((s & 1 ? 0 : TILE) + (mt * 32 + 16 * part) * (D * 2)));
         };
         auto load_c = [&](int mt, int nt, int buf) __attribute__((always_inline)) {
             fc[buf] = read_tokens<D>(reinterpret_cast<lds_u8_ptr>(sk + (ta0 ^ (unsigned)(nt << 5))) + mt * 32 * (D * 2));
         };
-        load_a(0, 0, 0, 0);
-        load_a(0, 0, 0, 1);
+        load_a(0, 0, 0);
+        load_a(0, 0, 1);
 #pragma unroll
         for (int mt = 0; mt < (FINE ? 1 : 2); ++mt) {
             f32x4_t st[2][2], dpt[2][2];            // [16 keys][16 queries]
 #pragma unroll
             for (int s = 0; s < 2 * KS; ++s) {
-                const int k16 = s / KS, ks = s % KS, buf = s & 1;
+                const int ks = s / 2;
                 const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
-                    const int t = m & 1;
+                    const int k16 = m >> 1, t = (m & 1) ^ k16;
                     if (m < 2) {
-                        if (s + 1 < 2 * KS) load_a(mt, s + 1, (s + 1) & 1, m);
+                        if (s + 1 < 2 * KS) load_a(mt, s + 1, m);
                         else if (m == 0) load_c(mt, 0, 0);
                     }
                     CF_SCHED_FENCE();
-                    if (m < 2) dpt[k16][t] = mfma16(fa[buf][0], dof[t][ks], ks == 0 ? negD[t] : dpt[k16][t]);
-                    else st[k16][t] = mfma16(fa[buf][1], qf[t][ks], ks == 0 ? z : st[k16][t]);
+                    if (s % 2 == 0) dpt[k16][t] = mfma16(fa[0][k16], dof[t][ks], ks == 0 ? negD[t] : dpt[k16][t]);
+                    else st[k16][t] = mfma16(fa[1][k16], qf[t][ks], ks == 0 ? z : st[k16][t]);
                     CF_SCHED_FENCE();
                 }
             }
@@ -522,10 +522,13 @@ __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_
 #pragma unroll
             for (int c = 0; c < NT; ++c) {
                 if (c + 1 < NT) load_c(mt, c + 1, (c + 1) & 1);
-                else if (!FINE && mt == 0) { load_a(mt + 1, 0, 0, 0); load_a(mt + 1, 0, 0, 1); }
+                else if (!FINE && mt == 0) { load_a(mt + 1, 0, 0); load_a(mt + 1, 0, 1); }
                 CF_SCHED_FENCE();
 #pragma unroll
-                for (int t = 0; t < 2; ++t) acc[t][c] = mfma16(fc[c & 1], a[t], acc[t][c]);
+                for (int m = 0; m < 2; ++m) {
+                    const int t = (m ^ c) & 1;
+                    acc[t][c] = mfma16(fc[c & 1], a[t], acc[t][c]);
+                }
                 CF_SCHED_FENCE();
             }
         }
@@ -737,9 +740,11 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     // register pairs and are issued three slots ahead of their MFMAs, across iteration boundaries
     // too (the LDS answers a read in a few hundred cycles when four waves keep it busy; a single slot
     // of lookahead left every group waiting for it).
-    // A slot = four MFMAs: A slot s = {S[q][u] += Qfrag * K[u][ks], dP[q][u] += dOfrag * V[u][ks]} for both groups u of 16 keys,
-    // q = s / KS the group of 16 queries and ks = s % KS the 32 columns; C slot nt = {dK[u][nt] += Qtokens * dS[u],
-    // dV[u][nt] += dOtokens * P[u]}.  dP accumulates from -D on.
+    // A slot = four MFMAs, two fragments by both groups u of 16 keys: A slot s = {S[q][u] += Qfrag[q] * K[u][ks]} (s even) or
+    // {dP[q][u] += dOfrag[q] * V[u][ks]} (odd) for both groups q of 16 queries, ks = s / 2 the 32 columns; C slot c = {dV[u][nt] +=
+    // dOtokens[nt] * P[u]} (even) or {dK[u][nt] += Qtokens[nt] * dS[u]} (odd) for two blocks nt of 16 columns.  Back and forth: an MFMA
+    // shares an operand with the one before it and the other with the one after (see gemm.hip; here and in the dQ kernel: [2 x 2048 of 4096
+    // rows, 32/8 heads] call 349 and 345 us, [8192 of 16384, 24/8] 1663 and 1640).  dP accumulates from -D on.
     // Iterations come in pairs (even t = 2s, odd t = 2s+1) so that stage halves are compile-time.  In
     // the even iteration all C slots come first (with a third of the A slots between them): after
     // them no wave reads stage s-1 any more, so ONE barrier there both frees that stage for the loads
@@ -763,15 +768,15 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     constexpr auto slot_index = [](bool even, int p) constexpr { return dkv_slot_index(NT, even, p); };
     // reads of an A slot (row fragments of Q and dO, half hf of the stage at sb) or of a C slot (token
     // fragments) into ring entry r
-    // (part 0: of dO and -D, part 1: of Q)
+    // (part: group q of queries or block of columns; -D goes with the first fragments of dO)
     auto read_a = [&](unsigned sb, int hf, int s, int r, int part) __attribute__((always_inline)) {
-        const int row = hf * 32 + (s / KS) * 16;
-        op[r][part] = read_rows(reinterpret_cast<lds_u8_ptr>(sb + ra[s % KS]) + ((part == 0 ? TILE : 0) + row * (D * 2)));
-        if (part == 0 && s % KS == 0)
-            nd[s / KS] = *reinterpret_cast<lds_f4_cptr>(reinterpret_cast<lds_u8_ptr>(sb + 2 * TILE + 16 * qd) + (64 + row) * 4);
+        const int row = hf * 32 + part * 16;
+        op[r][part] = read_rows(reinterpret_cast<lds_u8_ptr>(sb + ra[s / 2]) + ((s & 1 ? TILE : 0) + row * (D * 2)));
+        if (s == 1)
+            nd[part] = *reinterpret_cast<lds_f4_cptr>(reinterpret_cast<lds_u8_ptr>(sb + 2 * TILE + 16 * qd) + (64 + row) * 4);
     };
-    auto read_c = [&](unsigned sb, int hf, int nt, int r, int part) __attribute__((always_inline)) {
-        op[r][part] = read_tokens<D>(reinterpret_cast<lds_u8_ptr>(sb + ta[nt]) + ((part == 0 ? TILE : 0) + hf * 32 * (D * 2)));
+    auto read_c = [&](unsigned sb, int hf, int c, int r, int part) __attribute__((always_inline)) {
+        op[r][part] = read_tokens<D>(reinterpret_cast<lds_u8_ptr>(sb + ta[(c & ~1) + part]) + ((c & 1 ? 0 : TILE) + hf * 32 * (D * 2)));
     };
     // log2(e)*LSE of this lane's queries (4*qd on) of group q of half hf of the stage at sb
     auto read_lse = [&](unsigned sb, int hf, int q) __attribute__((always_inline)) {
@@ -850,33 +855,36 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
                     if constexpr (VPS == 2 || m == 3) soft_ds(parB, v);
                 }
                 CF_SCHED_FENCE();
-                constexpr int u = m & 1;
+                constexpr int f = m >> 1, u = (m & 1) ^ f;      // fragment of the slot, group of keys
                 if constexpr (is_a(EVEN, pp)) {
                     if constexpr (KIND != 2) {
-                        constexpr int s = slot_index(EVEN, pp), q = s / KS, ks = s % KS;
+                        constexpr int s = slot_index(EVEN, pp), ks = s / 2;
                         // Inline assembly keeps S and dP in the VGPR file, where the softmax arithmetic reads them:
                         // with the builtin the register allocator accumulates them in AGPRs and copies all 32
                         // registers of a half out again, one v_accvgpr_read each.  The price is that the compiler
-                        // no longer sees these MFMAs' latency.  A softmax value is read eight MFMAs or more after the last one that writes
-                        // it: query group 0 is complete in the middle of an iteration, group 1's first value is read in slot 4 / VPS.
-                        if constexpr (m < 2) {
+                        // no longer sees these MFMAs' latency.  A softmax step reads a value five MFMAs or more after the last one that
+                        // writes it (S is complete a slot before dP).
+                        if constexpr (s % 2 == 0) {
                             if constexpr (ks == 0)
-                                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" : "=&v"(dpt[parA][q][u]) : "v"(op[pp % RING][0]), "v"(vf[u][ks]), "v"(nd[q]));
+                                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(st[parA][f][u]) : "v"(op[pp % RING][f]), "v"(kf[u][ks]));
                             else
-                                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(dpt[parA][q][u]) : "v"(op[pp % RING][0]), "v"(vf[u][ks]));
+                                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(st[parA][f][u]) : "v"(op[pp % RING][f]), "v"(kf[u][ks]));
                         } else {
                             if constexpr (ks == 0)
-                                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(st[parA][q][u]) : "v"(op[pp % RING][1]), "v"(kf[u][ks]));
+                                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" : "=&v"(dpt[parA][f][u]) : "v"(op[pp % RING][f]), "v"(vf[u][ks]), "v"(nd[f]));
                             else
-                                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(st[parA][q][u]) : "v"(op[pp % RING][1]), "v"(kf[u][ks]));
+                                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(dpt[parA][f][u]) : "v"(op[pp % RING][f]), "v"(vf[u][ks]));
                         }
-                        // -D keeps its registers to the end of the slot: the vector ALU must not write to them while an MFMA reads them
-                        if constexpr (ks == 0 && m == 3) asm volatile("" : : "v"(nd[q]));
                     }
                 } else if constexpr (KIND != 1) {
-                    constexpr int nt = slot_index(EVEN, pp);
-                    if constexpr (m < 2) dv[u][nt] = mfma16(op[pp % RING][0], operand(ap[parC][u]), dv[u][nt]);
-                    else dk[u][nt] = mfma16(op[pp % RING][1], operand(ads[parC][u]), dk[u][nt]);
+                    constexpr int c = slot_index(EVEN, pp), nt = (c & ~1) + f;
+                    if constexpr (c % 2 == 0) dv[u][nt] = mfma16(op[pp % RING][f], operand(ap[parC][u]), dv[u][nt]);
+                    else dk[u][nt] = mfma16(op[pp % RING][f], operand(ads[parC][u]), dk[u][nt]);
+                }
+                // -D keeps its registers into the slot after the one that reads it: the vector ALU must not write to them while an MFMA
+                // reads them
+                if constexpr (m == 2 && pp > 0 && KIND != 2) {
+                    if constexpr (is_a(EVEN, pp - 1) && slot_index(EVEN, pp - 1) == 1) asm volatile("" : : "v"(nd[0]), "v"(nd[1]));
                 }
                 CF_SCHED_FENCE();
             });
@@ -905,13 +913,14 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     // head: A(0), then the row terms and the fragment reads that the first iteration starts with
     {
         static_for<NT>([&](auto S_) __attribute__((always_inline)) {
-            constexpr int s = decltype(S_)::value, q = s / KS, ks = s % KS;
+            constexpr int s = decltype(S_)::value, ks = s / 2;
             read_a(lds0, 0, s, s % RING, 0);
             read_a(lds0, 0, s, s % RING, 1);
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                dpt[0][q][u] = mfma16(op[s % RING][0], vf[u][ks], ks == 0 ? nd[q] : dpt[0][q][u]);
-                st[0][q][u] = mfma16(op[s % RING][1], kf[u][ks], ks == 0 ? z : st[0][q][u]);
+            for (int m = 0; m < 4; ++m) {
+                const int q = m >> 1, u = (m & 1) ^ q;
+                if (s % 2 == 0) st[0][q][u] = mfma16(op[s % RING][q], kf[u][ks], ks == 0 ? z : st[0][q][u]);
+                else dpt[0][q][u] = mfma16(op[s % RING][q], vf[u][ks], ks == 0 ? nd[q] : dpt[0][q][u]);
             }
         });
         read_lse(lds0, 0, 0);
