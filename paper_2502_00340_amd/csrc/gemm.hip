@@ -448,13 +448,15 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int K0x, con
     //   * a share of the wave-loads: the pair at (seg, k0) is loaded in NG groups, group 0 in the last
     //     sub-step of a pair (into the pair of stages its barrier has just retired), groups 1.. in the first
     //     sub-steps of the next pair.
+    constexpr bool BACK = !DEEP;        // the order of a sub-step's MFMAs, see there
     auto substep = [&](auto P, auto T) __attribute__((always_inline)) {
         constexpr int p = decltype(P)::value, t = decltype(T)::value;
         constexpr int ks = t / TM, a = t % TM;
         constexpr int nxt = ks == 0 ? p : (p + 1) % NPR;            // pair of the next K-step
         constexpr bool last = t == 2 * TM - 1;
         constexpr int a_pair = a + 1 < TM ? p : nxt, a_ks = a + 1 < TM ? ks : ks ^ 1, a_blk = a + 1 < TM ? a + 1 : 0;
-        // reads of this sub-step, in the order their first users come: A fragments, B fragments
+        // reads of this sub-step, in the order their first users come: A fragments, B fragments (BACK) or A fragment 0, B
+        // fragments, A fragment 1
         constexpr int NB = ks == 0 ? 0 : (last ? FN : 0);           // all B fragments at once
         constexpr int b_lo = ks == 0 ? (a * FN) / TM : 0, b_hi = ks == 0 ? ((a + 1) * FN) / TM : NB;
         constexpr int NR = 2 + (b_hi - b_lo);
@@ -467,8 +469,9 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int K0x, con
             static_for<NR>([&](auto R) __attribute__((always_inline)) {
                 constexpr int r = decltype(R)::value;
                 if constexpr ((r * NQ) / NR == q) {
-                    if constexpr (r < 2) frag_one(ic<a_pair>{}, ic<a_ks>{}, ic<2 * a_blk + r>{}, ic<((a + 1) & 1)>{});
-                    else frag_one(ic<nxt>{}, ic<(ks ^ 1)>{}, ic<FM + b_lo + r - 2>{}, ic<(ks ^ 1)>{});
+                    constexpr int f = BACK ? (r < 2 ? r : -1) : (r == 0 ? 0 : (r == NR - 1 ? 1 : -1));
+                    if constexpr (f >= 0) frag_one(ic<a_pair>{}, ic<a_ks>{}, ic<2 * a_blk + f>{}, ic<((a + 1) & 1)>{});
+                    else frag_one(ic<nxt>{}, ic<(ks ^ 1)>{}, ic<FM + b_lo + r - (BACK ? 2 : 1)>{}, ic<(ks ^ 1)>{});
                 }
             });
             CF_SCHED_FENCE();
@@ -480,8 +483,9 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int K0x, con
                 // Both A fragments per B fragment, back and forth: an MFMA shares an operand with the one before it and the other
                 // with the one after, which costs less power than eight B fragments in a row for one A fragment (a register-resident
                 // loop 2060 and 2107 TFLOP/s; X^T*dY and dY*W^T of [4096, 4096 -> 14336] 654 and 646 us, the layer step with
-                // these sizes 3180 and 3157).
-                constexpr int j = q >> 1, h = (q & 1) ^ (j & 1), i = 2 * a + h;
+                // these sizes 3180 and 3157).  The small tile, which waits for its operands, runs the other way: there A fragment 1 has
+                // half a sub-step longer to arrive ([841, 4096], K = 3584 out of HBM: 40 us back and forth, 36).
+                constexpr int j = BACK ? q >> 1 : q % FN, h = BACK ? (q & 1) ^ (j & 1) : q / FN, i = 2 * a + h;
                 constexpr int dsel = load_in_gap(q, e_hi - e_lo, NQ);       // the wave-load that goes with this MFMA
                 if constexpr (dsel >= 0) {
                     constexpr int e = dsel + e_lo;
