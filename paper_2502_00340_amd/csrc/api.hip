@@ -248,7 +248,9 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     const void* dy_rows = own_dy ? w.dy_k : dy;
     GemmTnProb dws[TN_MAX];
     int n_dw = 0;
-    auto dw_launch = [&](const GemmTnProb* ps, int np) { return launch_gemm_tn(dt, ps, np, N, mg ? 1.f : 0.f, st, mg, nd); };
+    auto dw_launch = [&](const GemmTnProb* ps, int np, const GainGrads* gains = nullptr) {
+        return launch_gemm_tn(dt, ps, np, N, mg ? 1.f : 0.f, st, mg, nd, gains);
+    };
     auto dw = [&](const void* A, const void* B, void* C, int M, int Ncols) { dws[n_dw++] = GemmTnProb{A, B, C, M, Ncols}; };
 
     // ---- SwiGLU FFN: y = r + act*Wd --------------------------------------------
@@ -307,11 +309,11 @@ cf_status layer_core(const cf_layer_desc& L, const cf_saved& sv, const cf_weight
     // dx = dr + rmsnorm_bwd(dh1; x, g1);  dg1; h1 = rmsnorm(x)*g1 on the way (see h2 above), over dh1: h2 is still an operand
     void* h1 = dh1;
     CF_HIP(launch_rmsnorm_bwd(dt, dh1, sv.x, W.g1, idx, w.dr, rows, H, L.rms_eps, G.dx, w.dg_partial1, st, parts, h1));
-    CF_HIP(launch_gain_grads(dt, w.dg_partial1, w.dg_partial2, rows, H, G.dg1, G.dg2, mg, st));
     dw(h1, w.dq, G.dwq, H, Nq);
     dw(h1, w.dk, G.dwk, H, Nkv);
     dw(h1, w.dv, G.dwv, H, Nkv);
-    CF_HIP(dw_launch(dws, n_dw));
+    const GainGrads gains{w.dg_partial1, w.dg_partial2, G.dg1, G.dg2, H, N, nd};
+    CF_HIP(dw_launch(dws, n_dw, &gains));
     return CF_OK;
 }
 

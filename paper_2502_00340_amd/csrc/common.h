@@ -196,8 +196,10 @@ struct GemmTnProb {
     void* C;
     int M, N;
 };
+// gains (nullable): the gain gradients, too, c_f32 as their acc_f32; no product may read them.
+struct GainGrads;
 hipError_t launch_gemm_tn(int dtype, const GemmTnProb* probs, int np, int K, float beta, hipStream_t st, bool c_f32 = false,
-                          const int32_t* n_dev = nullptr);
+                          const int32_t* n_dev = nullptr, const GainGrads* gains = nullptr);
 
 // One launch for up to GROUP_MAX independent products C [M,N] = alpha * op(A) * op(B) with few output tiles:
 //   mode 0 ("NT"): A [M,K], B [N,K]    1 ("TN"): A [K,M], B [K,N]    2 ("NN"): A [M,K], B [K,N]
@@ -234,9 +236,14 @@ int rmsnorm_bwd_blocks(int n_rows);
 hipError_t launch_rmsnorm_bwd(int dtype, void* dh, const void* x, const void* g,
                               const int32_t* idx, const void* res, RowCount rows, int H, float eps,
                               void* dx_out, float* dg_partial, hipStream_t st, const NtParts& parts, void* h_out = nullptr);
-// The gain gradients of both norms from their partials.  acc_f32: dg1 and dg2 are fp32 [H] and added to instead of written.
-hipError_t launch_gain_grads(int dtype, const float* partial1, const float* partial2, RowCount rows, int H, void* dg1, void* dg2,
-                             bool acc_f32, hipStream_t st);
+// The gain gradients of both norms from their partials: gain_grads_block in launches of their own or with a launch_gemm_tn.
+struct GainGrads {
+    const float *partial1, *partial2;   // of the norm whose gain gradient dg1 / dg2 is
+    void *dg1, *dg2;                    // [H]; fp32 and added to (acc_f32), or of the dtype and written
+    int H, n_rows;
+    const int32_t* n_dev;
+};
+hipError_t launch_gain_grads(int dtype, const GainGrads& g, bool acc_f32, hipStream_t st);
 // fp32 gq [n_rows, hq*d] and gk [n_rows, hk*d], in place: transposed rotary rotation at position idx[j] % S
 // (idx null: j % S); cos, sin are [S, d/2] fp32
 hipError_t launch_rope_bwd_f32(void* gq, int hq, void* gk, int hk, const int32_t* idx, RowCount rows, int d, int S,
@@ -260,6 +267,45 @@ inline int compute_units() {
         c.store(n, std::memory_order_relaxed);
     }
     return n;
+}
+
+// Blocks that the rmsnorm backward deals its live rows out to, two rows per iteration, and so the partials of a gain gradient.
+__host__ __device__ inline int rmsnorm_bwd_nblk(int n_rows) {
+    const int pairs = (n_rows + 1) / 2;
+    return pairs < 512 ? pairs : 512;
+}
+
+// Block `unit` of gain_grad_units(H), of 256 threads: out[c] = sum_b partial[b,c] for 32 columns of one norm (8 lanes x 4 columns), 32 row groups
+// stride through the partials with 16-byte loads, many in flight; H is a multiple of 4.
+// The order of the additions is fixed, so the result is reproducible.  ACC: out is fp32 and the
+// sum is added to it (main-gradient accumulation).  red: LDS.
+__host__ __device__ inline int gain_grad_units(int H) { return 2 * ((H + 31) / 32); }
+template <typename T, bool ACC>
+__device__ __forceinline__ void gain_grads_block(const GainGrads& g, int unit, float (*red)[33]) {
+    const int H = g.H, norm = unit & 1, c0 = (unit >> 1) * 32;
+    const float* partial = norm == 0 ? g.partial1 : g.partial2;
+    T* out = (T*)(norm == 0 ? g.dg1 : g.dg2);
+    const int nblk = rmsnorm_bwd_nblk(live_rows(g.n_rows, g.n_dev));     // the partials that the backward kernel wrote
+    const int cq = threadIdx.x & 7, rg = threadIdx.x >> 3;
+    const int c = c0 + cq * 4;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    if (c < H) {
+#pragma unroll 8
+        for (int b = rg; b < nblk; b += 32) {
+            const float4 v = *reinterpret_cast<const float4*>(partial + (int64_t)b * H + c);
+            s[0] += v.x; s[1] += v.y; s[2] += v.z; s[3] += v.w;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[rg][cq * 4 + e] = s[e];
+    __syncthreads();
+    if (threadIdx.x < 32 && c0 + (int)threadIdx.x < H) {
+        float t = 0.f;
+#pragma unroll
+        for (int r = 0; r < 32; ++r) t += red[r][threadIdx.x];
+        if (ACC) out[c0 + threadIdx.x] += from_f32<T>(t);
+        else out[c0 + threadIdx.x] = from_f32<T>(t);
+    }
 }
 
 }  // namespace cf

@@ -110,6 +110,8 @@ struct GemmArgs {
 struct TnArgs : GemmArgs {
     GemmTnProb p[TN_MAX];
     int end[TN_MAX];    // tiles of products 0..j
+    int n_blocks;       // blocks that walk through the tiles; those behind them sum the gain gradients up
+    GainGrads gain;
 };
 
 // How the tiles of the last, partial round are cut.  The cost of a round of sub-tiles
@@ -731,14 +733,13 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int K0x, con
 }
 
 // The work items of a launch: the n_full whole tiles first, then the sub-tiles of the remaining
-// tiles.  Block b takes items b, b + gridDim.x, ...: with as many blocks as CUs every block runs
+// tiles.  Block b takes items b, b + stride, ...: with as many blocks as CUs every block runs
 // its share of the whole tiles back to back and then at most a few sub-tiles, and the items of
 // one block stay on one XCD (item id mod 8 = block id mod 8).
 // locate(l, t, bm, bn): logical tile l of the launch -> the product it belongs to (t without its origin) and its tile coordinates.
 template <int MODE, bool CF32, typename Locate>
 __device__ __forceinline__ void gemm_items(const GemmArgs& g, const int K0x, const int tiles, const int n_full, const int sub,
-                                           Locate locate, unsigned char* smem) {
-    const int stride = (int)gridDim.x;
+                                           const int stride, Locate locate, unsigned char* smem) {
     const int n_items = n_full + (tiles - n_full) * sub;
     // item -> tile; false when a sub-tile lies outside the matrix
     auto decode = [&](int w, TileRef& t) __attribute__((always_inline)) {
@@ -855,7 +856,7 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs g) {
         }, smem);
         return;
     }
-    gemm_items<0, false>(g, g.K[0], tiles_m * tiles_n, n_full, sub, [&](int l, TileRef& t, int& bm, int& bn) __attribute__((always_inline)) {
+    gemm_items<0, false>(g, g.K[0], tiles_m * tiles_n, n_full, sub, (int)gridDim.x, [&](int l, TileRef& t, int& bm, int& bn) __attribute__((always_inline)) {
         t = whole;
         tile_coords(l, tiles_m, tiles_n, bm, bn);
     }, smem);
@@ -865,13 +866,20 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs g) {
 template <bool CF32>
 __global__ __launch_bounds__(256) void gemm_tn_kernel(TnArgs g) {
     extern __shared__ __align__(16) unsigned char smem[];
+    // Blocks behind those of the tiles sum the gain gradients up: where a CU has no tile left in the last, partial round they cost
+    // nothing, where a launch of their own is 5 us ([841 of 2103 rows, H = 4096, F = 1792, 4/1 heads] layer call 231.0 and 226.3 us).
+    if ((int)blockIdx.x >= g.n_blocks) {
+        using T = std::conditional_t<CF32, float, bf16_t>;
+        gain_grads_block<T, CF32>(g.gain, (int)blockIdx.x - g.n_blocks, reinterpret_cast<float (*)[33]>(smem));
+        return;
+    }
     int K0x = g.K[0];
     if (g.n_dev != nullptr) {           // the contraction is over the kept tokens: only its length depends on the count
         int n = *g.n_dev;
         n = __builtin_amdgcn_readfirstlane(n < 0 ? 0 : n);
         K0x = n < K0x ? n : K0x;
     }
-    gemm_items<1, CF32>(g, K0x, g.end[TN_MAX - 1], g.n_full, g.sub, [&](int l, TileRef& t, int& bm, int& bn) __attribute__((always_inline)) {
+    gemm_items<1, CF32>(g, K0x, g.end[TN_MAX - 1], g.n_full, g.sub, g.n_blocks, [&](int l, TileRef& t, int& bm, int& bn) __attribute__((always_inline)) {
         int j = 0, first = 0;
 #pragma unroll
         for (int q = 0; q + 1 < TN_MAX; ++q) {
@@ -1219,9 +1227,13 @@ hipError_t launch_gemm_nt(int dtype, const GemmSeg* segs, int nseg, void* C, int
 }
 
 hipError_t launch_gemm_tn(int dtype, const GemmTnProb* probs, int np, int K, float beta, hipStream_t st, bool c_f32,
-                          const int32_t* n_dev) {
+                          const int32_t* n_dev, const GainGrads* gains) {
     if (np < 1 || np > TN_MAX) return hipErrorInvalidValue;
     if (c_f32 && dtype == CF_BF16 && beta != 1.f) return hipErrorInvalidValue;
+    if (gains != nullptr && (K <= 0 || dtype == CF_F32)) {
+        const hipError_t e = launch_gain_grads(dtype, *gains, c_f32, st);
+        if (e != hipSuccess) return e;
+    }
     if (K <= 0) {           // empty contraction: C = beta*C; only beta in {0,1} is supported by the API
         for (int j = 0; j < np && beta == 0.f; ++j) {
             const hipError_t e = launch_fill_zero(probs[j].C, (size_t)probs[j].M * probs[j].N * dtype_size(dtype), st);
@@ -1255,7 +1267,16 @@ hipError_t launch_gemm_tn(int dtype, const GemmTnProb* probs, int np, int K, flo
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), GEMM_SMEM, c_f32 ? lds_ok_f32 : lds_ok);
     if (e != hipSuccess) return e;
     plan_tiles(tiles, compute_units(), g.n_full, g.sub);
-    kernel<<<std::min(g.n_full + (tiles - g.n_full) * g.sub, compute_units()), 256, GEMM_SMEM, st>>>(g);
+    g.n_blocks = std::min(g.n_full + (tiles - g.n_full) * g.sub, compute_units());
+    int more = 0;
+    if (gains != nullptr && tiles > compute_units()) {
+        g.gain = *gains;
+        more = gain_grad_units(gains->H);
+    } else if (gains != nullptr) {      // up to one round: a launch of their own, as the route tests count them
+        const hipError_t eg = launch_gain_grads(dtype, *gains, c_f32, st);
+        if (eg != hipSuccess) return eg;
+    }
+    kernel<<<g.n_blocks + more, 256, GEMM_SMEM, st>>>(g);
     return hipGetLastError();
 }
 

@@ -89,11 +89,6 @@ __global__ __launch_bounds__(256) void swiglu_bwd_kernel(T* d_act,
 // The rows are dealt out to rmsnorm_bwd_nblk(live rows) blocks whatever the grid is (a grid sized for
 // an upper bound of the row count leaves the blocks past that number idle), so the partial sums, and
 // with them the rounding of the gain gradient, depend on the number of live rows alone.
-__host__ __device__ inline int rmsnorm_bwd_nblk(int n_rows) {
-    const int pairs = (n_rows + 1) / 2;             // a block takes two rows per iteration
-    return pairs < 512 ? pairs : 512;
-}
-
 template <typename T, int NV>
 __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(T* dh,
                                                           const T* __restrict__ x,
@@ -207,38 +202,10 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(T* dh,
     }
 }
 
-// out[c] = sum_b partial[b,c]: a block owns 32 columns (8 lanes x 4 columns), 32 row groups
-// stride through the partials with 16-byte loads, many in flight; H is a multiple of 4.
-// The order of the additions is fixed, so the result is reproducible.  ACC: out is fp32 and the
-// sum is added to it (main-gradient accumulation).  blockIdx.y: which of the two norms' partials (one launch for both: 5 us).
 template <typename T, bool ACC = false>
-__global__ __launch_bounds__(256) void colsum_finish_kernel(const float* __restrict__ partial1, const float* __restrict__ partial2,
-                                                            int n_max, const int32_t* __restrict__ n_dev, int H,
-                                                            T* __restrict__ out1, T* __restrict__ out2) {
+__global__ __launch_bounds__(256) void colsum_finish_kernel(GainGrads g) {
     __shared__ float red[32][33];
-    const float* partial = blockIdx.y == 0 ? partial1 : partial2;
-    T* out = blockIdx.y == 0 ? out1 : out2;
-    const int nblk = rmsnorm_bwd_nblk(live_rows(n_max, n_dev));     // the partials that the backward kernel wrote
-    const int cq = threadIdx.x & 7, rg = threadIdx.x >> 3;
-    const int c = blockIdx.x * 32 + cq * 4;
-    float s[4] = {0.f, 0.f, 0.f, 0.f};
-    if (c < H) {
-#pragma unroll 8
-        for (int b = rg; b < nblk; b += 32) {
-            const float4 v = *reinterpret_cast<const float4*>(partial + (int64_t)b * H + c);
-            s[0] += v.x; s[1] += v.y; s[2] += v.z; s[3] += v.w;
-        }
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) red[rg][cq * 4 + e] = s[e];
-    __syncthreads();
-    if (threadIdx.x < 32 && blockIdx.x * 32 + threadIdx.x < H) {
-        float t = 0.f;
-#pragma unroll
-        for (int r = 0; r < 32; ++r) t += red[r][threadIdx.x];
-        if (ACC) out[blockIdx.x * 32 + threadIdx.x] += from_f32<T>(t);
-        else out[blockIdx.x * 32 + threadIdx.x] = from_f32<T>(t);
-    }
+    gain_grads_block<T, ACC>(g, blockIdx.x, red);
 }
 
 // D[j,h] = sum_c da[j,h*d+c] * a[row,h*d+c]   (the FlashAttention-backward row term), row = a_idx ?
@@ -375,12 +342,11 @@ hipError_t launch_rmsnorm_bwd(int dtype, void* dh, const void* x, const void* g,
     return hipGetLastError();
 }
 
-hipError_t launch_gain_grads(int dtype, const float* partial1, const float* partial2, RowCount rows, int H, void* dg1, void* dg2,
-                             bool acc_f32, hipStream_t st) {
-    const dim3 grid(ceil_div(H, 32), 2);
-    if (acc_f32) colsum_finish_kernel<float, true><<<grid, 256, 0, st>>>(partial1, partial2, rows.n, rows.dev, H, (float*)dg1, (float*)dg2);
-    else if (dtype == CF_F32) colsum_finish_kernel<float><<<grid, 256, 0, st>>>(partial1, partial2, rows.n, rows.dev, H, (float*)dg1, (float*)dg2);
-    else colsum_finish_kernel<bf16_t><<<grid, 256, 0, st>>>(partial1, partial2, rows.n, rows.dev, H, (bf16_t*)dg1, (bf16_t*)dg2);
+hipError_t launch_gain_grads(int dtype, const GainGrads& g, bool acc_f32, hipStream_t st) {
+    const int grid = gain_grad_units(g.H);
+    if (acc_f32) colsum_finish_kernel<float, true><<<grid, 256, 0, st>>>(g);
+    else if (dtype == CF_F32) colsum_finish_kernel<float><<<grid, 256, 0, st>>>(g);
+    else colsum_finish_kernel<bf16_t><<<grid, 256, 0, st>>>(g);
     return hipGetLastError();
 }
 
