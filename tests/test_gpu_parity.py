@@ -777,6 +777,26 @@ def test_layer_main_grad_full_round_and_a_remainder(F, kept):
             assert bad.numel() == 0, (name, rep, bad.shape[0], bad[0].tolist())
 
 
+@pytest.mark.parametrize("F", [1792, 4864])
+def test_layer_gain_gradients_beside_the_products(F):
+    """The column sums of the gain gradients go out with the parameter-gradient products where these have more than one round of
+    tiles (F = 4864: 513 and more tiles on 256 CUs), before them otherwise; H is no multiple of a block's 32 columns.  The fp32
+    buffers come from the same sums, so rounded they have the bits of the bf16 call, and doubled by a second call they double exactly."""
+    shape = WL.LayerShape("gain_grads", B=2, S=40, H=2056, Hq=4, Hkv=2, d=64, F=F, dtype="bf16")
+    say("layer gain gradients F=%d" % F)
+    p = Hn.Problem(shape, F, "independent", rho=0.5)
+    got, ridx, n = _run_layer(p)
+    Hn.check_layer(p, got, p.oracle(), ridx, Hn.TOL["bf16"])
+    sv, W, dy, mask = p.device_tensors(DEV)
+    plan = Bn.LayerBackward(p.desc(), device=DEV, main_grad=True)
+    ref = Bn.LayerBackward(p.desc(), device=DEV)
+    ref.filtered(sv, W, dy, mask)
+    for rep in (1, 2):
+        plan.filtered(sv, W, dy, mask)
+        for name in ("dg1", "dg2"):
+            assert torch.equal((plan.grads[name] / rep).to(torch.bfloat16), ref.grads[name]), (name, rep)
+
+
 @pytest.mark.parametrize("main_grad", [False, True])
 @pytest.mark.parametrize("H,Hq,Hkv,d,F", [(512, 8, 2, 64, 256), (840, 12, 4, 64, 2312), (2048, 32, 4, 64, 4864), (2048, 32, 4, 64, 5632)])
 def test_layer_parameter_gradients_in_one_launch_or_one_by_one(H, Hq, Hkv, d, F, main_grad):
