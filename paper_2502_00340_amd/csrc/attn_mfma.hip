@@ -658,26 +658,6 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     const int c0 = seq_begin + kt * 128;            // compact row of the tile's first key
     const int keys_in_tile = min(128, cnt - kt * 128);
 
-    // this lane's two keys, 16 apart
-    int jk[2];
-    bool kvalid[2];
-    bf16x8_t kf[2][KS], vf[2][KS];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        jk[u] = c0 + wave * 32 + u * 16 + slot;
-        kvalid[u] = wave * 32 + u * 16 + slot < keys_in_tile;
-        const int64_t tok = kvalid[u] ? (p.idx ? p.idx[jk[u]] : jk[u]) : 0;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            uint4 a = make_uint4(0, 0, 0, 0), c = make_uint4(0, 0, 0, 0);
-            if (kvalid[u]) {
-                a = *reinterpret_cast<const uint4*>(p.k_full + tok * Nkv + g * D + ks * 32 + qd * 8);
-                c = *reinterpret_cast<const uint4*>(p.v_full + tok * Nkv + g * D + ks * 32 + qd * 8);
-            }
-            kf[u][ks] = __builtin_bit_cast(bf16x8_t, a);
-            vf[u][ks] = __builtin_bit_cast(bf16x8_t, c);
-        }
-    }
     const float scale2 = p.scale * LOG2E;
     const int steps = (seq_end - c0 + 63) / 64;     // query tiles from the first key to the sequence end
 
@@ -728,6 +708,39 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
         dma4(sq + 2 * TILE + 256, rsD, off);
     };
     constexpr int LPS = 2 * NLD + 2;                // loads per wave and step
+    // The first rows of the first head are on their way before the keys, whose addresses take two more loads, are asked for (with the
+    // mask as below: [3 x 280 of 701 rows, 4/1 heads] call 39.7 us, so 39.0; [950 of 1900, 32/8] 84.0 and 83.4).
+    open_head(h0);
+    issue_q(0, 0);
+    issue_q(1, 1);
+    issue_q(2, 2);
+
+    // this lane's two keys, 16 apart
+    int jk[2];
+    int tok[2];
+    bool kvalid[2];
+    bf16x8_t kf[2][KS], vf[2][KS];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        jk[u] = c0 + wave * 32 + u * 16 + slot;
+        kvalid[u] = wave * 32 + u * 16 + slot < keys_in_tile;
+        tok[u] = kvalid[u] ? (p.idx ? p.idx[jk[u]] : jk[u]) : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            uint4 a = make_uint4(0, 0, 0, 0), c = make_uint4(0, 0, 0, 0);
+            if (kvalid[u]) {
+                a = *reinterpret_cast<const uint4*>(p.k_full + (int64_t)tok[u] * Nkv + g * D + ks * 32 + qd * 8);
+                c = *reinterpret_cast<const uint4*>(p.v_full + (int64_t)tok[u] * Nkv + g * D + ks * 32 + qd * 8);
+            }
+            kf[u][ks] = __builtin_bit_cast(bf16x8_t, a);
+            vf[u][ks] = __builtin_bit_cast(bf16x8_t, c);
+        }
+    }
+    // compact row less 4 * qd from which on a query sees the key; none sees one that does not exist
+    const int first_row[2] = {(kvalid[0] ? jk[0] : INT32_MAX) - 4 * qd, (kvalid[1] ? jk[1] : INT32_MAX) - 4 * qd};
 
     // ---- the pipeline.  The query rows go by in HALVES of 32 (two per 64-row step / LDS stage).  A
     // half n needs three kinds of work: A(n) = S and dP (8*KS MFMAs against the wave's K and V
@@ -783,14 +796,11 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
         lq[q] = *reinterpret_cast<lds_f4_cptr>(reinterpret_cast<lds_u8_ptr>(sb + 2 * TILE + 16 * qd) + (hf * 32 + q * 16) * 4);
     };
     // P and dS of value v (key group v / 8, query 16*(v/4 % 2) + 4*qd + v%4 of half t): lane = key, register = query
-    auto soft_p = [&](int par, int v, int qrow0, auto MASKED) __attribute__((always_inline)) {
+    auto soft_p = [&](int par, int v, const int (&lim)[2], auto MASKED) __attribute__((always_inline)) {
         constexpr bool masked = decltype(MASKED)::value != 0;
         const int u = v >> 3, q = (v >> 2) & 1, e = v & 3;
         float pr = __builtin_amdgcn_exp2f(st[par][q][u][e] * scale2 - lq[q][e]);
-        if (masked) {
-            const bool ok = kvalid[u] & (qrow0 + 16 * q + 4 * qd + e >= jk[u]);
-            pr = ok ? pr : 0.f;
-        }
+        if (masked) pr = 16 * q + e >= lim[u] ? pr : 0.f;
         st[par][q][u][e] = pr;
     };
     auto soft_ds = [&](int par, int v) __attribute__((always_inline)) {
@@ -820,7 +830,9 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
         const unsigned sbA_n = lds0 + (unsigned)((s + 1) & 3) * STAGE;
         const unsigned sbB_n = lds0 + (unsigned)((EVEN ? s : s + 1) & 3) * STAGE;
         const unsigned sbC_n = lds0 + (unsigned)(s & 3) * STAGE;
+        // the mask as a compare with a constant per value: first row of half t that sees this lane's keys, less the lane's 4 * qd
         const int qrow0 = c0 + (2 * s + (EVEN ? 0 : 1)) * 32;       // compact row of the first query of half t
+        const int lim[2] = {first_row[0] - qrow0, first_row[1] - qrow0};
         static_for<NP>([&](auto P) __attribute__((always_inline)) {
             constexpr int pp = decltype(P)::value;
             if constexpr (EVEN && pp == 3 * NT / 2 && KIND != 2) {
@@ -850,7 +862,7 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
                     if constexpr (VPS == 2 || m == 2) {
                         if constexpr (v == 0) read_lse(sbB, hfB, 1);
                         if constexpr (v == 12) read_lse(sbB_n, hfB_n, 0);
-                        soft_p(parB, v, qrow0, MASKED);
+                        soft_p(parB, v, lim, MASKED);
                     }
                     if constexpr (VPS == 2 || m == 3) soft_ds(parB, v);
                 }
@@ -896,14 +908,16 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     // the group's sum over these heads costs no partial buffer and a tile's fixed costs (fragment fetch,
     // write-out) are paid once per HP heads.
     for (int hi = 0; hi < HP; ++hi) {
-    open_head(h0 + hi);
-    if (hi > 0) lds_barrier();                      // every wave is done with the previous head's stages
     // Ring of four stages: the loads of step s+3 are issued in pair s, into the stage that step s-1
     // used.  Steps past the end are issued as well (every row out of range: zero fill), so the number
     // of loads in flight is the same in every pair.
-    issue_q(0, 0);
-    issue_q(1, 1);
-    issue_q(2, 2);
+    if (hi > 0) {
+        lds_barrier();                              // every wave is done with the previous head's stages
+        open_head(h0 + hi);
+        issue_q(0, 0);
+        issue_q(1, 1);
+        issue_q(2, 2);
+    }
     // Everything is waited for here, not only stage 0: the K and V fragments above come from ordinary
     // loads, and as long as the compiler cannot see them completed ahead of the loop it guards their
     // first use inside the loop with a wait of its own, which the hardware applies to the loads just
