@@ -598,15 +598,15 @@ __global__ __launch_bounds__(256, 2) void attn_dq_kernel(AttnParams p) {
 // ---------------------------------------------------------------------------
 // dK/dV kernel, one block per CU: one key tile and HP query heads per block (d = 64 has a second kernel below)
 // ---------------------------------------------------------------------------
-// Slot order of an iteration of the kernel's pipeline (2*KS positions, KS "A" slots and KS "C" slots;
+// Slot order of an iteration of the kernel's pipeline (2*N positions, N "A" slots and N "C" slots;
 // see the kernel): odd iterations alternate A, C; even iterations put all C slots into the first
-// 3*KS/2 positions, every third of which is an A slot, and the remaining A slots behind them.
-__host__ __device__ constexpr bool dkv_is_a(int KS, bool even, int p) {
-    return even ? (p < 3 * KS / 2 ? (p % 3 == 1) : true) : (p % 2 == 0);
+// 3*N/2 positions, every third of which is an A slot, and the remaining A slots behind them.
+__host__ __device__ constexpr bool dkv_is_a(int N, bool even, int p) {
+    return even ? (p < 3 * N / 2 ? (p % 3 == 1) : true) : (p % 2 == 0);
 }
-__host__ __device__ constexpr int dkv_slot_index(int KS, bool even, int p) {
+__host__ __device__ constexpr int dkv_slot_index(int N, bool even, int p) {
     int n = 0;
-    for (int q = 0; q < p; ++q) n += (dkv_is_a(KS, even, q) == dkv_is_a(KS, even, p)) ? 1 : 0;
+    for (int q = 0; q < p; ++q) n += (dkv_is_a(N, even, q) == dkv_is_a(N, even, p)) ? 1 : 0;
     return n;
 }
 
