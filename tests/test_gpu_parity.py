@@ -446,6 +446,16 @@ def test_attn_bwd_filtered_rows_around_groups_of_16(Hq, Hkv, d):
     _attn_case("bf16", len(counts), 140, Hq, Hkv, d, mask, seed=Hq + d)
 
 
+@pytest.mark.parametrize("S,Hq,Hkv,d,n", [(2700, 16, 4, 64, 2673), (2700, 16, 4, 64, 2692), (1500, 4, 1, 128, 1377), (400, 8, 2, 128, 258)])
+def test_attn_bwd_partials_of_ragged_key_tiles(S, Hq, Hkv, d, n):
+    """dK/dV partials leave by way of LDS, two (d = 128) or four rows to a store: last tiles of 2 to 113 keys, behind long chains at d = 64,
+    which the pipelined kernel takes there."""
+    say("attn bf16 ragged partials S=%d Hq=%d Hkv=%d d=%d rows=%d" % (S, Hq, Hkv, d, n))
+    mask = np.zeros((1, S), np.uint8)
+    mask[0, np.random.default_rng(n).permutation(S)[:n]] = 1
+    _attn_case("bf16", 1, S, Hq, Hkv, d, mask, seed=n, f8=np.float32)
+
+
 def test_attn_fp32_small_head_dims():
     for d in (8, 32):
         say("attn f32 d=%d" % d)
