@@ -903,7 +903,8 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
                         // with the builtin the register allocator accumulates them in AGPRs and copies all 32
                         // registers of a half out again, one v_accvgpr_read each.  The price is that the compiler
                         // no longer sees these MFMAs' latency.  A softmax step reads a value five MFMAs or more after the last one that
-                        // writes it (S is complete a slot before dP).
+                        // writes it (S is complete a slot before dP).  The allocator must not copy unfinished results either, which gave
+                        // wrong values in a variant of this loop: test_kernel_code.py reads the built code for both.
                         if constexpr (s % 2 == 0) {
                             if constexpr (ks == 0)
                                 asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(st[parA][f][u]) : "v"(op[pp % RING][f]), "v"(kf[u][ks]));
@@ -921,9 +922,11 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
                     if constexpr (c % 2 == 0) dv[u][nt] = mfma16(op[pp % RING][f], operand(ap[parC][u]), dv[u][nt]);
                     else dk[u][nt] = mfma16(op[pp % RING][f], operand(ads[parC][u]), dk[u][nt]);
                 }
-                // -D keeps its registers into the slot after the one that reads it: the vector ALU must not write to them while an MFMA
-                // reads them
-                if constexpr (m == 2 && pp > 0 && KIND != 2) {
+                // -D keeps its registers into the next slot with MFMAs after the one that reads it (the very first iteration has none in
+                // C slots): the vector ALU must not write to them while an MFMA reads them, and three more have started by then
+                if constexpr (m == 2 && KIND == 1) {
+                    if constexpr (is_a(EVEN, pp) && slot_index(EVEN, pp) == 2) asm volatile("" : : "v"(nd[0]), "v"(nd[1]));
+                } else if constexpr (m == 2 && pp > 0 && KIND == 0) {
                     if constexpr (is_a(EVEN, pp - 1) && slot_index(EVEN, pp - 1) == 1) asm volatile("" : : "v"(nd[0]), "v"(nd[1]));
                 }
                 CF_SCHED_FENCE();
