@@ -293,28 +293,33 @@ __device__ __forceinline__ bf16x8_t pack8(const f32x4_t& a, const f32x4_t& b) {
     return __builtin_bit_cast(bf16x8_t, make_uint4(pack2(a[0], a[1]), pack2(a[2], a[3]), pack2(b[0], b[1]), pack2(b[2], b[3])));
 }
 
-// One row of a head, times scale, as bf16: acc[nt] holds columns nt*16 + {0..3} from `out` on.  ROPE: rotated back to before the rotary
-// embedding; rope_cos and rope_sin point to those columns of the row's position.
-template <int D, bool ROPE>
-__device__ __forceinline__ void store_row(bf16_t* out, const f32x4_t (&acc)[D / 16], float scale, const float* __restrict__ rope_cos,
-                                          const float* __restrict__ rope_sin) {
+// One row of a head, times scale, as bf16: acc[nt] holds columns nt*16 + {0..3} from the lane's first one on, and put(nt, ..) takes
+// them.  ROPE: rotated back to before the rotary embedding; rope_cos and rope_sin point to the lane's first column of the row's position.
+template <int D, bool ROPE, typename Put>
+__device__ __forceinline__ void round_row(const f32x4_t (&acc)[D / 16], float scale, const float* __restrict__ rope_cos,
+                                          const float* __restrict__ rope_sin, Put put) {
     constexpr int NT = D / 16;
-    auto store = [&](int nt, const f32x4_t& y) __attribute__((always_inline)) {
-        *reinterpret_cast<uint2*>(out + nt * 16) = make_uint2(pack2(y[0], y[1]), pack2(y[2], y[3]));
-    };
+    auto round = [&](int nt, const f32x4_t& y) __attribute__((always_inline)) { put(nt, make_uint2(pack2(y[0], y[1]), pack2(y[2], y[3]))); };
     if constexpr (ROPE) {
 #pragma unroll
         for (int nt = 0; nt < NT / 2; ++nt) {
             const f32x4_t c = *reinterpret_cast<const f32x4_t*>(rope_cos + nt * 16);
             const f32x4_t s = *reinterpret_cast<const f32x4_t*>(rope_sin + nt * 16);
             const f32x4_t a = acc[nt] * scale, b = acc[nt + NT / 2] * scale;
-            store(nt, a * c + b * s);
-            store(nt + NT / 2, b * c - a * s);
+            round(nt, a * c + b * s);
+            round(nt + NT / 2, b * c - a * s);
         }
     } else {
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) store(nt, acc[nt] * scale);
+        for (int nt = 0; nt < NT; ++nt) round(nt, acc[nt] * scale);
     }
+}
+// ... to memory; out: the row's first column of the lane
+template <int D, bool ROPE>
+__device__ __forceinline__ void store_row(bf16_t* out, const f32x4_t (&acc)[D / 16], float scale, const float* __restrict__ rope_cos,
+                                          const float* __restrict__ rope_sin) {
+    round_row<D, ROPE>(acc, scale, rope_cos, rope_sin,
+                       [&](int nt, uint2 y) __attribute__((always_inline)) { *reinterpret_cast<uint2*>(out + nt * 16) = y; });
 }
 
 // global -> LDS: a [64][D] tile goes in as 1 KB wave-loads (16 bytes per lane): wave w, load i fills
@@ -627,32 +632,28 @@ __device__ __forceinline__ void store_dkv(const AttnParams& p, bool whole, int64
     }
 }
 
-// A wave's 32 rows, fp32, to `out` (its first row and the head's first column; `stride` elements apart) by way of its own 32*D*4 bytes of
-// LDS; the rows from `rows` on do not exist.  Straight from the accumulators neighbouring lanes store to different rows, and a
-// store of 16 bytes a lane takes a cycle a lane: the write-out of a block at d = 128 8100 to 9800 cycles (lanes traded so that eight of
-// them write a whole 128-byte line: 8500), this way, with neighbouring lanes on neighbouring 16 bytes, 5950.  Where sequences are
-// short that decides: [3 x 394 of 878 rows, 32/8 heads] call 75.5 and 72.7 us, [153 of 307, 32/8] 32.6 and 31.0, [3 x 280 of 701, 4/1] 39.0
-// and 37.8.
-template <int D>
-__device__ __forceinline__ void store_rows_by_lds(float* out, int64_t stride, int rows, unsigned char* buf, int lane,
-                                                  const f32x4_t (&acc)[2][D / 16]) {
-    constexpr int LPR = D / 4, RPS = 64 / LPR;      // lanes to a row, rows to a store
+// A wave's 32 rows of one head, fp32 or bf16, to `out` (the first row and the head's first column; `stride` elements apart) by way of
+// its own 32 * D elements of LDS, into which write(at) puts them, at(row, c) being the c-th 16 bytes of a row.
+// Straight from the accumulators neighbouring lanes store to different rows, and such a store takes a cycle a lane, of 16 bytes (fp32) as
+// of 8 (bf16): the write-out of a block's fp32 at d = 128 8100 to 9800 cycles (lanes traded so that eight of them write a whole
+// 128-byte line: 8500), this way, with neighbouring lanes on neighbouring 16 bytes, 5950.  Where sequences are short that decides.  Whole
+// attention call at d = 128, fp32 [3 x 394 of 878 rows, 32/8 heads] 75.5 and 72.7 us, [153 of 307, 32/8] 32.6 and 31.0; bf16 [2 x 137 of
+// 144, 32/32] 26.3 and 23.3, [8 x 207 of 350, 16/16] 37.7 and 35.4, [1024 of 4096, 32/32] 106.6 and 104.4.
+// A wave with fewer than 32 rows stores them straight, a cycle for every lane that has one: by way of LDS too [5 x 129 of 151, 32/8]
+// takes 41.1 us, so 39.7, and [3 x 13 of 48, 16/16] 14.1 and 13.5.
+template <int D, typename T, typename Write>
+__device__ __forceinline__ void store_rows_by_lds(T* out, int64_t stride, unsigned char* buf, int lane, Write write) {
+    constexpr int ROW = D * (int)sizeof(T), LPR = ROW / 16, RPS = 64 / LPR, N = 32 / RPS;   // bytes of and lanes to a row, rows to a store
     auto at = [&](int row, int chunk) __attribute__((always_inline)) {      // eight neighbouring lanes share no bank, either way
-        return reinterpret_cast<f32x4_t*>(buf + row * (D * 4) + ((chunk ^ (row & 7)) << 4));
+        return buf + row * ROW + ((chunk ^ (row & 7)) << 4);
     };
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int nt = 0; nt < D / 16; ++nt) *at(u * 16 + (lane & 15), nt * 4 + (lane >> 4)) = acc[u][nt];
+    write(at);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
     __builtin_amdgcn_wave_barrier();
     const int r0 = lane / LPR, c = lane % LPR;
-    out += r0 * stride + c * 4;
+    out += r0 * stride + c * (16 / (int)sizeof(T));
 #pragma unroll
-    for (int i = 0; i < 32 / RPS; ++i) {
-        const f32x4_t v = *at(r0 + i * RPS, c);
-        if (r0 + i * RPS < rows) *reinterpret_cast<f32x4_t*>(out + i * RPS * stride) = v;
-    }
+    for (int i = 0; i < N; ++i) *reinterpret_cast<u32x4_t*>(out + i * RPS * stride) = *reinterpret_cast<u32x4_t*>(at(r0 + i * RPS, c));
 }
 
 template <int D, bool ROPE>
@@ -998,18 +999,45 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     wait_vmcnt<0>();                                // the zero-fill loads of the steps past the end
     }
 
-    if (G == HP) {
+    constexpr int HALF = 32 * D * 4;
+    static_assert(4 * 2 * HALF <= 4 * STAGE, "the four waves' rows lie over the stages");
+    const bool whole = G == HP;
+    const int64_t part = whole ? 0 : (int64_t)((h0 - g * G) / HP) * p.n_kept * Nkv;
+    lds_barrier();                                  // every wave is done with the stages, and so are its loads
+    if (keys_in_tile < wave * 32 + 32) {
 #pragma unroll
         for (int u = 0; u < 2; ++u)
-            if (kvalid[u]) store_dkv<D, ROPE>(p, true, (int64_t)jk[u] * Nkv + g * D + 4 * qd, b, jk[u], qd, dk[u], dv[u]);
+            if (kvalid[u]) store_dkv<D, ROPE>(p, whole, part + (int64_t)jk[u] * Nkv + g * D + 4 * qd, b, jk[u], qd, dk[u], dv[u]);
+        return;
+    }
+    unsigned char* const buf = smem + wave * (2 * HALF);
+    const int64_t at0 = part + (int64_t)(c0 + wave * 32) * Nkv + g * D;
+    if (whole) {
+        auto rounded = [&](const f32x4_t (&acc)[2][NT], float scale, auto ROPE_) __attribute__((always_inline)) {
+            return [&, scale](auto at) __attribute__((always_inline)) {
+                constexpr bool rope = decltype(ROPE_)::value != 0;
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int64_t tab = rope ? (int64_t)((p.idx ? p.idx[jk[u]] : jk[u]) - b * p.S) * (D / 2) + 4 * qd : 0;
+                    round_row<D, rope>(acc[u], scale, p.rope_cos + tab, p.rope_sin + tab, [&](int nt, uint2 y) __attribute__((always_inline)) {
+                        *reinterpret_cast<uint2*>(at(u * 16 + slot, nt * 2 + (qd >> 1)) + (qd & 1) * 8) = y;
+                    });
+                }
+            };
+        };
+        store_rows_by_lds<D>(p.dk_kept + at0, Nkv, buf, lane, rounded(dk, p.scale, ic<ROPE>{}));
+        store_rows_by_lds<D>(p.dv_kept + at0, Nkv, buf + HALF, lane, rounded(dv, 1.f, ic<0>{}));
     } else {
-        constexpr int HALF = 32 * D * 4;
-        static_assert(4 * 2 * HALF <= 4 * STAGE, "the four waves' rows lie over the stages");
-        lds_barrier();                              // every wave is done with these, and so are its loads
-        const int64_t at = ((int64_t)((h0 - g * G) / HP) * p.n_kept + c0 + wave * 32) * Nkv + g * D;
-        const int rows = keys_in_tile - wave * 32;
-        store_rows_by_lds<D>(p.dk_part + at, Nkv, rows, smem + wave * (2 * HALF), lane, dk);
-        store_rows_by_lds<D>(p.dv_part + at, Nkv, rows, smem + wave * (2 * HALF) + HALF, lane, dv);
+        auto plain = [&](const f32x4_t (&acc)[2][NT]) __attribute__((always_inline)) {
+            return [&](auto at) __attribute__((always_inline)) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<f32x4_t*>(at(u * 16 + slot, nt * 4 + qd)) = acc[u][nt];
+            };
+        };
+        store_rows_by_lds<D>(p.dk_part + at0, Nkv, buf, lane, plain(dk));
+        store_rows_by_lds<D>(p.dv_part + at0, Nkv, buf + HALF, lane, plain(dv));
     }
 }
 

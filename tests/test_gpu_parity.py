@@ -456,6 +456,18 @@ def test_attn_bwd_partials_of_ragged_key_tiles(S, Hq, Hkv, d, n):
     _attn_case("bf16", 1, S, Hq, Hkv, d, mask, seed=n, f8=np.float32)
 
 
+@pytest.mark.parametrize("Hq,d,counts", [(2, 128, (300, 128, 127, 97, 96, 95, 64, 63, 33, 32, 31)), (16, 64, (2692,)), (16, 64, (2689,))])
+def test_attn_bwd_whole_and_ragged_rows_of_a_wave_without_groups(Hq, d, counts):
+    """Without KV groups dK and dV leave as bf16: 32 rows of a wave by way of LDS, four (d = 128) or eight to a store, fewer straight."""
+    S = max(counts) + 30
+    say("attn bf16 rows of a wave Hq=%d d=%d rows=%s" % (Hq, d, counts))
+    rng = np.random.default_rng(d + len(counts))
+    mask = np.zeros((len(counts), S), np.uint8)
+    for b, c in enumerate(counts):
+        mask[b, rng.permutation(S)[:c]] = 1
+    _attn_case("bf16", len(counts), S, Hq, Hq, d, mask, seed=Hq + counts[0], f8=np.float32)
+
+
 def test_attn_fp32_small_head_dims():
     for d in (8, 32):
         say("attn f32 d=%d" % d)
