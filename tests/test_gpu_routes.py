@@ -98,6 +98,39 @@ def test_layer_output_behind_the_upstream_gradient(main_grad):
             assert torch.equal(a, b), (where, k)
 
 
+@pytest.mark.parametrize("main_grad", [False, True])
+@pytest.mark.parametrize("which", ["dg1", "dg2"])
+def test_layer_gain_gradient_over_an_operand_of_the_products_beside_it(which, main_grad):
+    """More than one round of parameter-gradient tiles, so that the gain gradients are summed up while the products run: one that lies
+    over the caller's upstream gradient (an operand of dWd) or attention output (of dWo, dense) gives the bits of outputs elsewhere."""
+    shape = WL.LayerShape("gain_overlap", B=1, S=400, H=2056, Hq=4, Hkv=2, d=64, F=4864, dtype="bf16")
+    sv, W, dy = _random_layer(shape, 5)
+    mask = torch.zeros((1, 400), dtype=torch.uint8, device=DEV)
+    mask[0, torch.randperm(400, generator=torch.Generator().manual_seed(6))[:300].to(DEV)] = 1
+    idx, cu, n_dev, n = Bn.build_keep_index(mask)
+    dyk = Bn.gather_rows(dy, idx, n)
+    plan = lambda: Bn.LayerBackward(Bn.make_desc(1, 400, 2056, 4, 2, 64, 4864, "bf16"), device=DEV, main_grad=main_grad)
+    size = 2056 * (4 if main_grad else 2)
+    for src, call in (("dy", lambda p, dy, a: p.compact_dev(sv, W, dy, idx, cu, n_dev)),
+                      ("attn_out", lambda p, dy, a: p.dense(dict(sv, attn_out=a), W, dy))):
+        say("layer, %s over %s" % (which, src))
+        kept = dyk if src == "dy" else dy
+        ref, p = plan(), plan()
+        call(ref, kept, sv["attn_out"])
+        under = (kept if src == "dy" else sv["attn_out"]).clone()
+        first = 16000                                                       # inside both, on a 16-byte boundary
+        bytes_ = under.view(torch.uint8).view(-1)
+        p.grads[which] = bytes_[first:first + size].view(p.grads[which].dtype)
+        setattr(p._g, which, p.grads[which].data_ptr())
+        if main_grad:       # what is added to: the operand's own bytes, so the expected sum starts from them
+            ref.grads[which].copy_(ref.grads[which] + p.grads[which])
+        call(p, under if src == "dy" else kept, under if src != "dy" else sv["attn_out"])
+        torch.cuda.synchronize()
+        for k in ref.grads:
+            a, b = (t[:n] if k == "dx" and src == "dy" else t for t in (p.grads[k], ref.grads[k]))
+            assert torch.equal(a, b), (src, k)
+
+
 def _attn_call(B, S, Hq, Hkv, d, n):
     """cf_attn_bwd_filtered of n rows, the first n / B of every sequence."""
     bf = lambda *s: torch.randn(s, device=DEV).to(torch.bfloat16)
