@@ -36,9 +36,10 @@
 // Large attention calls run at the chip's power limit (on all-zero inputs the same instructions take 0.76 to 0.83 of the time), and
 // this MFMA moves half the accumulator bytes per flop that the 32x32x16 one does.  It also leaves four registers with the same row
 // terms instead of sixteen, so that dP can accumulate from -D on instead of a subtraction per score (with 32x32x16 the sixteen
-// registers of -D spilled).  Whole attention call with the larger and with this MFMA, [2 x 2048 of 4096 rows, 32/8 heads, d = 128]
-// 369 and 338 us, [8192 of 16384, 24/8] 1805 and 1629, [2 x 4096, 24/8] 691 and 620; d = 64 [4 x 2048, 32/4] 284 and 258,
-// [4915 of 8192, 8/8] 157 and 141, [3 x 459 of 1531, 32/4] 53.7 and 50.2.
+// registers of -D spilled).  Whole attention call with the larger MFMA and with this one, the other work spread between the MFMAs and their
+// order back and forth (what each of these gives stands where it is done), [2 x 2048 of 4096 rows, 32/8 heads, d = 128] 388 and 349 us, [8192 of
+// 16384, 24/8] 1879 and 1671, [2 x 4096, 24/8] 732 and 677; d = 64 [4 x 2048, 32/4] 297 and 271, [4915 of 8192, 8/8] 163 and 147,
+// [3 x 459 of 1531, 32/4] 55.0 and 51.8.
 #include <algorithm>
 
 #include "common.h"
@@ -110,29 +111,32 @@ __host__ __device__ inline int attn_heads_per_block(int n_rows, int Hq, int G, i
 
 // Live rows up to which the dQ blocks take tiles of 64 queries, with the keys of a tile shared out inside the block: up to one
 // 128-query tile per CU (d = 128) or one and a half (d = 64).  A lone block's step is a chain of LDS reads, MFMAs, exponentials and
-// a barrier, 1.3 us at d = 64 where its MFMAs take 0.35: half the step and twice the blocks, which fill the CUs more evenly,
-// for twice the K/V loads.  Whole attention call on coarse and fine tiles, over 1088 calls of 4 to 64 heads: 128-255 tiles 1.14 times as
-// fast (d = 64) and 1.11 (d = 128), 256-383 tiles 1.12 and 1.06 (0.87 to 1.28), 384-511 tiles 1.03 and 0.95, more tiles
-// 0.83-0.99.  [1377 rows, 32/4 heads, d = 64, S = 1531]: dQ 36 -> 30 us (a third stage of the K/V ring: 32).
-// Several sequences need more room (993 calls at d = 128, of one to forty sequences: fine tiles where the rows alone say
-// so 0.72 to 1.39 times as fast as coarse ones, with these lines 1.061 in the mean, the worst 0.955, at 4 heads in key ranges;
-// 351 calls at d = 64: 0.77 to 1.32, 1.066, 0.962):
+// a barrier: half the step and twice the blocks, which fill the CUs more evenly, for twice the K/V loads.  Whole attention call, over 1500 calls
+// of 4 to 64 heads at either d: with 128-255 tiles fine ones are 1.14 times as fast as coarse ones (d = 64) and 1.08 (d = 128), 256-383 tiles 1.12
+// and 1.05 (0.75 to 1.36), 384-511 tiles 1.08 and 1.02 (0.83 to 1.27), 512-767 tiles 1.02 and 0.97, more 0.97 and 0.92.  [1377 rows, 32/4 heads,
+// d = 64, S = 1531]: 68.3 us coarse, 60.6 fine.  All these calls by these lines: 1.076 (d = 64) and 1.044 times as fast as on coarse tiles alone; the
+// better tile in every call would be 1.009 and 1.013 times as fast again, most where one long sequence makes 260 to 500 tiles ([1545 of
+// 8085, 32/8 of 128] 273 coarse, as taken, and 214 fine).
+// Several sequences need more room (where the rows alone say so, fine tiles are 0.75 to 1.39 times as fast as coarse ones at d = 128, 1.058 in
+// the mean, and 0.84 to 1.45 at d = 64, 1.086; where these lines do, 0.957 at worst and 1.089 in the mean, 0.952 and 1.094 at d = 64):
 //   * up to twelve key tiles every sequence but the first counts as 48 rows more: it ends in a part of a tile, and blocks that do not
-//     fit beside the others do not pay ([1200 rows in eight sequences, S = 300, 24/8 heads of 128] 60.8 and 55.2 us, [450 in three,
-//     S = 300, 64/8] 58.6 and 55.7, d = 64 [768 in eight, S = 320, 64/8] 1.13 times as long; [1200 in four, S = 600, 24/8 of 128] 50.7 and 55.4; longer
-//     chains even out: [4095 in three, S = 5460, 8/8] 186 and 237);
+//     fit beside the others do not pay (fine and coarse: [1200 rows in eight sequences, S = 300, 24/8 heads of 128] 56.4 and 52.6 us, [450 in three,
+//     S = 300, 64/8] 57.3 and 53.9, d = 64 [768 in eight, S = 320, 64/8] 47.8 and 41.5; [1200 in four, S = 600, 24/8 of 128] 49.1 and 52.5; longer
+//     chains even out: [4095 in three, S = 5460, 8/8] 137 and 175);
 //   * up to four key tiles further blocks on a CU gain nothing: half the rows, a further sequence as 32 ([768 in four, S = 192,
-//     32/32 of 128] 31.1 and 28.8; [400 in four, S = 200, 32/32] 24.4 and 26.5), and all of up to 128 rows a sequence where their blocks
-//     take a quarter of the slots at most ([512 in four, S = 256, 32/32] 26.5 and 28.9; eight, 32/8: 1.04 times as long);
+//     32/32 of 128] 29.7 and 27.2; [400 in four, S = 200, 32/32] 22.1 and 24.7), and all of up to 128 rows a sequence where their blocks
+//     take a quarter of the slots at most ([512 in four, S = 256, 32/32] 24.6 and 27.3; eight, 32/8: 32.9 and 32.4);
 //   * up to two key tiles (one at d = 64) with no second tile of queries per sequence are a single short step each ([64 rows, S = 64,
-//     24/8 of 128] 21.7 and 20.6, S = 128 22.6 and 22.1, d = 64 [64 rows, S = 64, 8/8] 12.8 and 12.4; [90 rows, S = 90, 24/8 of 128] 24.5 and 25.4).
+//     24/8 of 128] 20.6 and 19.5, S = 128 21.5 and 20.9, d = 64 [64 rows, S = 64, 8/8] 11.9 and 11.6; [90 rows, S = 90, 24/8 of 128] 23.7 and 24.7).
 // Where no sequence has a second 128-query tile, in the mean, the coarse blocks of B * Hq tiles all run from the start on two or
-// three slots per CU, and fine ones pay while they leave some free (439 calls of up to 40 such sequences, S from 300 to 2000):
-//   * 65 to 128 rows each make two blocks of every one: up to 7/8 of the slots at d = 128 (448 blocks 0.93 to 1.00 of the coarse time, 480
-//     0.97 to 1.06, 512 0.97 to 1.16, 768 1.22 to 1.35), all at d = 64 (768 0.93 to 1.00, 800 1.00 to 1.16, 1024 1.15 to 1.27);
-//   * 33 to 64 rows each as many blocks of half the work: up to 13/16 of them (d = 128: 400 and 416 blocks 0.95 to 1.03, 448 0.98 to 1.04,
-//     512 1.00 to 1.07; d = 64: 512 0.89 to 0.98, 640 1.00 to 1.06, 768 0.99 to 1.06) and again where coarse ones need a second
-//     round (0.85 to 0.98); up to 32 rows half of a block's waves have nothing to do (0.95 to 1.03 with 448 to 512 blocks).
+// three slots per CU, and fine ones pay while they leave some free (1340 calls of up to 40 such sequences, S from 300 to 2000; fine time
+// over coarse, the better one in every call would be 1.007 times as fast as these lines):
+//   * 65 to 128 rows each make two blocks of every one: up to 7/8 of the slots at d = 128 (up to 447 blocks 0.76 to 1.12, 0.93 in the mean, 448-479
+//     1.01, 512-767 1.11, more 1.21), all at d = 64 (641-767 blocks 0.91, 768-799 0.96, 800-1023 1.11, more 1.15);
+//   * 33 to 64 rows each as many blocks of half the work: up to 13/16 of them (d = 128: up to 415 blocks 0.79 to 1.02, 416-447 0.99, 448-511 1.01,
+//     more 1.01; d = 64: up to 511 0.70 to 0.95, 512-624 0.99, 640-767 1.02) and again where coarse ones need a second
+//     round (d = 64: 0.98; 0.91 to 1.05); up to 32 rows half of a block's waves have nothing to do (0.97 with 416 to 511 blocks at d = 128, 0.96 to 0.99
+//     with 512 to 767 at d = 64).
 static void attn_dq_fine_rows(const cf_layer_desc& L, AttnParams& p) {
     const int n_cu = compute_units(), tiles = L.d == 64 ? n_cu * 3 / 2 : n_cu;
     const int64_t more = L.B - 1, blocks = (int64_t)L.B * L.Hq, slots = n_cu * (L.d == 64 ? 3 : 2);
@@ -151,14 +155,13 @@ __host__ __device__ inline bool attn_dq_fine(const AttnParams& p, int n_live) {
 }
 
 // Live rows up to which the dK/dV blocks at d = 64 take tiles of 64 keys: up to one and a quarter 128-key tiles per
-// CU.  Whole attention call, coarse (the better of the two kernels) and fine, over 541 calls of 4 to 64 heads:
-// up to 320 tiles 1.03 to 1.10 times as fast, 320-512 tiles 0.97 to 1.02, more 0.90-0.98.  Up to 512 kept rows in a sequence, in the
+// CU.  Whole attention call on coarse tiles (the better of the two kernels) over fine ones, 1500 calls of 4 to 64 heads: one sequence up to 320 tiles
+// 1.08 in the mean (0.97 to 1.21), 320-511 tiles 1.02, more 0.96.  Up to 512 kept rows in a sequence, in the
 // mean, each counts as 128 more: it ends in a part of a tile, of which there are twice as many, and short chains make short blocks, whose fixed
-// cost counts ([447 rows in three sequences, S = 298, 64/8 heads] 35.8 us fine and 32.8 coarse, [1120 in sixteen, S = 1500, 32/4] 1.23 times as
-// long; [5120 in two, S = 5120, 8/8] 99 and 114; layer call, [1216 of 1280, 32/4] 149 and 156).  Over 656 calls of one to sixteen
-// sequences fine tiles are 1.004 times as fast by the rows alone, 0.81 at worst; with this 1.023, 0.97; left out are gains of up to 5 %.
-// (Each as 112: 0.93 at worst; up to 320 rows: 0.90; up to 704: gains of 7 % left out, [1088 in two, S = 1088, 32/4].  Of the rows of a
-// single tile up to 32 gain 2 to 3 % by fine ones, 33 to 64 lose up to 1.)
+// cost counts (fine and coarse: [447 rows in three sequences, S = 298, 64/8 heads] 32.6 and 31.6 us, [1120 in sixteen, S = 1500, 32/4] 90.6 and
+// 74.3; [5120 in two, S = 5120, 8/8] 91.9 and 99.8, [1216 of 1280, 32/4] 49.3 and 53.3).  Where the rows alone say so fine tiles are 1.055 times as fast,
+// 0.85 at worst; with this 1.064, 0.96; what it leaves out is slower by 4 % in the mean.  (Each as 112, or up to 320 or 704 rows, changes nothing in the
+// mean.  Of the rows of a single tile up to 32 gain 1 % by fine ones, 33 to 64 lose 1 and 65 to 128 gain 5.)
 static void attn_dkv_fine_rows(const cf_layer_desc& L, AttnParams& p) {
     const int64_t rows = L.d == 64 ? compute_units() * 5 / 4 / L.Hq * 128 : 0;
     const int64_t less = std::max<int64_t>(rows - (int64_t)128 * L.B, 0), few = std::min<int64_t>((int64_t)512 * L.B, rows);
@@ -172,7 +175,8 @@ __host__ __device__ inline bool attn_dkv_fine(const AttnParams& p, int n_live) {
 
 // Key ranges per query tile of the dQ kernel.  Where a batch of few heads (a tensor-parallel share) has few query tiles, each
 // of them is a serial chain on a CU of its own: several blocks per tile, one per range of keys, shorten it, at the price of
-// fp32 partials and their sum: [2662 of 7479 rows, 4/1 heads, d = 128] 184 -> 75 us on 84 tiles.
+// fp32 partials and their sum: [2662 of 7479 rows, 4/1 heads, d = 128], 84 tiles, 184 -> 128 us for the whole attention call (coarse ones
+// 247 -> 143).
 // The most ranges that a batch shape may take, which grid and workspace are sized for: at least 128 keys in a range (192 on
 // coarse tiles), about four blocks per CU; with more than one tile per CU at least 1536 keys; none above two.
 static int attn_dq_split(const cf_layer_desc& L, bool fine = true) {
@@ -185,13 +189,13 @@ static int attn_dq_split(const cf_layer_desc& L, bool fine = true) {
 }
 
 // The ranges that a call takes of them.  What the partials cost goes with the live rows: 8 bytes per element and range,
-// written and read at about 3.5 TB/s, against the chain of S keys, 6.6 ns * d per 64 of them on fine tiles, 9.4 on coarse ones.  (With the
-// fine tiles' 6.6 for both, coarse calls were split too little: [4200 rows, 12/4 heads, d = 64] 171 us whole and 154 in two ranges,
-// [3481 of 4096, 16/16] 148 and 139.)  Without KV groups the split
+// written and read at about 3.5 TB/s, against the chain of S keys, 6.6 ns * d per 64 of them on fine tiles, 9.4 on coarse ones (fitted to chains of
+// 32x32x16 MFMAs; with these, over 1155 calls of up to 512 tiles, the best ranges in every call would be 1.011 (d = 128) and 1.005 times as
+// fast as those taken; whole tiles take 1.04 times as long).  (With the fine tiles' 6.6 for both, coarse calls would be split too little: [4200 rows, 12/4 heads, d = 64] 157 us
+// whole and 142 in two ranges, [3481 of 4096, 16/16] 132 and 124.)  Without KV groups the split
 // also costs a launch that would not be there otherwise, about 1 us; with them that launch is there and gains 1 us by a dQ kernel
 // that ends sooner.  A gain below 1/64 of the chain is none.  (Decided from the batch shape alone, calls that keep
-// most of their tokens were split as far as sparse ones: 32/32 heads, d = 128, S = 1024, all kept, four ranges 88 us, none 69.
-// Over the 1088 calls above, fine tiles with these ranges against coarse ones with the ranges fitted to them: 1.09 times as fast.)
+// most of their tokens would be split as far as sparse ones: 32/32 heads, d = 128, S = 1024, all kept, four ranges 102 us, none 61.)
 // In units of 1/16 ns per column: k > 1 ranges gain A(k) - k * part, A(k) = chain - chain/k - launch, part = what
 // one range's partials cost; k = 1 counts as a gain of chain / 64.  The k of the largest gain, the smaller one of
 // equals, is k or more exactly if some j >= k gains more than every i < k, which is a limit on part and so on the rows.  These
@@ -660,7 +664,7 @@ template <int D, bool ROPE>
 __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     constexpr int KS = D / 32, NT = D / 16;
     constexpr int TILE = 64 * D * 2;
-    constexpr int STAGE = 2 * TILE + 512;       // Q tile, dO tile, lse2[64], D[64]
+    constexpr int STAGE = 2 * TILE + 512;       // Q tile, dO tile, lse2[64], -D[64]
     extern __shared__ __align__(16) unsigned char smem[];
 
     // the wave number is the same in all lanes: saying so keeps everything derived from it in scalar registers
@@ -776,7 +780,7 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
     // fragments), B(n) = P and dS from them (vector ALU: exp2, mask, products, packing), C(n) = dV and
     // dK (4*NT MFMAs).  A wave runs alone on its SIMD, so nothing overlaps unless the instruction
     // stream interleaves it: ITERATION t issues A(t+1), B(t) and C(t-1) together, one softmax value
-    // (two at d = 64) and the LDS reads of a later slot between two groups of four MFMAs, so that in the steady
+    // (two at d = 64) and the LDS reads of a later slot spread over the four MFMAs of a slot, a quarter ahead of each, so that in the steady
     // state the matrix core runs back to back while the exponentials of the half before and the
     // fragment reads of the slots ahead proceed under it.  Fragment reads go through a ring of four
     // register pairs and are issued three slots ahead of their MFMAs, across iteration boundaries
@@ -1048,7 +1052,7 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
 // d = 64 accumulators, K/V fragments and scores of a wave take half the registers, so two waves fit a SIMD and
 // overlap each other's matrix, vector and LDS phases; a plain order of the phases is then better than the software pipeline
 // that a lone wave needs, as long as there are two blocks for every CU and more to follow: whole attention call at d = 64, this
-// kernel and the pipelined one, [8192 rows, 32/32 heads, S = 2048] 274 and 322 us, [4096, 64/64, S = 1024] 177 and 212.  Fragment reads
+// kernel and the pipelined one, [8192 rows, 32/32 heads, S = 2048] 243 and 281 us, [4096, 64/64, S = 1024] 161 and 193.  Fragment reads
 // run one group of four MFMAs ahead.  The accumulation order of every element is that of the pipelined kernel.
 // FINE: 64 keys per block; the two waves of a group of 32 keys take the first and the second 32 queries of every step, and their sums
 // meet in LDS at the end: half the step and twice the blocks, as in the dQ kernel (attn_dkv_fine_rows says where).
@@ -1056,7 +1060,7 @@ template <bool ROPE, bool FINE>
 __device__ __forceinline__ void attn_dkv64_block(const AttnParams& p, const int n_live, unsigned char* smem) {
     constexpr int D = 64, KS = D / 32, NT = D / 16, KT = FINE ? 64 : 128;
     constexpr int TILE = 64 * D * 2;
-    constexpr int STAGE = 2 * TILE + 512;       // Q tile, dO tile, lse2[64], D[64]
+    constexpr int STAGE = 2 * TILE + 512;       // Q tile, dO tile, lse2[64], -D[64]
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave = FINE ? wv & 1 : wv, qh = FINE ? wv >> 1 : 0;       // group of 32 keys; half of the steps
     const int slot = lane & 15, qd = lane >> 4;
@@ -1426,16 +1430,17 @@ static hipError_t launch_t(AttnParams& p, int dq_cap, const bf16_t* o_full, bf16
     const int tiles = ceil_div(max_per_seq, 128), n_cu = compute_units();
     // dK/dV kernel at d = 64.  Without a third block per CU to follow, the launch lasts as long as its longest chains, and a
     // block that shares its CU from the start walks through its own more slowly than the pipelined kernel does alone: whole call,
-    // two per CU and pipelined, [8192 rows, 8/8 heads, S = 8192: 512 blocks] 317 and 298 us, [3072, 16/16: 384] 117 and 108,
-    // [2048, 4/4: 64] 62.6 and 58.7; just above the line [4593 rows, 16/16, S = 1531: 576] 90 and 101 us.  Chains of less than
-    // 12 tiles are too short for that to make up for two full rounds ([4096, 16/16, S = 1024: 512] 55 and 58 us).
-    // On a single tile the two take the same time, and the plain one less for a few rows
-    // (13 rows, 16/16: 6.2 and 6.5 us).
+    // two per CU and pipelined, both on coarse tiles, [8192 rows, 8/8 heads, S = 8192: 512 blocks] 283 and 266 us, [3072, 16/16: 384] 100 and 91,
+    // [2048, 4/4: 64] 57.9 and 54.4; just above the line [4593 rows, 16/16, S = 1531: 576] 76 and 83 us.  Chains of less than
+    // 12 tiles are too short for that to make up for two full rounds ([4096, 16/16, S = 1024: 512] 52.2 and 52.7 us).  Over 534 calls on coarse tiles the
+    // pipelined kernel is 1.04 times as fast on its side of the line (0.95 at worst), the plain one 1.08 on the other (0.95).
+    // On a single tile the two take the same time (13 rows, 16/16: 10.0 and 9.9 us).
     // Only the plain kernel has the fine tiles that few live rows take (attn_dkv_fine_rows).  Both sum in the same order on coarse tiles and walk
     // through one head per block where chains decide, so the choice does not show.  With a device-side count either may be
-    // needed: chains of 20 tiles and more launch both, and one of them leaves at once.  Layer calls, the plain kernel alone and both: [7296 of 7680
-    // rows, 8/8 heads] 447 and 431 us, [4500 of 4736, 12/4] 335 and 312, on fine tiles [3840 of 7680] 259 and 260, [1600 of 3200, 16/16] 166 and
-    // 169.  With fewer tiles the pipelined kernel gains no more than a launch costs ([1946 of 2048, 32/4] plain 213.4, pipelined 212.6).
+    // needed: chains of 20 tiles and more launch both, and one of them leaves at once.  Layer calls (H = 64 * heads, F = 2H), the plain kernel alone and
+    // both: [7296 of 7680 rows, 8/8 heads] 447 and 424 us, [4500 of 4736, 12/4] 367 and 357, on fine tiles [3840 of 7680] 254 and 256, [1600 of 3200,
+    // 16/16] 207 and 210.  With fewer tiles the pipelined kernel gains no more than a launch costs ([1946 of 2048, 32/4] plain 213.4, pipelined 212.6,
+    // with 32x32x16 MFMAs).
     const bool chains = (int64_t)p.Hq * p.B * tiles * 4 <= (int64_t)n_cu * (tiles < 12 ? 7 : 8);
     bool paired = D == 64;
     p.dkv_both = 0;

@@ -484,8 +484,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, const int K0x, con
                 // per K-step, so two MFMAs on the same registers are never back to back.
                 // Both A fragments per B fragment, back and forth: an MFMA shares an operand with the one before it and the other
                 // with the one after, which costs less power than eight B fragments in a row for one A fragment (a register-resident
-                // loop 2060 and 2107 TFLOP/s; X^T*dY and dY*W^T of [4096, 4096 -> 14336] 654 and 646 us, the layer step with
-                // these sizes 3180 and 3157).  The small tile, which waits for its operands, runs the other way: there A fragment 1 has
+                // loop 2060 and 2107 TFLOP/s; X^T*dY and dY*W^T of [4096, 4096 -> 14336] 694 and 688 us, the layer step with
+                // these sizes 3265 and 3230).  The small tile, which waits for its operands, runs the other way: there A fragment 1 has
                 // half a sub-step longer to arrive ([841, 4096], K = 3584 out of HBM: 40 us back and forth, 36).
                 constexpr int j = BACK ? q >> 1 : q % FN, h = BACK ? (q & 1) ^ (j & 1) : q / FN, i = 2 * a + h;
                 constexpr int dsel = load_in_gap(q, e_hi - e_lo, NQ);       // the wave-load that goes with this MFMA
@@ -1272,7 +1272,9 @@ hipError_t launch_gemm_tn(int dtype, const GemmTnProb* probs, int np, int K, flo
     if (gains != nullptr && tiles > compute_units()) {
         g.gain = *gains;
         more = gain_grad_units(gains->H);
-    } else if (gains != nullptr) {      // up to one round: a launch of their own, as the route tests count them
+    } else if (gains != nullptr) {
+        // Up to one round a launch of their own, as the number of launches of such a call has always been, which test_gpu_routes.py
+        // holds to.  Not for speed: beside the products 94 layer calls of 7 to 228 tiles are 1.03 times as fast (1.01 to 1.07, 1 to 7 us).
         const hipError_t eg = launch_gain_grads(dtype, *gains, c_f32, st);
         if (eg != hipSuccess) return eg;
     }
