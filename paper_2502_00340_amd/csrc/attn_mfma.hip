@@ -362,60 +362,82 @@ __device__ __forceinline__ void attn_dq_block(const AttnParams& p, const uint64_
     // This lane's two queries, 16 rows apart: their fragments and row terms.  D = rowsum(dO*O) is formed here, from the dO fragments that
     // the kernel holds anyway, unless a pass before had to read O for its compact copy (a pass of its own over dO and O
     // costs 16 us where the dQ kernel gets 6 us slower: [4096 rows, 32 heads, d = 128], 206 us).
-    int pos[2];
+    // The loads of both go out before anything waits for one; a query that does not exist takes the rows of the tile's last one (masked below,
+    // never stored), unless none of its 16 does.  One after the other, the blocks of tiles with at most 16 rows, which had nothing to load for the
+    // second, started earlier than those of the sequence's other tiles and took K and V through the XCD's L2 ahead of them: [7 x 129 of
+    // 1085 rows, 32/4 heads, d = 128] call 94.3 us, so 86.2.  2100 calls: 1.006 (d = 128) and 1.010
+    // times as fast, 0.98 at worst.
+    int jq[2], pos[2];
+    bool qvalid[2], some[2];
     float lse2[2], Dq[2];
     bf16x8_t qf[2][KS], dof[2][KS];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-        const int r = wave * 32 + t * 16 + slot, jq = j0 + r;
-        const bool qvalid = r < rows_in_tile;
-        pos[t] = qvalid ? (p.idx ? p.idx[jq] : jq) - b * p.S : -1;
-        lse2[t] = Dq[t] = 0.f;
-        const int64_t off_q = (int64_t)jq * Nq + h * D + qd * 8;
+        const int r = wave * 32 + t * 16 + slot;
+        qvalid[t] = r < rows_in_tile;
+        jq[t] = j0 + min(r, rows_in_tile - 1);
+        pos[t] = (p.idx ? p.idx[jq[t]] : jq[t]) - b * p.S;
+        const int64_t off_q = (int64_t)jq[t] * Nq + h * D + qd * 8;
+        some[t] = wave * 32 + t * 16 < rows_in_tile;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            uint4 a = make_uint4(0, 0, 0, 0), c = make_uint4(0, 0, 0, 0);
-            if (qvalid) {
-                a = *reinterpret_cast<const uint4*>(p.q_kept + off_q + ks * 32);
-                c = *reinterpret_cast<const uint4*>(p.do_kept + off_q + ks * 32);
+        for (int ks = 0; ks < KS; ++ks) qf[t][ks] = dof[t][ks] = __builtin_bit_cast(bf16x8_t, make_uint4(0, 0, 0, 0));
+        if (some[t]) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                qf[t][ks] = *reinterpret_cast<const bf16x8_t*>(p.q_kept + off_q + ks * 32);
+                dof[t][ks] = *reinterpret_cast<const bf16x8_t*>(p.do_kept + off_q + ks * 32);
             }
-            qf[t][ks] = __builtin_bit_cast(bf16x8_t, a);
-            dof[t][ks] = __builtin_bit_cast(bf16x8_t, c);
-        }
-        if (p.o_kept != nullptr) {
-            // summed in the order of attn_stats_kernel, so that both give the same bits: 8 columns in sequence, then a tree
-            if (qvalid) {
-                float part[KS];
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    part[ks] = 0.f;
-                    const uint4 o = *reinterpret_cast<const uint4*>(p.o_kept + off_q + ks * 32);
-                    const uint4 c = __builtin_bit_cast(uint4, dof[t][ks]);
-                    const unsigned ow[4] = {o.x, o.y, o.z, o.w}, cw[4] = {c.x, c.y, c.z, c.w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        part[ks] += __uint_as_float(cw[e] << 16) * __uint_as_float(ow[e] << 16);
-                        part[ks] += __uint_as_float(cw[e] & 0xFFFF0000u) * __uint_as_float(ow[e] & 0xFFFF0000u);
-                    }
-                }
-#pragma unroll
-                for (int o = KS / 2; o > 0; o >>= 1)
-#pragma unroll
-                    for (int ks = 0; ks < o; ++ks) part[ks] += part[ks + o];
-                Dq[t] = part[0];
-                lse2[t] = p.lse_full[((int64_t)b * p.Hq + h) * p.S + pos[t]] * LOG2E;
-            }
-            Dq[t] += __shfl_xor(Dq[t], 32, 64);     // the other quarters of the row's columns
-            Dq[t] += __shfl_xor(Dq[t], 16, 64);
-            if (qvalid && qd == 0 && blockIdx.z == 0 && kw == 0) {
-                p.stat[(int64_t)h * p.n_kept + jq] = lse2[t];
-                p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq] = -Dq[t];
-            }
-        } else if (qvalid) {
-            lse2[t] = p.stat[(int64_t)h * p.n_kept + jq];
-            Dq[t] = -p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq];
         }
     }
+    if (p.o_kept != nullptr) {
+        // summed in the order of attn_stats_kernel, so that both give the same bits: 8 columns in sequence, then a tree
+        uint4 of[2][KS];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) of[t][ks] = make_uint4(0, 0, 0, 0);
+            if (some[t])
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+                    of[t][ks] = *reinterpret_cast<const uint4*>(p.o_kept + (int64_t)jq[t] * Nq + h * D + qd * 8 + ks * 32);
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) lse2[t] = p.lse_full[((int64_t)b * p.Hq + h) * p.S + pos[t]] * LOG2E;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            float part[KS];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                part[ks] = 0.f;
+                const uint4 o = of[t][ks], c = __builtin_bit_cast(uint4, dof[t][ks]);
+                const unsigned ow[4] = {o.x, o.y, o.z, o.w}, cw[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    part[ks] += __uint_as_float(cw[e] << 16) * __uint_as_float(ow[e] << 16);
+                    part[ks] += __uint_as_float(cw[e] & 0xFFFF0000u) * __uint_as_float(ow[e] & 0xFFFF0000u);
+                }
+            }
+#pragma unroll
+            for (int o = KS / 2; o > 0; o >>= 1)
+#pragma unroll
+                for (int ks = 0; ks < o; ++ks) part[ks] += part[ks + o];
+            Dq[t] = part[0];
+            Dq[t] += __shfl_xor(Dq[t], 32, 64);     // the other quarters of the row's columns
+            Dq[t] += __shfl_xor(Dq[t], 16, 64);
+            if (qvalid[t] && qd == 0 && blockIdx.z == 0 && kw == 0) {
+                p.stat[(int64_t)h * p.n_kept + jq[t]] = lse2[t];
+                p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq[t]] = -Dq[t];
+            }
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            lse2[t] = p.stat[(int64_t)h * p.n_kept + jq[t]];
+            Dq[t] = -p.stat[(int64_t)(p.Hq + h) * p.n_kept + jq[t]];
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) pos[t] = qvalid[t] ? pos[t] : -1;
     const int jlast = j0 + rows_in_tile - 1;
     const int maxpos = (p.idx ? p.idx[jlast] : jlast) - b * p.S;
     // the block's range of key tiles: all of them, or its share (possibly empty) of a split tile
