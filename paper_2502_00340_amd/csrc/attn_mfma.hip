@@ -763,13 +763,6 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
         dma4(sq + 2 * TILE + 256, rsD, off);
     };
     constexpr int LPS = 2 * NLD + 2;                // loads per wave and step
-    // The first rows of the first head are on their way before the keys, whose addresses take two more loads, are asked for (with the
-    // mask as below: [3 x 280 of 701 rows, 4/1 heads] call 39.7 us, so 39.0; [950 of 1900, 32/8] 84.0 and 83.4).
-    open_head(h0);
-    issue_q(0, 0);
-    issue_q(1, 1);
-    issue_q(2, 2);
-
     // this lane's two keys, 16 apart
     int jk[2];
     int tok[2];
@@ -794,7 +787,15 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
             vf[u][ks] = __builtin_bit_cast(bf16x8_t, c);
         }
     }
-    // compact row less 4 * qd from which on a query sees the key; none sees one that does not exist
+    // The keys' loads lead, their addresses take two more; behind the first rows' loads they come no earlier (2100 calls 0.998 times as fast, [3 x
+    // 394 of 878 rows, 32/8 heads] 72.7 us, so 71.7).
+    open_head(h0);
+    issue_q(0, 0);
+    issue_q(1, 1);
+    issue_q(2, 2);
+
+    // compact row less 4 * qd from which on a query sees the key; none sees one that does not exist.  The mask is one compare with a constant per
+    // value ([950 of 1900 rows, 32/8 heads] 82.0 us with the row formed for each, so 81.6; 900 calls of up to 700 positions 1.004 times as fast)
     const int first_row[2] = {(kvalid[0] ? jk[0] : INT32_MAX) - 4 * qd, (kvalid[1] ? jk[1] : INT32_MAX) - 4 * qd};
 
     // ---- the pipeline.  The query rows go by in HALVES of 32 (two per 64-row step / LDS stage).  A
