@@ -1045,7 +1045,7 @@ __global__ __launch_bounds__(256, 1) void attn_dkv_kernel(AttnParams p) {
                 constexpr bool rope = decltype(ROPE_)::value != 0;
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    const int64_t tab = rope ? (int64_t)((p.idx ? p.idx[jk[u]] : jk[u]) - b * p.S) * (D / 2) + 4 * qd : 0;
+                    const int64_t tab = rope ? (int64_t)(tok[u] - b * p.S) * (D / 2) + 4 * qd : 0;
                     round_row<D, rope>(acc[u], scale, p.rope_cos + tab, p.rope_sin + tab, [&](int nt, uint2 y) __attribute__((always_inline)) {
                         *reinterpret_cast<uint2*>(at(u * 16 + slot, nt * 2 + (qd >> 1)) + (qd & 1) * 8) = y;
                     });

@@ -88,3 +88,15 @@ def test_registers_of_mfmas_that_the_compiler_does_not_wait_for(kernels):
             assert c <= d or _mfmas_before(code, at, i, overwrites) >= 1, (name, hex(off), op, ops, "C overwritten")
             assert _mfmas_before(code, at, i, touches) >= 2, (name, hex(off), op, ops, "result touched")
         assert found >= 64, (name, found)
+
+
+def test_loops_around_mfmas_are_uniform(kernels):
+    """A loop that the compiler takes for a divergent one counts in vector registers, beside every MFMA, and masks lanes."""
+    for name, code in kernels.items():
+        at = {c[0]: i for i, c in enumerate(code)}
+        first = next(i for i, c in enumerate(code) if c[1].startswith("v_mfma"))
+        loops = [(at[target], i) for i, (_, _, _, target) in enumerate(code) if target is not None and at[target] < i]
+        loops = [(a, b) for a, b in loops if first < a and sum(c[1].startswith("v_mfma") for c in code[a:b]) >= 32]
+        assert len(loops) >= 2, name            # the steps of a head with and without the mask
+        for a, b in loops:
+            assert not code[b][1].startswith("s_cbranch_exec"), (name, hex(code[a][0]), hex(code[b][0]), code[b][1])
